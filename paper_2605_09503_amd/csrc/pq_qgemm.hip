@@ -67,25 +67,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-  // ---- tile assignment: consecutive workgroup ids land on different XCDs (8 of them, each
-  // with its own L2); give every XCD a contiguous range of tiles, and walk tiles in bands of
-  // 8 along M so that concurrently running workgroups share A and W strips.
-  const int n_tiles = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  {
-    // XCD x runs the workgroups with id % 8 == x: (n_tiles - x + 7) / 8 of them, which get the tiles
-    // from x * (n_tiles / 8) + min(x, n_tiles % 8) on
-    const int x = pid & 7, q8 = n_tiles >> 3, r8 = n_tiles & 7;
-    pid = x * q8 + min(x, r8) + (pid >> 3);
-  }
-  constexpr int BAND = 8;
-  const int band_sz = BAND * tiles_n;
-  const int band = pid / band_sz;
-  const int band_m0 = band * BAND;
-  const int band_h = min(BAND, tiles_m - band_m0);
-  const int in_band = pid - band * band_sz;
-  const int tile_m = band_m0 + in_band % band_h;
-  const int tile_n = in_band / band_h;
+  int tile_m, tile_n;
+  assign_tile(tiles_m, tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   const int tid = threadIdx.x;
@@ -277,88 +260,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
     }
   }
 
-  // ---- epilogue: lane holds, per MFMA tile, column m = lane % 32 and rows
-  // n = 8 * (r / 4) + 4 * (lane / 32) + r % 4.  The bf16 tile is staged through LDS (the
-  // operand stages are free after the last barrier) so that global stores are 16 bytes per
-  // lane and contiguous along n; the fp32 variant (a checking aid) stores directly.
-  constexpr int C_ROW_BYTES = BN * 2 + 16;
-  static_assert(BM * C_ROW_BYTES <= 2 * STAGE_BYTES, "output tile fits in the operand stages");
-  // The column factors (and the optional bias of the linear layer, y = x W^T + b) do not depend on
-  // the row block: loaded once (16 per MFMA tile column).
-  const uint16_t* __restrict__ bias = W.bias;               // uniform
-  float wm[TN][16], wb[TN][16];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = n0 + wave_n * WTN + i * 32 + q * 8 + frag_half * 4 + e;
-        wm[i][q * 4 + e] = w_mul[(int64_t)(min(n, N - 1) * w_mul_stride)];
-        wb[i][q * 4 + e] = bias ? bf16_to_f32(bias[min(n, N - 1)]) : 0.0f;
-      }
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    if (RAGGED_M && j >= tm_cnt) break;         // wave-uniform
-    const int ml = wave_m * WTM + j * 32 + frag_row;
-    const int m = m0 + ml;
-    const float am = a_mul[(int64_t)(min(m, M - 1) * a_mul_stride)];
-#pragma unroll
-    for (int i = 0; i < TN; ++i) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int nl = wave_n * WTN + i * 32 + q * 8 + frag_half * 4;
-        const int n = n0 + nl;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][q * 4 + e] * (am * wm[i][q * 4 + e]);
-        if (bias) {                     // without a bias the product is stored as it is (a -0 stays -0)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] += wb[i][q * 4 + e];
-        }
-        if constexpr (OUT_F32) {
-          if (m < M && n < N) {
-            float* yo = reinterpret_cast<float*>(y) + (int64_t)m * ldy + n;
-            if (n + 3 < N) {
-              *reinterpret_cast<float4*>(yo) = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-              for (int e = 0; e < 4 && n + e < N; ++e) yo[e] = v[e];
-            }
-          }
-        } else {
-          // round to nearest even, two values per instruction (v_cvt_pk_bf16_f32)
-          typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-          typedef float f32x2_t __attribute__((ext_vector_type(2)));
-          const bf16x2_t lo = __builtin_convertvector((f32x2_t){v[0], v[1]}, bf16x2_t);
-          const bf16x2_t hi = __builtin_convertvector((f32x2_t){v[2], v[3]}, bf16x2_t);
-          *reinterpret_cast<uint2*>(smem + ml * C_ROW_BYTES + nl * 2) =
-              make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-        }
-      }
-    }
-  }
-  if constexpr (!OUT_F32) {
-    __syncthreads();
-    constexpr int CHUNKS_PER_ROW = BN / 8;               // 16-byte chunks of 8 bf16
-    uint16_t* yb = reinterpret_cast<uint16_t*>(y);
-#pragma unroll 4
-    for (int c = tid; c < BM * CHUNKS_PER_ROW; c += T) {
-      const int row = c / CHUNKS_PER_ROW, cc = c % CHUNKS_PER_ROW;
-      const int m = m0 + row, n = n0 + cc * 8;
-      if (m >= M || n >= N) continue;
-      const uint4 v = *reinterpret_cast<const uint4*>(smem + row * C_ROW_BYTES + cc * 16);
-      uint16_t* yo = yb + (int64_t)m * ldy + n;
-      if (n + 7 < N) {
-        // the output is not read again by this kernel: a streaming store keeps it from displacing
-        // the operand strips in L2
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store((u32x4){v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(yo));
-      } else {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        for (int e = 0; e < 8 && n + e < N; ++e) yo[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-      }
-    }
-  }
+  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, 2 * STAGE_BYTES, OUT_F32>(
+      acc, smem, a_mul, a_mul_stride, w_mul, w_mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f, y, ldy);
 }
 
 // ------------------------------------------------------------------------ INT scale prepass
@@ -531,6 +434,9 @@ static int launch_views_fg(const OperandView& A, const OperandView& W, int M, in
 // the product kernel on two operand views (any mix of layouts)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
                        int64_t N, int64_t K, void* y, int64_t ldy, bool out_f32, hipStream_t st) {
+  const int tile = choose_tile((int)M, (int)N);
+  if ((fmt == PQ_FMT_INT4 || fmt == PQ_FMT_INT3) && (group == 64 || group == 128 || group == 256) && tile != 2)
+    return launch_qgemm_group(fmt, group, A, W, (int)M, (int)N, (int)K, y, ldy, out_f32, tile, st);
 #define PQ_ARGS A, W, (int)M, (int)N, (int)K, y, ldy, out_f32, st
   if (fmt == PQ_FMT_NVFP4) return launch_views_fg<kNvfp4, 16>(PQ_ARGS);
   if (fmt == PQ_FMT_INT4) {

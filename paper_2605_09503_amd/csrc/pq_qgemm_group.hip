@@ -1,0 +1,377 @@
+// Low-bit GEMM for the integer formats on the 8- and 4-bit matrix instructions (paper Eq. 8):
+//     Y[m, n] = sum_g (sa[m, g] sw[n, g]) I_g[m, n],   I_g[m, n] = sum_{k in g} a[m, k] w[n, k]
+//
+// The codes go to the matrix unit as they are and the scales stay outside:
+//   P = v_mfma_f32_32x32x64_f8f6f4 of 64 codes of k (no accumulator input): the exact integer I_g in fp32,
+//       |I_g| <= 64 * 49, times a power of two;
+//   S = v_mfma_f32_32x32x8_f16 with a single non-zero k: the outer product of the two scale columns, 8-bit
+//       times 8-bit significands (the fp16 scale units of the operand layout), exact in fp32;
+//   acc += P * S, one fused multiply-add per output and group on the vector unit.
+// The only roundings are those fused multiply-adds, one per 64 k (a product of fp16 operands that carry
+// their scale accumulates with a rounding per matrix instruction, four per 64 k), and the epilogue's.
+//
+// Code formats.  INT4: E4M3, whose subnormals and first binade are the integers 0..15 times 2^-9, so a byte
+// sign << 7 | |z| is z 2^-9 exactly (all sixteen nibbles, -8 included).  INT3: E2M1, where 0, .5, 1, 1.5, 2
+// are the codes 0..4, so a nibble sign << 3 | |z| is z / 2 exactly for |z| <= 4.
+//
+// What bounds it.  On this chip the matrix and the vector instructions of a SIMD's two waves hardly overlap
+// (measured: a 32-cycle matrix instruction hides four to five vector instructions, every further one costs 2.2 to
+// 2.8 cycles), so a 32 x 32 x 64 block costs about the sum of both:
+//   fp16 operands that carry their scale (pq_qgemm.hip)   128 matrix cycles + 16 vector instructions (the unpack)
+//   8-bit codes (here, INT4)                          64 + 32 matrix cycles + 31 (16 multiply-adds, 11 of unpack)
+//   4-bit codes (here, INT3)                          32 + 32 matrix cycles + 23 (16 multiply-adds, 4 of unpack)
+// and the 8- and 4-bit instructions draw less power: the chip holds 2.3 GHz here and 1.9 GHz there.  Forming S
+// on the vector unit instead would be 16 more instructions a block.  Measured, us and TFLOP/s (before: fp16):
+//   INT3 g64   4608 x 3072 x 3072     79 -> 53  (1.64 PFLOP/s)    8192 x 12288 x 3072   483 -> 322 (1.92)
+//   INT4 g64   4608 x 3072 x 3072     82 -> 75  (1.15)            8192 x 12288 x 3072   512 -> 427 (1.45)
+//   INT4 g64   4608 x 3072 x 12288   295 -> 239 (1.46)
+// Groups of 32 would need two half-empty matrix products and two scale products a block, 128 matrix cycles again,
+// and 32 multiply-adds: 510 us against 477 on INT3 8192 x 12288 x 3072, so they stay on the fp16 kernel, as do NVFP4's
+// groups of 16.  Issuing the next block's matrix instructions before this block's multiply-adds needs 16 to 32
+// more registers than a wave has: spilled, and slower (INT4 75 -> 95 us).
+//
+// Structure as in pq_qgemm.hip: one workgroup per output tile, every thread unpacks one 32-code slice of
+// each operand per 64-wide step, global loads run ahead in registers.  LDS holds four steps, so that the one
+// barrier of a step can sit in its middle: the first fragments of the next step are fetched before the current
+// one ends, and no wave starts a step waiting for LDS (with three stages and the barrier at the end of the step
+// 89 us instead of 78 on INT4 4608 x 3072 x 3072).
+#include "pq_qgemm_common.h"
+
+namespace pq {
+
+namespace {
+
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef int int8v __attribute__((ext_vector_type(8)));
+typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+
+// four two's complement nibbles, one per byte of n (top nibbles 0), m = their sign bits: bytes sign << 7 | |z|
+__device__ __forceinline__ uint32_t e4m3_bytes(uint32_t n, uint32_t m) {
+  const uint32_t f = __builtin_amdgcn_perm(0u, 0x00008F00u, m);      // 0x8F where negative
+  return (n ^ f) + m;                                                // 16 - n <= 8 under the sign: no carry
+}
+
+// eight nibbles z (two's complement, |z| <= 4) -> eight nibbles sign << 3 | |z|
+__device__ __forceinline__ uint32_t e2m1_nibbles(uint32_t d) {
+  const uint32_t s = d & 0x88888888u, m = s >> 3;
+  return (d ^ (s - m)) + m;
+}
+
+}  // namespace
+
+// FP4: E2M1 codes (INT3), else E4M3 (INT4).  Groups are a multiple of 64 (2^g_shift).
+template <bool FP4, int BM, int BN, int WGM, int WGN, bool OUT_F32>
+__global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView A, OperandView W, int M, int N,
+                                                                    int K, int g_shift, void* __restrict__ y,
+                                                                    int64_t ldy, int tiles_m, int tiles_n) {
+  constexpr int T = WGM * WGN * 64;
+  constexpr int WTM = (BM + WGM * 32 - 1) / (WGM * 32) * 32, WTN = BN / WGN;
+  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int TM_LAST = (BM - (WGM - 1) * WTM) / 32;
+  constexpr bool RAGGED_M = TM_LAST != TM;
+  constexpr int SL = BN * 2 / T;
+  static_assert(BN * 2 % T == 0 && (BM * 2 + T - 1) / T == SL, "whole slices per thread, as many for A as for W");
+  static_assert(BM % 32 == 0 && WTN % 32 == 0 && TM_LAST >= 1 && TM_LAST <= TM, "wave tile");
+  static_assert(!RAGGED_M || (WGM == 2 && WGN == 4), "the uneven split is laid out for 2 x 4 waves");
+  constexpr int A_ROWS = SL * (T / 2);
+  constexpr int RB = FP4 ? 32 : 64;                    // LDS bytes of a row: 64 codes
+  constexpr int NP = RB / 32;                          // 16-byte pieces of a 32-code slice
+  constexpr int A_CODES = 0, W_CODES = A_ROWS * RB, A_SC = W_CODES + BN * RB, W_SC = A_SC + A_ROWS * 2;
+  constexpr int STAGE_BYTES = W_SC + BN * 2, STAGES = 4;
+  constexpr int OUT_BYTES = OUT_F32 ? 0 : BM * (BN * 2 + 16);
+  constexpr int SMEM_BYTES = STAGES * STAGE_BYTES > OUT_BYTES ? STAGES * STAGE_BYTES : OUT_BYTES;
+  constexpr int FMT_SEL = FP4 ? 4 : 0;                 // operand format field of the matrix instruction
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+  int tile_m, tile_n;
+  assign_tile(tiles_m, tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int wave_m = RAGGED_M ? ((wave >> 2) ^ wave) & 1 : wave % WGM;
+  const int wave_n = RAGGED_M ? wave >> 1 : wave / WGM;
+  const int tm_cnt = RAGGED_M ? __builtin_amdgcn_readfirstlane(wave_m == WGM - 1 ? TM_LAST : TM) : TM;
+
+  // loader: this thread owns tile rows tid / 2 + q * (T / 2), k offset 32 * (tid & 1), of both operands
+  const int ld_row = tid >> 1, ld_half = tid & 1;
+  bool a_ok[SL], w_ok[SL];
+  // addresses: a uniform part (the tile, the step) and a 32-bit offset inside the tile
+  uint32_t a_coff[SL], w_coff[SL], a_soff[SL], w_soff[SL];
+#pragma unroll
+  for (int q = 0; q < SL; ++q) {
+    const int r = ld_row + q * (T / 2);
+    a_ok[q] = m0 + r < M && r < BM;
+    w_ok[q] = n0 + r < N;
+    const int a_row = min(r, M - 1 - m0), w_row = min(r, N - 1 - n0);
+    a_coff[q] = (uint32_t)a_row * (uint32_t)A.code_row;
+    w_coff[q] = (uint32_t)w_row * (uint32_t)W.code_row;
+    a_soff[q] = (uint32_t)a_row * (uint32_t)A.sc_row;
+    w_soff[q] = (uint32_t)w_row * (uint32_t)W.sc_row;
+  }
+  const uint8_t* a_codes = A.codes + (int64_t)m0 * A.code_row;
+  const uint8_t* w_codes = W.codes + (int64_t)n0 * W.code_row;
+  const uint8_t* a_scales = A.scales + (int64_t)m0 * A.sc_row;
+  const uint8_t* w_scales = W.scales + (int64_t)n0 * W.sc_row;
+  // Loads never leave the operand and never branch (a branch in the loop would split its schedule): a step
+  // past the last re-reads the last, the missing upper half of a last step of 32 k the lower one.  What such
+  // a slice holds does not matter: its scale is stored as zero.
+  const int ksteps = (K + kBK - 1) / kBK;
+  auto load_ops = [&](const uint8_t* codes, const uint32_t (&coff)[SL], int code_step, const uint8_t* scales,
+                      const uint32_t (&soff)[SL], int sc_step, int step, Slice (&r)[SL]) {
+    const int st = min(step, ksteps - 1);                             // uniform
+    const uint32_t half = st * kBK + ld_half * 32 < K ? ld_half : 0;
+    const uint8_t* c = codes + (int64_t)st * code_step;
+    const uint8_t* sc = scales + (int64_t)((st * kBK) >> g_shift) * sc_step;
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+      r[q].codes = *reinterpret_cast<const uint4*>(c + (coff[q] + half * 16u));
+      r[q].sc = *reinterpret_cast<const uint16_t*>(sc + soff[q]);
+    }
+  };
+  auto load_a = [&](int step, Slice (&r)[SL]) { load_ops(a_codes, a_coff, A.code_step, a_scales, a_soff, A.sc_step, step, r); };
+  auto load_w = [&](int step, Slice (&r)[SL]) { load_ops(w_codes, w_coff, W.code_step, w_scales, w_soff, W.sc_step, step, r); };
+
+  // Placement of a row's 16-byte pieces: rotated by the row so that the 16 rows that share a 256-byte line
+  // of banks in a fragment read use different banks.
+  auto piece_at = [&](int row, int piece) {
+    const int f = FP4 ? (row >> 3) & 1 : (row >> 2) & 3;
+    return row * RB + ((piece ^ f) << 4);
+  };
+  // piece 0 of this thread's slice q; piece 1 is 16 bytes beside it, on the side the rotation says (stages and
+  // tiles start at multiples of 32 bytes: an exclusive or)
+  int st_off[SL];
+#pragma unroll
+  for (int q = 0; q < SL; ++q) st_off[q] = piece_at(ld_row + q * (T / 2), ld_half * NP);
+  auto put_scale = [&](int sc, const Slice& s, bool ok, int q) {
+    *reinterpret_cast<uint16_t*>(smem + sc + (ld_row + q * (T / 2)) * 2) = (uint16_t)(ok ? s.sc : 0u);
+  };
+  // 16-byte piece c of slice q: unpacked and stored
+  auto put_piece = [&](const Slice& s, int codes, int q, int c) {
+    const uint32_t d[4] = {s.codes.x, s.codes.y, s.codes.z, s.codes.w};
+    if constexpr (FP4) {
+      *reinterpret_cast<uint4*>(smem + (codes + st_off[q])) =
+          make_uint4(e2m1_nibbles(d[0]), e2m1_nibbles(d[1]), e2m1_nibbles(d[2]), e2m1_nibbles(d[3]));
+    } else {
+      uint32_t o[4];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t v = c == 0 ? d[e] : d[2 + e];
+        o[2 * e] = e4m3_bytes(v & 0x0F0F0F0Fu, (v >> 3) & 0x01010101u);
+        o[2 * e + 1] = e4m3_bytes((v >> 4) & 0x0F0F0F0Fu, (v >> 7) & 0x01010101u);
+      }
+      *reinterpret_cast<uint4*>(smem + ((codes + st_off[q]) ^ (c << 4))) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+  };
+
+  // fragment addresses inside a stage: the row of a tile is lane % 32, its half of the 64 k lane / 32; tiles
+  // lie 32 rows apart, which leaves the placement of the pieces unchanged
+  const int frag_row = lane & 31, frag_half = lane >> 5;
+  const int x_base = A_CODES + piece_at(wave_m * WTM + frag_row, frag_half * NP);
+  const int w_base = W_CODES + piece_at(wave_n * WTN + frag_row, frag_half * NP);
+  const int xs_base = A_SC + (wave_m * WTM + frag_row) * 2;
+  const int ws_base = W_SC + (wave_n * WTN + frag_row) * 2;
+
+  struct Frag {
+    int4v v[NP];
+  };
+  auto read_frag = [&](int base, int stage, int tile) {
+    Frag f;
+#pragma unroll
+    for (int c = 0; c < NP; ++c)
+      f.v[c] = *reinterpret_cast<const int4v*>(smem + ((stage + base) ^ (c << 4)) + tile * 32 * RB);
+    return f;
+  };
+  auto read_scale = [&](int base, int stage, int tile) {
+    return (uint32_t)*reinterpret_cast<const uint16_t*>(smem + stage + base + tile * 64);
+  };
+  auto operand = [&](const Frag& f) {
+    if constexpr (FP4) return (int8v){f.v[0].x, f.v[0].y, f.v[0].z, f.v[0].w, 0, 0, 0, 0};
+    else return (int8v){f.v[0].x, f.v[0].y, f.v[0].z, f.v[0].w, f.v[NP - 1].x, f.v[NP - 1].y, f.v[NP - 1].z, f.v[NP - 1].w};
+  };
+  auto scale_operand = [&](uint32_t h) {
+    const uint2 u = make_uint2(h, 0u);
+    return __builtin_bit_cast(half4v, u);
+  };
+
+  float16_t acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  // Slices on their way from memory: two steps' worth with 4-bit codes; with 8-bit codes, whose fragments take
+  // twice the registers, one step's, reloaded as soon as it is unpacked.
+  constexpr int RS = FP4 ? 2 : 1;
+  Slice raw_a[2][SL], raw_w[2][SL];                    // [1] is dead after the prologue for RS = 1
+
+  // ---- prologue: stages 0 and 1 <- steps 0 and 1, raw[0] <- step 2 (raw[1] <- step 3)
+  load_a(0, raw_a[0]);
+  load_w(0, raw_w[0]);
+  load_a(1, raw_a[1]);
+  load_w(1, raw_w[1]);
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int st = p * STAGE_BYTES;
+    const bool k_ok = p * kBK < K;
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        put_piece(raw_a[p][q], st + A_CODES, q, c);
+        put_piece(raw_w[p][q], st + W_CODES, q, c);
+      }
+      put_scale(st + A_SC, raw_a[p][q], a_ok[q] && k_ok, q);
+      put_scale(st + W_SC, raw_w[p][q], w_ok[q] && k_ok, q);
+    }
+    if (p < RS) {
+      load_a(p + 2, raw_a[p]);
+      load_w(p + 2, raw_w[p]);
+    }
+  }
+  __syncthreads();
+
+  const float16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
+                          0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  Frag wf[TN], xf[2];
+  uint32_t sw[TN], sx[2];
+#pragma unroll
+  for (int i = 0; i < TN; ++i) {
+    wf[i] = read_frag(w_base, 0, i);
+    sw[i] = read_scale(ws_base, 0, i);
+  }
+  xf[0] = read_frag(x_base, 0, 0);
+  sx[0] = read_scale(xs_base, 0, 0);
+  int st_cur = 0;                                      // byte offset of the stage being multiplied
+  auto stage_after = [&](int st, int n) {
+    const int v = st + n * STAGE_BYTES;
+    return v >= STAGES * STAGE_BYTES ? v - STAGES * STAGE_BYTES : v;
+  };
+
+  // X0: which of the two activation fragments tile row 0 of this step sits in
+  auto body = [&](auto Pc, auto TMc, auto X0c, int s) {
+    constexpr int P = decltype(Pc)::value;
+    constexpr int TMW = decltype(TMc)::value;
+    constexpr int X0 = decltype(X0c)::value;
+    constexpr int NT = TMW * TN;                       // tiles of this wave
+    constexpr int NW = 2 * SL * NP;                    // pieces to unpack, all in the first half of the tiles
+    Slice(&ra)[SL] = raw_a[P % RS];
+    Slice(&rw)[SL] = raw_w[P % RS];
+    const int st_next = stage_after(st_cur, 1), st_put = stage_after(st_cur, 2);
+    const bool k_ok = (s + 2) * kBK < K;
+
+    half4v swz[TN];
+#pragma unroll
+    for (int i = 0; i < TN; ++i) swz[i] = scale_operand(frag_half == 0 ? sw[i] : 0u);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = t / TN, i = t % TN;
+      const int8v xo = operand(xf[(X0 + j) & 1]);
+      const float16_t sc = __builtin_amdgcn_mfma_f32_32x32x8f16(swz[i], scale_operand(sx[(X0 + j) & 1]), zero, 0, 0, 0);
+      const float16_t p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(wf[i]), xo, zero, FMT_SEL, FMT_SEL, 0, 0, 0, 0);
+      // while the matrix unit works: fragments to come, and this thread's share of step s + 2
+      if (i == 0) {
+        const int nx = (X0 + j + 1) & 1;
+        if (j + 1 < TMW) {
+          xf[nx] = read_frag(x_base, st_cur, j + 1);
+          sx[nx] = read_scale(xs_base, st_cur, j + 1);
+        } else {
+          xf[nx] = read_frag(x_base, st_next, 0);
+          sx[nx] = read_scale(xs_base, st_next, 0);
+        }
+      }
+      if (j == TMW - 1) {                              // the last use of weight fragment i in this step
+        wf[i] = read_frag(w_base, st_next, i);
+        sw[i] = read_scale(ws_base, st_next, i);
+      }
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        if (u * (NT / 2) / NW != t) continue;
+        const int q = (u / NP) % SL, c = u % NP;
+        if (u < SL * NP) {
+          put_piece(ra[q], st_put + A_CODES, q, c);
+          if (c == 0) put_scale(st_put + A_SC, ra[q], a_ok[q] && k_ok, q);
+        } else {
+          put_piece(rw[q], st_put + W_CODES, q, c);
+          if (c == 0) put_scale(st_put + W_SC, rw[q], w_ok[q] && k_ok, q);
+        }
+        if (u == SL * NP - 1) load_a(s + 2 + RS, ra);
+        if (u == NW - 1) load_w(s + 2 + RS, rw);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(p[r], sc[r], acc[i][j][r]);
+      __builtin_amdgcn_sched_barrier(0);
+      // One barrier a step, in its middle.  It publishes the stage written above, whose first fragments are
+      // read at the end of the next step; and the stage written in the next step was last read in the step
+      // before this one.
+      if (t == NT / 2) {
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    st_cur = st_next;
+  };
+
+  // two steps per trip (the register sets are compile-time constants); an odd step count runs one extra step
+  // on zero scales
+  if (!RAGGED_M || tm_cnt == TM) {
+    for (int s = 0; s < ksteps; s += 2) {
+      body(IntC<0>{}, IntC<TM>{}, IntC<0>{}, s);
+      body(IntC<1>{}, IntC<TM>{}, IntC<TM & 1>{}, s + 1);
+    }
+  } else {
+    for (int s = 0; s < ksteps; s += 2) {
+      body(IntC<0>{}, IntC<TM_LAST>{}, IntC<0>{}, s);
+      body(IntC<1>{}, IntC<TM_LAST>{}, IntC<TM_LAST & 1>{}, s + 1);
+    }
+  }
+
+  __syncthreads();                                     // the output tile reuses the stages
+  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT_F32>(
+      acc, smem, A.mul, A.mul_stride, W.mul, W.mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid,
+      FP4 ? 4.0f : 262144.0f, y, ldy);
+}
+
+template <bool FP4, int BM, int BN, int WGM, int WGN, bool OUT_F32>
+static int launch_group(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
+                        int64_t ldy, hipStream_t st) {
+  constexpr int T = WGM * WGN * 64;
+  constexpr int A_ROWS = (BM * 2 + T - 1) / T * (T / 2);
+  constexpr size_t stages = 4 * (size_t)(A_ROWS + BN) * ((FP4 ? 32 : 64) + 2);
+  constexpr size_t out = OUT_F32 ? 0 : (size_t)BM * (BN * 2 + 16);
+  constexpr size_t shmem = stages > out ? stages : out;
+  auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT_F32>;
+  if (shmem > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(qgemm_group_kernel)");
+  }
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
+  if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, g_shift, y, ldy, tiles_m,
+                     tiles_n);
+  return check_hip(hipGetLastError(), "qgemm_group_kernel");
+}
+
+template <bool FP4, bool OUT_F32>
+static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
+                      int64_t ldy, int choice, hipStream_t st) {
+  if (choice == 1) return launch_group<FP4, 256, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+  return launch_group<FP4, 224, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+}
+
+// INT4 and INT3 with groups of 64, 128 or 256, large tiles
+int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
+                       void* y, int64_t ldy, bool out_f32, int choice, hipStream_t st) {
+  const int g_shift = group == 64 ? 6 : group == 128 ? 7 : 8;
+#define PQ_ARGS A, W, M, N, K, g_shift, y, ldy, choice, st
+  if (fmt == PQ_FMT_INT4) return out_f32 ? group_tile<false, true>(PQ_ARGS) : group_tile<false, false>(PQ_ARGS);
+  return out_f32 ? group_tile<true, true>(PQ_ARGS) : group_tile<true, false>(PQ_ARGS);
+#undef PQ_ARGS
+}
+
+}  // namespace pq

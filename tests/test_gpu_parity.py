@@ -599,6 +599,43 @@ def test_qgemm_square_tile_path(fmt, g):
     _gemm_case(fmt, g, 4096 - 6, 4096 - 9, 128, 750 + g)
 
 
+@pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_INT4, 64, 4096 - 6, 4096 - 9, 64),          # one step; square tile
+    (pq.FMT_INT4, 128, 2304 + 40, 3584 + 72, 384),      # 224-row tile, odd number of 128-wide groups
+    (pq.FMT_INT4, 256, 4096 - 6, 4096 - 9, 256),
+    (pq.FMT_INT3, 64, 2304 + 40, 3584 + 72, 192),       # odd number of steps
+    (pq.FMT_INT3, 64, 4096 - 6, 4096 - 9, 320),
+    (pq.FMT_INT3, 256, 2304 + 40, 3584 + 72, 512),
+])
+def test_qgemm_codes_on_the_matrix_unit(fmt, g, M, N, K):
+    # the integer formats' kernel with the scales outside the matrix instructions: every code format, both tile
+    # heights, ragged edges, one step, odd and even step counts, groups of one, two and four steps
+    _gemm_case(fmt, g, M, N, K, 760 + g + K)
+
+
+@pytest.mark.parametrize("fmt,g,lo,hi", [(pq.FMT_INT4, 64, -8, 8), (pq.FMT_INT3, 128, -4, 4)])
+def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
+    # every nibble the code formats of the matrix unit hold, the one below -Q included; all scales 1, so the
+    # accumulator holds Q^2 times the integer product (|.| <= 64 * 256 < 2^24 / 49) exactly and the epilogue
+    # rounds at most three times.  Packed and row-major operands: the same bits.
+    M, N, K = 2304, 3584, 256
+    rng = np.random.default_rng(905 + g)
+    za = rng.integers(lo, hi, size=(M, K))
+    zw = rng.integers(lo, hi, size=(N, K))
+    a_codes = torch.from_numpy(OF.pack_nibbles(OF.int_to_nibble(za))).to(DEV)
+    w_codes = torch.from_numpy(OF.pack_nibbles(OF.int_to_nibble(zw))).to(DEV)
+    sa = torch.ones((M, K // g), dtype=torch.float32, device=DEV)
+    sw = torch.ones((N, K // g), dtype=torch.float32, device=DEV)
+    y = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    pq.pq_qgemm_f32(fmt, g, a_codes, sa, None, w_codes, sw, None, y)
+    y_packed = torch.zeros_like(y)
+    pq.pq_qgemm_packed_f32(fmt, g, pq.pq_pack_operand(fmt, g, a_codes, sa), None, pq.pq_pack_operand(fmt, g, w_codes, sw),
+                           None, y_packed, M, N, K)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(y.cpu().numpy(), (za @ zw.T).astype(np.float32), rtol=3 * 2.0 ** -24, atol=0)
+    assert torch.equal(y, y_packed)
+
+
 @pytest.mark.parametrize("fmt,g", FMTS[:4])
 def test_qgemm_tiny(fmt, g):
     _gemm_case(fmt, g, 1, 8, 2 * max(g, 32), 800 + g)
