@@ -114,6 +114,36 @@ __device__ __forceinline__ uint32_t unpack_pair(uint32_t d, const PairScale& sc)
 // tile row `r`, 16-byte piece `piece` (0..7) -> byte offset inside one LDS operand tile
 __device__ __forceinline__ int lds_off(int r, int piece) { return r * kRowBytes + (piece << 4); }
 
+// ------------------------------------------------------------------------ codes for the matrix unit
+// (pq_qgemm_group.hip says why these are exact)
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef int int8v __attribute__((ext_vector_type(8)));
+typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+
+// four two's complement nibbles, one per byte of n (top nibbles 0), m = their sign bits: bytes sign << 7 | |z|
+__device__ __forceinline__ uint32_t e4m3_bytes(uint32_t n, uint32_t m) {
+  const uint32_t f = __builtin_amdgcn_perm(0u, 0x00008F00u, m);      // 0x8F where negative
+  return (n ^ f) + m;                                                // 16 - n <= 8 under the sign: no carry
+}
+
+// eight nibbles z (two's complement, |z| <= 4) -> eight nibbles sign << 3 | |z|
+__device__ __forceinline__ uint32_t e2m1_nibbles(uint32_t d) {
+  const uint32_t s = d & 0x88888888u, m = s >> 3;
+  return (d ^ (s - m)) + m;
+}
+
+// fp16 scale unit as the one non-zero k of an outer product's operand
+__device__ __forceinline__ half4v scale_operand(uint32_t h) {
+  return __builtin_bit_cast(half4v, make_uint2(h, 0u));
+}
+
+// two fp32 rounded to nearest even bf16, packed (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){lo, hi}, bf16x2_t));
+}
+
 template <int V>
 struct IntC {
   static constexpr int value = V;
@@ -202,13 +232,8 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
             }
           }
         } else {
-          // round to nearest even, two values per instruction (v_cvt_pk_bf16_f32)
-          typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-          typedef float f32x2_t __attribute__((ext_vector_type(2)));
-          const bf16x2_t lo = __builtin_convertvector((f32x2_t){v[0], v[1]}, bf16x2_t);
-          const bf16x2_t hi = __builtin_convertvector((f32x2_t){v[2], v[3]}, bf16x2_t);
           *reinterpret_cast<uint2*>(smem + ml * C_ROW_BYTES + nl * 2) =
-              make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+              make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
         }
       }
     }
@@ -262,7 +287,12 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
 // the product kernel on two operand views (pq_qgemm.hip)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
                        int64_t N, int64_t K, void* y, int64_t ldy, bool out_f32, hipStream_t st);
-// the integer formats' share of it (pq_qgemm_group.hip); tile: as choose_tile numbers them
+// output tiles of the product kernels (choose_tile in pq_qgemm.hip)
+enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kTileSplit64x32 = 5, kTileSplit64 = 6, kTileSplit64x96 = 7 };
+// small outputs (pq_qgemm_split.hip)
+int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
+                       void* y, int64_t ldy, bool out_f32, int tile, hipStream_t st);
+// the integer formats' large outputs with groups of 64 and more (pq_qgemm_group.hip)
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        void* y, int64_t ldy, bool out_f32, int tile, hipStream_t st);
 

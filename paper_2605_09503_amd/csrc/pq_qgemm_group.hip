@@ -39,26 +39,6 @@
 
 namespace pq {
 
-namespace {
-
-typedef int int4v __attribute__((ext_vector_type(4)));
-typedef int int8v __attribute__((ext_vector_type(8)));
-typedef _Float16 half4v __attribute__((ext_vector_type(4)));
-
-// four two's complement nibbles, one per byte of n (top nibbles 0), m = their sign bits: bytes sign << 7 | |z|
-__device__ __forceinline__ uint32_t e4m3_bytes(uint32_t n, uint32_t m) {
-  const uint32_t f = __builtin_amdgcn_perm(0u, 0x00008F00u, m);      // 0x8F where negative
-  return (n ^ f) + m;                                                // 16 - n <= 8 under the sign: no carry
-}
-
-// eight nibbles z (two's complement, |z| <= 4) -> eight nibbles sign << 3 | |z|
-__device__ __forceinline__ uint32_t e2m1_nibbles(uint32_t d) {
-  const uint32_t s = d & 0x88888888u, m = s >> 3;
-  return (d ^ (s - m)) + m;
-}
-
-}  // namespace
-
 // FP4: E2M1 codes (INT3), else E4M3 (INT4).  Groups are a multiple of 64 (2^g_shift).
 template <bool FP4, int BM, int BN, int WGM, int WGN, bool OUT_F32>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView A, OperandView W, int M, int N,
@@ -190,11 +170,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
     if constexpr (FP4) return (int8v){f.v[0].x, f.v[0].y, f.v[0].z, f.v[0].w, 0, 0, 0, 0};
     else return (int8v){f.v[0].x, f.v[0].y, f.v[0].z, f.v[0].w, f.v[NP - 1].x, f.v[NP - 1].y, f.v[NP - 1].z, f.v[NP - 1].w};
   };
-  auto scale_operand = [&](uint32_t h) {
-    const uint2 u = make_uint2(h, 0u);
-    return __builtin_bit_cast(half4v, u);
-  };
-
   float16_t acc[TN][TM];
 #pragma unroll
   for (int i = 0; i < TN; ++i)
@@ -360,7 +335,7 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
 template <bool FP4, bool OUT_F32>
 static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
                       int64_t ldy, int choice, hipStream_t st) {
-  if (choice == 1) return launch_group<FP4, 256, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+  if (choice == kTile256) return launch_group<FP4, 256, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
   return launch_group<FP4, 224, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
 }
 

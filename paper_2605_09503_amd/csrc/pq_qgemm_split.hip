@@ -1,0 +1,281 @@
+// Low-bit GEMM of the quantized layer (paper Eq. 8) for outputs too small to fill the chip with the tiles of
+// pq_qgemm.hip, or with too few steps of K to pay for their pipelines.
+//
+// The waves of a workgroup split K between them: wave w of KS takes the 64-wide steps w, w + KS, ... of a tile of
+// 32 x 32 to 64 x 96 outputs, and the partial sums are added in a fixed order through LDS at the end.  Nothing else is
+// shared: in the panel layout a fragment of 32 rows and one step is 1 KB of consecutive codes, so a wave loads its
+// fragments straight into the registers the matrix unit reads, two of its steps ahead, and unpacks them there.  No
+// operand goes through LDS and the loop has no barrier.
+//
+// What bounds it.  The small ones are a chain: launch, one load, the unpack and the product of a few steps, the sums.
+// A 128 x 128 tile of four waves, which these shapes took before, spends 0.35 to 0.7 us in every step and
+// walks all of K alone.  The larger ones are bound by the sum of matrix and vector instructions (the two hardly
+// overlap, see pq_qgemm_group.hip): a 64 x 96 tile unpacks five fragments for six 32 x 32 x 64 products, 1.5 times what
+// a staged 128 x 128 tile unpacks, but its four-wave workgroups need no barrier and run two to a compute unit.  Four
+// waves and not eight share a 64 x 96 tile because the second workgroup then covers the first one's ends
+// (NVFP4 512 x 9216 x 3072: 32 us, with eight waves 42).  Kernel alone, us, before -> now:
+//   NVFP4     256 x 512 x 512     9.2 ->  3.9     512 x 3072 x 3072   30 -> 13.8    512 x 3072 x 12288  102 -> 43
+//   NVFP4     512 x 9216 x 3072    47 -> 32       64 x 12288 x 3072   29 -> 11      16 x 512 x 12288    100 -> 13
+//   INT4 g128  77 x 1000 x 1152  15.4 ->  4.6     INT4 g64   1024 x 3072 x 3072  33 -> 25
+//   INT3 g64  512 x 3072 x 3072    32 -> 12       INT3 g64   2048 x 3072 x 3072  50 -> 32
+// INT4 in the 8-bit form of pq_qgemm_group.hip gained nothing here (15.5 -> 16.5, 46.9 -> 43.6 us): fp16 operands.
+#include "pq_qgemm_common.h"
+
+namespace pq {
+
+// What the matrix unit is fed with: fp16 operands that carry their group's scale (pq_qgemm.hip), or the codes with
+// the scales outside (pq_qgemm_group.hip)
+enum SplitMode : int { kSplitNvfp4 = 0, kSplitInt = 1, kSplitE2m1 = 2 };
+
+template <int MODE, int TM, int TN, int KS, bool OUT_F32>
+__global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, OperandView W, int M, int N,
+                                                                      int K, int g_shift, void* __restrict__ y,
+                                                                      int64_t ldy, int tiles_m, int tiles_n) {
+  constexpr int T = KS * 64;
+  constexpr int BM = TM * 32, BN = TN * 32;
+  constexpr bool CODES = MODE == kSplitE2m1;
+  constexpr int PD = 2;                                // own steps in flight
+  constexpr int ROW = 32 + 4;                          // floats of a partial sum's row in LDS
+  extern __shared__ __attribute__((aligned(16))) float part[];        // [KS][BM][ROW]: one 32-column strip
+
+  int tile_m, tile_n;
+  assign_tile(tiles_m, tiles_n, tile_m, tile_n);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);            // this wave's share of K: steps ks, ks + KS, ...
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int frag_row = lane & 31, frag_half = lane >> 5;
+
+  // a fragment's lane: row lane % 32, k 32 * (lane / 32) .. + 31 of the step: 16 bytes of codes, one scale unit
+  uint32_t a_coff[TM], w_coff[TN], a_soff[TM], w_soff[TN];
+  bool a_ok[TM], w_ok[TN];
+#pragma unroll
+  for (int j = 0; j < TM; ++j) {
+    const int r = j * 32 + frag_row;
+    a_ok[j] = m0 + r < M;
+    a_coff[j] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)A.code_row;
+    a_soff[j] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)A.sc_row;
+  }
+#pragma unroll
+  for (int i = 0; i < TN; ++i) {
+    const int r = i * 32 + frag_row;
+    w_ok[i] = n0 + r < N;
+    w_coff[i] = (uint32_t)min(r, N - 1 - n0) * (uint32_t)W.code_row;
+    w_soff[i] = (uint32_t)min(r, N - 1 - n0) * (uint32_t)W.sc_row;
+  }
+  const uint8_t* a_codes = A.codes + (int64_t)m0 * A.code_row;
+  const uint8_t* w_codes = W.codes + (int64_t)n0 * W.code_row;
+  const uint8_t* a_scales = A.scales + (int64_t)m0 * A.sc_row;
+  const uint8_t* w_scales = W.scales + (int64_t)n0 * W.sc_row;
+  const int ksteps = (K + kBK - 1) / kBK;
+  const bool per_half = g_shift == 5;                  // a scale unit covers 32 k: the lane halves have their own
+
+  struct Step {
+    Slice a[TM], w[TN];
+  };
+  // a step past the last re-reads the last, the missing upper half of a last step of 32 k the lower one (both are
+  // neutralised by a zero scale)
+  auto load = [&](int step, Step& f) {
+    const int st = min(step, ksteps - 1);              // uniform
+    const uint32_t half = st * kBK + frag_half * 32 < K ? frag_half : 0;
+    const int unit = (st * kBK) >> g_shift;
+    const uint8_t *ac = a_codes + (int64_t)st * A.code_step, *wc = w_codes + (int64_t)st * W.code_step;
+    const uint8_t *as = a_scales + (int64_t)unit * A.sc_step, *ws = w_scales + (int64_t)unit * W.sc_step;
+    const uint32_t ah = per_half ? half * (uint32_t)A.sc_step : 0u, wh = per_half ? half * (uint32_t)W.sc_step : 0u;
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      f.a[j].codes = *reinterpret_cast<const uint4*>(ac + (a_coff[j] + half * 16u));
+      f.a[j].sc = *reinterpret_cast<const uint16_t*>(as + (a_soff[j] + ah));
+    }
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      f.w[i].codes = *reinterpret_cast<const uint4*>(wc + (w_coff[i] + half * 16u));
+      f.w[i].sc = *reinterpret_cast<const uint16_t*>(ws + (w_soff[i] + wh));
+    }
+  };
+
+  float16_t acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  auto multiply = [&](const Step& f, int step) {
+    const bool k_ok = step * kBK + frag_half * 32 < K;
+    if constexpr (!CODES) {
+      constexpr int FMT = MODE == kSplitNvfp4 ? kNvfp4 : kInt4;       // INT3 nibbles unpack like INT4's
+      PairScale sa[TM][2], sw[TN][2];
+#pragma unroll
+      for (int j = 0; j < TM; ++j) slice_scales<FMT>(f.a[j], a_ok[j] && k_ok, sa[j][0], sa[j][1]);
+#pragma unroll
+      for (int i = 0; i < TN; ++i) slice_scales<FMT>(f.w[i], w_ok[i] && k_ok, sw[i][0], sw[i][1]);
+      auto unpack = [&](const uint4& codes, int kk, const PairScale (&sc)[2]) {
+        const uint32_t d = kk == 0 ? codes.x : kk == 1 ? codes.y : kk == 2 ? codes.z : codes.w;
+        const PairScale& s = sc[kk / 2];
+        const uint4 v = make_uint4(unpack_pair<FMT, 0>(d, s), unpack_pair<FMT, 1>(d, s), unpack_pair<FMT, 2>(d, s),
+                                   unpack_pair<FMT, 3>(d, s));
+        return __builtin_bit_cast(half8_t, v);
+      };
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        half8_t x[TM], w[TN];
+#pragma unroll
+        for (int j = 0; j < TM; ++j) x[j] = unpack(f.a[j].codes, kk, sa[j]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) w[i] = unpack(f.w[i].codes, kk, sw[i]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+          for (int j = 0; j < TM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i], x[j], acc[i][j], 0, 0, 0);
+      }
+    } else {
+      const float16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
+                              0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+      int8v x[TM], w[TN];
+      half4v sx[TM], sw[TN];
+      auto codes = [&](const uint4& c) {
+        return (int8v){(int)e2m1_nibbles(c.x), (int)e2m1_nibbles(c.y), (int)e2m1_nibbles(c.z), (int)e2m1_nibbles(c.w),
+                       0, 0, 0, 0};
+      };
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        x[j] = codes(f.a[j].codes);
+        sx[j] = scale_operand(a_ok[j] && k_ok ? f.a[j].sc : 0u);
+      }
+#pragma unroll
+      for (int i = 0; i < TN; ++i) {
+        w[i] = codes(f.w[i].codes);
+        sw[i] = scale_operand(w_ok[i] && frag_half == 0 ? f.w[i].sc : 0u);
+      }
+#pragma unroll
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+          const float16_t s = __builtin_amdgcn_mfma_f32_32x32x8f16(sw[i], sx[j], zero, 0, 0, 0);
+          const float16_t p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w[i], x[j], zero, 4, 4, 0, 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(p[r], s[r], acc[i][j][r]);
+        }
+    }
+  };
+
+  Step raw[PD];
+  const int n_own = (ksteps - ks + KS - 1) / KS;       // steps ks, ks + KS, ...
+#pragma unroll
+  for (int p = 0; p < PD; ++p) load(ks + p * KS, raw[p]);
+  for (int o = 0; o < n_own; o += PD) {
+#pragma unroll
+    for (int p = 0; p < PD; ++p) {
+      if (o + p < n_own) {                             // uniform
+        multiply(raw[p], ks + (o + p) * KS);
+        load(ks + (o + p + PD) * KS, raw[p]);
+      }
+    }
+  }
+
+  // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
+  const uint16_t* __restrict__ bias = W.bias;
+  constexpr int CHUNKS = 4;                            // eight columns each
+  constexpr float unit = CODES ? 4.0f : 1.0f;          // undoes the E2M1 codes' factor 1/2 on either side
+#pragma unroll
+  for (int i = 0; i < TN; ++i) {
+    if (i) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float* p = part + (size_t)(ks * BM + j * 32 + frag_row) * ROW + q * 8 + frag_half * 4;
+        *reinterpret_cast<float4*>(p) =
+            make_float4(acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]);
+      }
+    __syncthreads();
+    for (int c = tid; c < BM * CHUNKS; c += T) {
+      const int row = c / CHUNKS, cc = c % CHUNKS;
+      const int m = m0 + row, n = n0 + i * 32 + cc * 8;
+      if (m >= M || n >= N) continue;
+      float v[8];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const float4* p = reinterpret_cast<const float4*>(part + (size_t)(s * BM + row) * ROW + cc * 8);
+        const float4 lo = p[0], hi = p[1];
+        const float t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = s == 0 ? t[e] : v[e] + t[e];
+      }
+      const float am = A.mul[(int64_t)m * A.mul_stride];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int nn = min(n + e, N - 1);
+        v[e] = (v[e] * unit) * (am * W.mul[(int64_t)nn * W.mul_stride]);
+        if (bias) v[e] += bf16_to_f32(bias[nn]);
+      }
+      if constexpr (OUT_F32) {
+        float* yo = reinterpret_cast<float*>(y) + (int64_t)m * ldy + n;
+        if (n + 7 < N) {
+          *reinterpret_cast<float4*>(yo) = make_float4(v[0], v[1], v[2], v[3]);
+          *reinterpret_cast<float4*>(yo + 4) = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + e < N) yo[e] = v[e];
+        }
+      } else {
+        uint16_t* yo = reinterpret_cast<uint16_t*>(y) + (int64_t)m * ldy + n;
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = cvt_pk_bf16(v[2 * e], v[2 * e + 1]);
+        if (n + 7 < N) {
+          *reinterpret_cast<uint4*>(yo) = make_uint4(w[0], w[1], w[2], w[3]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + e < N) yo[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        }
+      }
+    }
+  }
+}
+
+template <int MODE, int TM, int TN, int KS, bool OUT_F32>
+static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
+                        int64_t ldy, hipStream_t st) {
+  constexpr int BM = TM * 32, BN = TN * 32;
+  constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4;
+  static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
+  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT_F32>;
+  if (shmem > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(qgemm_split_kernel)");
+  }
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
+  if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, y,
+                     ldy, tiles_m, tiles_n);
+  return check_hip(hipGetLastError(), "qgemm_split_kernel");
+}
+
+template <int MODE, bool OUT_F32>
+static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
+                      int64_t ldy, int tile, hipStream_t st) {
+  switch (tile) {
+    case kTileSplit32: return launch_split<MODE, 1, 1, 8, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+    case kTileSplit64x32: return launch_split<MODE, 2, 1, 8, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+    case kTileSplit64: return launch_split<MODE, 2, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+    default: return launch_split<MODE, 2, 3, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+  }
+}
+
+int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
+                       void* y, int64_t ldy, bool out_f32, int tile, hipStream_t st) {
+  const int g_shift = fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
+#define PQ_ARGS A, W, M, N, K, g_shift, y, ldy, tile, st
+  if (fmt == PQ_FMT_NVFP4) return out_f32 ? split_tile<kSplitNvfp4, true>(PQ_ARGS) : split_tile<kSplitNvfp4, false>(PQ_ARGS);
+  if (fmt == PQ_FMT_INT3 && group != 32) return out_f32 ? split_tile<kSplitE2m1, true>(PQ_ARGS) : split_tile<kSplitE2m1, false>(PQ_ARGS);
+  return out_f32 ? split_tile<kSplitInt, true>(PQ_ARGS) : split_tile<kSplitInt, false>(PQ_ARGS);
+#undef PQ_ARGS
+}
+
+}  // namespace pq

@@ -601,7 +601,7 @@ def test_qgemm_square_tile_path(fmt, g):
 
 @pytest.mark.parametrize("fmt,g,M,N,K", [
     (pq.FMT_INT4, 64, 4096 - 6, 4096 - 9, 64),          # one step; square tile
-    (pq.FMT_INT4, 128, 2304 + 40, 3584 + 72, 384),      # 224-row tile, odd number of 128-wide groups
+    (pq.FMT_INT4, 128, 3000, 4096 - 9, 640),            # 224-row tile, odd number of 128-wide groups
     (pq.FMT_INT4, 256, 4096 - 6, 4096 - 9, 256),
     (pq.FMT_INT3, 64, 2304 + 40, 3584 + 72, 192),       # odd number of steps
     (pq.FMT_INT3, 64, 4096 - 6, 4096 - 9, 320),
@@ -616,9 +616,9 @@ def test_qgemm_codes_on_the_matrix_unit(fmt, g, M, N, K):
 @pytest.mark.parametrize("fmt,g,lo,hi", [(pq.FMT_INT4, 64, -8, 8), (pq.FMT_INT3, 128, -4, 4)])
 def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     # every nibble the code formats of the matrix unit hold, the one below -Q included; all scales 1, so the
-    # accumulator holds Q^2 times the integer product (|.| <= 64 * 256 < 2^24 / 49) exactly and the epilogue
+    # accumulator holds Q^2 times the integer product (|.| <= 64 * 256 or 16 * 512, times 49) exactly and the epilogue
     # rounds at most three times.  Packed and row-major operands: the same bits.
-    M, N, K = 2304, 3584, 256
+    M, N, K = (4096, 4096, 256) if fmt == pq.FMT_INT4 else (2304, 3584, 512)      # 256- and 224-row tiles
     rng = np.random.default_rng(905 + g)
     za = rng.integers(lo, hi, size=(M, K))
     zw = rng.integers(lo, hi, size=(N, K))
@@ -632,8 +632,32 @@ def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     pq.pq_qgemm_packed_f32(fmt, g, pq.pq_pack_operand(fmt, g, a_codes, sa), None, pq.pq_pack_operand(fmt, g, w_codes, sw),
                            None, y_packed, M, N, K)
     torch.cuda.synchronize()
-    np.testing.assert_allclose(y.cpu().numpy(), (za @ zw.T).astype(np.float32), rtol=3 * 2.0 ** -24, atol=0)
+    want = (za.astype(np.float64) @ zw.T.astype(np.float64)).astype(np.float32)
+    np.testing.assert_allclose(y.cpu().numpy(), want, rtol=3 * 2.0 ** -24, atol=0)
     assert torch.equal(y, y_packed)
+
+
+@pytest.mark.parametrize("fmt,g,K", [(pq.FMT_NVFP4, 16, 96), (pq.FMT_INT4, 64, 192), (pq.FMT_INT3, 256, 256)])
+def test_qgemm_128_tile(fmt, g, K):
+    # few steps and some 200 tiles of 128 x 128; ragged rows and columns
+    _gemm_case(fmt, g, 1500, 2056, K, 765 + g)
+
+
+# one shape for each tile in which the waves split K (32 x 32, 64 x 32, 64 x 64, 64 x 96 outputs), for each way of
+# feeding the matrix unit: NVFP4, INT with a scale unit per half step, INT with one per step and per four steps, INT3
+# codes.  K from half a step over fewer steps than waves to an odd number of them; ragged rows and columns.
+@pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_NVFP4, 16, 33, 41, 32), (pq.FMT_NVFP4, 16, 130, 257, 1120),
+    (pq.FMT_NVFP4, 16, 70, 3000, 96), (pq.FMT_NVFP4, 16, 2300, 333, 96), (pq.FMT_NVFP4, 16, 300, 4087, 416),
+    (pq.FMT_INT4, 32, 33, 41, 32), (pq.FMT_INT4, 32, 70, 3000, 96), (pq.FMT_INT3, 32, 130, 3656, 160),
+    (pq.FMT_INT4, 32, 300, 4087, 416),
+    (pq.FMT_INT4, 64, 131, 150, 704), (pq.FMT_INT4, 256, 70, 3000, 256), (pq.FMT_INT4, 256, 130, 3656, 768),
+    (pq.FMT_INT4, 128, 300, 4087, 640),
+    (pq.FMT_INT3, 64, 33, 41, 64), (pq.FMT_INT3, 256, 70, 3000, 256), (pq.FMT_INT3, 64, 1500, 1003, 320),
+    (pq.FMT_INT3, 256, 300, 4087, 768),
+])
+def test_qgemm_waves_split_k(fmt, g, M, N, K):
+    _gemm_case(fmt, g, M, N, K, 770 + g + K)
 
 
 @pytest.mark.parametrize("fmt,g", FMTS[:4])
