@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/permuquant.h"
 
 namespace pq {
@@ -21,6 +23,20 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // PQ_OK, or the error for an unknown format / unsupported (format, group) pair / K % group.
 int check_format(pq_format fmt, int group, int64_t K);
+
+// Lets a kernel have more than 48 KB of dynamic LDS.  The attribute belongs to the kernel and the device, so it is set
+// once for each: `done` (one per kernel, a bit per device) says where it is; devices past the 64th set it every time.
+inline int allow_lds(const void* kern, size_t bytes, std::atomic<uint64_t>& done, const char* what) {
+  if (bytes <= 48 * 1024) return PQ_OK;
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+  if (done.load(std::memory_order_acquire) & bit) return PQ_OK;
+  hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) return check_hip(e, what);
+  done.fetch_or(bit, std::memory_order_release);
+  return PQ_OK;
+}
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 

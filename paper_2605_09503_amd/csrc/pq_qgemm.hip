@@ -267,11 +267,20 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
 // ------------------------------------------------------------------------ INT scale prepass
 // One wave per row of scales: recover each group's bf16 maximum h = bf16_rne(s * Q), find the
 // row's largest exponent, and emit fp16 h * 2^-E plus the fp32 epilogue factor 2^E / Q, with E
-// chosen so that the largest h * 2^-E stays below 2^11.
-__global__ __launch_bounds__(256) void int_scale_prep_kernel(const float* __restrict__ s, int rows,
-                                                             int groups, float Q,
-                                                             uint16_t* __restrict__ h_out,
-                                                             float* __restrict__ mul_out) {
+// chosen so that the largest h * 2^-E stays below 2^11.  blockIdx.y: the operand (a launch for each took 2.5 us
+// more than one for both).
+struct ScalePrep {
+  const float* s;
+  uint16_t* h;
+  float* mul;
+  int rows;
+};
+__global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScalePrep w, int groups, float Q) {
+  const ScalePrep& o = blockIdx.y ? w : a;
+  const float* __restrict__ s = o.s;
+  uint16_t* __restrict__ h_out = o.h;
+  float* __restrict__ mul_out = o.mul;
+  const int rows = o.rows;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= rows) return;
@@ -382,11 +391,8 @@ static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N,
   constexpr int T = WGM * WGN * 64;
   constexpr size_t shmem = 2 * (size_t)((BM * 2 + T - 1) / T * (T / 2) + BN) * kRowBytes;
   auto kern = qgemm_kernel<FMT, G, BM, BN, WGM, WGN, OUT_F32>;
-  if (shmem > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(qgemm_kernel)");
-  }
+  static std::atomic<uint64_t> raised{0};
+  if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_kernel)")) return rc;
   int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
@@ -511,10 +517,10 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     carve_gemm(ws, fmt, group, M, N, K, &G);
     const float Q = qmax_of((int)fmt);
     if (phases & 1) {
-      hipLaunchKernelGGL(int_scale_prep_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st,
-                         (const float*)a_scales, (int)M, (int)(K / group), Q, G.a_h, G.a_mul);
-      hipLaunchKernelGGL(int_scale_prep_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, st,
-                         (const float*)w_scales, (int)N, (int)(K / group), Q, G.w_h, G.w_mul);
+      const int64_t most = M > N ? M : N;
+      hipLaunchKernelGGL(int_scale_prep_kernel, dim3((unsigned)((most + 3) / 4), 2), dim3(256), 0, st,
+                         ScalePrep{(const float*)a_scales, G.a_h, G.a_mul, (int)M},
+                         ScalePrep{(const float*)w_scales, G.w_h, G.w_mul, (int)N}, (int)(K / group), Q);
       int rc = check_hip(hipGetLastError(), "int_scale_prep_kernel");
       if (rc) return rc;
     }

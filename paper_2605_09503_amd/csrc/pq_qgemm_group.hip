@@ -319,11 +319,8 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
   constexpr size_t out = OUT_F32 ? 0 : (size_t)BM * (BN * 2 + 16);
   constexpr size_t shmem = stages > out ? stages : out;
   auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT_F32>;
-  if (shmem > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(qgemm_group_kernel)");
-  }
+  static std::atomic<uint64_t> raised{0};
+  if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_group_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");

@@ -244,11 +244,8 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4;
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
   auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT_F32>;
-  if (shmem > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(qgemm_split_kernel)");
-  }
+  static std::atomic<uint64_t> raised{0};
+  if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_split_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
