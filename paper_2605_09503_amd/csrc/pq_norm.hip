@@ -644,9 +644,12 @@ int norm_waves_per_group(Kern kern, int norm, bool is_int, int64_t rows, int64_t
       per_cu = 1;
     const int64_t groups = (rows + w - 1) / w;
     const int64_t rounds = (groups + 256 * (int64_t)per_cu - 1) / (256 * (int64_t)per_cu);
-    // time ~ rounds x (row work + vector staging shared by w rows), in units of one row's work;
-    // among equal costs prefer more waves in flight per compute unit
-    const double cost = (double)rounds * (1.0 + 0.35 / w) - 1e-3 * (double)std::min(per_cu * w, 32);
+    // time ~ rounds x (row work + vector staging shared by w rows), in units of one row's work, plus what the
+    // rows that meet on the busiest of the 256 units cost each other (the transform's passes share the unit's
+    // LDS: 512 x 4096 takes 26 us with eight rows a workgroup on 64 units, 13 with two on 256; 1024 x 3072 10.6 and
+    // 8.9; RMSNorm 1024 x 3072 7.3 and 7.1); among equal costs prefer more waves in flight per compute unit
+    const double crowd = (norm == kHadamard ? 0.06 : 0.012) * (double)((groups + 255) / 256 * w);
+    const double cost = (double)rounds * (1.0 + 0.35 / w) + crowd - 1e-3 * (double)std::min(per_cu * w, 32);
     if (cost < best_cost) best_cost = cost, best = w;
   }
   return best;
@@ -692,11 +695,17 @@ int launch_norm_team(const void* x, int64_t rows, int64_t K, int64_t ld, const f
 }
 
 // One wave per row up to kWideRow channels; wider rows are shared by the kWideTeam waves of a workgroup
-// (a wave alone would leave a compute unit with two or three rows in flight).
+// (a wave alone would leave a compute unit with two or three rows in flight).  So are the rows of a launch too
+// short to give every unit several of them: a row's chain of loads, passes and gathers is then what takes the time,
+// and four waves walk it four times as fast.  Measured, one wave -> four, us, K = 3072: RMSNorm + NVFP4 256 rows
+// 7.1 -> 5.4, 512 rows 7.2 -> 6.2, 768 rows 7.2 -> 7.0, 1024 rows 7.3 -> 8.0; Hadamard + INT4 256 rows 10.8 -> 5.8, 512
+// rows 10.9 -> 6.5, 768 rows 11.0 -> 7.6, 1024 rows 11.0 (9.5 with fewer rows a workgroup) -> 10.6.  Below 1024
+// channels a row has less than two chunks for each of 256 lanes (512 x 768: 4.7 -> 5.0).
 template <int FMT, int G, int NORM>
 int launch_norm_rows(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts, const OperandLayout& L,
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
-  if (K > kWideRow) return launch_norm_team<FMT, G, NORM, kWideTeam>(x, rows, K, ld, ts, L, operand, na, st);
+  const bool few = rows <= (NORM == kHadamard ? 768 : 512) && K >= 1024;
+  if (K > kWideRow || few) return launch_norm_team<FMT, G, NORM, kWideTeam>(x, rows, K, ld, ts, L, operand, na, st);
   return launch_norm_team<FMT, G, NORM, 1>(x, rows, K, ld, ts, L, operand, na, st);
 }
 

@@ -202,3 +202,25 @@ def test_unsupported_widths_are_refused():
         with pytest.raises(pq.PQError) as e:
             pq.pq_hadamard_reorder(x)
         assert e.value.code == -2
+
+
+@pytest.mark.parametrize("rows,K", [(768, 1024), (769, 1024), (768, 1280), (769, 1280), (768, 1536), (769, 1536),
+                                    (300, 4096), (800, 4096)])
+def test_rows_at_the_edge_of_a_short_launch(rows, K):
+    """Up to 768 rows of 1024 channels and more are shared by four waves, the others walked by one (and spread over
+    the units, a few rows a workgroup): results as the oracle's on both sides, and the quantizing call still equals
+    rotation followed by quantizer."""
+    rng = np.random.default_rng(9950 + rows + K)
+    x_bits = _activations(rng, rows, K)
+    perm = rng.permutation(K).astype(np.int32)
+    perm_d = torch.from_numpy(perm).to(DEV)
+    y = pq.pq_hadamard_reorder(_dev(x_bits), perm_d)
+    torch.cuda.synchronize()
+    _check_close(_host_bits(y), OH.rotate_reordered(OF.bf16_bits_to_f64(x_bits), perm), "hadamard_reorder")
+    for fmt, g in ((pq.FMT_NVFP4, 16), (pq.FMT_INT3, 256)):
+        ts = torch.full((1,), 0.01, dtype=torch.float32, device=DEV)
+        want, got = (torch.zeros(pq.pq_operand_bytes(fmt, g, rows, K), dtype=torch.uint8, device=DEV) for _ in range(2))
+        pq.pq_quantize_act_packed(fmt, g, y, ts, operand=want)
+        pq.pq_hadamard_quantize_act_packed(fmt, g, _dev(x_bits), ts, perm=perm_d, operand=got)
+        torch.cuda.synchronize()
+        assert torch.equal(want, got)

@@ -314,3 +314,27 @@ def test_wide_rows_share_a_workgroup(kind, rows, K, rows_per_mod):
                                                  operand=torch.zeros_like(want), y=y2)
             torch.cuda.synchronize()
             assert torch.equal(y2, y) and torch.equal(got, want), (fmt, g)
+
+
+@pytest.mark.parametrize("kind", [RMS, ADALN])
+@pytest.mark.parametrize("rows,K", [(512, 1024), (513, 1024), (512, 1016), (40, 1024), (513, 3072)])
+def test_rows_at_the_edge_of_a_short_launch(kind, rows, K):
+    """Up to 512 rows of 1024 channels and more are shared by four waves, the others walked by one: results as the
+    oracle's on both sides of the line, and the quantizing call still equals norm followed by quantizer."""
+    rng = np.random.default_rng(9500 + rows + K + kind)
+    x_bits = _activations(rng, rows, K)
+    perm = rng.permutation(K).astype(np.int32)
+    gamma_bits, s_bits, b_bits = (_bits(c + 0.3 * rng.standard_normal((1, K))) for c in (1.0, 0.0, 0.0))
+    args = (1e-6, torch.from_numpy(perm).to(DEV), _dev(gamma_bits[0]), _dev(s_bits), _dev(b_bits), 0)
+    y = pq.pq_norm_reorder(kind, _dev(x_bits), *args)
+    torch.cuda.synchronize()
+    _check_close(_host_bits(y), _oracle(kind, x_bits, perm, gamma_bits[0], s_bits, b_bits, 0, 1e-6), "norm_reorder")
+    if K % 32:
+        return
+    for fmt, g in ((pq.FMT_NVFP4, 16), (pq.FMT_INT4, 256)):
+        ts = torch.full((1,), 0.01, dtype=torch.float32, device=DEV)
+        want, got = (torch.zeros(pq.pq_operand_bytes(fmt, g, rows, K), dtype=torch.uint8, device=DEV) for _ in range(2))
+        pq.pq_quantize_act_packed(fmt, g, y, ts, operand=want)
+        pq.pq_norm_quantize_act_packed(kind, fmt, g, _dev(x_bits), args[0], ts, *args[1:], operand=got)
+        torch.cuda.synchronize()
+        assert torch.equal(want, got)
