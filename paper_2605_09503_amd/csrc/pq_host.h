@@ -59,6 +59,11 @@ int launch_quantize_rows(pq_format fmt, int group, const void* x, int64_t rows, 
                          const int32_t* perm, const float* tensor_scale, uint8_t* codes, void* scales,
                          hipStream_t st);
 
+// the same, gathered, straight into the operand layout; a row of K <= 65536 and its group maxima fit a workgroup's LDS
+constexpr size_t kPanelRowLds = 65536 * 2 + 65536 / 32 * 4;
+int launch_quantize_rows_panel(pq_format fmt, int group, const void* x, int64_t rows, int64_t K, const int32_t* perm,
+                               const float* ts, void* operand, hipStream_t st);
+
 // The error evaluation keeps one row as fp32 in LDS, one spare slot per eight channels: 4.5 K bytes of the
 // 150 KB a workgroup may take.
 constexpr int64_t kSelectMaxK = 34128;      // largest multiple of 16 with 4.5 K <= 150 * 1024

@@ -39,9 +39,9 @@ namespace pq {
 // Every MFMA is followed by its share of vector-ALU and LDS work in program order, pinned
 // with scheduling barriers, so that the matrix pipe and the vector ALU overlap inside a wave
 // instead of alternating in phases.
-template <int FMT, int G, int BM, int BN, int WGM, int WGN, bool OUT_F32>
+template <int FMT, int G, int BM, int BN, int WGM, int WGN, int OUT>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, OperandView W, int M, int N,
-                                                              int K, void* __restrict__ y, int64_t ldy,
+                                                              int K, Output out,
                                                               int tiles_m, int tiles_n) {
   const float* __restrict__ a_mul = A.mul;
   const float* __restrict__ w_mul = W.mul;
@@ -260,8 +260,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
     }
   }
 
-  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, 2 * STAGE_BYTES, OUT_F32>(
-      acc, smem, a_mul, a_mul_stride, w_mul, w_mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f, y, ldy);
+  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, 2 * STAGE_BYTES, OUT>(
+      acc, smem, a_mul, a_mul_stride, w_mul, w_mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f,
+      tile_m * tiles_n + tile_n, out);
 }
 
 // ------------------------------------------------------------------------ INT scale prepass
@@ -385,18 +386,18 @@ size_t qgemm_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int
   return carve_gemm(nullptr, fmt, group, M, N, K, nullptr);
 }
 
-template <int FMT, int G, int BM, int BN, int WGM, int WGN, bool OUT_F32>
-static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N, int K, void* y, int64_t ldy,
+template <int FMT, int G, int BM, int BN, int WGM, int WGN, int OUT>
+static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out,
                        hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
   constexpr size_t shmem = 2 * (size_t)((BM * 2 + T - 1) / T * (T / 2) + BN) * kRowBytes;
-  auto kern = qgemm_kernel<FMT, G, BM, BN, WGM, WGN, OUT_F32>;
+  auto kern = qgemm_kernel<FMT, G, BM, BN, WGM, WGN, OUT>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_kernel)")) return rc;
   int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, y, ldy, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, out, tiles_m, tiles_n);
   return check_hip(hipGetLastError(), "qgemm_kernel");
 }
 
@@ -455,33 +456,39 @@ static int choose_tile(pq_format fmt, int group, int M, int N, int K) {
   return best;
 }
 
-template <int FMT, int G, bool OUT_F32>
-static int pick_tile(const OperandView& A, const OperandView& W, int M, int N, int K, void* y, int64_t ldy,
+template <int FMT, int G, int OUT>
+static int pick_tile(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out,
                      int choice, hipStream_t st) {
   if constexpr (G <= 32) {                             // larger groups: pq_qgemm_group.hip
-    if (choice == kTile256) return launch_gemm<FMT, G, 256, 256, 2, 4, OUT_F32>(A, W, M, N, K, y, ldy, st);
-    if (choice == kTile224) return launch_gemm<FMT, G, 224, 256, 2, 4, OUT_F32>(A, W, M, N, K, y, ldy, st);
+    if (choice == kTile256) return launch_gemm<FMT, G, 256, 256, 2, 4, OUT>(A, W, M, N, K, out, st);
+    if (choice == kTile224) return launch_gemm<FMT, G, 224, 256, 2, 4, OUT>(A, W, M, N, K, out, st);
   }
-  return launch_gemm<FMT, G, 128, 128, 2, 2, OUT_F32>(A, W, M, N, K, y, ldy, st);
+  return launch_gemm<FMT, G, 128, 128, 2, 2, OUT>(A, W, M, N, K, out, st);
 }
 
 template <int FMT, int G>
-static int launch_views_fg(const OperandView& A, const OperandView& W, int M, int N, int K, void* y,
-                           int64_t ldy, bool out_f32, int tile, hipStream_t st) {
-  if (out_f32) return pick_tile<FMT, G, true>(A, W, M, N, K, y, ldy, tile, st);
-  return pick_tile<FMT, G, false>(A, W, M, N, K, y, ldy, tile, st);
+static int launch_views_fg(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out, int tile,
+                           hipStream_t st) {
+  if (out.kind == kOutF32) return pick_tile<FMT, G, kOutF32>(A, W, M, N, K, out, tile, st);
+  if (out.kind == kOutDiff) return pick_tile<FMT, G, kOutDiff>(A, W, M, N, K, out, tile, st);
+  return pick_tile<FMT, G, kOutBf16>(A, W, M, N, K, out, tile, st);
+}
+
+int64_t qgemm_tiles(pq_format fmt, int group, int64_t M, int64_t N, int64_t K) {
+  const TileSize& z = kTileSize[choose_tile(fmt, group, (int)M, (int)N, (int)K)];
+  return ((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn);
 }
 
 // the product kernel on two operand views (any mix of layouts)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
-                       int64_t N, int64_t K, void* y, int64_t ldy, bool out_f32, hipStream_t st) {
+                       int64_t N, int64_t K, const Output& out, hipStream_t st) {
   const int tile = choose_tile(fmt, group, (int)M, (int)N, (int)K);
   if (tile >= kTileSplit32)
-    return launch_qgemm_split(fmt, group, A, W, (int)M, (int)N, (int)K, y, ldy, out_f32, tile, st);
+    return launch_qgemm_split(fmt, group, A, W, (int)M, (int)N, (int)K, out, tile, st);
   // groups of 64 and more in large tiles: the codes go to the matrix unit as they are
   if (fmt != PQ_FMT_NVFP4 && group != 32 && tile != kTile128)
-    return launch_qgemm_group(fmt, group, A, W, (int)M, (int)N, (int)K, y, ldy, out_f32, tile, st);
-#define PQ_ARGS A, W, (int)M, (int)N, (int)K, y, ldy, out_f32, tile, st
+    return launch_qgemm_group(fmt, group, A, W, (int)M, (int)N, (int)K, out, tile, st);
+#define PQ_ARGS A, W, (int)M, (int)N, (int)K, out, tile, st
   if (fmt == PQ_FMT_NVFP4) return launch_views_fg<kNvfp4, 16>(PQ_ARGS);
   if (fmt == PQ_FMT_INT4 || fmt == PQ_FMT_INT3) {      // the nibbles of both unpack alike
     switch (group) {
@@ -532,7 +539,7 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     A.mul_stride = W.mul_stride = 1;
   }
   if (!(phases & 2)) return PQ_OK;
-  return launch_qgemm_views(fmt, group, A, W, M, N, K, y, ldy, out_f32, st);
+  return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}, st);
 }
 
 }  // namespace pq

@@ -173,15 +173,43 @@ __device__ __forceinline__ void assign_tile(int tiles_m, int tiles_n, int& tile_
 }
 
 // ------------------------------------------------------------------------ epilogue
+// What becomes of the product: rounded to bf16, stored in fp32, or compared with a reference -- then only the sum of
+// (ref - product)^2 over a workgroup's tile is kept, in fp64 (each difference exact, the sum in a fixed order):
+// y[tile] = or += that sum.
+enum OutKind : int { kOutBf16 = 0, kOutF32 = 1, kOutDiff = 2 };
+struct Output {
+  int kind;
+  void* y;              // bf16 or float [M, ldy]; kOutDiff: double [tiles]
+  int64_t ldy;          // kOutDiff: of ref
+  const float* ref;     // kOutDiff only
+  bool add;             // kOutDiff only
+};
+
+// the sums of a workgroup's threads, in a fixed order, to y[tile] (called by all threads; red: free LDS)
+__device__ __forceinline__ void store_diff(double d2, double* red, int threads, int tile, const Output& out) {
+  d2 = wave_sum(d2);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = d2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < threads / 64; ++w) t += red[w];
+    double* p = reinterpret_cast<double*>(out.y) + tile;
+    *p = out.add ? *p + t : t;
+  }
+}
+
 // The accumulators of a workgroup's output tile, scaled and stored.  unit: a power of two that undoes the
 // operands' fixed code scale (1 where they have none; the product with it is exact).
-template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, bool OUT_F32>
+template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT>
 __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsigned char* smem,
                                            const float* __restrict__ a_mul, int a_mul_stride,
                                            const float* __restrict__ w_mul, int w_mul_stride,
                                            const uint16_t* __restrict__ bias, int M, int N, int m0, int n0,
-                                           int wave_m, int wave_n, int tm_cnt, int tid, float unit,
-                                           void* __restrict__ y, int64_t ldy) {
+                                           int wave_m, int wave_n, int tm_cnt, int tid, float unit, int tile,
+                                           const Output& out) {
+  void* __restrict__ y = out.y;
+  const int64_t ldy = out.ldy;
+  double d2 = 0.0;
   const int lane = tid & 63;
   const int frag_row = lane & 31, frag_half = lane >> 5;
   // A lane holds, per MFMA tile, column m = lane % 32 and rows
@@ -189,7 +217,7 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
   // operand stages are free after the last barrier) so that global stores are 16 bytes per
   // lane and contiguous along n; the fp32 variant (a checking aid) stores directly.
   constexpr int C_ROW_BYTES = BN * 2 + 16;
-  static_assert(OUT_F32 || BM * C_ROW_BYTES <= SMEM_BYTES, "output tile fits in the operand stages");
+  static_assert(OUT != kOutBf16 || BM * C_ROW_BYTES <= SMEM_BYTES, "output tile fits in the operand stages");
   // The column factors (and the optional bias of the linear layer, y = x W^T + b) do not depend on
   // the row block: loaded once (16 per MFMA tile column).
   float wm[TN][16], wb[TN][16];
@@ -222,7 +250,18 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] += wb[i][q * 4 + e];
         }
-        if constexpr (OUT_F32) {
+        if constexpr (OUT == kOutDiff) {
+          if (m < M) {
+            const float* r = out.ref + (int64_t)m * ldy + n;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              if (n + e < N) {
+                const double d = (double)r[e] - (double)v[e];
+                d2 = fma(d, d, d2);
+              }
+            }
+          }
+        } else if constexpr (OUT == kOutF32) {
           if (m < M && n < N) {
             float* yo = reinterpret_cast<float*>(y) + (int64_t)m * ldy + n;
             if (n + 3 < N) {
@@ -238,7 +277,8 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
       }
     }
   }
-  if constexpr (!OUT_F32) {
+  if constexpr (OUT == kOutDiff) store_diff(d2, reinterpret_cast<double*>(smem), T, tile, out);
+  if constexpr (OUT == kOutBf16) {
     __syncthreads();
     constexpr int CHUNKS_PER_ROW = BN / 8;               // 16-byte chunks of 8 bf16
     uint16_t* yb = reinterpret_cast<uint16_t*>(y);
@@ -286,14 +326,20 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
 
 // the product kernel on two operand views (pq_qgemm.hip)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
-                       int64_t N, int64_t K, void* y, int64_t ldy, bool out_f32, hipStream_t st);
+                       int64_t N, int64_t K, const Output& out, hipStream_t st);
+// tiles (= workgroups) of that launch
+int64_t qgemm_tiles(pq_format fmt, int group, int64_t M, int64_t N, int64_t K);
+// the product of two packed operands
+int run_qgemm_packed_out(pq_format fmt, int group, const void* a_operand, const float* a_ts, const void* w_operand,
+                         const float* w_ts, int64_t M, int64_t N, int64_t K, const void* bias, const Output& out,
+                         hipStream_t st);
 // output tiles of the product kernels (choose_tile in pq_qgemm.hip)
 enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kTileSplit64x32 = 5, kTileSplit64 = 6, kTileSplit64x96 = 7 };
 // small outputs (pq_qgemm_split.hip)
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       void* y, int64_t ldy, bool out_f32, int tile, hipStream_t st);
+                       const Output& out, int tile, hipStream_t st);
 // the integer formats' large outputs with groups of 64 and more (pq_qgemm_group.hip)
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       void* y, int64_t ldy, bool out_f32, int tile, hipStream_t st);
+                       const Output& out, int tile, hipStream_t st);
 
 }  // namespace pq

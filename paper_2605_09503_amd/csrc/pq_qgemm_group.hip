@@ -40,10 +40,10 @@
 namespace pq {
 
 // FP4: E2M1 codes (INT3), else E4M3 (INT4).  Groups are a multiple of 64 (2^g_shift).
-template <bool FP4, int BM, int BN, int WGM, int WGN, bool OUT_F32>
+template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView A, OperandView W, int M, int N,
-                                                                    int K, int g_shift, void* __restrict__ y,
-                                                                    int64_t ldy, int tiles_m, int tiles_n) {
+                                                                    int K, int g_shift, Output out, int tiles_m,
+                                                                    int tiles_n) {
   constexpr int T = WGM * WGN * 64;
   constexpr int WTM = (BM + WGM * 32 - 1) / (WGM * 32) * 32, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   constexpr int NP = RB / 32;                          // 16-byte pieces of a 32-code slice
   constexpr int A_CODES = 0, W_CODES = A_ROWS * RB, A_SC = W_CODES + BN * RB, W_SC = A_SC + A_ROWS * 2;
   constexpr int STAGE_BYTES = W_SC + BN * 2, STAGES = 4;
-  constexpr int OUT_BYTES = OUT_F32 ? 0 : BM * (BN * 2 + 16);
+  constexpr int OUT_BYTES = OUT != kOutBf16 ? 0 : BM * (BN * 2 + 16);
   constexpr int SMEM_BYTES = STAGES * STAGE_BYTES > OUT_BYTES ? STAGES * STAGE_BYTES : OUT_BYTES;
   constexpr int FMT_SEL = FP4 ? 4 : 0;                 // operand format field of the matrix instruction
 
@@ -305,44 +305,50 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   }
 
   __syncthreads();                                     // the output tile reuses the stages
-  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT_F32>(
+  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT>(
       acc, smem, A.mul, A.mul_stride, W.mul, W.mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid,
-      FP4 ? 4.0f : 262144.0f, y, ldy);
+      FP4 ? 4.0f : 262144.0f, tile_m * tiles_n + tile_n, out);
 }
 
-template <bool FP4, int BM, int BN, int WGM, int WGN, bool OUT_F32>
-static int launch_group(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
-                        int64_t ldy, hipStream_t st) {
+template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT>
+static int launch_group(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+                        hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
   constexpr int A_ROWS = (BM * 2 + T - 1) / T * (T / 2);
   constexpr size_t stages = 4 * (size_t)(A_ROWS + BN) * ((FP4 ? 32 : 64) + 2);
-  constexpr size_t out = OUT_F32 ? 0 : (size_t)BM * (BN * 2 + 16);
-  constexpr size_t shmem = stages > out ? stages : out;
-  auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT_F32>;
+  constexpr size_t tile_bytes = OUT != kOutBf16 ? 0 : (size_t)BM * (BN * 2 + 16);
+  constexpr size_t shmem = stages > tile_bytes ? stages : tile_bytes;
+  auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_group_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, g_shift, y, ldy, tiles_m,
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
                      tiles_n);
   return check_hip(hipGetLastError(), "qgemm_group_kernel");
 }
 
-template <bool FP4, bool OUT_F32>
-static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
-                      int64_t ldy, int choice, hipStream_t st) {
-  if (choice == kTile256) return launch_group<FP4, 256, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
-  return launch_group<FP4, 224, 256, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+template <bool FP4, int OUT>
+static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+                      int choice, hipStream_t st) {
+  if (choice == kTile256) return launch_group<FP4, 256, 256, 2, 4, OUT>(A, W, M, N, K, g_shift, out, st);
+  return launch_group<FP4, 224, 256, 2, 4, OUT>(A, W, M, N, K, g_shift, out, st);
 }
 
 // INT4 and INT3 with groups of 64, 128 or 256, large tiles
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       void* y, int64_t ldy, bool out_f32, int choice, hipStream_t st) {
+                       const Output& out, int choice, hipStream_t st) {
   const int g_shift = group == 64 ? 6 : group == 128 ? 7 : 8;
-#define PQ_ARGS A, W, M, N, K, g_shift, y, ldy, choice, st
-  if (fmt == PQ_FMT_INT4) return out_f32 ? group_tile<false, true>(PQ_ARGS) : group_tile<false, false>(PQ_ARGS);
-  return out_f32 ? group_tile<true, true>(PQ_ARGS) : group_tile<true, false>(PQ_ARGS);
+#define PQ_ARGS (A, W, M, N, K, g_shift, out, choice, st)
+  if (fmt == PQ_FMT_INT4) {
+    if (out.kind == kOutF32) return group_tile<false, kOutF32> PQ_ARGS;
+    if (out.kind == kOutDiff) return group_tile<false, kOutDiff> PQ_ARGS;
+    return group_tile<false, kOutBf16> PQ_ARGS;
+  }
+  if (out.kind == kOutF32) return group_tile<true, kOutF32> PQ_ARGS;
+  if (out.kind == kOutDiff) return group_tile<true, kOutDiff> PQ_ARGS;
+  return group_tile<true, kOutBf16> PQ_ARGS;
 #undef PQ_ARGS
 }
 

@@ -27,10 +27,10 @@ namespace pq {
 // the scales outside (pq_qgemm_group.hip)
 enum SplitMode : int { kSplitNvfp4 = 0, kSplitInt = 1, kSplitE2m1 = 2 };
 
-template <int MODE, int TM, int TN, int KS, bool OUT_F32>
+template <int MODE, int TM, int TN, int KS, int OUT>
 __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, OperandView W, int M, int N,
-                                                                      int K, int g_shift, void* __restrict__ y,
-                                                                      int64_t ldy, int tiles_m, int tiles_n) {
+                                                                      int K, int g_shift, Output out, int tiles_m,
+                                                                      int tiles_n) {
   constexpr int T = KS * 64;
   constexpr int BM = TM * 32, BN = TN * 32;
   constexpr bool CODES = MODE == kSplitE2m1;
@@ -176,6 +176,9 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
 
   // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
   const uint16_t* __restrict__ bias = W.bias;
+  void* __restrict__ y = out.y;
+  const int64_t ldy = out.ldy;
+  double d2 = 0.0;
   constexpr int CHUNKS = 4;                            // eight columns each
   constexpr float unit = CODES ? 4.0f : 1.0f;          // undoes the E2M1 codes' factor 1/2 on either side
 #pragma unroll
@@ -210,7 +213,16 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
         v[e] = (v[e] * unit) * (am * W.mul[(int64_t)nn * W.mul_stride]);
         if (bias) v[e] += bf16_to_f32(bias[nn]);
       }
-      if constexpr (OUT_F32) {
+      if constexpr (OUT == kOutDiff) {
+        const float* r = out.ref + (int64_t)m * ldy + n;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (n + e < N) {
+            const double d = (double)r[e] - (double)v[e];
+            d2 = fma(d, d, d2);
+          }
+        }
+      } else if constexpr (OUT == kOutF32) {
         float* yo = reinterpret_cast<float*>(y) + (int64_t)m * ldy + n;
         if (n + 7 < N) {
           *reinterpret_cast<float4*>(yo) = make_float4(v[0], v[1], v[2], v[3]);
@@ -234,45 +246,51 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
         }
       }
     }
+  }  if constexpr (OUT == kOutDiff) {
+    __syncthreads();                                   // the partial sums have been read
+    store_diff(d2, reinterpret_cast<double*>(part), T, tile_m * tiles_n + tile_n, out);
   }
 }
 
-template <int MODE, int TM, int TN, int KS, bool OUT_F32>
-static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
-                        int64_t ldy, hipStream_t st) {
+template <int MODE, int TM, int TN, int KS, int OUT>
+static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+                        hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
   constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4;
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
-  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT_F32>;
+  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_split_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, y,
-                     ldy, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
+                     tiles_n);
   return check_hip(hipGetLastError(), "qgemm_split_kernel");
 }
 
-template <int MODE, bool OUT_F32>
-static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, void* y,
-                      int64_t ldy, int tile, hipStream_t st) {
+template <int MODE, int OUT>
+static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+                      int tile, hipStream_t st) {
   switch (tile) {
-    case kTileSplit32: return launch_split<MODE, 1, 1, 8, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
-    case kTileSplit64x32: return launch_split<MODE, 2, 1, 8, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
-    case kTileSplit64: return launch_split<MODE, 2, 2, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
-    default: return launch_split<MODE, 2, 3, 4, OUT_F32>(A, W, M, N, K, g_shift, y, ldy, st);
+    case kTileSplit32: return launch_split<MODE, 1, 1, 8, OUT>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64x32: return launch_split<MODE, 2, 1, 8, OUT>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64: return launch_split<MODE, 2, 2, 4, OUT>(A, W, M, N, K, g_shift, out, st);
+    default: return launch_split<MODE, 2, 3, 4, OUT>(A, W, M, N, K, g_shift, out, st);
   }
 }
 
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       void* y, int64_t ldy, bool out_f32, int tile, hipStream_t st) {
+                       const Output& out, int tile, hipStream_t st) {
   const int g_shift = fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
-#define PQ_ARGS A, W, M, N, K, g_shift, y, ldy, tile, st
-  if (fmt == PQ_FMT_NVFP4) return out_f32 ? split_tile<kSplitNvfp4, true>(PQ_ARGS) : split_tile<kSplitNvfp4, false>(PQ_ARGS);
-  if (fmt == PQ_FMT_INT3 && group != 32) return out_f32 ? split_tile<kSplitE2m1, true>(PQ_ARGS) : split_tile<kSplitE2m1, false>(PQ_ARGS);
-  return out_f32 ? split_tile<kSplitInt, true>(PQ_ARGS) : split_tile<kSplitInt, false>(PQ_ARGS);
-#undef PQ_ARGS
+#define PQ_SPLIT(MODE)                                                                                   \
+  return out.kind == kOutF32    ? split_tile<MODE, kOutF32>(A, W, M, N, K, g_shift, out, tile, st)        \
+         : out.kind == kOutDiff ? split_tile<MODE, kOutDiff>(A, W, M, N, K, g_shift, out, tile, st)       \
+                                : split_tile<MODE, kOutBf16>(A, W, M, N, K, g_shift, out, tile, st)
+  if (fmt == PQ_FMT_NVFP4) PQ_SPLIT(kSplitNvfp4);
+  if (fmt == PQ_FMT_INT3 && group != 32) PQ_SPLIT(kSplitE2m1);
+  PQ_SPLIT(kSplitInt);
+#undef PQ_SPLIT
 }
 
 }  // namespace pq

@@ -2,10 +2,11 @@
 // of "the candidate with the smallest quantization error on the calibration data" (paper Sec. 3.3):
 //     E_out(pi) = sum_b ||X_b W^T - Q(X_b P) Q(P^T W)^T||^2 / sum_b ||X_b W^T||^2        (Eq. 8)
 // The candidate orders are those of pq_select_perm (joint score, Eq. 9, alpha grid).  The quantized
-// product runs through the forward path itself (gathering quantizer -> operand layout -> product
-// kernel with an fp32 result); the unquantized product comes from a plain bf16 MFMA kernel below.
-// Offline work: per candidate and batch four launches; nothing here is tuned beyond being correct
-// and deterministic (fixed summation order).
+// product runs through the forward path (gathering quantizer straight into the operand layout, product kernel whose
+// epilogue keeps the squared difference to the unquantized product instead of a result); the unquantized product
+// comes from a plain bf16 MFMA kernel below, which also sums its squares.  Every sum has a fixed order.
+// Per candidate and batch two launches and one quantizer for the weights; with an fp32 result, a packing pass and
+// three reduction launches of their own there were five, and 1024 x 3072 x 3072 with two batches of INT4 took 955 us.
 #include <string.h>
 
 #include "pq_qgemm_common.h"
@@ -17,28 +18,50 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kRefTile = 128;                 // output tile edge
-constexpr int kRefStep = 32;                  // K elements per step
-constexpr int kRefRowBytes = kRefStep * 2 + 16;   // padded LDS row: 80 bytes
+constexpr int kRefStep = 64;                  // K elements per step
+constexpr int kRefRowBytes = kRefStep * 2 + 16;   // padded LDS row, as in pq_qgemm.hip
+constexpr int kRefStage = 2 * kRefTile * kRefRowBytes;
 
-// Y[m, n] = sum_k X[m, k] W[n, k], bf16 inputs, fp32 accumulation (v_mfma_f32_32x32x16_bf16),
-// fp32 output.  128 x 128 tile, four waves of 64 x 64; K % 32 == 0.
+// Y[m, n] = sum_k X[m, k] W[n, k], bf16 inputs, fp32 accumulation (v_mfma_f32_32x32x16_bf16), fp32 output, and the
+// tile's sum of squares (+)= to sq.  128 x 128 tile, four waves of 64 x 64; K % 32 == 0.  A step's pieces are
+// loaded while the one before it is multiplied and stored into the other of two stages: one barrier a step (one
+// stage with two barriers and half the step: 61 us at 1024 x 3072 x 3072).
 __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
-                                                       int M, int N, int K, float* __restrict__ y, int64_t ldy) {
-  __shared__ __align__(16) unsigned char lds[2 * kRefTile * kRefRowBytes];
-  unsigned char* a_t = lds;
-  unsigned char* w_t = lds + kRefTile * kRefRowBytes;
+                                                       int M, int N, int K, float* __restrict__ y, int64_t ldy,
+                                                       double* __restrict__ sq, int add) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_m = wave & 1, wave_n = wave >> 1;
   const int m0 = blockIdx.x * kRefTile, n0 = blockIdx.y * kRefTile;
-  // loader: 128 rows x 64 bytes per operand = 512 pieces of 16 bytes; thread t takes pieces t, t + 256
-  const int ld_row = tid >> 2, ld_piece = tid & 3;
-  const uint16_t* xa = x + (int64_t)min(m0 + ld_row, M - 1) * K + ld_piece * 8;
-  const uint16_t* xb = x + (int64_t)min(m0 + ld_row + 64, M - 1) * K + ld_piece * 8;
-  const uint16_t* wa = w + (int64_t)min(n0 + ld_row, N - 1) * K + ld_piece * 8;
-  const uint16_t* wb2 = w + (int64_t)min(n0 + ld_row + 64, N - 1) * K + ld_piece * 8;
-  const int st_a = ld_row * kRefRowBytes + ld_piece * 16;
-  const int st_b = (ld_row + 64) * kRefRowBytes + ld_piece * 16;
+  // loader: 128 rows x 128 bytes per operand; thread t takes piece t % 8 of rows t / 8 + 32 i
+  const int ld_row = tid >> 3, ld_piece = tid & 7;
+  const uint16_t *xr[4], *wr[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    xr[i] = x + (int64_t)min(m0 + ld_row + 32 * i, M - 1) * K + ld_piece * 8;
+    wr[i] = w + (int64_t)min(n0 + ld_row + 32 * i, N - 1) * K + ld_piece * 8;
+  }
+  const int st = ld_row * kRefRowBytes + ld_piece * 16;
   const int frag_row = lane & 31, frag_half = lane >> 5;
+  uint4 ra[4], rw[4];
+  auto load = [&](int k0) {
+    const bool ok = k0 + ld_piece * 8 < K;               // the upper half of a last step of 32 is zero
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ra[i] = rw[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (ok) {
+        ra[i] = *reinterpret_cast<const uint4*>(xr[i] + k0);
+        rw[i] = *reinterpret_cast<const uint4*>(wr[i] + k0);
+      }
+    }
+  };
+  auto put = [&](unsigned char* stage) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      *reinterpret_cast<uint4*>(stage + st + 32 * i * kRefRowBytes) = ra[i];
+      *reinterpret_cast<uint4*>(stage + kRefTile * kRefRowBytes + st + 32 * i * kRefRowBytes) = rw[i];
+    }
+  };
 
   float16_t acc[2][2];
 #pragma unroll
@@ -48,22 +71,17 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restric
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  uint4 ra = *reinterpret_cast<const uint4*>(xa), rb = *reinterpret_cast<const uint4*>(xb);
-  uint4 rc = *reinterpret_cast<const uint4*>(wa), rd = *reinterpret_cast<const uint4*>(wb2);
+  load(0);
+  put(lds);
+  __syncthreads();
+  int cur = 0;
   for (int k0 = 0; k0 < K; k0 += kRefStep) {
-    *reinterpret_cast<uint4*>(a_t + st_a) = ra;
-    *reinterpret_cast<uint4*>(a_t + st_b) = rb;
-    *reinterpret_cast<uint4*>(w_t + st_a) = rc;
-    *reinterpret_cast<uint4*>(w_t + st_b) = rd;
-    __syncthreads();
-    if (k0 + kRefStep < K) {                       // next step's pieces while this one is multiplied
-      ra = *reinterpret_cast<const uint4*>(xa + k0 + kRefStep);
-      rb = *reinterpret_cast<const uint4*>(xb + k0 + kRefStep);
-      rc = *reinterpret_cast<const uint4*>(wa + k0 + kRefStep);
-      rd = *reinterpret_cast<const uint4*>(wb2 + k0 + kRefStep);
-    }
+    const bool more = k0 + kRefStep < K;                 // uniform
+    if (more) load(k0 + kRefStep);
+    const unsigned char* a_t = lds + cur;
+    const unsigned char* w_t = a_t + kRefTile * kRefRowBytes;
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
+    for (int kk = 0; kk < 4; ++kk) {
       bf16x8_t xf[2], wf[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -79,9 +97,12 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restric
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i], xf[j], acc[i][j], 0, 0, 0);
     }
+    cur = kRefStage - cur;
+    if (more) put(lds + cur);
     __syncthreads();
   }
   // lane holds, per 32 x 32 block, column m = lane % 32 and rows n = 8 (r / 4) + 4 (lane / 32) + r % 4
+  double s2 = 0.0;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int m = m0 + wave_m * 64 + j * 32 + frag_row;
@@ -91,62 +112,41 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restric
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int n = n0 + wave_n * 64 + i * 32 + q * 8 + frag_half * 4;
+        float* yo = y + (int64_t)m * ldy + n;
+        const float v[4] = {acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+        if (n + 3 < N) *reinterpret_cast<float4*>(yo) = make_float4(v[0], v[1], v[2], v[3]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < N) y[(int64_t)m * ldy + n + e] = acc[i][j][q * 4 + e];
+        for (int e = 0; e < 4; ++e) {
+          if (n + e < N) {
+            if (n + 3 >= N) yo[e] = v[e];
+            s2 = fma((double)v[e], (double)v[e], s2);
+          }
+        }
       }
   }
+  store_diff(s2, reinterpret_cast<double*>(lds), 256, blockIdx.y * gridDim.x + blockIdx.x,
+             Output{kOutDiff, sq, 0, nullptr, add != 0});
 }
 
-constexpr int kDiffBlocks = 1024;
-
-// partial[b] = sum over the block's share of (ref - hat)^2, partial[kDiffBlocks + b] of ref^2 (fp64)
-__global__ __launch_bounds__(256) void sqdiff_partial_kernel(const float* __restrict__ ref, const float* __restrict__ hat,
-                                                             int64_t rows, int N, int64_t ld, double* __restrict__ partial) {
-  __shared__ double red[2][4];
-  double d2 = 0.0, r2 = 0.0;
-  const int64_t total = rows * N;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t r = i / N;
-    const int64_t at = r * ld + (i - r * N);
-    const double a = (double)ref[at], b = (double)hat[at];
-    d2 += (a - b) * (a - b);
-    r2 += a * a;
-  }
-  d2 = wave_sum(d2);
-  r2 = wave_sum(r2);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[0][wave] = d2;
-    red[1][wave] = r2;
-  }
+// sums[c] = sum of the tiles of candidate c (c < n_cand), sums[den_at] = sum of the reference's tiles; fixed order
+__global__ __launch_bounds__(256) void tile_sums_kernel(const double* __restrict__ num, int64_t num_stride, int64_t tiles,
+                                                        const double* __restrict__ den, int64_t den_tiles, int n_cand,
+                                                        int den_at, double* __restrict__ sums) {
+  __shared__ double red[4];
+  const bool is_den = (int)blockIdx.x == n_cand;
+  const double* p = is_den ? den : num + (int64_t)blockIdx.x * num_stride;
+  const int64_t n = is_den ? den_tiles : tiles;
+  double s = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += 256) s += p[i];
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    partial[blockIdx.x] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    partial[kDiffBlocks + blockIdx.x] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-  }
+  if (threadIdx.x == 0) sums[is_den ? den_at : (int)blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// sums[0] += sum of the first kDiffBlocks partials, sums[1] += sum of the second (one wave, fixed order)
-__global__ __launch_bounds__(64) void sqdiff_finish_kernel(const double* __restrict__ partial, double* __restrict__ num,
-                                                           double* __restrict__ den) {
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < kDiffBlocks; i += 64) {
-    a += partial[i];
-    b += partial[kDiffBlocks + i];
-  }
-  a = wave_sum(a);
-  b = wave_sum(b);
-  if (threadIdx.x == 0) {
-    *num += a;
-    if (den) *den += b;
-  }
-}
-
-// moved[j] = number of positions where candidate j differs from the identity; block 0 also clears the
-// n_sums running sums (which do not overlap moved[])
-__global__ __launch_bounds__(256) void moved_kernel(const int32_t* __restrict__ cands, int K, double* __restrict__ sums,
-                                                    int n_sums, double* __restrict__ moved) {
+// moved[j] = number of positions where candidate j differs from the identity
+__global__ __launch_bounds__(256) void moved_kernel(const int32_t* __restrict__ cands, int K,
+                                                    double* __restrict__ moved) {
   const int j = blockIdx.x;
   int c = 0;
   for (int i = threadIdx.x; i < K; i += 256) c += cands[(int64_t)j * K + i] != i;
@@ -158,8 +158,6 @@ __global__ __launch_bounds__(256) void moved_kernel(const int32_t* __restrict__ 
     __syncthreads();
   }
   if (threadIdx.x == 0) moved[j] = (double)red[0];
-  if (j == 0)
-    for (int i = threadIdx.x; i < n_sums; i += 256) sums[i] = 0.0;
 }
 
 struct OutWs {
@@ -167,22 +165,20 @@ struct OutWs {
   int32_t* cands;
   int32_t* rank;
   float* y_ref;        // [n_batches][M][ldn]
-  float* y_hat;        // [M][ldn]
-  uint8_t* x_codes;
-  void* x_scales;
-  uint8_t* w_codes;
-  void* w_scales;
   uint8_t* x_op;
   uint8_t* w_op;
   float* ts;           // [2] activation and weight tensor scale
-  double* partial;     // [2 * kDiffBlocks]
+  double* num;         // [kMaxCandOut][tiles of the product, at most out_tiles(M, N)]
+  double* den;         // [tiles of the reference product]
   double* sums;        // [kMaxCandOut] numerators, [1] denominator, [PQ_MAX_ALPHAS] moved counts
 };
 constexpr int kMaxCandOut = PQ_MAX_ALPHAS + 1;
 constexpr int kNumSums = kMaxCandOut + 1 + PQ_MAX_ALPHAS;
 
-size_t scale_bytes(pq_format fmt, int group, int64_t rows, int64_t K) {
-  return fmt == PQ_FMT_NVFP4 ? (size_t)rows * (K / 16) : (size_t)rows * (K / group) * 4;
+// tiles of the smallest size any product kernel takes
+size_t out_tiles(int64_t M, int64_t N) { return (size_t)((M + 31) / 32) * ((N + 31) / 32); }
+size_t ref_tiles(int64_t M, int64_t N) {
+  return (size_t)((M + kRefTile - 1) / kRefTile) * ((N + kRefTile - 1) / kRefTile);
 }
 
 size_t carve_out(void* base, pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, OutWs* w) {
@@ -197,15 +193,11 @@ size_t carve_out(void* base, pq_format fmt, int group, int64_t M, int64_t N, int
   const size_t o_cands = take((size_t)PQ_MAX_ALPHAS * K * 4);
   const size_t o_rank = take((size_t)PQ_MAX_ALPHAS * K * 4);
   const size_t o_ref = take((size_t)n_batches * M * ldn * 4);
-  const size_t o_hat = take((size_t)M * ldn * 4);
-  const size_t o_xc = take((size_t)M * K / 2);
-  const size_t o_xs = take(scale_bytes(fmt, group, M, K));
-  const size_t o_wc = take((size_t)N * K / 2);
-  const size_t o_wsc = take(scale_bytes(fmt, group, N, K));
   const size_t o_xop = take(operand_bytes(fmt, group, M, K));
   const size_t o_wop = take(operand_bytes(fmt, group, N, K));
   const size_t o_ts = take(2 * sizeof(float));
-  const size_t o_part = take((size_t)2 * kDiffBlocks * 8);
+  const size_t o_num = take(kMaxCandOut * out_tiles(M, N) * 8);
+  const size_t o_den = take(ref_tiles(M, N) * 8);
   const size_t o_sums = take((size_t)kNumSums * 8);
   if (w) {
     char* b = (char*)base;
@@ -213,15 +205,11 @@ size_t carve_out(void* base, pq_format fmt, int group, int64_t M, int64_t N, int
     w->cands = (int32_t*)(b + o_cands);
     w->rank = (int32_t*)(b + o_rank);
     w->y_ref = (float*)(b + o_ref);
-    w->y_hat = (float*)(b + o_hat);
-    w->x_codes = (uint8_t*)(b + o_xc);
-    w->x_scales = b + o_xs;
-    w->w_codes = (uint8_t*)(b + o_wc);
-    w->w_scales = b + o_wsc;
     w->x_op = (uint8_t*)(b + o_xop);
     w->w_op = (uint8_t*)(b + o_wop);
     w->ts = (float*)(b + o_ts);
-    w->partial = (double*)(b + o_part);
+    w->num = (double*)(b + o_num);
+    w->den = (double*)(b + o_den);
     w->sums = (double*)(b + o_sums);
   }
   return off;
@@ -243,37 +231,37 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
   const int n_cand = n_alpha + 1;              // candidate 0 is the original order
   int rc;
   if ((rc = launch_candidate_orders(act_sumsq, w_sumsq, K, alphas, n_alpha, W.keys, W.rank, W.cands, st))) return rc;
-  hipLaunchKernelGGL(moved_kernel, dim3(n_alpha), dim3(256), 0, st, W.cands, (int)K, W.sums, kMaxCandOut + 1,
-                     W.sums + kMaxCandOut + 1);
+  hipLaunchKernelGGL(moved_kernel, dim3(n_alpha), dim3(256), 0, st, W.cands, (int)K, W.sums + kMaxCandOut + 1);
   if ((rc = check_hip(hipGetLastError(), "moved_kernel"))) return rc;
   if ((rc = launch_fill_float(W.ts, act_ts, st))) return rc;
   if ((rc = launch_fill_float(W.ts + 1, w_ts, st))) return rc;
 
   // the unquantized products, once
+  static std::atomic<uint64_t> raised{0};
+  if ((rc = allow_lds(reinterpret_cast<const void*>(ref_gemm_kernel), 2 * kRefStage, raised,
+                      "hipFuncSetAttribute(ref_gemm_kernel)")))
+    return rc;
   const dim3 ref_grid((unsigned)((M + kRefTile - 1) / kRefTile), (unsigned)((N + kRefTile - 1) / kRefTile));
   for (int b = 0; b < n_batches; ++b) {
-    hipLaunchKernelGGL(ref_gemm_kernel, ref_grid, dim3(256), 0, st, (const uint16_t*)x_calib[b], (const uint16_t*)w,
-                       (int)M, (int)N, (int)K, W.y_ref + (size_t)b * M * ldn, ldn);
+    hipLaunchKernelGGL(ref_gemm_kernel, ref_grid, dim3(256), 2 * kRefStage, st, (const uint16_t*)x_calib[b],
+                       (const uint16_t*)w, (int)M, (int)N, (int)K, W.y_ref + (size_t)b * M * ldn, ldn, W.den, b > 0);
   }
   if ((rc = check_hip(hipGetLastError(), "ref_gemm_kernel"))) return rc;
 
+  const size_t num_stride = out_tiles(M, N);
   for (int c = 0; c < n_cand; ++c) {
     const int32_t* perm = c == 0 ? nullptr : W.cands + (int64_t)(c - 1) * K;
     // the tensor scale of the weights does not depend on the order: the caller's value is used
-    if ((rc = launch_quantize_rows(fmt, group, w, N, K, K, perm, W.ts + 1, W.w_codes, W.w_scales, st))) return rc;
-    if ((rc = run_pack_operand(fmt, group, W.w_codes, W.w_scales, N, K, W.w_op, false, st))) return rc;
+    if ((rc = launch_quantize_rows_panel(fmt, group, w, N, K, perm, W.ts + 1, W.w_op, st))) return rc;
     for (int b = 0; b < n_batches; ++b) {
-      if ((rc = launch_quantize_rows(fmt, group, x_calib[b], M, K, K, perm, W.ts, W.x_codes, W.x_scales, st))) return rc;
-      if ((rc = run_pack_operand(fmt, group, W.x_codes, W.x_scales, M, K, W.x_op, false, st))) return rc;
-      if ((rc = run_qgemm_packed(fmt, group, W.x_op, W.ts, W.w_op, W.ts + 1, M, N, K, nullptr, W.y_hat, ldn, true, st)))
-        return rc;
-      hipLaunchKernelGGL(sqdiff_partial_kernel, dim3(kDiffBlocks), dim3(256), 0, st,
-                         W.y_ref + (size_t)b * M * ldn, W.y_hat, M, (int)N, ldn, W.partial);
-      hipLaunchKernelGGL(sqdiff_finish_kernel, dim3(1), dim3(64), 0, st, W.partial, W.sums + c,
-                         c == 0 ? W.sums + kMaxCandOut : nullptr);
+      if ((rc = launch_quantize_rows_panel(fmt, group, x_calib[b], M, K, perm, W.ts, W.x_op, st))) return rc;
+      const Output out{kOutDiff, W.num + (size_t)c * num_stride, ldn, W.y_ref + (size_t)b * M * ldn, b > 0};
+      if ((rc = run_qgemm_packed_out(fmt, group, W.x_op, W.ts, W.w_op, W.ts + 1, M, N, K, nullptr, out, st))) return rc;
     }
-    if ((rc = check_hip(hipGetLastError(), "sqdiff kernels"))) return rc;
   }
+  hipLaunchKernelGGL(tile_sums_kernel, dim3((unsigned)(n_cand + 1)), dim3(256), 0, st, W.num, (int64_t)num_stride,
+                     qgemm_tiles(fmt, group, M, N, K), W.den, (int64_t)ref_tiles(M, N), n_cand, kMaxCandOut, W.sums);
+  if ((rc = check_hip(hipGetLastError(), "tile_sums_kernel"))) return rc;
 
   double* h = pinned_doubles(kNumSums);
   if (!h) return fail(PQ_ERR_HIP, "pq_select_perm_output_error: no pinned host memory for the sums");

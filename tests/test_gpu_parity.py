@@ -357,6 +357,40 @@ def test_select_perm_output_error_matches_oracle(name, fmt, g, M, N, K, nb):
     np.testing.assert_array_equal(perm_out.cpu().numpy(), np.arange(K))
 
 
+@pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_NVFP4, 16, 4090, 4087, 160), (pq.FMT_NVFP4, 16, 2304, 3656, 288), (pq.FMT_NVFP4, 16, 1500, 2056, 96),
+    (pq.FMT_INT4, 64, 4090, 4087, 192), (pq.FMT_INT3, 64, 2300, 3656, 192), (pq.FMT_INT4, 128, 300, 4087, 640),
+    (pq.FMT_INT3, 32, 33, 41, 96), (pq.FMT_INT3, 256, 70, 3000, 256), (pq.FMT_NVFP4, 16, 2300, 333, 96),
+])
+def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K):
+    # the selection's error of the original order against the same product stored in fp32, summed in fp64: every tile
+    # of the product kernels keeps its own squared difference, ragged edges and two batches included
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(55 + M + K)
+    xs = [torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
+    w = (0.02 * torch.randn((N, K), generator=gen, device=DEV)).to(torch.bfloat16)
+    sa, sw = (torch.zeros(K, dtype=torch.float64, device=DEV) for _ in range(2))
+    amax = torch.zeros(2, dtype=torch.float32, device=DEV)
+    pq.pq_calib_moments_batched(xs, sa, amax[:1])
+    pq.pq_calib_moments(w, sw, amax[1:])
+    ts = amax / 2688.0
+    perm = torch.empty(K, dtype=torch.int32, device=DEV)
+    rep = pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, float(ts[0]), float(ts[1]), perm, alphas=(0.5,))
+    codes, scales = pq.alloc_quantized(fmt, g, N, K, DEV)
+    pq.pq_quantize_act(fmt, g, w, None, ts[1:], codes, scales)
+    w_op = pq.pq_pack_operand(fmt, g, codes, scales)
+    num = den = 0.0
+    y = torch.empty((M, (N + 7) // 8 * 8), dtype=torch.float32, device=DEV)
+    for x in xs:
+        x_op = pq.pq_quantize_act_packed(fmt, g, x, ts[:1])
+        pq.pq_qgemm_packed_f32(fmt, g, x_op, ts[:1], w_op, ts[1:], y, M, N, K)
+        ref = x.double() @ w.double().t()
+        num += float((ref - y[:, :N].double()).square().sum())
+        den += float(ref.square().sum())
+    assert abs(rep.sum_x2 - den) <= 1e-5 * den          # fp32 accumulation of both products
+    assert abs(rep.e_orig - num / den) <= 1e-5 * rep.e_orig
+
+
 def test_select_perm_candidates_and_ties():
     # equal second moments: the sort must keep ascending channel index (stable)
     K, M, N = 256, 32, 32
