@@ -154,6 +154,7 @@ struct TensorList {
 // fewest rows a workgroup of the error evaluation covers (bounds the number of partial sums)
 constexpr int kQeMinRowsPerBlock = 8;
 constexpr int kQeMaxWaves = 16;           // waves of such a workgroup
+constexpr size_t kQeLds = 150 * 1024;     // LDS its resident rows may take
 constexpr int64_t kQeParts(int64_t rows) { return (rows / kQeMinRowsPerBlock + 1) * kQeMaxWaves; }
 
 template <int R>
@@ -293,8 +294,10 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
     }
   }
   const int n_items = n_orders * wave_chunks;
-  const int per_wave = (n_items + n_waves - 1) / n_waves;
-  const int it0 = wave * per_wave, it1 = min(n_items, it0 + per_wave);
+  // The runs differ by one item; a SIMD's waves (w, w + 4, ...; a launch has a multiple of four) take neighbouring
+  // runs, so that the SIMDs get the same number of items but for one.
+  const int run = (wave & 3) * (n_waves >> 2) + (wave >> 2);
+  const int it0 = run * n_items / n_waves, it1 = (run + 1) * n_items / n_waves;
   const int ord0 = it0 / wave_chunks, blk0 = it0 - ord0 * wave_chunks;       // uniform over the wave
   auto cand_of = [&](int ord) { return (int)((order_list >> (4 * ord)) & 15u); };
   for (int rg = row0; rg < row_end; rg += R) {
@@ -594,17 +597,19 @@ static QeShape qe_shape(pq_format fmt, int64_t rows, int64_t K, int n_tensors, i
   const bool nv = fmt == PQ_FMT_NVFP4;
   const int chunk = nv ? QeChunk<kNvfp4>::value : QeChunk<kInt4>::value;
   const size_t slot_floats = (size_t)(K + K / 8);
-  q.r = slot_floats * 16 <= 64 * 1024 ? 4 : slot_floats * 8 <= 128 * 1024 ? 2 : 1;
+  // Resident rows: as many as LDS holds, four at most -- one gather and one load of offsets then serve four
+  // elements (K = 4096: 148 us with two rows, 134 with four; K = 7680, one workgroup a unit: 138 and 126).
+  q.r = slot_floats * 16 <= kQeLds ? 4 : slot_floats * 8 <= kQeLds ? 2 : 1;
   q.shmem = slot_floats * q.r * sizeof(float);
-  // waves: the work items of a set of resident rows (candidate x block of 64 chunks) are shared out
-  // evenly; take the fewest waves that need the fewest turns.  Two workgroups share a compute unit when
-  // their rows fit its LDS twice (one stages while the other computes): half of the waves the unit's
-  // registers hold each then (the NVFP4 instances need up to 128 registers a lane: sixteen waves a unit;
-  // the integer ones up to 96: twenty), sixteen otherwise.
+  // Waves, a multiple of four: the waves of a workgroup are dealt to the four SIMDs in turn, both workgroups of a
+  // unit from the same SIMD on, and the busiest SIMD sets the pace (INT4, K = 3072: 315 us with nine waves, 254 with
+  // eight, 246 with twelve; NVFP4, K = 12288, two batches: 403 with fourteen, 389 with sixteen).  Two workgroups share
+  // a unit where their rows fit its LDS twice (one stages while the other computes): half of the waves that the
+  // registers allow each (the NVFP4 instances need up to 128 a lane: sixteen waves a unit; the integer ones 84:
+  // twenty-four), sixteen otherwise.  No more than there are work items (candidate x block of 64 chunks).
   const int items = n_cand * (int)((K / chunk + 63) / 64);
-  const int max_waves = 2 * q.shmem <= 160 * 1024 ? (nv ? 8 : 10) : kQeMaxWaves;
-  const int turns = (items + max_waves - 1) / max_waves;
-  q.threads = 64 * ((items + turns - 1) / turns);
+  const int max_waves = 2 * q.shmem <= 160 * 1024 ? (nv ? 8 : 12) : kQeMaxWaves;
+  q.threads = 64 * (items < max_waves ? (items + 3) / 4 * 4 : max_waves);
   // Rows per workgroup: the workgroups run in rounds of as many as the chip holds at once (256 compute
   // units, one or two each), every round lasts about as long as a workgroup's rows plus a fixed start-up
   // (taken as half a row); among kQeMinRowsPerBlock .. 64 rows take the smallest size whose total is
@@ -636,7 +641,7 @@ static int launch_qe_r(const TensorList& xs, int n_tensors, int64_t rows, int K,
   (void)hipGetDevice(&dev);
   if (q.shmem > 48 * 1024 && (dev < 0 || dev >= kMaxDevicesSeen || !raised[dev].load(std::memory_order_acquire))) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kQeLds);
     if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(quant_error_kernel)");
     if (dev >= 0 && dev < kMaxDevicesSeen) raised[dev].store(true, std::memory_order_release);
   }
@@ -662,7 +667,7 @@ static int launch_quant_error(pq_format fmt, int group, const TensorList& x, int
                               int identity_first, ScaleArg T, const uint32_t* same_as, double* part,
                               hipStream_t st) {
   if (rows > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many rows");
-  if (q.shmem > 150 * 1024) return fail(PQ_ERR_SHAPE, "K=%d too large for the LDS-resident row", K);   // the entry points refuse this earlier
+  if (q.shmem > kQeLds) return fail(PQ_ERR_SHAPE, "K=%d too large for the LDS-resident row", K);   // the entry points refuse this earlier
   if (fmt == PQ_FMT_NVFP4)
     return launch_qe<kNvfp4, 16>(x, n_tensors, rows, K, q, offs, n_cand, identity_first, T, same_as, part, st);
 #define PQ_INT_CASE(F, FE)                                                                                  \
