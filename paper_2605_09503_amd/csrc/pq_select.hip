@@ -2,13 +2,12 @@
 // (Prop. 1), calibration error of every candidate order, alpha search and acceptance rule.
 //
 // Kernels
-//   key_kernel        key[j][i] = alpha_j ln Sa[i] + (1 - alpha_j) ln Sw[i], fp64, all j in one
-//                     launch; a term whose weight is zero is skipped.
-//   rank_count_kernel / rank_scatter_kernel
-//                     stable descending sort by counting: rank(i) = #{j : key_j > key_i or
-//                     (key_j == key_i and j < i)}; perm[rank(i)] = i.  O(K^2) compares, K <= 65536,
-//                     split over (channel block, key chunk, candidate) workgroups, integer
-//                     counts added atomically, fully deterministic.
+//   block_order_kernel  key[j][i] = alpha_j ln Sa[i] + (1 - alpha_j) ln Sw[i], fp64, all j in one
+//                     launch (a term whose weight is zero is skipped), in order inside every block of 256 channels.
+//   rank_merge_kernel / rank_scatter_kernel
+//                     stable descending sort: rank(i) = #{j : key_j > key_i or (key_j == key_i and
+//                     j < i)}, from the sorted blocks by bisection, integer counts added atomically
+//                     (deterministic); perm[rank(i)] = i.  K <= 65536.
 //   same_order_kernel  which candidate orders repeat an earlier one (or the original order): those are
 //                     evaluated once.
 //   quant_error_kernel a workgroup stages a few rows in LDS at a time; for every candidate order
@@ -36,60 +35,110 @@ struct AlphaList {
   double a[PQ_MAX_ALPHAS];
 };
 
-// key[j][i] for every alpha_j of the grid (blockIdx.y = j)
-__global__ __launch_bounds__(256) void key_kernel(const double* __restrict__ sa,
-                                                  const double* __restrict__ sw, int64_t K,
-                                                  AlphaList alphas, double* __restrict__ key,
-                                                  int32_t* __restrict__ rank, uint32_t* __restrict__ differs) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (differs && i == 0) differs[blockIdx.y] = 0u;    // same_order_kernel ORs into it
-  if (i >= K) return;
-  rank[(int64_t)blockIdx.y * K + i] = 0;          // the counting pass adds to it
-  const double alpha = alphas.a[blockIdx.y];
-  double k = 0.0;
-  if (alpha != 0.0) k += alpha * log(sa[i]);
-  if (alpha != 1.0) k += (1.0 - alpha) * log(sw[i]);
-  key[(int64_t)blockIdx.y * K + i] = k;
+// The stable descending sort, in blocks of 256 channels: block_order_kernel puts every block in order, and the rank
+// of a channel is its place there plus, for every other block, the number of keys that sort before its own, found by
+// bisection.  Both passes, six orders: 24 us at K = 12288 and 10.8 at K = 3072, where a pass for the keys and one that
+// counts against all K of them took 63 and 12.
+constexpr int kSortBlock = 256;
+constexpr int kMergeBlocks = 4;    // blocks a workgroup of the merging pass bisects in
+constexpr int kSortShares = 4;     // threads that share a channel's comparisons inside its block
+
+// Workgroup (x, y): the keys of channel block x for alpha_y,
+//     key[i] = alpha ln Sa[i] + (1 - alpha) ln Sw[i],
+// in descending order, equal keys in ascending channel order: keys into key[y], channels into order[y].  With
+// sa == nullptr the keys are in key[] already.  Also clears what the passes after it add to.
+__global__ __launch_bounds__(kSortBlock * kSortShares) void block_order_kernel(const double* __restrict__ sa,
+                                                                 const double* __restrict__ sw, int64_t K,
+                                                                 AlphaList alphas, double* __restrict__ keys,
+                                                                 int32_t* __restrict__ order, int32_t* __restrict__ rank,
+                                                                 uint32_t* __restrict__ differs) {
+  __shared__ double tile[kSortBlock];
+  __shared__ int before_of[kSortShares][kSortBlock];
+  const int t = threadIdx.x % kSortBlock, share = threadIdx.x / kSortBlock;      // share: uniform over a wave
+  const int64_t i0 = (int64_t)blockIdx.x * kSortBlock, i = i0 + t;
+  double* key = keys + (int64_t)blockIdx.y * K;
+  double k = -__builtin_inf();
+  if (share == 0) {
+    if (differs && i == 0) differs[blockIdx.y] = 0u;  // same_order_kernel ORs into it
+    if (i < K) {
+      if (sa) {
+        const double alpha = alphas.a[blockIdx.y];
+        k = 0.0;
+        if (alpha != 0.0) k += alpha * log(sa[i]);
+        if (alpha != 1.0) k += (1.0 - alpha) * log(sw[i]);
+      } else {
+        k = key[i];
+      }
+      if (!(k == k)) k = -__builtin_inf();            // no number (a negative statistic): last, and still an order
+      rank[(int64_t)blockIdx.y * K + i] = 0;          // the merging pass adds to it
+    }
+    tile[t] = k;                                      // past K: after every channel, and after its equals
+  }
+  __syncthreads();
+  k = tile[t];
+  int before = 0;
+  constexpr int kShare = kSortBlock / kSortShares;
+#pragma unroll 16
+  for (int j = share * kShare; j < (share + 1) * kShare; ++j) {
+    // without short-circuit evaluation: no branches
+    const double kj = tile[j];
+    const int gt = kj > k ? 1 : 0, eq = kj == k ? 1 : 0, earlier = j < t ? 1 : 0;
+    before += gt | (eq & earlier);
+  }
+  before_of[share][t] = before;
+  __syncthreads();
+  if (share == 0 && i < K) {
+    int at = 0;
+#pragma unroll
+    for (int q = 0; q < kSortShares; ++q) at += before_of[q][t];
+    key[i0 + at] = k;
+    order[(int64_t)blockIdx.y * K + i0 + at] = (int32_t)i;
+  }
 }
 
-constexpr int kRankChunk = 128;    // keys compared per workgroup of the counting pass (divides 256)
-
-// Counting pass of the stable descending sort: workgroup (x, y, z) compares its 256 channels i
-// with the kRankChunk keys j of chunk y of candidate z and adds how many of them sort before i to
-// rank[z][i] (integer atomics: the sum does not depend on the order of the workgroups).
-// A chunk lies inside one channel block, so every key of a chunk in an earlier block has j < i (it
-// sorts before i when key_j >= key_i), every key in a later block has j > i (key_j > key_i), and
-// only the chunks of the workgroup's own block need the index comparison.  A wave's time is the
-// chain of its scalar key loads, hence short chunks and deep unrolling.
-__global__ __launch_bounds__(256) void rank_count_kernel(const double* __restrict__ keys, int K,
-                                                         int32_t* __restrict__ rank) {
+// Workgroup (x, y, z): for the channels of block x of order z, how many keys of blocks y * kMergeBlocks ... sort before
+// theirs, added to rank[z] (integer atomics: the sum does not depend on order).  A key of an earlier block sorts
+// before an equal one, of a later block after it.  The channel's place in its own block is added along with it.
+__global__ __launch_bounds__(kSortBlock) void rank_merge_kernel(const double* __restrict__ keys,
+                                                                const int32_t* __restrict__ order, int K, int n_blocks,
+                                                                int32_t* __restrict__ rank) {
+  __shared__ double tile[kMergeBlocks][kSortBlock];
   const double* key = keys + (int64_t)blockIdx.z * K;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int j0 = blockIdx.y * kRankChunk;
-  const int n = min(kRankChunk, K - j0);
+  const int b0 = blockIdx.y * kMergeBlocks;
+  // a missing key is the smallest there is: never greater than another, and only the last block, which no channel
+  // comes after, is short
+#pragma unroll
+  for (int b = 0; b < kMergeBlocks; ++b) {
+    const int j = (b0 + b) * kSortBlock + threadIdx.x;
+    tile[b][threadIdx.x] = j < K ? key[j] : -__builtin_inf();
+  }
+  __syncthreads();
+  const int i = blockIdx.x * kSortBlock + threadIdx.x;
   if (i >= K) return;
   const double ki = key[i];
-  // the keys of the chunk are the same for every lane: they come through scalar loads and sit in
-  // scalar registers, the compare takes them as an operand
-  const double* tile = key + j0;
-  int before = 0;
-  const int key_block = blockIdx.y / (256 / kRankChunk);      // the channel block the chunk lies in
-  if (key_block < (int)blockIdx.x) {
-#pragma unroll 32
-    for (int t = 0; t < n; ++t) before += tile[t] >= ki ? 1 : 0;
-  } else if (key_block > (int)blockIdx.x) {
-#pragma unroll 32
-    for (int t = 0; t < n; ++t) before += tile[t] > ki ? 1 : 0;
-  } else {
-#pragma unroll 32
-    for (int t = 0; t < n; ++t) {
-      // without short-circuit evaluation: no branches, the loads of a whole unrolled trip go out together
-      const double kj = tile[t];
-      const int gt = kj > ki ? 1 : 0, eq = kj == ki ? 1 : 0, earlier = j0 + t < i ? 1 : 0;
-      before += gt | (eq & earlier);
+  int before[kMergeBlocks];
+#pragma unroll
+  for (int b = 0; b < kMergeBlocks; ++b) before[b] = 0;
+  // in step with each other, so that the chains of reads overlap
+#pragma unroll
+  for (int half = kSortBlock / 2; half >= 1; half >>= 1) {
+#pragma unroll
+    for (int b = 0; b < kMergeBlocks; ++b) {
+      const double kj = tile[b][before[b] + half - 1];
+      const bool ahead = b0 + b < (int)blockIdx.x ? kj >= ki : kj > ki;
+      before[b] += ahead ? half : 0;
     }
   }
-  atomicAdd(&rank[(int64_t)blockIdx.z * K + i], before);
+  int sum = 0;
+#pragma unroll
+  for (int b = 0; b < kMergeBlocks; ++b) {
+    // the bisection stops short of the block's last key
+    const double kj = tile[b][kSortBlock - 1];
+    const bool all = before[b] == kSortBlock - 1 && (b0 + b < (int)blockIdx.x ? kj >= ki : kj > ki);
+    const int n = before[b] + (all ? 1 : 0);
+    sum += b0 + b >= n_blocks ? 0 : b0 + b == (int)blockIdx.x ? (int)threadIdx.x : n;
+  }
+  atomicAdd(&rank[(int64_t)blockIdx.z * K + order[(int64_t)blockIdx.z * K + i]], sum);
 }
 
 // perm[z][rank(i)] = i; with offs, also the LDS byte offset of channel i's slot in the error evaluation
@@ -107,7 +156,7 @@ __global__ __launch_bounds__(256) void rank_scatter_kernel(const int32_t* __rest
 // Which candidate orders repeat an earlier one.  Candidate 0 is the original order, candidate 1 + j the order
 // of alpha_j.  differs[j] collects a bit per earlier candidate c <= j that differs from order j somewhere
 // (integer OR: no order dependence); workgroup (x, j) looks at 256 positions.  differs[] is zeroed by
-// key_kernel, which runs before on the same stream.
+// block_order_kernel, which runs before on the same stream.
 __global__ __launch_bounds__(256) void same_order_kernel(const int32_t* __restrict__ perms, int K,
                                                          uint32_t* __restrict__ differs) {
   __shared__ unsigned block_bits;
@@ -697,8 +746,6 @@ struct SelectWs {
                      // errors, |X|^2, |W|^2, moved-channel counts
 };
 
-static int rank_chunks(int64_t K) { return (int)((K + kRankChunk - 1) / kRankChunk); }
-
 static size_t carve_select(void* base, int64_t M, int64_t N, int64_t K, int n_batches, SelectWs* w) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -757,6 +804,16 @@ int run_quant_error(pq_format fmt, int group, const void* x, int64_t rows, int64
   return check_hip(hipGetLastError(), "reduce_rows_kernel");
 }
 
+// rank[n][K] of the channels in n descending orders; order[n][K] is scratch (overwritten by the scatter that follows)
+static void launch_ranks(const double* act_sumsq, const double* w_sumsq, int64_t K, const AlphaList& al, int n,
+                         double* keys, int32_t* order, int32_t* rank, uint32_t* differs, hipStream_t st) {
+  const unsigned kb = (unsigned)((K + kSortBlock - 1) / kSortBlock);
+  hipLaunchKernelGGL(block_order_kernel, dim3(kb, n), dim3(kSortBlock * kSortShares), 0, st, act_sumsq, w_sumsq, K, al, keys, order,
+                     rank, differs);
+  hipLaunchKernelGGL(rank_merge_kernel, dim3(kb, (kb + kMergeBlocks - 1) / kMergeBlocks, n), dim3(kSortBlock), 0, st,
+                     keys, order, (int)K, (int)kb, rank);
+}
+
 // The candidate orders of the alpha grid (joint score, descending stable sort) into
 // cands[n_alpha][K]; keys [PQ_MAX_ALPHAS][K] doubles and rank [PQ_MAX_ALPHAS][K] ints are scratch.
 // With offs ([n_alpha][K]), the same orders are also written as slot offsets of slot_bytes a slot.
@@ -764,11 +821,9 @@ int launch_candidate_orders(const double* act_sumsq, const double* w_sumsq, int6
                             int n_alpha, double* keys, int32_t* rank, int32_t* cands, hipStream_t st,
                             int32_t* offs, int slot_bytes, uint32_t* differs) {
   const unsigned kb = (unsigned)((K + 255) / 256);
-  const int chunks = rank_chunks(K);
   AlphaList al;
   for (int j = 0; j < PQ_MAX_ALPHAS; ++j) al.a[j] = j < n_alpha ? alphas[j] : 0.0;
-  hipLaunchKernelGGL(key_kernel, dim3(kb, n_alpha), dim3(256), 0, st, act_sumsq, w_sumsq, K, al, keys, rank, differs);
-  hipLaunchKernelGGL(rank_count_kernel, dim3(kb, chunks, n_alpha), dim3(256), 0, st, keys, (int)K, rank);
+  launch_ranks(act_sumsq, w_sumsq, K, al, n_alpha, keys, cands, rank, differs, st);
   hipLaunchKernelGGL(rank_scatter_kernel, dim3(kb, n_alpha), dim3(256), 0, st, rank, (int)K, cands, offs,
                      slot_bytes);
   if (differs)          // which orders repeat an earlier candidate (or the original order)
@@ -788,8 +843,7 @@ __global__ __launch_bounds__(256) void round_robin_kernel(const int32_t* __restr
 
 // random: key[i] = -(splitmix64(seed + i) >> 11) as a double (53 bits: exact), so that the descending
 // stable sort used for the scores gives ascending hashes with ties in ascending channel order
-__global__ __launch_bounds__(256) void random_key_kernel(uint64_t seed, int K, double* __restrict__ keys,
-                                                        int32_t* __restrict__ rank) {
+__global__ __launch_bounds__(256) void random_key_kernel(uint64_t seed, int K, double* __restrict__ keys) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= K) return;
   uint64_t z = seed + (uint64_t)i + 0x9E3779B97F4A7C15ull;
@@ -797,7 +851,6 @@ __global__ __launch_bounds__(256) void random_key_kernel(uint64_t seed, int K, d
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
   z = z ^ (z >> 31);
   keys[i] = -(double)(z >> 11);
-  rank[i] = 0;
 }
 
 int launch_round_robin(const int32_t* order, int64_t K, int group, int32_t* perm, hipStream_t st) {
@@ -811,8 +864,8 @@ int launch_random_order(uint64_t seed, int64_t K, int32_t* perm, void* ws, hipSt
   double* keys = (double*)ws;
   int32_t* rank = (int32_t*)((char*)ws + align_up((size_t)K * 8, 256));
   const unsigned kb = (unsigned)((K + 255) / 256);
-  hipLaunchKernelGGL(random_key_kernel, dim3(kb), dim3(256), 0, st, seed, (int)K, keys, rank);
-  hipLaunchKernelGGL(rank_count_kernel, dim3(kb, rank_chunks(K), 1), dim3(256), 0, st, keys, (int)K, rank);
+  hipLaunchKernelGGL(random_key_kernel, dim3(kb), dim3(256), 0, st, seed, (int)K, keys);
+  launch_ranks(nullptr, nullptr, K, AlphaList{}, 1, keys, perm, rank, nullptr, st);
   hipLaunchKernelGGL(rank_scatter_kernel, dim3(kb, 1), dim3(256), 0, st, rank, (int)K, perm,
                      (int32_t*)nullptr, 0);
   return check_hip(hipGetLastError(), "random order kernels");

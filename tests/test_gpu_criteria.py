@@ -110,3 +110,20 @@ def test_criteria_rank_as_in_the_ablation_on_structured_channels():
     assert errs["second_moment"] < 0.8 * errs["orig"]
     assert errs["round_robin"] > errs["orig"] > errs["second_moment"]
     assert 0.8 * errs["orig"] < errs["random"] < 1.25 * errs["orig"]
+
+
+@pytest.mark.parametrize("K", [1, 255, 256, 257, 2048, 2049, 4361, 65536])
+def test_order_across_sort_blocks(K):
+    """Few distinct statistics, zeros among them, over one to 256 blocks of the sort, the last one short or full:
+    the stable descending order.  A negative statistic has no logarithm: it sorts last, and the order is still one."""
+    rng = np.random.default_rng(9870 + K)
+    stat = np.exp(rng.integers(-3, 4, size=K).astype(np.float64))
+    stat[rng.random(K) < 0.1] = 0.0
+    for negative in (False, True):
+        if negative:
+            stat[rng.random(K) < 0.02] = -1.0
+        got = pq.pq_order_by_score(torch.from_numpy(stat).to(DEV), torch.ones(K, dtype=torch.float64, device=DEV), 1.0,
+                                   torch.empty(K, dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        want = np.argsort(-np.maximum(stat, 0.0), kind="stable")
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
