@@ -63,7 +63,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
   // and are never read)
   constexpr int A_TILE_BYTES = SL * (T / 2) * kRowBytes, W_TILE_BYTES = BN * kRowBytes;
   constexpr int STAGE_BYTES = A_TILE_BYTES + W_TILE_BYTES;
-  constexpr int NT = 8 * SL;                         // unpack pair tasks per k slice
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -165,19 +164,34 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
   load_w(2, raw_w[0]);
   __syncthreads();
 
+  // weight fragments: one set, each reloaded for the next k slice right after its last MFMA; activation
+  // fragments: two sets (they are used by every MFMA of a slice)
+  half8_t wf[TN], xf[2][TM];
+  auto read_w = [&](const unsigned char* stage, int kk, int i) {
+    wf[i] = *reinterpret_cast<const half8_t*>(stage + A_TILE_BYTES + w_frag_base[i] + piece_off[kk]);
+  };
+  auto read_x = [&](const unsigned char* stage, int set, int kk, int j) {
+    xf[set][j] = *reinterpret_cast<const half8_t*>(stage + x_frag_base[j] + piece_off[kk]);
+  };
+#pragma unroll
+  for (int j = 0; j < TM; ++j)
+    if (!RAGGED_M || j < tm_cnt) read_x(smem, 0, 0, j);
+#pragma unroll
+  for (int i = 0; i < TN; ++i) read_w(smem, 0, i);
+
   // TMc: the MFMA tile rows of the calling wave as a compile-time constant (TM, or TM_LAST for the
   // short wave row of an uneven split) -- each kind of wave runs its own straight-line loop
   auto body = [&](auto Pc, auto TMc, int s) {
     constexpr int P = decltype(Pc)::value;
     constexpr int TMW = decltype(TMc)::value;
     constexpr int NM = TN * TMW;                     // MFMAs per 16-wide k slice
-    const unsigned char* a_t = smem + P * STAGE_BYTES;
-    const unsigned char* w_t = a_t + A_TILE_BYTES;
+    const unsigned char* stage = smem + P * STAGE_BYTES;
+    const unsigned char* next = smem + (P ^ 1) * STAGE_BYTES;
     unsigned char* a_nx = smem + (P ^ 1) * STAGE_BYTES;
     unsigned char* w_nx = a_nx + A_TILE_BYTES;
 
     // step s + 1 sits in raw[P ^ 1]; it is unpacked during this step and the registers are
-    // refilled with step s + 3 as soon as they are free (A after half the step, W at the end)
+    // refilled with step s + 3 as soon as they are free
     Slice(&ca)[SL] = raw_a[P ^ 1];
     Slice(&cw)[SL] = raw_w[P ^ 1];
     PairScale sc_a[SL][2], sc_w[SL][2];
@@ -188,60 +202,56 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
       slice_scales<FMT>(cw[q], w_ok[q] && k_ok, sc_w[q][0], sc_w[q][1]);
     }
 
-    // weight fragments: one set, each reloaded for the next k slice right after its last MFMA;
-    // activation fragments: two sets (they are used by every MFMA of a slice)
-    half8_t wf[TN], xf[2][TM];
-    auto read_w = [&](int kk, int i) {
-      wf[i] = *reinterpret_cast<const half8_t*>(w_t + w_frag_base[i] + piece_off[kk]);
-    };
-    auto read_x = [&](int set, int kk, int j) {
-      xf[set][j] = *reinterpret_cast<const half8_t*>(a_t + x_frag_base[j] + piece_off[kk]);
-    };
-#pragma unroll
-    for (int j = 0; j < TMW; ++j) read_x(0, 0, j);
-#pragma unroll
-    for (int i = 0; i < TN; ++i) read_w(0, i);
-
     uint32_t pk[4];        // the unit (one dword of codes -> one 16-byte piece) being assembled
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const int cur = kk & 1;
+      // The step's barrier stands before its last slice, whose fragments are in registers by then: the first
+      // fragments of the next step are on their way while that slice is multiplied, and no wave starts a step waiting
+      // for LDS.
+      if (kk == 3) {
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int mi = 0; mi < NM; ++mi) {
         const int i = mi / TMW, j = mi % TMW;
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[i], xf[cur][j], acc[i][j], 0, 0, 0);
         if (kk < 3) {
-          if (j == TMW - 1) read_w(kk + 1, i);                // wf[i] is free now
-          if (mi < TMW) read_x(cur ^ 1, kk + 1, mi);          // next slice's activations, early
+          if (j == TMW - 1) read_w(stage, kk + 1, i);                // wf[i] is free now
+          if (mi < TMW) read_x(stage, cur ^ 1, kk + 1, mi);          // next slice's activations, early
+        } else {
+          if (j == TMW - 1) read_w(next, 0, i);
+          if (mi < TMW) read_x(next, 0, 0, mi);
         }
-        // unpack tasks: NT pairs per k slice, spread evenly over the MFMAs.  Task order over
-        // the whole step: A slot 0 (4 pieces x 4 pairs), A slot 1, ..., then the W slots.
+        // unpack tasks: 32 SL pairs, spread evenly over the MFMAs of the first three slices (their pieces have to be in
+        // LDS at the barrier).  Task order: A slot 0 (4 pieces x 4 pairs), A slot 1, ..., then the W slots.
+        if (kk < 3) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          if (t * NM / NT != mi) continue;
-          const int g = kk * NT + t;          // global pair task 0 .. 32 * SL - 1
-          const int u = g / 4;                // unit: one dword of codes -> one LDS piece
-          const int jp = g % 4;
-          const bool is_w = u >= 4 * SL;
-          const int q = (u / 4) % SL, c = u % 4;
-          const Slice& src = is_w ? cw[q] : ca[q];
-          const uint32_t d = c == 0 ? src.codes.x : c == 1 ? src.codes.y : c == 2 ? src.codes.z : src.codes.w;
-          const PairScale& sc = is_w ? sc_w[q][c / 2] : sc_a[q][c / 2];
-          if (jp == 0) pk[0] = unpack_pair<FMT, 0>(d, sc);
-          if (jp == 1) pk[1] = unpack_pair<FMT, 1>(d, sc);
-          if (jp == 2) pk[2] = unpack_pair<FMT, 2>(d, sc);
-          if (jp == 3) {
-            pk[3] = unpack_pair<FMT, 3>(d, sc);
-            unsigned char* dst = (is_w ? w_nx : a_nx) + st_off[q][c];
-            *reinterpret_cast<uint4*>(dst) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+          for (int g = 0; g < 32 * SL; ++g) {
+            if (g * 3 * NM / (32 * SL) != kk * NM + mi) continue;
+            const int u = g / 4;                // unit: one dword of codes -> one LDS piece
+            const int jp = g % 4;
+            const bool is_w = u >= 4 * SL;
+            const int q = (u / 4) % SL, c = u % 4;
+            const Slice& src = is_w ? cw[q] : ca[q];
+            const uint32_t d = c == 0 ? src.codes.x : c == 1 ? src.codes.y : c == 2 ? src.codes.z : src.codes.w;
+            const PairScale& sc = is_w ? sc_w[q][c / 2] : sc_a[q][c / 2];
+            if (jp == 0) pk[0] = unpack_pair<FMT, 0>(d, sc);
+            if (jp == 1) pk[1] = unpack_pair<FMT, 1>(d, sc);
+            if (jp == 2) pk[2] = unpack_pair<FMT, 2>(d, sc);
+            if (jp == 3) {
+              pk[3] = unpack_pair<FMT, 3>(d, sc);
+              unsigned char* dst = (is_w ? w_nx : a_nx) + st_off[q][c];
+              *reinterpret_cast<uint4*>(dst) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+            }
+            if (g == 16 * SL - 1) load_a(s + 3, ca);
+            if (g == 32 * SL - 1) load_w(s + 3, cw);
           }
         }
-        if (kk == 1 && mi == NM - 1) load_a(s + 3, ca);
-        if (kk == 3 && mi == NM - 1) load_w(s + 3, cw);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __syncthreads();
   };
 
   // two steps per trip so that the LDS stage and the register set are compile-time constants;
@@ -260,6 +270,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
     }
   }
 
+  __syncthreads();                                     // the output tile reuses the stages
   store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, 2 * STAGE_BYTES, OUT>(
       acc, smem, a_mul, a_mul_stride, w_mul, w_mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f,
       tile_m * tiles_n + tile_n, out);
