@@ -271,10 +271,12 @@ int pq_quantize_act(pq_format fmt, int group, const void* x_bf16, int64_t M, int
  * the quantizers above; a_tensor_scale / w_tensor_scale: float [1] device (NVFP4; ignored for
  * INT, may be NULL).  y_bf16: bf16 [M, ldy], ldy >= N, ldy % 8 == 0.
  * INT scales must be of the form fl32(h / Q) with h a bf16 value, which is what the quantizers
- * above produce from bf16 inputs (the kernel folds h exactly into its fp16 MFMA operands; the
- * product then differs from the stored-scale one by the 2^-24 rounding of h / Q per factor).  Scales
- * of another origin give a different product without an error: check them once with
- * pq_qgemm_check_int_scales.  Inside a row the operand holds h * 2^-E with E from the row's largest
+ * above produce from bf16 inputs (the kernels work with h, either folded exactly into fp16 MFMA operands
+ * or applied to the exact integer sum of a group; the product then differs from the stored-scale one by
+ * the 2^-24 rounding of h / Q per factor).  Scales of another origin give a different product without an
+ * error: check them once with pq_qgemm_check_int_scales.  INT3 codes are 3-bit values, -4 .. 3, as the
+ * quantizers and pq_int3_unpack store them (with groups of 64 and more the matrix unit takes them as E2M1,
+ * which holds the integers up to 4).  Inside a row the operand holds h * 2^-E with E from the row's largest
  * group: a group more than 2^24 below it loses low bits of h (below 2^-35: all of them) -- its terms
  * are then below 2^-24 of the row's largest terms, the resolution of the fp32 accumulation anyway.
  * workspace: pq_workspace_bytes(PQ_OP_QGEMM, fmt, group, M, N, K, 0) bytes.
@@ -512,8 +514,9 @@ int pq_probe_mfma(int iters, float* sink, double* flops_out, void* stream);
  * clock, the sooner the more the operands switch from one instruction to the next), so the reference for
  * the product on given data is this loop on that data: every lane unpacks eight fragments of a_operand
  * and four of w_operand (operands as written by pq_quantize_act_packed / pq_pack_operand for these
- * fmt, group, M, N, K; K a multiple of 64) with the product kernel's own code and the loop cycles
- * through them.  sink, flops_out as for pq_probe_mfma.
+ * fmt, group, M, N, K; K a multiple of 64) to the fp16 values that carry their group's scale, with the
+ * fp16 product kernel's own code, and the loop cycles through them (also for the integer formats with
+ * groups of 64 and more, whose large products run on the 8- and 4-bit instructions instead).  sink, flops_out as for pq_probe_mfma.
  */
 int pq_probe_mfma_operands(pq_format fmt, int group, const void* a_operand, const void* w_operand, int64_t M,
                            int64_t N, int64_t K, int iters, float* sink, double* flops_out, void* stream);

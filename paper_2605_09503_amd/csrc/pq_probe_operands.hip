@@ -4,7 +4,7 @@
 // lowers its clock, and how soon depends on the switching activity of the operands.  A loop that reuses
 // one pair of constant fragments (pq_probe_mfma) therefore overstates what a GEMM on real data can reach.
 // Here every lane unpacks eight fragments of the activation operand and four of the weight operand --
-// with the product kernel's own loader and unpack code, from rows and K positions spread over the
+// with the fp16 product kernel's own loader and unpack code, from rows and K positions spread over the
 // operands -- and the loop cycles through them, so that both MFMA inputs change from one instruction to
 // the next.  No LDS, no vector work, no memory traffic inside the loop.
 #include "pq_qgemm_common.h"

@@ -1,7 +1,9 @@
 // Low-bit GEMM of the reordered quantized layer (paper Eq. 8):
 //     Y[m, n] = Ta Tw sum_g sa[m, g] sw[n, g] sum_{k in g} a[m, k] w[n, k]
 //
-// Design for gfx950.  The contraction runs on the fp16 MFMA (v_mfma_f32_32x32x16_f16, fp32
+// Design for gfx950.  Large outputs are computed here, those of the integer formats with groups of 64 and more in
+// pq_qgemm_group.hip, small outputs in pq_qgemm_split.hip; choose_tile says which.
+// The contraction runs on the fp16 MFMA (v_mfma_f32_32x32x16_f16, fp32
 // accumulate).  Both operands stay 4-bit in HBM and L2; a workgroup unpacks its A and W tiles
 // once per K step straight into fp16 values that already carry the per-group scale, and stages
 // them in LDS:
@@ -35,7 +37,7 @@ namespace pq {
 //     issued one slice ahead,
 //   - between MFMAs the wave unpacks its slice of step s + 1 (already in registers) pair by
 //     pair and writes it to stage P ^ 1,
-//   - one barrier ends the step.
+//   - one barrier, before the last k slice: the first fragments of step s + 1 are read during that slice.
 // Every MFMA is followed by its share of vector-ALU and LDS work in program order, pinned
 // with scheduling barriers, so that the matrix pipe and the vector ALU overlap inside a wave
 // instead of alternating in phases.
