@@ -274,9 +274,9 @@ int pq_quantize_act(pq_format fmt, int group, const void* x_bf16, int64_t M, int
  * above produce from bf16 inputs (the kernels work with h, either folded exactly into fp16 MFMA operands
  * or applied to the exact integer sum of a group; the product then differs from the stored-scale one by
  * the 2^-24 rounding of h / Q per factor).  Scales of another origin give a different product without an
- * error: check them once with pq_qgemm_check_int_scales.  INT3 codes are 3-bit values, -4 .. 3, as the
- * quantizers and pq_int3_unpack store them (with groups of 64 and more the matrix unit takes them as E2M1,
- * which holds the integers up to 4).  Inside a row the operand holds h * 2^-E with E from the row's largest
+ * error: check them once with pq_qgemm_check_int_scales.  Codes are multiplied as the nibbles they are, -8 .. 7,
+ * also where the quantizers write less (INT3: -3 .. 3; a row with codes outside -4 .. 3 is slower with groups of 64
+ * and more, whose products take the codes in a form that holds no more than that).  Inside a row the operand holds h * 2^-E with E from the row's largest
  * group: a group more than 2^24 below it loses low bits of h (below 2^-35: all of them) -- its terms
  * are then below 2^-24 of the row's largest terms, the resolution of the fp32 accumulation anyway.
  * workspace: pq_workspace_bytes(PQ_OP_QGEMM, fmt, group, M, N, K, 0) bytes.

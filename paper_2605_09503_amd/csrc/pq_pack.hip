@@ -10,7 +10,8 @@
 //     codes   [ceil(K / 64)][rows][32 bytes]
 //     scales  [units][rows][2 bytes]   units: pairs of E4M3 bytes per 32 k (NVFP4), or the fp16
 //                                      normalised group maximum per group (INT)
-//     mul     [rows] fp32              INT only: 2^E(row) / Q
+//     mul     [rows] fp32              INT only: 2^E(row) / Q; INT3 with groups of 64 and more: negative where
+//                                      the row holds codes outside -4 .. 3 (see wide_codes_tile)
 // so a wave reads whole lines.  For INT the scale normalisation of pq_qgemm.hip (recover the
 // group's bf16 maximum h = bf16_rne(s * Q), divide by a per-row power of two that puts the row
 // maximum in [2^10, 2^11)) happens here, once, instead of in a pass of its own.
@@ -40,7 +41,14 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
                                                            float* __restrict__ p_mul) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t r0 = (int64_t)blockIdx.x * kPackRows;
+  constexpr bool MARK = FMT == kInt3 && G >= 64 && !DENSE3;          // three bits hold no wide code
+  __shared__ int row_wide[kPackRows];
+  if constexpr (MARK) {
+    if (tid < kPackRows) row_wide[tid] = 0;
+    __syncthreads();
+  }
   {
+    uint32_t wide = 0;
     const int s_local = lane >> 4, r_local = (lane & 15) >> 1, half = lane & 1;
     const int64_t r = r0 + r_local;
     // four trips' loads in flight before the first store
@@ -64,7 +72,12 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
       for (int t = 0; t < 4; ++t) {
         const int64_t step = s0 + t * 16 + wave * 4 + s_local;
         if (r < rows && step < steps) *reinterpret_cast<uint4*>(p_codes + (step * rows + r) * 32 + half * 16) = v[t];
+        if constexpr (MARK) wide |= wide_codes(v[t].x) | wide_codes(v[t].y) | wide_codes(v[t].z) | wide_codes(v[t].w);
       }
+    }
+    if constexpr (MARK) {
+      if (wide & wide_mask(kWideCodes)) row_wide[r_local] = 1;
+      __syncthreads();
     }
   }
   const int r_local = lane & 7, u_local = lane >> 3;
@@ -98,7 +111,8 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
       const int E = max(-120, min(120, e - 10));
       if ((lane & 31) == 0) {
         row_down[rr] = as_f32((uint32_t)(127 - E) << 23);                            // 2^-E
-        if (row < rows) p_mul[row] = as_f32((uint32_t)(127 + E) << 23) / Q;          // 2^E / Q
+        const float up = as_f32((uint32_t)(127 + E) << 23) / Q;                      // 2^E / Q
+        if (row < rows) p_mul[row] = MARK && row_wide[rr] ? -up : up;
       }
     }
     __syncthreads();

@@ -35,6 +35,7 @@ struct Slice {
 //   panel (K-step-major, see pq_pack.hip):  code_row = 32, code_step = 32 * rows;
 //                                           sc_row = 2, sc_step = 2 * rows
 // mul: per-row epilogue factor (stride 1) or a single factor (stride 0).
+// marked: the sign of a row's factor says that the row holds INT3 codes beyond three bits (pq_pack.hip)
 // bias: bf16 value per row of this operand added to the product in the epilogue (used for the
 // weight operand, whose rows are the output columns), or null.
 struct OperandView {
@@ -47,6 +48,7 @@ struct OperandView {
   const float* mul;
   int mul_stride;
   const uint16_t* bias = nullptr;
+  bool marked = false;
 };
 
 // Branch-free load of one slice.  `codes_row` / `sc_row` point at a valid row (the caller
@@ -132,6 +134,18 @@ __device__ __forceinline__ uint32_t e2m1_nibbles(uint32_t d) {
   return (d ^ (s - m)) + m;
 }
 
+// 32 codes of a row -> the 32 E4M3 bytes of a lane's operand (any order of k, as long as it is the same for A and W)
+__device__ __forceinline__ int8v e4m3_operand(const uint4& c) {
+  const uint32_t d[4] = {c.x, c.y, c.z, c.w};
+  int8v o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    o[2 * e] = (int)e4m3_bytes(d[e] & 0x0F0F0F0Fu, (d[e] >> 3) & 0x01010101u);
+    o[2 * e + 1] = (int)e4m3_bytes((d[e] >> 4) & 0x0F0F0F0Fu, (d[e] >> 7) & 0x01010101u);
+  }
+  return o;
+}
+
 // fp16 scale unit as the one non-zero k of an outer product's operand
 __device__ __forceinline__ half4v scale_operand(uint32_t h) {
   return __builtin_bit_cast(half4v, make_uint2(h, 0u));
@@ -198,15 +212,95 @@ __device__ __forceinline__ void store_diff(double d2, double* red, int threads, 
   }
 }
 
+// ------------------------------------------------------------------------ INT3 codes beyond three bits
+// The quantizers write INT3 codes of -3 .. 3, but a nibble holds -8 .. 7, and an operand with any of them is
+// multiplied as it is (E2M1 holds neither 5 nor 7).  Packing marks the rows that hold such codes in the sign of
+// their factor, where the kernels meet it in the epilogue; on the row-major layout they look at every code.  A
+// workgroup that finds one computes its tile again with E4M3 operands straight from memory, over what it stored.
+// The sums are those of the kernel that calls, in its order (KS shares of the steps; every factor that differs is a
+// power of two), so rows without such codes keep their bits.  Groups are a multiple of 64.  Looking at every code
+// in the packed case as well took 13 to 20 % of a split tile's time and 2 to 5 of a large one's.
+enum WideTest : int { kWideNone = 0, kWideMarks = 1, kWideCodes = 2 };
+
+// nonzero bits under wide_mask: a code beyond three bits (its bits 3 and 2 differ), a marked row
+__device__ __forceinline__ uint32_t wide_codes(uint32_t d) { return d ^ (d << 1); }
+__device__ __forceinline__ uint32_t wide_mark(float mul) { return as_u32(mul); }
+constexpr uint32_t wide_mask(int test) { return test == kWideMarks ? 0x80000000u : 0x88888888u; }
+
+// whether any thread of the workgroup found one (called by all of them; also orders their stores before what
+// follows); flags: an int per wave of LDS that nothing else uses
+template <int WAVES>
+__device__ __forceinline__ bool any_wide(uint32_t wide, int* flags) {
+  const int mine = __any(wide != 0);
+  if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = mine;
+  __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int v = 0; v < WAVES; ++v) any |= flags[v];
+  return __builtin_amdgcn_readfirstlane(any) != 0;
+}
+
+template <int BM, int BN, int WAVES, int KS, int OUT>
+__device__ __forceinline__ void wide_codes_tile(const OperandView& A, const OperandView& W, int M, int N, int K,
+                                                int g_shift, int m0, int n0, const Output& out) {
+  static_assert(OUT != kOutDiff, "the selection quantizes its operands itself");
+  const int lane = threadIdx.x & 63;
+  const int row = lane & 31, half = lane >> 5;
+  const int ksteps = K / kBK;
+  const float16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
+                          0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  for (int b = threadIdx.x >> 6; b < BM / 32 * (BN / 32); b += WAVES) {
+    const int m = m0 + b % (BM / 32) * 32 + row, nb = n0 + b / (BM / 32) * 32;
+    const int64_t ar = min(m, M - 1), wr = min(nb + row, N - 1);
+    const uint8_t *ac = A.codes + ar * A.code_row + half * 16, *wc = W.codes + wr * W.code_row + half * 16;
+    const uint8_t *as = A.scales + ar * A.sc_row, *ws = W.scales + wr * W.sc_row;
+    float16_t sum = zero;
+#pragma unroll 1
+    for (int ks = 0; ks < KS; ++ks) {
+      float16_t acc = zero;
+#pragma unroll 1
+      for (int s = ks; s < ksteps; s += KS) {
+        const int64_t unit = (s * kBK) >> g_shift;
+        const uint4 a = *reinterpret_cast<const uint4*>(ac + (int64_t)s * A.code_step);
+        const uint4 w = *reinterpret_cast<const uint4*>(wc + (int64_t)s * W.code_step);
+        const uint32_t sa = *reinterpret_cast<const uint16_t*>(as + unit * A.sc_step);
+        const uint32_t sw = *reinterpret_cast<const uint16_t*>(ws + unit * W.sc_step);
+        const float16_t sc = __builtin_amdgcn_mfma_f32_32x32x8f16(scale_operand(half == 0 ? sw : 0u), scale_operand(sa),
+                                                                  zero, 0, 0, 0);
+        const float16_t p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(e4m3_operand(w), e4m3_operand(a), zero, 0, 0,
+                                                                            0, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = __builtin_fmaf(p[r], sc[r], acc[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[r] = ks == 0 ? acc[r] : sum[r] + acc[r];
+    }
+    if (m >= M) continue;
+    const float am = fabsf(A.mul[(int64_t)m * A.mul_stride]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int n = nb + r / 4 * 8 + half * 4 + r % 4;
+      if (n >= N) continue;
+      float v = (sum[r] * 262144.0f) * (am * fabsf(W.mul[(int64_t)n * W.mul_stride]));
+      if (W.bias) v += bf16_to_f32(W.bias[n]);
+      if constexpr (OUT == kOutF32)
+        reinterpret_cast<float*>(out.y)[(int64_t)m * out.ldy + n] = v;
+      else
+        reinterpret_cast<uint16_t*>(out.y)[(int64_t)m * out.ldy + n] = (uint16_t)cvt_pk_bf16(v, 0.0f);
+    }
+  }
+}
+
 // The accumulators of a workgroup's output tile, scaled and stored.  unit: a power of two that undoes the
-// operands' fixed code scale (1 where they have none; the product with it is exact).
-template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT>
+// operands' fixed code scale (1 where they have none; the product with it is exact).  INT: the factors are magnitudes,
+// their sign a mark (collected in marks).
+template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT, bool INT>
 __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsigned char* smem,
                                            const float* __restrict__ a_mul, int a_mul_stride,
                                            const float* __restrict__ w_mul, int w_mul_stride,
                                            const uint16_t* __restrict__ bias, int M, int N, int m0, int n0,
                                            int wave_m, int wave_n, int tm_cnt, int tid, float unit, int tile,
-                                           const Output& out) {
+                                           const Output& out, uint32_t& marks) {
   void* __restrict__ y = out.y;
   const int64_t ldy = out.ldy;
   double d2 = 0.0;
@@ -228,7 +322,9 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int n = n0 + wave_n * WTN + i * 32 + q * 8 + frag_half * 4 + e;
-        wm[i][q * 4 + e] = w_mul[(int64_t)(min(n, N - 1) * w_mul_stride)];
+        const float f = w_mul[(int64_t)(min(n, N - 1) * w_mul_stride)];
+        if (INT) marks |= wide_mark(f);
+        wm[i][q * 4 + e] = INT ? fabsf(f) : f;
         wb[i][q * 4 + e] = bias ? bf16_to_f32(bias[min(n, N - 1)]) : 0.0f;
       }
 #pragma unroll
@@ -236,7 +332,9 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
     if (RAGGED_M && j >= tm_cnt) break;         // wave-uniform
     const int ml = wave_m * WTM + j * 32 + frag_row;
     const int m = m0 + ml;
-    const float am = a_mul[(int64_t)(min(m, M - 1) * a_mul_stride)];
+    const float f = a_mul[(int64_t)(min(m, M - 1) * a_mul_stride)];
+    if (INT) marks |= wide_mark(f);
+    const float am = INT ? fabsf(f) : f;
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
 #pragma unroll
@@ -320,6 +418,7 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
   } else {
     v.mul = (const float*)(o + L.mul);
     v.mul_stride = 1;
+    v.marked = true;
   }
   return v;
 }

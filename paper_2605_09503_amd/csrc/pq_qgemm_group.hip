@@ -39,8 +39,9 @@
 
 namespace pq {
 
-// FP4: E2M1 codes (INT3), else E4M3 (INT4).  Groups are a multiple of 64 (2^g_shift).
-template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT>
+// FP4: E2M1 codes (INT3), else E4M3 (INT4).  Groups are a multiple of 64 (2^g_shift).  WIDE: how codes that E2M1 does
+// not hold are found.
+template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT, int WIDE>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView A, OperandView W, int M, int N,
                                                                     int K, int g_shift, Output out, int tiles_m,
                                                                     int tiles_n) {
@@ -127,10 +128,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   auto put_scale = [&](int sc, const Slice& s, bool ok, int q) {
     *reinterpret_cast<uint16_t*>(smem + sc + (ld_row + q * (T / 2)) * 2) = (uint16_t)(ok ? s.sc : 0u);
   };
+  uint32_t wide = 0;
   // 16-byte piece c of slice q: unpacked and stored
   auto put_piece = [&](const Slice& s, int codes, int q, int c) {
     const uint32_t d[4] = {s.codes.x, s.codes.y, s.codes.z, s.codes.w};
     if constexpr (FP4) {
+      if constexpr (WIDE == kWideCodes) wide |= wide_codes(d[0]) | wide_codes(d[1]) | wide_codes(d[2]) | wide_codes(d[3]);
       *reinterpret_cast<uint4*>(smem + (codes + st_off[q])) =
           make_uint4(e2m1_nibbles(d[0]), e2m1_nibbles(d[1]), e2m1_nibbles(d[2]), e2m1_nibbles(d[3]));
     } else {
@@ -305,20 +308,25 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   }
 
   __syncthreads();                                     // the output tile reuses the stages
-  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT>(
+  uint32_t marks = 0;
+  store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT, true>(
       acc, smem, A.mul, A.mul_stride, W.mul, W.mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid,
-      FP4 ? 4.0f : 262144.0f, tile_m * tiles_n + tile_n, out);
+      FP4 ? 4.0f : 262144.0f, tile_m * tiles_n + tile_n, out, marks);
+  if constexpr (WIDE != kWideNone) {                   // here, where the accumulators are dead
+    if (any_wide<T / 64>((WIDE == kWideMarks ? marks : wide) & wide_mask(WIDE), reinterpret_cast<int*>(smem + SMEM_BYTES)))
+      wide_codes_tile<BM, BN, T / 64, 1, OUT>(A, W, M, N, K, g_shift, m0, n0, out);
+  }
 }
 
-template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT>
+template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT, int WIDE>
 static int launch_group(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                         hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
   constexpr int A_ROWS = (BM * 2 + T - 1) / T * (T / 2);
   constexpr size_t stages = 4 * (size_t)(A_ROWS + BN) * ((FP4 ? 32 : 64) + 2);
   constexpr size_t tile_bytes = OUT != kOutBf16 ? 0 : (size_t)BM * (BN * 2 + 16);
-  constexpr size_t shmem = stages > tile_bytes ? stages : tile_bytes;
-  auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT>;
+  constexpr size_t shmem = (stages > tile_bytes ? stages : tile_bytes) + (WIDE != kWideNone ? WGM * WGN * 4 : 0);
+  auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT, WIDE>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_group_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -329,11 +337,11 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
   return check_hip(hipGetLastError(), "qgemm_group_kernel");
 }
 
-template <bool FP4, int OUT>
+template <bool FP4, int OUT, int WIDE>
 static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                       int choice, hipStream_t st) {
-  if (choice == kTile256) return launch_group<FP4, 256, 256, 2, 4, OUT>(A, W, M, N, K, g_shift, out, st);
-  return launch_group<FP4, 224, 256, 2, 4, OUT>(A, W, M, N, K, g_shift, out, st);
+  if (choice == kTile256) return launch_group<FP4, 256, 256, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+  return launch_group<FP4, 224, 256, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
 }
 
 // INT4 and INT3 with groups of 64, 128 or 256, large tiles
@@ -342,13 +350,18 @@ int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const Ope
   const int g_shift = group == 64 ? 6 : group == 128 ? 7 : 8;
 #define PQ_ARGS (A, W, M, N, K, g_shift, out, choice, st)
   if (fmt == PQ_FMT_INT4) {
-    if (out.kind == kOutF32) return group_tile<false, kOutF32> PQ_ARGS;
-    if (out.kind == kOutDiff) return group_tile<false, kOutDiff> PQ_ARGS;
-    return group_tile<false, kOutBf16> PQ_ARGS;
+    if (out.kind == kOutF32) return group_tile<false, kOutF32, kWideNone> PQ_ARGS;
+    if (out.kind == kOutDiff) return group_tile<false, kOutDiff, kWideNone> PQ_ARGS;
+    return group_tile<false, kOutBf16, kWideNone> PQ_ARGS;
   }
-  if (out.kind == kOutF32) return group_tile<true, kOutF32> PQ_ARGS;
-  if (out.kind == kOutDiff) return group_tile<true, kOutDiff> PQ_ARGS;
-  return group_tile<true, kOutBf16> PQ_ARGS;
+  // the selection (kOutDiff) multiplies what it quantized itself
+  if (out.kind == kOutDiff) return group_tile<true, kOutDiff, kWideNone> PQ_ARGS;
+  if (A.marked && W.marked) {
+    if (out.kind == kOutF32) return group_tile<true, kOutF32, kWideMarks> PQ_ARGS;
+    return group_tile<true, kOutBf16, kWideMarks> PQ_ARGS;
+  }
+  if (out.kind == kOutF32) return group_tile<true, kOutF32, kWideCodes> PQ_ARGS;
+  return group_tile<true, kOutBf16, kWideCodes> PQ_ARGS;
 #undef PQ_ARGS
 }
 

@@ -27,7 +27,8 @@ namespace pq {
 // the scales outside (pq_qgemm_group.hip)
 enum SplitMode : int { kSplitNvfp4 = 0, kSplitInt = 1, kSplitE2m1 = 2 };
 
-template <int MODE, int TM, int TN, int KS, int OUT>
+// WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
 __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, OperandView W, int M, int N,
                                                                       int K, int g_shift, Output out, int tiles_m,
                                                                       int tiles_n) {
@@ -36,7 +37,7 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
   constexpr bool CODES = MODE == kSplitE2m1;
   constexpr int PD = 2;                                // own steps in flight
   constexpr int ROW = 32 + 4;                          // floats of a partial sum's row in LDS
-  extern __shared__ __attribute__((aligned(16))) float part[];        // [KS][BM][ROW]: one 32-column strip
+  extern __shared__ __attribute__((aligned(16))) float part[];        // [KS][BM][ROW]: one 32-column strip; then [KS] flags
 
   int tile_m, tile_n;
   assign_tile(tiles_m, tiles_n, tile_m, tile_n);
@@ -101,6 +102,7 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
+  uint32_t wide = 0;
   auto multiply = [&](const Step& f, int step) {
     const bool k_ok = step * kBK + frag_half * 32 < K;
     if constexpr (!CODES) {
@@ -135,6 +137,7 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
       int8v x[TM], w[TN];
       half4v sx[TM], sw[TN];
       auto codes = [&](const uint4& c) {
+        if constexpr (WIDE == kWideCodes) wide |= wide_codes(c.x) | wide_codes(c.y) | wide_codes(c.z) | wide_codes(c.w);
         return (int8v){(int)e2m1_nibbles(c.x), (int)e2m1_nibbles(c.y), (int)e2m1_nibbles(c.z), (int)e2m1_nibbles(c.w),
                        0, 0, 0, 0};
       };
@@ -206,11 +209,17 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = s == 0 ? t[e] : v[e] + t[e];
       }
-      const float am = A.mul[(int64_t)m * A.mul_stride];
+      constexpr bool INT = MODE != kSplitNvfp4;         // factors of magnitude, the sign a mark
+      float am = A.mul[(int64_t)m * A.mul_stride];
+      if constexpr (WIDE == kWideMarks) wide |= wide_mark(am);
+      if constexpr (INT) am = fabsf(am);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int nn = min(n + e, N - 1);
-        v[e] = (v[e] * unit) * (am * W.mul[(int64_t)nn * W.mul_stride]);
+        float wm = W.mul[(int64_t)nn * W.mul_stride];
+        if constexpr (WIDE == kWideMarks) wide |= wide_mark(wm);
+        if constexpr (INT) wm = fabsf(wm);
+        v[e] = (v[e] * unit) * (am * wm);
         if (bias) v[e] += bf16_to_f32(bias[nn]);
       }
       if constexpr (OUT == kOutDiff) {
@@ -246,19 +255,24 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
         }
       }
     }
-  }  if constexpr (OUT == kOutDiff) {
+  }
+  if constexpr (OUT == kOutDiff) {
     __syncthreads();                                   // the partial sums have been read
     store_diff(d2, reinterpret_cast<double*>(part), T, tile_m * tiles_n + tile_n, out);
   }
+  if constexpr (WIDE != kWideNone) {                   // here, where the accumulators are dead
+    if (any_wide<KS>(wide & wide_mask(WIDE), reinterpret_cast<int*>(part + (size_t)KS * BM * ROW)))
+      wide_codes_tile<BM, BN, KS, KS, OUT>(A, W, M, N, K, g_shift, m0, n0, out);
+  }
 }
 
-template <int MODE, int TM, int TN, int KS, int OUT>
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
 static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
-  constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4;
+  constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4 + (WIDE != kWideNone ? KS * 4 : 0);
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
-  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT>;
+  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_split_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -269,27 +283,31 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   return check_hip(hipGetLastError(), "qgemm_split_kernel");
 }
 
-template <int MODE, int OUT>
+template <int MODE, int OUT, int WIDE>
 static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                       int tile, hipStream_t st) {
   switch (tile) {
-    case kTileSplit32: return launch_split<MODE, 1, 1, 8, OUT>(A, W, M, N, K, g_shift, out, st);
-    case kTileSplit64x32: return launch_split<MODE, 2, 1, 8, OUT>(A, W, M, N, K, g_shift, out, st);
-    case kTileSplit64: return launch_split<MODE, 2, 2, 4, OUT>(A, W, M, N, K, g_shift, out, st);
-    default: return launch_split<MODE, 2, 3, 4, OUT>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit32: return launch_split<MODE, 1, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64x32: return launch_split<MODE, 2, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64: return launch_split<MODE, 2, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    default: return launch_split<MODE, 2, 3, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
   }
 }
 
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Output& out, int tile, hipStream_t st) {
   const int g_shift = fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
-#define PQ_SPLIT(MODE)                                                                                   \
-  return out.kind == kOutF32    ? split_tile<MODE, kOutF32>(A, W, M, N, K, g_shift, out, tile, st)        \
-         : out.kind == kOutDiff ? split_tile<MODE, kOutDiff>(A, W, M, N, K, g_shift, out, tile, st)       \
-                                : split_tile<MODE, kOutBf16>(A, W, M, N, K, g_shift, out, tile, st)
-  if (fmt == PQ_FMT_NVFP4) PQ_SPLIT(kSplitNvfp4);
-  if (fmt == PQ_FMT_INT3 && group != 32) PQ_SPLIT(kSplitE2m1);
-  PQ_SPLIT(kSplitInt);
+#define PQ_SPLIT(MODE, WIDE)                                                                                     \
+  return out.kind == kOutF32    ? split_tile<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st)          \
+         : out.kind == kOutDiff ? split_tile<MODE, kOutDiff, kWideNone>(A, W, M, N, K, g_shift, out, tile, st)    \
+                                : split_tile<MODE, kOutBf16, WIDE>(A, W, M, N, K, g_shift, out, tile, st)
+  if (fmt == PQ_FMT_NVFP4) PQ_SPLIT(kSplitNvfp4, kWideNone);
+  if (fmt == PQ_FMT_INT3 && group != 32) {
+    // the selection (kOutDiff) multiplies what it quantized itself
+    if (A.marked && W.marked) PQ_SPLIT(kSplitE2m1, kWideMarks);
+    PQ_SPLIT(kSplitE2m1, kWideCodes);
+  }
+  PQ_SPLIT(kSplitInt, kWideNone);
 #undef PQ_SPLIT
 }
 

@@ -674,6 +674,60 @@ def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     assert torch.equal(y, y_packed)
 
 
+@pytest.mark.parametrize("g,M,N,K", [
+    (64, 33, 41, 64), (256, 70, 3000, 256), (64, 1500, 1003, 320), (256, 300, 4087, 768),      # waves split K
+    (256, 1500, 2056, 256),                                                                    # 128 x 128
+    (128, 2304, 3584, 512), (64, 4090, 4087, 320),                                             # 224 and 256 x 256
+])
+def test_qgemm_int3_multiplies_every_nibble(g, M, N, K):
+    # INT3 codes beyond the three bits that the quantizers write, -8 .. 7, are multiplied as they are, packed and
+    # row-major to the same bits.  All scales 1, so the accumulator holds Q^2 times the integer product (|.| <= 64 * 768,
+    # times 9) exactly and the epilogue rounds at most three times.  With such codes in a few rows of either operand
+    # (K's first, middle or last nibble), the other outputs keep the bits they have without them.
+    rng = np.random.default_rng(935 + g + M)
+    sa = torch.ones((M, K // g), dtype=torch.float32, device=DEV)
+    sw = torch.ones((N, K // g), dtype=torch.float32, device=DEV)
+
+    def product(za, zw, bias=None):
+        a_codes = torch.from_numpy(OF.pack_nibbles(OF.int_to_nibble(za))).to(DEV)
+        w_codes = torch.from_numpy(OF.pack_nibbles(OF.int_to_nibble(zw))).to(DEV)
+        a_op, w_op = pq.pq_pack_operand(pq.FMT_INT3, g, a_codes, sa), pq.pq_pack_operand(pq.FMT_INT3, g, w_codes, sw)
+        ldy = (N + 7) // 8 * 8
+        ys = [torch.full((M, ldy), 777.0, dtype=dt, device=DEV) for dt in (torch.float32, torch.float32, torch.bfloat16, torch.bfloat16)]
+        pq.pq_qgemm_f32(pq.FMT_INT3, g, a_codes, sa, None, w_codes, sw, None, ys[0], M=M, N=N, K=K, ldy=ldy)
+        pq.pq_qgemm_packed_f32(pq.FMT_INT3, g, a_op, None, w_op, None, ys[1], M, N, K, ldy=ldy)
+        pq.pq_qgemm(pq.FMT_INT3, g, a_codes, sa, None, w_codes, sw, None, ys[2], M=M, N=N, K=K, ldy=ldy)
+        if bias is None:
+            pq.pq_qgemm_packed(pq.FMT_INT3, g, a_op, None, w_op, None, ys[3], M, N, K, ldy=ldy)
+        else:
+            pq.pq_qgemm_packed_bias(pq.FMT_INT3, g, a_op, None, w_op, None, bias, ys[3], M, N, K, ldy=ldy)
+        torch.cuda.synchronize()
+        assert all(torch.all(y[:, N:] == 777.0) for y in ys)
+        return [y[:, :N] for y in ys]
+
+    za, zw = rng.integers(-8, 8, size=(M, K)), rng.integers(-8, 8, size=(N, K))
+    want = (za.astype(np.float64) @ zw.T.astype(np.float64)).astype(np.float32)
+    bias = torch.from_numpy(rng.standard_normal(N)).to(torch.bfloat16).to(DEV)
+    y, y_packed, yb, yb_bias = product(za, zw, bias)
+    np.testing.assert_allclose(y.cpu().numpy(), want, rtol=3 * 2.0 ** -24, atol=0)
+    assert torch.equal(y, y_packed) and torch.equal(yb, y.to(torch.bfloat16))
+    assert torch.equal(yb_bias, (y + bias.float()).to(torch.bfloat16))
+
+    za, zw = rng.integers(-4, 4, size=(M, K)), rng.integers(-4, 4, size=(N, K))
+    plain = product(za, zw)
+    rows, cols = [0, M - 1, M // 2], [0, N - 1, N // 3]
+    for i, v in enumerate((7, -8, 5)):
+        za[rows[i], [0, K // 2, K - 1][i]] = v
+        zw[cols[i], [K - 1, 0, K // 2][i]] = v
+    got = product(za, zw)
+    want = (za.astype(np.float64) @ zw.T.astype(np.float64)).astype(np.float32)
+    np.testing.assert_allclose(got[0].cpu().numpy(), want, rtol=3 * 2.0 ** -24, atol=0)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[2], got[3]) and torch.equal(got[2], got[0].to(torch.bfloat16))
+    m, n = np.setdiff1d(np.arange(M), rows), np.setdiff1d(np.arange(N), cols)
+    for p, q in zip(plain, got):
+        assert torch.equal(p[m][:, n], q[m][:, n])
+
+
 @pytest.mark.parametrize("fmt,g,K", [(pq.FMT_NVFP4, 16, 96), (pq.FMT_INT4, 64, 192), (pq.FMT_INT3, 256, 256)])
 def test_qgemm_128_tile(fmt, g, K):
     # few steps and some 200 tiles of 128 x 128; ragged rows and columns
