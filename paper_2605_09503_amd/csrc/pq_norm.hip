@@ -697,14 +697,16 @@ int launch_norm_team(const void* x, int64_t rows, int64_t K, int64_t ld, const f
 // One wave per row up to kWideRow channels; wider rows are shared by the kWideTeam waves of a workgroup
 // (a wave alone would leave a compute unit with two or three rows in flight).  So are the rows of a launch too
 // short to give every unit several of them: a row's chain of loads, passes and gathers is then what takes the time,
-// and four waves walk it four times as fast.  Measured, one wave -> four, us, K = 3072: RMSNorm + NVFP4 256 rows
-// 7.1 -> 5.4, 512 rows 7.2 -> 6.2, 768 rows 7.2 -> 7.0, 1024 rows 7.3 -> 8.0; Hadamard + INT4 256 rows 10.8 -> 5.8, 512
-// rows 10.9 -> 6.5, 768 rows 11.0 -> 7.6, 1024 rows 11.0 (9.5 with fewer rows a workgroup) -> 10.6.  Below 1024
-// channels a row has less than two chunks for each of 256 lanes (512 x 768: 4.7 -> 5.0).
+// and four waves walk it four times as fast.  Measured, one wave -> four, us: RMSNorm + NVFP4, K = 3072, 256 rows
+// 7.1 -> 5.4, 512 rows 7.2 -> 6.2, 768 rows 7.2 -> 7.0, 1024 rows 7.3 -> 8.0; K = 1024, where a lane has half a chunk
+// of the row, 256 rows 4.9 -> 4.5 (LayerNorm 6.1 -> 5.7), 384 rows 4.9 -> 5.0 (6.1 -> 6.3), 512 rows 4.9 -> 5.0 (6.2 ->
+// 6.4); K = 1152, 512 rows 5.3 -> 5.1 (7.1 -> 6.5).  Hadamard + INT4, K = 3072, 256 rows 10.8 -> 5.8, 512 rows 10.9 ->
+// 6.5, 768 rows 11.0 -> 7.6, 1024 rows 11.0 (9.5 with fewer rows a workgroup) -> 10.6; K = 1024, 768 rows 9.0 -> 7.2.
+// Below 1024 channels nothing is gained (512 x 768: 4.7 -> 5.0).
 template <int FMT, int G, int NORM>
 int launch_norm_rows(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts, const OperandLayout& L,
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
-  const bool few = rows <= (NORM == kHadamard ? 768 : 512) && K >= 1024;
+  const bool few = rows <= (NORM == kHadamard ? 768 : K > 1024 ? 512 : 256) && K >= 1024;
   if (K > kWideRow || few) return launch_norm_team<FMT, G, NORM, kWideTeam>(x, rows, K, ld, ts, L, operand, na, st);
   return launch_norm_team<FMT, G, NORM, 1>(x, rows, K, ld, ts, L, operand, na, st);
 }

@@ -317,10 +317,12 @@ def test_wide_rows_share_a_workgroup(kind, rows, K, rows_per_mod):
 
 
 @pytest.mark.parametrize("kind", [RMS, ADALN])
-@pytest.mark.parametrize("rows,K", [(512, 1024), (513, 1024), (512, 1016), (40, 1024), (513, 3072)])
+@pytest.mark.parametrize("rows,K", [(512, 1024), (513, 1024), (512, 1016), (40, 1024), (513, 3072),
+                                    (256, 1024), (257, 1024), (512, 1032), (513, 1032), (512, 1280), (513, 1280)])
 def test_rows_at_the_edge_of_a_short_launch(kind, rows, K):
-    """Up to 512 rows of 1024 channels and more are shared by four waves, the others walked by one: results as the
-    oracle's on both sides of the line, and the quantizing call still equals norm followed by quantizer."""
+    """Up to 512 rows of more than 1024 channels, and 256 of 1024, are shared by four waves, the others walked by one:
+    results as the oracle's on both sides of the line, and the quantizing call still equals norm followed by
+    quantizer."""
     rng = np.random.default_rng(9500 + rows + K + kind)
     x_bits = _activations(rng, rows, K)
     perm = rng.permutation(K).astype(np.int32)
