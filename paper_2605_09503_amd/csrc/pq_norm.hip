@@ -647,8 +647,10 @@ int norm_waves_per_group(Kern kern, int norm, bool is_int, int64_t rows, int64_t
     // time ~ rounds x (row work + vector staging shared by w rows), in units of one row's work, plus what the
     // rows that meet on the busiest of the 256 units cost each other (the transform's passes share the unit's
     // LDS: 512 x 4096 takes 26 us with eight rows a workgroup on 64 units, 13 with two on 256; 1024 x 3072 10.6 and
-    // 8.9; RMSNorm 1024 x 3072 7.3 and 7.1); among equal costs prefer more waves in flight per compute unit
-    const double crowd = (norm == kHadamard ? 0.06 : 0.012) * (double)((groups + 255) / 256 * w);
+    // 8.9; the norms less: modulated LayerNorm 1024 x 3072 8.7 and 8.1, RMSNorm + NVFP4 7.4 and 7.3, where one round
+    // holds the launch: beyond it 4608 x 4096 lost 2 to 3 %, and with 0.012 RMSNorm + INT4 1280 x 3072 7.9 -> 8.2); among equal costs prefer more waves in flight per compute unit
+    const double shared = norm == kHadamard ? 0.06 : rounds == 1 ? 0.008 : 0.0;
+    const double crowd = shared * (double)((groups + 255) / 256 * w);
     const double cost = (double)rounds * (1.0 + 0.35 / w) + crowd - 1e-3 * (double)std::min(per_cu * w, 32);
     if (cost < best_cost) best_cost = cost, best = w;
   }
