@@ -276,9 +276,10 @@ int pq_quantize_act(pq_format fmt, int group, const void* x_bf16, int64_t M, int
  * the 2^-24 rounding of h / Q per factor).  Scales of another origin give a different product without an
  * error: check them once with pq_qgemm_check_int_scales.  Codes are multiplied as the nibbles they are, -8 .. 7,
  * also where the quantizers write less (INT3: -3 .. 3; a row with codes outside -4 .. 3 is slower with groups of 64
- * and more, whose products take the codes in a form that holds no more than that).  Inside a row the operand holds h * 2^-E with E from the row's largest
- * group: a group more than 2^24 below it loses low bits of h (below 2^-35: all of them) -- its terms
- * are then below 2^-24 of the row's largest terms, the resolution of the fp32 accumulation anyway.
+ * and more, whose products take the codes in a form that holds no more than that).  Inside a row the operand holds
+ * h * 2^-E with E from the row's largest group: a group more than 2^24 below it loses low bits of h (below 2^-35:
+ * all of them) -- its terms are then below 2^-24 of the row's largest terms, the resolution of the fp32
+ * accumulation anyway.
  * workspace: pq_workspace_bytes(PQ_OP_QGEMM, fmt, group, M, N, K, 0) bytes.
  */
 int pq_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_scales,
@@ -317,6 +318,12 @@ int pq_qgemm_f32(pq_format fmt, int group, const uint8_t* a_codes, const void* a
                  const float* a_tensor_scale, const uint8_t* w_codes, const void* w_scales,
                  const float* w_tensor_scale, int64_t M, int64_t N, int64_t K, float* y_f32,
                  int64_t ldy, void* workspace, size_t workspace_bytes, void* stream);
+
+/* The output tile (rows x columns of Y a workgroup computes) that a product of this shape takes: 256 x 256, 224 x 256,
+ * 128 x 128, or one of 64 x 96, 64 x 64, 64 x 32 and 32 x 32 whose waves split K.  Host only.  K is added in fp32 in
+ * an order that is fixed for a tile and differs between them, so a row of Y is the same bits from run to run but may
+ * differ by the rounding of that sum between calls with other M or N.                                          */
+int pq_qgemm_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int* tile_m, int* tile_n);
 
 /*
  * The same product from operands in the GEMM's own layout (paper Eq. 8; Sec. 3.3: the weights

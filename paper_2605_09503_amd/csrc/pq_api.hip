@@ -327,6 +327,16 @@ int pq_qgemm_f32(pq_format fmt, int group, const uint8_t* a_codes, const void* a
                       w_tensor_scale, M, N, K, y_f32, ldy, true, 3, workspace, workspace_bytes, stream);
 }
 
+int pq_qgemm_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int* tile_m, int* tile_n) {
+  if (!tile_m || !tile_n) return fail(PQ_ERR_NULL, "pq_qgemm_tile: a required pointer is NULL");
+  int rc = check_format(fmt, group, K);
+  if (rc) return rc;
+  if (M <= 0 || N <= 0 || K % 32 || M > (1 << 24) || N > (1 << 24) || K > (1 << 24))
+    return fail(PQ_ERR_SHAPE, "pq_qgemm_tile: no product of M=%lld N=%lld K=%lld", (long long)M, (long long)N, (long long)K);
+  tile_size(choose_tile(fmt, group, M, N, K), tile_m, tile_n);
+  return PQ_OK;
+}
+
 size_t pq_operand_bytes(pq_format fmt, int group, int64_t rows, int64_t K) {
   if (check_format(fmt, group, K) || rows <= 0 || K % 32) return 0;
   return operand_bytes(fmt, group, rows, K);

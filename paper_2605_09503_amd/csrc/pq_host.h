@@ -64,6 +64,10 @@ constexpr size_t kPanelRowLds = 65536 * 2 + 65536 / 32 * 4;
 int launch_quantize_rows_panel(pq_format fmt, int group, const void* x, int64_t rows, int64_t K, const int32_t* perm,
                                const float* ts, void* operand, hipStream_t st);
 
+// output tile of the product that a shape takes, and its size (pq_qgemm_tile.hip)
+int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K);
+void tile_size(int tile, int* bm, int* bn);
+
 // The error evaluation keeps one row as fp32 in LDS, one spare slot per eight channels: 4.5 K bytes of the
 // 150 KB a workgroup may take.
 constexpr int64_t kSelectMaxK = 34128;      // largest multiple of 16 with 4.5 K <= 150 * 1024

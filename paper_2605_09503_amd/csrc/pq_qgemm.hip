@@ -2,7 +2,7 @@
 //     Y[m, n] = Ta Tw sum_g sa[m, g] sw[n, g] sum_{k in g} a[m, k] w[n, k]
 //
 // Design for gfx950.  Large outputs are computed here, those of the integer formats with groups of 64 and more in
-// pq_qgemm_group.hip, small outputs in pq_qgemm_split.hip; choose_tile says which.
+// pq_qgemm_group.hip, small outputs in pq_qgemm_split.hip; choose_tile (pq_qgemm_tile.hip) says which.
 // The contraction runs on the fp16 MFMA (v_mfma_f32_32x32x16_f16, fp32
 // accumulate).  Both operands stay 4-bit in HBM and L2; a workgroup unpacks its A and W tiles
 // once per K step straight into fp16 values that already carry the per-group scale, and stages
@@ -415,61 +415,6 @@ static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N,
   return check_hip(hipGetLastError(), "qgemm_kernel");
 }
 
-// Tile choice: the tile with the shortest predicted time.  n workgroups run on 256 compute units, each does s
-// 64-wide steps; with c = ceil(n / 256) rounds and r = max(n / 256, 1) of them really filled,
-//     time = l0 + rounds * (a + b s),  rounds = th c + (1 - th) r,  and for the split and 128-row tiles, whose
-//     workgroups share a unit, at least l0 + l1 s, the latency of one workgroup's chain of steps.
-// The coefficients (us) are least-squares fits of the logarithm of measured times, graph replays of 20 launches,
-// over 235 shapes of 1e7 to 6e11 operations with every size drawn over its range (16 to 8192 rows, 128 to 12288
-// columns, K 160 to 12288, 40 % of the larger ones round sizes): the fit is 3 to 5 % off for the split tiles and 5 to
-// 11 % for the others (whose clock depends on how much of the chip they fill), and the choices cost 1.5 % over the
-// best tile of each shape.  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
-// 1024 x 3072 22 | 30 (of 128 x 128), 2048 x 3072 41 | 47, 4608 x 3072 92 | 79.
-struct TileCost {
-  float a, b, l0, l1, th;
-};
-struct TileSize {
-  int bm, bn;
-};
-static constexpr TileSize kTileSize[] = {{0, 0}, {256, 256}, {128, 128}, {224, 256}, {32, 32}, {64, 32}, {64, 64}, {64, 96}};
-// rows: NVFP4; INT4 and INT3 with groups of 32; INT4 and INT3 with larger groups.  Columns: the tiles in the order of
-// their numbers.
-static constexpr TileCost kTileCost[4][8] = {
-    {{}, {10.5f, 1.200f, 0.0f, 0.0f, 1.0f}, {2.43f, 0.496f, 4.17f, 0.202f, 0.54f}, {10.0f, 1.107f, 0.0f, 0.0f, 1.0f},
-     {0.52f, 0.0523f, 2.86f, 0.063f, 1.0f}, {1.06f, 0.0768f, 2.44f, 0.077f, 0.88f}, {1.08f, 0.119f, 3.38f, 0.153f, 0.83f},
-     {2.09f, 0.163f, 3.37f, 0.195f, 0.64f}},
-    {{}, {10.9f, 1.277f, 0.0f, 0.0f, 1.0f}, {2.12f, 0.564f, 4.03f, 0.330f, 0.47f}, {10.9f, 1.164f, 0.0f, 0.0f, 1.0f},
-     {0.51f, 0.0643f, 2.99f, 0.059f, 1.0f}, {1.06f, 0.0940f, 2.73f, 0.097f, 1.0f}, {1.10f, 0.144f, 3.39f, 0.158f, 0.80f},
-     {2.23f, 0.194f, 3.31f, 0.226f, 0.71f}},
-    {{}, {11.0f, 1.272f, 2.65f, 0.0f, 1.0f}, {2.19f, 0.540f, 5.31f, 0.567f, 0.50f}, {9.4f, 1.183f, 3.32f, 0.0f, 1.0f},
-     {0.51f, 0.0643f, 2.99f, 0.059f, 1.0f}, {1.06f, 0.0923f, 2.55f, 0.097f, 1.0f}, {1.09f, 0.140f, 3.49f, 0.158f, 0.85f},
-     {2.22f, 0.188f, 3.44f, 0.225f, 0.65f}},
-    {{}, {10.8f, 0.933f, 0.0f, 0.0f, 1.0f}, {1.81f, 0.528f, 5.44f, 0.147f, 0.51f}, {9.95f, 0.837f, 0.31f, 0.0f, 1.0f},
-     {0.68f, 0.0325f, 2.81f, 0.044f, 0.84f}, {1.24f, 0.0447f, 2.43f, 0.065f, 0.85f}, {1.23f, 0.0752f, 3.74f, 0.155f, 0.83f},
-     {2.39f, 0.107f, 3.91f, 0.176f, 0.75f}},
-};
-
-static int choose_tile(pq_format fmt, int group, int M, int N, int K) {
-  const int cls = fmt == PQ_FMT_NVFP4 ? 0 : group == 32 ? 1 : fmt == PQ_FMT_INT4 ? 2 : 3;
-  const float s = (float)((K + kBK - 1) / kBK);
-  int best = kTile256;
-  float best_t = 0.0f;
-  for (int t = kTile256; t <= kTileSplit64x96; ++t) {
-    const TileCost& k = kTileCost[cls][t];
-    const TileSize& z = kTileSize[t];
-    const int64_t n = (int64_t)((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn);
-    const float c = (float)((n + 255) / 256), r = n > 256 ? (float)n / 256.0f : 1.0f;
-    float time = (k.th * c + (1.0f - k.th) * r) * (k.a + k.b * s);
-    if (time < k.l1 * s) time = k.l1 * s;
-    time += k.l0;
-    if (t == kTile256 || time < best_t) {
-      best = t;
-      best_t = time;
-    }
-  }
-  return best;
-}
-
 template <int FMT, int G, int OUT>
 static int pick_tile(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out,
                      int choice, hipStream_t st) {
@@ -488,15 +433,10 @@ static int launch_views_fg(const OperandView& A, const OperandView& W, int M, in
   return pick_tile<FMT, G, kOutBf16>(A, W, M, N, K, out, tile, st);
 }
 
-int64_t qgemm_tiles(pq_format fmt, int group, int64_t M, int64_t N, int64_t K) {
-  const TileSize& z = kTileSize[choose_tile(fmt, group, (int)M, (int)N, (int)K)];
-  return ((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn);
-}
-
 // the product kernel on two operand views (any mix of layouts)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
                        int64_t N, int64_t K, const Output& out, hipStream_t st) {
-  const int tile = choose_tile(fmt, group, (int)M, (int)N, (int)K);
+  const int tile = choose_tile(fmt, group, M, N, K);
   if (tile >= kTileSplit32)
     return launch_qgemm_split(fmt, group, A, W, (int)M, (int)N, (int)K, out, tile, st);
   // groups of 64 and more in large tiles: the codes go to the matrix unit as they are

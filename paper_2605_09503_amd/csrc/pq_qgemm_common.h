@@ -432,7 +432,7 @@ int64_t qgemm_tiles(pq_format fmt, int group, int64_t M, int64_t N, int64_t K);
 int run_qgemm_packed_out(pq_format fmt, int group, const void* a_operand, const float* a_ts, const void* w_operand,
                          const float* w_ts, int64_t M, int64_t N, int64_t K, const void* bias, const Output& out,
                          hipStream_t st);
-// output tiles of the product kernels (choose_tile in pq_qgemm.hip)
+// output tiles of the product kernels (choose_tile in pq_qgemm_tile.hip)
 enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kTileSplit64x32 = 5, kTileSplit64 = 6, kTileSplit64x96 = 7 };
 // small outputs (pq_qgemm_split.hip)
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,

@@ -84,6 +84,7 @@ def load():
     lib.pq_qgemm_f32.argtypes = gemm_args
     lib.pq_qgemm_run.argtypes = gemm_args
     lib.pq_qgemm_prep.argtypes = [i32, i32, vp, vp, i64, i64, i64, vp, sz, vp]
+    lib.pq_qgemm_tile.argtypes = [i32, i32, i64, i64, i64, C.POINTER(i32), C.POINTER(i32)]
     lib.pq_operand_bytes.restype = sz
     lib.pq_operand_bytes.argtypes = [i32, i32, i64, i64]
     lib.pq_pack_operand.argtypes = [i32, i32, vp, vp, i64, i64, vp, sz, vp]
@@ -336,6 +337,13 @@ def pq_qgemm_f32(fmt: int, group: int, a_codes, a_scales, a_tensor_scale, w_code
     """Same product, fp32 output (accumulator before the bf16 rounding)."""
     _gemm(load().pq_qgemm_f32, fmt, group, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
           w_tensor_scale, y, workspace, M, N, K, ldy)
+
+
+def pq_qgemm_tile(fmt: int, group: int, M: int, N: int, K: int):
+    """(rows, columns) of the output tile that a product of this shape takes."""
+    m, n = C.c_int(), C.c_int()
+    _check(load().pq_qgemm_tile(fmt, group, M, N, K, C.byref(m), C.byref(n)))
+    return m.value, n.value
 
 
 def pq_operand_bytes(fmt: int, group: int, rows: int, K: int) -> int:

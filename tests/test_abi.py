@@ -354,3 +354,29 @@ def test_header_is_plain_c_and_links(tmp_path, lib):
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "NULL" in r.stdout
+
+
+def test_qgemm_tile_validation(lib):
+    m, n = C.c_int(), C.c_int()
+    f = lib.pq_qgemm_tile
+    assert f(pq.FMT_INT4, 64, 8, 8, 64, None, C.byref(n)) == PQ_ERR_NULL
+    assert f(pq.FMT_INT4, 48, 8, 8, 96, C.byref(m), C.byref(n)) == PQ_ERR_FORMAT
+    assert f(pq.FMT_INT4, 64, 8, 8, 96, C.byref(m), C.byref(n)) == PQ_ERR_SHAPE
+    assert f(pq.FMT_NVFP4, 16, 8, 8, 48, C.byref(m), C.byref(n)) == PQ_ERR_SHAPE
+    assert f(pq.FMT_NVFP4, 16, 0, 8, 64, C.byref(m), C.byref(n)) == PQ_ERR_SHAPE
+    assert f(pq.FMT_NVFP4, 16, 1 << 24, 1 << 24, 1 << 24, C.byref(m), C.byref(n)) == 0 and (m.value, n.value) == (256, 256)
+
+
+# tiles measured within 2 % of the fastest one; columns past the last whole eight are what a large tile pays most for
+@pytest.mark.parametrize("fmt,g,M,N,K,tiles", [
+    (pq.FMT_INT3, 64, 2892, 2765, 832, {(64, 64)}),                # 224 x 256: 26.6 us, 128 x 128 24.4, 64 x 64 21.7
+    (pq.FMT_INT4, 32, 4608, 4608, 384, {(224, 256)}),              # 128 x 128: 32.8 us, 224 x 256 31.8
+    (pq.FMT_INT3, 32, 4608, 4608, 384, {(224, 256)}),
+    (pq.FMT_INT3, 128, 1320, 5726, 768, {(64, 64)}),               # 224 x 256: 26.4 us, 64 x 64 20.5
+    (pq.FMT_INT3, 32, 5653, 3430, 1312, {(128, 128)}),             # 224 x 256: 78.3 us, 128 x 128 69.4
+    (pq.FMT_NVFP4, 16, 2835, 6592, 1376, {(128, 128)}),            # 224 x 256: 68.0 us, 128 x 128 63.5
+    (pq.FMT_NVFP4, 16, 4608, 9216, 3072, {(256, 256), (224, 256)}),
+    (pq.FMT_NVFP4, 16, 256, 512, 512, {(32, 32)}),
+])
+def test_qgemm_tile_of_measured_shapes(lib, fmt, g, M, N, K, tiles):
+    assert pq.pq_qgemm_tile(fmt, g, M, N, K) in tiles
