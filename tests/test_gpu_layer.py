@@ -176,13 +176,19 @@ def test_forward_path_replays_from_a_captured_graph():
         assert torch.equal(y.view(torch.int16), y_eager.view(torch.int16)), "replay %d differs" % i
 
 
-@pytest.mark.parametrize("fmt,g,M,N,K", [(pq.FMT_NVFP4, 16, 300, 264, 1088), (pq.FMT_INT4, 64, 520, 200, 1024),
-                                          (pq.FMT_NVFP4, 16, 4608, 512, 12288)])
-def test_forward_path_in_a_hip_graph(fmt, g, M, N, K):
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_NVFP4, 16, 300, 264, 1088, (32, 32)), (pq.FMT_INT4, 64, 520, 200, 1024, (32, 32)),
+    (pq.FMT_NVFP4, 16, 4608, 512, 12288, (64, 96)), (pq.FMT_NVFP4, 16, 4608, 3072, 3072, (224, 256)),
+    (pq.FMT_INT3, 32, 3600, 4088, 192, (256, 256)), (pq.FMT_INT4, 64, 2344, 3656, 256, (224, 256)),
+    (pq.FMT_INT3, 64, 4090, 4088, 320, (256, 256)),
+])
+def test_forward_path_in_a_hip_graph(fmt, g, M, N, K, tile):
     """The deployment path (activations quantized straight into the GEMM's operand layout, then the product)
     captured into a HIP graph: every replay, with eager work and synchronisations in between, gives the
     bits of the eager run.  Nothing in the two calls allocates, synchronises or clears memory, so they can be
-    captured as they are.  (The third shape takes the large-tensor quantizer and the 224 x 256 product tile.)"""
+    captured as they are.  (The third shape takes the large-tensor quantizer; the last four the large tiles of the two
+    product kernels.)"""
+    assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile, "this shape is here for the tile it takes: choose another"
     _say("forward path in a graph fmt=%d g=%d %dx%dx%d" % (fmt, g, M, N, K))
     rng = np.random.default_rng(9970 + g + M)
     x = _dev(_bits(rng.standard_normal((M, K)) * np.exp(0.5 * rng.standard_normal(K))))

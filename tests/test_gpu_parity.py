@@ -24,9 +24,18 @@ FMTS = [(pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64), (pq.FMT_INT4, 32), (pq.FMT_INT3, 
         (pq.FMT_INT4, 128), (pq.FMT_INT3, 256)]
 
 
+# output tiles of the product kernels: codes or fp16 operands staged in LDS, and the four whose waves split K
+T256, T224, T128 = (256, 256), (224, 256), (128, 128)
+S32, S64X32, S64, S64X96 = (32, 32), (64, 32), (64, 64), (64, 96)
+
+
 def _say(msg):
     print(msg, flush=True)
     sys.stdout.flush()
+
+
+def _takes(tile, fmt, g, M, N, K):
+    assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile, "this shape is here for the tile it takes: choose another"
 
 
 def _rand_bits(rng, rows, K, spread=2.0, outliers=4):
@@ -357,14 +366,22 @@ def test_select_perm_output_error_matches_oracle(name, fmt, g, M, N, K, nb):
     np.testing.assert_array_equal(perm_out.cpu().numpy(), np.arange(K))
 
 
-@pytest.mark.parametrize("fmt,g,M,N,K", [
-    (pq.FMT_NVFP4, 16, 4090, 4087, 160), (pq.FMT_NVFP4, 16, 2304, 3656, 288), (pq.FMT_NVFP4, 16, 1500, 2056, 96),
-    (pq.FMT_INT4, 64, 4090, 4087, 192), (pq.FMT_INT3, 64, 2300, 3656, 192), (pq.FMT_INT4, 128, 300, 4087, 640),
-    (pq.FMT_INT3, 32, 33, 41, 96), (pq.FMT_INT3, 256, 70, 3000, 256), (pq.FMT_NVFP4, 16, 2300, 333, 96),
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_NVFP4, 16, 3600, 4081, 160, T256), (pq.FMT_NVFP4, 16, 2304, 3656, 288, T224),
+    (pq.FMT_NVFP4, 16, 4090, 4087, 160, T128), (pq.FMT_NVFP4, 16, 1500, 2056, 96, T128),
+    (pq.FMT_INT4, 64, 3600, 4081, 192, T256), (pq.FMT_INT4, 128, 3000, 4087, 640, T224), (pq.FMT_INT4, 64, 4090, 4087, 192, T128),
+    (pq.FMT_INT3, 64, 4090, 4087, 320, T256), (pq.FMT_INT3, 64, 2300, 3656, 192, T224), (pq.FMT_INT3, 32, 3000, 3585, 96, T224),
+    (pq.FMT_INT3, 32, 33, 41, 96, S32), (pq.FMT_INT3, 256, 70, 3000, 256, S64X32), (pq.FMT_NVFP4, 16, 2300, 333, 96, S64X32),
+    (pq.FMT_INT4, 128, 300, 4087, 640, S64X32), (pq.FMT_INT4, 256, 130, 3656, 768, S64), (pq.FMT_NVFP4, 16, 300, 4087, 768, S64X96),
+    (pq.FMT_INT3, 256, 500, 3000, 768, S64X96),
+    # a row and its group maxima beyond 48 KB of LDS in the gathering quantizer, up to its limit
+    (pq.FMT_NVFP4, 16, 40, 33, 24640, None), (pq.FMT_INT4, 64, 40, 33, 24640, None), (pq.FMT_INT3, 32, 9, 33, 65536, None),
 ])
-def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K):
-    # the selection's error of the original order against the same product stored in fp32, summed in fp64: every tile
-    # of the product kernels keeps its own squared difference, ragged edges and two batches included
+def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K, tile):
+    # the selection's error of the original order and of a candidate's against the same product stored in fp32, summed
+    # in fp64: every tile of the product kernels keeps its own squared difference, ragged edges and two batches included
+    if tile:
+        _takes(tile, fmt, g, M, N, K)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(55 + M + K)
     xs = [torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
@@ -375,20 +392,24 @@ def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K):
     pq.pq_calib_moments(w, sw, amax[1:])
     ts = amax / 2688.0
     perm = torch.empty(K, dtype=torch.int32, device=DEV)
-    rep = pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, float(ts[0]), float(ts[1]), perm, alphas=(0.5,))
+    # a threshold below any gain: the candidate's order comes back
+    rep = pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, float(ts[0]), float(ts[1]), perm, alphas=(0.5,), tau=-1e30)
+    assert rep.accepted
     codes, scales = pq.alloc_quantized(fmt, g, N, K, DEV)
-    pq.pq_quantize_act(fmt, g, w, None, ts[1:], codes, scales)
-    w_op = pq.pq_pack_operand(fmt, g, codes, scales)
-    num = den = 0.0
     y = torch.empty((M, (N + 7) // 8 * 8), dtype=torch.float32, device=DEV)
-    for x in xs:
-        x_op = pq.pq_quantize_act_packed(fmt, g, x, ts[:1])
-        pq.pq_qgemm_packed_f32(fmt, g, x_op, ts[:1], w_op, ts[1:], y, M, N, K)
-        ref = x.double() @ w.double().t()
-        num += float((ref - y[:, :N].double()).square().sum())
-        den += float(ref.square().sum())
-    assert abs(rep.sum_x2 - den) <= 1e-5 * den          # fp32 accumulation of both products
-    assert abs(rep.e_orig - num / den) <= 1e-5 * rep.e_orig
+    for order, err in ((None, rep.e_orig), (perm, rep.e_cand[0])):
+        pq.pq_quantize_act(fmt, g, w, order, ts[1:], codes, scales)
+        w_op = pq.pq_pack_operand(fmt, g, codes, scales)
+        num = den = 0.0
+        for x in xs:
+            xo = x if order is None else x[:, order.long()].contiguous()
+            x_op = pq.pq_quantize_act_packed(fmt, g, xo, ts[:1])
+            pq.pq_qgemm_packed_f32(fmt, g, x_op, ts[:1], w_op, ts[1:], y, M, N, K)
+            ref = x.double() @ w.double().t()
+            num += float((ref - y[:, :N].double()).square().sum())
+            den += float(ref.square().sum())
+        assert abs(rep.sum_x2 - den) <= 1e-5 * den          # fp32 accumulation of both products
+        assert abs(err - num / den) <= 1e-5 * err
 
 
 def test_select_perm_candidates_and_ties():
@@ -617,45 +638,57 @@ def _gemm_case(fmt, g, M, N, K, seed, ldy_pad=0):
 
 @pytest.mark.parametrize("fmt,g", FMTS)
 def test_qgemm_small_ragged(fmt, g):
-    # 128x128 tiles, several of them, ragged in M and N
+    # 32 x 32 tiles, a few dozen of them, ragged in M and N
     K = 512 if g <= 128 else 768
+    _takes(S32, fmt, g, 200, 328, K)
     _gemm_case(fmt, g, 200, 328, K, 600 + g)
 
 
-@pytest.mark.parametrize("fmt,g", FMTS[:4])
-def test_qgemm_large_tile_path(fmt, g):
-    # enough outputs to select the large-tile kernel -- here the 224 x 256 tile (wave rows of 128 + 96),
-    # 11 x 15 of them; ragged edges; odd tile count
-    _gemm_case(fmt, g, 2304 + 40, 3584 + 72, 256, 700 + g, ldy_pad=8)
-
-
-@pytest.mark.parametrize("fmt,g", [(pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64)])
-def test_qgemm_square_tile_path(fmt, g):
-    # 16 x 16 tiles of 256 x 256 fill the compute units exactly (tiles 224 rows high would need a second
-    # round), so the square tile is chosen; ragged last row and column of tiles
-    _gemm_case(fmt, g, 4096 - 6, 4096 - 9, 128, 750 + g)
+@pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_NVFP4, 16, 2344, 3656, 256), (pq.FMT_NVFP4, 16, 2344, 3585, 96), (pq.FMT_INT4, 64, 2344, 3656, 256),
+    (pq.FMT_INT4, 32, 2344, 4081, 160), (pq.FMT_INT4, 32, 3000, 3585, 256), (pq.FMT_INT3, 32, 2344, 4081, 192),
+    (pq.FMT_INT4, 128, 2344, 3656, 256),
+])
+def test_qgemm_large_tile_path(fmt, g, M, N, K):
+    # the 224 x 256 tile (wave rows of 128 + 96), of either product kernel; ragged edges, odd tile counts, odd and
+    # even numbers of steps
+    _takes(T224, fmt, g, M, N, K)
+    _gemm_case(fmt, g, M, N, K, 700 + g, ldy_pad=8)
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K", [
-    (pq.FMT_INT4, 64, 4096 - 6, 4096 - 9, 64),          # one step; square tile
-    (pq.FMT_INT4, 128, 3000, 4096 - 9, 640),            # 224-row tile, odd number of 128-wide groups
-    (pq.FMT_INT4, 256, 4096 - 6, 4096 - 9, 256),
-    (pq.FMT_INT3, 64, 2304 + 40, 3584 + 72, 192),       # odd number of steps
-    (pq.FMT_INT3, 64, 4096 - 6, 4096 - 9, 320),
-    (pq.FMT_INT3, 256, 2304 + 40, 3584 + 72, 512),
+    (pq.FMT_NVFP4, 16, 3600, 4081, 128), (pq.FMT_NVFP4, 16, 3600, 4082, 96), (pq.FMT_INT4, 64, 3600, 4081, 128),
+    (pq.FMT_INT4, 32, 3600, 4081, 160), (pq.FMT_INT3, 32, 3600, 4082, 192),
 ])
-def test_qgemm_codes_on_the_matrix_unit(fmt, g, M, N, K):
+def test_qgemm_square_tile_path(fmt, g, M, N, K):
+    # 15 x 16 tiles of 256 x 256 nearly fill the compute units (tiles 224 rows high would need a second round);
+    # ragged last row and column of tiles
+    _takes(T256, fmt, g, M, N, K)
+    _gemm_case(fmt, g, M, N, K, 750 + g)
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_INT4, 64, 3600, 4081, 64, T256),            # one step
+    (pq.FMT_INT4, 128, 3000, 4096 - 9, 640, T224),      # odd number of 128-wide groups
+    (pq.FMT_INT4, 256, 4096 - 6, 4096 - 9, 256, T256),
+    (pq.FMT_INT3, 64, 2304 + 40, 3584 + 72, 192, T224), # odd number of steps
+    (pq.FMT_INT3, 64, 4096 - 6, 4096 - 9, 320, T256),
+    (pq.FMT_INT3, 256, 2304 + 40, 3584 + 72, 512, T224),
+])
+def test_qgemm_codes_on_the_matrix_unit(fmt, g, M, N, K, tile):
+    _takes(tile, fmt, g, M, N, K)
     # the integer formats' kernel with the scales outside the matrix instructions: every code format, both tile
     # heights, ragged edges, one step, odd and even step counts, groups of one, two and four steps
     _gemm_case(fmt, g, M, N, K, 760 + g + K)
 
 
-@pytest.mark.parametrize("fmt,g,lo,hi", [(pq.FMT_INT4, 64, -8, 8), (pq.FMT_INT3, 128, -4, 4)])
+@pytest.mark.parametrize("fmt,g,lo,hi", [(pq.FMT_INT4, 64, -8, 8), (pq.FMT_INT3, 256, -4, 4)])
 def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     # every nibble the code formats of the matrix unit hold, the one below -Q included; all scales 1, so the
     # accumulator holds Q^2 times the integer product (|.| <= 64 * 256 or 16 * 512, times 49) exactly and the epilogue
     # rounds at most three times.  Packed and row-major operands: the same bits.
-    M, N, K = (4096, 4096, 256) if fmt == pq.FMT_INT4 else (2304, 3584, 512)      # 256- and 224-row tiles
+    M, N, K, tile = (4096, 4096, 256, T256) if fmt == pq.FMT_INT4 else (2344, 3656, 512, T224)
+    _takes(tile, fmt, g, M, N, K)
     rng = np.random.default_rng(905 + g)
     za = rng.integers(lo, hi, size=(M, K))
     zw = rng.integers(lo, hi, size=(N, K))
@@ -674,16 +707,16 @@ def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     assert torch.equal(y, y_packed)
 
 
-@pytest.mark.parametrize("g,M,N,K", [
-    (64, 33, 41, 64), (256, 70, 3000, 256), (64, 1500, 1003, 320), (256, 300, 4087, 768),      # waves split K
-    (256, 1500, 2056, 256),                                                                    # 128 x 128
-    (128, 2304, 3584, 512), (64, 4090, 4087, 320),                                             # 224 and 256 x 256
+@pytest.mark.parametrize("g,M,N,K,tile", [
+    (64, 33, 41, 64, S32), (256, 70, 3000, 256, S64X32), (64, 1500, 1003, 320, S64), (256, 500, 3000, 768, S64X96),
+    (256, 1500, 2056, 256, T128), (256, 2344, 3656, 512, T224), (64, 4090, 4087, 320, T256),
 ])
-def test_qgemm_int3_multiplies_every_nibble(g, M, N, K):
+def test_qgemm_int3_multiplies_every_nibble(g, M, N, K, tile):
     # INT3 codes beyond the three bits that the quantizers write, -8 .. 7, are multiplied as they are, packed and
     # row-major to the same bits.  All scales 1, so the accumulator holds Q^2 times the integer product (|.| <= 64 * 768,
     # times 9) exactly and the epilogue rounds at most three times.  With such codes in a few rows of either operand
     # (K's first, middle or last nibble), the other outputs keep the bits they have without them.
+    _takes(tile, pq.FMT_INT3, g, M, N, K)
     rng = np.random.default_rng(935 + g + M)
     sa = torch.ones((M, K // g), dtype=torch.float32, device=DEV)
     sw = torch.ones((N, K // g), dtype=torch.float32, device=DEV)
@@ -731,23 +764,29 @@ def test_qgemm_int3_multiplies_every_nibble(g, M, N, K):
 @pytest.mark.parametrize("fmt,g,K", [(pq.FMT_NVFP4, 16, 96), (pq.FMT_INT4, 64, 192), (pq.FMT_INT3, 256, 256)])
 def test_qgemm_128_tile(fmt, g, K):
     # few steps and some 200 tiles of 128 x 128; ragged rows and columns
+    _takes(T128, fmt, g, 1500, 2056, K)
     _gemm_case(fmt, g, 1500, 2056, K, 765 + g)
 
 
 # one shape for each tile in which the waves split K (32 x 32, 64 x 32, 64 x 64, 64 x 96 outputs), for each way of
 # feeding the matrix unit: NVFP4, INT with a scale unit per half step, INT with one per step and per four steps, INT3
 # codes.  K from half a step over fewer steps than waves to an odd number of them; ragged rows and columns.
-@pytest.mark.parametrize("fmt,g,M,N,K", [
-    (pq.FMT_NVFP4, 16, 33, 41, 32), (pq.FMT_NVFP4, 16, 130, 257, 1120),
-    (pq.FMT_NVFP4, 16, 70, 3000, 96), (pq.FMT_NVFP4, 16, 2300, 333, 96), (pq.FMT_NVFP4, 16, 300, 4087, 416),
-    (pq.FMT_INT4, 32, 33, 41, 32), (pq.FMT_INT4, 32, 70, 3000, 96), (pq.FMT_INT3, 32, 130, 3656, 160),
-    (pq.FMT_INT4, 32, 300, 4087, 416),
-    (pq.FMT_INT4, 64, 131, 150, 704), (pq.FMT_INT4, 256, 70, 3000, 256), (pq.FMT_INT4, 256, 130, 3656, 768),
-    (pq.FMT_INT4, 128, 300, 4087, 640),
-    (pq.FMT_INT3, 64, 33, 41, 64), (pq.FMT_INT3, 256, 70, 3000, 256), (pq.FMT_INT3, 64, 1500, 1003, 320),
-    (pq.FMT_INT3, 256, 300, 4087, 768),
-])
-def test_qgemm_waves_split_k(fmt, g, M, N, K):
+SPLIT_SHAPES = [
+    (pq.FMT_NVFP4, 16, 33, 41, 32, S32), (pq.FMT_NVFP4, 16, 130, 257, 1120, S32),
+    (pq.FMT_NVFP4, 16, 70, 3000, 96, S64X32), (pq.FMT_NVFP4, 16, 2300, 333, 96, S64X32), (pq.FMT_NVFP4, 16, 300, 4087, 416, S64X32),
+    (pq.FMT_NVFP4, 16, 33, 9000, 160, S64), (pq.FMT_NVFP4, 16, 300, 4087, 768, S64X96),
+    (pq.FMT_INT4, 32, 33, 41, 32, S32), (pq.FMT_INT3, 32, 130, 3656, 160, S32), (pq.FMT_INT4, 32, 70, 3000, 96, S64X32),
+    (pq.FMT_INT4, 32, 300, 4087, 416, S64X32), (pq.FMT_INT3, 32, 130, 3656, 416, S64), (pq.FMT_INT4, 32, 300, 3656, 416, S64X96),
+    (pq.FMT_INT4, 64, 131, 150, 704, S32), (pq.FMT_INT4, 256, 70, 3000, 256, S64X32), (pq.FMT_INT4, 128, 300, 4087, 640, S64X32),
+    (pq.FMT_INT4, 256, 130, 3656, 768, S64), (pq.FMT_INT4, 64, 300, 4087, 1024, S64X96),
+    (pq.FMT_INT3, 64, 33, 41, 64, S32), (pq.FMT_INT3, 256, 70, 3000, 256, S64X32), (pq.FMT_INT3, 256, 300, 4087, 768, S64X32),
+    (pq.FMT_INT3, 64, 1500, 1003, 320, S64), (pq.FMT_INT3, 256, 500, 3000, 768, S64X96),
+]
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", SPLIT_SHAPES)
+def test_qgemm_waves_split_k(fmt, g, M, N, K, tile):
+    _takes(tile, fmt, g, M, N, K)
     _gemm_case(fmt, g, M, N, K, 770 + g + K)
 
 
@@ -854,6 +893,41 @@ def test_qgemm_int_group_far_below_row_maximum():
     assert np.abs(part_ref).max() < 2.0 ** -24 * mag.min()
 
 
+# the same two edges on the kernels that keep the scales outside the matrix instructions, where they meet as an outer
+# product of fp16 numbers, subnormal ones among them, and on the fp16 tiles: sampled rows and columns
+@pytest.mark.parametrize("far", [False, True], ids=["wide", "far"])
+@pytest.mark.parametrize("fmt,g,M,N,tile", [
+    (pq.FMT_INT4, 64, 3600, 4081, T256), (pq.FMT_INT4, 64, 2344, 3656, T224), (pq.FMT_INT3, 64, 3600, 4081, T256),
+    (pq.FMT_INT3, 64, 2344, 3656, T224), (pq.FMT_INT4, 64, 1500, 2056, T128), (pq.FMT_INT4, 32, 2344, 4081, T224),
+    (pq.FMT_INT3, 32, 3600, 4081, T256), (pq.FMT_INT3, 64, 33, 41, S32), (pq.FMT_INT3, 64, 300, 4087, S64X32),
+    (pq.FMT_INT3, 64, 1000, 3000, S64), (pq.FMT_INT4, 64, 300, 4087, S64X32),
+])
+def test_qgemm_int_scale_ranges_of_every_kernel(fmt, g, M, N, tile, far):
+    K = 512
+    _takes(tile, fmt, g, M, N, K)
+    rng = np.random.default_rng(917 + g + M + far)
+    groups = K // g
+    scale_a = 2.0 ** np.array([0, -26, -13, -30] * (groups // 4)) if far else 2.0 ** rng.integers(-10, 10, size=groups)
+    scale_w = np.ones(groups) if far else scale_a[::-1]
+    xb = synth.f64_to_bf16_bits(rng.standard_normal((M, K)) * np.repeat(scale_a, g)[None, :])
+    wb = synth.f64_to_bf16_bits(rng.standard_normal((N, K)) * np.repeat(scale_w, g)[None, :])
+    a_codes, a_scales = pq.alloc_quantized(fmt, g, M, K, DEV)
+    w_codes, w_scales = pq.alloc_quantized(fmt, g, N, K, DEV)
+    one = torch.ones(1, dtype=torch.float32, device=DEV)
+    pq.pq_quantize_act(fmt, g, _to_dev(xb), None, None, a_codes, a_scales)
+    pq.pq_quantize_weights(fmt, g, _to_dev(wb), None, w_codes, w_scales, one)
+    y = torch.zeros((M, (N + 7) // 8 * 8), dtype=torch.float32, device=DEV)
+    pq.pq_qgemm_packed_f32(fmt, g, pq.pq_pack_operand(fmt, g, a_codes, a_scales), None,
+                           pq.pq_pack_operand(fmt, g, w_codes, w_scales), None, y, M, N, K)
+    torch.cuda.synchronize()
+    m, n = (np.unique(np.concatenate([[0, size - 1], rng.integers(0, size, 300)])) for size in (M, N))
+    qa, qw = OQ.quantize(fmt, g, OF.bf16_bits_to_f64(xb[m])), OQ.quantize(fmt, g, OF.bf16_bits_to_f64(wb[n]))
+    xa, xw = OQ.dequantize(fmt, g, qa), OQ.dequantize(fmt, g, qw)
+    err = np.abs(y.cpu().numpy()[np.ix_(m, n)].astype(np.float64) - xa @ xw.T)
+    mag = np.abs(xa) @ np.abs(xw).T
+    assert np.all(err <= T.GEMM_ACC_UNITS * 2.0 ** -24 * mag), float((err / mag).max())
+
+
 def test_qgemm_check_int_scales():
     """Scales written by the quantizers are of the form the product kernel reproduces exactly; arbitrary fp32
     scales are counted."""
@@ -876,13 +950,16 @@ def test_qgemm_check_int_scales():
 # ------------------------------------------------------------------- packed GEMM operands
 
 @pytest.mark.parametrize("fmt,g", FMTS)
-@pytest.mark.parametrize("M,N,K", [(300, 264, 1056), (64, 520, 96), (513, 257, 2048)])
+@pytest.mark.parametrize("M,N,K", [(300, 264, 1056), (64, 520, 96), (513, 257, 2048), (1500, 2056, 256),
+                                   (2344, 4081, 512), (3600, 4081, 256)])
 def test_qgemm_packed_equals_row_major(fmt, g, M, N, K):
     """The product from operands in the panel layout is the product from the stored layout, bit
     for bit (same kernel, same order of additions; only the addresses differ).  Shapes: ragged
-    tiles in both directions, a K that ends in a half step (96 = 64 + 32), several tiles."""
+    tiles in both directions, a K that ends in a half step (96 = 64 + 32), several tiles, the staged tiles."""
     if K % g:
         pytest.skip("K is not a multiple of this group size")
+    if M >= 1500:
+        _takes({1500: T128, 2344: T224, 3600: T256}[M], fmt, g, M, N, K)
     _say("packed gemm fmt=%d g=%d %dx%dx%d" % (fmt, g, M, N, K))
     rng = np.random.default_rng(7000 + M + K + g)
     xb = _rand_bits(rng, M, K)
@@ -1000,6 +1077,36 @@ def test_qgemm_packed_bias(fmt, g, M, N, K):
     assert np.all(err <= tol), "worst %g of tolerance" % float((err / tol).max())
     assert torch.all(y[:, N:] == 3.0)
     assert torch.equal(y0.float(), y_plain.float())          # -0 + 0 = +0: compare values, not bits
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_NVFP4, 16, 3600, 4081, 128, T256), (pq.FMT_NVFP4, 16, 2344, 3656, 256, T224), (pq.FMT_NVFP4, 16, 1500, 2056, 96, T128),
+    (pq.FMT_INT4, 32, 3600, 4081, 160, T256), (pq.FMT_INT3, 32, 2344, 4081, 192, T224), (pq.FMT_INT4, 64, 1500, 2056, 192, T128),
+    (pq.FMT_INT4, 64, 3600, 4081, 192, T256), (pq.FMT_INT4, 128, 3000, 4087, 640, T224),
+    (pq.FMT_INT3, 64, 4090, 4087, 320, T256), (pq.FMT_INT3, 256, 2344, 3656, 512, T224),
+] + SPLIT_SHAPES)
+def test_qgemm_packed_bias_of_every_tile(fmt, g, M, N, K, tile):
+    """With a bias, the bf16 output is the fp32 product of the same tile (checked against the oracle above) plus the
+    bias in fp32, rounded once: bit for bit, and nothing beyond column N."""
+    _takes(tile, fmt, g, M, N, K)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7750 + M + K + g)
+    x = torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16)
+    w = (0.02 * torch.randn((N, K), generator=gen, device=DEV)).to(torch.bfloat16)
+    bias = (0.5 * torch.randn(N, generator=gen, device=DEV)).to(torch.bfloat16)
+    Ta = torch.full((1,), 0.002, dtype=torch.float32, device=DEV)
+    Tw = torch.empty(1, dtype=torch.float32, device=DEV)
+    w_codes, w_scales = pq.alloc_quantized(fmt, g, N, K, DEV)
+    pq.pq_quantize_weights(fmt, g, w, None, w_codes, w_scales, Tw)
+    a_op, w_op = pq.pq_quantize_act_packed(fmt, g, x, Ta), pq.pq_pack_operand(fmt, g, w_codes, w_scales)
+    ldy = (N + 7) // 8 * 8 + 8
+    y32 = torch.full((M, ldy), 3.0, dtype=torch.float32, device=DEV)
+    y = torch.full((M, ldy), 3.0, dtype=torch.bfloat16, device=DEV)
+    pq.pq_qgemm_packed_f32(fmt, g, a_op, Ta, w_op, Tw, y32, M, N, K, ldy=ldy)
+    pq.pq_qgemm_packed_bias(fmt, g, a_op, Ta, w_op, Tw, bias, y, M, N, K, ldy=ldy)
+    torch.cuda.synchronize()
+    assert torch.equal(y[:, :N], (y32[:, :N] + bias.float()).to(torch.bfloat16))
+    assert torch.all(y[:, N:] == 3.0) and torch.all(y32[:, N:] == 3.0)
 
 
 @pytest.mark.parametrize("fmt,g", FMTS)
