@@ -641,7 +641,7 @@ struct QeShape {
   int parts() const { return blocks * (threads / 64); }    // partial sums per tensor and candidate
 };
 
-static QeShape qe_shape(pq_format fmt, int64_t rows, int64_t K, int n_tensors, int n_cand) {
+static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n_tensors, int n_cand) {
   QeShape q;
   const bool nv = fmt == PQ_FMT_NVFP4;
   const int chunk = nv ? QeChunk<kNvfp4>::value : QeChunk<kInt4>::value;
@@ -654,16 +654,20 @@ static QeShape qe_shape(pq_format fmt, int64_t rows, int64_t K, int n_tensors, i
   // unit from the same SIMD on, and the busiest SIMD sets the pace (INT4, K = 3072: 315 us with nine waves, 254 with
   // eight, 246 with twelve; NVFP4, K = 12288, two batches: 403 with fourteen, 389 with sixteen).  Two workgroups share
   // a unit where their rows fit its LDS twice (one stages while the other computes): half of the waves that the
-  // registers allow each (the NVFP4 instances need up to 128 a lane: sixteen waves a unit; the integer ones 84:
-  // twenty-four), sixteen otherwise.  No more than there are work items (candidate x block of 64 chunks).
+  // registers allow each (the NVFP4 instances need up to 128 a lane: sixteen waves a unit; the integer ones up to 80:
+  // twenty-four), sixteen otherwise.  The integer instance of groups of 256 with two rows needs 84, which leaves twenty
+  // waves: one workgroup of sixteen (INT4, K = 8960, 4096 + 2048 rows 182 us, 512 + 512 + 512 rows 134; two of eight 184
+  // and 150, one of twelve 192 and 139; held to 80 registers it spills: 181 and 148).  No more waves than there are
+  // work items (candidate x block of 64 chunks), rounded up to four.
   const int items = n_cand * (int)((K / chunk + 63) / 64);
-  const int max_waves = 2 * q.shmem <= 160 * 1024 ? (nv ? 8 : 12) : kQeMaxWaves;
+  const bool two = 2 * q.shmem <= 160 * 1024 && !(!nv && group == 256 && q.r == 2);
+  const int max_waves = two ? (nv ? 8 : 12) : kQeMaxWaves;
   q.threads = 64 * (items < max_waves ? (items + 3) / 4 * 4 : max_waves);
   // Rows per workgroup: the workgroups run in rounds of as many as the chip holds at once (256 compute
   // units, one or two each), every round lasts about as long as a workgroup's rows plus a fixed start-up
   // (taken as half a row); among kQeMinRowsPerBlock .. 64 rows take the smallest size whose total is
   // within 2 % of the shortest (smaller workgroups even out better when their times differ).
-  const int64_t resident = (2 * q.shmem <= 160 * 1024 ? 2 : 1) * 256;
+  const int64_t resident = (two ? 2 : 1) * 256;
   const int64_t lo = (kQeMinRowsPerBlock + q.r - 1) / q.r * q.r;
   auto cost_of = [&](int64_t rpb) {
     const int64_t wgs = (rows + rpb - 1) / rpb * n_tensors;
@@ -789,7 +793,7 @@ int run_quant_error(pq_format fmt, int group, const void* x, int64_t rows, int64
   double* part = (double*)ws;
   TensorList tl;
   for (int b = 0; b < kMaxMomentBatches; ++b) tl.p[b] = (const uint16_t*)x;
-  const QeShape q = qe_shape(fmt, rows, K, 1, 1);
+  const QeShape q = qe_shape(fmt, group, rows, K, 1, 1);
   int32_t* offs = nullptr;
   if (perm) {
     offs = (int32_t*)((char*)ws + align_up((size_t)kQeParts(rows) * 8, 256));
@@ -913,8 +917,8 @@ int run_select(pq_format fmt, int group, const double* act_sumsq, const double* 
   const int n_cand = n_alpha + 1;            // candidate 0 is the original order
   int rc;
   // activations: all batches of a launch share one grid (up to kMaxMomentBatches per launch)
-  const QeShape qa = qe_shape(fmt, M, K, n_batches < kMaxMomentBatches ? n_batches : kMaxMomentBatches, n_cand);
-  const QeShape qw = qe_shape(fmt, N, K, 1, n_cand);       // the same resident rows (a function of K): one set of offsets
+  const QeShape qa = qe_shape(fmt, group, M, K, n_batches < kMaxMomentBatches ? n_batches : kMaxMomentBatches, n_cand);
+  const QeShape qw = qe_shape(fmt, group, N, K, 1, n_cand);       // the same resident rows (a function of K): one set of offsets
   if ((rc = launch_candidate_orders(act_sumsq, w_sumsq, K, alphas, n_alpha, W.keys, W.rank, W.cands, st, W.offs,
                                     qe_slot_bytes(qa.r), W.same_as)))
     return rc;
