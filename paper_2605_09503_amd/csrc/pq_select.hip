@@ -29,7 +29,6 @@
 namespace pq {
 
 constexpr int kMaxCand = PQ_MAX_ALPHAS + 1;   // identity + candidates
-constexpr int kMaxDevicesSeen = 64;
 
 struct AlphaList {
   double a[PQ_MAX_ALPHAS];
@@ -687,16 +686,10 @@ static int launch_qe_r(const TensorList& xs, int n_tensors, int64_t rows, int K,
                        const int32_t* offs, int n_cand, int identity_first, ScaleArg T, const uint32_t* same_as,
                        double* part, hipStream_t st) {
   auto kern = quant_error_kernel<FMT, G, R>;
-  // the attribute is per kernel instance and device; it is raised once per instance to the most any
-  // launch may ask for, not on every call
-  static std::atomic<bool> raised[kMaxDevicesSeen];
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  if (q.shmem > 48 * 1024 && (dev < 0 || dev >= kMaxDevicesSeen || !raised[dev].load(std::memory_order_acquire))) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kQeLds);
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(quant_error_kernel)");
-    if (dev >= 0 && dev < kMaxDevicesSeen) raised[dev].store(true, std::memory_order_release);
+  static std::atomic<uint64_t> raised{0};              // to the most any launch of the instance may ask for
+  if (q.shmem > 48 * 1024) {
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kQeLds, raised, "hipFuncSetAttribute(quant_error_kernel)"))
+      return rc;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)q.blocks, (unsigned)n_tensors), dim3(q.threads), q.shmem, st, xs,
                      (int)rows, K, offs, n_cand, identity_first, T, q.rows_per_block, same_as, part);
