@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
       }
     }
     if constexpr (MARK) {
-      if (wide & wide_mask(kWideCodes)) row_wide[r_local] = 1;
+      if (wide & kWideBits) row_wide[r_local] = 1;
       __syncthreads();
     }
   }

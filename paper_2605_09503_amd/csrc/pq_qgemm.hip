@@ -273,10 +273,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
   }
 
   __syncthreads();                                     // the output tile reuses the stages
-  uint32_t marks = 0;                                  // fp16 operands hold every code of a nibble: not looked at
   store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, 2 * STAGE_BYTES, OUT, FMT != kNvfp4>(
       acc, smem, a_mul, a_mul_stride, w_mul, w_mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f,
-      tile_m * tiles_n + tile_n, out, marks);
+      tile_m * tiles_n + tile_n, out);
 }
 
 // ------------------------------------------------------------------------ INT scale prepass

@@ -47,8 +47,8 @@ struct OperandView {
   int sc_step;
   const float* mul;
   int mul_stride;
-  const uint16_t* bias = nullptr;
   bool marked = false;
+  const uint16_t* bias = nullptr;
 };
 
 // Branch-free load of one slice.  `codes_row` / `sc_row` point at a valid row (the caller
@@ -215,23 +215,35 @@ __device__ __forceinline__ void store_diff(double d2, double* red, int threads, 
 // ------------------------------------------------------------------------ INT3 codes beyond three bits
 // The quantizers write INT3 codes of -3 .. 3, but a nibble holds -8 .. 7, and an operand with any of them is
 // multiplied as it is (E2M1 holds neither 5 nor 7).  Packing marks the rows that hold such codes in the sign of
-// their factor, where the kernels meet it in the epilogue; on the row-major layout they look at every code.  A
+// their factor, which the kernels look at in the epilogue; on the row-major layout they look at every code.  A
 // workgroup that finds one computes its tile again with E4M3 operands straight from memory, over what it stored.
 // The sums are those of the kernel that calls, in its order (KS shares of the steps; every factor that differs is a
-// power of two), so rows without such codes keep their bits.  Groups are a multiple of 64.  Looking at every code
-// in the packed case as well took 13 to 20 % of a split tile's time and 2 to 5 of a large one's.
+// power of two), so rows without such codes keep their bits.  Groups are a multiple of 64.  The marks cost nothing
+// that shows (INT3 g64 512 x 3072 x 3072 14.2 us with and without); looking at every code takes 13 to 20 % of a
+// split tile's time and 2 to 5 of a large one's.
 enum WideTest : int { kWideNone = 0, kWideMarks = 1, kWideCodes = 2 };
 
-// nonzero bits under wide_mask: a code beyond three bits (its bits 3 and 2 differ), a marked row
+// a code beyond three bits sets bit 3 of its nibble (its bits 3 and 2 differ)
+constexpr uint32_t kWideBits = 0x88888888u;
 __device__ __forceinline__ uint32_t wide_codes(uint32_t d) { return d ^ (d << 1); }
-__device__ __forceinline__ uint32_t wide_mark(float mul) { return as_u32(mul); }
-constexpr uint32_t wide_mask(int test) { return test == kWideMarks ? 0x80000000u : 0x88888888u; }
 
-// whether any thread of the workgroup found one (called by all of them; also orders their stores before what
-// follows); flags: an int per wave of LDS that nothing else uses
+// the factors of a tile's rows and columns, or-ed over what a lane loads: every wave looks at all of them, so that
+// none has to tell the others.  Called before the epilogue and tested after it, so that nothing waits for the loads.
+template <int BM, int BN>
+__device__ __forceinline__ uint32_t tile_marks(const OperandView& A, const OperandView& W, int M, int N, int m0, int n0) {
+  uint32_t v = 0;
+#pragma unroll
+  for (int r = 0; r < BM; r += 64) v |= as_u32(A.mul[min(m0 + r + (int)(threadIdx.x & 63), M - 1)]);
+#pragma unroll
+  for (int r = 0; r < BN; r += 64) v |= as_u32(W.mul[min(n0 + r + (int)(threadIdx.x & 63), N - 1)]);
+  return v;
+}
+
+// whether any thread of the workgroup met a wide code (called by all of them); flags: an int per wave of LDS that
+// nothing else uses
 template <int WAVES>
 __device__ __forceinline__ bool any_wide(uint32_t wide, int* flags) {
-  const int mine = __any(wide != 0);
+  const int mine = __any((wide & kWideBits) != 0);
   if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = mine;
   __syncthreads();
   int any = 0;
@@ -293,14 +305,14 @@ __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const Oper
 
 // The accumulators of a workgroup's output tile, scaled and stored.  unit: a power of two that undoes the
 // operands' fixed code scale (1 where they have none; the product with it is exact).  INT: the factors are magnitudes,
-// their sign a mark (collected in marks).
+// their sign a mark.
 template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT, bool INT>
 __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsigned char* smem,
                                            const float* __restrict__ a_mul, int a_mul_stride,
                                            const float* __restrict__ w_mul, int w_mul_stride,
                                            const uint16_t* __restrict__ bias, int M, int N, int m0, int n0,
                                            int wave_m, int wave_n, int tm_cnt, int tid, float unit, int tile,
-                                           const Output& out, uint32_t& marks) {
+                                           const Output& out) {
   void* __restrict__ y = out.y;
   const int64_t ldy = out.ldy;
   double d2 = 0.0;
@@ -323,7 +335,6 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
       for (int e = 0; e < 4; ++e) {
         const int n = n0 + wave_n * WTN + i * 32 + q * 8 + frag_half * 4 + e;
         const float f = w_mul[(int64_t)(min(n, N - 1) * w_mul_stride)];
-        if (INT) marks |= wide_mark(f);
         wm[i][q * 4 + e] = INT ? fabsf(f) : f;
         wb[i][q * 4 + e] = bias ? bf16_to_f32(bias[min(n, N - 1)]) : 0.0f;
       }
@@ -333,7 +344,6 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
     const int ml = wave_m * WTM + j * 32 + frag_row;
     const int m = m0 + ml;
     const float f = a_mul[(int64_t)(min(m, M - 1) * a_mul_stride)];
-    if (INT) marks |= wide_mark(f);
     const float am = INT ? fabsf(f) : f;
 #pragma unroll
     for (int i = 0; i < TN; ++i) {

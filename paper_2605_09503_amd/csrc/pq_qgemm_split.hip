@@ -177,6 +177,9 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
     }
   }
 
+  uint32_t marks = 0;
+  if constexpr (WIDE == kWideMarks) marks = tile_marks<BM, BN>(A, W, M, N, m0, n0);
+
   // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
   const uint16_t* __restrict__ bias = W.bias;
   void* __restrict__ y = out.y;
@@ -211,13 +214,11 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
       }
       constexpr bool INT = MODE != kSplitNvfp4;         // factors of magnitude, the sign a mark
       float am = A.mul[(int64_t)m * A.mul_stride];
-      if constexpr (WIDE == kWideMarks) wide |= wide_mark(am);
       if constexpr (INT) am = fabsf(am);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int nn = min(n + e, N - 1);
         float wm = W.mul[(int64_t)nn * W.mul_stride];
-        if constexpr (WIDE == kWideMarks) wide |= wide_mark(wm);
         if constexpr (INT) wm = fabsf(wm);
         v[e] = (v[e] * unit) * (am * wm);
         if (bias) v[e] += bf16_to_f32(bias[nn]);
@@ -261,8 +262,13 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
     store_diff(d2, reinterpret_cast<double*>(part), T, tile_m * tiles_n + tile_n, out);
   }
   if constexpr (WIDE != kWideNone) {                   // here, where the accumulators are dead
-    if (any_wide<KS>(wide & wide_mask(WIDE), reinterpret_cast<int*>(part + (size_t)KS * BM * ROW)))
+    const bool any = WIDE == kWideMarks ? __any((int)marks < 0) != 0
+                                        : any_wide<KS>(wide, reinterpret_cast<int*>(part + (size_t)KS * BM * ROW));
+    if (any) {
+      __threadfence();                                 // what the waves stored has arrived
+      __syncthreads();
       wide_codes_tile<BM, BN, KS, KS, OUT>(A, W, M, N, K, g_shift, m0, n0, out);
+    }
   }
 }
 
@@ -270,7 +276,7 @@ template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
 static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
-  constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4 + (WIDE != kWideNone ? KS * 4 : 0);
+  constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4 + (WIDE == kWideCodes ? KS * 4 : 0);
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
   auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE>;
   static std::atomic<uint64_t> raised{0};
