@@ -229,9 +229,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
         // unpack tasks: 32 SL pairs, spread evenly over the MFMAs of the first three slices (their pieces have to be in
         // LDS at the barrier).  Task order: A slot 0 (4 pieces x 4 pairs), A slot 1, ..., then the W slots.
         if (kk < 3) {
+          const int slot = kk * NM + mi;             // tasks that start in it: g 3 NM / (32 SL) == slot
 #pragma unroll
-          for (int g = 0; g < 32 * SL; ++g) {
-            if (g * 3 * NM / (32 * SL) != kk * NM + mi) continue;
+          for (int g = (slot * 32 * SL + 3 * NM - 1) / (3 * NM); g < ((slot + 1) * 32 * SL + 3 * NM - 1) / (3 * NM); ++g) {
             const int u = g / 4;                // unit: one dword of codes -> one LDS piece
             const int jp = g % 4;
             const bool is_w = u >= 4 * SL;
