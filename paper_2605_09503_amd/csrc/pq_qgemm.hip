@@ -288,8 +288,11 @@ struct ScalePrep {
   uint16_t* h;
   float* mul;
   int rows;
+  const uint8_t* codes;      // MARK only
 };
-__global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScalePrep w, int groups, float Q) {
+// MARK: rows with codes outside -4 .. 3 are marked (see wide_codes_tile)
+template <bool MARK>
+__global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScalePrep w, int groups, float Q, int K) {
   const ScalePrep& o = blockIdx.y ? w : a;
   const float* __restrict__ s = o.s;
   uint16_t* __restrict__ h_out = o.h;
@@ -299,6 +302,10 @@ __global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScaleP
   const int lane = threadIdx.x & 63;
   if (row >= rows) return;
   const float* sr = s + (int64_t)row * groups;
+  // 16-byte pieces of the row's codes; the first on its way with the scales
+  const uint4* cr = MARK ? reinterpret_cast<const uint4*>(o.codes + (int64_t)row * (K / 2)) : nullptr;
+  uint4 first = make_uint4(0u, 0u, 0u, 0u);
+  if (MARK && lane < K / 32) first = cr[lane];
   float mx = 0.0f;
   for (int g = lane; g < groups; g += 64) {
     float h = as_f32(f32_to_bf16_rne(sr[g] * Q) << 16);
@@ -319,7 +326,17 @@ __global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScaleP
     _Float16 hh = (_Float16)(h * down);                      // exact unless far below the row max
     h_out[(int64_t)row * groups + g] = __builtin_bit_cast(uint16_t, hh);
   }
-  if (lane == 0) mul_out[row] = up / Q;
+  bool marked = false;
+  if constexpr (MARK) {
+    uint32_t wide = wide_codes(first.x) | wide_codes(first.y) | wide_codes(first.z) | wide_codes(first.w);
+#pragma unroll 4
+    for (int c = lane + 64; c < K / 32; c += 64) {
+      const uint4 v = cr[c];
+      wide |= wide_codes(v.x) | wide_codes(v.y) | wide_codes(v.z) | wide_codes(v.w);
+    }
+    marked = __any((wide & kWideBits) != 0);
+  }
+  if (lane == 0) mul_out[row] = marked ? -(up / Q) : up / Q;
 }
 
 // ------------------------------------------------------------------------ INT scale form check
@@ -476,11 +493,14 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     GemmWs G;
     carve_gemm(ws, fmt, group, M, N, K, &G);
     const float Q = qmax_of((int)fmt);
+    const bool mark = phases == 3 && fmt == PQ_FMT_INT3 && group != 32;
     if (phases & 1) {
       const int64_t most = M > N ? M : N;
-      hipLaunchKernelGGL(int_scale_prep_kernel, dim3((unsigned)((most + 3) / 4), 2), dim3(256), 0, st,
-                         ScalePrep{(const float*)a_scales, G.a_h, G.a_mul, (int)M},
-                         ScalePrep{(const float*)w_scales, G.w_h, G.w_mul, (int)N}, (int)(K / group), Q);
+      hipLaunchKernelGGL(mark ? int_scale_prep_kernel<true> : int_scale_prep_kernel<false>,
+                         dim3((unsigned)((most + 3) / 4), 2), dim3(256), 0, st,
+                         ScalePrep{(const float*)a_scales, G.a_h, G.a_mul, (int)M, a_codes},
+                         ScalePrep{(const float*)w_scales, G.w_h, G.w_mul, (int)N, w_codes},
+                         (int)(K / group), Q, (int)K);
       int rc = check_hip(hipGetLastError(), "int_scale_prep_kernel");
       if (rc) return rc;
     }
@@ -490,6 +510,7 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     A.mul = G.a_mul;
     W.mul = G.w_mul;
     A.mul_stride = W.mul_stride = 1;
+    A.marked = W.marked = mark;
   }
   if (!(phases & 2)) return PQ_OK;
   return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}, st);

@@ -35,7 +35,8 @@ struct Slice {
 //   panel (K-step-major, see pq_pack.hip):  code_row = 32, code_step = 32 * rows;
 //                                           sc_row = 2, sc_step = 2 * rows
 // mul: per-row epilogue factor (stride 1) or a single factor (stride 0).
-// marked: the sign of a row's factor says that the row holds INT3 codes beyond three bits (pq_pack.hip)
+// panel: the panel layout.  marked: the sign of a row's factor says that the row holds INT3 codes beyond three bits
+// (always in the panel layout; set by the scale preparation of a row-major operand when it sees the codes)
 // bias: bf16 value per row of this operand added to the product in the epilogue (used for the
 // weight operand, whose rows are the output columns), or null.
 struct OperandView {
@@ -47,7 +48,7 @@ struct OperandView {
   int sc_step;
   const float* mul;
   int mul_stride;
-  bool marked = false;
+  bool panel = false, marked = false;
   const uint16_t* bias = nullptr;
 };
 
@@ -214,13 +215,13 @@ __device__ __forceinline__ void store_diff(double d2, double* red, int threads, 
 
 // ------------------------------------------------------------------------ INT3 codes beyond three bits
 // The quantizers write INT3 codes of -3 .. 3, but a nibble holds -8 .. 7, and an operand with any of them is
-// multiplied as it is (E2M1 holds neither 5 nor 7).  Packing marks the rows that hold such codes in the sign of
-// their factor, which the kernels look at in the epilogue; on the row-major layout they look at every code.  A
-// workgroup that finds one computes its tile again with E4M3 operands straight from memory, over what it stored.
-// The sums are those of the kernel that calls, in its order (KS shares of the steps; every factor that differs is a
-// power of two), so rows without such codes keep their bits.  Groups are a multiple of 64.  The marks cost nothing
-// that shows (INT3 g64 512 x 3072 x 3072 14.2 us with and without); looking at every code takes 13 to 20 % of a
-// split tile's time and 2 to 5 of a large one's.
+// multiplied as it is (E2M1 holds neither 5 nor 7).  Packing, and on the row-major layout the scale preparation of
+// pq_qgemm, marks the rows that hold such codes in the sign of their factor, which the kernels look at in the
+// epilogue; pq_qgemm_run, whose preparation has not seen the codes, looks at every code.  A workgroup that finds one
+// computes its tile again with E4M3 operands straight from memory, over what it stored.  The sums are those of the
+// kernel that calls, in its order (KS shares of the steps; every factor that differs is a power of two), so rows
+// without such codes keep their bits.  Groups are a multiple of 64.  The marks cost nothing that shows (INT3 g64 512 x 3072 x 3072 14.2 us with and without; the scale preparation that sets them 0 to 0.6 us);
+// looking at every code takes 13 to 20 % of a split tile's time and 2 to 5 of a large one's.
 enum WideTest : int { kWideNone = 0, kWideMarks = 1, kWideCodes = 2 };
 
 // a code beyond three bits sets bit 3 of its nibble (its bits 3 and 2 differ)
@@ -416,6 +417,7 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
   const OperandLayout L = operand_layout(fmt, group, rows, K);
   const uint8_t* o = (const uint8_t*)operand;
   OperandView v;
+  v.panel = v.marked = true;
   v.codes = o + L.codes;
   v.code_row = 32;
   v.code_step = (int)(rows * 32);
@@ -428,7 +430,6 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
   } else {
     v.mul = (const float*)(o + L.mul);
     v.mul_stride = 1;
-    v.marked = true;
   }
   return v;
 }

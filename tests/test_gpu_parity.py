@@ -710,12 +710,13 @@ def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
 @pytest.mark.parametrize("g,M,N,K,tile", [
     (64, 33, 41, 64, S32), (256, 70, 3000, 256, S64X32), (64, 1500, 1003, 320, S64), (256, 500, 3000, 768, S64X96),
     (256, 1500, 2056, 256, T128), (256, 2344, 3656, 512, T224), (64, 4090, 4087, 320, T256),
+    (64, 300, 4090, 256, S64), (64, 515, 1003, 3200, S64X32), (64, 2000, 2050, 2048, S64X96),    # row-major through LDS
 ])
 def test_qgemm_int3_multiplies_every_nibble(g, M, N, K, tile):
     # INT3 codes beyond the three bits that the quantizers write, -8 .. 7, are multiplied as they are, packed and
     # row-major to the same bits.  All scales 1, so the accumulator holds Q^2 times the integer product (|.| <= 64 * 768,
-    # times 9) exactly and the epilogue rounds at most three times.  With such codes in a few rows of either operand
-    # (K's first, middle or last nibble), the other outputs keep the bits they have without them.
+    # times 9) exactly (64 * 3200 * 9 is below 2^24) and the epilogue rounds at most three times.  With such codes in a
+    # few rows of either operand (K's first, middle or last nibble), the other outputs keep the bits they have without them.
     _takes(tile, pq.FMT_INT3, g, M, N, K)
     rng = np.random.default_rng(935 + g + M)
     sa = torch.ones((M, K // g), dtype=torch.float32, device=DEV)
@@ -730,6 +731,12 @@ def test_qgemm_int3_multiplies_every_nibble(g, M, N, K, tile):
         pq.pq_qgemm_f32(pq.FMT_INT3, g, a_codes, sa, None, w_codes, sw, None, ys[0], M=M, N=N, K=K, ldy=ldy)
         pq.pq_qgemm_packed_f32(pq.FMT_INT3, g, a_op, None, w_op, None, ys[1], M, N, K, ldy=ldy)
         pq.pq_qgemm(pq.FMT_INT3, g, a_codes, sa, None, w_codes, sw, None, ys[2], M=M, N=N, K=K, ldy=ldy)
+        # the same in two calls, the first of which does not see the codes
+        ws = torch.empty(pq.pq_workspace_bytes(pq.OP_QGEMM, pq.FMT_INT3, g, M, N, K), dtype=torch.uint8, device=DEV)
+        y_run = torch.full((M, ldy), 777.0, dtype=torch.bfloat16, device=DEV)
+        pq.pq_qgemm_prep(pq.FMT_INT3, g, sa, sw, M, N, K, ws)
+        pq.pq_qgemm_run(pq.FMT_INT3, g, a_codes, sa, None, w_codes, sw, None, y_run, workspace=ws, M=M, N=N, K=K, ldy=ldy)
+        assert torch.equal(y_run, ys[2])
         if bias is None:
             pq.pq_qgemm_packed(pq.FMT_INT3, g, a_op, None, w_op, None, ys[3], M, N, K, ldy=ldy)
         else:
