@@ -5,7 +5,7 @@
 // 32 x 32 to 64 x 96 outputs, and the partial sums are added in a fixed order through LDS at the end.  Nothing else is
 // shared: in the panel layout a fragment of 32 rows and one step is 1 KB of consecutive codes, so a wave loads its
 // fragments straight into the registers the matrix unit reads, two of its steps ahead, and unpacks them there.  No
-// operand goes through LDS and the loop has no barrier.
+// operand goes through LDS and the loop has no barrier (row-major operands of larger outputs: see ROWS).
 //
 // What bounds it.  The small ones are a chain: launch, one load, the unpack and the product of a few steps, the sums.
 // A 128 x 128 tile of four waves, which these shapes took before, spends 0.35 to 0.7 us in every step and
@@ -27,8 +27,23 @@ namespace pq {
 // the scales outside (pq_qgemm_group.hip)
 enum SplitMode : int { kSplitNvfp4 = 0, kSplitInt = 1, kSplitE2m1 = 2 };
 
+// LDS layout of one set of KS steps of row-major operands
+template <int TM, int TN, int KS>
+struct RowSet {
+  static constexpr int kRows = (TM + TN) * 32;
+  static constexpr int kRow = KS * 32 + 16;            // bytes of a row's codes and one spare piece: the 16-byte reads of
+                                                       // 32 rows at one position spread over all banks
+  static constexpr int kScales = kRows * kRow;         // then two bytes a slice
+  static constexpr int kScaleRow = KS * 4 + 4;
+  static constexpr int kBytes = (kScales + kRows * kScaleRow + 15) / 16 * 16;
+};
+
+// ROWS (row-major operands only): a fragment read straight from a row-major operand touches a line for each of its 32
+// rows and takes a quarter of it.  Here the workgroup loads the codes and scale units of its next KS steps together,
+// whole runs of 32 KS bytes of every row, and the waves pick their step out of LDS (two sets of steps, a barrier for
+// each).  The sums are the same as without, and as those of the packed operands, bit for bit.  See rows_through_lds.
 // WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
-template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
 __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, OperandView W, int M, int N,
                                                                       int K, int g_shift, Output out, int tiles_m,
                                                                       int tiles_n) {
@@ -46,7 +61,8 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int frag_row = lane & 31, frag_half = lane >> 5;
 
-  // a fragment's lane: row lane % 32, k 32 * (lane / 32) .. + 31 of the step: 16 bytes of codes, one scale unit
+  // a fragment's lane: row lane % 32, k 32 * (lane / 32) .. + 31 of the step: 16 bytes of codes, one scale unit (packed
+  // operands; see below for ROWS)
   uint32_t a_coff[TM], w_coff[TN], a_soff[TM], w_soff[TN];
   bool a_ok[TM], w_ok[TN];
 #pragma unroll
@@ -163,17 +179,82 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
     }
   };
 
-  Step raw[PD];
-  const int n_own = (ksteps - ks + KS - 1) / KS;       // steps ks, ks + KS, ...
+  if constexpr (!ROWS) {
+    Step raw[PD];
+    const int n_own = (ksteps - ks + KS - 1) / KS;     // steps ks, ks + KS, ...
 #pragma unroll
-  for (int p = 0; p < PD; ++p) load(ks + p * KS, raw[p]);
-  for (int o = 0; o < n_own; o += PD) {
+    for (int p = 0; p < PD; ++p) load(ks + p * KS, raw[p]);
+    for (int o = 0; o < n_own; o += PD) {
 #pragma unroll
-    for (int p = 0; p < PD; ++p) {
-      if (o + p < n_own) {                             // uniform
-        multiply(raw[p], ks + (o + p) * KS);
-        load(ks + (o + p + PD) * KS, raw[p]);
+      for (int p = 0; p < PD; ++p) {
+        if (o + p < n_own) {                           // uniform
+          multiply(raw[p], ks + (o + p) * KS);
+          load(ks + (o + p + PD) * KS, raw[p]);
+        }
       }
+    }
+  } else {
+    // set: [rows of A, then of W] of KS steps; a row's codes with one spare piece, then the scale units of all rows
+    using L = RowSet<TM, TN, KS>;
+    unsigned char* lds = reinterpret_cast<unsigned char*>(part);
+    // thread t has slice t % (2 KS) of the set's 2 KS, of row t / (2 KS) of each 32
+    const int slot = tid % (2 * KS), ld_row = tid / (2 * KS), ld_half = slot & 1;
+    int4v codes[TM + TN];                              // the thread's slices of the set to come
+    uint16_t units[TM + TN];
+    auto fetch = [&](int set) {
+      const int step = set * KS + (slot >> 1);
+      const int st = min(step, ksteps - 1);
+      const int half = st * kBK + ld_half * 32 < K ? ld_half : 0;
+      const int unit = ((st * kBK) >> g_shift) + (per_half ? half : 0);
+      const int k0 = st * 32 + half * 16;
+#pragma unroll
+      for (int q = 0; q < TM + TN; ++q) {
+        const OperandView& v = q < TM ? A : W;
+        const int row = q < TM ? min(m0 + q * 32 + ld_row, M - 1) : min(n0 + (q - TM) * 32 + ld_row, N - 1);
+        codes[q] = *reinterpret_cast<const int4v*>(v.codes + (int64_t)row * v.code_row + k0);
+        units[q] = *reinterpret_cast<const uint16_t*>(v.scales + (int64_t)row * v.sc_row + unit * 2);
+      }
+    };
+    auto put = [&](unsigned char* set) {
+#pragma unroll
+      for (int q = 0; q < TM + TN; ++q) {
+        const int r = q * 32 + ld_row;
+        *reinterpret_cast<int4v*>(set + r * L::kRow + slot * 16) = codes[q];
+        *reinterpret_cast<uint16_t*>(set + L::kScales + r * L::kScaleRow + slot * 2) = units[q];
+      }
+    };
+    const int mine = 2 * ks + frag_half;
+    const int n_sets = (ksteps + KS - 1) / KS;
+    // set o: out of LDS stage o % 2, while set o + 1 goes into the other one, which was last read before the barrier
+    // in between, and set o + 2 is asked for
+    auto turn = [&](auto Pc, int o) {
+      constexpr int P = decltype(Pc)::value;           // o % 2
+      const unsigned char* have = lds + P * L::kBytes;
+      Step own;
+#pragma unroll
+      for (int q = 0; q < TM; ++q) {
+        own.a[q].codes = *reinterpret_cast<const uint4*>(have + (q * 32 + frag_row) * L::kRow + mine * 16);
+        own.a[q].sc = *reinterpret_cast<const uint16_t*>(have + L::kScales + (q * 32 + frag_row) * L::kScaleRow + mine * 2);
+      }
+#pragma unroll
+      for (int q = 0; q < TN; ++q) {
+        own.w[q].codes = *reinterpret_cast<const uint4*>(have + ((TM + q) * 32 + frag_row) * L::kRow + mine * 16);
+        own.w[q].sc = *reinterpret_cast<const uint16_t*>(have + L::kScales + ((TM + q) * 32 + frag_row) * L::kScaleRow + mine * 2);
+      }
+      if (o + 1 < n_sets) {                            // uniform over the workgroup
+        put(lds + (P ^ 1) * L::kBytes);
+        fetch(o + 2);
+      }
+      if (o * KS + ks < ksteps) multiply(own, o * KS + ks);          // uniform over the wave
+      __syncthreads();
+    };
+    fetch(0);
+    put(lds);
+    fetch(1);
+    __syncthreads();
+    for (int o = 0; o < n_sets; o += 2) {
+      turn(IntC<0>{}, o);
+      if (o + 1 < n_sets) turn(IntC<1>{}, o + 1);      // uniform over the workgroup
     }
   }
 
@@ -272,13 +353,30 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
   }
 }
 
-template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
+// Whether a product of row-major operands reads them through LDS.  Up to one workgroup a unit its chain of loads is what
+// takes the time, and the direct loads are two steps ahead without a barrier (INT4 g128 77 x 1000 x 1152, 96 tiles: 7.0 us
+// direct, 7.8 through LDS).  With more, the lines of a unit's workgroups push each other out of its cache before all of
+// their quarters are read, the more so where every row starts at a line (K a multiple of 256); below the step counts here
+// the barriers cost as much.  Measured over 652 shapes at the tiles that they take, through LDS against direct, tiles of
+// four waves beyond 256: K a multiple of 256 0.57 to 0.99 of the time, else NVFP4 and fp16 operands from 8 steps on 0.67 to
+// 1.05, E2M1 codes from 24 on 0.60 to 1.04 (before that 0.9 to 1.2); of eight waves from 48 steps on 0.58 to 1.05.  us, direct
+// | through LDS | the staged tiles that these shapes took once: NVFP4 2048 x 3072 x 3072 72 | 47 | 56, 512 x 9216 x 3072
+// 57 | 38 | 53, INT4 g64 1024 x 3072 x 3072 41 | 32 | 37, INT3 g64 2048 x 3072 x 3072 84 | 50 | 58.
+static bool rows_through_lds(int mode, int64_t n_tiles, int ks, int K) {
+  if (n_tiles <= 256) return false;
+  const int steps = ks == 8 ? 48 : K % 256 == 0 ? 4 : mode == kSplitE2m1 ? 24 : 8;
+  return K >= steps * kBK;
+}
+
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
 static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
-  constexpr size_t shmem = (size_t)KS * BM * (32 + 4) * 4 + (WIDE == kWideCodes ? KS * 4 : 0);
+  constexpr size_t sums = (size_t)KS * BM * (32 + 4) * 4 + (WIDE == kWideCodes ? KS * 4 : 0);
+  constexpr size_t sets = ROWS ? 2 * (size_t)RowSet<TM, TN, KS>::kBytes : 0;
+  constexpr size_t shmem = sums > sets ? sums : sets;
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
-  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE>;
+  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE, ROWS>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_split_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -289,27 +387,38 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   return check_hip(hipGetLastError(), "qgemm_split_kernel");
 }
 
+// the loader of the operands' layout and the shape
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
+static int split_loader(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+                        hipStream_t st) {
+  if constexpr (OUT != kOutDiff) {                     // the selection, which keeps the difference, packs its operands
+    const int64_t n_tiles = (int64_t)((M + TM * 32 - 1) / (TM * 32)) * ((N + TN * 32 - 1) / (TN * 32));
+    if (!(A.panel && W.panel) && rows_through_lds(MODE, n_tiles, KS, K))
+      return launch_split<MODE, TM, TN, KS, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
+  }
+  return launch_split<MODE, TM, TN, KS, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
+}
+
 template <int MODE, int OUT, int WIDE>
 static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                       int tile, hipStream_t st) {
   switch (tile) {
-    case kTileSplit32: return launch_split<MODE, 1, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
-    case kTileSplit64x32: return launch_split<MODE, 2, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
-    case kTileSplit64: return launch_split<MODE, 2, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
-    default: return launch_split<MODE, 2, 3, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit32: return split_loader<MODE, 1, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64x32: return split_loader<MODE, 2, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64: return split_loader<MODE, 2, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    default: return split_loader<MODE, 2, 3, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
   }
 }
 
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Output& out, int tile, hipStream_t st) {
   const int g_shift = fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
-#define PQ_SPLIT(MODE, WIDE)                                                                                     \
-  return out.kind == kOutF32    ? split_tile<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st)          \
-         : out.kind == kOutDiff ? split_tile<MODE, kOutDiff, kWideNone>(A, W, M, N, K, g_shift, out, tile, st)    \
+#define PQ_SPLIT(MODE, WIDE)                                                                                 \
+  return out.kind == kOutF32    ? split_tile<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st)      \
+         : out.kind == kOutDiff ? split_tile<MODE, kOutDiff, kWideNone>(A, W, M, N, K, g_shift, out, tile, st) \
                                 : split_tile<MODE, kOutBf16, WIDE>(A, W, M, N, K, g_shift, out, tile, st)
   if (fmt == PQ_FMT_NVFP4) PQ_SPLIT(kSplitNvfp4, kWideNone);
   if (fmt == PQ_FMT_INT3 && group != 32) {
-    // the selection (kOutDiff) multiplies what it quantized itself
     if (A.marked && W.marked) PQ_SPLIT(kSplitE2m1, kWideMarks);
     PQ_SPLIT(kSplitE2m1, kWideCodes);
   }

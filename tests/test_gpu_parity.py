@@ -996,6 +996,43 @@ def test_qgemm_packed_equals_row_major(fmt, g, M, N, K):
                            y1.view(torch.int16 if dtype == torch.bfloat16 else torch.int32))
 
 
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_NVFP4, 16, 515, 2050, 256, S64), (pq.FMT_NVFP4, 16, 1000, 2050, 2080, S64X96),
+    (pq.FMT_NVFP4, 16, 515, 1003, 4128, S64X32), (pq.FMT_NVFP4, 16, 130, 3001, 3104, S32),
+    (pq.FMT_INT4, 32, 700, 4090, 2080, S64X96), (pq.FMT_INT4, 32, 193, 2050, 3104, S32), (pq.FMT_INT4, 64, 515, 3001, 576, S64),
+    (pq.FMT_INT4, 128, 1300, 1500, 640, S64), (pq.FMT_INT4, 128, 1000, 2050, 1664, S64X96), (pq.FMT_INT4, 64, 130, 3001, 3200, S32),
+    (pq.FMT_INT3, 64, 300, 4090, 256, S64), (pq.FMT_INT3, 256, 1000, 2050, 512, S64), (pq.FMT_INT3, 64, 1000, 2050, 1600, S64),
+    (pq.FMT_INT3, 64, 2000, 2050, 2048, S64X96), (pq.FMT_INT3, 64, 515, 1003, 3200, S64X32), (pq.FMT_INT3, 64, 130, 3001, 3200, S32),
+    (pq.FMT_INT3, 128, 1024, 1024, 256, S64), (pq.FMT_INT3, 128, 1024, 1080, 256, S64),   # 256 and 272 tiles
+    (pq.FMT_INT4, 64, 515, 3001, 448, S64), (pq.FMT_INT3, 64, 1000, 2050, 1472, S64),     # a step short of going through LDS
+])
+def test_qgemm_row_major_loaders_equal_packed(fmt, g, M, N, K, tile):
+    """Where the waves split K, row-major operands are read straight or through LDS, by the number of tiles and steps:
+    either way the bits of the packed product.  Ragged tiles, sets of steps that are not full, K ending in a half step,
+    rows that start at a line and rows that do not."""
+    _takes(tile, fmt, g, M, N, K)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7060 + M + K + g)
+    x = torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16)
+    w = (0.02 * torch.randn((N, K), generator=gen, device=DEV)).to(torch.bfloat16)
+    Ta = torch.full((1,), 0.002, dtype=torch.float32, device=DEV)
+    Tw = torch.empty(1, dtype=torch.float32, device=DEV)
+    a_codes, a_scales = pq.alloc_quantized(fmt, g, M, K, DEV)
+    w_codes, w_scales = pq.alloc_quantized(fmt, g, N, K, DEV)
+    pq.pq_quantize_act(fmt, g, x, None, Ta, a_codes, a_scales)
+    pq.pq_quantize_weights(fmt, g, w, None, w_codes, w_scales, Tw)
+    a_op, w_op = pq.pq_pack_operand(fmt, g, a_codes, a_scales), pq.pq_pack_operand(fmt, g, w_codes, w_scales)
+    ldy = (N + 7) // 8 * 8
+    ws = torch.empty(max(16, pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K)), dtype=torch.uint8, device=DEV)
+    for dtype, plain, packed in ((torch.float32, pq.pq_qgemm_f32, pq.pq_qgemm_packed_f32),
+                                 (torch.bfloat16, pq.pq_qgemm, pq.pq_qgemm_packed)):
+        y0, y1 = (torch.full((M, ldy), 3.0, dtype=dtype, device=DEV) for _ in range(2))
+        plain(fmt, g, a_codes, a_scales, Ta, w_codes, w_scales, Tw, y0, M=M, N=N, K=K, ldy=ldy, workspace=ws)
+        packed(fmt, g, a_op, Ta, w_op, Tw, y1, M, N, K, ldy=ldy)
+        torch.cuda.synchronize()
+        assert torch.equal(y0, y1)
+
+
 def test_pack_operand_then_gemm_matches_oracle():
     """End to end through the packed path against the fp64 product (the row-major path is checked
     against the oracle above; this pins the packed one directly)."""
