@@ -14,17 +14,17 @@
 // sign << 7 | |z| is z 2^-9 exactly (all sixteen nibbles, -8 included).  INT3: E2M1, where 0, .5, 1, 1.5, 2
 // are the codes 0..4, so a nibble sign << 3 | |z| is z / 2 exactly for |z| <= 4.
 //
-// What bounds it.  On this chip the matrix and the vector instructions of a SIMD's two waves hardly overlap
-// (measured: a 32-cycle matrix instruction hides four to five vector instructions, every further one costs 2.2 to
-// 2.8 cycles), so a 32 x 32 x 64 block costs about the sum of both:
+// What bounds it.  On this chip the matrix and the vector instructions of a SIMD's two waves overlap in part only
+// (measured: a 32-cycle matrix instruction hides four vector instructions, a 64-cycle one twelve, every further one costs
+// 2.7 cycles, as much as alone), so a 32 x 32 x 64 block costs not much less than the sum of both:
 //   fp16 operands that carry their scale (pq_qgemm.hip)   128 matrix cycles + 16 vector instructions (the unpack)
 //   8-bit codes (here, INT4)                          64 + 32 matrix cycles + 31 (16 multiply-adds, 11 of unpack)
 //   4-bit codes (here, INT3)                          32 + 32 matrix cycles + 23 (16 multiply-adds, 4 of unpack)
 // and the 8- and 4-bit instructions draw less power: the chip holds 2.3 GHz here and 1.9 GHz there.  Forming S
 // on the vector unit instead would be 16 more instructions a block.  Measured, us and TFLOP/s (before: fp16):
-//   INT3 g64   4608 x 3072 x 3072     79 -> 53  (1.64 PFLOP/s)    8192 x 12288 x 3072   483 -> 322 (1.92)
-//   INT4 g64   4608 x 3072 x 3072     82 -> 75  (1.15)            8192 x 12288 x 3072   512 -> 427 (1.45)
-//   INT4 g64   4608 x 3072 x 12288   295 -> 239 (1.46)
+//   INT3 g64   4608 x 3072 x 3072     76 -> 52  (1.67 PFLOP/s)    8192 x 12288 x 3072   490 -> 332 (1.86)
+//   INT4 g64   4608 x 3072 x 3072     80 -> 68  (1.28)            8192 x 12288 x 3072   515 -> 430 (1.44)
+//   INT4 g64   4608 x 3072 x 12288   295 -> 240 (1.45)
 // Groups of 32 would need two half-empty matrix products and two scale products a block, 128 matrix cycles again,
 // and 32 multiply-adds: 510 us against 477 on INT3 8192 x 12288 x 3072, so they stay on the fp16 kernel, as do NVFP4's
 // groups of 16.  Issuing the next block's matrix instructions before this block's multiply-adds needs 16 to 32

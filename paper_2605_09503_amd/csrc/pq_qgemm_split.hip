@@ -9,15 +9,15 @@
 //
 // What bounds it.  The small ones are a chain: launch, one load, the unpack and the product of a few steps, the sums.
 // A 128 x 128 tile of four waves, which these shapes took before, spends 0.35 to 0.7 us in every step and
-// walks all of K alone.  The larger ones are bound by the sum of matrix and vector instructions (the two hardly
-// overlap, see pq_qgemm_group.hip): a 64 x 96 tile unpacks five fragments for six 32 x 32 x 64 products, 1.5 times what
+// walks all of K alone.  The larger ones are bound by the sum of matrix and vector instructions (the two overlap
+// in part only, see pq_qgemm_group.hip): a 64 x 96 tile unpacks five fragments for six 32 x 32 x 64 products, 1.5 times what
 // a staged 128 x 128 tile unpacks, but its four-wave workgroups need no barrier and run two to a compute unit.  Four
 // waves and not eight share a 64 x 96 tile because the second workgroup then covers the first one's ends
 // (NVFP4 512 x 9216 x 3072: 32 us, with eight waves 42).  Kernel alone, us, before -> now:
-//   NVFP4     256 x 512 x 512     9.2 ->  3.9     512 x 3072 x 3072   30 -> 13.8    512 x 3072 x 12288  102 -> 43
-//   NVFP4     512 x 9216 x 3072    47 -> 32       64 x 12288 x 3072   29 -> 11      16 x 512 x 12288    100 -> 13
-//   INT4 g128  77 x 1000 x 1152  15.4 ->  4.6     INT4 g64   1024 x 3072 x 3072  33 -> 25
-//   INT3 g64  512 x 3072 x 3072    32 -> 12       INT3 g64   2048 x 3072 x 3072  50 -> 32
+//   NVFP4     256 x 512 x 512     9.4 ->  3.9     512 x 3072 x 3072   30 -> 15      512 x 3072 x 12288  104 -> 43
+//   NVFP4     512 x 9216 x 3072    44 -> 32       64 x 12288 x 3072   29 -> 11      16 x 512 x 12288    103 -> 13
+//   INT4 g128  77 x 1000 x 1152  15.3 ->  4.5     INT4 g64   1024 x 3072 x 3072  33 -> 27
+//   INT3 g64  512 x 3072 x 3072    31 -> 13       INT3 g64   2048 x 3072 x 3072  49 -> 32
 // INT4 in the 8-bit form of pq_qgemm_group.hip gained nothing here (15.5 -> 16.5, 46.9 -> 43.6 us): fp16 operands.
 #include "pq_qgemm_common.h"
 

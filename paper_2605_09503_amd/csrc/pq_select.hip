@@ -646,7 +646,9 @@ static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n
   const int chunk = nv ? QeChunk<kNvfp4>::value : QeChunk<kInt4>::value;
   const size_t slot_floats = (size_t)(K + K / 8);
   // Resident rows: as many as LDS holds, four at most -- one gather and one load of offsets then serve four
-  // elements (K = 4096: 148 us with two rows, 134 with four; K = 7680, one workgroup a unit: 138 and 126).
+  // elements.  That pays where four rows leave room for one workgroup a unit only (K above 4551), too: a whole selection
+  // with four rows takes 0.86 to 0.99 of its time with two, over K = 4096 to 8448, every format and group, and 4608 + 3072
+  // or 512 + 512 + 1024 rows (INT4 g64, K = 7680: 188 -> 173 and 135 -> 116 us; NVFP4 194 -> 185 and 135 -> 124).
   q.r = slot_floats * 16 <= kQeLds ? 4 : slot_floats * 8 <= kQeLds ? 2 : 1;
   q.shmem = slot_floats * q.r * sizeof(float);
   // Waves, a multiple of four: the waves of a workgroup are dealt to the four SIMDs in turn, both workgroups of a
