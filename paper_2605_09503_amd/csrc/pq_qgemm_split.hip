@@ -19,6 +19,8 @@
 //   INT4 g128  77 x 1000 x 1152  15.3 ->  4.5     INT4 g64   1024 x 3072 x 3072  33 -> 27
 //   INT3 g64  512 x 3072 x 3072    31 -> 13       INT3 g64   2048 x 3072 x 3072  49 -> 32
 // INT4 in the 8-bit form of pq_qgemm_group.hip gained nothing here (15.5 -> 16.5, 46.9 -> 43.6 us): fp16 operands.
+#include <type_traits>
+
 #include "pq_qgemm_common.h"
 
 namespace pq {
@@ -38,15 +40,18 @@ struct RowSet {
   static constexpr int kBytes = (kScales + kRows * kScaleRow + 15) / 16 * 16;
 };
 
+typedef uint32_t uint32_any __attribute__((aligned(2)));              // two scale units, at any unit
+
 // ROWS (row-major operands only): a fragment read straight from a row-major operand touches a line for each of its 32
 // rows and takes a quarter of it.  Here the workgroup loads the codes and scale units of its next KS steps together,
 // whole runs of 32 KS bytes of every row, and the waves pick their step out of LDS (two sets of steps, a barrier for
 // each).  The sums are the same as without, and as those of the packed operands, bit for bit.  See rows_through_lds.
 // WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
+template <int TM, int TN, int WIDE, bool ROWS>
+constexpr int kSplitWaves = ROWS && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
-__global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, OperandView W, int M, int N,
-                                                                      int K, int g_shift, Output out, int tiles_m,
-                                                                      int tiles_n) {
+__global__ __launch_bounds__(KS * 64, (kSplitWaves<TM, TN, WIDE, ROWS>)) void qgemm_split_kernel(
+    OperandView A, OperandView W, int M, int N, int K, int g_shift, Output out, int tiles_m, int tiles_n) {
   constexpr int T = KS * 64;
   constexpr int BM = TM * 32, BN = TN * 32;
   constexpr bool CODES = MODE == kSplitE2m1;
@@ -194,25 +199,60 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
       }
     }
   } else {
-    // set: [rows of A, then of W] of KS steps; a row's codes with one spare piece, then the scale units of all rows
+    // set: [rows of A, then of W] of KS steps; a row's codes with one spare piece, then the scale units of all rows: one for
+    // each slice, or (CODES) a row's consecutive units of the set, of which the last set has the last ones of the row
     using L = RowSet<TM, TN, KS>;
     unsigned char* lds = reinterpret_cast<unsigned char*>(part);
     // thread t has slice t % (2 KS) of the set's 2 KS, of row t / (2 KS) of each 32
     const int slot = tid % (2 * KS), ld_row = tid / (2 * KS), ld_half = slot & 1;
     int4v codes[TM + TN];                              // the thread's slices of the set to come
-    uint16_t units[TM + TN];
+    uint32_t coff[TM + TN];
+#pragma unroll
+    for (int q = 0; q < TM + TN; ++q) {
+      const int row = q < TM ? min(q * 32 + ld_row, M - 1 - m0) : min((q - TM) * 32 + ld_row, N - 1 - n0);
+      coff[q] = (uint32_t)row * (uint32_t)(q < TM ? A.code_row : W.code_row);
+    }
+    // CODES: KS / 2 threads share a row's units of a set, two each for groups of 64, else one.  Registers decide here: with a
+    // unit for each slice the 64 x 64 tile has 174 and two workgroups on a compute unit, so 168 and three (52 shapes of more
+    // than 256 tiles: 0.83 of the time).  The fp16 operands need fewer, and their units by slice are 1 to 3 % faster than this.
+    constexpr int NU = CODES ? (L::kRows * (KS / 2) + T - 1) / T : TM + TN;
+    const int set_units = KS * kBK >> g_shift, last_units = (K >> g_shift) - set_units;      // >= 0, see rows_through_lds
+    const int piece = g_shift == 6 ? 2 : 1;
+    const int sc_piece = min(tid % (KS / 2) * piece, set_units - piece) * 2, sc_row = tid / (KS / 2);
+    const uint8_t* sc_from[NU];
+    uint32_t soff[NU];
+    std::conditional_t<CODES, uint32_t, uint16_t> units[NU];
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      if constexpr (CODES) {
+        const int row = sc_row + i * (T / (KS / 2));
+        sc_from[i] = (row < BM ? a_scales + (int64_t)min(row, M - 1 - m0) * A.sc_row
+                               : w_scales + (int64_t)min(row - BM, N - 1 - n0) * W.sc_row) + sc_piece;
+      } else {
+        const int row = i < TM ? min(i * 32 + ld_row, M - 1 - m0) : min((i - TM) * 32 + ld_row, N - 1 - n0);
+        soff[i] = (uint32_t)row * (uint32_t)(i < TM ? A.sc_row : W.sc_row);
+      }
+    }
     auto fetch = [&](int set) {
-      const int step = set * KS + (slot >> 1);
-      const int st = min(step, ksteps - 1);
+      const int st = min(set * KS + (slot >> 1), ksteps - 1);
       const int half = st * kBK + ld_half * 32 < K ? ld_half : 0;
-      const int unit = ((st * kBK) >> g_shift) + (per_half ? half : 0);
-      const int k0 = st * 32 + half * 16;
+      const uint32_t k0 = (uint32_t)(st * 32 + half * 16);
+      const uint32_t slice_unit = 2u * (uint32_t)(((st * kBK) >> g_shift) + (per_half ? half : 0));
 #pragma unroll
       for (int q = 0; q < TM + TN; ++q) {
-        const OperandView& v = q < TM ? A : W;
-        const int row = q < TM ? min(m0 + q * 32 + ld_row, M - 1) : min(n0 + (q - TM) * 32 + ld_row, N - 1);
-        codes[q] = *reinterpret_cast<const int4v*>(v.codes + (int64_t)row * v.code_row + k0);
-        units[q] = *reinterpret_cast<const uint16_t*>(v.scales + (int64_t)row * v.sc_row + unit * 2);
+        codes[q] = *reinterpret_cast<const int4v*>((q < TM ? a_codes : w_codes) + (coff[q] + k0));
+        if constexpr (!CODES)
+          units[q] = *reinterpret_cast<const uint16_t*>((q < TM ? a_scales : w_scales) + (soff[q] + slice_unit));
+      }
+      if constexpr (CODES) {
+        const int first = min(set * set_units, last_units) * 2;
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+          if (g_shift == 6)
+            units[i] = *reinterpret_cast<const uint32_any*>(sc_from[i] + first);
+          else
+            units[i] = *reinterpret_cast<const uint16_t*>(sc_from[i] + first);
+        }
       }
     };
     auto put = [&](unsigned char* set) {
@@ -220,7 +260,19 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
       for (int q = 0; q < TM + TN; ++q) {
         const int r = q * 32 + ld_row;
         *reinterpret_cast<int4v*>(set + r * L::kRow + slot * 16) = codes[q];
-        *reinterpret_cast<uint16_t*>(set + L::kScales + r * L::kScaleRow + slot * 2) = units[q];
+        if constexpr (!CODES) *reinterpret_cast<uint16_t*>(set + L::kScales + r * L::kScaleRow + slot * 2) = units[q];
+      }
+      if constexpr (CODES) {
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+          const int row = sc_row + i * (T / (KS / 2));
+          if (L::kRows * (KS / 2) % T != 0 && row >= L::kRows) continue;
+          unsigned char* to = set + L::kScales + row * L::kScaleRow + sc_piece;
+          if (g_shift == 6)
+            *reinterpret_cast<uint32_t*>(to) = units[i];
+          else
+            *reinterpret_cast<uint16_t*>(to) = (uint16_t)units[i];
+        }
       }
     };
     const int mine = 2 * ks + frag_half;
@@ -230,22 +282,25 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
     auto turn = [&](auto Pc, int o) {
       constexpr int P = decltype(Pc)::value;           // o % 2
       const unsigned char* have = lds + P * L::kBytes;
+      const int step = o * KS + ks;
+      const int unit = CODES ? (min(step, ksteps - 1) * kBK >> g_shift) - min(o * set_units, last_units) : mine;
+      const unsigned char* have_sc = have + L::kScales + unit * 2;
       Step own;
 #pragma unroll
       for (int q = 0; q < TM; ++q) {
         own.a[q].codes = *reinterpret_cast<const uint4*>(have + (q * 32 + frag_row) * L::kRow + mine * 16);
-        own.a[q].sc = *reinterpret_cast<const uint16_t*>(have + L::kScales + (q * 32 + frag_row) * L::kScaleRow + mine * 2);
+        own.a[q].sc = *reinterpret_cast<const uint16_t*>(have_sc + (q * 32 + frag_row) * L::kScaleRow);
       }
 #pragma unroll
       for (int q = 0; q < TN; ++q) {
         own.w[q].codes = *reinterpret_cast<const uint4*>(have + ((TM + q) * 32 + frag_row) * L::kRow + mine * 16);
-        own.w[q].sc = *reinterpret_cast<const uint16_t*>(have + L::kScales + ((TM + q) * 32 + frag_row) * L::kScaleRow + mine * 2);
+        own.w[q].sc = *reinterpret_cast<const uint16_t*>(have_sc + ((TM + q) * 32 + frag_row) * L::kScaleRow);
       }
       if (o + 1 < n_sets) {                            // uniform over the workgroup
         put(lds + (P ^ 1) * L::kBytes);
         fetch(o + 2);
       }
-      if (o * KS + ks < ksteps) multiply(own, o * KS + ks);          // uniform over the wave
+      if (step < ksteps) multiply(own, step);          // uniform over the wave
       __syncthreads();
     };
     fetch(0);
@@ -355,17 +410,15 @@ __global__ __launch_bounds__(KS * 64, 2) void qgemm_split_kernel(OperandView A, 
 
 // Whether a product of row-major operands reads them through LDS.  Up to one workgroup a unit its chain of loads is what
 // takes the time, and the direct loads are two steps ahead without a barrier (INT4 g128 77 x 1000 x 1152, 96 tiles: 7.0 us
-// direct, 7.8 through LDS).  With more, the lines of a unit's workgroups push each other out of its cache before all of
-// their quarters are read, the more so where every row starts at a line (K a multiple of 256); below the step counts here
-// the barriers cost as much.  Measured over 652 shapes at the tiles that they take, through LDS against direct, tiles of
-// four waves beyond 256: K a multiple of 256 0.57 to 0.99 of the time, else NVFP4 and fp16 operands from 8 steps on 0.67 to
-// 1.05, E2M1 codes from 24 on 0.60 to 1.04 (before that 0.9 to 1.2); of eight waves from 48 steps on 0.58 to 1.05.  us, direct
-// | through LDS | the staged tiles that these shapes took once: NVFP4 2048 x 3072 x 3072 72 | 47 | 56, 512 x 9216 x 3072
-// 57 | 38 | 53, INT4 g64 1024 x 3072 x 3072 41 | 32 | 37, INT3 g64 2048 x 3072 x 3072 84 | 50 | 58.
-static bool rows_through_lds(int mode, int64_t n_tiles, int ks, int K) {
-  if (n_tiles <= 256) return false;
-  const int steps = ks == 8 ? 48 : K % 256 == 0 ? 4 : mode == kSplitE2m1 ? 24 : 8;
-  return K >= steps * kBK;
+// direct, 7.8 through LDS; 212 shapes 0.71 to 1.20).  With more, the lines of a unit's workgroups push each other out of its
+// cache before all of their quarters are read.  A first set has to be full, and a few steps have to pay for the barriers.
+// Measured over 433 shapes of more than 256 tiles, at the tiles that they take, through LDS against direct: tiles of eight
+// waves from a full set on 0.55 to 1.03; of four waves from 4 steps on where every row starts at a line (K a multiple of
+// 256) 0.46 to 0.99, else from 6 steps on 0.56 to 1.05 (before that 0.97 to 1.06).  us, direct | through LDS | the staged
+// tiles that these shapes took once: NVFP4 2048 x 3072 x 3072 73 | 48 | 56, 512 x 9216 x 3072 57 | 37 | 53, INT4 g64
+// 1024 x 3072 x 3072 41 | 32 | 38, INT3 g64 2048 x 3072 x 3072 84 | 41 | 59.
+static bool rows_through_lds(int64_t n_tiles, int ks, int K) {
+  return n_tiles > 256 && K >= (ks == 8 ? 8 : K % 256 == 0 ? 4 : 6) * kBK;
 }
 
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
@@ -393,7 +446,7 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
                         hipStream_t st) {
   if constexpr (OUT != kOutDiff) {                     // the selection, which keeps the difference, packs its operands
     const int64_t n_tiles = (int64_t)((M + TM * 32 - 1) / (TM * 32)) * ((N + TN * 32 - 1) / (TN * 32));
-    if (!(A.panel && W.panel) && rows_through_lds(MODE, n_tiles, KS, K))
+    if (!(A.panel && W.panel) && rows_through_lds(n_tiles, KS, K))
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
   }
   return launch_split<MODE, TM, TN, KS, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);

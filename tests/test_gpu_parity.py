@@ -1004,7 +1004,14 @@ def test_qgemm_packed_equals_row_major(fmt, g, M, N, K):
     (pq.FMT_INT3, 64, 300, 4090, 256, S64), (pq.FMT_INT3, 256, 1000, 2050, 512, S64), (pq.FMT_INT3, 64, 1000, 2050, 1600, S64),
     (pq.FMT_INT3, 64, 2000, 2050, 2048, S64X96), (pq.FMT_INT3, 64, 515, 1003, 3200, S64X32), (pq.FMT_INT3, 64, 130, 3001, 3200, S32),
     (pq.FMT_INT3, 128, 1024, 1024, 256, S64), (pq.FMT_INT3, 128, 1024, 1080, 256, S64),   # 256 and 272 tiles
-    (pq.FMT_INT4, 64, 515, 3001, 448, S64), (pq.FMT_INT3, 64, 1000, 2050, 1472, S64),     # a step short of going through LDS
+    (pq.FMT_INT4, 64, 515, 3001, 448, S64), (pq.FMT_INT3, 64, 1000, 2050, 1472, S64),
+    # the last number of steps that is read straight and the first that goes through LDS: 5 and 6, of eight waves 7 and 8
+    (pq.FMT_INT4, 64, 515, 3001, 320, S64), (pq.FMT_INT4, 64, 515, 3001, 384, S64), (pq.FMT_INT3, 64, 1000, 2050, 320, S64),
+    (pq.FMT_INT3, 64, 1000, 2050, 384, S64), (pq.FMT_NVFP4, 16, 1000, 2050, 416, S64), (pq.FMT_INT3, 64, 515, 1003, 448, S64X32),
+    (pq.FMT_INT3, 64, 515, 1003, 512, S64X32), (pq.FMT_NVFP4, 16, 515, 1003, 480, S32), (pq.FMT_NVFP4, 16, 130, 3001, 544, S32),
+    # scale units of a set: groups of 64, 128 and 256, the last set not full
+    (pq.FMT_INT3, 64, 130, 3001, 576, S32), (pq.FMT_INT3, 128, 515, 1003, 640, S64X32), (pq.FMT_INT3, 256, 515, 1003, 768, S64X32),
+    (pq.FMT_INT3, 128, 1000, 2050, 640, S64), (pq.FMT_INT3, 256, 700, 4090, 768, S64),
 ])
 def test_qgemm_row_major_loaders_equal_packed(fmt, g, M, N, K, tile):
     """Where the waves split K, row-major operands are read straight or through LDS, by the number of tiles and steps:
