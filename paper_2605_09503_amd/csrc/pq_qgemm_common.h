@@ -220,8 +220,10 @@ __device__ __forceinline__ void store_diff(double d2, double* red, int threads, 
 // epilogue; pq_qgemm_run, whose preparation has not seen the codes, looks at every code.  A workgroup that finds one
 // computes its tile again with E4M3 operands straight from memory, over what it stored.  The sums are those of the
 // kernel that calls, in its order (KS shares of the steps; every factor that differs is a power of two), so rows
-// without such codes keep their bits.  Groups are a multiple of 64.  The marks cost nothing that shows (INT3 g64 512 x 3072 x 3072 14.2 us with and without; the scale preparation that sets them 0 to 0.6 us);
-// looking at every code takes 13 to 20 % of a split tile's time and 2 to 5 of a large one's.
+// without such codes keep their bits.  Groups are a multiple of 64.  The marks cost nothing that shows (INT3 g64
+// 512 x 3072 x 3072 14.2 us with and without); the scale preparation that sets them takes 0.3 to 1 us longer (2.2 at
+// 31 x 2337 x 12288; four of a lane's pieces of codes asked for at once instead of one: the same), and looking at every
+// code takes 13 to 20 % of a split tile's time and 2 to 5 of a large one's.
 enum WideTest : int { kWideNone = 0, kWideMarks = 1, kWideCodes = 2 };
 
 // a code beyond three bits sets bit 3 of its nibble (its bits 3 and 2 differ)
