@@ -210,7 +210,9 @@ int pq_select_perm_device_scales(pq_format fmt, int group, const double* act_sum
  * through a plain bf16 MFMA kernel, both with fp32 accumulation: E_out carries a relative error of
  * about 1e-5 against exact arithmetic).  report->sum_x2 holds sum_b ||X_b W^T||^2, sum_w2 is 0.
  * workspace: pq_workspace_bytes(PQ_OP_SELECT_PERM_OUTPUT, fmt, group, M, N, K, n_batches) bytes -- it
- * holds the fp32 reference products of all batches (4 n_batches M N bytes).
+ * holds the fp32 reference products of all batches (4 n_batches M N bytes) and the operands of as many batches and
+ * orders as one launch takes.  A smaller one is accepted as long as it holds those of one batch and one order; the call
+ * then multiplies them one after the other.
  */
 int pq_select_perm_output_error(pq_format fmt, int group, const double* act_sumsq, const double* w_sumsq,
                                 int64_t K, const void* const* x_calib, int n_batches, int64_t M,

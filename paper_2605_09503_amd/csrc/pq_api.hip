@@ -159,14 +159,15 @@ static int select_common(bool output_metric, pq_format fmt, int group, const dou
     if (!aligned16(x_calib[b])) return fail(PQ_ERR_SHAPE, "%s: x_calib[%d] must be 16-byte aligned", who, b);
   }
   if (!aligned16(w_bf16)) return fail(PQ_ERR_SHAPE, "%s: w must be 16-byte aligned", who);
-  const size_t need = output_metric ? select_output_workspace_bytes(fmt, group, M, N, K, n_batches)
+  const size_t need = output_metric ? select_output_least_workspace_bytes(fmt, group, M, N, K, n_batches)
                                     : select_workspace_bytes(M, N, K, n_batches);
   if (!workspace || workspace_bytes < need)
     return fail(PQ_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", who, need,
                 workspace ? workspace_bytes : (size_t)0);
   if (output_metric)
     return run_select_output(fmt, group, act_sumsq, w_sumsq, K, x_calib, n_batches, M, w_bf16, N, act_tensor_scale,
-                             w_tensor_scale, alphas, n_alpha, tau, perm_out, report, workspace, as_stream(stream));
+                             w_tensor_scale, alphas, n_alpha, tau, perm_out, report, workspace, workspace_bytes,
+                             as_stream(stream));
   return run_select(fmt, group, act_sumsq, w_sumsq, K, x_calib, n_batches, M, w_bf16, N,
                     act_tensor_scale, w_tensor_scale, act_ts_dev, w_ts_dev, alphas, n_alpha, tau, perm_out, report,
                     workspace, as_stream(stream));

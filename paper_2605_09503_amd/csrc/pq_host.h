@@ -59,13 +59,28 @@ int launch_quantize_rows(pq_format fmt, int group, const void* x, int64_t rows, 
                          const int32_t* perm, const float* tensor_scale, uint8_t* codes, void* scales,
                          hipStream_t st);
 
-// the same, gathered, straight into the operand layout; a row of K <= 65536 and its group maxima fit a workgroup's LDS
+// the same, gathered, straight into the operand layout, in several orders at once; a row of K <= 65536 and its group
+// maxima fit a workgroup's LDS
 constexpr size_t kPanelRowLds = 65536 * 2 + 65536 / 32 * 4;
-int launch_quantize_rows_panel(pq_format fmt, int group, const void* x, int64_t rows, int64_t K, const int32_t* perm,
-                               const float* ts, void* operand, hipStream_t st);
+// up to kMaxMomentBatches tensors of `rows` rows, one below the other
+struct RowBatches {
+  const uint16_t* p[kMaxMomentBatches];
+  int64_t rows;
+};
+// `rows` rows into n operands (one an order), `next` bytes apart; ts: the NVFP4 tensor scale
+struct PanelJob {
+  RowBatches x;
+  int64_t rows;
+  uint8_t* operand;
+  size_t next;
+  const float* ts;
+};
+// orders first .. first + n - 1: order 0 is the original one, order c > 0 is perms[c - 1][K]
+int launch_quantize_rows_panel(pq_format fmt, int group, const PanelJob& a, const PanelJob& w, int64_t K,
+                               const int32_t* perms, int first, int n, hipStream_t st);
 
 // output tile of the product that a shape takes, and its size (pq_qgemm_tile.hip)
-int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K);
+int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int problems = 1);
 void tile_size(int tile, int* bm, int* bn);
 
 // The error evaluation keeps one row as fp32 in LDS, one spare slot per eight channels: 4.5 K bytes of the
@@ -91,11 +106,13 @@ int launch_channel_stats(const void* x, int64_t rows, int64_t K, int64_t ld, dou
 int launch_channel_variance(const double* sum, const double* sumsq, int64_t n_rows, int64_t K, double* out,
                             hipStream_t st);
 int launch_channel_absmax_sq(const float* absmax, int64_t K, double* out, hipStream_t st);
+// workspace of the selection by output error, and the least that it takes
 size_t select_output_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches);
+size_t select_output_least_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches);
 int run_select_output(pq_format fmt, int group, const double* act_sumsq, const double* w_sumsq, int64_t K,
                       const void* const* x_calib, int n_batches, int64_t M, const void* w, int64_t N,
                       float act_ts, float w_ts, const double* alphas, int n_alpha, double tau,
-                      int32_t* perm_out, pq_select_report* report, void* ws, hipStream_t st);
+                      int32_t* perm_out, pq_select_report* report, void* ws, size_t ws_bytes, hipStream_t st);
 int run_quant_error(pq_format fmt, int group, const void* x, int64_t rows, int64_t K,
                     const int32_t* perm, float ts, double* err_out, void* ws, hipStream_t st);
 

@@ -172,18 +172,12 @@ int run_pack_operand(pq_format fmt, int group, const uint8_t* codes, const void*
 int run_qgemm_packed(pq_format fmt, int group, const void* a_operand, const float* a_ts,
                      const void* w_operand, const float* w_ts, int64_t M, int64_t N, int64_t K,
                      const void* bias, void* y, int64_t ldy, bool out_f32, hipStream_t st) {
-  return run_qgemm_packed_out(fmt, group, a_operand, a_ts, w_operand, w_ts, M, N, K, bias,
-                              Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}, st);
-}
-
-int run_qgemm_packed_out(pq_format fmt, int group, const void* a_operand, const float* a_ts, const void* w_operand,
-                         const float* w_ts, int64_t M, int64_t N, int64_t K, const void* bias, const Output& out,
-                         hipStream_t st) {
   if (M * 32 > 0x7FFFFFFF || N * 32 > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many rows for the panel layout");
   const OperandView A = panel_view(fmt, group, a_operand, M, K, a_ts);
   OperandView W = panel_view(fmt, group, w_operand, N, K, w_ts);
   W.bias = (const uint16_t*)bias;
-  return launch_qgemm_views(fmt, group, A, W, M, N, K, out, st);
+  return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false},
+                            choose_tile(fmt, group, M, N, K), st);
 }
 
 }  // namespace pq

@@ -45,6 +45,7 @@ template <int FMT, int G, int BM, int BN, int WGM, int WGN, int OUT>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, OperandView W, int M, int N,
                                                               int K, Output out,
                                                               int tiles_m, int tiles_n) {
+  if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   const float* __restrict__ a_mul = A.mul;
   const float* __restrict__ w_mul = W.mul;
   const int a_mul_stride = A.mul_stride, w_mul_stride = W.mul_stride;
@@ -427,7 +428,7 @@ static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N,
   int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, out, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles, out.problems), dim3(T), shmem, st, A, W, M, N, K, out, tiles_m, tiles_n);
   return check_hip(hipGetLastError(), "qgemm_kernel");
 }
 
@@ -451,8 +452,7 @@ static int launch_views_fg(const OperandView& A, const OperandView& W, int M, in
 
 // the product kernel on two operand views (any mix of layouts)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
-                       int64_t N, int64_t K, const Output& out, hipStream_t st) {
-  const int tile = choose_tile(fmt, group, M, N, K);
+                       int64_t N, int64_t K, const Output& out, int tile, hipStream_t st) {
   if (tile >= kTileSplit32)
     return launch_qgemm_split(fmt, group, A, W, (int)M, (int)N, (int)K, out, tile, st);
   // groups of 64 and more in large tiles: the codes go to the matrix unit as they are
@@ -513,7 +513,8 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     A.marked = W.marked = mark;
   }
   if (!(phases & 2)) return PQ_OK;
-  return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}, st);
+  return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false},
+                            choose_tile(fmt, group, M, N, K), st);
 }
 
 }  // namespace pq

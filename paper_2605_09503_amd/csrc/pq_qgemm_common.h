@@ -190,7 +190,8 @@ __device__ __forceinline__ void assign_tile(int tiles_m, int tiles_n, int& tile_
 // ------------------------------------------------------------------------ epilogue
 // What becomes of the product: rounded to bf16, stored in fp32, or compared with a reference -- then only the sum of
 // (ref - product)^2 over a workgroup's tile is kept, in fp64 (each difference exact, the sum in a fixed order):
-// y[tile] = or += that sum.
+// y[tile] = or += that sum.  A launch that compares may hold several problems of one shape and one reference, problem z in
+// blockIdx.y: its operands lie z * a_next and z * w_next bytes further on, its sums z * y_next.
 enum OutKind : int { kOutBf16 = 0, kOutF32 = 1, kOutDiff = 2 };
 struct Output {
   int kind;
@@ -198,7 +199,23 @@ struct Output {
   int64_t ldy;          // kOutDiff: of ref
   const float* ref;     // kOutDiff only
   bool add;             // kOutDiff only
+  size_t a_next = 0, w_next = 0;
+  int64_t y_next = 0;
+  unsigned problems = 1;
 };
+
+// the operands and the sums of this workgroup's problem (a factor of stride 0 is a tensor scale, the same for all)
+__device__ __forceinline__ void enter_problem(OperandView& A, OperandView& W, Output& out) {
+  const size_t z = blockIdx.y;
+  auto move = [&](OperandView& v, size_t by) {
+    v.codes += by;
+    v.scales += by;
+    if (v.mul_stride) v.mul = reinterpret_cast<const float*>(reinterpret_cast<const char*>(v.mul) + by);
+  };
+  move(A, z * out.a_next);
+  move(W, z * out.w_next);
+  out.y = reinterpret_cast<double*>(out.y) + (int64_t)z * out.y_next;
+}
 
 // the sums of a workgroup's threads, in a fixed order, to y[tile] (called by all threads; red: free LDS)
 __device__ __forceinline__ void store_diff(double d2, double* red, int threads, int tile, const Output& out) {
@@ -362,14 +379,23 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
           for (int e = 0; e < 4; ++e) v[e] += wb[i][q * 4 + e];
         }
         if constexpr (OUT == kOutDiff) {
-          if (m < M) {
+          if (m < M && n < N) {
             const float* r = out.ref + (int64_t)m * ldy + n;
+            float f[4];
+            if (n + 3 < N) {
+              const float4 whole = *reinterpret_cast<const float4*>(r);
+              f[0] = whole.x; f[1] = whole.y; f[2] = whole.z; f[3] = whole.w;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                f[e] = n + e < N ? r[e] : 0.0f;
+                v[e] = n + e < N ? v[e] : 0.0f;        // no column: no difference
+              }
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              if (n + e < N) {
-                const double d = (double)r[e] - (double)v[e];
-                d2 = fma(d, d, d2);
-              }
+              const double d = (double)f[e] - (double)v[e];
+              d2 = fma(d, d, d2);
             }
           }
         } else if constexpr (OUT == kOutF32) {
@@ -436,15 +462,11 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
   return v;
 }
 
-// the product kernel on two operand views (pq_qgemm.hip)
+// the product kernel on two operand views (pq_qgemm.hip), with the given tile
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
-                       int64_t N, int64_t K, const Output& out, hipStream_t st);
+                       int64_t N, int64_t K, const Output& out, int tile, hipStream_t st);
 // tiles (= workgroups) of that launch
-int64_t qgemm_tiles(pq_format fmt, int group, int64_t M, int64_t N, int64_t K);
-// the product of two packed operands
-int run_qgemm_packed_out(pq_format fmt, int group, const void* a_operand, const float* a_ts, const void* w_operand,
-                         const float* w_ts, int64_t M, int64_t N, int64_t K, const void* bias, const Output& out,
-                         hipStream_t st);
+int64_t qgemm_tiles(int tile, int64_t M, int64_t N);
 // output tiles of the product kernels (choose_tile in pq_qgemm_tile.hip)
 enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kTileSplit64x32 = 5, kTileSplit64 = 6, kTileSplit64x96 = 7 };
 // small outputs (pq_qgemm_split.hip)

@@ -45,6 +45,7 @@ template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT, int WIDE>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView A, OperandView W, int M, int N,
                                                                     int K, int g_shift, Output out, int tiles_m,
                                                                     int tiles_n) {
+  if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   constexpr int T = WGM * WGN * 64;
   constexpr int WTM = (BM + WGM * 32 - 1) / (WGM * 32) * 32, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -338,7 +339,7 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(T), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles, out.problems), dim3(T), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
                      tiles_n);
   return check_hip(hipGetLastError(), "qgemm_group_kernel");
 }

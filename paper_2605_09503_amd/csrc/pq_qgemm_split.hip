@@ -52,6 +52,7 @@ constexpr int kSplitWaves = ROWS && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2; 
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
 __global__ __launch_bounds__(KS * 64, (kSplitWaves<TM, TN, WIDE, ROWS>)) void qgemm_split_kernel(
     OperandView A, OperandView W, int M, int N, int K, int g_shift, Output out, int tiles_m, int tiles_n) {
+  if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   constexpr int T = KS * 64;
   constexpr int BM = TM * 32, BN = TN * 32;
   constexpr bool CODES = MODE == kSplitE2m1;
@@ -361,12 +362,22 @@ __global__ __launch_bounds__(KS * 64, (kSplitWaves<TM, TN, WIDE, ROWS>)) void qg
       }
       if constexpr (OUT == kOutDiff) {
         const float* r = out.ref + (int64_t)m * ldy + n;
+        float f[8];
+        if (n + 7 < N) {
+          const float4 lo = *reinterpret_cast<const float4*>(r), hi = *reinterpret_cast<const float4*>(r + 4);
+          f[0] = lo.x; f[1] = lo.y; f[2] = lo.z; f[3] = lo.w;
+          f[4] = hi.x; f[5] = hi.y; f[6] = hi.z; f[7] = hi.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            f[e] = n + e < N ? r[e] : 0.0f;
+            v[e] = n + e < N ? v[e] : 0.0f;            // no column: no difference
+          }
+        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          if (n + e < N) {
-            const double d = (double)r[e] - (double)v[e];
-            d2 = fma(d, d, d2);
-          }
+          const double d = (double)f[e] - (double)v[e];
+          d2 = fma(d, d, d2);
         }
       } else if constexpr (OUT == kOutF32) {
         float* yo = reinterpret_cast<float*>(y) + (int64_t)m * ldy + n;
@@ -435,7 +446,7 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles, out.problems), dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
                      tiles_n);
   return check_hip(hipGetLastError(), "qgemm_split_kernel");
 }

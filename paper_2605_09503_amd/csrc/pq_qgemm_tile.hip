@@ -3,7 +3,7 @@
 
 namespace pq {
 
-// The tile with the shortest predicted time.  n workgroups run on 256 compute units, each does s 64-wide steps; with
+// The tile with the shortest predicted time of `problems` products of that shape in one launch.  n workgroups run on 256 compute units, each does s 64-wide steps; with
 // c = ceil(n / 256) rounds and r = max(n / 256, 1) of them really filled,
 //     time = l0 + odd (N mod 8) + max(rounds (a + b s), l1 s),  rounds = th c + (1 - th) r,
 // where l1 s is the latency of one workgroup's chain of steps in the tiles whose workgroups share a unit, and odd the
@@ -42,7 +42,7 @@ static constexpr TileCost kTileCost[4][8] = {
      {2.32f, 0.1103f, 4.02f, 0.176f, 0.698f, 0.038f}},
 };
 
-int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K) {
+int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int problems) {
   const int cls = fmt == PQ_FMT_NVFP4 ? 0 : group == 32 ? 1 : fmt == PQ_FMT_INT4 ? 2 : 3;
   const float s = (float)((K + kBK - 1) / kBK), past = (float)(N % 8);
   int best = kTile256;
@@ -50,7 +50,7 @@ int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K) {
   for (int t = kTile256; t <= kTileSplit64x96; ++t) {
     const TileCost& k = kTileCost[cls][t];
     const TileSize& z = kTileSize[t];
-    const int64_t n = ((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn);
+    const int64_t n = ((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn) * problems;
     const float c = (float)((n + 255) / 256), r = n > 256 ? (float)n / 256.0f : 1.0f;
     float time = (k.th * c + (1.0f - k.th) * r) * (k.a + k.b * s);
     if (time < k.l1 * s) time = k.l1 * s;
@@ -68,8 +68,8 @@ void tile_size(int tile, int* bm, int* bn) {
   *bn = kTileSize[tile].bn;
 }
 
-int64_t qgemm_tiles(pq_format fmt, int group, int64_t M, int64_t N, int64_t K) {
-  const TileSize& z = kTileSize[choose_tile(fmt, group, M, N, K)];
+int64_t qgemm_tiles(int tile, int64_t M, int64_t N) {
+  const TileSize& z = kTileSize[tile];
   return ((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn);
 }
 

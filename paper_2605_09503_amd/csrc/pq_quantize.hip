@@ -184,106 +184,121 @@ int launch_quantize_rows(pq_format fmt, int group, const void* x, int64_t rows, 
 
 // ------------------------------------------------------------------ gather and quantize into the panel
 // quantize_rows_kernel followed by pack_operand_kernel in one pass over the row, for the selection by output error,
-// which prepares every operand once for each candidate order: a workgroup per row, the channels picked out of LDS, the
-// group maxima kept there until the row's largest fixes the power of two of its INT scale units.  Bound by its launch
-// and one row's chain at 1024 x 3072 (4.8 + 4.8 us as two kernels, 5.3 so).
+// which prepares every operand once for each candidate order: a workgroup per row, which stays in LDS for all the
+// orders that it takes (grid.y shares them out), the channels picked out of it, the group maxima kept there until the
+// row's largest fixes the power of two of its INT scale units.  Bound by a row's chain (order, gather, store, barrier),
+// so a launch takes as many rows and orders as there are, both operands in one: a launch an order and tensor took 21
+// launches and 145 us for seven orders of 2 x 1024 + 3072 rows of 3072, this one 55 us.
 template <int FMT, int G>
-__global__ __launch_bounds__(256) void quantize_rows_panel_kernel(const uint16_t* __restrict__ x, int64_t rows,
-                                                                  int64_t K, const int32_t* __restrict__ perm,
-                                                                  const float* __restrict__ tensor_scale, int units,
-                                                                  uint8_t* __restrict__ p_codes,
-                                                                  uint16_t* __restrict__ p_scales,
-                                                                  float* __restrict__ p_mul) {
+__global__ __launch_bounds__(256) void quantize_rows_panel_kernel(PanelJob a_job, PanelJob w_job, int64_t K,
+                                                                  const int32_t* __restrict__ perms, int first, int n,
+                                                                  int per_wg, OperandLayout a_lay, OperandLayout w_lay) {
   extern __shared__ __align__(16) uint16_t row_lds[];       // the row, K elements, then the INT group maxima
   __shared__ float wave_mx[4];
+  const bool is_w = (int64_t)blockIdx.x >= a_job.rows;
+  const PanelJob& job = is_w ? w_job : a_job;
+  const OperandLayout& lay = is_w ? w_lay : a_lay;
   float T = 0.0f, encT = 0.0f;
   if constexpr (FMT == kNvfp4) {
-    T = *tensor_scale;
+    T = *job.ts;
     encT = nv4_enc_scale(T);
   }
-  const int64_t row = blockIdx.x;
-  const uint16_t* xr = x + row * K;
+  const int64_t rows = job.rows, row = (int64_t)blockIdx.x - (is_w ? a_job.rows : 0);
+  const int batch = (int)(row / job.x.rows);
+  const uint16_t* xr = job.x.p[batch] + (row - batch * job.x.rows) * K;
   float* h_lds = reinterpret_cast<float*>(row_lds + K);
-  const int chunks = (int)(K / 8);
+  const int chunks = (int)(K / 8), units = (int)lay.units;
   for (int c = threadIdx.x; c < chunks; c += 256)
     reinterpret_cast<uint4*>(row_lds)[c] = *reinterpret_cast<const uint4*>(xr + (int64_t)c * 8);
   __syncthreads();
-  float row_max = 0.0f;
-  // all 256 lanes iterate together so the group reduction always sees whole groups
-  for (int c0 = 0; c0 < chunks; c0 += 256) {
-    const int c = c0 + threadIdx.x, cc = min(c, chunks - 1);
-    float v[8];
-    if (perm) {
-      const int4* pp = reinterpret_cast<const int4*>(perm + (int64_t)cc * 8);
-      const int4 i0 = pp[0], i1 = pp[1];
-      v[0] = bf16_to_f32(row_lds[i0.x]); v[1] = bf16_to_f32(row_lds[i0.y]);
-      v[2] = bf16_to_f32(row_lds[i0.z]); v[3] = bf16_to_f32(row_lds[i0.w]);
-      v[4] = bf16_to_f32(row_lds[i1.x]); v[5] = bf16_to_f32(row_lds[i1.y]);
-      v[6] = bf16_to_f32(row_lds[i1.z]); v[7] = bf16_to_f32(row_lds[i1.w]);
-    } else {
-      unpack8(reinterpret_cast<const uint4*>(row_lds)[cc], v);
+  const int q0 = (int)blockIdx.y * per_wg, q1 = min(n, q0 + per_wg);
+  for (int q = q0; q < q1; ++q) {
+    const int32_t* perm = first + q == 0 ? nullptr : perms + (int64_t)(first + q - 1) * K;
+    uint8_t* operand = job.operand + (size_t)q * job.next;
+    uint8_t* p_codes = operand + lay.codes;
+    uint16_t* p_scales = reinterpret_cast<uint16_t*>(operand + lay.scales);
+    float row_max = 0.0f;
+    // all 256 lanes iterate together so the group reduction always sees whole groups
+    for (int c0 = 0; c0 < chunks; c0 += 256) {
+      const int c = c0 + threadIdx.x, cc = min(c, chunks - 1);
+      float v[8];
+      if (perm) {
+        const int4* pp = reinterpret_cast<const int4*>(perm + (int64_t)cc * 8);
+        const int4 i0 = pp[0], i1 = pp[1];
+        v[0] = bf16_to_f32(row_lds[i0.x]); v[1] = bf16_to_f32(row_lds[i0.y]);
+        v[2] = bf16_to_f32(row_lds[i0.z]); v[3] = bf16_to_f32(row_lds[i0.w]);
+        v[4] = bf16_to_f32(row_lds[i1.x]); v[5] = bf16_to_f32(row_lds[i1.y]);
+        v[6] = bf16_to_f32(row_lds[i1.z]); v[7] = bf16_to_f32(row_lds[i1.w]);
+      } else {
+        unpack8(reinterpret_cast<const uint4*>(row_lds)[cc], v);
+      }
+      const float a = group_max<G / 8>(fmaxf(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))),
+                                             fmaxf(fmaxf(fabsf(v[4]), fabsf(v[5])), fmaxf(fabsf(v[6]), fabsf(v[7])))));
+      const ChunkOut<FMT> o = quantize_chunk<FMT, G>(v, T, encT);
+      if constexpr (FMT == kNvfp4) {
+        // a scale unit is the bytes of 32 positions = four lanes; the first takes the byte of the second pair (lane ^ 2)
+        const uint32_t other = dpp_u32<0x4E>(o.scale);
+        if (c < chunks && (c & 3) == 0) p_scales[(int64_t)(c >> 2) * rows + row] = (uint16_t)(o.scale | (other << 8));
+      } else if (c < chunks) {
+        row_max = fmaxf(row_max, a);
+        if ((c & (G / 8 - 1)) == 0) h_lds[c / (G / 8)] = a;
+      }
+      if (c < chunks)
+        *reinterpret_cast<uint32_t*>(p_codes + ((int64_t)(c >> 3) * rows + row) * 32 + (c & 7) * 4) = o.codes;
     }
-    const float a = group_max<G / 8>(fmaxf(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))),
-                                           fmaxf(fmaxf(fabsf(v[4]), fabsf(v[5])), fmaxf(fabsf(v[6]), fabsf(v[7])))));
-    const ChunkOut<FMT> o = quantize_chunk<FMT, G>(v, T, encT);
-    if constexpr (FMT == kNvfp4) {
-      // a scale unit is the bytes of 32 positions = four lanes; the first takes the byte of the second pair (lane ^ 2)
-      const uint32_t other = dpp_u32<0x4E>(o.scale);
-      if (c < chunks && (c & 3) == 0) p_scales[(int64_t)(c >> 2) * rows + row] = (uint16_t)(o.scale | (other << 8));
-    } else if (c < chunks) {
-      row_max = fmaxf(row_max, a);
-      if ((c & (G / 8 - 1)) == 0) h_lds[c / (G / 8)] = a;
+    if constexpr (FMT != kNvfp4) {
+      // units h * 2^-E with E = exponent(row maximum) - 10, row factor 2^E / Q (see pack_operand_kernel)
+      constexpr float Q = qmax_of(FMT);
+      row_max = wave_max(row_max);
+      if ((threadIdx.x & 63) == 0) wave_mx[threadIdx.x >> 6] = row_max;
+      __syncthreads();
+      const float mx = fmaxf(fmaxf(wave_mx[0], wave_mx[1]), fmaxf(wave_mx[2], wave_mx[3]));
+      int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
+      if (mx == 0.0f) e = 0;
+      const int E = max(-120, min(120, e - 10));
+      const float down = as_f32((uint32_t)(127 - E) << 23);
+      if (threadIdx.x == 0) *(reinterpret_cast<float*>(operand + lay.mul) + row) = as_f32((uint32_t)(127 + E) << 23) / Q;
+      for (int u = threadIdx.x; u < units; u += 256)
+        p_scales[(int64_t)u * rows + row] = __builtin_bit_cast(uint16_t, (_Float16)(h_lds[u] * down));
+      if (q + 1 < q1) __syncthreads();                 // the maxima have been read
     }
-    if (c < chunks)
-      *reinterpret_cast<uint32_t*>(p_codes + ((int64_t)(c >> 3) * rows + row) * 32 + (c & 7) * 4) = o.codes;
-  }
-  if constexpr (FMT != kNvfp4) {
-    // units h * 2^-E with E = exponent(row maximum) - 10, row factor 2^E / Q (see pack_operand_kernel)
-    constexpr float Q = qmax_of(FMT);
-    row_max = wave_max(row_max);
-    if ((threadIdx.x & 63) == 0) wave_mx[threadIdx.x >> 6] = row_max;
-    __syncthreads();
-    const float mx = fmaxf(fmaxf(wave_mx[0], wave_mx[1]), fmaxf(wave_mx[2], wave_mx[3]));
-    int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
-    if (mx == 0.0f) e = 0;
-    const int E = max(-120, min(120, e - 10));
-    const float down = as_f32((uint32_t)(127 - E) << 23);
-    if (threadIdx.x == 0) p_mul[row] = as_f32((uint32_t)(127 + E) << 23) / Q;
-    for (int u = threadIdx.x; u < units; u += 256)
-      p_scales[(int64_t)u * rows + row] = __builtin_bit_cast(uint16_t, (_Float16)(h_lds[u] * down));
   }
 }
 
 template <int FMT, int G>
-static int launch_q_panel(const void* x, int64_t rows, int64_t K, const int32_t* perm, const float* ts,
-                          const OperandLayout& L, uint8_t* operand, hipStream_t st) {
-  const size_t shmem = (size_t)K * 2 + (FMT == kNvfp4 ? 0 : (size_t)L.units * 4);
+static int launch_q_panel(pq_format fmt, const PanelJob& a, const PanelJob& w, int64_t K, const int32_t* perms, int first,
+                          int n, hipStream_t st) {
+  const OperandLayout al = operand_layout(fmt, G, a.rows, K), wl = operand_layout(fmt, G, w.rows, K);
+  const size_t shmem = (size_t)K * 2 + (FMT == kNvfp4 ? 0 : (size_t)al.units * 4);
   auto kern = quantize_rows_panel_kernel<FMT, G>;
   if (shmem > kPanelRowLds) return fail(PQ_ERR_SHAPE, "K=%lld too large for a row in LDS", (long long)K);   // refused earlier
+  if (a.rows + w.rows > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many rows");
   static std::atomic<uint64_t> raised{0};
   if (shmem > 48 * 1024) {
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kPanelRowLds, raised,
                            "hipFuncSetAttribute(quantize_rows_panel_kernel)"))
       return rc;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(256), shmem, st, (const uint16_t*)x, rows, K, perm, ts,
-                     (int)L.units, operand + L.codes, (uint16_t*)(operand + L.scales), (float*)(operand + L.mul));
+  // orders a workgroup takes: all of them where the rows alone fill the chip (eight workgroups a unit), fewer below
+  const int64_t rows = a.rows + w.rows;
+  const int shares = (int)(rows >= 2048 ? 1 : rows * n <= 2048 ? n : (2048 + rows - 1) / rows);
+  const int per_wg = (n + shares - 1) / shares;
+  hipLaunchKernelGGL(kern, dim3((unsigned)rows, (unsigned)((n + per_wg - 1) / per_wg)), dim3(256), shmem, st, a, w, K, perms,
+                     first, n, per_wg, al, wl);
   return check_hip(hipGetLastError(), "quantize_rows_panel_kernel");
 }
 
-int launch_quantize_rows_panel(pq_format fmt, int group, const void* x, int64_t rows, int64_t K, const int32_t* perm,
-                               const float* ts, void* operand, hipStream_t st) {
-  const OperandLayout L = operand_layout(fmt, group, rows, K);
-  uint8_t* o = (uint8_t*)operand;
-  if (fmt == PQ_FMT_NVFP4) return launch_q_panel<kNvfp4, 16>(x, rows, K, perm, ts, L, o, st);
-#define PQ_INT_CASE(F, FE)                                                          \
-  if (fmt == F) {                                                                   \
-    switch (group) {                                                                \
-      case 32: return launch_q_panel<FE, 32>(x, rows, K, perm, ts, L, o, st);       \
-      case 64: return launch_q_panel<FE, 64>(x, rows, K, perm, ts, L, o, st);       \
-      case 128: return launch_q_panel<FE, 128>(x, rows, K, perm, ts, L, o, st);     \
-      case 256: return launch_q_panel<FE, 256>(x, rows, K, perm, ts, L, o, st);     \
-    }                                                                               \
+int launch_quantize_rows_panel(pq_format fmt, int group, const PanelJob& a, const PanelJob& w, int64_t K,
+                               const int32_t* perms, int first, int n, hipStream_t st) {
+  if (fmt == PQ_FMT_NVFP4) return launch_q_panel<kNvfp4, 16>(fmt, a, w, K, perms, first, n, st);
+#define PQ_INT_CASE(F, FE)                                                              \
+  if (fmt == F) {                                                                       \
+    switch (group) {                                                                    \
+      case 32: return launch_q_panel<FE, 32>(fmt, a, w, K, perms, first, n, st);        \
+      case 64: return launch_q_panel<FE, 64>(fmt, a, w, K, perms, first, n, st);        \
+      case 128: return launch_q_panel<FE, 128>(fmt, a, w, K, perms, first, n, st);      \
+      case 256: return launch_q_panel<FE, 256>(fmt, a, w, K, perms, first, n, st);      \
+    }                                                                                   \
   }
   PQ_INT_CASE(PQ_FMT_INT4, kInt4)
   PQ_INT_CASE(PQ_FMT_INT3, kInt3)

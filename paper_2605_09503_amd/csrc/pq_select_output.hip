@@ -5,10 +5,15 @@
 // product runs through the forward path (gathering quantizer straight into the operand layout, product kernel whose
 // epilogue keeps the squared difference to the unquantized product instead of a result); the unquantized product
 // comes from a plain bf16 MFMA kernel below, which also sums its squares.  Every sum has a fixed order.
-// Per candidate and batch two launches and one quantizer for the weights; with an fp32 result, a packing pass and
-// three reduction launches of their own there were five, and 1024 x 3072 x 3072 with two batches of INT4 took 955 us, now 700 to
-// 720.
+//
+// The batches of a call stand one below the other as the rows of one product, and several candidate orders share a
+// launch (see plan_of): one quantizer launch for all their operands, one product launch whose grid holds all their
+// tiles.  With a product launch for each order and batch, 1024 x 3072 x 3072 with two batches of INT4 took 14
+// products of 30 us, none of which filled the chip with large tiles, and 21 quantizer launches: 715 us, now 406
+// (NVFP4 659 -> 423, INT3 g64 3 x 700 x 1000 x 1152 354 -> 131, INT4 g64 4 x 4608 x 3072 x 3072 3.73 -> 3.14 ms).
 #include <string.h>
+
+#include <algorithm>
 
 #include "pq_qgemm_common.h"
 
@@ -24,10 +29,11 @@ constexpr int kRefRowBytes = kRefStep * 2 + 16;   // padded LDS row, as in pq_qg
 constexpr int kRefStage = 2 * kRefTile * kRefRowBytes;
 
 // Y[m, n] = sum_k X[m, k] W[n, k], bf16 inputs, fp32 accumulation (v_mfma_f32_32x32x16_bf16), fp32 output, and the
-// tile's sum of squares (+)= to sq.  128 x 128 tile, four waves of 64 x 64; K % 32 == 0.  A step's pieces are
-// loaded while the one before it is multiplied and stored into the other of two stages: one barrier a step (one
-// stage with two barriers and half the step: 61 us at 1024 x 3072 x 3072).
-__global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+// tile's sum of squares (+)= to sq.  X: the rows of all batches.  128 x 128 tile, four waves of 64 x 64; K % 32 == 0.  A
+// step's pieces are loaded two steps before they are multiplied and stored, a step before, into the other of two stages: one
+// barrier a step.  Bound by the stores and reads of the stages, which a tile of this size has two of for each product: 70 us
+// for 2048 x 3072 x 3072 (a launch for each half, loaded one step ahead: 48 us each).
+__global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint16_t* __restrict__ w,
                                                        int M, int N, int K, float* __restrict__ y, int64_t ldy,
                                                        double* __restrict__ sq, int add) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -39,28 +45,34 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restric
   const uint16_t *xr[4], *wr[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    xr[i] = x + (int64_t)min(m0 + ld_row + 32 * i, M - 1) * K + ld_piece * 8;
+    const int m = min(m0 + ld_row + 32 * i, M - 1), batch = m / (int)xs.rows;
+    const uint16_t* x = xs.p[0];
+#pragma unroll
+    for (int b = 1; b < kMaxMomentBatches; ++b) x = batch == b ? xs.p[b] : x;      // an index by lane would go through scratch
+    xr[i] = x + (int64_t)(m - batch * (int)xs.rows) * K + ld_piece * 8;
     wr[i] = w + (int64_t)min(n0 + ld_row + 32 * i, N - 1) * K + ld_piece * 8;
   }
   const int st = ld_row * kRefRowBytes + ld_piece * 16;
   const int frag_row = lane & 31, frag_half = lane >> 5;
-  uint4 ra[4], rw[4];
-  auto load = [&](int k0) {
-    const bool ok = k0 + ld_piece * 8 < K;               // the upper half of a last step of 32 is zero
+  struct Pieces {
+    int4v a[4], w[4];
+  };
+  // a step past the last re-reads the start of the rows and is not multiplied; the upper half of a last step of 32 is zero
+  auto load = [&](int k0, Pieces& p) {
+    const int k = k0 + ld_piece * 8 < K ? k0 : -ld_piece * 8;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      ra[i] = rw[i] = make_uint4(0u, 0u, 0u, 0u);
-      if (ok) {
-        ra[i] = *reinterpret_cast<const uint4*>(xr[i] + k0);
-        rw[i] = *reinterpret_cast<const uint4*>(wr[i] + k0);
-      }
+      p.a[i] = *reinterpret_cast<const int4v*>(xr[i] + k);
+      p.w[i] = *reinterpret_cast<const int4v*>(wr[i] + k);
     }
   };
-  auto put = [&](unsigned char* stage) {
+  auto put = [&](unsigned char* stage, int k0, const Pieces& p) {
+    const bool ok = k0 + ld_piece * 8 < K;
+    const int4v zero = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<uint4*>(stage + st + 32 * i * kRefRowBytes) = ra[i];
-      *reinterpret_cast<uint4*>(stage + kRefTile * kRefRowBytes + st + 32 * i * kRefRowBytes) = rw[i];
+      *reinterpret_cast<int4v*>(stage + st + 32 * i * kRefRowBytes) = ok ? p.a[i] : zero;
+      *reinterpret_cast<int4v*>(stage + kRefTile * kRefRowBytes + st + 32 * i * kRefRowBytes) = ok ? p.w[i] : zero;
     }
   };
 
@@ -72,14 +84,16 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restric
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  load(0);
-  put(lds);
+  Pieces pieces[2];
+  load(0, pieces[0]);
+  load(kRefStep, pieces[1]);
+  put(lds, 0, pieces[0]);
   __syncthreads();
-  int cur = 0;
-  for (int k0 = 0; k0 < K; k0 += kRefStep) {
-    const bool more = k0 + kRefStep < K;                 // uniform
-    if (more) load(k0 + kRefStep);
-    const unsigned char* a_t = lds + cur;
+  // step k0, in stage P; pieces[P ^ 1] holds the next one, pieces[P] is free
+  auto turn = [&](auto Pc, int k0) {
+    constexpr int P = decltype(Pc)::value;
+    load(k0 + 2 * kRefStep, pieces[P]);
+    const unsigned char* a_t = lds + P * kRefStage;
     const unsigned char* w_t = a_t + kRefTile * kRefRowBytes;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
@@ -98,9 +112,13 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const uint16_t* __restric
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i], xf[j], acc[i][j], 0, 0, 0);
     }
-    cur = kRefStage - cur;
-    if (more) put(lds + cur);
+    put(lds + (P ^ 1) * kRefStage, k0 + kRefStep, pieces[P ^ 1]);
     __syncthreads();
+  };
+  // two steps a trip; an odd last one is followed by a step of zeros
+  for (int k0 = 0; k0 < K; k0 += 2 * kRefStep) {
+    turn(IntC<0>{}, k0);
+    turn(IntC<1>{}, k0 + kRefStep);
   }
   // lane holds, per 32 x 32 block, column m = lane % 32 and rows n = 8 (r / 4) + 4 (lane / 32) + r % 4
   double s2 = 0.0;
@@ -145,36 +163,57 @@ __global__ __launch_bounds__(256) void tile_sums_kernel(const double* __restrict
   if (threadIdx.x == 0) sums[is_den ? den_at : (int)blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// moved[j] = number of positions where candidate j differs from the identity
-__global__ __launch_bounds__(256) void moved_kernel(const int32_t* __restrict__ cands, int K,
-                                                    double* __restrict__ moved) {
+// moved[j] = number of positions where candidate j differs from the identity; ts: the two tensor scales
+__global__ __launch_bounds__(1024) void moved_kernel(const int32_t* __restrict__ cands, int K, double* __restrict__ moved,
+                                                     float* __restrict__ ts, float act_ts, float w_ts) {
   const int j = blockIdx.x;
-  int c = 0;
-  for (int i = threadIdx.x; i < K; i += 256) c += cands[(int64_t)j * K + i] != i;
-  __shared__ int red[256];
-  red[threadIdx.x] = c;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  if (j == 0 && threadIdx.x == 0) {
+    ts[0] = act_ts;
+    ts[1] = w_ts;
   }
-  if (threadIdx.x == 0) moved[j] = (double)red[0];
+  __shared__ int red[16];
+  int c = 0;
+  for (int i = threadIdx.x; i < K; i += 1024) c += __popcll(__ballot(cands[(int64_t)j * K + i] != i));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int all = 0;
+    for (int w = 0; w < 16; ++w) all += red[w];
+    moved[j] = (double)all;
+  }
 }
+
+constexpr int kMaxCandOut = PQ_MAX_ALPHAS + 1;
+constexpr int kNumSums = kMaxCandOut + 1 + PQ_MAX_ALPHAS;
+
+// How a call is cut into launches: `stack` batches stand one below the other, `orders` orders are quantized and multiplied
+// together.  As many as give the product three rounds of its largest tile over the 256 units: from there on a launch
+// more costs less than the operands' memory (an order's operands take 4.25 bits an element).
+struct Plan {
+  int stack, orders;
+};
+Plan plan_of(int64_t M, int64_t N, int n_batches) {
+  constexpr int64_t kTiles = 3 * 256;
+  auto tiles = [&](int64_t rows) { return ((rows + 255) / 256) * ((N + 255) / 256); };
+  const int64_t most = n_batches < kMaxMomentBatches ? n_batches : kMaxMomentBatches;
+  const int64_t stack = std::min(most, (kTiles + tiles(M) - 1) / tiles(M));
+  const int64_t all = tiles(stack * M);
+  return Plan{(int)stack, (int)std::min<int64_t>(kMaxCandOut, (kTiles + all - 1) / all)};
+}
+constexpr Plan kOneByOne{1, 1};
 
 struct OutWs {
   double* keys;
   int32_t* cands;
   int32_t* rank;
   float* y_ref;        // [n_batches][M][ldn]
-  uint8_t* x_op;
-  uint8_t* w_op;
+  uint8_t* x_op;       // [orders] operands of stack * M rows
+  uint8_t* w_op;       // [orders]
   float* ts;           // [2] activation and weight tensor scale
-  double* num;         // [kMaxCandOut][tiles of the product, at most out_tiles(M, N)]
+  double* num;         // [kMaxCandOut][tiles of the product, at most out_tiles(stack * M, N)]
   double* den;         // [tiles of the reference product]
   double* sums;        // [kMaxCandOut] numerators, [1] denominator, [PQ_MAX_ALPHAS] moved counts
 };
-constexpr int kMaxCandOut = PQ_MAX_ALPHAS + 1;
-constexpr int kNumSums = kMaxCandOut + 1 + PQ_MAX_ALPHAS;
 
 // tiles of the smallest size any product kernel takes
 size_t out_tiles(int64_t M, int64_t N) { return (size_t)((M + 31) / 32) * ((N + 31) / 32); }
@@ -182,23 +221,24 @@ size_t ref_tiles(int64_t M, int64_t N) {
   return (size_t)((M + kRefTile - 1) / kRefTile) * ((N + kRefTile - 1) / kRefTile);
 }
 
-size_t carve_out(void* base, pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, OutWs* w) {
+size_t carve_out(void* base, const Plan& p, pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches,
+                 OutWs* w) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
     off = align_up(off + bytes, 256);
     return o;
   };
-  const int64_t ldn = (N + 7) / 8 * 8;
+  const int64_t ldn = (N + 7) / 8 * 8, rows = p.stack * M;
   const size_t o_keys = take((size_t)PQ_MAX_ALPHAS * K * 8);
   const size_t o_cands = take((size_t)PQ_MAX_ALPHAS * K * 4);
   const size_t o_rank = take((size_t)PQ_MAX_ALPHAS * K * 4);
   const size_t o_ref = take((size_t)n_batches * M * ldn * 4);
-  const size_t o_xop = take(operand_bytes(fmt, group, M, K));
-  const size_t o_wop = take(operand_bytes(fmt, group, N, K));
+  const size_t o_xop = take(p.orders * operand_bytes(fmt, group, rows, K));
+  const size_t o_wop = take(p.orders * operand_bytes(fmt, group, N, K));
   const size_t o_ts = take(2 * sizeof(float));
-  const size_t o_num = take(kMaxCandOut * out_tiles(M, N) * 8);
-  const size_t o_den = take(ref_tiles(M, N) * 8);
+  const size_t o_num = take(kMaxCandOut * out_tiles(rows, N) * 8);
+  const size_t o_den = take(ref_tiles(rows, N) * 8);
   const size_t o_sums = take((size_t)kNumSums * 8);
   if (w) {
     char* b = (char*)base;
@@ -219,49 +259,81 @@ size_t carve_out(void* base, pq_format fmt, int group, int64_t M, int64_t N, int
 }  // namespace
 
 size_t select_output_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches) {
-  return carve_out(nullptr, fmt, group, M, N, K, n_batches, nullptr);
+  return carve_out(nullptr, plan_of(M, N, n_batches), fmt, group, M, N, K, n_batches, nullptr);
+}
+size_t select_output_least_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches) {
+  return carve_out(nullptr, kOneByOne, fmt, group, M, N, K, n_batches, nullptr);
 }
 
 int run_select_output(pq_format fmt, int group, const double* act_sumsq, const double* w_sumsq, int64_t K,
                       const void* const* x_calib, int n_batches, int64_t M, const void* w, int64_t N,
                       float act_ts, float w_ts, const double* alphas, int n_alpha, double tau,
-                      int32_t* perm_out, pq_select_report* report, void* ws, hipStream_t st) {
+                      int32_t* perm_out, pq_select_report* report, void* ws, size_t ws_bytes, hipStream_t st) {
+  // a workspace that holds one order's operands and one batch only is taken as it is
+  Plan plan = plan_of(M, N, n_batches);
+  if (ws_bytes < carve_out(nullptr, plan, fmt, group, M, N, K, n_batches, nullptr)) plan = kOneByOne;
   OutWs W;
-  carve_out(ws, fmt, group, M, N, K, n_batches, &W);
+  carve_out(ws, plan, fmt, group, M, N, K, n_batches, &W);
   const int64_t ldn = (N + 7) / 8 * 8;
   const int n_cand = n_alpha + 1;              // candidate 0 is the original order
+  const int stack = plan.stack, orders = std::min(plan.orders, n_cand);
+  if (stack * M * 32 > 0x7FFFFFFF || N * 32 > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many rows for the panel layout");
   int rc;
   if ((rc = launch_candidate_orders(act_sumsq, w_sumsq, K, alphas, n_alpha, W.keys, W.rank, W.cands, st))) return rc;
-  hipLaunchKernelGGL(moved_kernel, dim3(n_alpha), dim3(256), 0, st, W.cands, (int)K, W.sums + kMaxCandOut + 1);
+  hipLaunchKernelGGL(moved_kernel, dim3(n_alpha), dim3(1024), 0, st, W.cands, (int)K, W.sums + kMaxCandOut + 1, W.ts, act_ts,
+                     w_ts);
   if ((rc = check_hip(hipGetLastError(), "moved_kernel"))) return rc;
-  if ((rc = launch_fill_float(W.ts, act_ts, st))) return rc;
-  if ((rc = launch_fill_float(W.ts + 1, w_ts, st))) return rc;
 
+  // batches b0 .. b0 + stack - 1 as rows
+  auto rows_from = [&](int b0, int64_t* rows) {
+    const int nb = std::min(stack, n_batches - b0);
+    RowBatches x;
+    for (int b = 0; b < kMaxMomentBatches; ++b) x.p[b] = (const uint16_t*)x_calib[b0 + (b < nb ? b : 0)];
+    x.rows = M;
+    *rows = nb * M;
+    return x;
+  };
   // the unquantized products, once
   static std::atomic<uint64_t> raised{0};
   if ((rc = allow_lds(reinterpret_cast<const void*>(ref_gemm_kernel), 2 * kRefStage, raised,
                       "hipFuncSetAttribute(ref_gemm_kernel)")))
     return rc;
-  const dim3 ref_grid((unsigned)((M + kRefTile - 1) / kRefTile), (unsigned)((N + kRefTile - 1) / kRefTile));
-  for (int b = 0; b < n_batches; ++b) {
-    hipLaunchKernelGGL(ref_gemm_kernel, ref_grid, dim3(256), 2 * kRefStage, st, (const uint16_t*)x_calib[b],
-                       (const uint16_t*)w, (int)M, (int)N, (int)K, W.y_ref + (size_t)b * M * ldn, ldn, W.den, b > 0);
+  for (int b0 = 0; b0 < n_batches; b0 += stack) {
+    int64_t rows;
+    const RowBatches x = rows_from(b0, &rows);
+    const dim3 grid((unsigned)((rows + kRefTile - 1) / kRefTile), (unsigned)((N + kRefTile - 1) / kRefTile));
+    hipLaunchKernelGGL(ref_gemm_kernel, grid, dim3(256), 2 * kRefStage, st, x, (const uint16_t*)w, (int)rows, (int)N, (int)K,
+                       W.y_ref + (size_t)b0 * M * ldn, ldn, W.den, b0 > 0);
   }
   if ((rc = check_hip(hipGetLastError(), "ref_gemm_kernel"))) return rc;
 
-  const size_t num_stride = out_tiles(M, N);
-  for (int c = 0; c < n_cand; ++c) {
-    const int32_t* perm = c == 0 ? nullptr : W.cands + (int64_t)(c - 1) * K;
-    // the tensor scale of the weights does not depend on the order: the caller's value is used
-    if ((rc = launch_quantize_rows_panel(fmt, group, w, N, K, perm, W.ts + 1, W.w_op, st))) return rc;
-    for (int b = 0; b < n_batches; ++b) {
-      if ((rc = launch_quantize_rows_panel(fmt, group, x_calib[b], M, K, perm, W.ts, W.x_op, st))) return rc;
-      const Output out{kOutDiff, W.num + (size_t)c * num_stride, ldn, W.y_ref + (size_t)b * M * ldn, b > 0};
-      if ((rc = run_qgemm_packed_out(fmt, group, W.x_op, W.ts, W.w_op, W.ts + 1, M, N, K, nullptr, out, st))) return rc;
+  const int64_t most_rows = stack * M;
+  // One tile for the whole call, that of a full launch: a last launch of fewer batches or orders adds its sums to
+  // the first slots of the same ones.
+  const int tile = choose_tile(fmt, group, most_rows, N, K, orders);
+  const size_t num_stride = out_tiles(stack * M, N);
+  const size_t w_next = operand_bytes(fmt, group, N, K);
+  const RowBatches w_rows = {{(const uint16_t*)w}, N};
+  for (int c0 = 0; c0 < n_cand; c0 += orders) {
+    const int n = std::min(orders, n_cand - c0);
+    for (int b0 = 0; b0 < n_batches; b0 += stack) {
+      int64_t rows;
+      const RowBatches x = rows_from(b0, &rows);
+      const size_t x_next = operand_bytes(fmt, group, rows, K);
+      // the tensor scale of the weights does not depend on the order: the caller's value is used
+      const PanelJob xj{x, rows, W.x_op, x_next, W.ts}, wj{w_rows, b0 ? 0 : N, W.w_op, w_next, W.ts + 1};
+      if ((rc = launch_quantize_rows_panel(fmt, group, xj, wj, K, W.cands, c0, n, st))) return rc;
+      Output out{kOutDiff, W.num + (size_t)c0 * num_stride, ldn, W.y_ref + (size_t)b0 * M * ldn, b0 > 0};
+      out.a_next = x_next;
+      out.w_next = w_next;
+      out.y_next = (int64_t)num_stride;
+      out.problems = (unsigned)n;
+      const OperandView A = panel_view(fmt, group, W.x_op, rows, K, W.ts), B = panel_view(fmt, group, W.w_op, N, K, W.ts + 1);
+      if ((rc = launch_qgemm_views(fmt, group, A, B, rows, N, K, out, tile, st))) return rc;
     }
   }
   hipLaunchKernelGGL(tile_sums_kernel, dim3((unsigned)(n_cand + 1)), dim3(256), 0, st, W.num, (int64_t)num_stride,
-                     qgemm_tiles(fmt, group, M, N, K), W.den, (int64_t)ref_tiles(M, N), n_cand, kMaxCandOut, W.sums);
+                     qgemm_tiles(tile, most_rows, N), W.den, (int64_t)ref_tiles(most_rows, N), n_cand, kMaxCandOut, W.sums);
   if ((rc = check_hip(hipGetLastError(), "tile_sums_kernel"))) return rc;
 
   double* h = pinned_doubles(kNumSums);

@@ -412,6 +412,57 @@ def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K, tile):
         assert abs(err - num / den) <= 1e-5 * err
 
 
+def _least_output_workspace(fmt, g, M, N, K, nb):
+    """What the selection by output error needs for one order's operands and one batch of rows at a time."""
+    tiles = lambda m, e: ((m + e - 1) // e) * ((N + e - 1) // e)
+    parts = [15 * K * 8, 15 * K * 4, 15 * K * 4, nb * M * ((N + 7) // 8 * 8) * 4, pq.pq_operand_bytes(fmt, g, M, K),
+             pq.pq_operand_bytes(fmt, g, N, K), 8, 16 * tiles(M, 32) * 8, tiles(M, 128) * 8, 32 * 8]
+    return sum((b + 255) // 256 * 256 for b in parts)
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K,nb,n_alpha", [
+    (pq.FMT_INT4, 64, 33, 41, 192, 17, 15),       # two groups of batches, the second of one; sixteen orders at once
+    (pq.FMT_NVFP4, 16, 2300, 4087, 96, 7, 3),     # six batches at once and a seventh alone, an order at a time
+    (pq.FMT_INT3, 32, 1500, 2056, 96, 3, 6),      # five orders at once, then two
+    (pq.FMT_INT3, 64, 257, 1000, 320, 2, 14),
+    (pq.FMT_INT4, 256, 1792, 300, 768, 2, 3),
+    (pq.FMT_INT4, 32, 1, 3, 65536, 2, 2),         # a row that fills the gathering quantizer's LDS
+])
+def test_output_error_in_several_launches(fmt, g, M, N, K, nb, n_alpha):
+    # however the batches and the orders share launches, the sums are those of one order and one batch at a time (both
+    # products accumulate in fp32, in another order: 1e-5 of a sum, as against the fp64 reference)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7 + M + K)
+    scale = torch.exp(torch.randn(K, generator=gen, device=DEV))
+    xs = [(torch.randn((M, K), generator=gen, device=DEV) * scale).to(torch.bfloat16) for _ in range(nb)]
+    w = (0.02 * torch.randn((N, K), generator=gen, device=DEV) * scale.flip(0)).to(torch.bfloat16)
+    sa = sum(x.double().square().sum(0) for x in xs)
+    sw = w.double().square().sum(0)
+    ts = [float(max(float(t.abs().max()) for t in ts_of) / 2688.0) for ts_of in (xs, [w])]
+    alphas = tuple(j / (n_alpha - 1) for j in range(n_alpha))
+    least = _least_output_workspace(fmt, g, M, N, K, nb)
+    full = pq.pq_workspace_bytes(pq.OP_SELECT_PERM_OUTPUT, fmt, g, M, N, K, nb)
+    assert full > least
+    got = []
+    for size in (full, full - 1, least):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device=DEV)
+        perm = torch.empty(K, dtype=torch.int32, device=DEV)
+        got.append((pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, ts[0], ts[1], perm, alphas=alphas, tau=-1e30,
+                                                   workspace=ws), perm))
+    with pytest.raises(pq.PQError):
+        pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, ts[0], ts[1], perm, alphas=alphas,
+                                       workspace=torch.empty(least - 1, dtype=torch.uint8, device=DEV))
+    one = got[2][0]
+    assert got[1][0] == one                              # a byte short of the full size is the least one
+    rep = got[0][0]
+    assert abs(rep.sum_x2 - one.sum_x2) <= 1e-5 * one.sum_x2
+    np.testing.assert_allclose([rep.e_orig] + rep.e_cand, [one.e_orig] + one.e_cand, rtol=1e-5)
+    wide = sum(float((x.double() @ w.double().t()).square().sum()) for x in xs)
+    assert abs(rep.sum_x2 - wide) <= 1e-5 * wide
+    if rep.alpha_index == one.alpha_index:
+        assert torch.equal(got[0][1], got[2][1])
+
+
 def test_select_perm_candidates_and_ties():
     # equal second moments: the sort must keep ascending channel index (stable)
     K, M, N = 256, 32, 32
