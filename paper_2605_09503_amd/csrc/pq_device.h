@@ -54,19 +54,19 @@ __device__ __forceinline__ float e4m3_decode(uint32_t byte) {
   return as_f32(((e + 120u) << 23) | (m << 20));       // 2^(e-7) * (1 + m/8)
 }
 
-// The same rounding without branches, with the rounded value itself: the step of the E4M3 grid at t
-// is max(2^(e-3), 2^-9), e the exponent of t.  Adding M = max(2^(e+20), 2^14) makes that step the last
-// place of the sum, so the adder rounds t onto the grid (nearest, ties to even); sum - M is the grid
-// value, exactly, and the sum's mantissa field counts the steps: m in 8..16 of a normal result (16 is the
-// next binade's first value -- the carry lands in the exponent field), or 0..8 steps of 2^-9 below 2^-6,
-// which is the subnormal byte itself.  byte = m + 8 (e + 6) for normals, with (e + 6) = field(M) - 141.
+// The same on the conversion unit, with the rounded value itself: v_cvt_pk_fp8_f32 rounds to nearest even, subnormals
+// included (compared with e4m3_rne_sat for every t in [0, 448]).  Two values take what one does.
+__device__ __forceinline__ void e4m3_round2(float t0, float t1, uint32_t& bytes, float& v0, float& v1) {
+  bytes = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(fminf(t0, 448.0f), fminf(t1, 448.0f), 0, false);
+  const auto v = __builtin_amdgcn_cvt_pk_f32_fp8((int)bytes, false);
+  v0 = v[0];
+  v1 = v[1];
+}
 __device__ __forceinline__ void e4m3_round(float t, uint32_t& byte, float& value) {
-  t = fminf(t, 448.0f);
-  const uint32_t eb = as_u32(t) & 0x7F800000u;
-  const uint32_t mb = max(eb + (20u << 23), 141u << 23);       // bits of M; 2^14 has the exponent field 141
-  const float sum = t + as_f32(mb);
-  value = sum - as_f32(mb);
-  byte = (as_u32(sum) - mb) + ((mb >> 20) - (141u << 3));
+  uint32_t two;
+  float again;
+  e4m3_round2(t, t, two, value, again);
+  byte = two & 0xFFu;
 }
 
 // ---------------------------------------------------------------- E2M1 (element codes)
@@ -112,10 +112,26 @@ __device__ __forceinline__ float group_max(float v) {
 
 __device__ __forceinline__ float wave_max(float v) { return group_max<64>(v); }
 
+// a double of the lane that a DPP control word selects
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, (uint64_t)dpp_u32<CTRL>((uint32_t)(u >> 32)) << 32 | dpp_u32<CTRL>((uint32_t)u));
+}
+// the sum over the wave, in every lane, in a fixed order: pairs, quads, rows of 8 and 16 lanes by DPP exchanges, then rows
+// and halves of the wave swapped.  No LDS round trip (six of them, as a shuffle tree needs, are some 800 cycles).
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+  v += dpp_f64<0xB1>(v);                                     // quad_perm [1,0,3,2]
+  v += dpp_f64<0x4E>(v);                                     // quad_perm [2,3,0,1]
+  v += dpp_f64<0x141>(v);                                    // row_half_mirror
+  v += dpp_f64<0x140>(v);                                    // row_mirror
+  const auto swapped = [](double x, auto swap) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const auto lo = swap((uint32_t)u), hi = swap((uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) + __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+  };
+  v = swapped(v, [](uint32_t w) { return __builtin_amdgcn_permlane16_swap(w, w, false, false); });
+  return swapped(v, [](uint32_t w) { return __builtin_amdgcn_permlane32_swap(w, w, false, false); });
 }
 
 // ---------------------------------------------------------------- exact divisions, cheaply
@@ -305,11 +321,6 @@ __device__ __forceinline__ Nv4Scale nv4_scale(float amax, float T, float encT) {
     r.inv = normal ? inv : 0.0f;
   }
   return r;
-}
-template <int R>
-__device__ __forceinline__ void nv4_scales(const float (&amax)[R], float T, float encT, Nv4Scale (&out)[R]) {
-#pragma unroll
-  for (int r = 0; r < R; ++r) out[r] = nv4_scale(amax[r], T, encT);
 }
 __device__ __forceinline__ uint32_t nv4_code(float x, float inv) {
   float v = x * inv;

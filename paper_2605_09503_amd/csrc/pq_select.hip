@@ -22,6 +22,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "pq_device.h"
 #include "pq_host.h"
@@ -205,27 +206,73 @@ constexpr int kQeMaxWaves = 16;           // waves of such a workgroup
 constexpr size_t kQeLds = 150 * 1024;     // LDS its resident rows may take
 constexpr int64_t kQeParts(int64_t rows) { return (rows / kQeMinRowsPerBlock + 1) * kQeMaxWaves; }
 
-template <int R>
-struct FloatVec;
-template <>
-struct FloatVec<1> { typedef float type; };
-template <>
-struct FloatVec<2> { typedef float type __attribute__((ext_vector_type(2))); };
-template <>
-struct FloatVec<4> { typedef float type __attribute__((ext_vector_type(4))); };
+// A sum with what its additions lost (Knuth's two-sum): the errors of NVFP4 are differences of sums some hundred times as
+// large, so a rounding of those is some hundred roundings of the error.
+struct Sum2 {
+  double s = 0.0, lost = 0.0;
+  __device__ __forceinline__ void add(double x) {
+    const double t = s + x, v = t - s;
+    lost += (s - (t - v)) + (x - v);
+    s = t;
+  }
+  __device__ __forceinline__ double value() const { return s + lost; }
+};
+
+// How the resident rows lie in LDS, as fp32 or as the bf16 values they are (packed: two instructions more for a pair of
+// gathered values), for the widths that LDS holds them at.  fetch_ahead: staging chunks (8 channels x the rows) a thread has
+// on their way.
+struct QeWide4 { static constexpr int rows = 4, channel_bytes = 16, max_waves = 16, fetch_ahead = 1; };
+struct QeWide2 { static constexpr int rows = 2, channel_bytes = 8, max_waves = 16, fetch_ahead = 2; };
+struct QePacked4 { static constexpr int rows = 4, channel_bytes = 8, max_waves = 12, fetch_ahead = 2; };
+struct QePacked2 { static constexpr int rows = 2, channel_bytes = 4, max_waves = 16, fetch_ahead = 3; };
+enum QeRows : int { kQeWide4, kQeWide2, kQePacked4, kQePacked2 };
 
 // channels of one work item of a lane: a whole NVFP4 group (its scale then needs no lane exchange and is
 // worked out once), eight for the integer formats, whose groups span lanes
 template <int FMT>
 struct QeChunk { static constexpr int value = FMT == kNvfp4 ? 16 : 8; };
 
-// byte offset of channel e's slot in the LDS image of R resident rows: slot e + e / 8 (the spare slot per
-// eight channels spreads the staging writes over the banks), R floats per slot
-__host__ __device__ constexpr int qe_slot_bytes(int r) { return r * 4; }
+// (channel e's slot in the LDS image of the resident rows is slot e + e / 8: the spare slot per eight channels spreads the
+// staging writes over the banks)
+
+// Block scales of R rows' NVFP4 groups for the error: the decoded scale, and a reciprocal of it times T that is the
+// quantizer's wherever the scale is not zero (a group whose scale is zero has error sum v^2 whatever its codes are, but its codes
+// have to be finite).  Returns the largest amax / T, which says whether a scale saturated.
+template <int R>
+__device__ __forceinline__ float nv4_error_scales(const float (&amax)[R], float T, float encT, float (&inv)[R],
+                                                  float (&value)[R]) {
+  float u[R], t[R], largest = 0.0f;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    u[r] = amax[r] * encT;
+    t[r] = div_const(u[r], 6.0f, 1.0f / 6.0f);
+    largest = fmaxf(largest, u[r]);
+  }
+  uint32_t bytes;
+#pragma unroll
+  for (int r = 0; r < R; r += 2) e4m3_round2(t[r], t[r + 1], bytes, value[r], value[r + 1]);
+  if (__builtin_expect(nv4_tensor_scale_is_tame(T), 1)) {        // uniform
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float d = fmaxf(value[r], 0.001953125f) * T;         // 2^-9: the smallest scale
+      const float q = __builtin_amdgcn_rcpf(d);
+      inv[r] = __builtin_fmaf(__builtin_fmaf(-d, q, 1.0f), q, q);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float d = value[r] * T;
+      const bool normal = is_normal32(d);
+      const float exact = recip_exact(d, normal);
+      inv[r] = normal ? exact : 0.0f;
+    }
+  }
+  return largest;
+}
 
 // Workgroup (x, y) evaluates rows [x * rows_per_block, (x + 1) * rows_per_block) of tensor y of
-// the list (equal shapes) for every candidate order.  R rows at a time are staged in LDS as
-// fp32, channel-major with the R rows of a channel adjacent; the rows after them are already on
+// the list (equal shapes) for every candidate order.  R rows at a time are staged in LDS (as ROWS says),
+// channel-major with the R rows of a channel adjacent; the rows after them are already on
 // their way from memory into registers while the resident ones are evaluated.  A candidate order
 // comes as the byte offsets of its channels' slots (offs[cand][position]), so a lane reads the
 // offsets of its chunk and gathers the R rows of each channel with one LDS read, no address
@@ -239,17 +286,26 @@ __host__ __device__ constexpr int qe_slot_bytes(int r) { return r * 4; }
 // reduces them over the wave once per candidate and set of resident rows.  Lane c of every wave
 // ends up with the wave's total for candidate c: part[y][c][x * waves + wave] (candidate-major, so
 // that the sums over the workgroups read contiguous memory).
-template <int FMT, int G, int R>
-__global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorList xs, int rows, int K,
+//
+// Bound by the vector unit: for an element and order NVFP4 needs 16.7 cycles of a SIMD (two multiply-adds 5.7, its half of a
+// conversion to E2M1 4.1 and back 2.1, the multiplication by the reciprocal 2.6, its half of a maximum 2.1), INT4 20.7 (the
+// conversion to fp64 and the fma there 8.9), the rest is a group's scale and the work item's own, 222 instructions in all for 32
+// elements.  8 x 4608 + 3072 rows of 12288, NVFP4, the whole selection 974 -> 880 us: rows asked for after the first
+// item's offsets and not before them, the offsets of a set's first item kept ready, no LDS round trips where a candidate ends,
+// block scales rounded two at a time on the conversion unit, the group's sum one fma chain (243 -> 222 instructions).
+template <int FMT, int G, class ROWS>
+__global__ __launch_bounds__(64 * ROWS::max_waves) void quant_error_kernel(TensorList xs, int rows, int K,
                                                           const int32_t* __restrict__ offs,
                                                           int n_cand, int identity_first, ScaleArg t_arg,
                                                           int rows_per_block, const uint32_t* __restrict__ differs,
                                                           double* __restrict__ part) {
-  typedef typename FloatVec<R>::type vec_t;
+  constexpr int R = ROWS::rows, SLOT = ROWS::channel_bytes;
+  constexpr bool PACKED = SLOT == R * 2;
+  typedef uint32_t vec_t __attribute__((ext_vector_type(SLOT / 4)));
   constexpr int C = QeChunk<FMT>::value;
-  constexpr int PF = 4 / R;                // staging chunks (8 channels x R rows) a thread fetches ahead
-  constexpr bool kOffsetsAhead = R < 4;    // the next item's offsets are loaded during the current item
-  extern __shared__ __attribute__((aligned(16))) float slots[];     // (K + K / 8) * R floats
+  constexpr int PF = ROWS::fetch_ahead;
+  constexpr bool kOffsetsAhead = SLOT < 16;  // the next item's offsets are loaded during the current item
+  extern __shared__ __attribute__((aligned(16))) unsigned char slots[];      // (K + K / 8) * SLOT bytes
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, n_waves = nthr >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -265,49 +321,57 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
   if (differs && lane < n_cand) same_as_lane = first_same_order(differs, lane);
   const float T = t_arg.dev ? *t_arg.dev : t_arg.value;           // uniform
   const float encT = (FMT == kNvfp4) ? nv4_enc_scale(T) : 0.0f;
+  const double half_T = 0.5 * (double)T;
   // The offsets are used as LDS addresses as they are: the staged rows are the kernel's only LDS object and
   // start at address 0 (adding a base would cost one instruction per gathered channel).  Should a
   // toolchain ever place them elsewhere, every partial sum of the launch is made a NaN.
   typedef const __attribute__((address_space(3))) vec_t* lds_vec_ptr;
-  const bool lds_at_zero = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)slots == 0u;
+  const bool lds_at_zero = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)slots == 0u;
 
-  // rows past the end count as zero rows: error 0
-  auto fetch_row = [&](int r, int c) {
-    uint4 p = make_uint4(0u, 0u, 0u, 0u);
-    if (r < row_end) p = *reinterpret_cast<const uint4*>(x + (int64_t)r * K + (int64_t)c * 8);
-    return p;
+  // The rows of the workgroup as a buffer (at most 64 rows of 34128 channels): a read past its end gives zero without a
+  // branch, so rows past the last count as zero rows, with error 0, and one offset is all an access needs.  A lane past the
+  // row's last chunk reads what lies there and leaves it unused.
+  const uint32_t row_bytes = (uint32_t)K * 2u;
+  const auto rows_buf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(x + (int64_t)row0 * K), 0, row_end > row0 ? (int)((uint32_t)(row_end - row0) * row_bytes) : 0, 0x00027000);
+  auto fetch_row = [&](uint32_t row_at, int c) {         // row_at: byte offset of the row
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rows_buf, (int)(row_at + (uint32_t)c * 16u), 0, 0));
   };
   double v_sq = 0.0;                       // NVFP4: this thread's share of the sum of squares of the rows
   auto put = [&](int c, const uint4 (&p)[R]) {
-    float v[R][8];
+    uint32_t w[R][4];
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
-      v[rr][0] = bf16_lo(p[rr].x); v[rr][1] = bf16_hi(p[rr].x); v[rr][2] = bf16_lo(p[rr].y); v[rr][3] = bf16_hi(p[rr].y);
-      v[rr][4] = bf16_lo(p[rr].z); v[rr][5] = bf16_hi(p[rr].z); v[rr][6] = bf16_lo(p[rr].w); v[rr][7] = bf16_hi(p[rr].w);
+      w[rr][0] = p[rr].x; w[rr][1] = p[rr].y; w[rr][2] = p[rr].z; w[rr][3] = p[rr].w;
       if constexpr (FMT == kNvfp4) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v_sq = fma((double)v[rr][j], (double)v[rr][j], v_sq);
+        for (int j = 0; j < 4; ++j) {
+          const double lo = (double)bf16_lo(w[rr][j]), hi = (double)bf16_hi(w[rr][j]);
+          v_sq = fma(lo, lo, v_sq);
+          v_sq = fma(hi, hi, v_sq);
+        }
       }
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       vec_t o;
-      if constexpr (R == 1) o = v[0][j];
-      else {
 #pragma unroll
-        for (int rr = 0; rr < R; ++rr) o[rr] = v[rr][j];
+      for (int i = 0; i < SLOT / 4; ++i) {
+        if constexpr (PACKED) {            // rows 2 i and 2 i + 1
+          o[i] = __builtin_amdgcn_perm(w[2 * i + 1][j / 2], w[2 * i][j / 2], j & 1 ? 0x07060302u : 0x05040100u);
+        } else {
+          o[i] = j & 1 ? w[i][j / 2] & 0xFFFF0000u : w[i][j / 2] << 16;
+        }
       }
-      *reinterpret_cast<vec_t*>(slots + (size_t)(9 * c + j) * R) = o;
+      *reinterpret_cast<vec_t*>(slots + (size_t)(9 * c + j) * SLOT) = o;
     }
   };
   uint4 ahead[PF][R];
-  auto fetch_ahead = [&](int rg) {
+  auto fetch_ahead = [&](uint32_t at) {
 #pragma unroll
-    for (int f = 0; f < PF; ++f) {
-      const int c = tid + f * nthr;
+    for (int f = 0; f < PF; ++f)
 #pragma unroll
-      for (int rr = 0; rr < R; ++rr) ahead[f][rr] = c < chunks8 ? fetch_row(rg + rr, c) : make_uint4(0u, 0u, 0u, 0u);
-    }
+      for (int rr = 0; rr < R; ++rr) ahead[f][rr] = fetch_row(at + (uint32_t)rr * row_bytes, tid + f * nthr);
   };
 
   // the slot offsets of the C channels of work item (cand, blk) of this lane
@@ -315,21 +379,21 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
     const int c_lane = blk * 64 + lane;
     const int c = c_lane < chunks ? c_lane : 0;
     if (!(identity_first && cand == 0)) {
-      const int4* po = reinterpret_cast<const int4*>(offs + (int64_t)(cand - identity_first) * K + c * C);
+      const char* po = reinterpret_cast<const char*>(offs + (int64_t)(cand - identity_first) * K);
 #pragma unroll
       for (int j = 0; j < C; j += 4) {
-        const int4 q = po[j / 4];
+        const int4 q = *reinterpret_cast<const int4*>(po + ((uint32_t)c * (C * 4u) + j * 4u));
         o[j] = q.x; o[j + 1] = q.y; o[j + 2] = q.z; o[j + 3] = q.w;
       }
     } else {
-      const int base = c * (C / 8 * 9) * qe_slot_bytes(R);
+      const int base = c * (C / 8 * 9) * SLOT;
 #pragma unroll
-      for (int j = 0; j < C; ++j) o[j] = base + ((j / 8) * 9 + (j & 7)) * qe_slot_bytes(R);
+      for (int j = 0; j < C; ++j) o[j] = base + ((j / 8) * 9 + (j & 7)) * SLOT;
     }
   };
 
-  double acc = 0.0;
-  fetch_ahead(row0);
+  Sum2 acc;
+  fetch_ahead(0u);
   // the orders to evaluate, four bits each (at most 16 candidates); the work items run over that list
   unsigned long long order_list = 0;
   int n_orders = 0;
@@ -348,7 +412,12 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
   const int it0 = run * n_items / n_waves, it1 = (run + 1) * n_items / n_waves;
   const int ord0 = it0 / wave_chunks, blk0 = it0 - ord0 * wave_chunks;       // uniform over the wave
   auto cand_of = [&](int ord) { return (int)((order_list >> (4 * ord)) & 15u); };
-  for (int rg = row0; rg < row_end; rg += R) {
+  uint32_t rg_at = 0;                      // byte offset of row rg
+  int o_ahead[kOffsetsAhead ? C : 1];
+  if constexpr (kOffsetsAhead) {
+    if (it0 < it1) load_offsets(cand_of(ord0), blk0, o_ahead);
+  }
+  for (int rg = row0; rg < row_end; rg += R, rg_at += R * row_bytes) {
     __syncthreads();                       // the previous rows have been read by every wave
 #pragma unroll
     for (int f = 0; f < PF; ++f) {
@@ -358,23 +427,21 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
     for (int c = tid + PF * nthr; c < chunks8; c += nthr) {     // wider rows than the registers hold ahead
       uint4 p[R];
 #pragma unroll
-      for (int rr = 0; rr < R; ++rr) p[rr] = fetch_row(rg + rr, c);
+      for (int rr = 0; rr < R; ++rr) p[rr] = fetch_row(rg_at + (uint32_t)rr * row_bytes, c);
       put(c, p);
     }
     __syncthreads();
-    // Loads return in issue order, so the order below matters: the offsets of the first item go out
-    // before the rows fetched ahead (they are needed at once), those of every later item while the item
-    // before it is evaluated (at its start when four rows are resident: the registers do not hold both
-    // then, and a second workgroup of the compute unit covers the wait), by which time the rows have
-    // long arrived.
+    // Loads return in issue order and a wave waits for all of them where the loop closes, so the order below matters: the
+    // next set of rows is asked for inside the first item, once the offsets that it needs are there, and has that item's
+    // time to arrive.  (Asked for before the first item they held its offsets up for a whole memory latency in every
+    // set.)  The offsets of every later item are on their way while the item before it is evaluated, or asked for at
+    // its start when four rows are resident: the registers do not hold both then, and a second workgroup of the compute unit
+    // covers the wait.
     int ord = ord0, blk = blk0;
     int cand = cand_of(ord);
-    int o_ahead[kOffsetsAhead ? C : 1];
-    if constexpr (kOffsetsAhead) {
-      if (it0 < it1) load_offsets(cand, blk, o_ahead);
-    }
-    if (rg + R < row_end) fetch_ahead(rg + R);     // in flight during the evaluation below
+    if (it0 == it1) fetch_ahead(rg_at + R * row_bytes);           // no item of its own (uniform)
     double run = 0.0;                      // this lane's error of the current candidate
+#pragma unroll 1                            // a first item of its own (peeled off) would cost registers
     for (int it = it0; it < it1; ++it) {
       // every lane runs the group reduction; a lane past the last chunk (its whole group is, K being a
       // multiple of the group size) works on chunk 0 and its result is dropped
@@ -390,19 +457,19 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
 #pragma unroll
       for (int j = 0; j < C; ++j) {
         const vec_t g = *(lds_vec_ptr)(uintptr_t)(uint32_t)o[j];
-        if constexpr (R == 1) v[0][j] = g;
-        else {
 #pragma unroll
-          for (int rr = 0; rr < R; ++rr) v[rr][j] = g[rr];
-        }
+        for (int rr = 0; rr < R; ++rr) v[rr][j] = !PACKED ? as_f32(g[rr]) : rr & 1 ? bf16_hi(g[rr / 2]) : bf16_lo(g[rr / 2]);
       }
       const bool cand_done = blk + 1 == wave_chunks || it + 1 == it1;     // uniform
       if constexpr (kOffsetsAhead) {
-        if (it + 1 < it1) load_offsets(cand_done ? cand_of(ord + 1) : cand, cand_done ? 0 : blk + 1, o_ahead);
+        const bool last = it + 1 == it1;             // then the first item's again, for the next set of rows
+        load_offsets(last ? cand_of(ord0) : cand_done ? cand_of(ord + 1) : cand, last ? blk0 : cand_done ? 0 : blk + 1, o_ahead);
       }
-      double errs[R];                               // one chain per resident row
-#pragma unroll
-      for (int rr = 0; rr < R; ++rr) errs[rr] = 0.0;
+      if (it == it0) {                                // uniform
+        uint32_t next = rg_at + R * row_bytes;
+        asm("" : "+s"(next));                         // the addresses are worked out here, not kept across the loop
+        fetch_ahead(next);
+      }
       constexpr bool kRows4 = FMT != kNvfp4 && R == 4 && G >= 32;    // scales shared out over a quad
       float amax[R];
 #pragma unroll
@@ -420,12 +487,11 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
         // multiple of 1/2), and |A| <= 16 * 6 * amax < 2^24 U as long as amax <= 48 d -- true unless the block
         // scale saturated far beyond its largest value (a tensor scale much too small for the data: the
         // wave then takes the element-wise fp64 sum instead).  B <= 16 * 36 in steps of 1/4.
-        Nv4Scale s[R];
-        nv4_scales<R>(amax, T, encT, s);
-        bool far_saturated = false;
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) far_saturated = far_saturated || amax[rr] * encT > 6.0f * 448.0f * 7.0f;
-        const bool exact_sums = !__any(far_saturated);          // uniform
+        // With d = b T (b the decoded block scale) the error is 2 T b ((T / 2) (b B) - A): b B is exact in fp32 (4 + 12
+        // bits), (T / 2) (b B) in fp64, and the factor 2 T is applied to the sum of all groups at the end.
+        float inv[R], value[R];
+        const float largest = nv4_error_scales<R>(amax, T, encT, inv, value);
+        const bool exact_sums = !__any(largest > 6.0f * 448.0f * 7.0f);          // uniform
         // eight elements on the conversion unit (a byte of `codes` per pair), decoded again
         auto quantize8 = [&](const float* x, float inv, float (&q)[8]) {
           uint32_t codes = 0u;
@@ -447,40 +513,43 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
 #pragma unroll
             for (int j = 0; j < C; j += 8) {
               float q[8];
-              quantize8(&v[rr][j], s[rr].inv, q);
+              quantize8(&v[rr][j], inv[rr], q);
 #pragma unroll
               for (int u = 0; u < 8; ++u) {
                 A = __builtin_fmaf(v[rr][j + u], q[u], A);
                 B = __builtin_fmaf(q[u], q[u], B);
               }
             }
-            // - 2 d A + d^2 B = d (d B - 2 A): d (4 + 24 bits) is exact, so are d B (+ 10 bits) and the
-            // difference; one rounding in the last product
-            const double d = (double)s[rr].value * (double)T;
-            errs[rr] = d * fma(d, (double)B, -2.0 * (double)A);
+            const float b = live ? value[rr] : 0.0f;
+            run = fma((double)b, fma(half_T, (double)(b * B), -(double)A), run);
           }
         } else {
+          double far = 0.0;
 #pragma unroll
           for (int rr = 0; rr < R; ++rr) {
-            const double d = (double)s[rr].value * (double)T;
+            const double d = (double)value[rr] * (double)T;
 #pragma unroll
             for (int j = 0; j < C; j += 8) {
               float q[8];
-              quantize8(&v[rr][j], s[rr].inv, q);
+              quantize8(&v[rr][j], inv[rr], q);
 #pragma unroll
               for (int u = 0; u < 8; ++u) {
                 const double x = (double)v[rr][j + u];
                 const double e = fma(-(double)q[u], d, x);      // product exact: 2 + 28 bits
-                errs[rr] = fma(e, e, errs[rr]);
-                errs[rr] = fma(-x, x, errs[rr]);                // the part counted by v_sq
+                far = fma(e, e, far);
+                far = fma(-x, x, far);                          // the part counted by v_sq
               }
             }
           }
+          run += live ? far / (2.0 * (double)T) : 0.0;          // the factor of the other sums (T > 0: something saturated)
         }
       } else {
         IntScale s[R];
         if constexpr (kRows4) int_scales_rows4<FMT, G / C>(amax, lane, s);
         else int_scales<FMT, R>(amax, s);
+        double errs[R];                             // one chain per resident row
+#pragma unroll
+        for (int rr = 0; rr < R; ++rr) errs[rr] = 0.0;
 #pragma unroll
         for (int rr = 0; rr < R; ++rr) {
 #pragma unroll
@@ -497,15 +566,15 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
             errs[rr] = fma(e, e, errs[rr]);
           }
         }
-      }
-      double err = errs[0];
+        double err = errs[0];
 #pragma unroll
-      for (int rr = 1; rr < R; ++rr) err += errs[rr];
-      run += live ? err : 0.0;
+        for (int rr = 1; rr < R; ++rr) err += errs[rr];
+        run += live ? err : 0.0;
+      }
       ++blk;
       if (cand_done) {                               // the candidate's last item of this wave
-        const double total = wave_sum(run);          // fixed xor-tree order
-        if (lane == cand) acc += total;
+        const double total = wave_sum(run);          // fixed order
+        acc.add(lane == cand ? total : 0.0);
         run = 0.0;
         blk = 0;
         ++ord;
@@ -513,14 +582,14 @@ __global__ __launch_bounds__(64 * kQeMaxWaves) void quant_error_kernel(TensorLis
       }
     }
   }
+  double err = acc.value();
   if constexpr (FMT == kNvfp4) {
     // every candidate's error contains the rows' sum of squares: the wave's share goes to each
-    const double share = wave_sum(v_sq);
-    if (lane < n_cand) acc += share;
+    err = fma(2.0 * (double)T, acc.s, wave_sum(v_sq)) + 2.0 * (double)T * acc.lost;
   }
-  if (!lds_at_zero) acc = __builtin_nan("");
+  if (!lds_at_zero) err = __builtin_nan("");
   if (lane < n_cand)
-    part[((int64_t)blockIdx.y * n_cand + lane) * ((int64_t)gridDim.x * n_waves) + (int64_t)blockIdx.x * n_waves + wave] = acc;
+    part[((int64_t)blockIdx.y * n_cand + lane) * ((int64_t)gridDim.x * n_waves) + (int64_t)blockIdx.x * n_waves + wave] = err;
 }
 
 // offs[i] = byte offset of channel perm[i]'s slot for R resident rows (the error evaluation of one given order)
@@ -588,17 +657,29 @@ __device__ __forceinline__ double strided_sum(const double* __restrict__ p, int6
 }
 
 __global__ __launch_bounds__(256) void select_tail_kernel(TailArgs a, double* __restrict__ out) {
-  __shared__ double red[256];
+  __shared__ double red[256], red_lost[256];
   const int n_x = a.n_cand * a.n_batches;
   int b = blockIdx.x;
-  double s = 0.0;
+  double s = 0.0, lost = 0.0;
   int64_t dst;
   if (b < n_x + a.n_cand) {
     const bool is_w = b >= n_x;
     const int seg = is_w ? 0 : b / a.n_cand, c = is_w ? b - n_x : b % a.n_cand;
     const int64_t n = is_w ? a.w_parts : a.x_parts;
     const double* base = is_w ? a.w_part : a.x_part + (int64_t)seg * n * a.n_cand;
-    s = strided_sum(base + (int64_t)first_same_order(a.differs, c) * n, threadIdx.x, n, 256);
+    const double* p = base + (int64_t)first_same_order(a.differs, c) * n;
+    Sum2 sum;
+    int64_t i = threadIdx.x;
+    for (; i + 7 * 256 < n; i += 8 * 256) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[i + u * 256];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) sum.add(v[u]);
+    }
+    for (; i < n; i += 256) sum.add(p[i]);
+    s = sum.s;
+    lost = sum.lost;
     dst = (int64_t)(is_w ? a.n_batches : seg) * kMaxCand + c;
   } else if (b < n_x + a.n_cand + 2) {
     const int which = b - n_x - a.n_cand;
@@ -621,18 +702,27 @@ __global__ __launch_bounds__(256) void select_tail_kernel(TailArgs a, double* __
     s = (double)n;                                    // small integers: every sum below is exact
     dst = (int64_t)(a.n_batches + 1) * kMaxCand + 2 + j;
   }
+  Sum2 sum{s, lost};
   red[threadIdx.x] = s;
+  red_lost[threadIdx.x] = lost;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+    if (threadIdx.x < st) {
+      sum.add(red[threadIdx.x + st]);
+      sum.lost += red_lost[threadIdx.x + st];
+      red[threadIdx.x] = sum.s;
+      red_lost[threadIdx.x] = sum.lost;
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[dst] = red[0];
+  if (threadIdx.x == 0) out[dst] = sum.value();
 }
 
 // Launch shape of the error evaluation of n_cand orders for `rows` rows per tensor of width K.
 struct QeShape {
-  int r;                 // rows resident in LDS together (1, 2 or 4)
+  QeRows kind;
+  int r;                 // rows resident in LDS together (2 or 4)
+  int slot;              // bytes of a channel there
   int threads;
   int rows_per_block;
   int blocks;            // per tensor
@@ -644,25 +734,29 @@ static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n
   QeShape q;
   const bool nv = fmt == PQ_FMT_NVFP4;
   const int chunk = nv ? QeChunk<kNvfp4>::value : QeChunk<kInt4>::value;
-  const size_t slot_floats = (size_t)(K + K / 8);
-  // Resident rows: as many as LDS holds, four at most -- one gather and one load of offsets then serve four
-  // elements.  That pays where four rows leave room for one workgroup a unit only (K above 4551), too: a whole selection
-  // with four rows takes 0.86 to 0.99 of its time with two, over K = 4096 to 8448, every format and group, and 4608 + 3072
-  // or 512 + 512 + 1024 rows (INT4 g64, K = 7680: 188 -> 173 and 135 -> 116 us; NVFP4 194 -> 185 and 135 -> 124).
-  q.r = slot_floats * 16 <= kQeLds ? 4 : slot_floats * 8 <= kQeLds ? 2 : 1;
-  q.shmem = slot_floats * q.r * sizeof(float);
+  const size_t slots = (size_t)(K + K / 8);
+  // Resident rows: four where LDS holds them, one gather and one load of offsets then serve four elements.  As fp32 up to K =
+  // 8533, also where that leaves room for one workgroup a unit only (K above 4551): against two rows a whole selection takes
+  // 0.86 to 0.99 of the time over K = 4096 to 8448.  Wider rows up to K = 17066: the integer formats as bf16 (against two
+  // rows of fp32: INT4 g64 1024 + 1024 + 1024 rows of 12288 160 -> 151 us, g32 2 x 1500 + 2000 of 16384 228 -> 216), which share
+  // a group's scale arithmetic over four rows; NVFP4, which does not, two rows of fp32 (2 x 1500 + 2000 of 16384 210
+  // against 218, 3 x 4608 + 3072 of 10240 357 against 366, 8 x 4608 + 3072 of 12288 883 against 874).  Wider still two rows of
+  // bf16 instead of one of fp32: INT4 g256 512 + 512 of 20480 290 -> 256, NVFP4 1500 + 2000 of 32768 380 -> 364.
+  q.kind = slots * QeWide4::channel_bytes <= kQeLds   ? kQeWide4
+           : slots * QeWide2::channel_bytes <= kQeLds ? (nv ? kQeWide2 : kQePacked4)
+                                                      : kQePacked2;
+  q.r = q.kind == kQeWide4 || q.kind == kQePacked4 ? 4 : 2;
+  q.slot = q.kind == kQeWide4 ? QeWide4::channel_bytes : q.kind == kQePacked2 ? QePacked2::channel_bytes : QeWide2::channel_bytes;
+  q.shmem = slots * q.slot;
   // Waves, a multiple of four: the waves of a workgroup are dealt to the four SIMDs in turn, both workgroups of a
   // unit from the same SIMD on, and the busiest SIMD sets the pace (INT4, K = 3072: 315 us with nine waves, 254 with
   // eight, 246 with twelve; NVFP4, K = 12288, two batches: 403 with fourteen, 389 with sixteen).  Two workgroups share
   // a unit where their rows fit its LDS twice (one stages while the other computes): half of the waves that the
   // registers allow each (the NVFP4 instances need up to 128 a lane: sixteen waves a unit; the integer ones up to 80:
-  // twenty-four), sixteen otherwise.  The integer instance of groups of 256 with two rows needs 84, which leaves twenty
-  // waves: one workgroup of sixteen (INT4, K = 8960, 4096 + 2048 rows 182 us, 512 + 512 + 512 rows 134; two of eight 184
-  // and 150, one of twelve 192 and 139; held to 80 registers it spills: 181 and 148).  No more waves than there are
-  // work items (candidate x block of 64 chunks), rounded up to four.
+  // twenty-four), sixteen otherwise.  No more waves than there are work items (candidate x block of 64 chunks), rounded up to four.
   const int items = n_cand * (int)((K / chunk + 63) / 64);
-  const bool two = 2 * q.shmem <= 160 * 1024 && !(!nv && group == 256 && q.r == 2);
-  const int max_waves = two ? (nv ? 8 : 12) : kQeMaxWaves;
+  const bool two = 2 * q.shmem <= 160 * 1024 && q.kind != kQePacked4;
+  const int max_waves = q.kind == kQePacked4 ? QePacked4::max_waves : two ? (nv ? 8 : 12) : kQeMaxWaves;
   q.threads = 64 * (items < max_waves ? (items + 3) / 4 * 4 : max_waves);
   // Rows per workgroup: the workgroups run in rounds of as many as the chip holds at once (256 compute
   // units, one or two each), every round lasts about as long as a workgroup's rows plus a fixed start-up
@@ -683,11 +777,11 @@ static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n
   return q;
 }
 
-template <int FMT, int G, int R>
+template <int FMT, int G, class ROWS>
 static int launch_qe_r(const TensorList& xs, int n_tensors, int64_t rows, int K, const QeShape& q,
                        const int32_t* offs, int n_cand, int identity_first, ScaleArg T, const uint32_t* same_as,
                        double* part, hipStream_t st) {
-  auto kern = quant_error_kernel<FMT, G, R>;
+  auto kern = quant_error_kernel<FMT, G, ROWS>;
   static std::atomic<uint64_t> raised{0};              // to the most any launch of the instance may ask for
   if (q.shmem > 48 * 1024) {
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kQeLds, raised, "hipFuncSetAttribute(quant_error_kernel)"))
@@ -702,14 +796,14 @@ template <int FMT, int G>
 static int launch_qe(const TensorList& xs, int n_tensors, int64_t rows, int K, const QeShape& q,
                      const int32_t* offs, int n_cand, int identity_first, ScaleArg T, const uint32_t* same_as,
                      double* part, hipStream_t st) {
-  switch (q.r) {
-    case 4: return launch_qe_r<FMT, G, 4>(xs, n_tensors, rows, K, q, offs, n_cand, identity_first, T, same_as, part, st);
-    case 2: return launch_qe_r<FMT, G, 2>(xs, n_tensors, rows, K, q, offs, n_cand, identity_first, T, same_as, part, st);
-    default: return launch_qe_r<FMT, G, 1>(xs, n_tensors, rows, K, q, offs, n_cand, identity_first, T, same_as, part, st);
-  }
+#define PQ_ARGS (xs, n_tensors, rows, K, q, offs, n_cand, identity_first, T, same_as, part, st)
+  if (q.kind == kQeWide4) return launch_qe_r<FMT, G, QeWide4> PQ_ARGS;
+  if (q.kind == kQePacked2) return launch_qe_r<FMT, G, QePacked2> PQ_ARGS;
+  return launch_qe_r<FMT, G, std::conditional_t<FMT == kNvfp4, QeWide2, QePacked4>> PQ_ARGS;
+#undef PQ_ARGS
 }
 
-// part: [n_tensors][n_cand][q.parts()]; offs: the candidate orders as slot offsets for q.r resident rows
+// part: [n_tensors][n_cand][q.parts()]; offs: the candidate orders as offsets of slots of q.slot bytes
 static int launch_quant_error(pq_format fmt, int group, const TensorList& x, int n_tensors, int64_t rows,
                               int K, const QeShape& q, const int32_t* offs, int n_cand,
                               int identity_first, ScaleArg T, const uint32_t* same_as, double* part,
@@ -793,7 +887,7 @@ int run_quant_error(pq_format fmt, int group, const void* x, int64_t rows, int64
   if (perm) {
     offs = (int32_t*)((char*)ws + align_up((size_t)kQeParts(rows) * 8, 256));
     hipLaunchKernelGGL(perm_to_offsets_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, perm, (int)K,
-                       qe_slot_bytes(q.r), offs);
+                       q.slot, offs);
   }
   int rc = launch_quant_error(fmt, group, tl, 1, rows, (int)K, q, offs, 1, perm ? 0 : 1, ScaleArg{ts, nullptr},
                               nullptr, part, st);
@@ -915,7 +1009,7 @@ int run_select(pq_format fmt, int group, const double* act_sumsq, const double* 
   const QeShape qa = qe_shape(fmt, group, M, K, n_batches < kMaxMomentBatches ? n_batches : kMaxMomentBatches, n_cand);
   const QeShape qw = qe_shape(fmt, group, N, K, 1, n_cand);       // the same resident rows (a function of K): one set of offsets
   if ((rc = launch_candidate_orders(act_sumsq, w_sumsq, K, alphas, n_alpha, W.keys, W.rank, W.cands, st, W.offs,
-                                    qe_slot_bytes(qa.r), W.same_as)))
+                                    qa.slot, W.same_as)))
     return rc;
   double* sums = W.sums;
   for (int b0 = 0; b0 < n_batches; b0 += kMaxMomentBatches) {

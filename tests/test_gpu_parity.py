@@ -498,15 +498,15 @@ def test_quant_error(fmt, g):
         np.testing.assert_allclose(out.item(), ref, rtol=T.ERRSUM_RTOL)
 
 
-# Shapes that walk the launch variants of the error evaluation: one, two or four rows resident in
-# LDS (by K), workgroup sizes that do and do not divide K / 8, row counts with ragged tails.
+# Shapes that walk the launch variants of the error evaluation: two or four rows resident in
+# LDS (by K and format), workgroup sizes that do and do not divide K / 8, row counts with ragged tails.
 @pytest.mark.parametrize("fmt,g,rows,K", [
     (pq.FMT_NVFP4, 16, 5, 272),       # 34 chunks of 8: a single wave with idle lanes
     (pq.FMT_INT4, 32, 13, 4096),      # four rows resident, two workgroups per compute unit
     (pq.FMT_INT4, 64, 9, 8192),       # four rows resident, one workgroup per compute unit
     (pq.FMT_NVFP4, 16, 9, 8192),
-    (pq.FMT_INT4, 64, 5, 16384),      # two rows resident
-    (pq.FMT_INT4, 64, 3, 20480),      # one row resident
+    (pq.FMT_INT4, 64, 5, 16384),      # four rows resident, as bf16
+    (pq.FMT_INT4, 64, 3, 20480),      # two rows resident, as bf16
     (pq.FMT_NVFP4, 16, 3, 20480),
     (pq.FMT_INT3, 32, 70, 3072),      # four rows resident, six work items for eight waves, 70 = 4 * 17 + 2 rows
     (pq.FMT_NVFP4, 16, 3, 12288),     # widest configuration, fewer rows than a workgroup covers
@@ -519,6 +519,31 @@ def test_quant_error_launch_variants(fmt, g, rows, K):
     x = _to_dev(bits)
     x64 = OF.bf16_bits_to_f64(bits)
     ts = float(OQ.nvfp4_tensor_scale(OC.absmax(x64))) if fmt == pq.FMT_NVFP4 else 1.0
+    perm = rng.permutation(K).astype(np.int32)
+    out = torch.zeros(1, dtype=torch.float64, device=DEV)
+    for p in (None, perm):
+        pq.pq_quant_error(fmt, g, x, None if p is None else torch.from_numpy(p).to(DEV), ts, out)
+        torch.cuda.synchronize()
+        ref = OC.squared_error(fmt, g, x64, p, np.float32(ts) if fmt == pq.FMT_NVFP4 else None)
+        np.testing.assert_allclose(out.item(), ref, rtol=T.ERRSUM_RTOL)
+
+
+# The widths between which the resident rows lie otherwise in LDS (fp32 up to 8533, two rows of fp32 or four of bf16 up to
+# 17066, two of bf16 up to 34128), rows past a set of them, and more chunks than a workgroup fetches ahead.  shrink: a tensor
+# scale that much too small, 1e3 the element-wise sums of a wave whose scales saturated.
+@pytest.mark.parametrize("fmt,g,rows,K,shrink", [
+    (pq.FMT_NVFP4, 16, 5, 8528, 1.0), (pq.FMT_NVFP4, 16, 5, 8544, 1.0), (pq.FMT_NVFP4, 16, 11, 8544, 1e3),
+    (pq.FMT_NVFP4, 16, 3, 17056, 1.0), (pq.FMT_NVFP4, 16, 3, 17072, 1.0), (pq.FMT_NVFP4, 16, 19, 17072, 1e3),
+    (pq.FMT_NVFP4, 16, 1, 34128, 1.0), (pq.FMT_INT4, 32, 5, 8512, 1.0), (pq.FMT_INT4, 32, 9, 8544, 1.0),
+    (pq.FMT_INT3, 64, 17, 8576, 1.0), (pq.FMT_INT4, 128, 6, 12416, 1.0), (pq.FMT_INT3, 256, 3, 16896, 1.0),
+    (pq.FMT_INT3, 32, 2, 17056, 1.0), (pq.FMT_INT4, 32, 3, 17088, 1.0), (pq.FMT_INT4, 256, 5, 33792, 1.0),
+])
+def test_quant_error_where_rows_lie_otherwise(fmt, g, rows, K, shrink):
+    rng = np.random.default_rng(77 + K + rows)
+    bits = _rand_bits(rng, rows, K)
+    x = _to_dev(bits)
+    x64 = OF.bf16_bits_to_f64(bits)
+    ts = float(np.float32(float(OQ.nvfp4_tensor_scale(OC.absmax(x64))) / shrink)) if fmt == pq.FMT_NVFP4 else 1.0
     perm = rng.permutation(K).astype(np.int32)
     out = torch.zeros(1, dtype=torch.float64, device=DEV)
     for p in (None, perm):
