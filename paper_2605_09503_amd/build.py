@@ -1,4 +1,5 @@
-"""Builds the C-ABI library (csrc/*.hip -> lib/libpermuquant.so) for gfx950 with hipcc.
+"""Builds the C-ABI library (csrc/*.hip -> lib/libpermuquant.so) for gfx950 with hipcc, and the binding of its hot calls
+(csrc/pq_calls.cpp -> lib/_pq_calls.so).
 
 Cross-compiles without a GPU.  Usage: `python -m paper_2605_09503_amd.build`.
 """
@@ -8,6 +9,7 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -23,6 +25,10 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
 ]
+
+
+# the Python binding of the hot calls (csrc/pq_calls.cpp): host code against this interpreter and its torch
+CALLS = os.path.join(LIBDIR, "_pq_calls.so")
 
 
 def sources():
@@ -42,6 +48,20 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_calls() -> None:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+           os.path.join(CSRC, "pq_calls.cpp"), "-o", CALLS, "-Wall", "-L", LIBDIR, "-lpermuquant", "-Wl,-rpath,$ORIGIN",
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building the binding failed:\n%s\n%s" % (r.stdout, r.stderr))
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(LIBDIR, exist_ok=True)
     os.makedirs(OBJDIR, exist_ok=True)
@@ -52,6 +72,7 @@ def build(verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
+    _build_calls()
     if verbose:
         print("built", LIB)
     return LIB

@@ -8,6 +8,8 @@ Functions carry the names of the C entry points.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
@@ -124,7 +126,7 @@ def load():
 
 def _check(rc: int):
     if rc != 0:
-        raise PQError(rc, load().pq_last_error().decode())
+        _raise(rc)
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -140,6 +142,50 @@ def _stream():
     if _raw_stream is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(torch.cuda.current_device())
+
+
+# ------------------------------------------------------------------------ the calls of a forward pass
+# pq_quantize_act, pq_quantize_act_packed, pq_norm_quantize_act_packed, pq_hadamard_quantize_act_packed, pq_qgemm,
+# pq_qgemm_packed, pq_qgemm_packed_f32, pq_qgemm_packed_bias and pq_calib_moments are marshalled by the module
+# _pq_calls (csrc/pq_calls.cpp, where their signatures are): a wrapper here and ctypes cost 2 us of the 5 a call took.
+_CALLS = ("pq_quantize_act", "pq_quantize_act_packed", "pq_norm_quantize_act_packed", "pq_hadamard_quantize_act_packed",
+          "pq_qgemm", "pq_qgemm_packed", "pq_qgemm_packed_f32", "pq_qgemm_packed_bias", "pq_calib_moments")
+_CALLS_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_pq_calls.so")
+
+
+def _raise(rc: int):
+    raise PQError(rc, load().pq_last_error().decode())
+
+
+def _new_operand(fmt: int, group: int, rows: int, K: int, like: torch.Tensor) -> torch.Tensor:
+    return torch.empty(max(pq_operand_bytes(fmt, group, rows, K), 16), dtype=torch.uint8, device=like.device)
+
+
+def _new_workspace(op: int, fmt: int, group: int, M: int, N: int, K: int, n_batches: int, like: torch.Tensor):
+    return _workspace(pq_workspace_bytes(op, fmt, group, M, N, K, n_batches), like.device)
+
+
+def _bind_calls():
+    load()
+    if not os.path.exists(_CALLS_PATH):
+        raise PQError(-100, "binding not built: %s (run python -m paper_2605_09503_amd.build)" % _CALLS_PATH)
+    loader = importlib.machinery.ExtensionFileLoader("_pq_calls", _CALLS_PATH)
+    calls = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pq_calls", loader))
+    loader.exec_module(calls)
+    calls.bind(_raise, _new_operand, _new_workspace)
+    globals().update((name, getattr(calls, name)) for name in _CALLS)
+
+
+def _unbound(name: str):
+    def call(*args, **kwargs):
+        _bind_calls()
+        return globals()[name](*args, **kwargs)
+    call.__name__ = call.__qualname__ = name
+    return call
+
+
+# Bound when this module is imported; where nothing is built yet, at the first call (which raises if still nothing is).
+globals().update((name, _unbound(name)) for name in _CALLS)
 
 
 def pq_last_error() -> str:
@@ -158,19 +204,6 @@ def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:
     if nbytes == 0:
         return None
     return torch.empty(nbytes, dtype=torch.uint8, device=device)
-
-
-def pq_calib_moments(x: torch.Tensor, sumsq: torch.Tensor, absmax: Optional[torch.Tensor] = None,
-                     workspace: Optional[torch.Tensor] = None, rows: Optional[int] = None,
-                     K: Optional[int] = None, ld: Optional[int] = None) -> None:
-    """sumsq[K] (float64, in/out) += column sums of squares of bf16 x[rows, ld]."""
-    rows = x.shape[0] if rows is None else rows
-    K = x.shape[1] if K is None else K
-    ld = x.stride(0) if ld is None else ld
-    if workspace is None:
-        workspace = _workspace(pq_workspace_bytes(OP_CALIB_MOMENTS, 0, 0, rows, 0, K, 1), x.device)
-    _check(load().pq_calib_moments(_ptr(x), rows, K, ld, _ptr(sumsq), _ptr(absmax), _ptr(workspace),
-                                   0 if workspace is None else workspace.numel(), _stream()))
 
 
 STATIC_SCRATCH_BYTES = 3 << 20      # PQ_STATIC_SCRATCH_BYTES of the header
@@ -286,16 +319,6 @@ def pq_quantize_weights(fmt: int, group: int, w: torch.Tensor, perm: Optional[to
                                       _ptr(tensor_scale_out), _stream()))
 
 
-def pq_quantize_act(fmt: int, group: int, x: torch.Tensor, perm: Optional[torch.Tensor],
-                    tensor_scale: Optional[torch.Tensor], codes: torch.Tensor, scales: torch.Tensor,
-                    M: Optional[int] = None, K: Optional[int] = None, ld: Optional[int] = None) -> None:
-    M = x.shape[0] if M is None else M
-    K = x.shape[1] if K is None else K
-    ld = x.stride(0) if ld is None else ld
-    _check(load().pq_quantize_act(fmt, group, _ptr(x), M, K, ld, _ptr(perm), _ptr(tensor_scale),
-                                  _ptr(codes), _ptr(scales), _stream()))
-
-
 def _gemm(fn, fmt, group, a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, y, workspace, M, N, K, ldy):
     M = a_codes.shape[0] if M is None else M
     K = a_codes.shape[1] * 2 if K is None else K
@@ -306,14 +329,6 @@ def _gemm(fn, fmt, group, a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, y, w
     _check(fn(fmt, group, _ptr(a_codes), _ptr(a_scales), _ptr(a_ts), _ptr(w_codes), _ptr(w_scales),
               _ptr(w_ts), M, N, K, _ptr(y), ldy, _ptr(workspace),
               0 if workspace is None else workspace.numel(), _stream()))
-
-
-def pq_qgemm(fmt: int, group: int, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
-             w_tensor_scale, y: torch.Tensor, workspace: Optional[torch.Tensor] = None,
-             M=None, N=None, K=None, ldy=None) -> None:
-    """y[M, N] (bf16) = dequant(A) @ dequant(W)^T."""
-    _gemm(load().pq_qgemm, fmt, group, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
-          w_tensor_scale, y, workspace, M, N, K, ldy)
 
 
 def pq_qgemm_prep(fmt: int, group: int, a_scales, w_scales, M: int, N: int, K: int,
@@ -395,19 +410,6 @@ def pq_pack_operand_int3(group: int, dense: torch.Tensor, scales: torch.Tensor, 
     return operand
 
 
-def pq_quantize_act_packed(fmt: int, group: int, x: torch.Tensor, tensor_scale: Optional[torch.Tensor],
-                           operand: Optional[torch.Tensor] = None, codes: Optional[torch.Tensor] = None,
-                           scales: Optional[torch.Tensor] = None, K: Optional[int] = None) -> torch.Tensor:
-    """Dynamic activation quantization straight into the GEMM's panel layout."""
-    M = x.shape[0]
-    K = x.shape[1] if K is None else K
-    if operand is None:
-        operand = torch.empty(max(pq_operand_bytes(fmt, group, M, K), 16), dtype=torch.uint8, device=x.device)
-    _check(load().pq_quantize_act_packed(fmt, group, _ptr(x), M, K, x.stride(0), _ptr(tensor_scale),
-                                         _ptr(operand), operand.numel(), _ptr(codes), _ptr(scales), _stream()))
-    return operand
-
-
 def pq_calib_channel_stats(x: torch.Tensor, total: Optional[torch.Tensor], absmax: Optional[torch.Tensor],
                            K: Optional[int] = None, workspace: Optional[torch.Tensor] = None) -> None:
     """Per channel: sum (fp64, accumulated into `total`) and largest magnitude (fp32, max into `absmax`)."""
@@ -479,24 +481,6 @@ def pq_norm_reorder(kind: int, x: torch.Tensor, eps: float, perm: Optional[torch
     return y
 
 
-def pq_norm_quantize_act_packed(kind: int, fmt: int, group: int, x: torch.Tensor, eps: float,
-                                tensor_scale: Optional[torch.Tensor], perm: Optional[torch.Tensor] = None,
-                                gamma: Optional[torch.Tensor] = None, mod_scale: Optional[torch.Tensor] = None,
-                                mod_shift: Optional[torch.Tensor] = None, rows_per_mod: int = 0,
-                                operand: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None,
-                                K: Optional[int] = None) -> torch.Tensor:
-    """The same layer feeding the activation quantizer directly: returns the GEMM operand."""
-    M = x.shape[0]
-    K = x.shape[1] if K is None else K
-    if operand is None:
-        operand = torch.empty(max(pq_operand_bytes(fmt, group, M, K), 16), dtype=torch.uint8, device=x.device)
-    p = _norm_params(kind, perm, gamma, mod_scale, mod_shift, rows_per_mod, eps)
-    _check(load().pq_norm_quantize_act_packed(C.byref(p), fmt, group, _ptr(x), M, K, x.stride(0),
-                                              _ptr(tensor_scale), _ptr(operand), operand.numel(), _ptr(y),
-                                              0 if y is None else y.stride(0), _stream()))
-    return operand
-
-
 def pq_hadamard_reorder(x: torch.Tensor, perm: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None,
                         K: Optional[int] = None) -> torch.Tensor:
     """x H with the columns of the result in the order `perm` (bf16 [M, K])."""
@@ -506,45 +490,6 @@ def pq_hadamard_reorder(x: torch.Tensor, perm: Optional[torch.Tensor] = None, y:
         y = torch.empty((M, K), dtype=torch.bfloat16, device=x.device)
     _check(load().pq_hadamard_reorder(_ptr(perm), _ptr(x), M, K, x.stride(0), _ptr(y), y.stride(0), _stream()))
     return y
-
-
-def pq_hadamard_quantize_act_packed(fmt: int, group: int, x: torch.Tensor, tensor_scale: Optional[torch.Tensor],
-                                    perm: Optional[torch.Tensor] = None, operand: Optional[torch.Tensor] = None,
-                                    y: Optional[torch.Tensor] = None, K: Optional[int] = None) -> torch.Tensor:
-    """The rotation feeding the activation quantizer directly: returns the GEMM operand."""
-    M = x.shape[0]
-    K = x.shape[1] if K is None else K
-    if operand is None:
-        operand = torch.empty(max(pq_operand_bytes(fmt, group, M, K), 16), dtype=torch.uint8, device=x.device)
-    _check(load().pq_hadamard_quantize_act_packed(_ptr(perm), fmt, group, _ptr(x), M, K, x.stride(0),
-                                                  _ptr(tensor_scale), _ptr(operand), operand.numel(), _ptr(y),
-                                                  0 if y is None else y.stride(0), _stream()))
-    return operand
-
-
-def _gemm_packed(fn, fmt, group, a_operand, a_ts, w_operand, w_ts, y, M, N, K, ldy):
-    _check(fn(fmt, group, _ptr(a_operand), _ptr(a_ts), _ptr(w_operand), _ptr(w_ts), M, N, K, _ptr(y),
-              y.stride(0) if ldy is None else ldy, _stream()))
-
-
-def pq_qgemm_packed(fmt: int, group: int, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
-                    y: torch.Tensor, M: int, N: int, K: int, ldy=None) -> None:
-    _gemm_packed(load().pq_qgemm_packed, fmt, group, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
-                 y, M, N, K, ldy)
-
-
-def pq_qgemm_packed_bias(fmt: int, group: int, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
-                         bias: torch.Tensor, y: torch.Tensor, M: int, N: int, K: int, ldy=None) -> None:
-    """The packed product plus the layer's bias (bf16 [N]), added before the rounding to bf16."""
-    _check(load().pq_qgemm_packed_bias(fmt, group, _ptr(a_operand), _ptr(a_tensor_scale), _ptr(w_operand),
-                                       _ptr(w_tensor_scale), M, N, K, _ptr(bias), _ptr(y),
-                                       y.stride(0) if ldy is None else ldy, _stream()))
-
-
-def pq_qgemm_packed_f32(fmt: int, group: int, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
-                        y: torch.Tensor, M: int, N: int, K: int, ldy=None) -> None:
-    _gemm_packed(load().pq_qgemm_packed_f32, fmt, group, a_operand, a_tensor_scale, w_operand,
-                 w_tensor_scale, y, M, N, K, ldy)
 
 
 def pq_probe_stream(src: torch.Tensor, read_bytes: int, dst: torch.Tensor, write_bytes: int) -> None:
@@ -594,3 +539,7 @@ def bf16_from_bits(bits_u16, device="cuda") -> torch.Tensor:
     import numpy as np
     t = torch.from_numpy(np.ascontiguousarray(bits_u16).view(np.int16))
     return t.to(device).view(torch.bfloat16)
+
+
+if os.path.exists(_LIB_PATH) and os.path.exists(_CALLS_PATH):
+    _bind_calls()

@@ -380,3 +380,39 @@ def test_qgemm_tile_validation(lib):
 ])
 def test_qgemm_tile_of_measured_shapes(lib, fmt, g, M, N, K, tiles):
     assert pq.pq_qgemm_tile(fmt, g, M, N, K) in tiles
+
+
+CALLS = {
+    "pq_quantize_act": "(fmt, group, x, perm, tensor_scale, codes, scales, M=None, K=None, ld=None)",
+    "pq_quantize_act_packed": "(fmt, group, x, tensor_scale, operand=None, codes=None, scales=None, K=None)",
+    "pq_norm_quantize_act_packed": "(kind, fmt, group, x, eps, tensor_scale, perm=None, gamma=None, mod_scale=None, "
+                                   "mod_shift=None, rows_per_mod=0, operand=None, y=None, K=None)",
+    "pq_hadamard_quantize_act_packed": "(fmt, group, x, tensor_scale, perm=None, operand=None, y=None, K=None)",
+    "pq_qgemm": "(fmt, group, a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, y, workspace=None, "
+                "M=None, N=None, K=None, ldy=None)",
+    "pq_qgemm_packed": "(fmt, group, a_operand, a_tensor_scale, w_operand, w_tensor_scale, y, M, N, K, ldy=None)",
+    "pq_qgemm_packed_f32": "(fmt, group, a_operand, a_tensor_scale, w_operand, w_tensor_scale, y, M, N, K, ldy=None)",
+    "pq_qgemm_packed_bias": "(fmt, group, a_operand, a_tensor_scale, w_operand, w_tensor_scale, bias, y, M, N, K, ldy=None)",
+    "pq_calib_moments": "(x, sumsq, absmax=None, workspace=None, rows=None, K=None, ld=None)",
+}
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_calls_take_their_arguments(lib, name):
+    # the natively marshalled calls take what functions of these signatures take, and refuse the rest as those do
+    import inspect
+    f = getattr(pq, name)
+    sig = inspect.signature(f)
+    assert str(sig) == CALLS[name]
+    required = [p for p in sig.parameters.values() if p.default is inspect.Parameter.empty]
+    with pytest.raises(TypeError, match=required[-1].name):
+        f(*[None] * (len(required) - 1))
+    with pytest.raises(TypeError, match="nonsense"):
+        f(*[None] * len(required), nonsense=1)
+    with pytest.raises(TypeError, match="multiple values"):
+        f(*[None] * len(required), **{required[0].name: 1})
+    with pytest.raises(TypeError, match="at most"):
+        f(*[None] * (len(sig.parameters) + 1))
+    if required[0].name in ("fmt", "kind"):
+        with pytest.raises((TypeError, AttributeError)):
+            f(*["1"] * len(required))

@@ -216,3 +216,76 @@ def test_forward_path_in_a_hip_graph(fmt, g, M, N, K, tile):
         # eager use of the same buffers between the replays
         pq.pq_quantize_act_packed(fmt, g, x, ta, a_op)
         torch.cuda.synchronize()
+
+
+class _Asked:
+    """A tensor that is only reached through its methods."""
+    def __init__(self, t):
+        self.t = t
+        self.shape = t.shape
+
+    device = property(lambda self: self.t.device)
+
+    def data_ptr(self):
+        return self.t.data_ptr()
+
+    def stride(self, d):
+        return self.t.stride(d)
+
+    def numel(self):
+        return self.t.numel()
+
+
+@pytest.mark.parametrize("wrap", [lambda t: t, torch.nn.Parameter, _Asked])
+@pytest.mark.parametrize("fmt,g", [(pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64)])
+def test_calls_by_position_by_name_and_on_another_stream(fmt, g, wrap):
+    # the natively marshalled calls: positions and names, tensors and what behaves like one, buffers given and made, the
+    # stream that is current
+    M, N, K = 33, 72, 192
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16)
+    hold = (lambda t: t) if wrap is torch.nn.Parameter else wrap       # a Parameter holds floating point only
+    x, w, bias = rnd(M, K), rnd(N, K), rnd(N)
+    tx, tw = torch.full((1,), 0.002, device=DEV), torch.empty(1, device=DEV)
+    wc, ws = pq.alloc_quantized(fmt, g, N, K, DEV)
+    pq.pq_quantize_weights(fmt, g, w, None, wc, ws, tw)
+    wo = pq.pq_pack_operand(fmt, g, wc, ws)
+    ac, asc = pq.alloc_quantized(fmt, g, M, K, DEV)
+    want = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    pq.pq_quantize_act(fmt, g, x, None, tx, ac, asc)
+    pq.pq_qgemm(fmt, g, ac, asc, tx, wc, ws, tw, want)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.no_grad():
+        torch.cuda._sleep(1000000)                       # what runs on another stream would be early
+        xs = torch.empty_like(x)
+        xs.copy_(x)
+        bc, bs = pq.alloc_quantized(fmt, g, M, K, DEV)
+        pq.pq_quantize_act(fmt, group=g, x=wrap(xs), perm=None, tensor_scale=hold(tx), codes=hold(bc), scales=hold(bs))
+        y, yb = (torch.empty_like(want) for _ in range(2))
+        yf = torch.empty((M, N), dtype=torch.float32, device=DEV)
+        y2 = torch.empty_like(want)
+        work = torch.empty(max(16, pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K)), dtype=torch.uint8, device=DEV)
+        pq.pq_qgemm(fmt, g, hold(bc), hold(bs), tx, hold(wc), hold(ws), tw, wrap(y), workspace=hold(work))
+        a = pq.pq_quantize_act_packed(fmt, g, wrap(xs), tx)
+        mine = torch.empty_like(a)
+        given = hold(mine)
+        assert pq.pq_quantize_act_packed(fmt, g, wrap(xs), tx, operand=given) is given
+        pq.pq_qgemm_packed(fmt, g, hold(a), tx, hold(wo), tw, wrap(y2), M, N, K)
+        pq.pq_qgemm_packed_bias(fmt, g, a, tx, wo, tw, wrap(bias), y=wrap(yb), M=M, N=N, K=K, ldy=N)
+        pq.pq_qgemm_packed_f32(fmt, g, a, tx, wo, tw, wrap(yf), M, N, K)
+        n = pq.pq_norm_quantize_act_packed(pq.NORM_RMS, fmt, g, wrap(xs), 1e-6, tx, gamma=wrap(rnd(K)), K=K)
+        sums = [torch.zeros(K, dtype=torch.float64, device=DEV) for _ in range(2)]
+        pq.pq_calib_moments(wrap(xs), wrap(sums[0]))
+        pq.pq_calib_moments(xs, sums[1], absmax=None, rows=M, K=K, ld=K)
+    side.synchronize()
+    assert torch.equal(bc, ac) and torch.equal(bs, asc) and torch.equal(mine, a) and n.numel() == a.numel()
+    assert torch.equal(y, want) and torch.equal(y2, want) and torch.equal(yf.to(torch.bfloat16), want)
+    assert torch.equal(sums[0], sums[1]) and torch.equal(sums[0], x.double().square().sum(0))
+    assert (yb.float() - want.float() - bias.float()).abs().max() <= 2.0 ** -7 * (want.float().abs().max() + 4)
+    with pytest.raises(pq.PQError) as e:
+        pq.pq_qgemm_packed(fmt, g, a, tx, wo, tw, y2, M, N, K, ldy=N - 1)
+    assert e.value.code == -2 and "ldy" in str(e.value)
+    with pytest.raises(IndexError):
+        pq.pq_quantize_act_packed(fmt, g, bias, tx)
