@@ -787,6 +787,7 @@ def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     (64, 33, 41, 64, S32), (256, 70, 3000, 256, S64X32), (64, 1500, 1003, 320, S64), (256, 500, 3000, 768, S64X96),
     (256, 1500, 2056, 256, T128), (256, 2344, 3656, 512, T224), (64, 4090, 4087, 320, T256),
     (64, 300, 4090, 256, S64), (64, 515, 1003, 3200, S64X32), (64, 2000, 2050, 2048, S64X96),    # row-major through LDS
+    (64, 512, 3065, 1408, S64X96),                                                               # eight waves a tile
 ])
 def test_qgemm_int3_multiplies_every_nibble(g, M, N, K, tile):
     # INT3 codes beyond the three bits that the quantizers write, -8 .. 7, are multiplied as they are, packed and
@@ -865,6 +866,22 @@ SPLIT_SHAPES = [
     (pq.FMT_INT3, 64, 33, 41, 64, S32), (pq.FMT_INT3, 256, 70, 3000, 256, S64X32), (pq.FMT_INT3, 256, 300, 4087, 768, S64X32),
     (pq.FMT_INT3, 64, 1500, 1003, 320, S64), (pq.FMT_INT3, 256, 500, 3000, 768, S64X96),
 ]
+
+
+# Tiles of 64 x 64 and 64 x 96 that eight waves share and not four: at most 256 of them and more than 21 steps of K.  Either
+# side of both lines, for each way of feeding the matrix unit; the last step half empty, steps that eight do not divide.
+EIGHT_WAVE_SHAPES = [
+    (pq.FMT_NVFP4, 16, 1000, 1023, 1376, S64), (pq.FMT_NVFP4, 16, 302, 4115, 3104, S64X96), (pq.FMT_NVFP4, 16, 500, 2040, 1344, S64),
+    (pq.FMT_NVFP4, 16, 1024, 1025, 1376, S64X96), (pq.FMT_INT4, 32, 517, 1250, 1376, S64), (pq.FMT_INT4, 64, 500, 3050, 1536, S64X96),
+    (pq.FMT_INT4, 256, 2012, 666, 1792, S64X96), (pq.FMT_INT3, 64, 512, 3065, 1408, S64X96), (pq.FMT_INT3, 32, 600, 1500, 1440, S64),
+]
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", EIGHT_WAVE_SHAPES)
+def test_qgemm_eight_waves_share_a_tile(fmt, g, M, N, K, tile):
+    _takes(tile, fmt, g, M, N, K)
+    _gemm_case(fmt, g, M, N, K, 990 + g + K)
+    test_qgemm_row_major_loaders_equal_packed(fmt, g, M, N, K, tile)
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K,tile", SPLIT_SHAPES)
