@@ -3,7 +3,7 @@
 // (pq_pack.hip), so that the forward path needs no packing pass.  Two kernels:
 //
 // quantize_panel_kernel (every format).  A workgroup of up to sixteen waves owns RPW rows; a wave works on
-// 64 / RPW chunks (one 64-wide K step for RPW = 8) of eight rows at a time: lane (64 / RPW) r + c holds
+// 64 / RPW chunks (one 64-wide K step for RPW = 8) of RPW rows at a time: lane (64 / RPW) r + c holds
 // chunk c (8 channels) of row r, the wave loads whole 128-byte lines and stores the rows' codes of a step
 // as one contiguous run of 32 RPW bytes.  INT: the waves share the workgroup's rows and take the group
 // blocks along K in turn; the group maxima are kept in LDS until the row maximum, and with it the per-row
@@ -195,9 +195,10 @@ __global__ __launch_bounds__(64 * kQuantPanelMaxWaves) void quantize_panel_kerne
   }
 }
 
+// one_trip: as many waves as it takes for each to have its blocks in flight together
 template <int FMT, int G, int RPW>
 static int launch_qpanel_r(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts,
-                           const OperandLayout& L, uint8_t* operand, uint8_t* codes, void* scales,
+                           const OperandLayout& L, uint8_t* operand, uint8_t* codes, void* scales, bool one_trip,
                            hipStream_t st) {
   const int64_t blocks = (rows + RPW - 1) / RPW;
   const size_t shmem = FMT == kNvfp4 ? 0 : (size_t)RPW * L.units * sizeof(float);
@@ -207,21 +208,27 @@ static int launch_qpanel_r(const void* x, int64_t rows, int64_t K, int64_t ld, c
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(quantize_panel_kernel)");
   }
-  // one wave per group block along K, up to eight (four workgroups per compute unit)
   constexpr int LPR = 64 / RPW;
   constexpr int SPG = G > LPR * 8 ? G / (LPR * 8) : 1;
+  constexpr int U = SPG == 1 ? 3 : 1;                              // blocks of a trip
   const int64_t k_blocks = (L.steps * 8 + SPG * LPR - 1) / (SPG * LPR);
   int n_waves = 1;
-  while (n_waves < 8 && n_waves * 3 <= k_blocks) n_waves *= 2;   // >= 2-3 trips per wave
+  if (one_trip) {
+    const int64_t want = (k_blocks + U - 1) / U, trips = (want + kQuantPanelMaxWaves - 1) / kQuantPanelMaxWaves;
+    n_waves = (int)((want + trips - 1) / trips);
+  } else {
+    // one wave per group block along K, up to eight (four workgroups per compute unit), two to three trips each
+    while (n_waves < 8 && n_waves * 3 <= k_blocks) n_waves *= 2;
+  }
   // NVFP4: four waves with RPW rows each; the group blocks along K are shared out over several workgroups
   // until there are enough of them (some eight per compute unit) for the dispatcher to even out the load
   // (one workgroup per row set of 4608 rows gave 576 workgroups, 2.25 per unit: some units got three)
   int k_split = 1;
   int64_t wgs = blocks;
   if (FMT == kNvfp4) {
-    n_waves = 32 / RPW;                                            // 32 rows per workgroup
+    n_waves = 4;
     wgs = (rows + RPW * n_waves - 1) / (RPW * n_waves);
-    while (wgs * k_split < 2048 && k_blocks / (k_split * 2) >= 3) k_split *= 2;
+    while (wgs * k_split < 2048 && (one_trip ? k_blocks > k_split * U : k_blocks / (k_split * 2) >= 3)) k_split *= 2;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs, (unsigned)k_split), dim3(64 * n_waves), shmem, st, (const uint16_t*)x, rows, K, ld, ts,
                      L.steps, L.units, operand + L.codes, (uint16_t*)(operand + L.scales),
@@ -229,14 +236,36 @@ static int launch_qpanel_r(const void* x, int64_t rows, int64_t K, int64_t ld, c
   return check_hip(hipGetLastError(), "quantize_panel_kernel");
 }
 
-// Eight rows per workgroup: four rows (twice the workgroups, spread more evenly over the compute
-// units when rows / 8 is a little above a multiple of 256) measured the same within 2 % on
-// 4608 x 3072 with either four or eight waves, so the template is instantiated for 8 only.
+// Rows of a workgroup (a wave, for NVFP4) and its waves.  With thousands of rows eight of them, whole lines in and 256-byte runs
+// out, and eight waves.  With fewer rows the chip has room and a workgroup's chain of trips, a memory latency each,
+// is what a launch takes: fewer rows, so that a trip covers more of K, and as many waves as have their blocks in one trip.
+// The lines between lie where the times cross over (eight formats and groups, 17 to 4608 rows, K 512 to 12288); us, eight rows and
+// eight waves | as here: INT4 g64 122 x 6912 7.4 | 4.0, 17 x 12288 11.5 | 4.3, 512 x 3072 4.6 | 3.9, 1024 x 3072 5.5 | 4.8, 2048 x
+// 6912 10.1 | 9.4; g128 122 x 1280 3.95 | 3.2; g256 122 x 2304 5.0 | 3.3; NVFP4 256 x 512 3.0 | 2.5.  Past the lines the others
+// lose: INT4 g64 122 x 1280 3.25 | 3.7 with one trip, 4608 x 3072 10.0 | 10.5, NVFP4 2048 x 6912 7.9 | 8.1 with four rows.
 template <int FMT, int G>
 static int launch_qpanel(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts,
                          const OperandLayout& L, uint8_t* operand, uint8_t* codes, void* scales,
                          hipStream_t st) {
-  return launch_qpanel_r<FMT, G, 8>(x, rows, K, ld, ts, L, operand, codes, scales, st);
+  int rpw = 8;
+  bool one_trip = false;
+  if constexpr (FMT == kNvfp4) {
+    one_trip = rows * K < (8 << 20);
+    if (one_trip) rpw = 4;
+  } else if (rows <= 2560 && (G > 64 || K > 1536)) {
+    one_trip = true;
+    const bool few = rows <= 512, some = rows <= 1280;
+    if (G <= 64) rpw = few ? 2 : some ? 4 : 8;
+    else if (G == 128) rpw = few && K > 1536 ? 2 : 8;
+    else rpw = few && K > 6144 ? 2 : some ? 4 : 8;
+  }
+#define PQ_ARGS (x, rows, K, ld, ts, L, operand, codes, scales, one_trip, st)
+  if constexpr (FMT != kNvfp4) {
+    if (rpw == 2) return launch_qpanel_r<FMT, G, 2> PQ_ARGS;
+  }
+  if (rpw == 4) return launch_qpanel_r<FMT, G, 4> PQ_ARGS;
+  return launch_qpanel_r<FMT, G, 8> PQ_ARGS;
+#undef PQ_ARGS
 }
 
 // NVFP4.  RW rows per wave, NW waves: a workgroup covers WR = RW * NW rows and walks column blocks of 512
