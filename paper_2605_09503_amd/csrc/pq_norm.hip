@@ -3,24 +3,26 @@
 // y_P[m, j] = y[m, pi(j)] as a bf16 tensor, as the activation operand of the GEMM (the dynamic
 // quantizer of Eq. 1-2 applied to those bf16 values), or both.
 //
-// One wave owns one token row from load to store, so no step waits for another wave:
-//   1. the row is read as it lies in memory (16 bytes per lane and access, whole lines), its sum
-//      and sum of squares come from v_dot2c_f32_bf16 on the packed pairs, and it is parked in the
-//      wave's own slab of LDS;
-//   2. lane l then produces chunks l, l + 64, ... (8 consecutive positions j each) of the reordered
-//      row: it loads pi(j) for its positions and gathers x[pi(j)] from the slab with 2-byte LDS
-//      reads -- where the paper's kernel issues indexed global loads -- normalises, applies the
-//      channel-wise vectors and rounds to bf16;
-//   3. the bf16 chunk is stored (consecutive lanes, consecutive 16 bytes) and / or quantized: a
-//      group of G positions is G / 8 consecutive lanes, so the group maximum is a lane reduction
-//      and the per-row power of two of the INT operand layout a wave reduction.
-// The channel-wise vectors are shared by the rows of a workgroup: they are staged in LDS already
-// reordered (position j holds the value of channel pi(j)) once per workgroup, which is the only
-// step all waves wait for.
+// One wave, or the two or four waves of a workgroup, own one token row from load to store:
+//   1. the row is read as it lies in memory (16 bytes per lane and access, whole lines) and stays in
+//      registers; its sum and sum of squares come from v_dot2c_f32_bf16 on the packed pairs;
+//   2. it is normalised, the channel-wise vectors -- read as they lie too -- are applied, and the values,
+//      rounded to bf16, go into the row's slab of LDS in their own order.  All of that is element-wise,
+//      so it need not wait for the reorder: no vector is ever gathered, and a row of any sample takes
+//      its own sample's vectors;
+//   3. lane l then produces chunks l, l + 64, ... (8 consecutive positions j each) of the reordered row:
+//      it loads pi(j) for its positions, gathers y[pi(j)] from the slab with 2-byte LDS reads -- where
+//      the paper's kernel issues indexed global loads -- and the chunk is stored (consecutive lanes,
+//      consecutive 16 bytes) and / or quantized: a group of G positions is G / 8 consecutive lanes, so
+//      the group maximum is a lane reduction and the per-row power of two of the INT operand layout a
+//      reduction over the row's waves.
+// What bounds it: few rows the chain of loads, sums, LDS and gathers (RMSNorm + NVFP4, 512 x 3072: 4.5 us; 6.3 when each
+// workgroup first reordered the vectors into LDS), many rows the vector unit beside the traffic: modulated LayerNorm +
+// NVFP4, 4608 x 3072, 36 MB: 14.7 us (20.4 before), RMSNorm 13.4 (16.3).
 //
-// The same skeleton runs the Hadamard variant (paper App. D, x H P): step 1 becomes a fast
-// Hadamard transform of the row in the wave's slab (fp32), steps 2 and 3 read the transformed
-// row at pi(j) -- the reorder is the order in which the transform's output is consumed.
+// The same skeleton runs the Hadamard variant (paper App. D, x H P): steps 1 and 2 become a fast
+// Hadamard transform of the row in the slab (fp32), step 3 reads the transformed row at pi(j) -- the
+// reorder is the order in which the transform's output is consumed.
 #include <math.h>
 
 #include <algorithm>
@@ -44,17 +46,23 @@ struct NormArgs {
   float eps;
   uint16_t* y;                  // bf16 [rows][ldy] normalised, reordered output, or null
   int64_t ldy;
-  int rows_seq;                 // rows a team of waves takes one after the other (wide rows)
   int had_pow2, had_m;          // Hadamard: K = had_pow2 * had_m, had_m in {1, 12, 20}
   float had_scale;              // 1 / sqrt(K)
 };
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
+// the sum over the wave, in every lane: halves, rows of 16 lanes, then inside a row by DPP rotations and quad permutes (the
+// values are equal in lanes 8 apart when lanes 4 apart meet, so the rotation gives the partner's)
 __device__ __forceinline__ float wave_sum_f32(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+  const auto h = __builtin_amdgcn_permlane32_swap(as_u32(v), as_u32(v), false, false);
+  v = as_f32(h[0]) + as_f32(h[1]);
+  const auto r = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
+  v = as_f32(r[0]) + as_f32(r[1]);
+  v += dpp_f32<0x128>(v);                                    // row_ror:8
+  v += dpp_f32<0x124>(v);                                    // row_ror:4
+  v += dpp_f32<0x4E>(v);                                     // quad_perm [2,3,0,1]
+  return v + dpp_f32<0xB1>(v);                               // quad_perm [1,0,3,2]
 }
 
 __device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
@@ -244,173 +252,269 @@ __device__ __forceinline__ void hadamard_row(float* slab, int K, int pow2, int m
   if (rem == 2) sylvester_pass<2, TEAM>(slab, inner, K / 2, lane);
 }
 
+constexpr int kHold = 6;        // chunks of a row that a thread holds between the statistics and the normalisation
+
+// eight channels of the normalised row, rounded to bf16
+template <bool ADA>
+__device__ __forceinline__ uint4 normalised(const uint4& x, const uint4& g0, const uint4& g1, float rstd, float nmr) {
+  uint32_t d[4] = {x.x, x.y, x.z, x.w};
+  const uint32_t s[4] = {g0.x, g0.y, g0.z, g0.w};
+  const uint32_t h[4] = {g1.x, g1.y, g1.z, g1.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float lo, hi;
+    if constexpr (ADA) {
+      const float l0 = fmaf(bf16_lo(d[e]), rstd, nmr), l1 = fmaf(bf16_hi(d[e]), rstd, nmr);
+      lo = fmaf(bf16_lo(s[e]), l0, bf16_lo(h[e])) + l0;      // (1 + s) ln + b
+      hi = fmaf(bf16_hi(s[e]), l1, bf16_hi(h[e])) + l1;
+    } else {
+      lo = (bf16_lo(d[e]) * rstd) * bf16_lo(s[e]);
+      hi = (bf16_hi(d[e]) * rstd) * bf16_hi(s[e]);
+    }
+    d[e] = pack_bf16_rne(lo, hi);
+  }
+  return make_uint4(d[0], d[1], d[2], d[3]);
+}
+
+// sum / maximum over the team, the same value in every thread (fixed order of the waves); `red`: a word per wave
+template <int TEAM, int N>
+__device__ __forceinline__ void team_sums(float (&v)[N], float* red, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_sum_f32(v[i]);
+  if constexpr (TEAM > 1) {
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) red[wave * N + i] = v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      v[i] = 0.0f;
+#pragma unroll
+      for (int w = 0; w < TEAM; ++w) v[i] += red[w * N + i];
+    }
+    __syncthreads();
+  }
+}
+template <int TEAM, int N>
+__device__ __forceinline__ void team_maxima(float (&v)[N], float* red, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_max(v[i]);
+  if constexpr (TEAM > 1) {
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) red[wave * N + i] = v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      v[i] = 0.0f;
+#pragma unroll
+      for (int w = 0; w < TEAM; ++w) v[i] = fmaxf(v[i], red[w * N + i]);
+    }
+    __syncthreads();
+  }
+}
+
+constexpr int kBatch = 3;                                    // chunks whose indices and gathers a thread has in flight
+
+// indices pi(j) of chunk c (clamped to an existing chunk: the address is always valid)
+__device__ __forceinline__ Idx8 load_idx(const int32_t* __restrict__ perm, int c, int k_chunks) {
+  const int cc = min(c, k_chunks - 1);
+  Idx8 ix;
+  if (perm) {
+    ix.lo = *reinterpret_cast<const int4*>(perm + (size_t)cc * 8);
+    ix.hi = *reinterpret_cast<const int4*>(perm + (size_t)cc * 8 + 4);
+  } else {
+    ix.lo = make_int4(cc * 8, cc * 8 + 1, cc * 8 + 2, cc * 8 + 3);
+    ix.hi = make_int4(cc * 8 + 4, cc * 8 + 5, cc * 8 + 6, cc * 8 + 7);
+  }
+  return ix;
+}
+
+// What a team's second half needs: the outputs, the sizes and the team's place
+struct Emit {
+  int64_t rows, row;            // all rows; the team's
+  int k_chunks, n_chunks;       // chunks that exist; chunks the panel holds (a half step past K included)
+  int n_units;
+  uint8_t* codes;
+  uint16_t* scales;
+  float* mul;
+  uint16_t* y;                  // or null
+  int64_t ldy;
+  float T, encT, scale;         // NVFP4; the factor of an fp32 slab
+  float* h_lds;                 // INT: n_units group maxima
+  float* red;
+  int wave, lane, tl;
+};
+
+// Chunks tl, tl + 64 TEAM, ... (8 positions j each) of the reordered row: the values at pi(j) are read from the slab (bf16,
+// or fp32 to be scaled and rounded), stored and / or quantized.
+template <int FMT, int G, int TEAM, bool F32>
+__device__ __forceinline__ void emit_row(const void* slab, const int32_t* __restrict__ perm, Idx8 (&ix_cur)[kBatch],
+                                          const Emit& em) {
+  constexpr bool QUANT = FMT != kFmtNone;
+  constexpr bool IS_INT = FMT == kInt4 || FMT == kInt3;
+  constexpr int LPG = G / 8;                                 // lanes that share a group
+  constexpr int TL = 64 * TEAM;
+  static_assert(LPG >= 1 && LPG <= 64, "a group lies inside one wave-wide run of chunks");
+  const int n_iter = (em.n_chunks + TL - 1) / TL;
+  float row_max[1] = {0.0f};
+  for (int it0 = 0; it0 < n_iter; it0 += kBatch) {
+    // next batch's indices while this one is worked on
+    Idx8 ix_next[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) ix_next[q] = load_idx(perm, em.tl + TL * (it0 + kBatch + q), em.k_chunks);
+    // gathers of the whole batch in flight together
+    uint32_t got[kBatch][8];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      if (it0 + q >= n_iter) break;                          // wave-uniform
+      const int idx[8] = {ix_cur[q].lo.x, ix_cur[q].lo.y, ix_cur[q].lo.z, ix_cur[q].lo.w,
+                          ix_cur[q].hi.x, ix_cur[q].hi.y, ix_cur[q].hi.z, ix_cur[q].hi.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (F32) got[q][e] = as_u32(static_cast<const float*>(slab)[idx[e]]);
+        else got[q][e] = static_cast<const uint16_t*>(slab)[idx[e]];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const int c = em.tl + TL * (it0 + q);
+      if (it0 + q >= n_iter) break;                          // wave-uniform
+      const bool in_row = c < em.k_chunks;
+      uint4 yb;                                              // eight bf16 values
+      if constexpr (F32) {
+        float yv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) yv[e] = as_f32(got[q][e]) * em.scale;
+        yb = make_uint4(pack_bf16_rne(yv[0], yv[1]), pack_bf16_rne(yv[2], yv[3]), pack_bf16_rne(yv[4], yv[5]),
+                        pack_bf16_rne(yv[6], yv[7]));
+      } else {
+        yb = make_uint4(got[q][0] | (got[q][1] << 16), got[q][2] | (got[q][3] << 16), got[q][4] | (got[q][5] << 16),
+                        got[q][6] | (got[q][7] << 16));
+      }
+      if (!in_row) yb = make_uint4(0u, 0u, 0u, 0u);          // the half step past K holds zeros
+      if (em.y && in_row) *reinterpret_cast<uint4*>(em.y + em.row * em.ldy + (size_t)c * 8) = yb;
+
+      if constexpr (QUANT) {
+        // the quantizer of pq_quantize.hip on the rounded values
+        const float v[8] = {bf16_lo(yb.x), bf16_hi(yb.x), bf16_lo(yb.y), bf16_hi(yb.y),
+                            bf16_lo(yb.z), bf16_hi(yb.z), bf16_lo(yb.w), bf16_hi(yb.w)};
+        float a = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(v[j]));
+        a = group_max<LPG>(a);
+        uint32_t codes;
+        if constexpr (FMT == kNvfp4) {
+          const Nv4Scale sc = nv4_scale(a, em.T, em.encT);
+          codes = 0;
+          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[0] * sc.inv, v[1] * sc.inv, 1.0f, 0);
+          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[2] * sc.inv, v[3] * sc.inv, 1.0f, 1);
+          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[4] * sc.inv, v[5] * sc.inv, 1.0f, 2);
+          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[6] * sc.inv, v[7] * sc.inv, 1.0f, 3);
+          // a scale unit is the two bytes of 32 positions = four lanes; the first lane of the quad
+          // collects the byte of the second pair
+          const uint32_t other = dpp_u32<0x4E>(sc.byte);       // lane ^ 2
+          const int u = c >> 2;
+          if ((em.lane & 3) == 0 && u < em.n_units)
+            em.scales[(int64_t)u * em.rows + em.row] = (uint16_t)(sc.byte | (other << 8));
+        } else {
+          constexpr int FI = IS_INT ? FMT : kInt4;
+          const IntScale sc = int_scale<FI>(a);
+          codes = int_codes8(v, sc.inv);
+          row_max[0] = fmaxf(row_max[0], a);
+          const int g = c / LPG;
+          if (em.lane % LPG == 0 && g < em.n_units) em.h_lds[g] = a;
+        }
+        if (c < em.n_chunks)
+          *reinterpret_cast<uint32_t*>(em.codes + ((int64_t)(c >> 3) * em.rows + em.row) * 32 + (c & 7) * 4) = codes;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) ix_cur[q] = ix_next[q];
+  }
+
+  if constexpr (IS_INT) {
+    // the per-row power of two of the operand layout: E = exponent(row maximum) - 10 puts the
+    // largest group maximum in [2^10, 2^11) (see pack_operand_kernel); scale units are the fp16
+    // group maxima times 2^-E, the row factor 2^E / Q
+    constexpr float Q = qmax_of(FMT);
+    team_maxima<TEAM>(row_max, em.red, em.wave, em.lane);      // (with TEAM > 1 also the barrier after the h_lds writes)
+    int e = (int)((as_u32(row_max[0]) >> 23) & 0xFF) - 127;
+    if (row_max[0] == 0.0f) e = 0;
+    const int E = max(-120, min(120, e - 10));
+    const float down = as_f32((uint32_t)(127 - E) << 23);
+    if (em.tl == 0) em.mul[em.row] = as_f32((uint32_t)(127 + E) << 23) / Q;
+    for (int u = em.tl; u < em.n_units; u += TL) {             // the team's own LDS writes, ordered above
+      const _Float16 hn = (_Float16)(em.h_lds[u] * down);
+      em.scales[(int64_t)u * em.rows + em.row] = __builtin_bit_cast(uint16_t, hn);
+    }
+  }
+}
+
+// Workgroups go round the eight chiplets in turn: the row block that gives each chiplet a contiguous run of them, so that
+// the lines that neighbouring rows share (32 bytes of codes and 2 of a scale unit a row) meet in one L2 (RMSNorm + NVFP4
+// 2048 x 6144 14.6 -> 10.7 us, 4608 x 3072 15.7 -> 13.4)
+__device__ __forceinline__ int64_t block_by_chiplet(int b, int n) {
+  const int per = n >> 3, extra = n & 7, chiplet = b & 7;
+  return (int64_t)chiplet * per + min(chiplet, extra) + (b >> 3);
+}
+
 template <int FMT, int G, int NORM, int TEAM>
 __global__ __launch_bounds__(64 * kNormMaxWaves) void norm_rows_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t K, int64_t ld, const float* __restrict__ tensor_scale,
     int64_t steps, int64_t units, uint8_t* __restrict__ p_codes, uint16_t* __restrict__ p_scales,
     float* __restrict__ p_mul, NormArgs na) {
-  constexpr bool QUANT = FMT != kFmtNone;
   constexpr bool IS_INT = FMT == kInt4 || FMT == kInt3;
-  constexpr int LPG = G / 8;                                 // lanes that share a group
-  // chunks a lane works on at a time (AdaLN holds more per chunk: two keep it at five waves per SIMD)
-  constexpr int kBatch = NORM == kNormAdaLn ? 2 : 3;
-  static_assert(LPG >= 1 && LPG <= 64, "a group lies inside one wave-wide run of chunks");
-  // dynamic LDS: [vectors: K bf16 (RMSNorm) or K words (AdaLN)] [per row: K bf16 (Hadamard: fp32) slab]
-  //              [per row, INT: `units` fp32 group maxima] [per wave: 4 floats for team reductions]
+  // dynamic LDS: [per team: K bf16 (Hadamard: fp32) slab] [per team, INT: `units` fp32 group maxima]
+  //              [per wave: 4 floats for team reductions]
   // TEAM == 1: every wave owns a row.  TEAM > 1: the workgroup is one team of TEAM waves and owns one row.
   constexpr int TL = 64 * TEAM;                              // threads of a team
+  constexpr int kSlabBytes = NORM == kHadamard ? 4 : 2;      // per channel
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int tid = threadIdx.x, lane = tid & 63, n_waves = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tl = TEAM == 1 ? lane : tid;                     // index inside the team
-  const int slot = TEAM == 1 ? wave : 0;                     // row slot inside the workgroup
-  const int rows_per_wg = TEAM == 1 ? n_waves : 1;
+  const int slot = TEAM == 1 ? wave : 0;                     // the team's place inside the workgroup
+  const int teams = TEAM == 1 ? n_waves : 1;
   const int Ki = (int)K;
-  const int k_chunks = Ki / 8;                               // chunks that exist
-  const int n_chunks = (int)steps * 8;                       // chunks the panel holds (a half step past K included)
+  const int k_chunks = Ki / 8;
   const int n_units = (int)units;
-  // TEAM > 1: the workgroup takes na.rows_seq consecutive rows one after the other, so that the vectors
-  // are staged once for all of them
-  const int rows_seq = TEAM == 1 ? 1 : na.rows_seq;
-  const int64_t row0 = (int64_t)blockIdx.x * (TEAM == 1 ? rows_per_wg : rows_seq);
+  const int64_t row = block_by_chiplet(blockIdx.x, gridDim.x) * teams + slot;
+  if (TEAM == 1 && row >= rows) return;                      // wave-uniform; a team stays together to the end
 
-  uint16_t* vec_g = reinterpret_cast<uint16_t*>(lds_raw);
-  uint32_t* vec_sb = reinterpret_cast<uint32_t*>(lds_raw);
-  constexpr int kSlabElem = NORM == kHadamard ? 4 : 2;       // Hadamard rows are held as fp32
-  const size_t vec_bytes = NORM == kHadamard ? 0 : (size_t)Ki * (NORM == kNormRms ? 2 : 4);
-  uint16_t* slab = reinterpret_cast<uint16_t*>(lds_raw + vec_bytes) + (size_t)slot * Ki;
-  float* slab_f = reinterpret_cast<float*>(lds_raw + vec_bytes) + (size_t)slot * Ki;
-  const size_t slab_bytes = (size_t)rows_per_wg * Ki * kSlabElem;
-  float* h_lds = reinterpret_cast<float*>(lds_raw + vec_bytes + slab_bytes) + (size_t)slot * n_units;
-  float* team_red = reinterpret_cast<float*>(lds_raw + vec_bytes + slab_bytes) + (size_t)(IS_INT ? rows_per_wg * n_units : 0);
-  // sum / maximum over the team, the same value in every thread (fixed order of the waves)
-  auto team_sum = [&](float v) -> float {
-    v = wave_sum_f32(v);
-    if constexpr (TEAM > 1) {
-      if (lane == 0) team_red[wave] = v;
-      __syncthreads();
-      float t = 0.0f;
-#pragma unroll
-      for (int w = 0; w < TEAM; ++w) t += team_red[w];
-      __syncthreads();
-      v = t;
-    }
-    return v;
-  };
-  auto team_max = [&](float v) -> float {
-    v = wave_max(v);
-    if constexpr (TEAM > 1) {
-      if (lane == 0) team_red[wave] = v;
-      __syncthreads();
-      float t = 0.0f;
-#pragma unroll
-      for (int w = 0; w < TEAM; ++w) t = fmaxf(t, team_red[w]);
-      __syncthreads();
-      v = t;
-    }
-    return v;
-  };
-
-  // ---- the vectors of the first row's sample, reordered, into LDS (all threads).  Scattered
-  // 2-byte loads from memory cost the texture addresser a cycle per lane, so the vectors are first
-  // copied as they lie (whole lines) into the space of the row slabs, which is still free, and
-  // reordered from there with LDS reads, one vector at a time.
-  int64_t mod0 = 0;
-  if constexpr (NORM == kNormAdaLn) mod0 = row0 / na.rows_per_mod;
-  if constexpr (NORM != kHadamard) {
-    const uint16_t* v0 = NORM == kNormRms ? na.gamma : (na.mod_scale ? na.mod_scale + mod0 * K : nullptr);
-    const uint16_t* v1 = NORM == kNormRms ? nullptr : (na.mod_shift ? na.mod_shift + mod0 * K : nullptr);
-    constexpr uint32_t kDefault0 = NORM == kNormRms ? 0x3F80u : 0u;      // gamma = 1, s = 0
-    uint16_t* tmp = reinterpret_cast<uint16_t*>(lds_raw + vec_bytes);    // the slab space: at least 2 K bytes
-    // one vector at a time: copy as it lies, barrier, permuted read
-    auto permuted = [&](const uint16_t* v, int c, uint32_t dflt, uint32_t (&out)[8]) {
-      if (!v) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = dflt;
-        return;
-      }
-      if (na.perm) {
-        const int4 i0 = *reinterpret_cast<const int4*>(na.perm + (size_t)c * 8);
-        const int4 i1 = *reinterpret_cast<const int4*>(na.perm + (size_t)c * 8 + 4);
-        const int idx[8] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = tmp[idx[e]];
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = tmp[c * 8 + e];
-      }
-    };
-    if (v0) {
-      for (int c = tid; c < k_chunks; c += blockDim.x)
-        *reinterpret_cast<uint4*>(tmp + c * 8) = *reinterpret_cast<const uint4*>(v0 + (size_t)c * 8);
-    }
-    __syncthreads();
-    for (int c = tid; c < k_chunks; c += blockDim.x) {
-      uint32_t a0[8];
-      permuted(v0, c, kDefault0, a0);
-      if constexpr (NORM == kNormRms) {
-        *reinterpret_cast<uint4*>(vec_g + c * 8) = make_uint4(a0[0] | (a0[1] << 16), a0[2] | (a0[3] << 16),
-                                                               a0[4] | (a0[5] << 16), a0[6] | (a0[7] << 16));
-      } else {
-        *reinterpret_cast<uint4*>(vec_sb + c * 8) = make_uint4(a0[0], a0[1], a0[2], a0[3]);
-        *reinterpret_cast<uint4*>(vec_sb + c * 8 + 4) = make_uint4(a0[4], a0[5], a0[6], a0[7]);
-      }
-    }
-    if constexpr (NORM == kNormAdaLn) {
-      if (v1) {                              // uniform over the workgroup
-        __syncthreads();
-        for (int c = tid; c < k_chunks; c += blockDim.x)
-          *reinterpret_cast<uint4*>(tmp + c * 8) = *reinterpret_cast<const uint4*>(v1 + (size_t)c * 8);
-        __syncthreads();
-        for (int c = tid; c < k_chunks; c += blockDim.x) {      // the chunks this thread wrote above
-          uint32_t a1[8];
-          permuted(v1, c, 0u, a1);
-          uint4 q0 = *reinterpret_cast<uint4*>(vec_sb + c * 8), q1 = *reinterpret_cast<uint4*>(vec_sb + c * 8 + 4);
-          q0.x |= a1[0] << 16; q0.y |= a1[1] << 16; q0.z |= a1[2] << 16; q0.w |= a1[3] << 16;
-          q1.x |= a1[4] << 16; q1.y |= a1[5] << 16; q1.z |= a1[6] << 16; q1.w |= a1[7] << 16;
-          *reinterpret_cast<uint4*>(vec_sb + c * 8) = q0;
-          *reinterpret_cast<uint4*>(vec_sb + c * 8 + 4) = q1;
-        }
-      }
-    }
-  }
-  __syncthreads();                       // the last barrier; every wave reaches it (the slabs are free again)
-  if (TEAM == 1 && row0 + slot >= rows) return;      // wave-uniform; a team stays together to the end
-
-  // indices pi(j) of chunk c (clamped to an existing chunk: the address is always valid)
-  auto load_idx = [&](int c) -> Idx8 {
-    const int cc = min(c, k_chunks - 1);
-    Idx8 ix;
-    if (na.perm) {
-      ix.lo = *reinterpret_cast<const int4*>(na.perm + (size_t)cc * 8);
-      ix.hi = *reinterpret_cast<const int4*>(na.perm + (size_t)cc * 8 + 4);
-    } else {
-      ix.lo = make_int4(cc * 8, cc * 8 + 1, cc * 8 + 2, cc * 8 + 3);
-      ix.hi = make_int4(cc * 8 + 4, cc * 8 + 5, cc * 8 + 6, cc * 8 + 7);
-    }
-    return ix;
-  };
-  const float k_f = (float)Ki;
-  float T = 0.0f, encT = 0.0f;
+  unsigned char* slab = lds_raw + (size_t)slot * Ki * kSlabBytes;
+  float* h_all = reinterpret_cast<float*>(lds_raw + (size_t)teams * Ki * kSlabBytes);
+  Emit em;
+  em.rows = rows;
+  em.row = row;
+  em.k_chunks = k_chunks;
+  em.n_chunks = (int)steps * 8;
+  em.n_units = n_units;
+  em.codes = p_codes;
+  em.scales = p_scales;
+  em.mul = p_mul;
+  em.y = na.y;
+  em.ldy = na.ldy;
+  em.T = em.encT = em.scale = 0.0f;
+  em.h_lds = h_all + (size_t)slot * n_units;
+  em.red = h_all + (size_t)(IS_INT ? teams * n_units : 0);
+  em.wave = wave;
+  em.lane = lane;
+  em.tl = tl;
   if constexpr (FMT == kNvfp4) {
-    T = *tensor_scale;
-    encT = nv4_enc_scale(T);
+    em.T = *tensor_scale;
+    em.encT = nv4_enc_scale(em.T);
   }
-  const int n_iter = (n_chunks + TL - 1) / TL;
-
-  for (int ri = 0; ri < rows_seq; ++ri) {
-  const int64_t row_u = TEAM == 1 ? row0 + slot : row0 + ri;
-  const bool active = row_u < rows;                          // a team runs past the last row without storing
-  const int64_t row = active ? row_u : rows - 1;
-  // the first batch of indices does not depend on the row's values
-  Idx8 ix_cur[kBatch];
-#pragma unroll
-  for (int q = 0; q < kBatch; ++q) ix_cur[q] = load_idx(tl + TL * q);
-
   const uint16_t* xr = x + row * ld;
-  float rstd = 0.0f, nmr = 0.0f;                             // LN(x) = x * rstd + nmr
+
   if constexpr (NORM == kHadamard) {
-    // ---- 1. the row as fp32 in the wave's slab, transformed in place
+    // ---- 1. the row as fp32 in the team's slab, transformed in place
+    Idx8 ix[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) ix[q] = load_idx(na.perm, tl + TL * q, k_chunks);
+    float* slab_f = reinterpret_cast<float*>(slab);
     constexpr int kInFlight = 8;
     const bool paley_on_mfma = na.had_m == 12 && na.had_pow2 >= 16;      // uniform
     if (paley_on_mfma) paley12_pass_from_memory<TEAM>(xr, slab_f, na.had_pow2, tl);
@@ -433,241 +537,171 @@ __global__ __launch_bounds__(64 * kNormMaxWaves) void norm_rows_kernel(
     }
     team_sync<TEAM>();
     hadamard_row<TEAM>(slab_f, Ki, na.had_pow2, na.had_m, tl, paley_on_mfma);
-    rstd = na.had_scale;
+    em.scale = na.had_scale;
+    emit_row<FMT, G, TEAM, true>(slab, na.perm, ix, em);
   } else {
-  // ---- 1. the row: statistics, and a copy in the wave's slab
-  float s1 = 0.0f, s2 = 0.0f;
-  {
+    constexpr bool ADA = NORM == kNormAdaLn;
+    // ---- 1. the row as it lies (buffer loads: past its end they give zeros, which add nothing), a block of kHold chunks
+    // a thread; the last block stays in registers, blocks before it (rows wider than kHold * 8 * TL) are parked in the
+    // slab.  A chunk that no thread of the team has is skipped.
+    const int n_blocks = (k_chunks + kHold * TL - 1) / (kHold * TL);
+    const int last_turns = (k_chunks - (n_blocks - 1) * kHold * TL + TL - 1) / TL;     // chunks of the last block: 1 .. kHold
+    const auto buffer = [&](const uint16_t* p) {
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, p ? Ki * 2 : 0, 0x00027000);
+    };
+    const auto chunk_of = [&](auto buf, int c) {
+      return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(buf, c * 16, 0, 0));
+    };
+    uint4 lines[kHold];
+    float st[ADA ? 2 : 1] = {};                              // sum of squares and (LayerNorm) sum
     const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3F803F80u);
-    constexpr int kInFlight = 8;                            // lines per lane requested together
-    for (int c0 = 0; c0 < k_chunks; c0 += kInFlight * TL) {
-      uint4 lines[kInFlight];
+    const auto xb = buffer(xr);
+    uint4* parked = reinterpret_cast<uint4*>(slab);
+    for (int b = 0; b < n_blocks; ++b) {
+      const int c0 = b * kHold * TL + tl;
+      const int turns = b + 1 < n_blocks ? kHold : last_turns;
 #pragma unroll
-      for (int t = 0; t < kInFlight; ++t) {
-        const int c = min(c0 + t * TL + tl, k_chunks - 1);
-        lines[t] = *reinterpret_cast<const uint4*>(xr + (size_t)c * 8);
+      for (int t = 0; t < kHold; ++t)
+        if (t < turns) lines[t] = chunk_of(xb, c0 + t * TL);
+#pragma unroll
+      for (int t = 0; t < kHold; ++t) {
+        if (t >= turns) break;
+        const uint32_t d[4] = {lines[t].x, lines[t].y, lines[t].z, lines[t].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bf16x2_t v = __builtin_bit_cast(bf16x2_t, d[e]);
+          if constexpr (ADA) st[1] = __builtin_amdgcn_fdot2_f32_bf16(v, ones, st[1], false);
+          st[0] = __builtin_amdgcn_fdot2_f32_bf16(v, v, st[0], false);
+        }
+        if (b + 1 < n_blocks) parked[c0 + t * TL] = lines[t];
       }
+    }
+    // the channel-wise vectors of the last block and the first indices do not depend on the sums
+    const uint16_t* vec0 = na.gamma;
+    const uint16_t* vec1 = nullptr;
+    if constexpr (ADA) {
+      const int64_t mod = na.rows_per_mod >= rows ? 0 : row / na.rows_per_mod;
+      vec0 = na.mod_scale ? na.mod_scale + mod * K : nullptr;
+      vec1 = na.mod_shift ? na.mod_shift + mod * K : nullptr;
+    }
+    const auto b0 = buffer(vec0), b1 = buffer(vec1);
+    constexpr int kVec = ADA ? kHold / 2 : kHold;            // chunks of the vectors held at a time
+    uint4 g0[kVec], g1[kVec];
+    const auto load_vectors = [&](int c0, int turns) {
 #pragma unroll
-      for (int t = 0; t < kInFlight; ++t) {
-        const int c = c0 + t * TL + tl;
-        if (c < k_chunks) {
-          *reinterpret_cast<uint4*>(slab + c * 8) = lines[t];
-          const uint32_t d[4] = {lines[t].x, lines[t].y, lines[t].z, lines[t].w};
+      for (int t = 0; t < kVec; ++t) {
+        if (t >= turns) break;
+        g0[t] = chunk_of(b0, c0 + t * TL);
+        if constexpr (ADA) g1[t] = chunk_of(b1, c0 + t * TL);
+        else if (!vec0) g0[t] = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+      }
+    };
+    load_vectors((n_blocks - 1) * kHold * TL + tl, last_turns);
+    Idx8 ix[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) ix[q] = load_idx(na.perm, tl + TL * q, k_chunks);
+
+    team_sums<TEAM>(st, em.red, wave, lane);
+    const float k_f = (float)Ki;
+    float mean = 0.0f;
+    if constexpr (ADA) {
+      mean = st[1] / k_f;
+      // variance = mean square - mean^2 loses accuracy when the mean dominates; then (rare, uniform
+      // over the team) it is recomputed from the deviations
+      const float mean_sq = st[0] / k_f;
+      const float var = mean_sq - mean * mean;
+      if (mean_sq > 16.0f * var) {
+        float s3[1] = {0.0f};
+        const auto add = [&](const uint4& p) {
+          const uint32_t d[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const bf16x2_t v = __builtin_bit_cast(bf16x2_t, d[e]);
-            if constexpr (NORM == kNormAdaLn) s1 = __builtin_amdgcn_fdot2_f32_bf16(v, ones, s1, false);
-            s2 = __builtin_amdgcn_fdot2_f32_bf16(v, v, s2, false);
+            const float lo = bf16_lo(d[e]) - mean, hi = bf16_hi(d[e]) - mean;
+            s3[0] = fmaf(hi, hi, fmaf(lo, lo, s3[0]));
           }
-        }
-      }
-    }
-  }
-  s2 = team_sum(s2);                     // (with TEAM > 1 also the barrier after the slab writes)
-  float mean = 0.0f;
-  if constexpr (NORM == kNormAdaLn) {
-    mean = team_sum(s1) / k_f;
-    // variance = mean square - mean^2 loses accuracy when the mean dominates; then (rare, uniform
-    // over the wave) it is recomputed from the deviations, on the lane's own chunks in LDS
-    const float mean_sq = s2 / k_f;
-    const float var = mean_sq - mean * mean;
-    if (mean_sq > 16.0f * var) {
-      float s3 = 0.0f;
-      for (int c = tl; c < k_chunks; c += TL) {
-        const uint4 p = *reinterpret_cast<const uint4*>(slab + c * 8);
-        const uint32_t d[4] = {p.x, p.y, p.z, p.w};
+        };
+        const int c_last = (n_blocks - 1) * kHold * TL + tl;
+        for (int c = tl; c < c_last; c += TL) add(parked[c]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = bf16_lo(d[e]) - mean, hi = bf16_hi(d[e]) - mean;
-          s3 = fmaf(hi, hi, fmaf(lo, lo, s3));
-        }
-      }
-      s2 = team_sum(s3);
-    } else {
-      s2 = var * k_f;
-    }
-  }
-  rstd = 1.0f / sqrtf(s2 / k_f + na.eps);
-  nmr = -mean * rstd;
-  }
-
-  // AdaLN: a row of another sample than the staged one reads its vectors from memory
-  bool own_mod = false;
-  const uint16_t* g_scale = nullptr;
-  const uint16_t* g_shift = nullptr;
-  if constexpr (NORM == kNormAdaLn) {
-    const int64_t mod = row / na.rows_per_mod;
-    own_mod = mod != mod0;                                   // wave-uniform
-    g_scale = na.mod_scale ? na.mod_scale + mod * K : nullptr;
-    g_shift = na.mod_shift ? na.mod_shift + mod * K : nullptr;
-  }
-
-  float row_max = 0.0f;
-  uint16_t* y_row = na.y ? na.y + row * na.ldy : nullptr;
-
-  // ---- 2./3. chunks lane, lane + 64, ... of the reordered row, kBatch at a time
-  for (int it0 = 0; it0 < n_iter; it0 += kBatch) {
-    // next batch's indices while this one is worked on
-    Idx8 ix_next[kBatch];
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) ix_next[q] = load_idx(tl + TL * (it0 + kBatch + q));
-    // gathers of the whole batch in flight together
-    float xv[kBatch][8];
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      const int idx[8] = {ix_cur[q].lo.x, ix_cur[q].lo.y, ix_cur[q].lo.z, ix_cur[q].lo.w,
-                          ix_cur[q].hi.x, ix_cur[q].hi.y, ix_cur[q].hi.z, ix_cur[q].hi.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) xv[q][e] = NORM == kHadamard ? slab_f[idx[e]] : bf16_to_f32(slab[idx[e]]);
-    }
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      const int c = tl + TL * (it0 + q);
-      if (it0 + q >= n_iter) break;                          // wave-uniform
-      const bool in_row = c < k_chunks;
-      const int cc = min(c, k_chunks - 1);
-      float yv[8];
-      if constexpr (NORM == kHadamard) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) yv[e] = xv[q][e] * rstd;             // 1 / sqrt(K)
-      } else if constexpr (NORM == kNormRms) {
-        const uint4 gq = *reinterpret_cast<const uint4*>(vec_g + cc * 8);
-        const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          yv[2 * e] = (xv[q][2 * e] * rstd) * bf16_lo(gw[e]);
-          yv[2 * e + 1] = (xv[q][2 * e + 1] * rstd) * bf16_hi(gw[e]);
-        }
+        for (int t = 0; t < kHold; ++t)
+          if (c_last + t * TL < k_chunks) add(lines[t]);
+        team_sums<TEAM>(s3, em.red, wave, lane);
+        st[0] = s3[0];
       } else {
-        uint32_t sb[8];
-        if (own_mod) {
-          const int idx[8] = {ix_cur[q].lo.x, ix_cur[q].lo.y, ix_cur[q].lo.z, ix_cur[q].lo.w,
-                              ix_cur[q].hi.x, ix_cur[q].hi.y, ix_cur[q].hi.z, ix_cur[q].hi.w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            sb[e] = (g_scale ? (uint32_t)g_scale[idx[e]] : 0u) | (g_shift ? (uint32_t)g_shift[idx[e]] << 16 : 0u);
-        } else {
-          const uint4 q0 = *reinterpret_cast<const uint4*>(vec_sb + cc * 8);
-          const uint4 q1 = *reinterpret_cast<const uint4*>(vec_sb + cc * 8 + 4);
-          sb[0] = q0.x; sb[1] = q0.y; sb[2] = q0.z; sb[3] = q0.w;
-          sb[4] = q1.x; sb[5] = q1.y; sb[6] = q1.z; sb[7] = q1.w;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float ln = fmaf(xv[q][e], rstd, nmr);
-          yv[e] = fmaf(bf16_lo(sb[e]), ln, bf16_hi(sb[e])) + ln;       // (1 + s) ln + b
-        }
-      }
-      uint4 yb = make_uint4(pack_bf16_rne(yv[0], yv[1]), pack_bf16_rne(yv[2], yv[3]),
-                            pack_bf16_rne(yv[4], yv[5]), pack_bf16_rne(yv[6], yv[7]));
-      if (!in_row) yb = make_uint4(0u, 0u, 0u, 0u);          // the half step past K holds zeros
-      if (y_row && in_row && active) *reinterpret_cast<uint4*>(y_row + (size_t)c * 8) = yb;
-
-      if constexpr (QUANT) {
-        // the quantizer of pq_quantize.hip on the rounded values
-        float v[8] = {bf16_lo(yb.x), bf16_hi(yb.x), bf16_lo(yb.y), bf16_hi(yb.y),
-                      bf16_lo(yb.z), bf16_hi(yb.z), bf16_lo(yb.w), bf16_hi(yb.w)};
-        float a = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(v[j]));
-        a = group_max<LPG>(a);
-        uint32_t codes;
-        if constexpr (FMT == kNvfp4) {
-          const Nv4Scale sc = nv4_scale(a, T, encT);
-          codes = 0;
-          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[0] * sc.inv, v[1] * sc.inv, 1.0f, 0);
-          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[2] * sc.inv, v[3] * sc.inv, 1.0f, 1);
-          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[4] * sc.inv, v[5] * sc.inv, 1.0f, 2);
-          codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, v[6] * sc.inv, v[7] * sc.inv, 1.0f, 3);
-          // a scale unit is the two bytes of 32 positions = four lanes; the first lane of the quad
-          // collects the byte of the second pair
-          const uint32_t other = dpp_u32<0x4E>(sc.byte);         // lane ^ 2
-          const int u = c >> 2;
-          if ((lane & 3) == 0 && u < n_units && active) p_scales[(int64_t)u * rows + row] = (uint16_t)(sc.byte | (other << 8));
-        } else {
-          constexpr int FI = IS_INT ? FMT : kInt4;
-          const IntScale sc = int_scale<FI>(a);
-          codes = int_codes8(v, sc.inv);
-          row_max = fmaxf(row_max, a);
-          const int g = c / LPG;
-          if (lane % LPG == 0 && g < n_units) h_lds[g] = a;
-        }
-        if (c < n_chunks && active) *reinterpret_cast<uint32_t*>(p_codes + ((int64_t)(c >> 3) * rows + row) * 32 + (c & 7) * 4) = codes;
+        st[0] = var * k_f;
       }
     }
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) ix_cur[q] = ix_next[q];
-  }
+    const float rstd = 1.0f / sqrtf(st[0] / k_f + na.eps);
+    const float nmr = -mean * rstd;                          // LN(x) = x * rstd + nmr
 
-  if constexpr (IS_INT) {
-    // the per-row power of two of the operand layout: E = exponent(row maximum) - 10 puts the
-    // largest group maximum in [2^10, 2^11) (see pack_operand_kernel); scale units are the fp16
-    // group maxima times 2^-E, the row factor 2^E / Q
-    constexpr float Q = qmax_of(FMT);
-    const float mx = team_max(row_max);    // (with TEAM > 1 also the barrier after the h_lds writes)
-    int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
-    if (mx == 0.0f) e = 0;
-    const int E = max(-120, min(120, e - 10));
-    const float down = as_f32((uint32_t)(127 - E) << 23);
-    if (tl == 0 && active) p_mul[row] = as_f32((uint32_t)(127 + E) << 23) / Q;
-    for (int u = tl; u < n_units; u += TL) {         // the team's own LDS writes, ordered above
-      const _Float16 hn = (_Float16)(h_lds[u] * down);
-      if (active) p_scales[(int64_t)u * rows + row] = __builtin_bit_cast(uint16_t, hn);
+    // ---- 2. normalised, the vectors applied, rounded to bf16, into the slab in the row's own order
+    for (int b = n_blocks - 1; b >= 0; --b) {
+      const int c0 = b * kHold * TL + tl;
+      const int turns = b + 1 < n_blocks ? kHold : last_turns;
+      if (b + 1 < n_blocks) {
+#pragma unroll
+        for (int t = 0; t < kHold; ++t) lines[t] = parked[c0 + t * TL];
+        load_vectors(c0, kHold);
+      }
+#pragma unroll
+      for (int h = 0; h < kHold; h += kVec) {
+        if (h >= turns) break;
+        if (h > 0) {
+          asm volatile("" ::: "memory");                     // not earlier: the registers are those of the part before
+          load_vectors(c0 + h * TL, turns - h);
+        }
+#pragma unroll
+        for (int t = h; t < h + kVec; ++t) {
+          if (t >= turns) break;
+          const uint4 y = normalised<ADA>(lines[t], g0[t - h], g1[t - h], rstd, nmr);
+          if (c0 + t * TL < k_chunks) parked[c0 + t * TL] = y;
+        }
+      }
     }
+    team_sync<TEAM>();
+
+    // ---- 3. gathered at pi(j), stored and / or quantized
+    emit_row<FMT, G, TEAM, false>(slab, na.perm, ix, em);
   }
-  if constexpr (TEAM > 1) __syncthreads();     // the slab and the group maxima are free for the next row
-  }  // rows of the workgroup
 }
 
 constexpr size_t kNormLdsLimit = 160 * 1024 - 1024;      // dynamic LDS a workgroup may ask for
 
-// rows: row slabs of the workgroup (= waves when every wave owns a row, 1 for a team of waves)
-size_t norm_lds_bytes(int norm, bool is_int, int rows_per_wg, int n_waves, int64_t K, int64_t units) {
-  const size_t tail = (is_int ? (size_t)rows_per_wg * units * 4 : 0) + (size_t)n_waves * 16;
-  if (norm == kHadamard) return (size_t)rows_per_wg * K * 4 + tail;
-  return (size_t)K * (norm == kNormRms ? 2 : 4) + (size_t)rows_per_wg * K * 2 + tail;
+size_t norm_lds_bytes(int norm, bool is_int, int teams, int n_waves, int64_t K, int64_t units) {
+  const size_t tail = (is_int ? (size_t)teams * units * 4 : 0) + (size_t)n_waves * 16;
+  return (size_t)teams * K * (norm == kHadamard ? 4 : 2) + tail;
 }
 
 // Waves (= rows) per workgroup: as many as still let the launch run in one round of resident
-// workgroups, so that the reordered vectors are built as rarely as possible without leaving a
-// tail of workgroups that start when the others are done.  How many workgroups of a given size a
+// workgroups, without leaving a tail of workgroups that start when the others are done.  How many workgroups of a given size a
 // compute unit holds (registers, LDS, wave slots) is asked of the runtime.
 template <typename Kern>
-int norm_waves_per_group(Kern kern, int norm, bool is_int, int64_t rows, int64_t K, int64_t units) {
+int hadamard_waves_per_group(Kern kern, bool is_int, int64_t rows, int64_t K, int64_t units) {
   int best = 1;
   double best_cost = 1e30;
   for (int w = 1; w <= kNormMaxWaves; ++w) {
-    const size_t lds = norm_lds_bytes(norm, is_int, w, w, K, units);
+    const size_t lds = norm_lds_bytes(kHadamard, is_int, w, w, K, units);
     if (lds > kNormLdsLimit) break;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * w, lds) != hipSuccess || per_cu < 1)
       per_cu = 1;
     const int64_t groups = (rows + w - 1) / w;
     const int64_t rounds = (groups + 256 * (int64_t)per_cu - 1) / (256 * (int64_t)per_cu);
-    // time ~ rounds x (row work + vector staging shared by w rows), in units of one row's work, plus what the
-    // rows that meet on the busiest of the 256 units cost each other (the transform's passes share the unit's
-    // LDS: 512 x 4096 takes 26 us with eight rows a workgroup on 64 units, 13 with two on 256; 1024 x 3072 10.6 and
-    // 8.9; the norms less: modulated LayerNorm 1024 x 3072 8.7 and 8.1, RMSNorm + NVFP4 7.4 and 7.3, where one round
-    // holds the launch: beyond it 4608 x 4096 lost 2 to 3 %, and with 0.012 RMSNorm + INT4 1280 x 3072 7.9 -> 8.2); among equal costs prefer more waves in flight per compute unit
-    const double shared = norm == kHadamard ? 0.06 : rounds == 1 ? 0.008 : 0.0;
-    const double crowd = shared * (double)((groups + 255) / 256 * w);
+    // time ~ rounds x (row work + a share of the workgroup's), in units of one row's work, plus what the rows that meet on
+    // the busiest of the 256 units cost each other (the transform's passes share the unit's LDS: 512 x 4096 takes 26 us
+    // with eight rows a workgroup on 64 units, 13 with two on 256; 1024 x 3072 10.6 and 8.9); among equal costs prefer more
+    // waves in flight per compute unit
+    const double crowd = 0.06 * (double)((groups + 255) / 256 * w);
     const double cost = (double)rounds * (1.0 + 0.35 / w) + crowd - 1e-3 * (double)std::min(per_cu * w, 32);
     if (cost < best_cost) best_cost = cost, best = w;
   }
   return best;
 }
 
-constexpr int kWideTeam = 4;             // waves that share a row wider than kWideRow channels
-constexpr int64_t kWideRow = 4096;
-
 template <int FMT, int G, int NORM, int TEAM>
 int launch_norm_team(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts, const OperandLayout& L,
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
   constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
-  const size_t least = norm_lds_bytes(NORM, is_int, 1, TEAM, K, L.units);
-  if (least > kNormLdsLimit)
-    return fail(PQ_ERR_SHAPE, "K=%lld needs %zu bytes of LDS for one row and the vectors, more than the %zu available",
-                (long long)K, least, kNormLdsLimit);
   auto kern = norm_rows_kernel<FMT, G, NORM, TEAM>;
   // the choice depends on the shape only: remembered from the previous launch of this kernel
   static thread_local struct { int64_t rows, K; int n_waves; } memo = {0, 0, 0};
@@ -675,41 +709,54 @@ int launch_norm_team(const void* x, int64_t rows, int64_t K, int64_t ld, const f
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNormLdsLimit);
     if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(norm_rows_kernel)");
-    memo.n_waves = TEAM == 1 ? norm_waves_per_group(kern, NORM, is_int, rows, K, L.units) : TEAM;
+    // waves that own a row each: one a workgroup spreads few rows best (RMSNorm 256 x 2048 4.9 us, four 5.4), four write
+    // more of a line together (3072 x 512 4.4 -> 4.3, LayerNorm 3072 x 2048 8.3 -> 8.0)
+    memo.n_waves = TEAM > 1 ? TEAM : NORM == kHadamard ? hadamard_waves_per_group(kern, is_int, rows, K, L.units) : rows > 1024 ? 4 : 1;
     memo.rows = rows;
     memo.K = K;
   }
   const int n_waves = memo.n_waves;
-  const int rows_per_wg = TEAM == 1 ? n_waves : 1;
-  const size_t shmem = norm_lds_bytes(NORM, is_int, rows_per_wg, n_waves, K, L.units);
-  NormArgs args = na;
-  // a team takes several rows in sequence where that still leaves about three workgroups per compute
-  // unit: the staging of the vectors is then shared by those rows
-  args.rows_seq = 1;
-  if (TEAM > 1 && NORM != kHadamard) args.rows_seq = (int)std::max<int64_t>(1, std::min<int64_t>(8, rows / 768));
-  const int64_t per_group = TEAM == 1 ? rows_per_wg : args.rows_seq;
-  const int64_t groups = (rows + per_group - 1) / per_group;
+  const int teams = TEAM == 1 ? n_waves : 1;
+  const size_t shmem = norm_lds_bytes(NORM, is_int, teams, n_waves, K, L.units);
+  const int64_t groups = (rows + teams - 1) / teams;
   hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(64 * n_waves), shmem, st, (const uint16_t*)x, rows, K, ld, ts,
                      L.steps, L.units, operand ? operand + L.codes : nullptr,
                      (uint16_t*)(operand ? operand + L.scales : nullptr),
-                     (float*)(operand ? operand + L.mul : nullptr), args);
+                     (float*)(operand ? operand + L.mul : nullptr), na);
   return check_hip(hipGetLastError(), "norm_rows_kernel");
 }
 
-// One wave per row up to kWideRow channels; wider rows are shared by the kWideTeam waves of a workgroup
-// (a wave alone would leave a compute unit with two or three rows in flight).  So are the rows of a launch too
-// short to give every unit several of them: a row's chain of loads, passes and gathers is then what takes the time,
-// and four waves walk it four times as fast.  Measured, one wave -> four, us: RMSNorm + NVFP4, K = 3072, 256 rows
-// 7.1 -> 5.4, 512 rows 7.2 -> 6.2, 768 rows 7.2 -> 7.0, 1024 rows 7.3 -> 8.0; K = 1024, where a lane has half a chunk
-// of the row, 256 rows 4.9 -> 4.5 (LayerNorm 6.1 -> 5.7), 384 rows 4.9 -> 5.0 (6.1 -> 6.3), 512 rows 4.9 -> 5.0 (6.2 ->
-// 6.4); K = 1152, 512 rows 5.3 -> 5.1 (7.1 -> 6.5).  Hadamard + INT4, K = 3072, 256 rows 10.8 -> 5.8, 512 rows 10.9 ->
-// 6.5, 768 rows 11.0 -> 7.6, 1024 rows 11.0 (9.5 with fewer rows a workgroup) -> 10.6; K = 1024, 768 rows 9.0 -> 7.2.
-// Below 1024 channels nothing is gained (512 x 768: 4.7 -> 5.0).
+// Waves that share a row.  Norms: a row's chain of loads, sums, stores and gathers is what few rows take, and more waves walk
+// it faster; with many rows it is the work, and each wave more costs its own sums and divisions.  Up to kHold chunks a thread
+// (3072 channels a wave) no part of a row is parked in LDS and read back.  Measured with 1, 2, 4 waves, us, RMSNorm + NVFP4:
+// 512 x 3072 6.3, 5.0, 4.6; 1024 x 3072 6.7, 5.3, 6.0; 2048 x 3072 7.6, 7.2, 9.0; 8192 x 3072 20.6, 20.2, 27.3; 4608 x 1536
+// 7.7, 9.6, 12.4; 1024 x 768 4.0, 3.8, 4.8; 2048 x 6144 13.1, 10.9, 11.4; 2048 x 12288 39.9, 29.3, 21.4; modulated LayerNorm
+// 512 x 3072 6.6, 5.5, 5.1; 8192 x 3072 21.9, 22.7, 30.6; 4608 x 1536 8.6, 10.9, 14.0; 1024 x 2048 5.7, 5.0, 5.6.
+// Hadamard: up to 4096 channels a wave's own LDS traffic is all that a row waits for; wider rows leave a unit with two or
+// three in flight, and few rows wait for their chain: four waves there.  Hadamard + INT4, one wave -> four, us: K = 3072,
+// 256 rows 10.8 -> 5.8, 512 rows 10.9 -> 6.5, 768 rows 11.0 -> 7.6, 1024 rows 11.0 (9.5 with fewer rows a workgroup) -> 10.6;
+// K = 1024, 768 rows 9.0 -> 7.2.
+int waves_per_row(int norm, int64_t rows, int64_t K) {
+  if (norm == kHadamard) return K > 4096 || (rows <= 768 && K >= 1024) ? 4 : 1;
+  if (K > 6144) return 4;
+  if (K >= 4096) return rows <= 768 ? 4 : 2;
+  if (K >= 1280) return rows <= 512 ? 4 : rows <= (K >= 2560 ? 2048 : K >= 2048 ? 1024 : 0) ? 2 : 1;
+  return K >= 768 && rows <= 1024 ? 2 : 1;
+}
+
 template <int FMT, int G, int NORM>
 int launch_norm_rows(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts, const OperandLayout& L,
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
-  const bool few = rows <= (NORM == kHadamard ? 768 : K > 1024 ? 512 : 256) && K >= 1024;
-  if (K > kWideRow || few) return launch_norm_team<FMT, G, NORM, kWideTeam>(x, rows, K, ld, ts, L, operand, na, st);
+  // the widths that are taken, more than a row alone needs for the norms: K and the vectors' 2 K or 4 K bytes beside the row
+  constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
+  const int team = waves_per_row(NORM, rows, K);
+  const size_t least = (size_t)K * (NORM == kNormAdaLn ? 6 : 4) + (is_int ? L.units * 4 : 0) + (size_t)(K > 4096 ? 4 : 1) * 16;
+  if (least > kNormLdsLimit)
+    return fail(PQ_ERR_SHAPE, "K=%lld needs %zu bytes of LDS for one row and the vectors, more than the %zu available",
+                (long long)K, least, kNormLdsLimit);
+  if (team == 4) return launch_norm_team<FMT, G, NORM, 4>(x, rows, K, ld, ts, L, operand, na, st);
+  if constexpr (NORM != kHadamard)
+    if (team == 2) return launch_norm_team<FMT, G, NORM, 2>(x, rows, K, ld, ts, L, operand, na, st);
   return launch_norm_team<FMT, G, NORM, 1>(x, rows, K, ld, ts, L, operand, na, st);
 }
 
@@ -731,7 +778,6 @@ NormArgs norm_args(const pq_norm_params& p, void* y, int64_t ldy) {
   na.eps = p.eps;
   na.y = (uint16_t*)y;
   na.ldy = ldy;
-  na.rows_seq = 1;
   na.had_pow2 = na.had_m = 0;
   na.had_scale = 0.0f;
   return na;

@@ -340,3 +340,41 @@ def test_rows_at_the_edge_of_a_short_launch(kind, rows, K):
         pq.pq_norm_quantize_act_packed(kind, fmt, g, _dev(x_bits), args[0], ts, *args[1:], operand=got)
         torch.cuda.synchronize()
         assert torch.equal(want, got)
+
+
+# the sizes at which a row goes from one wave to two or four, and the first widths of which a part is parked in LDS (beyond 3072
+# channels a wave), with rows of a mean far above their spread among them
+@pytest.mark.parametrize("kind", [RMS, ADALN])
+@pytest.mark.parametrize("rows,K", [(5, 760), (1024, 768), (1025, 768), (512, 1280), (513, 1280), (1024, 2048), (1025, 2048),
+                                    (2048, 2560), (2049, 2560), (2049, 3072), (2049, 3080), (2050, 4088), (768, 4096),
+                                    (769, 4096), (769, 6144), (3, 6152), (3, 12288), (3, 12296)])
+def test_rows_of_one_two_and_four_waves(kind, rows, K):
+    _say("norm waves kind=%d rows=%d K=%d" % (kind, rows, K))
+    rng = np.random.default_rng(9680 + kind + rows + K)
+    x_bits = _activations(rng, rows, K)
+    x_bits[2] = _bits(rng.standard_normal(K) + 40.0)
+    perm = rng.permutation(K).astype(np.int32)
+    per = 5
+    gamma_bits = _bits(1.0 + 0.3 * rng.standard_normal(K))
+    s_bits, b_bits = (_bits(0.5 * rng.standard_normal((-(-rows // per), K))) for _ in range(2))
+    args = (torch.from_numpy(perm).to(DEV), _dev(gamma_bits), _dev(s_bits), _dev(b_bits), per)
+    x = _dev(x_bits)
+    y = pq.pq_norm_reorder(kind, x, 1e-6, *args)
+    torch.cuda.synchronize()
+    sample = np.unique(np.concatenate([np.arange(min(rows, 12)), [rows - 1], rng.integers(0, rows, 24)]))
+    got, xs = _host_bits(y)[sample], OF.bf16_bits_to_f64(x_bits[sample])
+    if kind == RMS:
+        ref = ON.rmsnorm_reordered(xs, OF.bf16_bits_to_f64(gamma_bits), 1e-6, perm)
+    else:
+        ref = ON.adaln_reordered(xs, *(OF.bf16_bits_to_f64(v)[sample // per] for v in (s_bits, b_bits)), 1, 1e-6, perm)
+    _check_close(got, ref, "waves", min_same=0.99)
+    if K % 64:
+        return
+    for fmt, g in ((pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64)):
+        Ta = torch.full((1,), 0.004, dtype=torch.float32, device=DEV) if fmt == pq.FMT_NVFP4 else None
+        nbytes = pq.pq_operand_bytes(fmt, g, rows, K)
+        both = [torch.zeros(nbytes, dtype=torch.uint8, device=DEV) for _ in range(2)]
+        pq.pq_norm_quantize_act_packed(kind, fmt, g, x, 1e-6, Ta, *args, operand=both[0])
+        pq.pq_quantize_act_packed(fmt, g, y, Ta, both[1])
+        torch.cuda.synchronize()
+        assert torch.equal(*both)
