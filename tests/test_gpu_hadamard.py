@@ -224,3 +224,27 @@ def test_rows_at_the_edge_of_a_short_launch(rows, K):
         pq.pq_hadamard_quantize_act_packed(fmt, g, _dev(x_bits), ts, perm=perm_d, operand=got)
         torch.cuda.synchronize()
         assert torch.equal(want, got)
+
+
+# rows in the registers of one wave (8 to 64 values a lane) and of four, with each Paley order, on both sides of the lines
+# between them and between one row and four a workgroup; (3, 320) and (3, 192) are left to the passes over LDS
+@pytest.mark.parametrize("rows,K", [(3, 384), (1024, 512), (1025, 512), (3, 640), (3, 320), (3, 192), (1030, 768), (3, 1024),
+                                    (3, 1280), (768, 1536), (769, 1536), (1536, 2048), (1537, 2048), (1536, 2560), (1537, 2560),
+                                    (1536, 3072), (1538, 3072), (6144, 4096), (6145, 4096), (3, 6144), (3, 10240)])
+def test_rows_in_registers(rows, K):
+    _say("hadamard in registers rows=%d K=%d" % (rows, K))
+    rng = np.random.default_rng(9970 + rows + K)
+    x_bits = _activations(rng, rows, K)
+    perm = rng.permutation(K).astype(np.int32)
+    x, perm_d = _dev(x_bits), torch.from_numpy(perm).to(DEV)
+    y = pq.pq_hadamard_reorder(x, perm_d)
+    torch.cuda.synchronize()
+    sample = np.unique(np.concatenate([np.arange(min(rows, 6)), [rows - 1], rng.integers(0, rows, 8)]))
+    _check_close(_host_bits(y)[sample], OH.rotate_reordered(OF.bf16_bits_to_f64(x_bits[sample]), perm), "registers")
+    for fmt, g in ((pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64)):
+        ts = torch.full((1,), 0.01, dtype=torch.float32, device=DEV)
+        want, got = (torch.zeros(pq.pq_operand_bytes(fmt, g, rows, K), dtype=torch.uint8, device=DEV) for _ in range(2))
+        pq.pq_quantize_act_packed(fmt, g, y, ts, operand=want)
+        pq.pq_hadamard_quantize_act_packed(fmt, g, x, ts, perm=perm_d, operand=got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
