@@ -333,4 +333,13 @@ __device__ __forceinline__ uint32_t nv4_code_pair(float x0, float x1, float inv)
   return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x0 * inv, x1 * inv, 1.0f, 0) & 0xFFu;
 }
 
+// Workgroups go round the eight chiplets in turn: the row block that gives each chiplet a contiguous run of them, so that
+// the lines that neighbouring rows share (32 bytes of codes and 2 of a scale unit a row) meet in one L2.  us, before and
+// after: RMSNorm + NVFP4 2048 x 6144 14.6, 10.7, 4608 x 3072 15.7, 13.4; the quantizer with eight rows a workgroup, INT4
+// groups of 64, 4608 x 12288 29.7, 28.2, 512 x 3072 3.85, 3.70, NVFP4 4608 x 3072 7.8, 7.0; packing 9216 x 3072 7.5, 6.5.
+__device__ __forceinline__ int64_t block_by_chiplet(int b, int n) {
+  const int per = n >> 3, extra = n & 7, chiplet = b & 7;
+  return (int64_t)chiplet * per + min(chiplet, extra) + (b >> 3);
+}
+
 }  // namespace pq

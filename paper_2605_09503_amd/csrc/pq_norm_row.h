@@ -227,14 +227,6 @@ __device__ __forceinline__ void emit_row(const void* slab, const int32_t* __rest
   }
 }
 
-// Workgroups go round the eight chiplets in turn: the row block that gives each chiplet a contiguous run of them, so that
-// the lines that neighbouring rows share (32 bytes of codes and 2 of a scale unit a row) meet in one L2 (RMSNorm + NVFP4
-// 2048 x 6144 14.6 -> 10.7 us, 4608 x 3072 15.7 -> 13.4)
-__device__ __forceinline__ int64_t block_by_chiplet(int b, int n) {
-  const int per = n >> 3, extra = n & 7, chiplet = b & 7;
-  return (int64_t)chiplet * per + min(chiplet, extra) + (b >> 3);
-}
-
 constexpr size_t kNormLdsLimit = 160 * 1024 - 1024;      // dynamic LDS a workgroup may ask for
 
 }  // namespace

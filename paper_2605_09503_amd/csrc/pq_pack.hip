@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
                                                            uint16_t* __restrict__ p_scales,
                                                            float* __restrict__ p_mul) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t r0 = (int64_t)blockIdx.x * kPackRows;
+  const int64_t r0 = block_by_chiplet(blockIdx.x, gridDim.x) * kPackRows;
   constexpr bool MARK = FMT == kInt3 && G >= 64 && !DENSE3;          // three bits hold no wide code
   __shared__ int row_wide[kPackRows];
   if constexpr (MARK) {

@@ -50,7 +50,8 @@ __global__ __launch_bounds__(64 * kQuantPanelMaxWaves) void quantize_panel_kerne
   // workgroup write one run of n_waves * RPW * 32 bytes of the panel (1 KB with four waves) instead of
   // 256-byte pieces a whole panel step apart, and a wave's loads in flight are consecutive pieces of its rows.
   constexpr bool kWaveRows = FMT == kNvfp4;
-  const int64_t r0 = kWaveRows ? ((int64_t)blockIdx.x * n_waves + wave) * RPW : (int64_t)blockIdx.x * RPW;
+  const int64_t block = block_by_chiplet(blockIdx.x, gridDim.x);
+  const int64_t r0 = kWaveRows ? (block * n_waves + wave) * RPW : block * RPW;
   const int64_t r = r0 + r_local;
   const bool r_ok = r < rows;
   const int n_chunks = (int)steps * 8;                      // chunks per row, a half step past K included

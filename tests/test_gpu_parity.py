@@ -1301,3 +1301,10 @@ def test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad):
 ])
 def test_quantize_act_packed_where_its_shape_changes(fmt, g, M, K, pad):
     test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad)
+
+
+# Row blocks that are shared out over eight chiplets: one to nine of them, and as many with a remainder of one to seven
+@pytest.mark.parametrize("fmt,g,M", [(f, g, M) for f, g in ((pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64))
+                                     for M in (1, 9, 17, 57, 64, 65, 66, 135, 153, 1000, 2571)])
+def test_row_blocks_in_every_remainder_of_eight(fmt, g, M):
+    test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, 192, 0)
