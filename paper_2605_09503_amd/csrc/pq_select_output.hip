@@ -358,10 +358,7 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
   for (int j = 0; j < n_alpha; ++j) report->e_cand[j] = E[1 + j];
   report->sum_x2 = den;            // here: ||X W^T||^2 over the calibration batches
   report->sum_w2 = 0.0;
-  if (accepted)
-    return check_hip(hipMemcpyAsync(perm_out, W.cands + (int64_t)best * K, (size_t)K * 4, hipMemcpyDeviceToDevice, st),
-                     "copy permutation");
-  return launch_identity_order(perm_out, K, st);
+  return launch_emit_order(accepted ? W.cands + (int64_t)best * K : nullptr, perm_out, K, st);
 }
 
 }  // namespace pq

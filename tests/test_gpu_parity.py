@@ -1308,3 +1308,33 @@ def test_quantize_act_packed_where_its_shape_changes(fmt, g, M, K, pad):
                                      for M in (1, 9, 17, 57, 64, 65, 66, 135, 153, 1000, 2571)])
 def test_row_blocks_in_every_remainder_of_eight(fmt, g, M):
     test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, 192, 0)
+
+
+@pytest.mark.parametrize("K", [32, 64, 288, 1056])
+@pytest.mark.parametrize("where", ["first", "last"])
+def test_select_perm_orders_that_differ_in_one_place(K, where):
+    """The activations' and the weights' moments sort alike but for two neighbouring channels, of the first or the last
+    block: the orders of the alphas fall into two classes that differ in those two places only, and none is taken for a
+    repeat of the other."""
+    fmt, g, M, N = pq.FMT_INT4, 32, 24, 16
+    rng = np.random.default_rng(1500 + K)
+    step = np.linspace(3.0, 0.0, K)                            # log scales, at least 3 / K apart
+    at = 0 if where == "first" else K - 2
+    swapped = step.copy()
+    swapped[[at, at + 1]] = swapped[[at + 1, at]]
+    # columns of one magnitude each: the moments are the squares of the scales, up to the rounding of bf16
+    sign = lambda n: np.sign(rng.standard_normal((n, K)))
+    xb, wb = (synth.f64_to_bf16_bits(sign(n) * (1.0 + 0.5 * rng.random((n, 1))) * np.exp(4.0 * s)[None, :])
+              for n, s in ((M, step), (N, swapped)))
+    xs, w = [_to_dev(xb)], _to_dev(wb)
+    x64, w64 = OF.bf16_bits_to_f64(xb), OF.bf16_bits_to_f64(wb)
+    sa, sw, _, _ = _gpu_moments(xs, w, K)
+    perm_out = torch.empty(K, dtype=torch.int32, device=DEV)
+    rep = pq.pq_select_perm(fmt, g, sa, sw, xs, w, 1.0, 1.0, perm_out)
+    torch.cuda.synchronize()
+    ref = OC.select_permutation(fmt, g, [x64], w64)
+    assert len({tuple(p) for p in ref.cand_perms[:6]}) >= 2
+    np.testing.assert_allclose(rep.e_orig, ref.e_orig, rtol=1e-10)
+    np.testing.assert_allclose(rep.e_cand[:6], ref.e_cand[:6], rtol=1e-10)
+    assert rep.accepted == ref.accepted and rep.alpha_index == ref.alpha_index
+    np.testing.assert_array_equal(perm_out.cpu().numpy(), ref.perm)
