@@ -456,9 +456,9 @@ int pq_dynamic_tensor_scale(const void* x_bf16, int64_t M, int64_t K, int64_t ld
  *   rows_per_mod  tokens per modulation row; <= 0 means one row for all tokens
  *   eps           added to the mean square / variance under the root
  * x: bf16 [M, ld], ld >= K, ld % 8 == 0.  y: bf16 [M, ldy], ldy >= K, ldy % 8 == 0, may not overlap x.
- * K % 8 == 0 (K % 32 == 0 for the quantizing variant) and small enough for one row and the vectors
- * to be staged in a workgroup's LDS: 6 K bytes (RMS: 4 K) plus 4 bytes per INT group of a row must
- * stay below 159 KB (K <= 26000 for AdaLN), else PQ_ERR_SHAPE.
+ * K % 8 == 0 (K % 32 == 0 for the quantizing variant), and 6 K bytes (RMS: 4 K) plus 4 bytes per INT
+ * group of a row must stay below 159 KB (K <= 26000 for AdaLN): room for one row and the vectors in a
+ * workgroup's LDS; else PQ_ERR_SHAPE.
  * pq_norm_quantize_act_packed: operand as for pq_quantize_act_packed; y optional (NULL to skip;
  * ldy ignored then).  Both run on `stream` and return PQ_OK or a PQ_ERR_* code.
  */
@@ -490,7 +490,7 @@ int pq_norm_quantize_act_packed(const pq_norm_params* p, pq_format fmt, int grou
  * pq_hadamard_quantize_act_packed feeds the rounded values to the activation quantizer:
  *     == pq_quantize_act_packed(pq_hadamard_reorder(x))   bit for bit.
  * perm: int32 [K] device or NULL (identity).  x, y, ld, ldy, operand, tensor_scale as for pq_norm_reorder /
- * pq_norm_quantize_act_packed.  One fp32 row per wave is held in LDS: K <= 39000.
+ * pq_norm_quantize_act_packed.  An fp32 row must fit a workgroup's LDS: K <= 39000.
  */
 int pq_hadamard_reorder(const int32_t* perm, const void* x_bf16, int64_t M, int64_t K, int64_t ld,
                         void* y_bf16, int64_t ldy, void* stream);
