@@ -19,7 +19,7 @@
 // exchanges and the quantizer -- at four or five waves a SIMD; m = 12 and 20 leave a quarter and three eighths of the lanes idle.
 #include <math.h>
 
-#include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "pq_norm_row.h"
@@ -518,16 +518,14 @@ int launch_hadamard_team(const void* x, int64_t rows, int64_t K, int64_t ld, con
                          uint8_t* operand, const HadamardArgs& ha, hipStream_t st) {
   constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
   auto kern = hadamard_rows_kernel<FMT, G, TEAM, M, WIDE>;
-  static thread_local bool ready = false;
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNormLdsLimit);
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(hadamard_rows_kernel)");
-    ready = true;
-  }
   const int n_waves = TEAM > 1 ? TEAM : rows > 1024 ? 4 : 1;
   const int teams = TEAM == 1 ? n_waves : 1;
   const size_t shmem = (size_t)teams * (K * (M == 0 ? 4 : TEAM == 1 ? 2 : 6) + (is_int ? L.units * 4 : 0)) + (size_t)n_waves * 16;
+  static std::atomic<uint64_t> raised{0};
+  if (shmem > 48 * 1024) {
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kNormLdsLimit, raised, "hipFuncSetAttribute(hadamard_rows_kernel)"))
+      return rc;
+  }
   const int64_t groups = (rows + teams - 1) / teams;
   hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(64 * n_waves), shmem, st, (const uint16_t*)x, rows, K, ld, ts,
                      L.steps, L.units, operand ? operand + L.codes : nullptr,

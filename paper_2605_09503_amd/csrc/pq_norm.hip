@@ -21,7 +21,7 @@
 // NVFP4, 4608 x 3072, 36 MB: 14.7 us (20.4 before), RMSNorm 13.4 (16.3).
 #include <math.h>
 
-#include <algorithm>
+#include <atomic>
 
 #include "pq_norm_row.h"
 
@@ -246,21 +246,16 @@ int launch_norm_team(const void* x, int64_t rows, int64_t K, int64_t ld, const f
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
   constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
   auto kern = norm_rows_kernel<FMT, G, NORM, TEAM>;
-  // the choice depends on the shape only: remembered from the previous launch of this kernel
-  static thread_local struct { int64_t rows, K; int n_waves; } memo = {0, 0, 0};
-  if (memo.rows != rows || memo.K != K) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNormLdsLimit);
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(norm_rows_kernel)");
-    // waves that own a row each: one a workgroup spreads few rows best (RMSNorm 256 x 2048 4.9 us, four 5.4), four write
-    // more of a line together (3072 x 512 4.4 -> 4.3, LayerNorm 3072 x 2048 8.3 -> 8.0)
-    memo.n_waves = TEAM > 1 ? TEAM : rows > 1024 ? 4 : 1;
-    memo.rows = rows;
-    memo.K = K;
-  }
-  const int n_waves = memo.n_waves;
+  // waves that own a row each: one a workgroup spreads few rows best (RMSNorm 256 x 2048 4.9 us, four 5.4), four write
+  // more of a line together (3072 x 512 4.4 -> 4.3, LayerNorm 3072 x 2048 8.3 -> 8.0)
+  const int n_waves = TEAM > 1 ? TEAM : rows > 1024 && K <= 4096 ? 4 : 1;
   const int teams = TEAM == 1 ? n_waves : 1;
   const size_t shmem = norm_lds_bytes(is_int, teams, n_waves, K, L.units);
+  static std::atomic<uint64_t> raised{0};
+  if (shmem > 48 * 1024) {
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kNormLdsLimit, raised, "hipFuncSetAttribute(norm_rows_kernel)"))
+      return rc;
+  }
   const int64_t groups = (rows + teams - 1) / teams;
   hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(64 * n_waves), shmem, st, (const uint16_t*)x, rows, K, ld, ts,
                      L.steps, L.units, operand ? operand + L.codes : nullptr,
@@ -287,7 +282,8 @@ int launch_norm_rows(const void* x, int64_t rows, int64_t K, int64_t ld, const f
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
   // the widths that are taken, more than a row alone needs for the norms: K and the vectors' 2 K or 4 K bytes beside the row
   constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
-  const int team = waves_per_row(rows, K);
+  int team = waves_per_row(rows, K);
+  if (rows * 64 * team > UINT32_MAX) team = 1;               // more threads than a grid holds
   const size_t least = (size_t)K * (NORM == kNormAdaLn ? 6 : 4) + (is_int ? L.units * 4 : 0) + (size_t)(K > 4096 ? 4 : 1) * 16;
   if (least > kNormLdsLimit)
     return fail(PQ_ERR_SHAPE, "K=%lld needs %zu bytes of LDS for one row and the vectors, more than the %zu available",
