@@ -40,8 +40,13 @@ struct Ref {
   Ref& operator=(const Ref&) = delete;
 };
 
+// integers and what stands for one (__index__: numpy's integers, a tensor of one)
 int64_t as_int(PyObject* o) {
-  if (!PyLong_Check(o)) fail(PyExc_TypeError, "an integer is required");
+  if (!PyLong_Check(o)) {
+    if (!PyIndex_Check(o)) fail(PyExc_TypeError, "an integer is required");
+    Ref n(PyNumber_Index(o));
+    return as_int(n.p);
+  }
   const long long v = PyLong_AsLongLong(o);
   if (v == -1 && PyErr_Occurred()) throw PyFailed{};
   return v;

@@ -416,3 +416,41 @@ def test_calls_take_their_arguments(lib, name):
     if required[0].name in ("fmt", "kind"):
         with pytest.raises((TypeError, AttributeError)):
             f(*["1"] * len(required))
+
+
+class FakeTensor:
+    """A pointer with a shape; no call below is valid, so nothing is launched with it."""
+    shape = (8, 64)
+
+    def data_ptr(self):
+        return 0x1000
+
+    def stride(self, dim=None):
+        return 64
+
+    def numel(self):
+        return 1 << 20
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_calls_take_what_stands_for_an_integer(lib, name):
+    # sizes come from numpy and from tensors, too; groups of 48 are refused, so the call ends in the library's error, or
+    # (no GPU) in the missing stream's, and not in a TypeError
+    import inspect
+    import numpy as np
+    import torch
+    f, t = getattr(pq, name), FakeTensor()
+    sizes = {"fmt": 1, "group": 48, "M": 8, "N": 8, "K": 60, "ld": 64, "ldy": 64, "rows": 8, "kind": 0}
+    for integer in (int, np.int64, np.int32, torch.tensor):
+        args = {}
+        for p in inspect.signature(f).parameters.values():
+            if p.name in sizes:
+                args[p.name] = integer(sizes[p.name])
+            elif p.name == "eps":
+                args[p.name] = 1e-6
+            elif p.name != "rows_per_mod":
+                args[p.name] = t
+        with pytest.raises(RuntimeError):
+            f(**args)
+    with pytest.raises((TypeError, C.ArgumentError)):
+        f(**dict(args, **{"fmt" if "fmt" in args else "K": 1.0}))
