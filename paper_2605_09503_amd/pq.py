@@ -2,7 +2,8 @@
 
 Argument marshalling only: every step of the path runs inside the library's HIP kernels.
 torch tensors provide device memory and the current stream; nothing is computed here and
-there is no CPU fallback -- if the library cannot be loaded the first call raises.
+there is no CPU fallback -- if the library cannot be loaded the first call raises.  Importing this module loads the
+library where it is built (host code only: the GPU is not touched).
 Functions carry the names of the C entry points.
 """
 from __future__ import annotations
@@ -11,6 +12,7 @@ import ctypes as C
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
@@ -53,13 +55,23 @@ def lib_path() -> str:
 
 
 def load():
-    """Load libpermuquant.so (built in-tree by paper_2605_09503_amd.build). Raises if missing."""
+    """Load libpermuquant.so (built in-tree by paper_2605_09503_amd.build). Raises if it is missing or another version's."""
     global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise PQError(-100, "library not built: %s (run python -m paper_2605_09503_amd.build)" % _LIB_PATH)
-    lib = C.CDLL(_LIB_PATH)
+    try:
+        lib = C.CDLL(_LIB_PATH)
+        _declare(lib)
+    except (OSError, AttributeError) as e:
+        raise PQError(-100, "library not usable: %s (run python -m paper_2605_09503_amd.build)" % e) from e
+    _lib = lib
+    _bind_calls()
+    return lib
+
+
+def _declare(lib):
     vp, i64, i32, sz = C.c_void_p, C.c_int64, C.c_int, C.c_size_t
     lib.pq_last_error.restype = C.c_char_p
     lib.pq_last_error.argtypes = []
@@ -120,8 +132,6 @@ def load():
                  "pq_probe_mfma", "pq_pack_operand", "pq_qgemm_packed", "pq_qgemm_packed_f32",
                  "pq_quantize_act_packed"):
         getattr(lib, name).restype = i32
-    _lib = lib
-    return lib
 
 
 def _check(rc: int):
@@ -145,12 +155,13 @@ def _stream():
 
 
 # ------------------------------------------------------------------------ the calls of a forward pass
-# pq_quantize_act, pq_quantize_act_packed, pq_norm_quantize_act_packed, pq_hadamard_quantize_act_packed, pq_qgemm,
-# pq_qgemm_packed, pq_qgemm_packed_f32, pq_qgemm_packed_bias and pq_calib_moments are marshalled by the module
-# _pq_calls (csrc/pq_calls.cpp, where their signatures are): a wrapper here and ctypes cost 2 us of the 5 a call took.
+# A wrapper here and ctypes cost 2 us of the 5 that a call takes, so these are marshalled by the module _pq_calls
+# (csrc/pq_calls.cpp): it takes the place of the functions of these names below, which do the same and serve where the module
+# is not built (it needs a host compiler and the interpreter's headers) or was built for another torch.
 _CALLS = ("pq_quantize_act", "pq_quantize_act_packed", "pq_norm_quantize_act_packed", "pq_hadamard_quantize_act_packed",
           "pq_qgemm", "pq_qgemm_packed", "pq_qgemm_packed_f32", "pq_qgemm_packed_bias", "pq_calib_moments")
 _CALLS_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_pq_calls.so")
+_calls = None           # the module, or False where it cannot be had
 
 
 def _raise(rc: int):
@@ -166,26 +177,25 @@ def _new_workspace(op: int, fmt: int, group: int, M: int, N: int, K: int, n_batc
 
 
 def _bind_calls():
-    load()
-    if not os.path.exists(_CALLS_PATH):
-        raise PQError(-100, "binding not built: %s (run python -m paper_2605_09503_amd.build)" % _CALLS_PATH)
-    loader = importlib.machinery.ExtensionFileLoader("_pq_calls", _CALLS_PATH)
-    calls = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pq_calls", loader))
-    loader.exec_module(calls)
-    calls.bind(_raise, _new_operand, _new_workspace)
-    globals().update((name, getattr(calls, name)) for name in _CALLS)
-
-
-def _unbound(name: str):
-    def call(*args, **kwargs):
-        _bind_calls()
-        return globals()[name](*args, **kwargs)
-    call.__name__ = call.__qualname__ = name
-    return call
-
-
-# Bound when this module is imported; where nothing is built yet, at the first call (which raises if still nothing is).
-globals().update((name, _unbound(name)) for name in _CALLS)
+    """Puts _pq_calls in place of the functions of its names, once; without it they stay and a warning says so."""
+    global _calls
+    if _calls is not None:
+        return
+    _calls = False
+    try:
+        if not os.path.exists(_CALLS_PATH):
+            raise ImportError("not built: " + _CALLS_PATH)
+        loader = importlib.machinery.ExtensionFileLoader("_pq_calls", _CALLS_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pq_calls", loader))
+        loader.exec_module(module)
+        module.bind(_raise, _new_operand, _new_workspace)
+        bound = {name: getattr(module, name) for name in _CALLS}
+    except (ImportError, AttributeError, OSError) as e:
+        warnings.warn("the native binding of the hot calls cannot be used, ctypes takes 2 us more a call (%s); build it with "
+                      "python -m paper_2605_09503_amd.build" % e, RuntimeWarning)
+        return
+    _calls = module
+    globals().update(bound)
 
 
 def pq_last_error() -> str:
@@ -204,6 +214,19 @@ def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:
     if nbytes == 0:
         return None
     return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def pq_calib_moments(x: torch.Tensor, sumsq: torch.Tensor, absmax: Optional[torch.Tensor] = None,
+                     workspace: Optional[torch.Tensor] = None, rows: Optional[int] = None,
+                     K: Optional[int] = None, ld: Optional[int] = None) -> None:
+    """sumsq[K] (float64, in/out) += column sums of squares of bf16 x[rows, ld]."""
+    rows = x.shape[0] if rows is None else rows
+    K = x.shape[1] if K is None else K
+    ld = x.stride(0) if ld is None else ld
+    if workspace is None:
+        workspace = _workspace(pq_workspace_bytes(OP_CALIB_MOMENTS, 0, 0, rows, 0, K, 1), x.device)
+    _check(load().pq_calib_moments(_ptr(x), rows, K, ld, _ptr(sumsq), _ptr(absmax), _ptr(workspace),
+                                   0 if workspace is None else workspace.numel(), _stream()))
 
 
 STATIC_SCRATCH_BYTES = 3 << 20      # PQ_STATIC_SCRATCH_BYTES of the header
@@ -319,6 +342,16 @@ def pq_quantize_weights(fmt: int, group: int, w: torch.Tensor, perm: Optional[to
                                       _ptr(tensor_scale_out), _stream()))
 
 
+def pq_quantize_act(fmt: int, group: int, x: torch.Tensor, perm: Optional[torch.Tensor],
+                    tensor_scale: Optional[torch.Tensor], codes: torch.Tensor, scales: torch.Tensor,
+                    M: Optional[int] = None, K: Optional[int] = None, ld: Optional[int] = None) -> None:
+    M = x.shape[0] if M is None else M
+    K = x.shape[1] if K is None else K
+    ld = x.stride(0) if ld is None else ld
+    _check(load().pq_quantize_act(fmt, group, _ptr(x), M, K, ld, _ptr(perm), _ptr(tensor_scale),
+                                  _ptr(codes), _ptr(scales), _stream()))
+
+
 def _gemm(fn, fmt, group, a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, y, workspace, M, N, K, ldy):
     M = a_codes.shape[0] if M is None else M
     K = a_codes.shape[1] * 2 if K is None else K
@@ -329,6 +362,14 @@ def _gemm(fn, fmt, group, a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, y, w
     _check(fn(fmt, group, _ptr(a_codes), _ptr(a_scales), _ptr(a_ts), _ptr(w_codes), _ptr(w_scales),
               _ptr(w_ts), M, N, K, _ptr(y), ldy, _ptr(workspace),
               0 if workspace is None else workspace.numel(), _stream()))
+
+
+def pq_qgemm(fmt: int, group: int, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
+             w_tensor_scale, y: torch.Tensor, workspace: Optional[torch.Tensor] = None,
+             M=None, N=None, K=None, ldy=None) -> None:
+    """y[M, N] (bf16) = dequant(A) @ dequant(W)^T."""
+    _gemm(load().pq_qgemm, fmt, group, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
+          w_tensor_scale, y, workspace, M, N, K, ldy)
 
 
 def pq_qgemm_prep(fmt: int, group: int, a_scales, w_scales, M: int, N: int, K: int,
@@ -410,6 +451,19 @@ def pq_pack_operand_int3(group: int, dense: torch.Tensor, scales: torch.Tensor, 
     return operand
 
 
+def pq_quantize_act_packed(fmt: int, group: int, x: torch.Tensor, tensor_scale: Optional[torch.Tensor],
+                           operand: Optional[torch.Tensor] = None, codes: Optional[torch.Tensor] = None,
+                           scales: Optional[torch.Tensor] = None, K: Optional[int] = None) -> torch.Tensor:
+    """Dynamic activation quantization straight into the GEMM's panel layout."""
+    M = x.shape[0]
+    K = x.shape[1] if K is None else K
+    if operand is None:
+        operand = _new_operand(fmt, group, M, K, x)
+    _check(load().pq_quantize_act_packed(fmt, group, _ptr(x), M, K, x.stride(0), _ptr(tensor_scale),
+                                         _ptr(operand), operand.numel(), _ptr(codes), _ptr(scales), _stream()))
+    return operand
+
+
 def pq_calib_channel_stats(x: torch.Tensor, total: Optional[torch.Tensor], absmax: Optional[torch.Tensor],
                            K: Optional[int] = None, workspace: Optional[torch.Tensor] = None) -> None:
     """Per channel: sum (fp64, accumulated into `total`) and largest magnitude (fp32, max into `absmax`)."""
@@ -481,6 +535,24 @@ def pq_norm_reorder(kind: int, x: torch.Tensor, eps: float, perm: Optional[torch
     return y
 
 
+def pq_norm_quantize_act_packed(kind: int, fmt: int, group: int, x: torch.Tensor, eps: float,
+                                tensor_scale: Optional[torch.Tensor], perm: Optional[torch.Tensor] = None,
+                                gamma: Optional[torch.Tensor] = None, mod_scale: Optional[torch.Tensor] = None,
+                                mod_shift: Optional[torch.Tensor] = None, rows_per_mod: int = 0,
+                                operand: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None,
+                                K: Optional[int] = None) -> torch.Tensor:
+    """pq_norm_reorder feeding the activation quantizer directly: returns the GEMM operand."""
+    M = x.shape[0]
+    K = x.shape[1] if K is None else K
+    if operand is None:
+        operand = _new_operand(fmt, group, M, K, x)
+    p = _norm_params(kind, perm, gamma, mod_scale, mod_shift, rows_per_mod, eps)
+    _check(load().pq_norm_quantize_act_packed(C.byref(p), fmt, group, _ptr(x), M, K, x.stride(0),
+                                              _ptr(tensor_scale), _ptr(operand), operand.numel(), _ptr(y),
+                                              0 if y is None else y.stride(0), _stream()))
+    return operand
+
+
 def pq_hadamard_reorder(x: torch.Tensor, perm: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None,
                         K: Optional[int] = None) -> torch.Tensor:
     """x H with the columns of the result in the order `perm` (bf16 [M, K])."""
@@ -490,6 +562,47 @@ def pq_hadamard_reorder(x: torch.Tensor, perm: Optional[torch.Tensor] = None, y:
         y = torch.empty((M, K), dtype=torch.bfloat16, device=x.device)
     _check(load().pq_hadamard_reorder(_ptr(perm), _ptr(x), M, K, x.stride(0), _ptr(y), y.stride(0), _stream()))
     return y
+
+
+def pq_hadamard_quantize_act_packed(fmt: int, group: int, x: torch.Tensor, tensor_scale: Optional[torch.Tensor],
+                                    perm: Optional[torch.Tensor] = None, operand: Optional[torch.Tensor] = None,
+                                    y: Optional[torch.Tensor] = None, K: Optional[int] = None) -> torch.Tensor:
+    """The rotation feeding the activation quantizer directly: returns the GEMM operand."""
+    M = x.shape[0]
+    K = x.shape[1] if K is None else K
+    if operand is None:
+        operand = _new_operand(fmt, group, M, K, x)
+    _check(load().pq_hadamard_quantize_act_packed(_ptr(perm), fmt, group, _ptr(x), M, K, x.stride(0),
+                                                  _ptr(tensor_scale), _ptr(operand), operand.numel(), _ptr(y),
+                                                  0 if y is None else y.stride(0), _stream()))
+    return operand
+
+
+def _gemm_packed(fn, fmt, group, a_operand, a_ts, w_operand, w_ts, y, M, N, K, ldy):
+    _check(fn(fmt, group, _ptr(a_operand), _ptr(a_ts), _ptr(w_operand), _ptr(w_ts), M, N, K, _ptr(y),
+              y.stride(0) if ldy is None else ldy, _stream()))
+
+
+def pq_qgemm_packed(fmt: int, group: int, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
+                    y: torch.Tensor, M: int, N: int, K: int, ldy=None) -> None:
+    """y[M, N] (bf16) = the product of two packed operands."""
+    _gemm_packed(load().pq_qgemm_packed, fmt, group, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
+                 y, M, N, K, ldy)
+
+
+def pq_qgemm_packed_bias(fmt: int, group: int, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
+                         bias: torch.Tensor, y: torch.Tensor, M: int, N: int, K: int, ldy=None) -> None:
+    """The packed product plus the layer's bias (bf16 [N]), added before the rounding to bf16."""
+    _check(load().pq_qgemm_packed_bias(fmt, group, _ptr(a_operand), _ptr(a_tensor_scale), _ptr(w_operand),
+                                       _ptr(w_tensor_scale), M, N, K, _ptr(bias), _ptr(y),
+                                       y.stride(0) if ldy is None else ldy, _stream()))
+
+
+def pq_qgemm_packed_f32(fmt: int, group: int, a_operand, a_tensor_scale, w_operand, w_tensor_scale,
+                        y: torch.Tensor, M: int, N: int, K: int, ldy=None) -> None:
+    """The packed product in fp32, before the rounding to bf16."""
+    _gemm_packed(load().pq_qgemm_packed_f32, fmt, group, a_operand, a_tensor_scale, w_operand,
+                 w_tensor_scale, y, M, N, K, ldy)
 
 
 def pq_probe_stream(src: torch.Tensor, read_bytes: int, dst: torch.Tensor, write_bytes: int) -> None:
@@ -541,5 +654,9 @@ def bf16_from_bits(bits_u16, device="cuda") -> torch.Tensor:
     return t.to(device).view(torch.bfloat16)
 
 
-if os.path.exists(_LIB_PATH) and os.path.exists(_CALLS_PATH):
-    _bind_calls()
+# at import, so that names imported from here are the native ones; a library that cannot be loaded raises where it is used
+if os.path.exists(_LIB_PATH):
+    try:
+        load()
+    except PQError:
+        pass

@@ -16,9 +16,11 @@ PQ_ERR_NULL, PQ_ERR_SHAPE, PQ_ERR_FORMAT, PQ_ERR_WORKSPACE = -1, -2, -3, -4
 
 @pytest.fixture(scope="module")
 def lib():
-    if not os.path.exists(pq.lib_path()):
-        from paper_2605_09503_amd import build
+    from paper_2605_09503_amd import build
+    if not os.path.exists(pq.lib_path()) or not os.path.exists(build.CALLS):
         build.build(verbose=False)
+        pq._calls = None
+        pq._bind_calls()
     return pq.load()
 
 
@@ -454,3 +456,86 @@ def test_calls_take_what_stands_for_an_integer(lib, name):
             f(**args)
     with pytest.raises((TypeError, C.ArgumentError)):
         f(**dict(args, **{"fmt" if "fmt" in args else "K": 1.0}))
+
+
+# what a program sees where the library or the native binding is missing or unusable: run in a process of its own, on a
+# copy of the package whose lib/ holds the given files
+BARE = r"""
+import inspect, os, shutil, sys, warnings
+caught = []
+warnings.showwarning = lambda m, *a, **k: caught.append(str(m))
+from paper_2605_09503_amd.pq import pq_qgemm_packed as early, pq_calib_moments as early_moments
+from paper_2605_09503_amd import pq
+state, built = sys.argv[1], sys.argv[2]
+pq._stream = lambda: None
+class Fake:
+    shape = (8, 64)
+    def data_ptr(self): return 0x1000
+    def stride(self, dim=None): return 64
+    def numel(self): return 1 << 20
+t = Fake()
+def error(f, *args, **kw):
+    try:
+        f(*args, **kw)
+    except pq.PQError as e:
+        return str(e)
+    raise AssertionError("no error")
+def refused():
+    assert "group 32, 64" in error(early, 1, 48, t, None, t, None, t, 8, 8, 64)
+    assert "group 32, 64" in error(pq.pq_qgemm_packed, 1, 48, t, None, t, None, t, 8, 8, 64)
+    assert "group 32, 64" in error(pq.pq_qgemm_packed_f32, 1, 48, t, None, t, None, t, M=8, N=8, K=64, ldy=64)
+    assert "group 32, 64" in error(pq.pq_qgemm_packed_bias, 1, 48, t, None, t, None, t, t, 8, 8, 64)
+    assert "group 32, 64" in error(pq.pq_qgemm, 1, 48, t, t, None, t, t, None, t, workspace=t)
+    assert "group 32, 64" in error(pq.pq_quantize_act, 1, 48, t, None, None, t, t)
+    assert "group 32, 64" in error(pq.pq_quantize_act_packed, 1, 48, t, None, operand=t)
+    assert "group 32, 64" in error(pq.pq_norm_quantize_act_packed, 0, 1, 48, t, 1e-6, None, operand=t)
+    assert "group 32, 64" in error(pq.pq_hadamard_quantize_act_packed, 1, 48, t, None, operand=t)
+    assert "multiples of 8" in error(early_moments, t, t, workspace=t, K=60)
+lib = os.path.dirname(pq.lib_path())
+if state in ("no binding", "foreign binding"):
+    assert len(caught) == 1 and "paper_2605_09503_amd.build" in caught[0], caught
+    assert inspect.isfunction(pq.pq_qgemm)
+    refused()
+elif state == "foreign library":
+    assert "paper_2605_09503_amd.build" in error(early, 1, 48, t, None, t, None, t, 8, 8, 64)
+    assert "paper_2605_09503_amd.build" in error(pq.load)
+else:
+    assert state == "nothing" and "not built" in error(early, 1, 48, t, None, t, None, t, 8, 8, 64)
+    for f in ("libpermuquant.so", "_pq_calls.so"):
+        shutil.copy(os.path.join(built, f), lib)
+    assert "group 32, 64" in error(early, 1, 48, t, None, t, None, t, 8, 8, 64)
+    native = pq.pq_qgemm_packed
+    assert inspect.isbuiltin(native) and not caught
+    assert "group 32, 64" in error(early, 1, 48, t, None, t, None, t, 8, 8, 64)
+    assert pq.pq_qgemm_packed is native
+names = sys.argv[3:]
+assert len(names) == 9
+for n in names:
+    print(n, ", ".join(str(p.replace(annotation=p.empty)) for p in inspect.signature(getattr(pq, n)).parameters.values()), sep="|")
+"""
+
+
+@pytest.mark.parametrize("state", ["no binding", "foreign binding", "foreign library", "nothing"])
+def test_calls_without_the_native_binding(lib, tmp_path, state):
+    import shutil
+    import subprocess
+    import sys
+    pkg, built = tmp_path / "paper_2605_09503_amd", os.path.dirname(pq.lib_path())
+    (pkg / "lib").mkdir(parents=True)
+    for f in ("__init__.py", "pq.py"):
+        shutil.copy(os.path.join(os.path.dirname(pq.__file__), f), pkg)
+    if state in ("no binding", "foreign binding"):
+        shutil.copy(os.path.join(built, "libpermuquant.so"), pkg / "lib")
+    if state == "foreign binding":
+        (pkg / "lib" / "_pq_calls.so").write_bytes(b"not a module")
+    if state == "foreign library":
+        gcc = shutil.which("gcc")
+        if gcc is None:
+            pytest.skip("no C compiler")
+        (tmp_path / "old.c").write_text("int pq_version(void) { return 1; }\n")
+        subprocess.run([gcc, "-shared", "-fPIC", "-o", str(pkg / "lib" / "libpermuquant.so"), str(tmp_path / "old.c")], check=True)
+    r = subprocess.run([sys.executable, "-c", BARE, state, built] + sorted(CALLS), cwd=tmp_path, capture_output=True, text=True,
+                       env=dict(os.environ, PYTHONPATH=str(tmp_path)), timeout=240)
+    assert r.returncode == 0, r.stdout + r.stderr
+    # the same parameters as the native ones
+    assert dict(line.split("|") for line in r.stdout.split("\n") if "|" in line) == {n: s[1:-1] for n, s in CALLS.items()}

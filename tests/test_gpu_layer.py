@@ -289,3 +289,61 @@ def test_calls_by_position_by_name_and_on_another_stream(fmt, g, wrap):
     assert e.value.code == -2 and "ldy" in str(e.value)
     with pytest.raises(IndexError):
         pq.pq_quantize_act_packed(fmt, g, bias, tx)
+
+
+def _plain_binding(tmp_path):
+    """pq.py beside the library alone: its nine hot calls go through ctypes."""
+    import importlib.util
+    import os
+    import shutil
+    (tmp_path / "lib").mkdir()
+    os.symlink(pq.lib_path(), tmp_path / "lib" / "libpermuquant.so")
+    shutil.copy(pq.__file__, tmp_path / "plain_pq.py")
+    spec = importlib.util.spec_from_file_location("plain_pq", tmp_path / "plain_pq.py")
+    mod = importlib.util.module_from_spec(spec)
+    sys.modules["plain_pq"] = mod                        # dataclasses look their module up
+    try:
+        with pytest.warns(RuntimeWarning, match="native binding"):
+            spec.loader.exec_module(mod)
+    finally:
+        del sys.modules["plain_pq"]
+    return mod
+
+
+@pytest.mark.parametrize("fmt,g", [(pq.FMT_NVFP4, 16), (pq.FMT_INT4, 64)])
+def test_calls_without_the_native_binding_give_the_same(tmp_path, fmt, g):
+    import inspect
+    plain = _plain_binding(tmp_path)
+    assert inspect.isbuiltin(pq.pq_qgemm) and inspect.isfunction(plain.pq_qgemm)
+    M, N, K = 33, 72, 192
+    out = []
+    for mod, integer in ((pq, int), (pq, np.int64), (plain, int), (plain, np.int64)):
+        gen = torch.Generator(device=DEV)
+        gen.manual_seed(5)
+        rnd = lambda *s: torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16)
+        x, w, bias, gamma = rnd(M, K), rnd(N, K), rnd(N), rnd(K)
+        tx, tw = torch.full((1,), 0.002, device=DEV), torch.empty(1, device=DEV)
+        wc, ws = pq.alloc_quantized(fmt, g, N, K, DEV)
+        pq.pq_quantize_weights(fmt, g, w, None, wc, ws, tw)
+        wo = pq.pq_pack_operand(fmt, g, wc, ws)
+        ac, asc = pq.alloc_quantized(fmt, g, M, K, DEV)
+        y, yp, yb = (torch.empty((M, N), dtype=torch.bfloat16, device=DEV) for _ in range(3))
+        yf = torch.empty((M, N), dtype=torch.float32, device=DEV)
+        sums = torch.zeros(K, dtype=torch.float64, device=DEV)
+        fi, gi, m, n, k = (integer(v) for v in (fmt, g, M, N, K))
+        mod.pq_quantize_act(fi, gi, x, None, tx, ac, asc, M=m, K=k, ld=k)
+        a, norm, had = (torch.zeros(pq.pq_operand_bytes(fmt, g, M, K), dtype=torch.uint8, device=DEV) for _ in range(3))
+        assert mod.pq_quantize_act_packed(fi, gi, x, tx).numel() == a.numel()
+        assert mod.pq_quantize_act_packed(fi, gi, x, tx, operand=a, K=k) is a
+        mod.pq_norm_quantize_act_packed(integer(pq.NORM_RMS), fi, gi, x, 1e-6, tx, gamma=gamma, rows_per_mod=m, operand=norm, K=k)
+        mod.pq_hadamard_quantize_act_packed(fi, gi, x, tx, operand=had, K=k)
+        mod.pq_qgemm(fi, gi, ac, asc, tx, wc, ws, tw, y, M=m, N=n, K=k, ldy=n)
+        mod.pq_qgemm_packed(fi, gi, a, tx, wo, tw, yp, m, n, k, ldy=n)
+        mod.pq_qgemm_packed_f32(fi, gi, a, tx, wo, tw, yf, m, n, k)
+        mod.pq_qgemm_packed_bias(fi, gi, a, tx, wo, tw, bias, yb, m, n, k)
+        mod.pq_calib_moments(x, sums, rows=m, K=k, ld=k)
+        torch.cuda.synchronize()
+        out.append((ac, asc, a, norm, had, y, yp, yf, yb, sums))
+    for other in out[1:]:
+        for u, v in zip(out[0], other):
+            assert torch.equal(u, v)
