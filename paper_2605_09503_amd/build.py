@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -48,11 +49,24 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _build_calls() -> None:
-    import torch
+def _build_calls() -> bool:
+    """The binding; False, with a message, where what it is built with is missing: the library stands without it."""
+    cxx, headers = os.environ.get("CXX", "g++"), sysconfig.get_paths()["include"]
+    try:
+        import torch
+    except ImportError:
+        torch = None
+    missing = ("torch" if torch is None else
+               "a host compiler (%s)" % cxx if shutil.which(cxx) is None else
+               "the interpreter's headers (%s)" % headers if not os.path.exists(os.path.join(headers, "Python.h")) else None)
+    if missing:
+        if os.path.exists(CALLS):
+            os.remove(CALLS)                 # one of another build
+        sys.stderr.write("binding of the hot calls not built, %s is missing: %s goes without it\n" % (missing, LIB))
+        return False
     root = os.path.dirname(torch.__file__)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-I", headers, "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
            os.path.join(CSRC, "pq_calls.cpp"), "-o", CALLS, "-Wall", "-L", LIBDIR, "-lpermuquant", "-Wl,-rpath,$ORIGIN",
@@ -60,6 +74,7 @@ def _build_calls() -> None:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("building the binding failed:\n%s\n%s" % (r.stdout, r.stderr))
+    return True
 
 
 def build(verbose: bool = True) -> str:

@@ -539,3 +539,20 @@ def test_calls_without_the_native_binding(lib, tmp_path, state):
     assert r.returncode == 0, r.stdout + r.stderr
     # the same parameters as the native ones
     assert dict(line.split("|") for line in r.stdout.split("\n") if "|" in line) == {n: s[1:-1] for n, s in CALLS.items()}
+
+
+@pytest.mark.parametrize("missing", ["compiler", "headers", "torch"])
+def test_library_stands_where_the_binding_cannot_be_built(monkeypatch, capsys, tmp_path, missing):
+    import sys
+    from paper_2605_09503_amd import build
+    stale = tmp_path / "_pq_calls.so"
+    stale.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(build, "CALLS", str(stale))
+    if missing == "compiler":
+        monkeypatch.setenv("CXX", "/nonexistent/c++")
+    elif missing == "headers":
+        monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    else:
+        monkeypatch.setitem(sys.modules, "torch", None)
+    assert build._build_calls() is False
+    assert missing in capsys.readouterr().err and not stale.exists()
