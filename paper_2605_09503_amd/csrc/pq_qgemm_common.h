@@ -468,7 +468,8 @@ int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const Ope
 // tiles (= workgroups) of that launch
 int64_t qgemm_tiles(int tile, int64_t M, int64_t N);
 // output tiles of the product kernels (choose_tile in pq_qgemm_tile.hip)
-enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kTileSplit64x32 = 5, kTileSplit64 = 6, kTileSplit64x96 = 7 };
+enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kTileSplit64x32 = 5, kTileSplit64 = 6, kTileSplit64x96 = 7,
+                  kTileSplit64Eight = 8, kTileSplit64x96Eight = 9 };     // the same two with eight waves
 // small outputs (pq_qgemm_split.hip)
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Output& out, int tile, hipStream_t st);

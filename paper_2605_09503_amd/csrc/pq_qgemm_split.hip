@@ -13,7 +13,7 @@
 // in part only, see pq_qgemm_group.hip): a 64 x 96 tile unpacks five fragments for six 32 x 32 x 64 products, 1.5 times what
 // a staged 128 x 128 tile unpacks, but its four-wave workgroups need no barrier and run two to a compute unit.  Where there
 // is a second workgroup, four waves and not eight share a 64 x 96 tile because it then covers the first one's ends
-// (NVFP4 512 x 9216 x 3072: 32 us, with eight waves 42); where there is none see split_eight_waves.  Kernel alone, us, before -> now:
+// (NVFP4 512 x 9216 x 3072: 32 us, with eight waves 42); where there is none see choose_tile.  Kernel alone, us, before -> now:
 //   NVFP4     256 x 512 x 512     9.4 ->  3.9     512 x 3072 x 3072   30 -> 15      512 x 3072 x 12288  104 -> 43
 //   NVFP4     512 x 9216 x 3072    44 -> 32       64 x 12288 x 3072   29 -> 11      16 x 512 x 12288    103 -> 13
 //   INT4 g128  77 x 1000 x 1152  15.3 ->  4.5     INT4 g64   1024 x 3072 x 3072  33 -> 27
@@ -463,26 +463,16 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
   return launch_split<MODE, TM, TN, KS, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
 }
 
-// Whether eight waves and not four share a tile of 64 x 64 or 64 x 96: where no unit has a second workgroup to run beside
-// the first, and each wave has a few steps.  A wave issues a vector instruction every five cycles at most, so one wave a SIMD
-// leaves half of the vector unit idle and two do not.  Over 90 shapes of 130 to 256 tiles, eight against four: 20 steps
-// of K and fewer 1.00 to 1.10 of the time, 21 to 25 0.95 to 1.00, 30 to 60 0.87 to 0.98, more 0.83 to 0.95 (NVFP4 405 x 1549 x
-// 2688 11.6 -> 10.4 us, 98 x 9115 x 10112 37.6 -> 31.6, INT3 g64 512 x 3072 x 3072 14.9 -> 13.8).  With 512 and 768 tiles
-// 1.15: the second workgroup covers the first one's ends.  Sixteen waves for the smaller tiles: 0.96 to 1.23.
-static bool split_eight_waves(int64_t n_tiles, int K) { return n_tiles <= 256 && K > 21 * kBK; }
-
 template <int MODE, int OUT, int WIDE>
 static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
                       int tile, hipStream_t st) {
-  if (tile >= kTileSplit64 && split_eight_waves(qgemm_tiles(tile, M, N) * out.problems, K)) {
-    // no more than 256 tiles: row-major operands are read directly, see rows_through_lds
-    if (tile == kTileSplit64) return launch_split<MODE, 2, 2, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
-    return launch_split<MODE, 2, 3, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
-  }
   switch (tile) {
     case kTileSplit32: return split_loader<MODE, 1, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
     case kTileSplit64x32: return split_loader<MODE, 2, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
     case kTileSplit64: return split_loader<MODE, 2, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    // no more than 256 tiles: row-major operands are read directly, see rows_through_lds
+    case kTileSplit64Eight: return launch_split<MODE, 2, 2, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64x96Eight: return launch_split<MODE, 2, 3, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
     default: return split_loader<MODE, 2, 3, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
   }
 }

@@ -24,7 +24,7 @@ struct TileCost {
 struct TileSize {
   int bm, bn;
 };
-static constexpr TileSize kTileSize[] = {{0, 0}, {256, 256}, {128, 128}, {224, 256}, {32, 32}, {64, 32}, {64, 64}, {64, 96}};
+static constexpr TileSize kTileSize[] = {{0, 0}, {256, 256}, {128, 128}, {224, 256}, {32, 32}, {64, 32}, {64, 64}, {64, 96}, {64, 64}, {64, 96}};
 // rows: NVFP4; INT4 and INT3 with groups of 32; INT4 with larger groups; INT3 with larger groups.  Columns: the tiles in
 // the order of their numbers.
 static constexpr TileCost kTileCost[4][8] = {
@@ -42,6 +42,15 @@ static constexpr TileCost kTileCost[4][8] = {
      {2.32f, 0.1103f, 4.02f, 0.176f, 0.698f, 0.038f}},
 };
 
+// Whether eight waves and not four share a tile of 64 x 64 or 64 x 96: where no unit has a second workgroup to run beside
+// the first, and each wave has a few steps.  A wave issues a vector instruction every five cycles at most, so one wave a SIMD
+// leaves half of the vector unit idle and two do not.  Over 90 shapes of 130 to 256 tiles, eight against four: 20 steps
+// of K and fewer 1.00 to 1.10 of the time, 21 to 25 0.95 to 1.00, 30 to 60 0.87 to 0.98, more 0.83 to 0.95 (NVFP4 405 x 1549 x
+// 2688 11.6 -> 10.4 us, 98 x 9115 x 10112 37.6 -> 31.6, INT3 g64 512 x 3072 x 3072 14.9 -> 13.8).  With 512 and 768 tiles
+// 1.15: the second workgroup covers the first one's ends.  Sixteen waves for the smaller tiles: 0.96 to 1.23.
+static bool split_eight_waves(int64_t n_tiles, int64_t K) { return n_tiles <= 256 && K > 21 * kBK; }
+
+// A call of several launches takes one choice for all of them: the tile and its waves fix the order of the sums over K.
 int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int problems) {
   const int cls = fmt == PQ_FMT_NVFP4 ? 0 : group == 32 ? 1 : fmt == PQ_FMT_INT4 ? 2 : 3;
   const float s = (float)((K + kBK - 1) / kBK), past = (float)(N % 8);
@@ -59,6 +68,9 @@ int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int p
       best = t;
       best_t = time;
     }
+  }
+  if (best == kTileSplit64 || best == kTileSplit64x96) {
+    if (split_eight_waves(qgemm_tiles(best, M, N) * problems, K)) best = best == kTileSplit64 ? kTileSplit64Eight : kTileSplit64x96Eight;
   }
   return best;
 }

@@ -308,8 +308,8 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
   if ((rc = check_hip(hipGetLastError(), "ref_gemm_kernel"))) return rc;
 
   const int64_t most_rows = stack * M;
-  // One tile for the whole call, that of a full launch: a last launch of fewer batches or orders adds its sums to
-  // the first slots of the same ones.
+  // One tile and number of waves for the whole call, those of a full launch: a last launch of fewer batches adds its sums
+  // to the first slots of the same ones, and equal orders have equal sums whichever launch takes them.
   const int tile = choose_tile(fmt, group, most_rows, N, K, orders);
   const size_t num_stride = out_tiles(stack * M, N);
   const size_t w_next = operand_bytes(fmt, group, N, K);

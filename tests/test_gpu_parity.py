@@ -463,6 +463,26 @@ def test_output_error_in_several_launches(fmt, g, M, N, K, nb, n_alpha):
         assert torch.equal(got[0][1], got[2][1])
 
 
+@pytest.mark.parametrize("fmt,g,M,N,K,n_alpha", [
+    # 13 orders share a launch, the last is alone in the second: 3198 tiles of 64 x 64 and 246, K of more than 21 steps
+    (pq.FMT_NVFP4, 16, 7846, 33, 1536, 13),
+    (pq.FMT_INT4, 64, 7849, 39, 1408, 13),
+    (pq.FMT_INT4, 256, 7673, 46, 1536, 13),
+])
+def test_output_error_of_equal_orders_in_launches_of_different_size(fmt, g, M, N, K, n_alpha):
+    # ties go to the smallest alpha: the same order has the same error to the last bit whichever launch takes it
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3 + K)
+    xs = [torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
+    w = (0.02 * torch.randn((N, K), generator=gen, device=DEV)).to(torch.bfloat16)
+    sa = sum(x.double().square().sum(0) for x in xs)
+    sw = w.double().square().sum(0)
+    ts = [float(max(float(t.abs().max()) for t in ts_of) / 2688.0) for ts_of in (xs, [w])]
+    perm = torch.empty(K, dtype=torch.int32, device=DEV)
+    rep = pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, ts[0], ts[1], perm, alphas=(0.5,) * n_alpha, tau=-1e30)
+    assert len(set(rep.e_cand)) == 1 and rep.alpha_index == 0
+
+
 def test_select_perm_candidates_and_ties():
     # equal second moments: the sort must keep ascending channel index (stable)
     K, M, N = 256, 32, 32
