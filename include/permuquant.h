@@ -221,6 +221,19 @@ int pq_select_perm_output_error(pq_format fmt, int group, const double* act_sums
                                 pq_select_report* report, void* workspace, size_t workspace_bytes,
                                 void* stream);
 
+/* How a call of pq_select_perm_output_error with such a workspace is cut into launches: the batches that stand one below
+ * the other as the rows of one product, the orders (the original one and the candidates) that share a launch, and the
+ * output tile of the product with the waves of its workgroups, one choice for the call.  Host only; PQ_ERR_WORKSPACE for a
+ * workspace that the call would refuse.                                                                              */
+typedef struct {
+  int batches;
+  int orders;
+  int tile_m, tile_n;            /* as pq_qgemm_tile */
+  int tile_waves;
+} pq_output_plan;
+int pq_select_output_plan(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, int n_alpha,
+                          size_t workspace_bytes, pq_output_plan* plan);
+
 /*
  * Squared quantization error of one tensor in a given channel order (paper Eq. 3 on a finite
  * sample; the building block of E above, also what "quantization error with / without the

@@ -338,6 +338,22 @@ int pq_qgemm_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int
   return PQ_OK;
 }
 
+int pq_select_output_plan(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, int n_alpha,
+                          size_t workspace_bytes, pq_output_plan* plan) {
+  if (!plan) return fail(PQ_ERR_NULL, "pq_select_output_plan: plan is NULL");
+  int rc = check_format(fmt, group, K);
+  if (rc) return rc;
+  if (M <= 0 || N <= 0 || M > (1 << 24) || N > (1 << 24) || K % 32 || K > 65536 || n_batches <= 0 || n_alpha <= 0 ||
+      n_alpha > PQ_MAX_ALPHAS)
+    return fail(PQ_ERR_SHAPE, "pq_select_output_plan: no selection of M=%lld N=%lld K=%lld n_batches=%d n_alpha=%d", (long long)M,
+                (long long)N, (long long)K, n_batches, n_alpha);
+  const size_t need = select_output_least_workspace_bytes(fmt, group, M, N, K, n_batches);
+  if (workspace_bytes < need)
+    return fail(PQ_ERR_WORKSPACE, "pq_select_output_plan: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+  select_output_plan(fmt, group, M, N, K, n_batches, n_alpha, workspace_bytes, plan);
+  return PQ_OK;
+}
+
 size_t pq_operand_bytes(pq_format fmt, int group, int64_t rows, int64_t K) {
   if (check_format(fmt, group, K) || rows <= 0 || K % 32) return 0;
   return operand_bytes(fmt, group, rows, K);

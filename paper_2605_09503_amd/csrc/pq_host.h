@@ -82,6 +82,7 @@ int launch_quantize_rows_panel(pq_format fmt, int group, const PanelJob& a, cons
 // output tile of the product that a shape takes, and its size (pq_qgemm_tile.hip)
 int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int problems = 1);
 void tile_size(int tile, int* bm, int* bn);
+int tile_waves(int tile);
 
 // The error evaluation keeps one row as fp32 in LDS, one spare slot per eight channels: 4.5 K bytes of the
 // 150 KB a workgroup may take.
@@ -109,6 +110,8 @@ int launch_channel_absmax_sq(const float* absmax, int64_t K, double* out, hipStr
 // workspace of the selection by output error, and the least that it takes
 size_t select_output_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches);
 size_t select_output_least_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches);
+void select_output_plan(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, int n_alpha, size_t ws_bytes,
+                        pq_output_plan* out);
 int run_select_output(pq_format fmt, int group, const double* act_sumsq, const double* w_sumsq, int64_t K,
                       const void* const* x_calib, int n_batches, int64_t M, const void* w, int64_t N,
                       float act_ts, float w_ts, const double* alphas, int n_alpha, double tau,

@@ -80,6 +80,8 @@ void tile_size(int tile, int* bm, int* bn) {
   *bn = kTileSize[tile].bn;
 }
 
+int tile_waves(int tile) { return tile == kTile128 || tile == kTileSplit64 || tile == kTileSplit64x96 ? 4 : 8; }
+
 int64_t qgemm_tiles(int tile, int64_t M, int64_t N) {
   const TileSize& z = kTileSize[tile];
   return ((M + z.bm - 1) / z.bm) * ((N + z.bn - 1) / z.bn);

@@ -265,13 +265,32 @@ size_t select_output_least_workspace_bytes(pq_format fmt, int group, int64_t M, 
   return carve_out(nullptr, kOneByOne, fmt, group, M, N, K, n_batches, nullptr);
 }
 
+// the plan of a call with such a workspace: one that holds one order's operands and one batch only is taken as it is
+static Plan plan_within(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, size_t ws_bytes) {
+  const Plan plan = plan_of(M, N, n_batches);
+  return ws_bytes < carve_out(nullptr, plan, fmt, group, M, N, K, n_batches, nullptr) ? kOneByOne : plan;
+}
+// One tile and number of waves for the whole call, those of a full launch: a last launch of fewer batches adds its sums
+// to the first slots of the same ones, and equal orders have equal sums whichever launch takes them.
+static int tile_of_call(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, const Plan& plan, int n_cand) {
+  return choose_tile(fmt, group, plan.stack * M, N, K, std::min(plan.orders, n_cand));
+}
+
+void select_output_plan(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, int n_alpha, size_t ws_bytes,
+                        pq_output_plan* out) {
+  const Plan plan = plan_within(fmt, group, M, N, K, n_batches, ws_bytes);
+  const int tile = tile_of_call(fmt, group, M, N, K, plan, n_alpha + 1);
+  out->batches = plan.stack;
+  out->orders = std::min(plan.orders, n_alpha + 1);
+  tile_size(tile, &out->tile_m, &out->tile_n);
+  out->tile_waves = tile_waves(tile);
+}
+
 int run_select_output(pq_format fmt, int group, const double* act_sumsq, const double* w_sumsq, int64_t K,
                       const void* const* x_calib, int n_batches, int64_t M, const void* w, int64_t N,
                       float act_ts, float w_ts, const double* alphas, int n_alpha, double tau,
                       int32_t* perm_out, pq_select_report* report, void* ws, size_t ws_bytes, hipStream_t st) {
-  // a workspace that holds one order's operands and one batch only is taken as it is
-  Plan plan = plan_of(M, N, n_batches);
-  if (ws_bytes < carve_out(nullptr, plan, fmt, group, M, N, K, n_batches, nullptr)) plan = kOneByOne;
+  const Plan plan = plan_within(fmt, group, M, N, K, n_batches, ws_bytes);
   OutWs W;
   carve_out(ws, plan, fmt, group, M, N, K, n_batches, &W);
   const int64_t ldn = (N + 7) / 8 * 8;
@@ -308,9 +327,7 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
   if ((rc = check_hip(hipGetLastError(), "ref_gemm_kernel"))) return rc;
 
   const int64_t most_rows = stack * M;
-  // One tile and number of waves for the whole call, those of a full launch: a last launch of fewer batches adds its sums
-  // to the first slots of the same ones, and equal orders have equal sums whichever launch takes them.
-  const int tile = choose_tile(fmt, group, most_rows, N, K, orders);
+  const int tile = tile_of_call(fmt, group, M, N, K, plan, n_cand);
   const size_t num_stride = out_tiles(stack * M, N);
   const size_t w_next = operand_bytes(fmt, group, N, K);
   const RowBatches w_rows = {{(const uint16_t*)w}, N};

@@ -47,6 +47,11 @@ class NormParams(C.Structure):
                 ("mod_shift", C.c_void_p), ("rows_per_mod", C.c_int64), ("eps", C.c_float)]
 
 
+class OutputPlan(C.Structure):
+    """pq_output_plan of the header."""
+    _fields_ = [(n, C.c_int) for n in ("batches", "orders", "tile_m", "tile_n", "tile_waves")]
+
+
 NORM_RMS, NORM_ADALN = 0, 1
 
 
@@ -99,6 +104,7 @@ def _declare(lib):
     lib.pq_qgemm_run.argtypes = gemm_args
     lib.pq_qgemm_prep.argtypes = [i32, i32, vp, vp, i64, i64, i64, vp, sz, vp]
     lib.pq_qgemm_tile.argtypes = [i32, i32, i64, i64, i64, C.POINTER(i32), C.POINTER(i32)]
+    lib.pq_select_output_plan.argtypes = [i32, i32, i64, i64, i64, i32, i32, sz, C.POINTER(OutputPlan)]
     lib.pq_operand_bytes.restype = sz
     lib.pq_operand_bytes.argtypes = [i32, i32, i64, i64]
     lib.pq_pack_operand.argtypes = [i32, i32, vp, vp, i64, i64, vp, sz, vp]
@@ -322,6 +328,16 @@ def pq_select_perm_output_error(fmt: int, group: int, act_sumsq: torch.Tensor, w
     """The selection with the relative error of the layer's output as the metric."""
     return _select("pq_select_perm_output_error", OP_SELECT_PERM_OUTPUT, fmt, group, act_sumsq, w_sumsq, x_calib, w,
                    act_tensor_scale, w_tensor_scale, perm_out, alphas, tau, workspace)
+
+
+def pq_select_output_plan(fmt: int, group: int, M: int, N: int, K: int, n_batches: int, n_alpha: int,
+                          workspace_bytes: Optional[int] = None) -> OutputPlan:
+    """The launches of pq_select_perm_output_error with a workspace of that size (default: what pq_workspace_bytes says)."""
+    if workspace_bytes is None:
+        workspace_bytes = pq_workspace_bytes(OP_SELECT_PERM_OUTPUT, fmt, group, M, N, K, n_batches)
+    plan = OutputPlan()
+    _check(load().pq_select_output_plan(fmt, group, M, N, K, n_batches, n_alpha, workspace_bytes, C.byref(plan)))
+    return plan
 
 
 def pq_quant_error(fmt: int, group: int, x: torch.Tensor, perm: Optional[torch.Tensor],

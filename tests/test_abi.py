@@ -369,6 +369,21 @@ def test_qgemm_tile_validation(lib):
     assert f(pq.FMT_NVFP4, 16, 1 << 24, 1 << 24, 1 << 24, C.byref(m), C.byref(n)) == 0 and (m.value, n.value) == (256, 256)
 
 
+def test_select_output_plan_validation(lib):
+    p = pq.OutputPlan()
+    f = lib.pq_select_output_plan
+    big = 1 << 40
+    assert f(pq.FMT_INT4, 64, 64, 64, 64, 2, 6, big, None) == PQ_ERR_NULL
+    assert f(pq.FMT_INT4, 48, 64, 64, 96, 2, 6, big, C.byref(p)) == PQ_ERR_FORMAT
+    for M, N, K, nb, na in [(0, 64, 64, 2, 6), (64, -1, 64, 2, 6), (64, 64, 65600, 2, 6), (64, 64, 64, 0, 6), (64, 64, 64, 2, 0),
+                            (64, 64, 64, 2, 16), ((1 << 24) + 1, 64, 64, 2, 6)]:
+        assert f(pq.FMT_INT4, 64, M, N, K, nb, na, big, C.byref(p)) == PQ_ERR_SHAPE
+    assert f(pq.FMT_NVFP4, 16, 64, 64, 48, 2, 6, big, C.byref(p)) == PQ_ERR_SHAPE
+    assert f(pq.FMT_INT4, 64, 64, 64, 64, 2, 6, 1000, C.byref(p)) == PQ_ERR_WORKSPACE
+    assert f(pq.FMT_INT4, 64, 1024, 3072, 3072, 2, 6, big, C.byref(p)) == 0
+    assert (p.batches, p.orders, p.tile_m, p.tile_n, p.tile_waves) == (2, 7, 256, 256, 8)
+
+
 # tiles measured within 2 % of the fastest one; columns past the last whole eight are what a large tile pays most for
 @pytest.mark.parametrize("fmt,g,M,N,K,tiles", [
     (pq.FMT_INT3, 64, 2892, 2765, 832, {(64, 64)}),                # 224 x 256: 26.6 us, 128 x 128 24.4, 64 x 64 21.7

@@ -366,22 +366,33 @@ def test_select_perm_output_error_matches_oracle(name, fmt, g, M, N, K, nb):
     np.testing.assert_array_equal(perm_out.cpu().numpy(), np.arange(K))
 
 
-@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
-    (pq.FMT_NVFP4, 16, 3600, 4081, 160, T256), (pq.FMT_NVFP4, 16, 2304, 3656, 288, T224),
-    (pq.FMT_NVFP4, 16, 4090, 4087, 160, T128), (pq.FMT_NVFP4, 16, 1500, 2056, 96, T128),
-    (pq.FMT_INT4, 64, 3600, 4081, 192, T256), (pq.FMT_INT4, 128, 3000, 4087, 640, T224), (pq.FMT_INT4, 64, 4090, 4087, 192, T128),
-    (pq.FMT_INT3, 64, 4090, 4087, 320, T256), (pq.FMT_INT3, 64, 2300, 3656, 192, T224), (pq.FMT_INT3, 32, 3000, 3585, 96, T224),
-    (pq.FMT_INT3, 32, 33, 41, 96, S32), (pq.FMT_INT3, 256, 70, 3000, 256, S64X32), (pq.FMT_NVFP4, 16, 2300, 333, 96, S64X32),
-    (pq.FMT_INT4, 128, 300, 4087, 640, S64X32), (pq.FMT_INT4, 256, 130, 3656, 768, S64), (pq.FMT_NVFP4, 16, 300, 4087, 768, S64X96),
-    (pq.FMT_INT3, 256, 500, 3000, 768, S64X96),
+@pytest.mark.parametrize("fmt,g,M,N,K,tile,waves", [
+    (pq.FMT_NVFP4, 16, 3600, 4081, 160, T256, 8), (pq.FMT_NVFP4, 16, 1500, 2056, 96, T224, 8),
+    (pq.FMT_NVFP4, 16, 2304, 3656, 288, T128, 4), (pq.FMT_NVFP4, 16, 4090, 4087, 160, T128, 4),
+    (pq.FMT_NVFP4, 16, 33, 36, 160, S32, 8), (pq.FMT_NVFP4, 16, 1103, 38, 160, S64X32, 8),
+    (pq.FMT_NVFP4, 16, 2300, 333, 96, S64, 4), (pq.FMT_NVFP4, 16, 300, 4087, 768, S64, 4), (pq.FMT_NVFP4, 16, 1396, 65, 1376, S64, 8),
+    (pq.FMT_NVFP4, 16, 235, 1489, 224, S64X96, 4), (pq.FMT_NVFP4, 16, 68, 3041, 1376, S64X96, 8),
+    (pq.FMT_INT3, 32, 3000, 3585, 96, T256, 8), (pq.FMT_INT4, 32, 2015, 1185, 160, T224, 8), (pq.FMT_INT4, 32, 3250, 203, 160, T128, 4),
+    (pq.FMT_INT3, 32, 33, 41, 96, S32, 8), (pq.FMT_INT4, 32, 1164, 35, 160, S64X32, 8), (pq.FMT_INT3, 32, 65, 2641, 160, S64, 4),
+    (pq.FMT_INT4, 32, 1385, 66, 1440, S64, 8), (pq.FMT_INT4, 32, 1698, 129, 288, S64X96, 4),
+    (pq.FMT_INT3, 32, 36, 4194, 1376, S64X96, 8),
+    (pq.FMT_INT4, 64, 3600, 4081, 192, T256, 8), (pq.FMT_INT4, 128, 3000, 4087, 640, T256, 8), (pq.FMT_INT4, 64, 4090, 4087, 192, T256, 8),
+    (pq.FMT_INT4, 256, 3929, 513, 256, T224, 8), (pq.FMT_INT4, 64, 2931, 209, 192, T128, 4), (pq.FMT_INT4, 64, 33, 37, 192, S32, 8),
+    (pq.FMT_INT4, 64, 1090, 34, 192, S64X32, 8), (pq.FMT_INT4, 128, 300, 4087, 640, S64, 4), (pq.FMT_INT4, 256, 130, 3656, 768, S64, 4),
+    (pq.FMT_INT4, 64, 1370, 65, 1536, S64, 8), (pq.FMT_INT4, 64, 68, 3825, 384, S64X96, 4), (pq.FMT_INT4, 256, 35, 4163, 1536, S64X96, 8),
+    (pq.FMT_INT3, 64, 4090, 4087, 320, T256, 8), (pq.FMT_INT3, 64, 2300, 3656, 192, T224, 8), (pq.FMT_INT3, 64, 1023, 633, 192, T128, 4),
+    (pq.FMT_INT3, 256, 70, 3000, 256, S32, 8), (pq.FMT_INT3, 64, 1096, 33, 192, S64X32, 8), (pq.FMT_INT3, 256, 500, 3000, 768, S64, 4),
+    (pq.FMT_INT3, 128, 101, 2860, 640, S64X96, 4), (pq.FMT_INT3, 64, 65, 3370, 1408, S64X96, 8),
     # a row and its group maxima beyond 48 KB of LDS in the gathering quantizer, up to its limit
-    (pq.FMT_NVFP4, 16, 40, 33, 24640, None), (pq.FMT_INT4, 64, 40, 33, 24640, None), (pq.FMT_INT3, 32, 9, 33, 65536, None),
+    (pq.FMT_NVFP4, 16, 40, 33, 24640, None, 0), (pq.FMT_INT4, 64, 40, 33, 24640, None, 0), (pq.FMT_INT3, 32, 9, 33, 65536, None, 0),
 ])
-def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K, tile):
+def test_output_error_sums_of_every_product_tile(fmt, g, M, N, K, tile, waves):
     # the selection's error of the original order and of a candidate's against the same product stored in fp32, summed
     # in fp64: every tile of the product kernels keeps its own squared difference, ragged edges and two batches included
     if tile:
-        _takes(tile, fmt, g, M, N, K)
+        plan = pq.pq_select_output_plan(fmt, g, M, N, K, 2, 1)
+        assert (plan.tile_m, plan.tile_n, plan.tile_waves) == (*tile, waves), \
+            "this shape is here for the tile that the call takes: choose another"
     gen = torch.Generator(device=DEV)
     gen.manual_seed(55 + M + K)
     xs = [torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
@@ -471,6 +482,10 @@ def test_output_error_in_several_launches(fmt, g, M, N, K, nb, n_alpha):
 ])
 def test_output_error_of_equal_orders_in_launches_of_different_size(fmt, g, M, N, K, n_alpha):
     # ties go to the smallest alpha: the same order has the same error to the last bit whichever launch takes it
+    plan = pq.pq_select_output_plan(fmt, g, M, N, K, 2, n_alpha)
+    tiles = -(-2 * M // plan.tile_m) * -(-N // plan.tile_n)
+    alone = (n_alpha + 1) % plan.orders
+    assert (plan.tile_m, plan.tile_n, plan.tile_waves) == (64, 64, 4) and alone * tiles <= 256 < plan.orders * tiles
     gen = torch.Generator(device=DEV)
     gen.manual_seed(3 + K)
     xs = [torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
