@@ -212,7 +212,9 @@ int pq_select_perm_device_scales(pq_format fmt, int group, const double* act_sum
  * workspace: pq_workspace_bytes(PQ_OP_SELECT_PERM_OUTPUT, fmt, group, M, N, K, n_batches) bytes -- it
  * holds the fp32 reference products of all batches (4 n_batches M N bytes) and the operands of as many batches and
  * orders as one launch takes.  A smaller one is accepted as long as it holds those of one batch and one order; the call
- * then multiplies them one after the other.
+ * then takes more launches, of as many orders and batches as it holds.  The last bits of the errors depend on how the
+ * call is cut (the sums' order is fixed by M, N, K, n_batches, n_alpha and the workspace's size), equal orders have
+ * equal errors in any case.
  */
 int pq_select_perm_output_error(pq_format fmt, int group, const double* act_sumsq, const double* w_sumsq,
                                 int64_t K, const void* const* x_calib, int n_batches, int64_t M,

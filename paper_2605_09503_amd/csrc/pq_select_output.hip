@@ -265,23 +265,32 @@ size_t select_output_least_workspace_bytes(pq_format fmt, int group, int64_t M, 
   return carve_out(nullptr, kOneByOne, fmt, group, M, N, K, n_batches, nullptr);
 }
 
-// the plan of a call with such a workspace: one that holds one order's operands and one batch only is taken as it is
-static Plan plan_within(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, size_t ws_bytes) {
-  const Plan plan = plan_of(M, N, n_batches);
-  return ws_bytes < carve_out(nullptr, plan, fmt, group, M, N, K, n_batches, nullptr) ? kOneByOne : plan;
+// The plan of a call with such a workspace: where it does not hold the operands of plan_of, as many orders as fit, dealt
+// evenly over the launches, then (an order at a time) as many batches.  INT4 g64, 8 x 64 rows, 12288 x 12288 weights, seven
+// orders in one launch take 614 MB, four 363, one 113 (a batch at a time 109).
+static Plan plan_within(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, int n_cand, size_t ws_bytes) {
+  Plan p = plan_of(M, N, n_batches);
+  p.orders = std::min(p.orders, n_cand);
+  const auto fits = [&] { return carve_out(nullptr, p, fmt, group, M, N, K, n_batches, nullptr) <= ws_bytes; };
+  if (fits()) return p;
+  while (p.orders > 1 && !fits()) --p.orders;
+  while (p.stack > 1 && !fits()) --p.stack;
+  const int launches = (n_cand + p.orders - 1) / p.orders;
+  p.orders = (n_cand + launches - 1) / launches;
+  return p;
 }
 // One tile and number of waves for the whole call, those of a full launch: a last launch of fewer batches adds its sums
 // to the first slots of the same ones, and equal orders have equal sums whichever launch takes them.
-static int tile_of_call(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, const Plan& plan, int n_cand) {
-  return choose_tile(fmt, group, plan.stack * M, N, K, std::min(plan.orders, n_cand));
+static int tile_of_call(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, const Plan& plan) {
+  return choose_tile(fmt, group, plan.stack * M, N, K, plan.orders);
 }
 
 void select_output_plan(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches, int n_alpha, size_t ws_bytes,
                         pq_output_plan* out) {
-  const Plan plan = plan_within(fmt, group, M, N, K, n_batches, ws_bytes);
-  const int tile = tile_of_call(fmt, group, M, N, K, plan, n_alpha + 1);
+  const Plan plan = plan_within(fmt, group, M, N, K, n_batches, n_alpha + 1, ws_bytes);
+  const int tile = tile_of_call(fmt, group, M, N, K, plan);
   out->batches = plan.stack;
-  out->orders = std::min(plan.orders, n_alpha + 1);
+  out->orders = plan.orders;
   tile_size(tile, &out->tile_m, &out->tile_n);
   out->tile_waves = tile_waves(tile);
 }
@@ -290,12 +299,12 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
                       const void* const* x_calib, int n_batches, int64_t M, const void* w, int64_t N,
                       float act_ts, float w_ts, const double* alphas, int n_alpha, double tau,
                       int32_t* perm_out, pq_select_report* report, void* ws, size_t ws_bytes, hipStream_t st) {
-  const Plan plan = plan_within(fmt, group, M, N, K, n_batches, ws_bytes);
+  const int n_cand = n_alpha + 1;              // candidate 0 is the original order
+  const Plan plan = plan_within(fmt, group, M, N, K, n_batches, n_cand, ws_bytes);
   OutWs W;
   carve_out(ws, plan, fmt, group, M, N, K, n_batches, &W);
   const int64_t ldn = (N + 7) / 8 * 8;
-  const int n_cand = n_alpha + 1;              // candidate 0 is the original order
-  const int stack = plan.stack, orders = std::min(plan.orders, n_cand);
+  const int stack = plan.stack, orders = plan.orders;
   if (stack * M * 32 > 0x7FFFFFFF || N * 32 > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many rows for the panel layout");
   int rc;
   if ((rc = launch_candidate_orders(act_sumsq, w_sumsq, K, alphas, n_alpha, W.keys, W.rank, W.cands, st))) return rc;
@@ -327,7 +336,7 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
   if ((rc = check_hip(hipGetLastError(), "ref_gemm_kernel"))) return rc;
 
   const int64_t most_rows = stack * M;
-  const int tile = tile_of_call(fmt, group, M, N, K, plan, n_cand);
+  const int tile = tile_of_call(fmt, group, M, N, K, plan);
   const size_t num_stride = out_tiles(stack * M, N);
   const size_t w_next = operand_bytes(fmt, group, N, K);
   const RowBatches w_rows = {{(const uint16_t*)w}, N};

@@ -454,8 +454,17 @@ def test_output_error_in_several_launches(fmt, g, M, N, K, nb, n_alpha):
     least = _least_output_workspace(fmt, g, M, N, K, nb)
     full = pq.pq_workspace_bytes(pq.OP_SELECT_PERM_OUTPUT, fmt, g, M, N, K, nb)
     assert full > least
-    got = []
-    for size in (full, full - 1, least):
+    # between the two as many orders, then batches, as fit
+    most = pq.pq_select_output_plan(fmt, g, M, N, K, nb, n_alpha, full)
+    operand = pq.pq_operand_bytes(fmt, g, M, K) + pq.pq_operand_bytes(fmt, g, N, K)
+    got, sizes, shares = [], (full, full - operand - 512, (full + least) // 2, least), []
+    for size in sizes:
+        p = pq.pq_select_output_plan(fmt, g, M, N, K, nb, n_alpha, size)
+        shares.append(p.orders * p.batches)
+        assert p.orders <= most.orders and p.batches <= most.batches and (p.orders == 1 or p.batches == most.batches)
+    assert shares == sorted(shares, reverse=True) and shares[-1] == 1
+    assert shares[1] > 1 or shares[0] == 2
+    for size in sizes:
         ws = torch.full((size,), 0xFF, dtype=torch.uint8, device=DEV)
         perm = torch.empty(K, dtype=torch.int32, device=DEV)
         got.append((pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, ts[0], ts[1], perm, alphas=alphas, tau=-1e30,
@@ -463,15 +472,14 @@ def test_output_error_in_several_launches(fmt, g, M, N, K, nb, n_alpha):
     with pytest.raises(pq.PQError):
         pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, ts[0], ts[1], perm, alphas=alphas,
                                        workspace=torch.empty(least - 1, dtype=torch.uint8, device=DEV))
-    one = got[2][0]
-    assert got[1][0] == one                              # a byte short of the full size is the least one
-    rep = got[0][0]
-    assert abs(rep.sum_x2 - one.sum_x2) <= 1e-5 * one.sum_x2
-    np.testing.assert_allclose([rep.e_orig] + rep.e_cand, [one.e_orig] + one.e_cand, rtol=1e-5)
+    one = got[-1][0]
     wide = sum(float((x.double() @ w.double().t()).square().sum()) for x in xs)
-    assert abs(rep.sum_x2 - wide) <= 1e-5 * wide
-    if rep.alpha_index == one.alpha_index:
-        assert torch.equal(got[0][1], got[2][1])
+    for rep, perm in got:
+        assert abs(rep.sum_x2 - one.sum_x2) <= 1e-5 * one.sum_x2
+        np.testing.assert_allclose([rep.e_orig] + rep.e_cand, [one.e_orig] + one.e_cand, rtol=1e-5)
+        assert abs(rep.sum_x2 - wide) <= 1e-5 * wide
+        if rep.alpha_index == one.alpha_index:
+            assert torch.equal(perm, got[-1][1])
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K,n_alpha", [
