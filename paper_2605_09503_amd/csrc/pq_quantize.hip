@@ -192,10 +192,11 @@ int launch_quantize_rows(pq_format fmt, int group, const void* x, int64_t rows, 
 template <int FMT, int G>
 __global__ __launch_bounds__(256) void quantize_rows_panel_kernel(PanelJob a_job, PanelJob w_job, int64_t K,
                                                                   const int32_t* __restrict__ perms, int first, int n,
-                                                                  int per_wg, OperandLayout a_lay, OperandLayout w_lay) {
+                                                                  int per_wg, OperandLayout a_lay, OperandLayout w_lay,
+                                                                  int64_t row0) {
   extern __shared__ __align__(16) uint16_t row_lds[];       // the row, K elements, then the INT group maxima
   __shared__ float wave_mx[4];
-  const bool is_w = (int64_t)blockIdx.x >= a_job.rows;
+  const bool is_w = row0 + blockIdx.x >= a_job.rows;
   const PanelJob& job = is_w ? w_job : a_job;
   const OperandLayout& lay = is_w ? w_lay : a_lay;
   float T = 0.0f, encT = 0.0f;
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(256) void quantize_rows_panel_kernel(PanelJob a_job
     T = *job.ts;
     encT = nv4_enc_scale(T);
   }
-  const int64_t rows = job.rows, row = (int64_t)blockIdx.x - (is_w ? a_job.rows : 0);
+  const int64_t rows = job.rows, row = row0 + blockIdx.x - (is_w ? a_job.rows : 0);
   const int batch = (int)(row / job.x.rows);
   const uint16_t* xr = job.x.p[batch] + (row - batch * job.x.rows) * K;
   float* h_lds = reinterpret_cast<float*>(row_lds + K);
@@ -272,7 +273,6 @@ static int launch_q_panel(pq_format fmt, const PanelJob& a, const PanelJob& w, i
   const size_t shmem = (size_t)K * 2 + (FMT == kNvfp4 ? 0 : (size_t)al.units * 4);
   auto kern = quantize_rows_panel_kernel<FMT, G>;
   if (shmem > kPanelRowLds) return fail(PQ_ERR_SHAPE, "K=%lld too large for a row in LDS", (long long)K);   // refused earlier
-  if (a.rows + w.rows > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many rows");
   static std::atomic<uint64_t> raised{0};
   if (shmem > 48 * 1024) {
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kPanelRowLds, raised,
@@ -283,9 +283,14 @@ static int launch_q_panel(pq_format fmt, const PanelJob& a, const PanelJob& w, i
   const int64_t rows = a.rows + w.rows;
   const int shares = (int)(rows >= 2048 ? 1 : rows * n <= 2048 ? n : (2048 + rows - 1) / rows);
   const int per_wg = (n + shares - 1) / shares;
-  hipLaunchKernelGGL(kern, dim3((unsigned)rows, (unsigned)((n + per_wg - 1) / per_wg)), dim3(256), shmem, st, a, w, K, perms,
-                     first, n, per_wg, al, wl);
-  return check_hip(hipGetLastError(), "quantize_rows_panel_kernel");
+  constexpr int64_t kMostRows = UINT32_MAX / 256;      // a grid of more threads is cut short without an error
+  for (int64_t row0 = 0; row0 < rows; row0 += kMostRows) {
+    const int64_t part = rows - row0 < kMostRows ? rows - row0 : kMostRows;
+    hipLaunchKernelGGL(kern, dim3((unsigned)part, (unsigned)((n + per_wg - 1) / per_wg)), dim3(256), shmem, st, a, w, K, perms,
+                       first, n, per_wg, al, wl, row0);
+    if (int rc = check_hip(hipGetLastError(), "quantize_rows_panel_kernel")) return rc;
+  }
+  return PQ_OK;
 }
 
 int launch_quantize_rows_panel(pq_format fmt, int group, const PanelJob& a, const PanelJob& w, int64_t K,

@@ -226,3 +226,36 @@ def test_select_perm_full_size(name, nb):
     np.testing.assert_array_equal(got_perm, want)
     # with / without the permutation: the accepted order never raises the calibration error
     assert (not rep.accepted) or rep.e_best < rep.e_orig
+
+
+@pytest.mark.parametrize("fmt,g,M", [(pq.FMT_NVFP4, 16, (1 << 24) - 1), (pq.FMT_INT4, 32, 1 << 24)])
+def test_output_error_of_more_rows_than_one_grid_quantizes(fmt, g, M):
+    # a workgroup of 256 threads a row: the rows of both operands together are more threads than a grid holds (2^24 - 1 of
+    # one alone are not)
+    N, K = 8, 32
+    _say("output error fmt=%d M=%d N=%d K=%d" % (fmt, M, N, K))
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(9)
+    x = torch.empty((M, K), dtype=torch.bfloat16, device=DEV).normal_(generator=gen)
+    w = torch.empty((N, K), dtype=torch.bfloat16, device=DEV).normal_(generator=gen)
+    part = 1 << 21
+    sa = sum(x[i:i + part].double().square().sum(0) for i in range(0, M, part))
+    sw = w.double().square().sum(0)
+    ts = [torch.full((1,), float(t.abs().max()) / 2688.0, device=DEV) for t in (x, w)]
+    perm = torch.empty(K, dtype=torch.int32, device=DEV)
+    rep = pq.pq_select_perm_output_error(fmt, g, sa, sw, [x], w, float(ts[0]), float(ts[1]), perm, alphas=(0.5,), tau=-1e30)
+    codes, scales = pq.alloc_quantized(fmt, g, N, K, DEV)
+    for order, err in ((None, rep.e_orig), (perm, rep.e_cand[0])):
+        pq.pq_quantize_act(fmt, g, w, order, ts[1], codes, scales)
+        w_op = pq.pq_pack_operand(fmt, g, codes, scales)
+        num = den = 0.0
+        for i in range(0, M, part):
+            xi = x[i:i + part] if order is None else x[i:i + part][:, order.long()].contiguous()
+            m = xi.shape[0]
+            y = torch.empty((m, N), dtype=torch.float32, device=DEV)
+            pq.pq_qgemm_packed_f32(fmt, g, pq.pq_quantize_act_packed(fmt, g, xi, ts[0]), ts[0], w_op, ts[1], y, m, N, K)
+            ref = x[i:i + part].double() @ w.double().t()
+            num += float((ref - y.double()).square().sum())
+            den += float(ref.square().sum())
+        assert abs(rep.sum_x2 - den) <= 1e-5 * den          # fp32 accumulation of both products
+        assert abs(err - num / den) <= 1e-5 * err
