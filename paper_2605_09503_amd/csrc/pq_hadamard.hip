@@ -556,6 +556,7 @@ int launch_hadamard(const void* x, int64_t rows, int64_t K, int64_t ld, const fl
   };
   bool four = hadamard_four_waves(rows, K);
   if (!in_registers(four ? 4 : 1)) four = in_registers(4) || !(in_registers(1) || K <= 4096);
+  if (rows * 256 > UINT32_MAX) four = false;                  // more threads than a grid holds
   const bool wide = lane_values(K, ha.m, four ? 4 : 1) == 64;
 #define PQ_HADAMARD(TEAM, M, WIDE) return launch_hadamard_team<FMT, G, TEAM, M, WIDE>(x, rows, K, ld, ts, L, operand, ha, st)
 #define PQ_HADAMARD_M(M)                              \

@@ -155,6 +155,13 @@ static int launch_q(const void* x, int64_t rows, int64_t K, int64_t ld, const in
                        (const uint4*)x, n_chunks, ts, (uint32_t*)codes, scales);
     return check_hip(hipGetLastError(), "quantize_flat_kernel");
   }
+  if (rows * 256 > UINT32_MAX) {                       // more threads than a grid holds
+    const int64_t part = rows / 2, groups = part * (K / G);
+    const int rc = launch_q<FMT, G>(x, part, K, ld, perm, ts, codes, scales, st);
+    return rc ? rc
+              : launch_q<FMT, G>((const uint16_t*)x + part * ld, rows - part, K, ld, perm, ts, codes + part * (K / 2),
+                                 (uint8_t*)scales + groups * (FMT == kNvfp4 ? 1 : 4), st);
+  }
   // with a gather the row goes through LDS when it fits 48 KB
   const int staged = perm && K * 2 <= 48 * 1024 ? 1 : 0;
   hipLaunchKernelGGL((quantize_rows_kernel<FMT, G>), dim3((unsigned)rows), dim3(256), staged ? (size_t)K * 2 : 0, st,

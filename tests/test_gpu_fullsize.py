@@ -259,3 +259,20 @@ def test_output_error_of_more_rows_than_one_grid_quantizes(fmt, g, M):
             den += float(ref.square().sum())
         assert abs(rep.sum_x2 - den) <= 1e-5 * den          # fp32 accumulation of both products
         assert abs(err - num / den) <= 1e-5 * err
+
+
+@pytest.mark.parametrize("fmt,g", [(pq.FMT_NVFP4, 16), (pq.FMT_INT4, 32)])
+def test_gathering_quantizer_of_as_many_rows_as_it_takes(fmt, g):
+    # a workgroup of 256 threads a row: 2^24 rows are one thread more than a grid holds
+    M, K = 1 << 24, 32
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(10)
+    x = torch.empty((M, K), dtype=torch.bfloat16, device=DEV).normal_(generator=gen)
+    ts = torch.full((1,), float(x.abs().max()) / 2688.0, device=DEV)
+    perm = torch.randperm(K, generator=gen, device=DEV, dtype=torch.int32)
+    got, want = pq.alloc_quantized(fmt, g, M, K, DEV), pq.alloc_quantized(fmt, g, M, K, DEV)
+    for t in got:
+        t.zero_()
+    pq.pq_quantize_act(fmt, g, x, perm, ts, *got)
+    pq.pq_quantize_act(fmt, g, x[:, perm.long()].contiguous(), None, ts, *want)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
