@@ -238,23 +238,38 @@ __device__ __forceinline__ void swap_stage(float (&v)[V]) {
 
 typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
 
-// entries (b0 + 0 .. 3, n) of the Paley matrix of order M as bf16; zero outside of it
+// the non-zero squares modulo Q (Q prime), a bit each
+template <int Q>
+__host__ __device__ constexpr uint32_t squares() {
+  uint32_t m = 0;
+  for (int r = 1; r < Q; ++r)
+    if (legendre<Q>(r) > 0) m |= 1u << r;
+  return m;
+}
+// entry (b, n) of the Paley matrix of order M as bf16; zero outside of it, where the difference of the indices is no residue
+template <int M>
+__host__ __device__ constexpr uint32_t paley_bits(int b, int n) {
+  constexpr uint32_t kSquares = squares<M - 1>();
+  const int d = b - n + (b < n ? M - 1 : 0);
+  const bool positive = b == n || b == 0 || (n != 0 && ((kSquares >> (d & 31)) & 1));
+  return b < M && n < M ? (positive ? 0x3F80u : 0xBF80u) : 0u;
+}
+// every entry that a lane asks for; evaluated by the compiler, which refuses what the language leaves undefined
+template <int M>
+constexpr bool paley_bits_agree() {
+  for (int b = 0; b < 32; ++b)
+    for (int n = 0; n < 32; ++n)
+      if (paley_bits<M>(b, n) != (b >= M || n >= M ? 0u : paley_entry<M>(b, n) > 0 ? 0x3F80u : 0xBF80u)) return false;
+  return true;
+}
+static_assert(paley_bits_agree<12>() && paley_bits_agree<20>(), "the matrix of the matrix unit is the one of paley_pass");
+
+// entries (b0 + 0 .. 3, n)
 template <int M>
 __device__ __forceinline__ bf16x4_bits paley_column4(int b0, int n) {
-  constexpr uint32_t kSquares = [] {
-    uint32_t m = 0;
-    for (int r = 1; r < M - 1; ++r)
-      if (legendre<M - 1>(r) > 0) m |= 1u << r;
-    return m;
-  }();
   uint32_t e[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int b = b0 + i;
-    const int d = b - n + (b < n ? M - 1 : 0);
-    const bool positive = b == n || b == 0 || (n != 0 && ((kSquares >> d) & 1));
-    e[i] = b < M && n < M ? (positive ? 0x3F80u : 0xBF80u) : 0u;
-  }
+  for (int i = 0; i < 4; ++i) e[i] = paley_bits<M>(b0 + i, n);
   return __builtin_bit_cast(bf16x4_bits, make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16)));
 }
 
