@@ -55,7 +55,8 @@ __device__ __forceinline__ float e4m3_decode(uint32_t byte) {
 }
 
 // The same on the conversion unit, with the rounded value itself: v_cvt_pk_fp8_f32 rounds to nearest even, subnormals
-// included (compared with e4m3_rne_sat for every t in [0, 448]).  Two values take what one does.
+// included (the tests hold the bytes against the oracle's at, above and below every midpoint and value).  Two values take
+// what one does.
 __device__ __forceinline__ void e4m3_round2(float t0, float t1, uint32_t& bytes, float& v0, float& v1) {
   bytes = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(fminf(t0, 448.0f), fminf(t1, 448.0f), 0, false);
   const auto v = __builtin_amdgcn_cvt_pk_f32_fp8((int)bytes, false);

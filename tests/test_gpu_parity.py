@@ -506,6 +506,49 @@ def test_output_error_of_equal_orders_in_launches_of_different_size(fmt, g, M, N
     assert len(set(rep.e_cand)) == 1 and rep.alpha_index == 0
 
 
+def _e4m3_probe():
+    """bf16 bits of one value a group of 16 (the rest zeros) and tensor scales near 1/6, with which the quantizer's
+    t = fl(fl(amax / T) / 6) is every non-negative bf16 value up to 512 and its neighbours in binary32."""
+    top = np.arange(0, 0x4400, dtype=np.uint16)
+    top = np.concatenate([top, np.zeros(-len(top) % 1024, dtype=np.uint16)])
+    bits = np.zeros((len(top), 16), dtype=np.uint16)
+    at = np.arange(len(top))
+    bits[at, at % 16] = top | ((at // 16 % 2) << 15).astype(np.uint16)
+    sixth = np.float32(1.0) / np.float32(6.0)
+    scales = [np.int32(sixth.view(np.int32) + d).view(np.float32) for d in (-2, -1, 0, 1, 2)]
+    amax = OF.bf16_bits_to_f64(top).astype(np.float32)
+    t = [amax * (np.float32(1.0) / T_) / np.float32(6.0) for T_ in scales]
+    return bits.reshape(-1, 1024), scales, np.unique(np.concatenate(t))
+
+
+def test_e4m3_scale_bytes_around_every_midpoint():
+    # the block scales of NVFP4 are rounded by the conversion instruction: to nearest, ties to even, subnormals and the
+    # largest value included
+    bits, tensor_scales, t = _e4m3_probe()
+    grid = np.array([m / 8 * 2.0 ** -6 for m in range(8)] + [(1 + m / 8) * 2.0 ** e for e in range(-6, 9) for m in range(8)][:-1])
+    assert grid[-1] == 448.0 and len(grid) == 127
+    for edge in np.concatenate([(grid[1:] + grid[:-1]) / 2, grid[1:]]).astype(np.float32):
+        near = t[np.abs(t.view(np.int32) - edge.view(np.int32)) <= 2]
+        assert (near == edge).any() and (near < edge).any() and (near > edge).any(), edge
+    rows, K = bits.shape
+    x = _to_dev(bits)
+    x64 = OF.bf16_bits_to_f64(bits)
+    err = torch.zeros(1, dtype=torch.float64, device=DEV)
+    for T_ in tensor_scales:
+        ts = torch.full((1,), float(T_), device=DEV)
+        ref_codes, ref_scales, _ = T.oracle_quantize_bits(pq.FMT_NVFP4, 16, bits, None, T_)
+        codes, scales = pq.alloc_quantized(pq.FMT_NVFP4, 16, rows, K, DEV)
+        pq.pq_quantize_act(pq.FMT_NVFP4, 16, x, None, ts, codes, scales)
+        np.testing.assert_array_equal(scales.cpu().numpy(), ref_scales)
+        np.testing.assert_array_equal(codes.cpu().numpy(), ref_codes)
+        # into the operand layout, and two scales at a time in the error evaluation
+        codes2, scales2 = pq.alloc_quantized(pq.FMT_NVFP4, 16, rows, K, DEV)
+        pq.pq_quantize_act_packed(pq.FMT_NVFP4, 16, x, ts, codes=codes2, scales=scales2)
+        assert torch.equal(codes, codes2) and torch.equal(scales, scales2)
+        pq.pq_quant_error(pq.FMT_NVFP4, 16, x, None, float(T_), err)
+        np.testing.assert_allclose(err.item(), OC.squared_error(pq.FMT_NVFP4, 16, x64, None, T_), rtol=T.ERRSUM_RTOL)
+
+
 def test_select_perm_candidates_and_ties():
     # equal second moments: the sort must keep ascending channel index (stable)
     K, M, N = 256, 32, 32
