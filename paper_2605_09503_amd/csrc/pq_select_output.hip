@@ -89,10 +89,11 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint
   load(kRefStep, pieces[1]);
   put(lds, 0, pieces[0]);
   __syncthreads();
-  // step k0, in stage P; pieces[P ^ 1] holds the next one, pieces[P] is free
-  auto turn = [&](auto Pc, int k0) {
+  // step k0, in stage P; pieces[P ^ 1] holds the next one, if there is one, pieces[P] is free
+  auto turn = [&](auto Pc, int k0, auto last) {
     constexpr int P = decltype(Pc)::value;
-    load(k0 + 2 * kRefStep, pieces[P]);
+    constexpr bool kMore = !decltype(last)::value;
+    if constexpr (kMore) load(k0 + 2 * kRefStep, pieces[P]);
     const unsigned char* a_t = lds + P * kRefStage;
     const unsigned char* w_t = a_t + kRefTile * kRefRowBytes;
 #pragma unroll
@@ -112,14 +113,18 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i], xf[j], acc[i][j], 0, 0, 0);
     }
-    put(lds + (P ^ 1) * kRefStage, k0 + kRefStep, pieces[P ^ 1]);
-    __syncthreads();
+    if constexpr (kMore) {
+      put(lds + (P ^ 1) * kRefStage, k0 + kRefStep, pieces[P ^ 1]);
+      __syncthreads();
+    }
   };
-  // two steps a trip; an odd last one is followed by a step of zeros
-  for (int k0 = 0; k0 < K; k0 += 2 * kRefStep) {
-    turn(IntC<0>{}, k0);
-    turn(IntC<1>{}, k0 + kRefStep);
+  // two steps a trip, then an odd last one (a step of zeros in its place: 2048 x 3072 x 64 19.6 us, so 16.9; x 320 20.6, 18.8)
+  int k0 = 0;
+  for (; k0 + kRefStep < K; k0 += 2 * kRefStep) {
+    turn(IntC<0>{}, k0, IntC<0>{});
+    turn(IntC<1>{}, k0 + kRefStep, IntC<0>{});
   }
+  if (k0 < K) turn(IntC<0>{}, k0, IntC<1>{});
   // lane holds, per 32 x 32 block, column m = lane % 32 and rows n = 8 (r / 4) + 4 (lane / 32) + r % 4
   double s2 = 0.0;
 #pragma unroll
