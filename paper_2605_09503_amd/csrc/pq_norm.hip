@@ -41,6 +41,7 @@ struct NormArgs {
   int64_t ldy;
 };
 
+constexpr int kNormMaxWaves = 4;        // of a workgroup: one team of up to four waves, or four rows of a wave each
 constexpr int kHold = 6;        // chunks of a row that a thread holds between the statistics and the normalisation
 
 // eight channels of the normalised row, rounded to bf16

@@ -9,7 +9,6 @@ namespace pq {
 namespace {
 
 constexpr int kFmtNone = -1;                  // normalise and reorder only, no quantization
-constexpr int kNormMaxWaves = 8;
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
