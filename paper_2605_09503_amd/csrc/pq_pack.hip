@@ -176,7 +176,7 @@ int run_qgemm_packed(pq_format fmt, int group, const void* a_operand, const floa
   const OperandView A = panel_view(fmt, group, a_operand, M, K, a_ts);
   OperandView W = panel_view(fmt, group, w_operand, N, K, w_ts);
   W.bias = (const uint16_t*)bias;
-  return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false},
+  return launch_qgemm_views(fmt, group, A, W, M, N, K, Outputs{{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}},
                             choose_tile(fmt, group, M, N, K), st);
 }
 

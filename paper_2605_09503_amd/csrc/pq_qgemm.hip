@@ -43,7 +43,7 @@ namespace pq {
 // instead of alternating in phases.
 template <int FMT, int G, int BM, int BN, int WGM, int WGN, int OUT>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, OperandView W, int M, int N,
-                                                              int K, Output out,
+                                                              int K, KernelOutput<OUT> out,
                                                               int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   const float* __restrict__ a_mul = A.mul;
@@ -418,7 +418,7 @@ size_t qgemm_workspace_bytes(pq_format fmt, int group, int64_t M, int64_t N, int
 }
 
 template <int FMT, int G, int BM, int BN, int WGM, int WGN, int OUT>
-static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out,
+static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N, int K, const Outputs& out,
                        hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
   constexpr size_t shmem = 2 * (size_t)((BM * 2 + T - 1) / T * (T / 2) + BN) * kRowBytes;
@@ -433,7 +433,7 @@ static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N,
 }
 
 template <int FMT, int G, int OUT>
-static int pick_tile(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out,
+static int pick_tile(const OperandView& A, const OperandView& W, int M, int N, int K, const Outputs& out,
                      int choice, hipStream_t st) {
   if constexpr (G <= 32) {                             // larger groups: pq_qgemm_group.hip
     if (choice == kTile256) return launch_gemm<FMT, G, 256, 256, 2, 4, OUT>(A, W, M, N, K, out, st);
@@ -443,7 +443,7 @@ static int pick_tile(const OperandView& A, const OperandView& W, int M, int N, i
 }
 
 template <int FMT, int G>
-static int launch_views_fg(const OperandView& A, const OperandView& W, int M, int N, int K, const Output& out, int tile,
+static int launch_views_fg(const OperandView& A, const OperandView& W, int M, int N, int K, const Outputs& out, int tile,
                            hipStream_t st) {
   if (out.kind == kOutF32) return pick_tile<FMT, G, kOutF32>(A, W, M, N, K, out, tile, st);
   if (out.kind == kOutDiff) return pick_tile<FMT, G, kOutDiff>(A, W, M, N, K, out, tile, st);
@@ -452,7 +452,7 @@ static int launch_views_fg(const OperandView& A, const OperandView& W, int M, in
 
 // the product kernel on two operand views (any mix of layouts)
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
-                       int64_t N, int64_t K, const Output& out, int tile, hipStream_t st) {
+                       int64_t N, int64_t K, const Outputs& out, int tile, hipStream_t st) {
   if (tile >= kTileSplit32)
     return launch_qgemm_split(fmt, group, A, W, (int)M, (int)N, (int)K, out, tile, st);
   // groups of 64 and more in large tiles: the codes go to the matrix unit as they are
@@ -513,7 +513,7 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     A.marked = W.marked = mark;
   }
   if (!(phases & 2)) return PQ_OK;
-  return launch_qgemm_views(fmt, group, A, W, M, N, K, Output{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false},
+  return launch_qgemm_views(fmt, group, A, W, M, N, K, Outputs{{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}},
                             choose_tile(fmt, group, M, N, K), st);
 }
 

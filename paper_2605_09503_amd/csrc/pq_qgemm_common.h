@@ -1,6 +1,8 @@
 // Operand slices of the qgemm kernel, their loading and exact unpacking to scaled fp16 (see
 // pq_qgemm.hip for why fp16 operands carry the per-group scales exactly).
 #pragma once
+#include <type_traits>
+
 #include "pq_device.h"
 #include "pq_host.h"
 
@@ -190,8 +192,7 @@ __device__ __forceinline__ void assign_tile(int tiles_m, int tiles_n, int& tile_
 // ------------------------------------------------------------------------ epilogue
 // What becomes of the product: rounded to bf16, stored in fp32, or compared with a reference -- then only the sum of
 // (ref - product)^2 over a workgroup's tile is kept, in fp64 (each difference exact, the sum in a fixed order):
-// y[tile] = or += that sum.  A launch that compares may hold several problems of one shape and one reference, problem z in
-// blockIdx.y: its operands lie z * a_next and z * w_next bytes further on, its sums z * y_next.
+// y[tile] = or += that sum.
 enum OutKind : int { kOutBf16 = 0, kOutF32 = 1, kOutDiff = 2 };
 struct Output {
   int kind;
@@ -199,13 +200,22 @@ struct Output {
   int64_t ldy;          // kOutDiff: of ref
   const float* ref;     // kOutDiff only
   bool add;             // kOutDiff only
+};
+// A launch that compares may hold several problems of one shape and one reference, problem z in blockIdx.y: its operands
+// lie z * a_next and z * w_next bytes further on, its sums z * y_next.  Only the kernels that compare are handed these: in
+// the others the larger argument alone took the 32 x 32 tiles from 56 to 82 registers and from four workgroups a unit to
+// two (NVFP4 134 x 10981 x 320 8.6 us, 11.2 so; 73 x 6075 x 96 4.4, 5.5).
+struct Outputs : Output {
   size_t a_next = 0, w_next = 0;
   int64_t y_next = 0;
   unsigned problems = 1;
 };
+template <int OUT>
+using KernelOutput = std::conditional_t<OUT == kOutDiff, Outputs, Output>;
+static_assert(sizeof(Output) == 40, "a larger argument costs the 32 x 32 tiles their registers");
 
 // the operands and the sums of this workgroup's problem (a factor of stride 0 is a tensor scale, the same for all)
-__device__ __forceinline__ void enter_problem(OperandView& A, OperandView& W, Output& out) {
+__device__ __forceinline__ void enter_problem(OperandView& A, OperandView& W, Outputs& out) {
   const size_t z = blockIdx.y;
   auto move = [&](OperandView& v, size_t by) {
     v.codes += by;
@@ -464,7 +474,7 @@ inline OperandView panel_view(pq_format fmt, int group, const void* operand, int
 
 // the product kernel on two operand views (pq_qgemm.hip), with the given tile
 int launch_qgemm_views(pq_format fmt, int group, const OperandView& A, const OperandView& W, int64_t M,
-                       int64_t N, int64_t K, const Output& out, int tile, hipStream_t st);
+                       int64_t N, int64_t K, const Outputs& out, int tile, hipStream_t st);
 // tiles (= workgroups) of that launch
 int64_t qgemm_tiles(int tile, int64_t M, int64_t N);
 // output tiles of the product kernels (choose_tile in pq_qgemm_tile.hip)
@@ -472,9 +482,9 @@ enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kT
                   kTileSplit64Eight = 8, kTileSplit64x96Eight = 9 };     // the same two with eight waves
 // small outputs (pq_qgemm_split.hip)
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       const Output& out, int tile, hipStream_t st);
+                       const Outputs& out, int tile, hipStream_t st);
 // the integer formats' large outputs with groups of 64 and more (pq_qgemm_group.hip)
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       const Output& out, int tile, hipStream_t st);
+                       const Outputs& out, int tile, hipStream_t st);
 
 }  // namespace pq

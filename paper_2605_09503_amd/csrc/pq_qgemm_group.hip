@@ -43,7 +43,7 @@ namespace pq {
 // not hold are found.
 template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT, int WIDE>
 __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView A, OperandView W, int M, int N,
-                                                                    int K, int g_shift, Output out, int tiles_m,
+                                                                    int K, int g_shift, KernelOutput<OUT> out, int tiles_m,
                                                                     int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   constexpr int T = WGM * WGN * 64;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
 }
 
 template <bool FP4, int BM, int BN, int WGM, int WGN, int OUT, int WIDE>
-static int launch_group(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+static int launch_group(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
   constexpr int A_ROWS = (BM * 2 + T - 1) / T * (T / 2);
@@ -345,7 +345,7 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
 }
 
 template <bool FP4, int OUT, int WIDE>
-static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+static int group_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                       int choice, hipStream_t st) {
   if (choice == kTile256) return launch_group<FP4, 256, 256, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
   return launch_group<FP4, 224, 256, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
@@ -353,7 +353,7 @@ static int group_tile(const OperandView& A, const OperandView& W, int M, int N, 
 
 // INT4 and INT3 with groups of 64, 128 or 256, large tiles
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       const Output& out, int choice, hipStream_t st) {
+                       const Outputs& out, int choice, hipStream_t st) {
   const int g_shift = group == 64 ? 6 : group == 128 ? 7 : 8;
 #define PQ_ARGS (A, W, M, N, K, g_shift, out, choice, st)
   if (fmt == PQ_FMT_INT4) {

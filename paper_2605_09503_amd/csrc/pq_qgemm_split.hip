@@ -51,7 +51,7 @@ template <int TM, int TN, int WIDE, bool ROWS>
 constexpr int kSplitWaves = ROWS && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
 __global__ __launch_bounds__(KS * 64, (kSplitWaves<TM, TN, WIDE, ROWS>)) void qgemm_split_kernel(
-    OperandView A, OperandView W, int M, int N, int K, int g_shift, Output out, int tiles_m, int tiles_n) {
+    OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT> out, int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   constexpr int T = KS * 64;
   constexpr int BM = TM * 32, BN = TN * 32;
@@ -433,7 +433,7 @@ static bool rows_through_lds(int64_t n_tiles, int ks, int K) {
 }
 
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
-static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
   constexpr size_t sums = (size_t)KS * BM * (32 + 4) * 4 + (WIDE == kWideCodes ? KS * 4 : 0);
@@ -453,7 +453,7 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
 
 // the loader of the operands' layout and the shape
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
-static int split_loader(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+static int split_loader(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
   if constexpr (OUT != kOutDiff) {                     // the selection, which keeps the difference, packs its operands
     const int64_t n_tiles = (int64_t)((M + TM * 32 - 1) / (TM * 32)) * ((N + TN * 32 - 1) / (TN * 32));
@@ -464,7 +464,7 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
 }
 
 template <int MODE, int OUT, int WIDE>
-static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Output& out,
+static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                       int tile, hipStream_t st) {
   switch (tile) {
     case kTileSplit32: return split_loader<MODE, 1, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
@@ -478,7 +478,7 @@ static int split_tile(const OperandView& A, const OperandView& W, int M, int N, 
 }
 
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
-                       const Output& out, int tile, hipStream_t st) {
+                       const Outputs& out, int tile, hipStream_t st) {
   const int g_shift = fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
 #define PQ_SPLIT(MODE, WIDE)                                                                                 \
   return out.kind == kOutF32    ? split_tile<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st)      \

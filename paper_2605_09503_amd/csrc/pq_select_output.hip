@@ -354,7 +354,7 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
       // the tensor scale of the weights does not depend on the order: the caller's value is used
       const PanelJob xj{x, rows, W.x_op, x_next, W.ts}, wj{w_rows, b0 ? 0 : N, W.w_op, w_next, W.ts + 1};
       if ((rc = launch_quantize_rows_panel(fmt, group, xj, wj, K, W.cands, c0, n, st))) return rc;
-      Output out{kOutDiff, W.num + (size_t)c0 * num_stride, ldn, W.y_ref + (size_t)b0 * M * ldn, b0 > 0};
+      Outputs out{{kOutDiff, W.num + (size_t)c0 * num_stride, ldn, W.y_ref + (size_t)b0 * M * ldn, b0 > 0}};
       out.a_next = x_next;
       out.w_next = w_next;
       out.y_next = (int64_t)num_stride;
