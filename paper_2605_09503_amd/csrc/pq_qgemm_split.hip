@@ -419,7 +419,8 @@ __global__ __launch_bounds__(KS * 64, (kSplitWaves<TM, TN, WIDE, ROWS>)) void qg
   }
 }
 
-// Whether a product of row-major operands reads them through LDS.  Up to one workgroup a unit its chain of loads is what
+// Whether a product of row-major operands reads them through LDS (tiles of 64 rows with eight waves always do, see
+// split_eight).  Up to one workgroup a unit its chain of loads is what
 // takes the time, and the direct loads are two steps ahead without a barrier (INT4 g128 77 x 1000 x 1152, 96 tiles: 7.0 us
 // direct, 7.8 through LDS; 212 shapes 0.71 to 1.20).  With more, the lines of a unit's workgroups push each other out of its
 // cache before all of their quarters are read.  A first set has to be full, and a few steps have to pay for the barriers.
@@ -463,6 +464,17 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
   return launch_split<MODE, TM, TN, KS, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
 }
 
+// eight waves on 64 rows (choose_tile): row-major operands go through LDS.  The direct loads of eight waves push each other's
+// lines out of the cache: NVFP4 512 x 1650 x 3072 four waves 16.4 us, eight 18.6, eight through LDS 12.4.
+template <int MODE, int TN, int OUT, int WIDE>
+static int split_eight(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
+                       hipStream_t st) {
+  if constexpr (OUT != kOutDiff) {
+    if (!(A.panel && W.panel)) return launch_split<MODE, 2, TN, 8, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
+  }
+  return launch_split<MODE, 2, TN, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
+}
+
 template <int MODE, int OUT, int WIDE>
 static int split_tile(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                       int tile, hipStream_t st) {
@@ -470,9 +482,8 @@ static int split_tile(const OperandView& A, const OperandView& W, int M, int N, 
     case kTileSplit32: return split_loader<MODE, 1, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
     case kTileSplit64x32: return split_loader<MODE, 2, 1, 8, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
     case kTileSplit64: return split_loader<MODE, 2, 2, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
-    // no more than 256 tiles: row-major operands are read directly, see rows_through_lds
-    case kTileSplit64Eight: return launch_split<MODE, 2, 2, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
-    case kTileSplit64x96Eight: return launch_split<MODE, 2, 3, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64Eight: return split_eight<MODE, 2, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
+    case kTileSplit64x96Eight: return split_eight<MODE, 3, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
     default: return split_loader<MODE, 2, 3, 4, OUT, WIDE>(A, W, M, N, K, g_shift, out, st);
   }
 }

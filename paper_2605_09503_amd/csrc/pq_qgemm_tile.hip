@@ -44,11 +44,21 @@ static constexpr TileCost kTileCost[4][8] = {
 
 // Whether eight waves and not four share a tile of 64 x 64 or 64 x 96: where no unit has a second workgroup to run beside
 // the first, and each wave has a few steps.  A wave issues a vector instruction every five cycles at most, so one wave a SIMD
-// leaves half of the vector unit idle and two do not.  Over 90 shapes of 130 to 256 tiles, eight against four: 20 steps
-// of K and fewer 1.00 to 1.10 of the time, 21 to 25 0.95 to 1.00, 30 to 60 0.87 to 0.98, more 0.83 to 0.95 (NVFP4 405 x 1549 x
-// 2688 11.6 -> 10.4 us, 98 x 9115 x 10112 37.6 -> 31.6, INT3 g64 512 x 3072 x 3072 14.9 -> 13.8).  With 512 and 768 tiles
-// 1.15: the second workgroup covers the first one's ends.  Sixteen waves for the smaller tiles: 0.96 to 1.23.
-static bool split_eight_waves(int64_t n_tiles, int64_t K) { return n_tiles <= 256 && K > 21 * kBK; }
+// leaves half of the vector unit idle and two do not.  The lines lie where neither layout loses, as both take the sums in
+// one order.  Shapes of 112 to 256 tiles, eight against four, medians by steps of K (NVFP4, integer, INT3 codes):
+//   packed       24: 1.03 1.03 1.02   28: 1.00 1.01 0.98   36: 0.98 1.00 0.95   48: 0.96 0.99 0.93   70: 0.94 0.96 0.88
+//   row-major, rows that start at a line of the cache (K a multiple of 256), through LDS (split_eight)
+//                24: 0.80 1.00 1.00   28: 0.94 1.02 1.03   36: 0.91 1.02 1.02   48: 0.75 0.92 0.90   70: 0.75 0.83 0.77
+//   other rows   24: 1.01 1.03        28: 1.02 1.05 1.02   36: 0.94 1.05 1.06   48: 0.88 1.03 0.87   70: 0.81 0.98, up to 1.07
+// (sets of eight steps: multiples of eight are the good ones).  With the lines as here 5900 packed shapes take 0.953 of the
+// time of four waves throughout (three above 1.02), 5700 row-major ones 0.89 (98 above 1.02, at most 1.07: NVFP4 48 x 9169 x
+// 2656 10.7 -> 11.5 us).  With 512 and 768 tiles 1.15: the second workgroup covers the first one's ends.  Sixteen waves for
+// the smaller tiles: 0.96 to 1.23.
+static bool split_eight_waves(int cls, int64_t n_tiles, int64_t K) {
+  const bool lines = K % 256 == 0;
+  const int steps = cls == 0 ? (lines ? 24 : 36) : cls == 3 ? (lines ? 28 : 80) : lines ? 36 : 80;
+  return n_tiles <= 256 && K > steps * kBK;
+}
 
 // A call of several launches takes one choice for all of them: the tile and its waves fix the order of the sums over K.
 int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int problems) {
@@ -70,7 +80,7 @@ int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int p
     }
   }
   if (best == kTileSplit64 || best == kTileSplit64x96) {
-    if (split_eight_waves(qgemm_tiles(best, M, N) * problems, K)) best = best == kTileSplit64 ? kTileSplit64Eight : kTileSplit64x96Eight;
+    if (split_eight_waves(cls, qgemm_tiles(best, M, N) * problems, K)) best = best == kTileSplit64 ? kTileSplit64Eight : kTileSplit64x96Eight;
   }
   return best;
 }

@@ -38,6 +38,12 @@ def _takes(tile, fmt, g, M, N, K):
     assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile, "this shape is here for the tile it takes: choose another"
 
 
+def _split_waves(fmt, g, n_tiles, K):
+    """Waves that share a 64 x 64 or 64 x 96 tile of a launch of that many."""
+    lines = {pq.FMT_NVFP4: (24, 36)}.get(fmt, (28, 80) if fmt == pq.FMT_INT3 and g > 32 else (36, 80))
+    return 8 if n_tiles <= 256 and K > 64 * lines[K % 256 != 0] else 4
+
+
 def _rand_bits(rng, rows, K, spread=2.0, outliers=4):
     chan = np.exp(spread * 0.5 * rng.standard_normal(K))
     if outliers:
@@ -370,19 +376,19 @@ def test_select_perm_output_error_matches_oracle(name, fmt, g, M, N, K, nb):
     (pq.FMT_NVFP4, 16, 3600, 4081, 160, T256, 8), (pq.FMT_NVFP4, 16, 1500, 2056, 96, T224, 8),
     (pq.FMT_NVFP4, 16, 2304, 3656, 288, T128, 4), (pq.FMT_NVFP4, 16, 4090, 4087, 160, T128, 4),
     (pq.FMT_NVFP4, 16, 33, 36, 160, S32, 8), (pq.FMT_NVFP4, 16, 1103, 38, 160, S64X32, 8),
-    (pq.FMT_NVFP4, 16, 2300, 333, 96, S64, 4), (pq.FMT_NVFP4, 16, 300, 4087, 768, S64, 4), (pq.FMT_NVFP4, 16, 1396, 65, 1376, S64, 8),
-    (pq.FMT_NVFP4, 16, 235, 1489, 224, S64X96, 4), (pq.FMT_NVFP4, 16, 68, 3041, 1376, S64X96, 8),
+    (pq.FMT_NVFP4, 16, 2300, 333, 96, S64, 4), (pq.FMT_NVFP4, 16, 300, 4087, 768, S64, 4), (pq.FMT_NVFP4, 16, 2250, 34, 2336, S64, 8),
+    (pq.FMT_NVFP4, 16, 235, 1489, 224, S64X96, 4), (pq.FMT_NVFP4, 16, 40, 4278, 2336, S64X96, 8),
     (pq.FMT_INT3, 32, 3000, 3585, 96, T256, 8), (pq.FMT_INT4, 32, 2015, 1185, 160, T224, 8), (pq.FMT_INT4, 32, 3250, 203, 160, T128, 4),
     (pq.FMT_INT3, 32, 33, 41, 96, S32, 8), (pq.FMT_INT4, 32, 1164, 35, 160, S64X32, 8), (pq.FMT_INT3, 32, 65, 2641, 160, S64, 4),
-    (pq.FMT_INT4, 32, 1385, 66, 1440, S64, 8), (pq.FMT_INT4, 32, 1698, 129, 288, S64X96, 4),
-    (pq.FMT_INT3, 32, 36, 4194, 1376, S64X96, 8),
+    (pq.FMT_INT3, 32, 2055, 34, 2560, S64, 8), (pq.FMT_INT4, 32, 1698, 129, 288, S64X96, 4),
+    (pq.FMT_INT4, 32, 2889, 68, 2560, S64X96, 8),
     (pq.FMT_INT4, 64, 3600, 4081, 192, T256, 8), (pq.FMT_INT4, 128, 3000, 4087, 640, T256, 8), (pq.FMT_INT4, 64, 4090, 4087, 192, T256, 8),
     (pq.FMT_INT4, 256, 3929, 513, 256, T224, 8), (pq.FMT_INT4, 64, 2931, 209, 192, T128, 4), (pq.FMT_INT4, 64, 33, 37, 192, S32, 8),
     (pq.FMT_INT4, 64, 1090, 34, 192, S64X32, 8), (pq.FMT_INT4, 128, 300, 4087, 640, S64, 4), (pq.FMT_INT4, 256, 130, 3656, 768, S64, 4),
-    (pq.FMT_INT4, 64, 1370, 65, 1536, S64, 8), (pq.FMT_INT4, 64, 68, 3825, 384, S64X96, 4), (pq.FMT_INT4, 256, 35, 4163, 1536, S64X96, 8),
+    (pq.FMT_INT4, 64, 2099, 34, 5248, S64, 8), (pq.FMT_INT4, 64, 68, 3825, 384, S64X96, 4), (pq.FMT_INT4, 256, 33, 4107, 2816, S64X96, 8),
     (pq.FMT_INT3, 64, 4090, 4087, 320, T256, 8), (pq.FMT_INT3, 64, 2300, 3656, 192, T224, 8), (pq.FMT_INT3, 64, 1023, 633, 192, T128, 4),
     (pq.FMT_INT3, 256, 70, 3000, 256, S32, 8), (pq.FMT_INT3, 64, 1096, 33, 192, S64X32, 8), (pq.FMT_INT3, 256, 500, 3000, 768, S64, 4),
-    (pq.FMT_INT3, 128, 101, 2860, 640, S64X96, 4), (pq.FMT_INT3, 64, 65, 3370, 1408, S64X96, 8),
+    (pq.FMT_INT3, 128, 101, 2860, 640, S64X96, 4), (pq.FMT_INT3, 64, 2879, 67, 2048, S64X96, 8),
     # a row and its group maxima beyond 48 KB of LDS in the gathering quantizer, up to its limit
     (pq.FMT_NVFP4, 16, 40, 33, 24640, None, 0), (pq.FMT_INT4, 64, 40, 33, 24640, None, 0), (pq.FMT_INT3, 32, 9, 33, 65536, None, 0),
 ])
@@ -483,10 +489,11 @@ def test_output_error_in_several_launches(fmt, g, M, N, K, nb, n_alpha):
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K,n_alpha", [
-    # 13 orders share a launch, the last is alone in the second: 3198 tiles of 64 x 64 and 246, K of more than 21 steps
-    (pq.FMT_NVFP4, 16, 7846, 33, 1536, 13),
-    (pq.FMT_INT4, 64, 7849, 39, 1408, 13),
-    (pq.FMT_INT4, 256, 7673, 46, 1536, 13),
+    # 13 orders share a launch, the last is alone in the second: some 3100 tiles of 64 x 64 and 240, which would have eight
+    # waves in a launch of their own
+    (pq.FMT_NVFP4, 16, 7884, 43, 2304, 13),
+    (pq.FMT_INT4, 256, 7669, 33, 2816, 13),
+    (pq.FMT_INT3, 256, 7624, 36, 2048, 13),
 ])
 def test_output_error_of_equal_orders_in_launches_of_different_size(fmt, g, M, N, K, n_alpha):
     # ties go to the smallest alpha: the same order has the same error to the last bit whichever launch takes it
@@ -494,6 +501,7 @@ def test_output_error_of_equal_orders_in_launches_of_different_size(fmt, g, M, N
     tiles = -(-2 * M // plan.tile_m) * -(-N // plan.tile_n)
     alone = (n_alpha + 1) % plan.orders
     assert (plan.tile_m, plan.tile_n, plan.tile_waves) == (64, 64, 4) and alone * tiles <= 256 < plan.orders * tiles
+    assert _split_waves(fmt, g, alone * tiles, K) == 8
     gen = torch.Generator(device=DEV)
     gen.manual_seed(3 + K)
     xs = [torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
@@ -873,7 +881,7 @@ def test_qgemm_codes_on_the_matrix_unit_every_code(fmt, g, lo, hi):
     (64, 33, 41, 64, S32), (256, 70, 3000, 256, S64X32), (64, 1500, 1003, 320, S64), (256, 500, 3000, 768, S64X96),
     (256, 1500, 2056, 256, T128), (256, 2344, 3656, 512, T224), (64, 4090, 4087, 320, T256),
     (64, 300, 4090, 256, S64), (64, 515, 1003, 3200, S64X32), (64, 2000, 2050, 2048, S64X96),    # row-major through LDS
-    (64, 512, 3065, 1408, S64X96),                                                               # eight waves a tile
+    (64, 512, 3065, 1408, S64X96), (64, 259, 3858, 2048, S64X96),                                # four and eight waves a tile
 ])
 def test_qgemm_int3_multiplies_every_nibble(g, M, N, K, tile):
     # INT3 codes beyond the three bits that the quantizers write, -8 .. 7, are multiplied as they are, packed and
@@ -954,18 +962,25 @@ SPLIT_SHAPES = [
 ]
 
 
-# Tiles of 64 x 64 and 64 x 96 that eight waves share and not four: at most 256 of them and more than 21 steps of K.  Either
-# side of both lines, for each way of feeding the matrix unit; the last step half empty, steps that eight do not divide.
+# Tiles of 64 x 64 and 64 x 96 that eight waves share and not four: at most 256 of them and K beyond a line.  Either side of
+# the lines, for each way of feeding the matrix unit; rows that start at a line of the cache and rows that do not, the last
+# step half empty, steps that eight do not divide.
 EIGHT_WAVE_SHAPES = [
-    (pq.FMT_NVFP4, 16, 1000, 1023, 1376, S64), (pq.FMT_NVFP4, 16, 302, 4115, 3104, S64X96), (pq.FMT_NVFP4, 16, 500, 2040, 1344, S64),
-    (pq.FMT_NVFP4, 16, 1024, 1025, 1376, S64X96), (pq.FMT_INT4, 32, 517, 1250, 1376, S64), (pq.FMT_INT4, 64, 500, 3050, 1536, S64X96),
-    (pq.FMT_INT4, 256, 2012, 666, 1792, S64X96), (pq.FMT_INT3, 64, 512, 3065, 1408, S64X96), (pq.FMT_INT3, 32, 600, 1500, 1440, S64),
+    (pq.FMT_NVFP4, 16, 194, 3343, 2272, S64, 4), (pq.FMT_NVFP4, 16, 195, 3409, 2336, S64, 8), (pq.FMT_NVFP4, 16, 196, 3459, 1536, S64, 4),
+    (pq.FMT_NVFP4, 16, 201, 3394, 1792, S64, 8), (pq.FMT_NVFP4, 16, 302, 4115, 3104, S64X96, 8), (pq.FMT_NVFP4, 16, 500, 2040, 1344, S64, 4),
+    (pq.FMT_NVFP4, 16, 1000, 1023, 2336, S64, 8), (pq.FMT_NVFP4, 16, 1024, 1025, 1376, S64X96, 4),
+    (pq.FMT_INT4, 32, 202, 3223, 5088, S64, 4), (pq.FMT_INT4, 32, 200, 3278, 5152, S64, 8), (pq.FMT_INT3, 32, 199, 3236, 2304, S64, 4),
+    (pq.FMT_INT4, 32, 193, 3294, 2560, S64, 8), (pq.FMT_INT4, 32, 517, 1250, 1376, S64, 4), (pq.FMT_INT4, 64, 500, 3050, 2560, S64X96, 8),
+    (pq.FMT_INT4, 64, 257, 2582, 5184, S64, 8), (pq.FMT_INT4, 128, 194, 3278, 2560, S64, 8), (pq.FMT_INT4, 256, 2012, 666, 2816, S64X96, 8),
+    (pq.FMT_INT3, 64, 265, 3851, 1792, S64X96, 4), (pq.FMT_INT3, 64, 259, 3858, 2048, S64X96, 8), (pq.FMT_INT3, 128, 261, 3882, 2304, S64X96, 8),
+    (pq.FMT_INT3, 256, 265, 3915, 2816, S64X96, 8),
 ]
 
 
-@pytest.mark.parametrize("fmt,g,M,N,K,tile", EIGHT_WAVE_SHAPES)
-def test_qgemm_eight_waves_share_a_tile(fmt, g, M, N, K, tile):
+@pytest.mark.parametrize("fmt,g,M,N,K,tile,waves", EIGHT_WAVE_SHAPES)
+def test_qgemm_eight_waves_share_a_tile(fmt, g, M, N, K, tile, waves):
     _takes(tile, fmt, g, M, N, K)
+    assert _split_waves(fmt, g, -(-M // tile[0]) * -(-N // tile[1]), K) == waves
     _gemm_case(fmt, g, M, N, K, 990 + g + K)
     test_qgemm_row_major_loaders_equal_packed(fmt, g, M, N, K, tile)
 
