@@ -240,10 +240,12 @@ static int launch_qpanel_r(const void* x, int64_t rows, int64_t K, int64_t ld, c
 // Rows of a workgroup (a wave, for NVFP4) and its waves.  With thousands of rows eight of them, whole lines in and 256-byte runs
 // out, and eight waves.  With fewer rows the chip has room and a workgroup's chain of trips, a memory latency each,
 // is what a launch takes: fewer rows, so that a trip covers more of K, and as many waves as have their blocks in one trip.
-// The lines between lie where the times cross over (eight formats and groups, 17 to 4608 rows, K 512 to 12288); us, eight rows and
-// eight waves | as here: INT4 g64 122 x 6912 7.4 | 4.0, 17 x 12288 11.5 | 4.3, 512 x 3072 4.6 | 3.9, 1024 x 3072 5.5 | 4.8, 2048 x
-// 6912 10.1 | 9.4; g128 122 x 1280 3.95 | 3.2; g256 122 x 2304 5.0 | 3.3; NVFP4 256 x 512 3.0 | 2.5.  Past the lines the others
-// lose: INT4 g64 122 x 1280 3.25 | 3.7 with one trip, 4608 x 3072 10.0 | 10.5, NVFP4 2048 x 6912 7.9 | 8.1 with four rows.
+// The lines between lie where the times cross over: 43000 shapes of every format and group, 1 to 16384 rows, K 96 to 16384, take
+// 0.86 of the time of eight rows and eight waves throughout, 66 of them more than 1.05.  us, eight rows and eight waves | as
+// here: INT4 g64 122 x 6912 7.4 | 4.0, 17 x 12288 11.5 | 4.3, 512 x 3072 4.6 | 3.9, 1024 x 3072 5.5 | 4.8; g128 122 x 1280
+// 3.95 | 3.2; g256 122 x 2304 5.0 | 3.3; NVFP4 256 x 512 3.0 | 2.5.  Past the lines the others lose: INT4 g64 122 x 1280 3.25 | 3.7
+// with one trip, 2134 x 1792 4.6 | 5.0, g128 (groups of two blocks: sixteen waves with one each) 2419 x 1920 4.6 | 5.3, 960 x
+// 1920 1.08 times, g256 1253 x 4096 with four rows 1.10 times, NVFP4 four rows 4608 x 960 3.65 | 4.1, 13205 x 192 3.2 | 3.6.
 template <int FMT, int G>
 static int launch_qpanel(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts,
                          const OperandLayout& L, uint8_t* operand, uint8_t* codes, void* scales,
@@ -251,11 +253,11 @@ static int launch_qpanel(const void* x, int64_t rows, int64_t K, int64_t ld, con
   int rpw = 8;
   bool one_trip = false;
   if constexpr (FMT == kNvfp4) {
-    one_trip = rows * K < (8 << 20);
+    one_trip = rows <= 8192 && rows * K < (3 << 20);
     if (one_trip) rpw = 4;
-  } else if (rows <= 2560 && (G > 64 || K > 1536)) {
+  } else if (rows <= 2048 && (G > 64 || K > 1536) && !(G == 128 && rows > 512 && K > 1536 && K <= 3072)) {
     one_trip = true;
-    const bool few = rows <= 512, some = rows <= 1280;
+    const bool few = rows <= 512, some = rows <= 1024;
     if (G <= 64) rpw = few ? 2 : some ? 4 : 8;
     else if (G == 128) rpw = few && K > 1536 ? 2 : 8;
     else rpw = few && K > 6144 ? 2 : some ? 4 : 8;

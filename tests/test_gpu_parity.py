@@ -1390,15 +1390,18 @@ def test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad):
     assert torch.equal(got2, ref_op)
 
 
-# Either side of the lines between the quantizer's shapes (rows and waves of a workgroup): 512, 1280 and 2560 rows, K = 1536
-# and 6144, and NVFP4's 8 Mi elements; rows that a workgroup's do not divide, a K that ends in a half step, several trips.
+# Either side of the lines between the quantizer's shapes (rows and waves of a workgroup): 512, 1024 and 2048 rows, K = 1536, 3072
+# and 6144, and NVFP4's 3 Mi elements and 8192 rows; rows that a workgroup's do not divide, a K that ends in a half step,
+# several trips.
 @pytest.mark.parametrize("fmt,g,M,K,pad", [
-    (pq.FMT_INT4, 32, 511, 1568, 0), (pq.FMT_INT4, 64, 513, 1600, 8), (pq.FMT_INT3, 32, 1283, 1568, 0), (pq.FMT_INT3, 64, 2561, 1600, 0),
-    (pq.FMT_INT4, 64, 3, 12288, 0), (pq.FMT_INT4, 32, 21, 24608, 16), (pq.FMT_INT4, 64, 2559, 6912, 0),
-    (pq.FMT_INT4, 128, 510, 1536, 0), (pq.FMT_INT4, 128, 511, 1664, 0), (pq.FMT_INT3, 128, 514, 4224, 8), (pq.FMT_INT4, 128, 2563, 384, 0),
-    (pq.FMT_INT4, 256, 5, 256, 0), (pq.FMT_INT3, 256, 511, 6144, 0), (pq.FMT_INT4, 256, 511, 6400, 8), (pq.FMT_INT4, 256, 1281, 1280, 0),
-    (pq.FMT_INT4, 256, 2561, 768, 0),
-    (pq.FMT_NVFP4, 16, 13, 32, 0), (pq.FMT_NVFP4, 16, 1021, 8192, 0), (pq.FMT_NVFP4, 16, 1027, 8192, 0), (pq.FMT_NVFP4, 16, 5, 24608, 16),
+    (pq.FMT_INT4, 32, 511, 1568, 0), (pq.FMT_INT4, 64, 513, 1600, 8), (pq.FMT_INT3, 32, 1027, 1568, 0), (pq.FMT_INT3, 64, 2049, 1600, 0),
+    (pq.FMT_INT4, 64, 3, 12288, 0), (pq.FMT_INT4, 32, 21, 24608, 16), (pq.FMT_INT4, 64, 2047, 6912, 0), (pq.FMT_INT3, 32, 1283, 1568, 0),
+    (pq.FMT_INT4, 128, 510, 1536, 0), (pq.FMT_INT4, 128, 511, 1664, 0), (pq.FMT_INT3, 128, 514, 4224, 8), (pq.FMT_INT4, 128, 2049, 384, 0),
+    (pq.FMT_INT4, 128, 513, 1664, 0), (pq.FMT_INT4, 128, 2047, 3072, 0), (pq.FMT_INT3, 128, 2047, 3200, 0),
+    (pq.FMT_INT4, 256, 5, 256, 0), (pq.FMT_INT3, 256, 511, 6144, 0), (pq.FMT_INT4, 256, 511, 6400, 8), (pq.FMT_INT4, 256, 1025, 1280, 0),
+    (pq.FMT_INT4, 256, 2049, 768, 0),
+    (pq.FMT_NVFP4, 16, 13, 32, 0), (pq.FMT_NVFP4, 16, 383, 8192, 0), (pq.FMT_NVFP4, 16, 385, 8192, 0), (pq.FMT_NVFP4, 16, 5, 24608, 16),
+    (pq.FMT_NVFP4, 16, 8191, 96, 0), (pq.FMT_NVFP4, 16, 8193, 96, 0), (pq.FMT_NVFP4, 16, 1027, 8192, 0),
 ])
 def test_quantize_act_packed_where_its_shape_changes(fmt, g, M, K, pad):
     test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad)
