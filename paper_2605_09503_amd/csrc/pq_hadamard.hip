@@ -479,6 +479,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : 
     em.encT = nv4_enc_scale(em.T);
   }
   const uint16_t* xr = x + row * ld;
+  constexpr int kBatch = 3;
   if constexpr (M == 0) {
     float* slab_f = reinterpret_cast<float*>(slab);
     constexpr int kInFlight = 8;

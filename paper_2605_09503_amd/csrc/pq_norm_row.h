@@ -89,8 +89,6 @@ __device__ __forceinline__ void team_maxima(float (&v)[N], float* red, int wave,
   }
 }
 
-constexpr int kBatch = 3;                                    // chunks whose indices and gathers a thread has in flight
-
 // indices pi(j) of chunk c (clamped to an existing chunk: the address is always valid)
 __device__ __forceinline__ Idx8 load_idx(const int32_t* __restrict__ perm, int c, int k_chunks) {
   const int cc = min(c, k_chunks - 1);
@@ -122,8 +120,9 @@ struct Emit {
 };
 
 // Chunks tl, tl + 64 TEAM, ... (8 positions j each) of the reordered row: the values at pi(j) are read from the slab (bf16,
-// or fp32 to be scaled and rounded), stored and / or quantized.
-template <int FMT, int G, int TEAM, bool F32>
+// or fp32 to be scaled and rounded), stored and / or quantized.  kBatch: chunks whose indices and gathers a thread has in
+// flight; ix_cur: the indices of the first.
+template <int FMT, int G, int TEAM, bool F32, int kBatch>
 __device__ __forceinline__ void emit_row(const void* slab, const int32_t* __restrict__ perm, Idx8 (&ix_cur)[kBatch],
                                           const Emit& em) {
   constexpr bool QUANT = FMT != kFmtNone;
