@@ -275,12 +275,12 @@ int launch_norm_team(const void* x, int64_t rows, int64_t K, int64_t ld, const f
 // 512 x 3072 6.3, 5.0, 4.6; 1024 x 3072 6.7, 5.3, 6.0; 2048 x 3072 7.6, 7.2, 9.0; 8192 x 3072 20.6, 20.2, 27.3; 4608 x 1536
 // 7.7, 9.6, 12.4; 1024 x 768 4.0, 3.8, 4.8; 2048 x 6144 13.1, 10.9, 11.4; 2048 x 12288 39.9, 29.3, 21.4; modulated LayerNorm
 // 512 x 3072 6.6, 5.5, 5.1; 8192 x 3072 21.9, 22.7, 30.6; 4608 x 1536 8.6, 10.9, 14.0; 1024 x 2048 5.7, 5.0, 5.6.
-// Without a quantizer two waves share a row of more than 3072 channels however many rows there are: RMSNorm and reorder 4096 x
-// 4032 14.9, 13.6, 5200 x 3900 channels 0.83 of the time, 8192 x 3328 0.90.
-int waves_per_row(int64_t rows, int64_t K, bool quant) {
+// The same with and without a quantizer, and not two waves a row wherever the latter is faster so (more than 3072 channels: 0.83
+// to 1.0 of the time, with a quantizer 0.81 to 1.18): the statistics' sums take their order from it, and the quantizing call
+// equals norm followed by quantizer bit for bit.
+int waves_per_row(int64_t rows, int64_t K) {
   if (K > 6144) return 4;
   if (K >= 4096) return rows <= 768 ? 4 : 2;
-  if (K > 3072 && !quant) return rows <= 512 ? 4 : 2;
   if (K >= 1280) return rows <= 512 ? 4 : rows <= (K >= 2560 ? 2048 : K >= 2048 ? 1024 : 0) ? 2 : 1;
   return K >= 768 && rows <= 1024 ? 2 : 1;
 }
@@ -290,7 +290,7 @@ int launch_norm_rows(const void* x, int64_t rows, int64_t K, int64_t ld, const f
                      uint8_t* operand, const NormArgs& na, hipStream_t st) {
   // the widths that are taken, more than a row alone needs for the norms: K and the vectors' 2 K or 4 K bytes beside the row
   constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
-  int team = waves_per_row(rows, K, FMT != kFmtNone);
+  int team = waves_per_row(rows, K);
   if (rows * 64 * team > UINT32_MAX) team = 1;               // more threads than a grid holds
   const size_t least = (size_t)K * (NORM == kNormAdaLn ? 6 : 4) + (is_int ? L.units * 4 : 0) + (size_t)(K > 4096 ? 4 : 1) * 16;
   if (least > kNormLdsLimit)

@@ -320,9 +320,8 @@ def test_wide_rows_share_a_workgroup(kind, rows, K, rows_per_mod):
 @pytest.mark.parametrize("rows,K", [(512, 1024), (513, 1024), (512, 1016), (40, 1024), (513, 3072),
                                     (256, 1024), (257, 1024), (512, 1032), (513, 1032), (512, 1280), (513, 1280)])
 def test_rows_at_the_edge_of_a_short_launch(kind, rows, K):
-    """Up to 512 rows of more than 1024 channels, and 256 of 1024, are shared by four waves, the others walked by one:
-    results as the oracle's on both sides of the line, and the quantizing call still equals norm followed by
-    quantizer."""
+    """Rows and widths around the lines between one, two and four waves a row: results as the oracle's on both sides, and
+    the quantizing call still equals norm followed by quantizer."""
     rng = np.random.default_rng(9500 + rows + K + kind)
     x_bits = _activations(rng, rows, K)
     perm = rng.permutation(K).astype(np.int32)
@@ -346,7 +345,7 @@ def test_rows_at_the_edge_of_a_short_launch(kind, rows, K):
 # channels a wave), with rows of a mean far above their spread among them
 @pytest.mark.parametrize("kind", [RMS, ADALN])
 @pytest.mark.parametrize("rows,K", [(5, 760), (1024, 768), (1025, 768), (512, 1280), (513, 1280), (1024, 2048), (1025, 2048),
-                                    (2048, 2560), (2049, 2560), (2049, 3072), (2049, 3080), (2050, 4088), (768, 4096),
+                                    (2048, 2560), (2049, 2560), (2049, 3072), (2049, 3080), (2050, 4088), (2050, 3136), (2049, 4032), (768, 4096),
                                     (769, 4096), (769, 6144), (3, 6152), (3, 12288), (3, 12296)])
 def test_rows_of_one_two_and_four_waves(kind, rows, K):
     _say("norm waves kind=%d rows=%d K=%d" % (kind, rows, K))
