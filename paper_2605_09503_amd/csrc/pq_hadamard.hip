@@ -534,7 +534,9 @@ int launch_hadamard_team(const void* x, int64_t rows, int64_t K, int64_t ld, con
                          uint8_t* operand, const HadamardArgs& ha, hipStream_t st) {
   constexpr bool is_int = FMT == kInt4 || FMT == kInt3;
   auto kern = hadamard_rows_kernel<FMT, G, TEAM, M, WIDE>;
-  const int n_waves = TEAM > 1 ? TEAM : rows > 1024 ? 4 : 1;
+  // rows of a wave each: four a workgroup write more of a line together, one spreads few rows best (general path, reorder
+  // alone: 1250 x 256 four a workgroup 4.5 us, one 4.1)
+  const int n_waves = TEAM > 1 ? TEAM : rows > (M == 0 ? 1536 : 1024) ? 4 : 1;
   const int teams = TEAM == 1 ? n_waves : 1;
   const size_t shmem = (size_t)teams * (K * (M == 0 ? 4 : TEAM == 1 ? 2 : 6) + (is_int ? L.units * 4 : 0)) + (size_t)n_waves * 16;
   static std::atomic<uint64_t> raised{0};
