@@ -721,7 +721,8 @@ __global__ __launch_bounds__(256) void select_tail_kernel(TailArgs a, double* __
   if (threadIdx.x == 0) out[dst] = sum.value();
 }
 
-// Launch shape of the error evaluation of n_cand orders for `rows` rows per tensor of width K.
+// Launch shape of the error evaluation of n_cand orders for `rows` rows per tensor of width K; most_rows: those of the tensor
+// of the call that has most.
 struct QeShape {
   QeRows kind;
   int r;                 // rows resident in LDS together (2 or 4)
@@ -733,7 +734,7 @@ struct QeShape {
   int parts() const { return blocks * (threads / 64); }    // partial sums per tensor and candidate
 };
 
-static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n_tensors, int n_cand) {
+static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n_tensors, int n_cand, int64_t most_rows) {
   QeShape q;
   const bool nv = fmt == PQ_FMT_NVFP4;
   const int chunk = nv ? QeChunk<kNvfp4>::value : QeChunk<kInt4>::value;
@@ -744,10 +745,12 @@ static QeShape qe_shape(pq_format fmt, int group, int64_t rows, int64_t K, int n
   // rows of fp32: INT4 g64 1024 + 1024 + 1024 rows of 12288 160 -> 151 us, g32 2 x 1500 + 2000 of 16384 228 -> 216), which share
   // a group's scale arithmetic over four rows; NVFP4, which does not, two rows of fp32 (2 x 1500 + 2000 of 16384 210
   // against 218, 3 x 4608 + 3072 of 10240 357 against 366, 8 x 4608 + 3072 of 12288 883 against 874).  Wider still two rows of
-  // bf16 instead of one of fp32: INT4 g256 512 + 512 of 20480 290 -> 256, NVFP4 1500 + 2000 of 32768 380 -> 364.
-  q.kind = slots * QeWide4::channel_bytes <= kQeLds   ? kQeWide4
-           : slots * QeWide2::channel_bytes <= kQeLds ? (nv ? kQeWide2 : kQePacked4)
-                                                      : kQePacked2;
+  // bf16 instead of one of fp32: INT4 g256 512 + 512 of 20480 290 -> 256, NVFP4 1500 + 2000 of 32768 380 -> 364.  So where the
+  // call's tensors have no more than two rows, half of four would be zeros: INT4 g256 2 x 15616 11.2 -> 9.3 us.
+  q.kind = slots * QeWide4::channel_bytes <= kQeLds                     ? kQeWide4
+           : slots * QeWide2::channel_bytes <= kQeLds && nv             ? kQeWide2
+           : slots * QeWide2::channel_bytes <= kQeLds && most_rows > 2  ? kQePacked4
+                                                                        : kQePacked2;
   q.r = q.kind == kQeWide4 || q.kind == kQePacked4 ? 4 : 2;
   q.slot = q.kind == kQeWide4 ? QeWide4::channel_bytes : q.kind == kQePacked2 ? QePacked2::channel_bytes : QeWide2::channel_bytes;
   q.shmem = slots * q.slot;
@@ -885,7 +888,7 @@ int run_quant_error(pq_format fmt, int group, const void* x, int64_t rows, int64
   double* part = (double*)ws;
   TensorList tl;
   for (int b = 0; b < kMaxMomentBatches; ++b) tl.p[b] = (const uint16_t*)x;
-  const QeShape q = qe_shape(fmt, group, rows, K, 1, 1);
+  const QeShape q = qe_shape(fmt, group, rows, K, 1, 1, rows);
   int32_t* offs = nullptr;
   if (perm) {
     offs = (int32_t*)((char*)ws + align_up((size_t)kQeParts(rows) * 8, 256));
@@ -1009,8 +1012,10 @@ int run_select(pq_format fmt, int group, const double* act_sumsq, const double* 
   const int n_cand = n_alpha + 1;            // candidate 0 is the original order
   int rc;
   // activations: all batches of a launch share one grid (up to kMaxMomentBatches per launch)
-  const QeShape qa = qe_shape(fmt, group, M, K, n_batches < kMaxMomentBatches ? n_batches : kMaxMomentBatches, n_cand);
-  const QeShape qw = qe_shape(fmt, group, N, K, 1, n_cand);       // the same resident rows (a function of K): one set of offsets
+  const int64_t most_rows = M > N ? M : N;
+  const QeShape qa = qe_shape(fmt, group, M, K, n_batches < kMaxMomentBatches ? n_batches : kMaxMomentBatches, n_cand,
+                              most_rows);
+  const QeShape qw = qe_shape(fmt, group, N, K, 1, n_cand, most_rows);       // the same resident rows: one set of offsets
   if ((rc = launch_candidate_orders(act_sumsq, w_sumsq, K, alphas, n_alpha, W.keys, W.rank, W.cands, st, W.offs,
                                     qa.slot, W.same_as)))
     return rc;

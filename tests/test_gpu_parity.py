@@ -557,6 +557,21 @@ def test_e4m3_scale_bytes_around_every_midpoint():
         np.testing.assert_allclose(err.item(), OC.squared_error(pq.FMT_NVFP4, 16, x64, None, T_), rtol=T.ERRSUM_RTOL)
 
 
+@pytest.mark.parametrize("M,N", [(2, 1), (2, 3), (5, 2), (1, 2)])
+def test_select_perm_of_one_to_five_wide_rows(M, N):
+    # the rows of both operands lie in LDS in one way, two of bf16 where neither has more, else four
+    fmt, g, K = pq.FMT_INT4, 64, 12288
+    rng = np.random.default_rng(120 + M + 10 * N)
+    xb, wb = _rand_bits(rng, M, K), _rand_bits(rng, N, K)
+    xs, w = [_to_dev(xb)], _to_dev(wb)
+    sa, sw, _, _ = _gpu_moments(xs, w, K)
+    perm = torch.empty(K, dtype=torch.int32, device=DEV)
+    rep = pq.pq_select_perm(fmt, g, sa, sw, xs, w, 1.0, 1.0, perm)
+    x64, w64 = OF.bf16_bits_to_f64(xb), OF.bf16_bits_to_f64(wb)
+    ref = OC.select_permutation(fmt, g, [x64], w64)
+    np.testing.assert_allclose([rep.e_orig] + rep.e_cand, [ref.e_orig] + list(ref.e_cand), rtol=T.ERRSUM_RTOL)
+
+
 def test_select_perm_candidates_and_ties():
     # equal second moments: the sort must keep ascending channel index (stable)
     K, M, N = 256, 32, 32
@@ -631,6 +646,8 @@ def test_quant_error_launch_variants(fmt, g, rows, K):
     (pq.FMT_NVFP4, 16, 1, 34128, 1.0), (pq.FMT_INT4, 32, 5, 8512, 1.0), (pq.FMT_INT4, 32, 9, 8544, 1.0),
     (pq.FMT_INT3, 64, 17, 8576, 1.0), (pq.FMT_INT4, 128, 6, 12416, 1.0), (pq.FMT_INT3, 256, 3, 16896, 1.0),
     (pq.FMT_INT3, 32, 2, 17056, 1.0), (pq.FMT_INT4, 32, 3, 17088, 1.0), (pq.FMT_INT4, 256, 5, 33792, 1.0),
+    # no more than two rows: two of bf16 below 17066, too
+    (pq.FMT_INT4, 64, 2, 8576, 1.0), (pq.FMT_INT4, 64, 2, 8512, 1.0), (pq.FMT_INT3, 256, 1, 15872, 1.0), (pq.FMT_INT4, 128, 3, 15872, 1.0),
 ])
 def test_quant_error_where_rows_lie_otherwise(fmt, g, rows, K, shrink):
     rng = np.random.default_rng(77 + K + rows)
