@@ -202,9 +202,8 @@ struct Output {
   bool add;             // kOutDiff only
 };
 // A launch that compares may hold several problems of one shape and one reference, problem z in blockIdx.y: its operands
-// lie z * a_next and z * w_next bytes further on, its sums z * y_next.  Only the kernels that compare are handed these: in
-// the others the larger argument alone took the 32 x 32 tiles from 56 to 82 registers and from four workgroups a unit to
-// two (NVFP4 134 x 10981 x 320 8.6 us, 11.2 so; 73 x 6075 x 96 4.4, 5.5).
+// lie z * a_next and z * w_next bytes further on, its sums z * y_next.  Only the kernels that compare are handed these: the
+// larger argument alone changes how many registers the compiler gives the others (see FEW in pq_qgemm_split.hip).
 struct Outputs : Output {
   size_t a_next = 0, w_next = 0;
   int64_t y_next = 0;
@@ -212,7 +211,7 @@ struct Outputs : Output {
 };
 template <int OUT>
 using KernelOutput = std::conditional_t<OUT == kOutDiff, Outputs, Output>;
-static_assert(sizeof(Output) == 40, "a larger argument costs the 32 x 32 tiles their registers");
+static_assert(sizeof(Output) == 40, "a larger argument has changed the registers of the 32 x 32 tiles");
 
 // the operands and the sums of this workgroup's problem (a factor of stride 0 is a tensor scale, the same for all)
 __device__ __forceinline__ void enter_problem(OperandView& A, OperandView& W, Outputs& out) {

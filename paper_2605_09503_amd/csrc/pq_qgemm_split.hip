@@ -49,8 +49,11 @@ typedef uint32_t uint32_any __attribute__((aligned(2)));              // two sca
 // WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
 template <int TM, int TN, int WIDE, bool ROWS>
 constexpr int kSplitWaves = ROWS && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
-template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
-__global__ __launch_bounds__(KS * 64, (kSplitWaves<TM, TN, WIDE, ROWS>)) void qgemm_split_kernel(
+// FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 82 instead
+// of 56, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW>
+__global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitWaves<TM, TN, WIDE, ROWS>, FEW ? 4 : 8))) void
+qgemm_split_kernel(
     OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT> out, int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   constexpr int T = KS * 64;
@@ -433,7 +436,7 @@ static bool rows_through_lds(int64_t n_tiles, int ks, int K) {
   return n_tiles > 256 && K >= (ks == 8 ? 8 : K % 256 == 0 ? 4 : 6) * kBK;
 }
 
-template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS>
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW = false>
 static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
@@ -441,7 +444,7 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   constexpr size_t sets = ROWS ? 2 * (size_t)RowSet<TM, TN, KS>::kBytes : 0;
   constexpr size_t shmem = sums > sets ? sums : sets;
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
-  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE, ROWS>;
+  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE, ROWS, FEW>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_split_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -452,16 +455,23 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   return check_hip(hipGetLastError(), "qgemm_split_kernel");
 }
 
-// the loader of the operands' layout and the shape
+// The loader of the operands' layout and the shape.  FEW as long as two workgroups a unit hold the launch: NVFP4 109 x 140 x
+// 4928 (20 tiles) 12.7 us, FEW 12.2, 43 x 3659 x 10240 (230) 20.9, 19.9, 134 x 10981 x 320 (1720) 8.6, 11.2.  12500 shapes of these
+// tiles against FEW throughout 0.997 (0.81 to 0.95 beyond 512 tiles), 13300 against none 0.991.
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
 static int split_loader(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
+  const int64_t n_tiles = (int64_t)((M + TM * 32 - 1) / (TM * 32)) * ((N + TN * 32 - 1) / (TN * 32));
   if constexpr (OUT != kOutDiff) {                     // the selection, which keeps the difference, packs its operands
-    const int64_t n_tiles = (int64_t)((M + TM * 32 - 1) / (TM * 32)) * ((N + TN * 32 - 1) / (TN * 32));
     if (!(A.panel && W.panel) && rows_through_lds(n_tiles, KS, K))
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
   }
-  return launch_split<MODE, TM, TN, KS, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
+  constexpr bool kMayBeFew = TN == 1 && MODE != kSplitE2m1, kFew = kMayBeFew && TM == 2;
+  if constexpr (kMayBeFew && TM == 1) {
+    if (n_tiles * out.problems <= 512)
+      return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, true>(A, W, M, N, K, g_shift, out, st);
+  }
+  return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, kFew>(A, W, M, N, K, g_shift, out, st);
 }
 
 // eight waves on 64 rows (choose_tile): row-major operands go through LDS.  The direct loads of eight waves push each other's

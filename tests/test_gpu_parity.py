@@ -1002,6 +1002,17 @@ def test_qgemm_eight_waves_share_a_tile(fmt, g, M, N, K, tile, waves):
     test_qgemm_row_major_loaders_equal_packed(fmt, g, M, N, K, tile)
 
 
+# 512 tiles of 32 x 32, which two workgroups a unit hold, and a few more
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_NVFP4, 16, 31, 16383, 160, S32), (pq.FMT_NVFP4, 16, 63, 8223, 160, S32), (pq.FMT_INT4, 64, 31, 16383, 192, S32),
+    (pq.FMT_INT4, 128, 127, 4127, 128, S32), (pq.FMT_INT3, 32, 255, 2079, 96, S32),
+])
+def test_qgemm_either_side_of_two_workgroups_a_unit(fmt, g, M, N, K, tile):
+    _takes(tile, fmt, g, M, N, K)
+    _gemm_case(fmt, g, M, N, K, 780 + g + K)
+    test_qgemm_row_major_loaders_equal_packed(fmt, g, M, N, K, tile)
+
+
 @pytest.mark.parametrize("fmt,g,M,N,K,tile", SPLIT_SHAPES)
 def test_qgemm_waves_split_k(fmt, g, M, N, K, tile):
     _takes(tile, fmt, g, M, N, K)
