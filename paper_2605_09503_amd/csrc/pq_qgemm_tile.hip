@@ -3,8 +3,8 @@
 
 namespace pq {
 
-// The tile with the shortest predicted time of `problems` products of that shape in one launch.  n workgroups run on 256 compute units, each does s 64-wide steps; with
-// c = ceil(n / 256) rounds and r = max(n / 256, 1) of them really filled,
+// The tile with the shortest predicted time of `problems` products of that shape in one launch.  n workgroups run on 256
+// compute units, each does s 64-wide steps; with c = ceil(n / 256) rounds and r = max(n / 256, 1) of them really filled,
 //     time = l0 + odd (N mod 8) + max(rounds (a + b s), l1 s),  rounds = th c + (1 - th) r,
 // where l1 s is the latency of one workgroup's chain of steps in the tiles whose workgroups share a unit, and odd the
 // stores of the columns past the last whole eight, one by one in the workgroups of the right edge (3.5 to 10 us of a
@@ -13,10 +13,11 @@ namespace pq {
 // The coefficients (us) are least-squares fits of the logarithm of measured times, graph replays, over 1285 shapes of
 // 1e7 to 7e11 operations: NVFP4 303, INT4 and INT3 982 with groups of 32, 64, 128 and 256, 16 to 8192 rows, 128 to 12288
 // columns, K 96 to 12288, a quarter of them round sizes, half of them where a round of large tiles is partly or
-// just filled; then moved by at most 4 % a tile so that the choices cost least.  The choice costs 0.3 % over the
-// best tile of a shape in the mean (at most 19 %), and 0.4 % over 393 shapes it had not seen when it was made from the other 892.
-// Against the choice by rounds of 256-, 224- and 128-row tiles that all shapes took once, 13 of the 1285 are slower by
-// more than 2 %.  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
+// just filled; then moved by at most 4 % a tile so that the choices cost least.  They were fitted with four waves a 64 x 64
+// and 64 x 96 tile, to single products: what eight waves take (below) and launches of several problems is not in them.
+// Measured with the kernels as they are, all tiles of 16820 random shapes of these ranges, packed: the choice costs 0.55 %
+// over the best tile in the mean, more than 5 % for 4.6 % of them, at most 1.24 (INT3 g64 535 x 4937 x 192, 128 x 128 9.2 us, 64 x
+// 64 7.4).  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
 // 1024 x 3072 22 | 30 (of 128 x 128), 2048 x 3072 41 | 47, 4608 x 3072 92 | 79.
 struct TileCost {
   float a, b, l0, l1, th, odd;
@@ -44,19 +45,20 @@ static constexpr TileCost kTileCost[4][8] = {
 
 // Whether eight waves and not four share a tile of 64 x 64 or 64 x 96: where no unit has a second workgroup to run beside
 // the first, and each wave has a few steps.  A wave issues a vector instruction every five cycles at most, so one wave a SIMD
-// leaves half of the vector unit idle and two do not.  The lines lie where neither layout loses, as both take the sums in
-// one order.  Shapes of 112 to 256 tiles, eight against four, medians by steps of K (NVFP4, integer, INT3 codes):
+// leaves half of the vector unit idle and two do not.  Both layouts take the sums in one order, so a
+// line is one for both; where a few steps more let packed operands gain and row-major ones not yet, it lies between.
+// Shapes of 112 to 256 tiles, eight against four, medians by steps of K (NVFP4, integer, INT3 codes):
 //   packed       24: 1.03 1.03 1.02   28: 1.00 1.01 0.98   36: 0.98 1.00 0.95   48: 0.96 0.99 0.93   70: 0.94 0.96 0.88
 //   row-major, rows that start at a line of the cache (K a multiple of 256), through LDS (split_eight)
 //                24: 0.80 1.00 1.00   28: 0.94 1.02 1.03   36: 0.91 1.02 1.02   48: 0.75 0.92 0.90   70: 0.75 0.83 0.77
 //   other rows   24: 1.01 1.03        28: 1.02 1.05 1.02   36: 0.94 1.05 1.06   48: 0.88 1.03 0.87   70: 0.81 0.98, up to 1.07
-// (sets of eight steps: multiples of eight are the good ones).  With the lines as here 5900 packed shapes take 0.953 of the
-// time of four waves throughout (three above 1.02), 5700 row-major ones 0.89 (98 above 1.02, at most 1.07: NVFP4 48 x 9169 x
-// 2656 10.7 -> 11.5 us).  With 512 and 768 tiles 1.15: the second workgroup covers the first one's ends.  Sixteen waves for
-// the smaller tiles: 0.96 to 1.23.
+// (sets of eight steps: multiples of eight are the good ones).  With the lines as here 2700 packed shapes take 0.955 of the
+// time of four waves throughout (16 above 1.02), 2600 row-major ones 0.89 (70 above 1.02, at most 1.10: INT4 g128 1712 x 356
+// x 4224 17.7 -> 19.4 us).  With 512 and 768 tiles 1.15: the second workgroup covers the first one's ends.  Sixteen waves for the
+// smaller tiles: 0.96 to 1.23.
 static bool split_eight_waves(int cls, int64_t n_tiles, int64_t K) {
   const bool lines = K % 256 == 0;
-  const int steps = cls == 0 ? (lines ? 24 : 36) : cls == 3 ? (lines ? 28 : 80) : lines ? 36 : 80;
+  const int steps = cls == 0 ? (lines ? 24 : 36) : cls == 3 ? (lines ? 28 : 44) : lines ? 36 : 56;
   return n_tiles <= 256 && K > steps * kBK;
 }
 

@@ -40,7 +40,7 @@ def _takes(tile, fmt, g, M, N, K):
 
 def _split_waves(fmt, g, n_tiles, K):
     """Waves that share a 64 x 64 or 64 x 96 tile of a launch of that many."""
-    lines = {pq.FMT_NVFP4: (24, 36)}.get(fmt, (28, 80) if fmt == pq.FMT_INT3 and g > 32 else (36, 80))
+    lines = {pq.FMT_NVFP4: (24, 36)}.get(fmt, (28, 44) if fmt == pq.FMT_INT3 and g > 32 else (36, 56))
     return 8 if n_tiles <= 256 and K > 64 * lines[K % 256 != 0] else 4
 
 
@@ -986,11 +986,11 @@ EIGHT_WAVE_SHAPES = [
     (pq.FMT_NVFP4, 16, 194, 3343, 2272, S64, 4), (pq.FMT_NVFP4, 16, 195, 3409, 2336, S64, 8), (pq.FMT_NVFP4, 16, 196, 3459, 1536, S64, 4),
     (pq.FMT_NVFP4, 16, 201, 3394, 1792, S64, 8), (pq.FMT_NVFP4, 16, 302, 4115, 3104, S64X96, 8), (pq.FMT_NVFP4, 16, 500, 2040, 1344, S64, 4),
     (pq.FMT_NVFP4, 16, 1000, 1023, 2336, S64, 8), (pq.FMT_NVFP4, 16, 1024, 1025, 1376, S64X96, 4),
-    (pq.FMT_INT4, 32, 202, 3223, 5088, S64, 4), (pq.FMT_INT4, 32, 200, 3278, 5152, S64, 8), (pq.FMT_INT3, 32, 199, 3236, 2304, S64, 4),
+    (pq.FMT_INT4, 32, 202, 3223, 3552, S64, 4), (pq.FMT_INT4, 32, 200, 3278, 3616, S64, 8), (pq.FMT_INT3, 32, 199, 3236, 2304, S64, 4),
     (pq.FMT_INT4, 32, 193, 3294, 2560, S64, 8), (pq.FMT_INT4, 32, 517, 1250, 1376, S64, 4), (pq.FMT_INT4, 64, 500, 3050, 2560, S64X96, 8),
-    (pq.FMT_INT4, 64, 257, 2582, 5184, S64, 8), (pq.FMT_INT4, 128, 194, 3278, 2560, S64, 8), (pq.FMT_INT4, 256, 2012, 666, 2816, S64X96, 8),
+    (pq.FMT_INT4, 64, 257, 2582, 3648, S64, 8), (pq.FMT_INT4, 64, 257, 2582, 3520, S64, 4), (pq.FMT_INT4, 128, 194, 3278, 2560, S64, 8), (pq.FMT_INT4, 256, 2012, 666, 2816, S64X96, 8),
     (pq.FMT_INT3, 64, 265, 3851, 1792, S64X96, 4), (pq.FMT_INT3, 64, 259, 3858, 2048, S64X96, 8), (pq.FMT_INT3, 128, 261, 3882, 2304, S64X96, 8),
-    (pq.FMT_INT3, 256, 265, 3915, 2816, S64X96, 8),
+    (pq.FMT_INT3, 256, 265, 3915, 2816, S64X96, 8), (pq.FMT_INT3, 64, 261, 3882, 2752, S64X96, 4), (pq.FMT_INT3, 64, 259, 3858, 2880, S64X96, 8),
 ]
 
 
