@@ -15,9 +15,9 @@ namespace pq {
 // columns, K 96 to 12288, a quarter of them round sizes, half of them where a round of large tiles is partly or
 // just filled; then moved by at most 4 % a tile so that the choices cost least.  They were fitted with four waves a 64 x 64
 // and 64 x 96 tile, to single products: what eight waves take (below) and launches of several problems is not in them.
-// Measured with the kernels as they are, all tiles of 16820 random shapes of these ranges, packed: the choice costs 0.55 %
-// over the best tile in the mean, more than 5 % for 4.6 % of them, at most 1.24 (INT3 g64 535 x 4937 x 192, 128 x 128 9.2 us, 64 x
-// 64 7.4).  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
+// Measured with the kernels as they are, all tiles of 10900 random shapes of these ranges, packed: the choice costs 0.54 %
+// over the best tile in the mean, more than 5 % for 4.3 % of them, at most 21 % (INT4 g32 132 x 11376 x 160, 128 x 128 8.9 us, 64 x
+// 64 7.3).  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
 // 1024 x 3072 22 | 30 (of 128 x 128), 2048 x 3072 41 | 47, 4608 x 3072 92 | 79.
 struct TileCost {
   float a, b, l0, l1, th, odd;
