@@ -165,8 +165,8 @@ int pq_tensor_scale(const float* absmax, float* tensor_scale_out, void* stream);
  * w_bf16: bf16 [N, K] contiguous.
  * act_tensor_scale / w_tensor_scale: NVFP4 only (host floats, T of the header comment; the
  * activation one comes from the calibration absmax, the weight one from max|W|); ignored for INT.
- * K <= 34128: one row as fp32 must fit the LDS of the error evaluation (4.5 K bytes of 150 KB);
- * pq_workspace_bytes returns 0 beyond, the call PQ_ERR_SHAPE before anything is launched.
+ * K <= 34128: two rows, as bf16 in one 32-bit slot a channel, must fit the LDS of the error evaluation
+ * (4.5 K bytes of 150 KB); pq_workspace_bytes returns 0 beyond, the call PQ_ERR_SHAPE before anything is launched.
  * alphas: HOST array of n_alpha values in [0, 1], 1 <= n_alpha <= PQ_MAX_ALPHAS.
  * perm_out: int32 [K] device.  report: HOST struct, filled on return.
  * This call synchronises `stream` once before returning (the decision is taken on the host).

@@ -84,8 +84,8 @@ int choose_tile(pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int p
 void tile_size(int tile, int* bm, int* bn);
 int tile_waves(int tile);
 
-// The error evaluation keeps one row as fp32 in LDS, one spare slot per eight channels: 4.5 K bytes of the
-// 150 KB a workgroup may take.
+// The widest rows of the error evaluation lie two together in LDS, as bf16 in one 32-bit slot a channel and one spare
+// slot per eight channels: 4.5 K bytes of the 150 KB a workgroup may take.
 constexpr int64_t kSelectMaxK = 34128;      // largest multiple of 16 with 4.5 K <= 150 * 1024
 size_t select_workspace_bytes(int64_t M, int64_t N, int64_t K, int n_batches);
 size_t quant_error_workspace_bytes(int64_t rows, int64_t K);
