@@ -237,6 +237,14 @@ static int launch_qpanel_r(const void* x, int64_t rows, int64_t K, int64_t ld, c
   return check_hip(hipGetLastError(), "quantize_panel_kernel");
 }
 
+// Workgroups of an NVFP4 launch with eight rows a wave (launch_qpanel_r without one_trip)
+static int64_t nv4_workgroups(int64_t rows, int64_t steps) {
+  const int64_t wgs = (rows + 31) / 32;
+  int k_split = 1;
+  while (wgs * k_split < 2048 && steps / (k_split * 2) >= 3) k_split *= 2;
+  return wgs * k_split;
+}
+
 // Rows of a workgroup (a wave, for NVFP4) and its waves.  With thousands of rows eight of them, whole lines in and 256-byte runs
 // out, and eight waves.  With fewer rows the chip has room and a workgroup's chain of trips, a memory latency each,
 // is what a launch takes: fewer rows, so that a trip covers more of K, and as many waves as have their blocks in one trip.
@@ -245,7 +253,12 @@ static int launch_qpanel_r(const void* x, int64_t rows, int64_t K, int64_t ld, c
 // here: INT4 g64 122 x 6912 7.4 | 4.0, 17 x 12288 11.5 | 4.3, 512 x 3072 4.6 | 3.9, 1024 x 3072 5.5 | 4.8; g128 122 x 1280
 // 3.95 | 3.2; g256 122 x 2304 5.0 | 3.3; NVFP4 256 x 512 3.0 | 2.5.  Past the lines the others lose: INT4 g64 122 x 1280 3.25 | 3.7
 // with one trip, 2134 x 1792 4.6 | 5.0, g128 (groups of two blocks: sixteen waves with one each) 2419 x 1920 4.6 | 5.3, 960 x
-// 1920 1.08 times, g256 1253 x 4096 with four rows 1.10 times, NVFP4 four rows 4608 x 960 3.65 | 4.1, 13205 x 192 3.2 | 3.6.
+// 1920 1.08 times, g256 1253 x 4096 with four rows 1.10 times, NVFP4 four rows 13205 x 192 3.2 | 3.6.  NVFP4 crosses over where eight
+// rows fill the chip, about 700 workgroups: 1100 shapes of 3 to 8 Mi elements, four rows against eight, by workgroups of the
+// latter 200 to 400 0.87, 500 0.95, 700 1.00, 900 1.03, 1200 1.07 (1199 x 2688, 304, 3.45 | 4.1; 2048 x 3776, 1024, 5.4 | 4.8).
+// Beyond 8192 rows about 350: 9367 x 224 3.3 | 3.8, 45 shapes up to there 0.86 to 1.03, 12480 x 192 (390) 1.13.
+// 2049 to 2560 rows in one trip: g256 768 to 1280 wide 0.72 to 0.86, 3072 and wider 1.05 to 1.13; g128 up to 512 0.88, 1664 1.13.
+// 1025 to 1280 rows, four against eight: g256 up to 1280 0.95, 3072 1.13; g32 9216 and wider 0.95, 3072 0.95, 4928 1.07.
 template <int FMT, int G>
 static int launch_qpanel(const void* x, int64_t rows, int64_t K, int64_t ld, const float* ts,
                          const OperandLayout& L, uint8_t* operand, uint8_t* codes, void* scales,
@@ -253,11 +266,13 @@ static int launch_qpanel(const void* x, int64_t rows, int64_t K, int64_t ld, con
   int rpw = 8;
   bool one_trip = false;
   if constexpr (FMT == kNvfp4) {
-    one_trip = rows <= 8192 && rows * K < (3 << 20);
+    one_trip = rows * K < (8 << 20) && nv4_workgroups(rows, L.steps) < (rows <= 8192 ? 700 : 350);
     if (one_trip) rpw = 4;
-  } else if (rows <= 2048 && (G > 64 || K > 1536) && !(G == 128 && rows > 512 && K > 1536 && K <= 3072)) {
+  } else if (rows <= ((G == 256 && K < 3072) || (G == 128 && K <= 512) ? 2560 : 2048) && (G > 64 || K > 1536) &&
+             !(G == 128 && rows > 512 && K > 1536 && K <= 3072)) {
     one_trip = true;
-    const bool few = rows <= 512, some = rows <= 1024;
+    const bool to_1280 = G == 256 ? K <= 1280 : K >= 9216 || (K >= 2560 && K <= 3072);
+    const bool few = rows <= 512, some = rows <= (to_1280 ? 1280 : 1024);
     if (G <= 64) rpw = few ? 2 : some ? 4 : 8;
     else if (G == 128) rpw = few && K > 1536 ? 2 : 8;
     else rpw = few && K > 6144 ? 2 : some ? 4 : 8;

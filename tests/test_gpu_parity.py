@@ -1418,8 +1418,8 @@ def test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad):
     assert torch.equal(got2, ref_op)
 
 
-# Either side of the lines between the quantizer's shapes (rows and waves of a workgroup): 512, 1024 and 2048 rows, K = 1536, 3072
-# and 6144, and NVFP4's 3 Mi elements and 8192 rows; rows that a workgroup's do not divide, a K that ends in a half step,
+# Either side of the lines between the quantizer's shapes (rows and waves of a workgroup): 512, 1024, 1280, 2048 and 2560 rows, K = 512,
+# 1280, 1536, 3072, 6144 and 9216, and NVFP4's 700 (8192 rows and more: 350) workgroups of eight rows a wave and 8 Mi elements; rows that a workgroup's do not divide, a K that ends in a half step,
 # several trips.
 @pytest.mark.parametrize("fmt,g,M,K,pad", [
     (pq.FMT_INT4, 32, 511, 1568, 0), (pq.FMT_INT4, 64, 513, 1600, 8), (pq.FMT_INT3, 32, 1027, 1568, 0), (pq.FMT_INT3, 64, 2049, 1600, 0),
@@ -1430,6 +1430,10 @@ def test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad):
     (pq.FMT_INT4, 256, 2049, 768, 0),
     (pq.FMT_NVFP4, 16, 13, 32, 0), (pq.FMT_NVFP4, 16, 383, 8192, 0), (pq.FMT_NVFP4, 16, 385, 8192, 0), (pq.FMT_NVFP4, 16, 5, 24608, 16),
     (pq.FMT_NVFP4, 16, 8191, 96, 0), (pq.FMT_NVFP4, 16, 8193, 96, 0), (pq.FMT_NVFP4, 16, 1027, 8192, 0),
+    (pq.FMT_INT4, 256, 2559, 768, 0), (pq.FMT_INT3, 256, 2561, 768, 0), (pq.FMT_INT4, 256, 2049, 3072, 0), (pq.FMT_INT4, 256, 1279, 1280, 0),
+    (pq.FMT_INT3, 128, 2559, 512, 0), (pq.FMT_INT4, 128, 2561, 512, 0), (pq.FMT_INT4, 64, 1279, 3072, 8), (pq.FMT_INT4, 32, 1281, 3072, 0),
+    (pq.FMT_INT3, 32, 1027, 9248, 0), (pq.FMT_NVFP4, 16, 1375, 4096, 0), (pq.FMT_NVFP4, 16, 1377, 4096, 0),
+    (pq.FMT_NVFP4, 16, 11167, 224, 0), (pq.FMT_NVFP4, 16, 11169, 224, 0), (pq.FMT_NVFP4, 16, 2047, 4128, 0),
 ])
 def test_quantize_act_packed_where_its_shape_changes(fmt, g, M, K, pad):
     test_quantize_act_packed_equals_quantize_then_pack(fmt, g, M, K, pad)
