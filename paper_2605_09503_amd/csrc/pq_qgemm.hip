@@ -46,9 +46,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
                                                               int K, KernelOutput<OUT> out,
                                                               int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
-  const float* __restrict__ a_mul = A.mul;
-  const float* __restrict__ w_mul = W.mul;
-  const int a_mul_stride = A.mul_stride, w_mul_stride = W.mul_stride;
+  // NVFP4: the tensor scales, in scalar registers from here on
+  const float nv_mul = FMT == kNvfp4 ? A.mul[0] * W.mul[0] : 0.0f;
   constexpr int T = WGM * WGN * 64;
   // wave tile: WTM x WTN outputs.  BM need not divide evenly over the WGM wave rows: the last wave row
   // then owns TM_LAST < TM MFMA tiles along M (a 224-row tile is 128 + 96), and the waves are numbered so
@@ -158,6 +157,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
   load_w(0, raw_w[0]);
   load_a(1, raw_a[1]);
   load_w(1, raw_w[1]);
+  float* const factors = reinterpret_cast<float*>(smem + 2 * STAGE_BYTES);
+  {
+    Factors<BM, BN, T, FMT != kNvfp4> f;
+    f.load(A, W, M, N, m0, n0);
+    f.put(factors);
+  }
 #pragma unroll
   for (int q = 0; q < SL; ++q) {
     unpack_all(raw_a[0][q], a_ok[q] && ld_half * 32 < K, smem, q);
@@ -275,7 +280,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
 
   __syncthreads();                                     // the output tile reuses the stages
   store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, 2 * STAGE_BYTES, OUT, FMT != kNvfp4>(
-      acc, smem, a_mul, a_mul_stride, w_mul, w_mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f,
+      acc, smem, factors, nv_mul, W.bias != nullptr, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid, 1.0f,
       tile_m * tiles_n + tile_n, out);
 }
 
@@ -421,7 +426,7 @@ template <int FMT, int G, int BM, int BN, int WGM, int WGN, int OUT>
 static int launch_gemm(const OperandView& A, const OperandView& W, int M, int N, int K, const Outputs& out,
                        hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
-  constexpr size_t shmem = 2 * (size_t)((BM * 2 + T - 1) / T * (T / 2) + BN) * kRowBytes;
+  constexpr size_t shmem = 2 * (size_t)((BM * 2 + T - 1) / T * (T / 2) + BN) * kRowBytes + kFactorBytes<BM, BN>;
   auto kern = qgemm_kernel<FMT, G, BM, BN, WGM, WGN, OUT>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_kernel)")) return rc;

@@ -239,6 +239,39 @@ __device__ __forceinline__ void store_diff(double d2, double* red, int threads, 
   }
 }
 
+// The epilogue's factors.  A product's rows and columns have a factor each (INT) and the columns perhaps a bias; they are
+// asked for at the start of the kernel and wait in LDS.  Loaded where they are used, one to four at a time, they were a chain
+// of memory latencies after the last step: 3.3 to 4.2 us of a 256 x 256 tile's epilogue (clock stamps; a round of tiles is
+// 80 us at K = 3072), and one for each strip of a split tile.  Kernel alone, us, before -> now: NVFP4 4608 x 9216 x 3072 214.9 -> 208.0,
+// 512 x 9216 x 3072 32.3 -> 29.6, 1024 x 3072 x 3072 22.2 -> 20.1, 256 x 512 x 512 3.60 -> 3.27; INT4 g64 4608 x 3072 x 3072 68.1 ->
+// 66.3; INT3 g32 8192 x 12288 x 3072 484 -> 472, g64 512 x 3072 x 3072 12.0 -> 10.8.  In LDS: BM factors of rows, BN of columns, BN
+// biases.
+template <int BM, int BN, int T, bool INT>
+struct Factors {
+  static_assert(BN <= T, "a bias a thread");
+  static constexpr int N = INT ? (BM + BN + T - 1) / T : 0;
+  float mul[N > 0 ? N : 1], bias = 0.0f;               // this thread's
+
+  __device__ __forceinline__ void load(const OperandView& A, const OperandView& W, int M, int N_, int m0, int n0) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int at = i * T + tid;
+      mul[i] = at < BM ? A.mul[min(m0 + at, M - 1)] : W.mul[min(n0 + min(at, BM + BN - 1) - BM, N_ - 1)];
+    }
+    if (W.bias) bias = bf16_to_f32(W.bias[min(n0 + min(tid, BN - 1), N_ - 1)]);
+  }
+  __device__ __forceinline__ void put(float* factors) const {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if ((i + 1) * T <= BM + BN || i * T + tid < BM + BN) factors[i * T + tid] = mul[i];
+    if (BN == T || tid < BN) factors[BM + BN + tid] = bias;
+  }
+};
+template <int BM, int BN>
+constexpr size_t kFactorBytes = (BM + 2 * BN) * sizeof(float);
+
 // ------------------------------------------------------------------------ INT3 codes beyond three bits
 // The quantizers write INT3 codes of -3 .. 3, but a nibble holds -8 .. 7, and an operand with any of them is
 // multiplied as it is (E2M1 holds neither 5 nor 7).  Packing, and on the row-major layout the scale preparation of
@@ -256,15 +289,13 @@ enum WideTest : int { kWideNone = 0, kWideMarks = 1, kWideCodes = 2 };
 constexpr uint32_t kWideBits = 0x88888888u;
 __device__ __forceinline__ uint32_t wide_codes(uint32_t d) { return d ^ (d << 1); }
 
-// the factors of a tile's rows and columns, or-ed over what a lane loads: every wave looks at all of them, so that
-// none has to tell the others.  Called before the epilogue and tested after it, so that nothing waits for the loads.
+// the factors of a tile's rows and columns, or-ed over what a lane reads: every wave looks at all of them, so that none has
+// to tell the others
 template <int BM, int BN>
-__device__ __forceinline__ uint32_t tile_marks(const OperandView& A, const OperandView& W, int M, int N, int m0, int n0) {
+__device__ __forceinline__ uint32_t tile_marks(const float* factors) {
   uint32_t v = 0;
 #pragma unroll
-  for (int r = 0; r < BM; r += 64) v |= as_u32(A.mul[min(m0 + r + (int)(threadIdx.x & 63), M - 1)]);
-#pragma unroll
-  for (int r = 0; r < BN; r += 64) v |= as_u32(W.mul[min(n0 + r + (int)(threadIdx.x & 63), N - 1)]);
+  for (int r = 0; r < BM + BN; r += 64) v |= as_u32(factors[min(r + (int)(threadIdx.x & 63), BM + BN - 1)]);
   return v;
 }
 
@@ -333,15 +364,12 @@ __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const Oper
 }
 
 // The accumulators of a workgroup's output tile, scaled and stored.  unit: a power of two that undoes the
-// operands' fixed code scale (1 where they have none; the product with it is exact).  INT: the factors are magnitudes,
-// their sign a mark.
-template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT, bool INT>
-__device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsigned char* smem,
-                                           const float* __restrict__ a_mul, int a_mul_stride,
-                                           const float* __restrict__ w_mul, int w_mul_stride,
-                                           const uint16_t* __restrict__ bias, int M, int N, int m0, int n0,
-                                           int wave_m, int wave_n, int tm_cnt, int tid, float unit, int tile,
-                                           const Output& out) {
+// operands' fixed code scale (1 where they have none; the product with it is exact).  factors: as Factors left them
+// (INT: magnitudes, their sign a mark); NVFP4 has one factor for all, nv_mul, the product of its tensor scales.
+template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT, bool INT, bool BIAS>
+__device__ __forceinline__ void store_tile_as(const float16_t (&acc)[TN][TM], unsigned char* smem, const float* factors,
+                                              float nv_mul, int M, int N, int m0, int n0, int wave_m, int wave_n, int tm_cnt,
+                                              int tid, float unit, int tile, const Output& out) {
   void* __restrict__ y = out.y;
   const int64_t ldy = out.ldy;
   double d2 = 0.0;
@@ -354,26 +382,34 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
   constexpr int C_ROW_BYTES = BN * 2 + 16;
   static_assert(OUT != kOutBf16 || BM * C_ROW_BYTES <= SMEM_BYTES, "output tile fits in the operand stages");
   // The column factors (and the optional bias of the linear layer, y = x W^T + b) do not depend on
-  // the row block: loaded once (16 per MFMA tile column).
-  float wm[TN][16], wb[TN][16];
+  // the row block: read once (16 per MFMA tile column).
+  float wm[INT ? TN : 1][16], wb[BIAS ? TN : 1][16];
 #pragma unroll
   for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = n0 + wave_n * WTN + i * 32 + q * 8 + frag_half * 4 + e;
-        const float f = w_mul[(int64_t)(min(n, N - 1) * w_mul_stride)];
-        wm[i][q * 4 + e] = INT ? fabsf(f) : f;
-        wb[i][q * 4 + e] = bias ? bf16_to_f32(bias[min(n, N - 1)]) : 0.0f;
+    for (int q = 0; q < 4; ++q) {
+      const float* at = factors + BM + wave_n * WTN + i * 32 + q * 8 + frag_half * 4;
+      if constexpr (INT) {
+        const float4 f = *reinterpret_cast<const float4*>(at);
+        wm[i][q * 4] = fabsf(f.x); wm[i][q * 4 + 1] = fabsf(f.y); wm[i][q * 4 + 2] = fabsf(f.z); wm[i][q * 4 + 3] = fabsf(f.w);
       }
+      if constexpr (BIAS) {
+        const float4 f = *reinterpret_cast<const float4*>(at + BN);
+        wb[i][q * 4] = f.x; wb[i][q * 4 + 1] = f.y; wb[i][q * 4 + 2] = f.z; wb[i][q * 4 + 3] = f.w;
+      }
+    }
+  float am[TM];
+#pragma unroll
+  for (int j = 0; j < TM; ++j) {
+    am[j] = 0.0f;
+    if constexpr (INT)
+      if (!RAGGED_M || j < tm_cnt) am[j] = fabsf(factors[wave_m * WTM + j * 32 + frag_row]);
+  }
 #pragma unroll
   for (int j = 0; j < TM; ++j) {
     if (RAGGED_M && j >= tm_cnt) break;         // wave-uniform
     const int ml = wave_m * WTM + j * 32 + frag_row;
     const int m = m0 + ml;
-    const float f = a_mul[(int64_t)(min(m, M - 1) * a_mul_stride)];
-    const float am = INT ? fabsf(f) : f;
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
 #pragma unroll
@@ -382,10 +418,9 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
         const int n = n0 + nl;
         float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (acc[i][j][q * 4 + e] * unit) * (am * wm[i][q * 4 + e]);
-        if (bias) {                     // without a bias the product is stored as it is (a -0 stays -0)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] += wb[i][q * 4 + e];
+        for (int e = 0; e < 4; ++e) {
+          v[e] = (acc[i][j][q * 4 + e] * unit) * (INT ? am[j] * wm[INT ? i : 0][q * 4 + e] : nv_mul);
+          if constexpr (BIAS) v[e] += wb[BIAS ? i : 0][q * 4 + e];
         }
         if constexpr (OUT == kOutDiff) {
           if (m < M && n < N) {
@@ -446,6 +481,19 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsig
       }
     }
   }
+}
+
+template <int BM, int BN, int WTM, int WTN, int TM, int TN, bool RAGGED_M, int T, int SMEM_BYTES, int OUT, bool INT>
+__device__ __forceinline__ void store_tile(const float16_t (&acc)[TN][TM], unsigned char* smem, const float* factors,
+                                           float nv_mul, bool bias, int M, int N, int m0, int n0, int wave_m, int wave_n,
+                                           int tm_cnt, int tid, float unit, int tile, const Output& out) {
+  // without a bias the product is stored as it is (a -0 stays -0)
+  if (OUT != kOutDiff && bias)
+    store_tile_as<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT, INT, true>(acc, smem, factors, nv_mul, M, N, m0, n0,
+                                                                                     wave_m, wave_n, tm_cnt, tid, unit, tile, out);
+  else
+    store_tile_as<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT, INT, false>(acc, smem, factors, nv_mul, M, N, m0, n0,
+                                                                                      wave_m, wave_n, tm_cnt, tid, unit, tile, out);
 }
 
 // view of an operand in the panel layout (pq_pack.hip)

@@ -192,6 +192,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   load_w(0, raw_w[0]);
   load_a(1, raw_a[1]);
   load_w(1, raw_w[1]);
+  float* const factors = reinterpret_cast<float*>(smem + SMEM_BYTES + (WIDE == kWideCodes ? T / 16 : 0));
+  {
+    Factors<BM, BN, T, true> f;
+    f.load(A, W, M, N, m0, n0);
+    f.put(factors);
+  }
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const int st = p * STAGE_BYTES;
@@ -310,9 +316,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
 
   __syncthreads();                                     // the output tile reuses the stages
   uint32_t marks = 0;
-  if constexpr (WIDE == kWideMarks) marks = tile_marks<BM, BN>(A, W, M, N, m0, n0);
+  if constexpr (WIDE == kWideMarks) marks = tile_marks<BM, BN>(factors);
   store_tile<BM, BN, WTM, WTN, TM, TN, RAGGED_M, T, SMEM_BYTES, OUT, true>(
-      acc, smem, A.mul, A.mul_stride, W.mul, W.mul_stride, W.bias, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid,
+      acc, smem, factors, 0.0f, W.bias != nullptr, M, N, m0, n0, wave_m, wave_n, tm_cnt, tid,
       FP4 ? 4.0f : 262144.0f, tile_m * tiles_n + tile_n, out);
   if constexpr (WIDE != kWideNone) {                   // here, where the accumulators are dead
     const bool any = WIDE == kWideMarks ? __any((int)marks < 0) != 0
@@ -332,7 +338,7 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
   constexpr int A_ROWS = (BM * 2 + T - 1) / T * (T / 2);
   constexpr size_t stages = 4 * (size_t)(A_ROWS + BN) * ((FP4 ? 32 : 64) + 2);
   constexpr size_t tile_bytes = OUT != kOutBf16 ? 0 : (size_t)BM * (BN * 2 + 16);
-  constexpr size_t shmem = (stages > tile_bytes ? stages : tile_bytes) + (WIDE == kWideCodes ? WGM * WGN * 4 : 0);
+  constexpr size_t shmem = (stages > tile_bytes ? stages : tile_bytes) + (WIDE == kWideCodes ? WGM * WGN * 4 : 0) + kFactorBytes<BM, BN>;
   auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT, WIDE>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_group_kernel)")) return rc;

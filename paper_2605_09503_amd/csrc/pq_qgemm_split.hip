@@ -29,6 +29,11 @@ namespace pq {
 // the scales outside (pq_qgemm_group.hip)
 enum SplitMode : int { kSplitNvfp4 = 0, kSplitInt = 1, kSplitE2m1 = 2 };
 
+// LDS bytes of the partial sums of one 32-column strip (and the flags of kWideCodes), or of two sets of steps of row-major
+// operands; the epilogue's factors lie behind them
+template <int TM, int TN, int KS, int WIDE, bool ROWS>
+constexpr size_t split_lds();
+
 // LDS layout of one set of KS steps of row-major operands
 template <int TM, int TN, int KS>
 struct RowSet {
@@ -39,6 +44,13 @@ struct RowSet {
   static constexpr int kScaleRow = KS * 4 + 4;
   static constexpr int kBytes = (kScales + kRows * kScaleRow + 15) / 16 * 16;
 };
+
+template <int TM, int TN, int KS, int WIDE, bool ROWS>
+constexpr size_t split_lds() {
+  constexpr size_t sums = (size_t)KS * TM * 32 * (32 + 4) * 4 + (WIDE == kWideCodes ? KS * 4 : 0);
+  constexpr size_t sets = ROWS ? 2 * (size_t)RowSet<TM, TN, KS>::kBytes : 0;
+  return sums > sets ? sums : sets;
+}
 
 typedef uint32_t uint32_any __attribute__((aligned(2)));              // two scale units, at any unit
 
@@ -69,6 +81,11 @@ qgemm_split_kernel(
   const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);            // this wave's share of K: steps ks, ks + KS, ...
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int frag_row = lane & 31, frag_half = lane >> 5;
+
+  constexpr bool INT = MODE != kSplitNvfp4;            // factors of magnitude, the sign a mark
+  const float nv_mul = INT ? 0.0f : A.mul[0] * W.mul[0];
+  Factors<BM, BN, T, INT> own_factors;
+  own_factors.load(A, W, M, N, m0, n0);
 
   // a fragment's lane: row lane % 32, k 32 * (lane / 32) .. + 31 of the step: 16 bytes of codes, one scale unit (packed
   // operands; see below for ROWS)
@@ -317,11 +334,11 @@ qgemm_split_kernel(
     }
   }
 
-  uint32_t marks = 0;
-  if constexpr (WIDE == kWideMarks) marks = tile_marks<BM, BN>(A, W, M, N, m0, n0);
+  float* const factors = part + split_lds<TM, TN, KS, WIDE, ROWS>() / 4;
+  own_factors.put(factors);
 
   // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
-  const uint16_t* __restrict__ bias = W.bias;
+  const bool bias = W.bias != nullptr;
   void* __restrict__ y = out.y;
   const int64_t ldy = out.ldy;
   double d2 = 0.0;
@@ -352,16 +369,18 @@ qgemm_split_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = s == 0 ? t[e] : v[e] + t[e];
       }
-      constexpr bool INT = MODE != kSplitNvfp4;         // factors of magnitude, the sign a mark
-      float am = A.mul[(int64_t)m * A.mul_stride];
-      if constexpr (INT) am = fabsf(am);
+      const float* col = factors + BM + i * 32 + cc * 8;
+      if constexpr (INT) {
+        const float am = fabsf(factors[row]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int nn = min(n + e, N - 1);
-        float wm = W.mul[(int64_t)nn * W.mul_stride];
-        if constexpr (INT) wm = fabsf(wm);
-        v[e] = (v[e] * unit) * (am * wm);
-        if (bias) v[e] += bf16_to_f32(bias[nn]);
+        for (int e = 0; e < 8; ++e) v[e] = (v[e] * unit) * (am * fabsf(col[e]));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= nv_mul;
+      }
+      if (bias) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += col[BN + e];
       }
       if constexpr (OUT == kOutDiff) {
         const float* r = out.ref + (int64_t)m * ldy + n;
@@ -412,7 +431,7 @@ qgemm_split_kernel(
     store_diff(d2, reinterpret_cast<double*>(part), T, tile_m * tiles_n + tile_n, out);
   }
   if constexpr (WIDE != kWideNone) {                   // here, where the accumulators are dead
-    const bool any = WIDE == kWideMarks ? __any((int)marks < 0) != 0
+    const bool any = WIDE == kWideMarks ? __any((int)tile_marks<BM, BN>(factors) < 0) != 0
                                         : any_wide<KS>(wide, reinterpret_cast<int*>(part + (size_t)KS * BM * ROW));
     if (any) {
       __threadfence();                                 // what the waves stored has arrived
@@ -440,9 +459,7 @@ template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool F
 static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
-  constexpr size_t sums = (size_t)KS * BM * (32 + 4) * 4 + (WIDE == kWideCodes ? KS * 4 : 0);
-  constexpr size_t sets = ROWS ? 2 * (size_t)RowSet<TM, TN, KS>::kBytes : 0;
-  constexpr size_t shmem = sums > sets ? sums : sets;
+  constexpr size_t shmem = split_lds<TM, TN, KS, WIDE, ROWS>() + kFactorBytes<BM, BN>;
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
   auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE, ROWS, FEW>;
   static std::atomic<uint64_t> raised{0};

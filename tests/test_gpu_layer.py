@@ -347,3 +347,54 @@ def test_calls_without_the_native_binding_give_the_same(tmp_path, fmt, g):
     for other in out[1:]:
         for u, v in zip(out[0], other):
             assert torch.equal(u, v)
+
+
+def _dequantized(fmt, g, x, T):
+    """Q(x) of the library's own quantizer in 64 bits, from its stored codes and scales."""
+    codes, scales = pq.alloc_quantized(fmt, g, x.shape[0], x.shape[1], DEV)
+    pq.pq_quantize_act(fmt, g, x, None, T, codes, scales)
+    c = torch.stack((codes & 15, codes >> 4), 2).reshape(x.shape).long()
+    if fmt == pq.FMT_NVFP4:
+        v = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6, 0, -.5, -1, -1.5, -2, -3, -4, -6], dtype=torch.float64, device=DEV)[c]
+        s = scales.view(torch.float8_e4m3fn).double() * T.double()
+    else:
+        v, s = (c - 16 * (c > 7).long()).double(), scales.double()
+    return codes, scales, v * s.repeat_interleave(g, 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
+    (pq.FMT_NVFP4, 16, 61, 1001, 1184, (32, 32)), (pq.FMT_NVFP4, 16, 500, 1021, 320, (64, 32)),
+    (pq.FMT_NVFP4, 16, 449, 3077, 96, (64, 64)), (pq.FMT_NVFP4, 16, 2309, 3077, 96, (128, 128)),
+    (pq.FMT_NVFP4, 16, 4099, 5125, 320, None), (pq.FMT_INT3, 32, 4099, 5125, 320, None),
+    (pq.FMT_INT4, 64, 77, 1001, 1152, (32, 32)), (pq.FMT_INT4, 64, 1100, 4099, 128, (64, 64)),
+    (pq.FMT_INT4, 64, 2309, 5125, 128, (224, 256)), (pq.FMT_INT3, 64, 2309, 5125, 128, (224, 256)),
+    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64)), (pq.FMT_INT3, 128, 100, 300, 256, (32, 32))])
+def test_row_and_column_factors_and_bias_of_every_tile(fmt, g, M, N, K, tile):
+    """Rows and columns of very different size, a bias, ragged edges: every tile's epilogue takes its own factors.  The
+    fp32 product against the 64-bit product of what the quantizer stored: K roundings of 2^-24 of the magnitudes (the INT
+    factors h / Q are rounded once more each); the bf16 one with the bias is the fp32 one plus the bias, rounded once."""
+    if tile is not None:
+        assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K + g)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=DEV)
+    rows, cols = torch.arange(M, device=DEV), torch.arange(N, device=DEV)
+    x = (rnd(M, K) * torch.exp2((rows % 11 - 5).float())[:, None]).to(torch.bfloat16)
+    w = (rnd(N, K) * torch.exp2((cols % 13 - 6).float())[:, None]).to(torch.bfloat16)
+    bias = rnd(N).to(torch.bfloat16)
+    Ta, Tw = ((t.float().abs().max() / 2688).reshape(1) for t in (x, w))
+    _, _, xq = _dequantized(fmt, g, x, Ta)
+    wc, ws, wq = _dequantized(fmt, g, w, Tw)
+    a, wo = pq.pq_quantize_act_packed(fmt, g, x, Ta), pq.pq_pack_operand(fmt, g, wc, ws)
+    ldy = (N + 7) // 8 * 8
+    yf = torch.empty((M, ldy), dtype=torch.float32, device=DEV)
+    yb = torch.empty((M, ldy), dtype=torch.bfloat16, device=DEV)
+    y = torch.empty((M, ldy), dtype=torch.bfloat16, device=DEV)
+    pq.pq_qgemm_packed_f32(fmt, g, a, Ta, wo, Tw, yf, M, N, K, ldy=ldy)
+    pq.pq_qgemm_packed_bias(fmt, g, a, Ta, wo, Tw, bias, yb, M, N, K, ldy=ldy)
+    pq.pq_qgemm_packed(fmt, g, a, Ta, wo, Tw, y, M, N, K, ldy=ldy)
+    yf, yb, y = yf[:, :N], yb[:, :N], y[:, :N]
+    bound = (K + 4) * 2.0 ** -24 * (xq.abs() @ wq.abs().t())
+    assert ((yf.double() - xq @ wq.t()).abs() <= bound).all()
+    assert torch.equal(y, yf.to(torch.bfloat16))
+    assert torch.equal(yb, (yf + bias.float()).to(torch.bfloat16))
