@@ -83,7 +83,7 @@ template <int FMT>
 __device__ __forceinline__ void slice_scales(const Slice& s, bool ok, PairScale& p0, PairScale& p1) {
   if constexpr (FMT == kNvfp4) {
     // E4M3 byte b -> fp16: bits (b << 7) read as fp16 are value * 2^-8, subnormals included
-    uint32_t two = ((s.sc & 0xFFu) << 7) | ((s.sc & 0xFF00u) << 15);
+    uint32_t two = __builtin_amdgcn_perm(0u, s.sc, 0x0C010C00u) << 7;
     two = ok ? two : 0u;
     half2_t v = as_h2(two) * (half2_t){(_Float16)256.0f, (_Float16)256.0f};
     p0.mul = (half2_t){v.x, v.x};

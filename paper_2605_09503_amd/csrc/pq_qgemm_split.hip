@@ -13,12 +13,17 @@
 // in part only, see pq_qgemm_group.hip): a 64 x 96 tile unpacks five fragments for six 32 x 32 x 64 products, 1.5 times what
 // a staged 128 x 128 tile unpacks, but its four-wave workgroups need no barrier and run two to a compute unit.  Where there
 // is a second workgroup, four waves and not eight share a 64 x 96 tile because it then covers the first one's ends
-// (NVFP4 512 x 9216 x 3072: 32 us, with eight waves 42); where there is none see choose_tile.  Kernel alone, us, before -> now:
-//   NVFP4     256 x 512 x 512     9.4 ->  3.9     512 x 3072 x 3072   30 -> 15      512 x 3072 x 12288  104 -> 43
-//   NVFP4     512 x 9216 x 3072    44 -> 32       64 x 12288 x 3072   29 -> 11      16 x 512 x 12288    103 -> 13
-//   INT4 g128  77 x 1000 x 1152  15.3 ->  4.5     INT4 g64   1024 x 3072 x 3072  33 -> 27
-//   INT3 g64  512 x 3072 x 3072    31 -> 13       INT3 g64   2048 x 3072 x 3072  49 -> 32
-// INT4 in the 8-bit form of pq_qgemm_group.hip gained nothing here (15.5 -> 16.5, 46.9 -> 43.6 us): fp16 operands.
+// (NVFP4 512 x 9216 x 3072: with eight waves 1.3 times as long); where there is none see choose_tile.  Beside a matrix
+// instruction of 32 cycles seven vector instructions are free (each takes an issue slot of 4.2 cycles, the matrix
+// instruction one).  So the loop tests nothing that only the last step needs (see CUT), tiles of several blocks unpack the next
+// 16 k between the matrix instructions of these, in an order that is prescribed, and a wave with a single step
+// runs nothing ahead.  Kernel alone, us: with 128 x 128 tiles -> split tiles -> the loop as it is and the factors in LDS
+//   NVFP4     256 x 512 x 512     9.4 ->  3.6 ->  2.9     512 x 3072 x 3072   30 -> 13.4 -> 11.4     500 x 1021 x 352  3.9 -> 3.35
+//   NVFP4     512 x 9216 x 3072    44 -> 32.3 -> 27.6     64 x 12288 x 3072   29 -> 10.2 ->  8.7     43 x 3659 x 10240  12.2 -> 11.2
+//   INT4 g128  77 x 1000 x 1152  15.3 ->  4.3 ->  3.9     INT4 g64   1024 x 3072 x 3072  33 -> 24.9 -> 21.5
+//   INT3 g64  512 x 3072 x 3072    31 -> 12.0 -> 10.2     INT3 g64   2048 x 3072 x 3072  49 -> 29.5 -> 28.7
+// INT4 in the 8-bit form of pq_qgemm_group.hip gained nothing here (15.5 -> 16.5, 46.9 -> 43.6 us): fp16 operands.  For the codes
+// of INT3 the next step's unpack between these blocks was 8 to 13 % slower (254 registers).
 #include <type_traits>
 
 #include "pq_qgemm_common.h"
@@ -60,7 +65,7 @@ typedef uint32_t uint32_any __attribute__((aligned(2)));              // two sca
 // each).  The sums are the same as without, and as those of the packed operands, bit for bit.  See rows_through_lds.
 // WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
 template <int TM, int TN, int WIDE, bool ROWS>
-constexpr int kSplitWaves = ROWS && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
+constexpr int kSplitWaves = (ROWS || WIDE == kWideMarks) && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
 // FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 82 instead
 // of 56, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW>
@@ -88,51 +93,56 @@ qgemm_split_kernel(
   own_factors.load(A, W, M, N, m0, n0);
 
   // a fragment's lane: row lane % 32, k 32 * (lane / 32) .. + 31 of the step: 16 bytes of codes, one scale unit (packed
-  // operands; see below for ROWS)
+  // operands; see below for ROWS).  Rows past the last re-read it; what they give is not stored.
+  const bool per_half = g_shift == 5;                  // a scale unit covers 32 k: the lane halves have their own
+  const uint32_t half_codes = frag_half * 16u, half_a = per_half ? frag_half * (uint32_t)A.sc_step : 0u,
+                 half_w = per_half ? frag_half * (uint32_t)W.sc_step : 0u;
   uint32_t a_coff[TM], w_coff[TN], a_soff[TM], w_soff[TN];
-  bool a_ok[TM], w_ok[TN];
 #pragma unroll
   for (int j = 0; j < TM; ++j) {
-    const int r = j * 32 + frag_row;
-    a_ok[j] = m0 + r < M;
-    a_coff[j] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)A.code_row;
-    a_soff[j] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)A.sc_row;
+    const uint32_t r = (uint32_t)min(j * 32 + frag_row, M - 1 - m0);
+    a_coff[j] = r * (uint32_t)A.code_row + half_codes;
+    a_soff[j] = r * (uint32_t)A.sc_row + half_a;
   }
 #pragma unroll
   for (int i = 0; i < TN; ++i) {
-    const int r = i * 32 + frag_row;
-    w_ok[i] = n0 + r < N;
-    w_coff[i] = (uint32_t)min(r, N - 1 - n0) * (uint32_t)W.code_row;
-    w_soff[i] = (uint32_t)min(r, N - 1 - n0) * (uint32_t)W.sc_row;
+    const uint32_t r = (uint32_t)min(i * 32 + frag_row, N - 1 - n0);
+    w_coff[i] = r * (uint32_t)W.code_row + half_codes;
+    w_soff[i] = r * (uint32_t)W.sc_row + half_w;
   }
   const uint8_t* a_codes = A.codes + (int64_t)m0 * A.code_row;
   const uint8_t* w_codes = W.codes + (int64_t)n0 * W.code_row;
   const uint8_t* a_scales = A.scales + (int64_t)m0 * A.sc_row;
   const uint8_t* w_scales = W.scales + (int64_t)n0 * W.sc_row;
   const int ksteps = (K + kBK - 1) / kBK;
-  const bool per_half = g_shift == 5;                  // a scale unit covers 32 k: the lane halves have their own
 
   struct Step {
     Slice a[TM], w[TN];
   };
-  // a step past the last re-reads the last, the missing upper half of a last step of 32 k the lower one (both are
-  // neutralised by a zero scale)
-  auto load = [&](int step, Step& f) {
+  // A step past the last re-reads the last.  CUT: K ends in a step of 32 k; its missing upper half re-reads the lower one,
+  // neutralised by a zero scale.  Other K have a loop without these tests: with them the 64 x 96 tile of NVFP4 takes 8.6 vector
+  // instructions for a matrix instruction, without 7.3.
+  auto load = [&](auto CUT, int step, Step& f) {
     const int st = min(step, ksteps - 1);              // uniform
-    const uint32_t half = st * kBK + frag_half * 32 < K ? frag_half : 0;
+    const bool drop = decltype(CUT)::value && st * kBK + 32 >= K;      // uniform
+    const uint32_t dc = drop ? half_codes : 0u, da = drop ? half_a : 0u, dw = drop ? half_w : 0u;
+    auto at = [](uint32_t off, uint32_t less) {
+      uint32_t o = off - less;
+      if constexpr (!decltype(CUT)::value) asm("" : "+v"(o));           // stays 32 bits: widened ahead of the loop it takes two
+      return o;                                                         // registers and a 64-bit addition a load
+    };
     const int unit = (st * kBK) >> g_shift;
     const uint8_t *ac = a_codes + (int64_t)st * A.code_step, *wc = w_codes + (int64_t)st * W.code_step;
     const uint8_t *as = a_scales + (int64_t)unit * A.sc_step, *ws = w_scales + (int64_t)unit * W.sc_step;
-    const uint32_t ah = per_half ? half * (uint32_t)A.sc_step : 0u, wh = per_half ? half * (uint32_t)W.sc_step : 0u;
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
-      f.a[j].codes = *reinterpret_cast<const uint4*>(ac + (a_coff[j] + half * 16u));
-      f.a[j].sc = *reinterpret_cast<const uint16_t*>(as + (a_soff[j] + ah));
+      f.a[j].codes = *reinterpret_cast<const uint4*>(ac + at(a_coff[j], dc));
+      f.a[j].sc = *reinterpret_cast<const uint16_t*>(as + at(a_soff[j], da));
     }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
-      f.w[i].codes = *reinterpret_cast<const uint4*>(wc + (w_coff[i] + half * 16u));
-      f.w[i].sc = *reinterpret_cast<const uint16_t*>(ws + (w_soff[i] + wh));
+      f.w[i].codes = *reinterpret_cast<const uint4*>(wc + at(w_coff[i], dc));
+      f.w[i].sc = *reinterpret_cast<const uint16_t*>(ws + at(w_soff[i], dw));
     }
   };
 
@@ -145,80 +155,137 @@ qgemm_split_kernel(
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
   uint32_t wide = 0;
-  auto multiply = [&](const Step& f, int step) {
-    const bool k_ok = step * kBK + frag_half * 32 < K;
-    if constexpr (!CODES) {
-      constexpr int FMT = MODE == kSplitNvfp4 ? kNvfp4 : kInt4;       // INT3 nibbles unpack like INT4's
-      PairScale sa[TM][2], sw[TN][2];
-#pragma unroll
-      for (int j = 0; j < TM; ++j) slice_scales<FMT>(f.a[j], a_ok[j] && k_ok, sa[j][0], sa[j][1]);
-#pragma unroll
-      for (int i = 0; i < TN; ++i) slice_scales<FMT>(f.w[i], w_ok[i] && k_ok, sw[i][0], sw[i][1]);
-      auto unpack = [&](const uint4& codes, int kk, const PairScale (&sc)[2]) {
-        const uint32_t d = kk == 0 ? codes.x : kk == 1 ? codes.y : kk == 2 ? codes.z : codes.w;
-        const PairScale& s = sc[kk / 2];
-        const uint4 v = make_uint4(unpack_pair<FMT, 0>(d, s), unpack_pair<FMT, 1>(d, s), unpack_pair<FMT, 2>(d, s),
-                                   unpack_pair<FMT, 3>(d, s));
-        return __builtin_bit_cast(half8_t, v);
-      };
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        half8_t x[TM], w[TN];
-#pragma unroll
-        for (int j = 0; j < TM; ++j) x[j] = unpack(f.a[j].codes, kk, sa[j]);
-#pragma unroll
-        for (int i = 0; i < TN; ++i) w[i] = unpack(f.w[i].codes, kk, sw[i]);
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-          for (int j = 0; j < TM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i], x[j], acc[i][j], 0, 0, 0);
-      }
-    } else {
-      const float16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
-                              0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-      int8v x[TM], w[TN];
-      half4v sx[TM], sw[TN];
-      auto codes = [&](const uint4& c) {
+  // What the matrix unit takes for a share of a step: fp16 operands of 16 k (four shares), or the codes of all 64 k (one).
+  constexpr int FMT = MODE == kSplitNvfp4 ? kNvfp4 : kInt4;           // INT3 nibbles unpack like INT4's
+  struct Frags {
+    std::conditional_t<CODES, int4v, half8_t> a[TM], w[TN];
+    uint32_t sa[CODES ? TM : 1], sw[CODES ? TN : 1];
+  };
+  PairScale sa[CODES ? 1 : TM][2], sw[CODES ? 1 : TN][2];             // of the step that is being unpacked
+  auto unpack = [&](auto KK, const Step& f, bool k_ok, Frags& to) {
+    constexpr int kk = decltype(KK)::value;
+    auto one = [&](const Slice& s, PairScale (&sc)[2]) {
+      if constexpr (CODES) {
+        const uint4& c = s.codes;
         if constexpr (WIDE == kWideCodes) wide |= wide_codes(c.x) | wide_codes(c.y) | wide_codes(c.z) | wide_codes(c.w);
-        return (int8v){(int)e2m1_nibbles(c.x), (int)e2m1_nibbles(c.y), (int)e2m1_nibbles(c.z), (int)e2m1_nibbles(c.w),
-                       0, 0, 0, 0};
-      };
+        return (int4v){(int)e2m1_nibbles(c.x), (int)e2m1_nibbles(c.y), (int)e2m1_nibbles(c.z), (int)e2m1_nibbles(c.w)};
+      } else {
+        if constexpr (kk == 0) slice_scales<FMT>(s, k_ok, sc[0], sc[1]);
+        const uint32_t d = kk == 0 ? s.codes.x : kk == 1 ? s.codes.y : kk == 2 ? s.codes.z : s.codes.w;
+        const PairScale& h = sc[kk / 2];
+        return __builtin_bit_cast(half8_t, make_uint4(unpack_pair<FMT, 0>(d, h), unpack_pair<FMT, 1>(d, h),
+                                                      unpack_pair<FMT, 2>(d, h), unpack_pair<FMT, 3>(d, h)));
+      }
+    };
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      to.a[j] = one(f.a[j], sa[CODES ? 0 : j]);
+      if constexpr (CODES) to.sa[j] = f.a[j].sc;
+    }
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      to.w[i] = one(f.w[i], sw[CODES ? 0 : i]);
+      if constexpr (CODES) to.sw[i] = frag_half == 0 ? f.w[i].sc : 0u;
+    }
+  };
+  auto multiply = [&](const Frags& f) {
+    const float16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
+                            0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
-        x[j] = codes(f.a[j].codes);
-        sx[j] = scale_operand(a_ok[j] && k_ok ? f.a[j].sc : 0u);
-      }
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        w[i] = codes(f.w[i].codes);
-        sw[i] = scale_operand(w_ok[i] && frag_half == 0 ? f.w[i].sc : 0u);
-      }
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j) {
-          const float16_t s = __builtin_amdgcn_mfma_f32_32x32x8f16(sw[i], sx[j], zero, 0, 0, 0);
-          const float16_t p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w[i], x[j], zero, 4, 4, 0, 0, 0, 0);
+        if constexpr (!CODES) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.w[i], f.a[j], acc[i][j], 0, 0, 0);
+        } else {
+          const int8v w = {f.w[i].x, f.w[i].y, f.w[i].z, f.w[i].w, 0, 0, 0, 0}, x = {f.a[j].x, f.a[j].y, f.a[j].z, f.a[j].w, 0, 0, 0, 0};
+          const float16_t s = __builtin_amdgcn_mfma_f32_32x32x8f16(scale_operand(f.sw[i]), scale_operand(f.sa[j]), zero, 0, 0, 0);
+          const float16_t p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, zero, 4, 4, 0, 0, 0, 0);
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(p[r], s[r], acc[i][j][r]);
+          // a block at a time where three workgroups share a unit: the compiler's own order takes more than 168 registers
+          if constexpr (TM * TN == 4) __builtin_amdgcn_sched_barrier(0);
         }
+      }
+  };
+  auto whole_step = [&](const Step& step, bool k_ok) {
+    Frags f;
+    unpack(IntC<0>{}, step, k_ok, f);
+    multiply(f);
+    if constexpr (!CODES) {
+      unpack(IntC<1>{}, step, k_ok, f);
+      multiply(f);
+      unpack(IntC<2>{}, step, k_ok, f);
+      multiply(f);
+      unpack(IntC<3>{}, step, k_ok, f);
+      multiply(f);
+    }
+  };
+  constexpr bool kAhead = !CODES && TM * TN >= 2;
+  // the order of a share's instructions: the next share's unpack between this one's matrix instructions
+  auto interleave = [&]() {
+    if constexpr (!CODES) {
+      constexpr int kUnpack = (TM + TN) * (FMT == kNvfp4 ? 8 : 12), N = TM * TN, EACH = (kUnpack + N - 1) / N;
+#pragma unroll
+      for (int t = 0; t < N; ++t) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, EACH, 0);
+      }
     }
   };
 
   if constexpr (!ROWS) {
     Step raw[PD];
     const int n_own = (ksteps - ks + KS - 1) / KS;     // steps ks, ks + KS, ...
+    auto all_steps = [&](auto CUT) {
 #pragma unroll
-    for (int p = 0; p < PD; ++p) load(ks + p * KS, raw[p]);
-    for (int o = 0; o < n_own; o += PD) {
+      for (int p = 0; p < PD; ++p) load(CUT, ks + p * KS, raw[p]);
+      auto k_ok = [&](int o) { return !decltype(CUT)::value || (ks + o * KS) * kBK + frag_half * 32 < K; };
+      if constexpr (!kAhead) {
+        for (int o = 0; o < n_own; o += PD) {
 #pragma unroll
-      for (int p = 0; p < PD; ++p) {
-        if (o + p < n_own) {                           // uniform
-          multiply(raw[p], ks + (o + p) * KS);
-          load(ks + (o + p + PD) * KS, raw[p]);
+          for (int p = 0; p < PD; ++p) {
+            if (o + p < n_own) {                       // uniform
+              whole_step(raw[p], k_ok(o + p));
+              load(CUT, ks + (o + p + PD) * KS, raw[p]);
+            }
+          }
+        }
+      } else {
+        Frags f[2];
+        unpack(IntC<0>{}, raw[0], k_ok(0), f[0]);
+        for (int o = 0; o < n_own; o += PD) {
+#pragma unroll
+          for (int p = 0; p < PD; ++p) {
+            if (o + p < n_own) {                       // uniform
+              unpack(IntC<1>{}, raw[p], k_ok(o + p), f[1]);
+              multiply(f[0]);
+              interleave();
+              unpack(IntC<2>{}, raw[p], k_ok(o + p), f[0]);
+              multiply(f[1]);
+              interleave();
+              unpack(IntC<3>{}, raw[p], k_ok(o + p), f[1]);
+              multiply(f[0]);
+              interleave();
+              load(CUT, ks + (o + p + PD) * KS, raw[p]);
+              unpack(IntC<0>{}, raw[(p + 1) % PD], k_ok(o + p + 1), f[0]);
+              multiply(f[1]);
+              interleave();
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
         }
       }
-    }
+    };
+    if (ksteps <= KS) {                                // a step each at most: nothing to run ahead of
+      if (ks < ksteps) {
+        load(IntC<!CODES>{}, ks, raw[0]);
+        whole_step(raw[0], ks * kBK + frag_half * 32 < K);
+      }
+    } else if (!CODES && K % kBK)
+      all_steps(IntC<!CODES>{});
+    else
+      all_steps(IntC<0>{});
   } else {
     // set: [rows of A, then of W] of KS steps; a row's codes with one spare piece, then the scale units of all rows: one for
     // each slice, or (CODES) a row's consecutive units of the set, of which the last set has the last ones of the row
@@ -321,7 +388,9 @@ qgemm_split_kernel(
         put(lds + (P ^ 1) * L::kBytes);
         fetch(o + 2);
       }
-      if (step < ksteps) multiply(own, step);          // uniform over the wave
+      if (step < ksteps) {                             // uniform over the wave
+        whole_step(own, step * kBK + frag_half * 32 < K);
+      }
       __syncthreads();
     };
     fetch(0);

@@ -369,7 +369,12 @@ def _dequantized(fmt, g, x, T):
     (pq.FMT_NVFP4, 16, 4099, 5125, 320, None), (pq.FMT_INT3, 32, 4099, 5125, 320, None),
     (pq.FMT_INT4, 64, 77, 1001, 1152, (32, 32)), (pq.FMT_INT4, 64, 1100, 4099, 128, (64, 64)),
     (pq.FMT_INT4, 64, 2309, 5125, 128, (224, 256)), (pq.FMT_INT3, 64, 2309, 5125, 128, (224, 256)),
-    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64)), (pq.FMT_INT3, 128, 100, 300, 256, (32, 32))])
+    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64)), (pq.FMT_INT3, 128, 100, 300, 256, (32, 32)),
+    # waves that have one step, two, an odd number of them, none; a last step of 32 k
+    (pq.FMT_NVFP4, 16, 61, 1001, 32, None), (pq.FMT_NVFP4, 16, 61, 1001, 512, None), (pq.FMT_NVFP4, 16, 61, 1001, 544, None),
+    (pq.FMT_NVFP4, 16, 500, 1021, 1056, None), (pq.FMT_NVFP4, 16, 500, 1021, 1120, None), (pq.FMT_NVFP4, 16, 449, 3077, 288, None),
+    (pq.FMT_NVFP4, 16, 449, 3077, 864, None), (pq.FMT_INT4, 32, 500, 1021, 1632, None), (pq.FMT_INT3, 32, 449, 3077, 1184, None),
+    (pq.FMT_NVFP4, 16, 512, 1650, 3104, None), (pq.FMT_INT3, 64, 512, 3072, 3136, None)])
 def test_row_and_column_factors_and_bias_of_every_tile(fmt, g, M, N, K, tile):
     """Rows and columns of very different size, a bias, ragged edges: every tile's epilogue takes its own factors.  The
     fp32 product against the 64-bit product of what the quantizer stored: K roundings of 2^-24 of the magnitudes (the INT
