@@ -300,10 +300,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
 }
 
 // ------------------------------------------------------------------------ INT scale prepass
-// One wave per row of scales: recover each group's bf16 maximum h = bf16_rne(s * Q), find the
-// row's largest exponent, and emit fp16 h * 2^-E plus the fp32 epilogue factor 2^E / Q, with E
-// chosen so that the largest h * 2^-E stays below 2^11.  blockIdx.y: the operand (a launch for each took 2.5 us
-// more than one for both).
+// One wave per row of scales (see int_row_scale).  blockIdx.y: the operand (a launch for each took 2.5 us more than one for
+// both).
 struct ScalePrep {
   const float* s;
   uint16_t* h;
@@ -328,25 +326,9 @@ __global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScaleP
   uint4 first = make_uint4(0u, 0u, 0u, 0u);
   if (MARK && lane < K / 32) first = cr[lane];
   float mx = 0.0f;
-  for (int g = lane; g < groups; g += 64) {
-    float h = as_f32(f32_to_bf16_rne(sr[g] * Q) << 16);
-    mx = fmaxf(mx, h);
-  }
-  mx = wave_max(mx);
-  // E = exponent(mx) - 10: the row maximum lands in [2^10, 2^11), so that the addend 24 * h of
-  // the unpack fma (and with it Q * h) stays below the fp16 maximum
-  int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
-  if (mx == 0.0f) e = 0;
-  int E = e - 10;
-  // clamp so that both 2^-E and 2^E are normal fp32 numbers
-  E = max(-120, min(120, E));
-  const float down = as_f32((uint32_t)(127 - E) << 23);     // 2^-E
-  const float up = as_f32((uint32_t)(127 + E) << 23);       // 2^E
-  for (int g = lane; g < groups; g += 64) {
-    float h = as_f32(f32_to_bf16_rne(sr[g] * Q) << 16);
-    _Float16 hh = (_Float16)(h * down);                      // exact unless far below the row max
-    h_out[(int64_t)row * groups + g] = __builtin_bit_cast(uint16_t, hh);
-  }
+  for (int g = lane; g < groups; g += 64) mx = fmaxf(mx, int_group_max(sr[g], Q));
+  const RowScale scale = int_row_scale(wave_max(mx));
+  for (int g = lane; g < groups; g += 64) h_out[(int64_t)row * groups + g] = int_scale_unit(sr[g], Q, scale.down);
   bool marked = false;
   if constexpr (MARK) {
     uint32_t wide = wide_codes(first.x) | wide_codes(first.y) | wide_codes(first.z) | wide_codes(first.w);
@@ -357,7 +339,7 @@ __global__ __launch_bounds__(256) void int_scale_prep_kernel(ScalePrep a, ScaleP
     }
     marked = __any((wide & kWideBits) != 0);
   }
-  if (lane == 0) mul_out[row] = marked ? -(up / Q) : up / Q;
+  if (lane == 0) mul_out[row] = marked ? -(scale.up / Q) : scale.up / Q;
 }
 
 // ------------------------------------------------------------------------ INT scale form check
@@ -513,6 +495,15 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     GemmWs G;
     carve_gemm(ws, fmt, group, M, N, K, &G);
     const float Q = qmax_of((int)fmt);
+    const int tile = choose_tile(fmt, group, M, N, K);
+    if (phases == 3 && split_takes_raw_scales(tile, group, M, N, K)) {
+      A.scales = (const uint8_t*)a_scales;
+      W.scales = (const uint8_t*)w_scales;
+      A.sc_row = W.sc_row = (K / group) * 4;
+      A.sc_step = W.sc_step = 4;
+      A.raw_q = W.raw_q = (uint8_t)Q;
+      return launch_qgemm_views(fmt, group, A, W, M, N, K, Outputs{{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}}, tile, st);
+    }
     const bool mark = phases == 3 && fmt == PQ_FMT_INT3 && group != 32;
     if (phases & 1) {
       const int64_t most = M > N ? M : N;

@@ -20,6 +20,24 @@ constexpr int kRowBytes = kBK * 2 + 16; // fp16 row in LDS, padded by one 16-byt
 __device__ __forceinline__ half2_t as_h2(uint32_t u) { return __builtin_bit_cast(half2_t, u); }
 __device__ __forceinline__ uint32_t h2_bits(half2_t h) { return __builtin_bit_cast(uint32_t, h); }
 
+// ------------------------------------------------------------------------ INT scales
+// The group maximum h = bf16_rne(s Q) goes into the operands as fp16 h 2^-E, E(row) such that the row's largest lands in
+// [2^10, 2^11): the addend 24 h of the unpack fma (and with it Q h) stays below the fp16 maximum.  2^E / Q goes to the epilogue.
+struct RowScale {
+  float down, up;                                      // 2^-E, 2^E
+};
+__device__ __forceinline__ float int_group_max(float s, float Q) { return as_f32(f32_to_bf16_rne(s * Q) << 16); }
+__device__ __forceinline__ RowScale int_row_scale(float largest) {
+  int e = (int)((as_u32(largest) >> 23) & 0xFF) - 127;
+  if (largest == 0.0f) e = 0;
+  const int E = max(-120, min(120, e - 10));           // both 2^-E and 2^E are normal fp32 numbers
+  return RowScale{as_f32((uint32_t)(127 - E) << 23), as_f32((uint32_t)(127 + E) << 23)};
+}
+// exact unless far below the row's largest
+__device__ __forceinline__ uint16_t int_scale_unit(float s, float Q, float down) {
+  return __builtin_bit_cast(uint16_t, (_Float16)(int_group_max(s, Q) * down));
+}
+
 // ------------------------------------------------------------------------ operand unpack
 // Per-thread slice of a tile row: 32 consecutive k (16 bytes of codes) plus its scales.
 struct Slice {
@@ -39,6 +57,8 @@ struct Slice {
 // mul: per-row epilogue factor (stride 1) or a single factor (stride 0).
 // panel: the panel layout.  marked: the sign of a row's factor says that the row holds INT3 codes beyond three bits
 // (always in the panel layout; set by the scale preparation of a row-major operand when it sees the codes)
+// raw_q: not 0 where `scales` are the INT quantizers' fp32 scales, of codes up to raw_q, which the split tiles prepare
+// themselves (RAW in pq_qgemm_split.hip); mul is null then
 // bias: bf16 value per row of this operand added to the product in the epilogue (used for the
 // weight operand, whose rows are the output columns), or null.
 struct OperandView {
@@ -51,6 +71,7 @@ struct OperandView {
   const float* mul;
   int mul_stride;
   bool panel = false, marked = false;
+  uint8_t raw_q = 0;
   const uint16_t* bias = nullptr;
 };
 
@@ -312,9 +333,10 @@ __device__ __forceinline__ bool any_wide(uint32_t wide, int* flags) {
   return __builtin_amdgcn_readfirstlane(any) != 0;
 }
 
-template <int BM, int BN, int WAVES, int KS, int OUT>
+// RAW: fp32 scales; the factors of the tile's rows and columns, and behind them 2^-E, are in LDS
+template <int BM, int BN, int WAVES, int KS, int OUT, bool RAW = false>
 __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const OperandView& W, int M, int N, int K,
-                                                int g_shift, int m0, int n0, const Output& out) {
+                                                int g_shift, int m0, int n0, const Output& out, const float* factors = nullptr) {
   static_assert(OUT != kOutDiff, "the selection quantizes its operands itself");
   const int lane = threadIdx.x & 63;
   const int row = lane & 31, half = lane >> 5;
@@ -326,6 +348,11 @@ __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const Oper
     const int64_t ar = min(m, M - 1), wr = min(nb + row, N - 1);
     const uint8_t *ac = A.codes + ar * A.code_row + half * 16, *wc = W.codes + wr * W.code_row + half * 16;
     const uint8_t *as = A.scales + ar * A.sc_row, *ws = W.scales + wr * W.sc_row;
+    const float* const downs = factors + kFactorBytes<BM, BN> / 4;
+    auto unit_at = [&](const uint8_t* at, int local) -> uint32_t {
+      if constexpr (RAW) return int_scale_unit(*reinterpret_cast<const float*>(at), (float)A.raw_q, downs[local]);
+      else return *reinterpret_cast<const uint16_t*>(at);
+    };
     float16_t sum = zero;
 #pragma unroll 1
     for (int ks = 0; ks < KS; ++ks) {
@@ -335,8 +362,7 @@ __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const Oper
         const int64_t unit = (s * kBK) >> g_shift;
         const uint4 a = *reinterpret_cast<const uint4*>(ac + (int64_t)s * A.code_step);
         const uint4 w = *reinterpret_cast<const uint4*>(wc + (int64_t)s * W.code_step);
-        const uint32_t sa = *reinterpret_cast<const uint16_t*>(as + unit * A.sc_step);
-        const uint32_t sw = *reinterpret_cast<const uint16_t*>(ws + unit * W.sc_step);
+        const uint32_t sa = unit_at(as + unit * A.sc_step, m - m0), sw = unit_at(ws + unit * W.sc_step, BM + nb - n0 + row);
         const float16_t sc = __builtin_amdgcn_mfma_f32_32x32x8f16(scale_operand(half == 0 ? sw : 0u), scale_operand(sa),
                                                                   zero, 0, 0, 0);
         const float16_t p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(e4m3_operand(w), e4m3_operand(a), zero, 0, 0,
@@ -348,12 +374,12 @@ __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const Oper
       for (int r = 0; r < 16; ++r) sum[r] = ks == 0 ? acc[r] : sum[r] + acc[r];
     }
     if (m >= M) continue;
-    const float am = fabsf(A.mul[(int64_t)m * A.mul_stride]);
+    const float am = fabsf(RAW ? factors[m - m0] : A.mul[(int64_t)m * A.mul_stride]);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int n = nb + r / 4 * 8 + half * 4 + r % 4;
       if (n >= N) continue;
-      float v = (sum[r] * 262144.0f) * (am * fabsf(W.mul[(int64_t)n * W.mul_stride]));
+      float v = (sum[r] * 262144.0f) * (am * fabsf(RAW ? factors[BM + n - n0] : W.mul[(int64_t)n * W.mul_stride]));
       if (W.bias) v += bf16_to_f32(W.bias[n]);
       if constexpr (OUT == kOutF32)
         reinterpret_cast<float*>(out.y)[(int64_t)m * out.ldy + n] = v;
@@ -530,6 +556,8 @@ enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kT
 // small outputs (pq_qgemm_split.hip)
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Outputs& out, int tile, hipStream_t st);
+// whether a product of row-major INT operands prepares their scales in the product kernel
+bool split_takes_raw_scales(int tile, int group, int64_t M, int64_t N, int64_t K);
 // the integer formats' large outputs with groups of 64 and more (pq_qgemm_group.hip)
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Outputs& out, int tile, hipStream_t st);

@@ -68,7 +68,9 @@ template <int TM, int TN, int WIDE, bool ROWS>
 constexpr int kSplitWaves = (ROWS || WIDE == kWideMarks) && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
 // FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 82 instead
 // of 56, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
-template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW>
+// RAW (row-major INT operands): the scales are the quantizers' fp32 ones.  The workgroup finds its rows' largest and a lane
+// turns each scale that it loads into the operand's unit.  See split_takes_raw_scales.
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW, bool RAW>
 __global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitWaves<TM, TN, WIDE, ROWS>, FEW ? 4 : 8))) void
 qgemm_split_kernel(
     OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT> out, int tiles_m, int tiles_n) {
@@ -89,7 +91,9 @@ qgemm_split_kernel(
 
   constexpr bool INT = MODE != kSplitNvfp4;            // factors of magnitude, the sign a mark
   const float nv_mul = INT ? 0.0f : A.mul[0] * W.mul[0];
-  Factors<BM, BN, T, INT> own_factors;
+  static_assert(!RAW || (INT && !ROWS), "fp32 scales are read directly");
+  float* const factors = part + split_lds<TM, TN, KS, WIDE, ROWS>() / 4;
+  Factors<BM, BN, T, INT && !RAW> own_factors;
   own_factors.load(A, W, M, N, m0, n0);
 
   // a fragment's lane: row lane % 32, k 32 * (lane / 32) .. + 31 of the step: 16 bytes of codes, one scale unit (packed
@@ -119,6 +123,7 @@ qgemm_split_kernel(
   struct Step {
     Slice a[TM], w[TN];
   };
+  using unit_t = std::conditional_t<RAW, uint32_t, uint16_t>;
   // A step past the last re-reads the last.  CUT: K ends in a step of 32 k; its missing upper half re-reads the lower one,
   // neutralised by a zero scale.  Other K have a loop without these tests: with them the 64 x 96 tile of NVFP4 takes 8.6 vector
   // instructions for a matrix instruction, without 7.3.
@@ -137,12 +142,12 @@ qgemm_split_kernel(
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
       f.a[j].codes = *reinterpret_cast<const uint4*>(ac + at(a_coff[j], dc));
-      f.a[j].sc = *reinterpret_cast<const uint16_t*>(as + at(a_soff[j], da));
+      f.a[j].sc = *reinterpret_cast<const unit_t*>(as + at(a_soff[j], da));
     }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
       f.w[i].codes = *reinterpret_cast<const uint4*>(wc + at(w_coff[i], dc));
-      f.w[i].sc = *reinterpret_cast<const uint16_t*>(ws + at(w_soff[i], dw));
+      f.w[i].sc = *reinterpret_cast<const unit_t*>(ws + at(w_soff[i], dw));
     }
   };
 
@@ -154,6 +159,41 @@ qgemm_split_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
+  float a_down[RAW ? TM : 1], w_down[RAW ? TN : 1];    // of this lane's rows
+  const float Q = (float)A.raw_q;
+  auto unit_of = [&](uint32_t sc, float down) -> uint32_t {
+    if constexpr (RAW) return int_scale_unit(as_f32(sc), Q, down);
+    else return sc;
+  };
+  // RAW: the factors of the tile's rows and columns to LDS, eight lanes a row, and what the scales are multiplied with here
+  auto prepare_rows = [&]() {
+    float* const downs = factors + kFactorBytes<BM, BN> / 4;
+    const int groups = K >> g_shift;
+#pragma unroll
+    for (int r0 = 0; r0 < BM + BN; r0 += T / 8) {
+      const int r = r0 + tid / 8, g0 = tid % 8;
+      const bool mine = r < BM + BN;
+      const int row = mine ? r : 0;
+      const float* s = reinterpret_cast<const float*>(
+          row < BM ? a_scales + (int64_t)min(row, M - 1 - m0) * A.sc_row : w_scales + (int64_t)min(row - BM, N - 1 - n0) * W.sc_row);
+      float mx = 0.0f;
+#pragma unroll 4
+      for (int g = g0; g < groups; g += 8) mx = fmaxf(mx, int_group_max(s[g], Q));
+#pragma unroll
+      for (int by = 1; by < 8; by <<= 1) mx = fmaxf(mx, __shfl_xor(mx, by, kWave));
+      const RowScale scale = int_row_scale(mx);
+      if (mine && g0 == 0) {
+        factors[r] = scale.up / Q;
+        downs[r] = scale.down;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TM; ++j) a_down[RAW ? j : 0] = downs[j * 32 + frag_row];
+#pragma unroll
+    for (int i = 0; i < TN; ++i) w_down[RAW ? i : 0] = downs[BM + i * 32 + frag_row];
+  };
+
   uint32_t wide = 0;
   // What the matrix unit takes for a share of a step: fp16 operands of 16 k (four shares), or the codes of all 64 k (one).
   constexpr int FMT = MODE == kSplitNvfp4 ? kNvfp4 : kInt4;           // INT3 nibbles unpack like INT4's
@@ -164,7 +204,9 @@ qgemm_split_kernel(
   PairScale sa[CODES ? 1 : TM][2], sw[CODES ? 1 : TN][2];             // of the step that is being unpacked
   auto unpack = [&](auto KK, const Step& f, bool k_ok, Frags& to) {
     constexpr int kk = decltype(KK)::value;
-    auto one = [&](const Slice& s, PairScale (&sc)[2]) {
+    auto one = [&](const Slice& raw, PairScale (&sc)[2], float down) {
+      Slice s = raw;
+      if constexpr (RAW && !CODES && kk == 0) s.sc = unit_of(raw.sc, down);
       if constexpr (CODES) {
         const uint4& c = s.codes;
         if constexpr (WIDE == kWideCodes) wide |= wide_codes(c.x) | wide_codes(c.y) | wide_codes(c.z) | wide_codes(c.w);
@@ -179,13 +221,13 @@ qgemm_split_kernel(
     };
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
-      to.a[j] = one(f.a[j], sa[CODES ? 0 : j]);
-      if constexpr (CODES) to.sa[j] = f.a[j].sc;
+      to.a[j] = one(f.a[j], sa[CODES ? 0 : j], a_down[RAW ? j : 0]);
+      if constexpr (CODES) to.sa[j] = unit_of(f.a[j].sc, a_down[RAW ? j : 0]);
     }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
-      to.w[i] = one(f.w[i], sw[CODES ? 0 : i]);
-      if constexpr (CODES) to.sw[i] = frag_half == 0 ? f.w[i].sc : 0u;
+      to.w[i] = one(f.w[i], sw[CODES ? 0 : i], w_down[RAW ? i : 0]);
+      if constexpr (CODES) to.sw[i] = frag_half == 0 ? unit_of(f.w[i].sc, w_down[RAW ? i : 0]) : 0u;
     }
   };
   auto multiply = [&](const Frags& f) {
@@ -240,6 +282,7 @@ qgemm_split_kernel(
     auto all_steps = [&](auto CUT) {
 #pragma unroll
       for (int p = 0; p < PD; ++p) load(CUT, ks + p * KS, raw[p]);
+      if constexpr (RAW) prepare_rows();
       auto k_ok = [&](int o) { return !decltype(CUT)::value || (ks + o * KS) * kBK + frag_half * 32 < K; };
       if constexpr (!kAhead) {
         for (int o = 0; o < n_own; o += PD) {
@@ -278,8 +321,9 @@ qgemm_split_kernel(
       }
     };
     if (ksteps <= KS) {                                // a step each at most: nothing to run ahead of
+      if (RAW || ks < ksteps) load(IntC<!CODES>{}, ks, raw[0]);
+      if constexpr (RAW) prepare_rows();
       if (ks < ksteps) {
-        load(IntC<!CODES>{}, ks, raw[0]);
         whole_step(raw[0], ks * kBK + frag_half * 32 < K);
       }
     } else if (!CODES && K % kBK)
@@ -403,8 +447,7 @@ qgemm_split_kernel(
     }
   }
 
-  float* const factors = part + split_lds<TM, TN, KS, WIDE, ROWS>() / 4;
-  own_factors.put(factors);
+  if constexpr (!RAW) own_factors.put(factors);
 
   // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
   const bool bias = W.bias != nullptr;
@@ -505,7 +548,7 @@ qgemm_split_kernel(
     if (any) {
       __threadfence();                                 // what the waves stored has arrived
       __syncthreads();
-      wide_codes_tile<BM, BN, KS, KS, OUT>(A, W, M, N, K, g_shift, m0, n0, out);
+      wide_codes_tile<BM, BN, KS, KS, OUT, RAW>(A, W, M, N, K, g_shift, m0, n0, out, factors);
     }
   }
 }
@@ -524,13 +567,24 @@ static bool rows_through_lds(int64_t n_tiles, int ks, int K) {
   return n_tiles > 256 && K >= (ks == 8 ? 8 : K % 256 == 0 ? 4 : 6) * kBK;
 }
 
-template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW = false>
+// Whether a product of row-major INT operands prepares their scales itself (RAW) instead of in a launch before it, which
+// takes 1.3 to 2.5 us of the device and 2.7 of the host.  Every workgroup then reads all scales of its rows ahead of its first
+// step and turns the units that it loads, which many groups a row or many rows a workgroup make longer than the launch.  Of
+// 110 random shapes of at most 256 tiles of all sizes the 75 that these lines take need 0.80 of the time, none more
+// than 1.006; the others 1.03, up to 1.23 (INT4 g64 841 x 1058 x 3392, 64 x 64 tiles, 14.9 -> 18.2 us).  us: INT4 g128 77 x 1000 x 1152 6.4 ->
+// 4.9, g64 48 x 1000 x 4096 13.4 -> 11.3, INT3 g128 300 x 1000 x 2048 12.8 -> 11.0.
+bool split_takes_raw_scales(int tile, int group, int64_t M, int64_t N, int64_t K) {
+  const int64_t groups = K / group;
+  return qgemm_tiles(tile, M, N) <= 256 && ((tile == kTileSplit32 && groups <= 128) || (tile == kTileSplit64x32 && groups <= 64));
+}
+
+template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW = false, bool RAW = false>
 static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
-  constexpr size_t shmem = split_lds<TM, TN, KS, WIDE, ROWS>() + kFactorBytes<BM, BN>;
+  constexpr size_t shmem = split_lds<TM, TN, KS, WIDE, ROWS>() + kFactorBytes<BM, BN> + (RAW ? (BM + BN) * 4 : 0);
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
-  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE, ROWS, FEW>;
+  auto kern = qgemm_split_kernel<MODE, TM, TN, KS, OUT, WIDE, ROWS, FEW, RAW>;
   static std::atomic<uint64_t> raised{0};
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), shmem, raised, "hipFuncSetAttribute(qgemm_split_kernel)")) return rc;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -553,6 +607,9 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
   }
   constexpr bool kMayBeFew = TN == 1 && MODE != kSplitE2m1, kFew = kMayBeFew && TM == 2;
+  if constexpr (TN == 1 && OUT != kOutDiff && (MODE == kSplitInt || (MODE == kSplitE2m1 && WIDE == kWideCodes))) {
+    if (A.raw_q) return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, kMayBeFew, true>(A, W, M, N, K, g_shift, out, st);
+  }
   if constexpr (kMayBeFew && TM == 1) {
     if (n_tiles * out.problems <= 512)
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, true>(A, W, M, N, K, g_shift, out, st);

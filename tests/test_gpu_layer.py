@@ -403,3 +403,46 @@ def test_row_and_column_factors_and_bias_of_every_tile(fmt, g, M, N, K, tile):
     assert ((yf.double() - xq @ wq.t()).abs() <= bound).all()
     assert torch.equal(y, yf.to(torch.bfloat16))
     assert torch.equal(yb, (yf + bias.float()).to(torch.bfloat16))
+
+
+def _int_operand(fmt, g, rows, K, gen, odd_codes):
+    """Row-major codes and scales of the quantizers' form fl32(h / Q), with rows of very different size, zero groups and a
+    zero row; odd_codes: nibbles that the quantizers do not write, in some rows."""
+    h = torch.exp2(torch.randint(-30, 30, (rows, 1), generator=gen, device=DEV).float()) * \
+        (torch.rand((rows, K // g), generator=gen, device=DEV) + 2.0 ** -12).to(torch.bfloat16).float()
+    h[torch.rand((rows, K // g), generator=gen, device=DEV) < 0.05] = 0.0
+    h[rows // 2] = 0.0
+    h = h.to(torch.bfloat16)
+    Q = 7 if fmt == pq.FMT_INT4 else 3
+    z = torch.randint(-Q, Q + 1, (rows, K), generator=gen, device=DEV)
+    if odd_codes:
+        z[::3] = torch.randint(-8, 8, z[::3].shape, generator=gen, device=DEV)
+    z &= 15
+    return (z[:, 0::2] | z[:, 1::2] << 4).to(torch.uint8).contiguous(), (h.double() / Q).float()
+
+
+@pytest.mark.parametrize("odd_codes", [False, True])
+@pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_INT4, 32, 1, 128, 32), (pq.FMT_INT4, 32, 77, 1000, 1184), (pq.FMT_INT4, 32, 33, 257, 4096), (pq.FMT_INT4, 64, 31, 45, 64),
+    (pq.FMT_INT4, 64, 500, 1021, 1088), (pq.FMT_INT4, 128, 77, 1000, 1152), (pq.FMT_INT4, 256, 300, 900, 512),
+    (pq.FMT_INT4, 32, 500, 1021, 2048), (pq.FMT_INT3, 32, 61, 1001, 544), (pq.FMT_INT3, 64, 61, 1001, 8192),
+    (pq.FMT_INT3, 128, 300, 900, 640), (pq.FMT_INT3, 64, 500, 1021, 4096), (pq.FMT_INT4, 64, 61, 1001, 8256)])
+def test_scales_prepared_in_the_product_kernel(fmt, g, M, N, K, odd_codes):
+    """pq_qgemm prepares the scales of small products inside the product kernel; pq_qgemm_prep and _run keep the launch for
+    it.  The same bits, on either side of the lines between the two, and those of the packed operands."""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K + g + odd_codes)
+    ac, as_ = _int_operand(fmt, g, M, K, gen, odd_codes)
+    wc, ws = _int_operand(fmt, g, N, K, gen, odd_codes)
+    ldy = (N + 7) // 8 * 8
+    ys = [torch.full((M, ldy), 3.0, dtype=t, device=DEV) for t in (torch.bfloat16, torch.bfloat16, torch.bfloat16, torch.float32, torch.float32)]
+    work = torch.empty(max(16, pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K)), dtype=torch.uint8, device=DEV)
+    pq.pq_qgemm(fmt, g, ac, as_, None, wc, ws, None, ys[0], workspace=work, N=N, ldy=ldy)
+    pq.pq_qgemm_prep(fmt, g, as_, ws, M, N, K, work)
+    pq.pq_qgemm_run(fmt, g, ac, as_, None, wc, ws, None, ys[1], work, N=N, ldy=ldy)
+    a, w = pq.pq_pack_operand(fmt, g, ac, as_), pq.pq_pack_operand(fmt, g, wc, ws)
+    pq.pq_qgemm_packed(fmt, g, a, None, w, None, ys[2], M, N, K, ldy=ldy)
+    pq.pq_qgemm_f32(fmt, g, ac, as_, None, wc, ws, None, ys[3], workspace=work, N=N, ldy=ldy)
+    pq.pq_qgemm_packed_f32(fmt, g, a, None, w, None, ys[4], M, N, K, ldy=ldy)
+    bits = [y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32) for y in ys]
+    assert torch.equal(bits[0], bits[1]) and torch.equal(bits[0], bits[2]) and torch.equal(bits[3], bits[4])
+    assert (ys[0][:, N:] == 3.0).all()
