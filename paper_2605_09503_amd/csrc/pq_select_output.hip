@@ -9,8 +9,8 @@
 // The batches of a call stand one below the other as the rows of one product, and several candidate orders share a
 // launch (see plan_of): one quantizer launch for all their operands, one product launch whose grid holds all their
 // tiles.  With a product launch for each order and batch, 1024 x 3072 x 3072 with two batches of INT4 took 14
-// products of 30 us, none of which filled the chip with large tiles, and 21 quantizer launches: 715 us, now 406
-// (NVFP4 659 -> 423, INT3 g64 3 x 700 x 1000 x 1152 354 -> 131, INT4 g64 4 x 4608 x 3072 x 3072 3.73 -> 3.14 ms).
+// products of 30 us, none of which filled the chip with large tiles, and 21 quantizer launches: 715 us, now 381
+// (NVFP4 659 -> 379, INT3 g64 3 x 700 x 1000 x 1152 354 -> 128, INT4 g64 4 x 4608 x 3072 x 3072 3.73 -> 2.98 ms).
 #include <string.h>
 
 #include <algorithm>
@@ -23,108 +23,150 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-constexpr int kRefTile = 128;                 // output tile edge
+constexpr int kRefRows = 128;                 // rows of an output tile
 constexpr int kRefStep = 64;                  // K elements per step
-constexpr int kRefRowBytes = kRefStep * 2 + 16;   // padded LDS row, as in pq_qgemm.hip
-constexpr int kRefStage = 2 * kRefTile * kRefRowBytes;
+constexpr int kRefRowBytes = kRefStep * 2;
+
+// Columns of the tile and stages of LDS: 128 with two, two workgroups a unit, or 192 with three and one.
+template <int TN>
+struct RefTile {
+  static constexpr int cols = TN * 64, stages = TN == 2 ? 2 : 3;
+  static constexpr int stage_bytes = (kRefRows + cols) * kRefRowBytes, lds_bytes = stages * stage_bytes;
+  static constexpr int loads = (kRefRows + cols) / 32;      // 16-byte pieces of a step, per thread
+};
+
+// 16 bytes a lane from memory into LDS, 1 KB a wave from byte `to` on, without a register in between: by a 64-bit address, or
+// by a uniform base and an offset.  The wait for them is ref_wait's; nothing else in the kernel uses m0.
+__device__ __forceinline__ void load_to_lds(uint32_t to, const uint8_t* from) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory");
+}
+__device__ __forceinline__ void load_to_lds(uint32_t to, const uint8_t* base, uint32_t offset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(offset), "s"(base) : "memory");
+}
+// all but the last N loads of this wave have arrived and its LDS reads are done; then the workgroup meets
+template <int N>
+__device__ __forceinline__ void ref_wait() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
 
 // Y[m, n] = sum_k X[m, k] W[n, k], bf16 inputs, fp32 accumulation (v_mfma_f32_32x32x16_bf16), fp32 output, and the
-// tile's sum of squares (+)= to sq.  X: the rows of all batches.  128 x 128 tile, four waves of 64 x 64; K % 32 == 0.  A
-// step's pieces are loaded two steps before they are multiplied and stored, a step before, into the other of two stages: one
-// barrier a step.  Bound by the stores and reads of the stages, which a tile of this size has two of for each product: 70 us
-// for 2048 x 3072 x 3072 (a launch for each half, loaded one step ahead: 48 us each).
+// tile's sum of squares (+)= to sq.  X: the rows of all batches.  Four waves of 64 x 32 TN; K % 32 == 0.  The pieces of a step go
+// from memory straight into LDS, one or two steps ahead: through registers their stores took more of the LDS pipe than the
+// reads did.  Rows of 128 bytes lie unpadded, a row's 16-byte pieces permuted by (row / 2) % 8, so that the 16 rows of
+// a read have a piece of every bank.  One barrier a step: behind it the step has arrived, and the stage of the step before is
+// free.  us, 128 x 128 tiles through registers -> now: 2048 x 3072 x 3072 69 -> 49
+// (128 x 192, one a unit), 3072 x 3072 x 1024 44 -> 41; 0.77 us a step of 64 and 12 to 16 that do not depend on K (a store of rows through LDS
+// and a start at another k for every tile: the same).
+template <int TN>
 __global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint16_t* __restrict__ w,
                                                        int M, int N, int K, float* __restrict__ y, int64_t ldy,
-                                                       double* __restrict__ sq, int add) {
+                                                       double* __restrict__ sq, int add, int tiles_m, int tiles_n) {
+  using R = RefTile<TN>;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = wave >> 1;
-  const int m0 = blockIdx.x * kRefTile, n0 = blockIdx.y * kRefTile;
-  // loader: 128 rows x 128 bytes per operand; thread t takes piece t % 8 of rows t / 8 + 32 i
-  const int ld_row = tid >> 3, ld_piece = tid & 7;
-  const uint16_t *xr[4], *wr[4];
+  int tile_m, tile_n;
+  assign_tile(tiles_m, tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * kRefRows, n0 = tile_n * R::cols;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+
+  // loader: the wave's load i takes rows 8 (4 i + wave) .. + 7 of an operand, lane l the piece that belongs at place l % 8 of
+  // row l / 8
+  constexpr int XL = kRefRows / 32, WL = R::cols / 32;
+  const uint8_t* x_at[XL];
+  uint32_t w_at[WL];
+  const int ld_row = lane >> 3;
+  auto piece_of = [&](int row) { return (lane & 7) ^ ((row >> 1) & 7); };
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = min(m0 + ld_row + 32 * i, M - 1), batch = m / (int)xs.rows;
+  for (int i = 0; i < XL; ++i) {
+    const int row = 8 * (4 * i + wave) + ld_row, m = min(m0 + row, M - 1), batch = m / (int)xs.rows;
     const uint16_t* x = xs.p[0];
 #pragma unroll
     for (int b = 1; b < kMaxMomentBatches; ++b) x = batch == b ? xs.p[b] : x;      // an index by lane would go through scratch
-    xr[i] = x + (int64_t)(m - batch * (int)xs.rows) * K + ld_piece * 8;
-    wr[i] = w + (int64_t)min(n0 + ld_row + 32 * i, N - 1) * K + ld_piece * 8;
+    x_at[i] = reinterpret_cast<const uint8_t*>(x + (int64_t)(m - batch * (int)xs.rows) * K) + piece_of(row) * 16;
   }
-  const int st = ld_row * kRefRowBytes + ld_piece * 16;
-  const int frag_row = lane & 31, frag_half = lane >> 5;
-  struct Pieces {
-    int4v a[4], w[4];
-  };
-  // a step past the last re-reads the start of the rows and is not multiplied; the upper half of a last step of 32 is zero
-  auto load = [&](int k0, Pieces& p) {
-    const int k = k0 + ld_piece * 8 < K ? k0 : -ld_piece * 8;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      p.a[i] = *reinterpret_cast<const int4v*>(xr[i] + k);
-      p.w[i] = *reinterpret_cast<const int4v*>(wr[i] + k);
+  for (int i = 0; i < WL; ++i) {
+    const int row = 8 * (4 * i + wave) + ld_row;
+    w_at[i] = (uint32_t)min(row, N - 1 - n0) * ((uint32_t)K * 2u) + piece_of(row) * 16;
+  }
+  const uint8_t* w_tile = reinterpret_cast<const uint8_t*>(w + (int64_t)n0 * K);
+  const int steps = (K + kRefStep - 1) / kRefStep;
+  const bool half_last = K % kRefStep != 0;
+  // a step past the last re-reads the last and is not multiplied; the missing upper half of a last step of 32 re-reads the lower
+  auto load = [&](int step, int stage) {
+    const int st = min(step, steps - 1);               // uniform
+    const uint32_t to = lds0 + stage * R::stage_bytes;
+    const bool half = half_last && st == steps - 1;    // uniform
+    const int64_t at = (int64_t)st * kRefRowBytes;
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const int row = 8 * (4 * i + wave) + ld_row;
+      load_to_lds(to + (4 * i + wave) * 1024, x_at[i] + (at - (half && piece_of(row) >= 4 ? 64 : 0)));
     }
-  };
-  auto put = [&](unsigned char* stage, int k0, const Pieces& p) {
-    const bool ok = k0 + ld_piece * 8 < K;
-    const int4v zero = {0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<int4v*>(stage + st + 32 * i * kRefRowBytes) = ok ? p.a[i] : zero;
-      *reinterpret_cast<int4v*>(stage + kRefTile * kRefRowBytes + st + 32 * i * kRefRowBytes) = ok ? p.w[i] : zero;
+    for (int i = 0; i < WL; ++i) {
+      const int row = 8 * (4 * i + wave) + ld_row;
+      load_to_lds(to + kRefRows * kRefRowBytes + (4 * i + wave) * 1024, w_tile + at, w_at[i] - (half && piece_of(row) >= 4 ? 64u : 0u));
     }
   };
 
-  float16_t acc[2][2];
+  const int frag_row = lane & 31, frag_half = lane >> 5;
+  int piece[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int kk = 0; kk < 4; ++kk) piece[kk] = ((kk * 2 + frag_half) ^ ((frag_row >> 1) & 7)) * 16;
+  const int x_row = (wave_m * 64 + frag_row) * kRefRowBytes;
+  const int w_row = (kRefRows + wave_n * (R::cols / 2) + frag_row) * kRefRowBytes;
+
+  float16_t acc[TN][2];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  Pieces pieces[2];
-  load(0, pieces[0]);
-  load(kRefStep, pieces[1]);
-  put(lds, 0, pieces[0]);
-  __syncthreads();
-  // step k0, in stage P; pieces[P ^ 1] holds the next one, if there is one, pieces[P] is free
-  auto turn = [&](auto Pc, int k0, auto last) {
-    constexpr int P = decltype(Pc)::value;
-    constexpr bool kMore = !decltype(last)::value;
-    if constexpr (kMore) load(k0 + 2 * kRefStep, pieces[P]);
-    const unsigned char* a_t = lds + P * kRefStage;
-    const unsigned char* w_t = a_t + kRefTile * kRefRowBytes;
+  // The fragments of 16 k are read while those before them are multiplied, the first of a step behind the barrier that stands
+  // before the last 16 k of the step before: there that step's stage is read and free for the step R::stages on.
+  bf16x8_t xf[2][2], wf[2][TN];
+  auto read = [&](int set, int stage, int kk) {
+    const unsigned char* at = lds + stage * R::stage_bytes + piece[kk];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      bf16x8_t xf[2], wf[2];
+    for (int j = 0; j < 2; ++j) xf[set][j] = *reinterpret_cast<const bf16x8_t*>(at + x_row + j * 32 * kRefRowBytes);
+#pragma unroll
+    for (int i = 0; i < TN; ++i) wf[set][i] = *reinterpret_cast<const bf16x8_t*>(at + w_row + i * 32 * kRefRowBytes);
+  };
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        xf[j] = *reinterpret_cast<const bf16x8_t*>(a_t + (wave_m * 64 + j * 32 + frag_row) * kRefRowBytes +
-                                                   (kk * 2 + frag_half) * 16);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        wf[i] = *reinterpret_cast<const bf16x8_t*>(w_t + (wave_n * 64 + i * 32 + frag_row) * kRefRowBytes +
-                                                   (kk * 2 + frag_half) * 16);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i], xf[j], acc[i][j], 0, 0, 0);
-    }
-    if constexpr (kMore) {
-      put(lds + (P ^ 1) * kRefStage, k0 + kRefStep, pieces[P ^ 1]);
-      __syncthreads();
-    }
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][i], xf[set][j], acc[i][j], 0, 0, 0);
   };
-  // two steps a trip, then an odd last one (a step of zeros in its place: 2048 x 3072 x 64 19.6 us, so 16.9; x 320 20.6, 18.8)
-  int k0 = 0;
-  for (; k0 + kRefStep < K; k0 += 2 * kRefStep) {
-    turn(IntC<0>{}, k0, IntC<0>{});
-    turn(IntC<1>{}, k0 + kRefStep, IntC<0>{});
+#pragma unroll
+  for (int p = 0; p < R::stages; ++p) load(p, p);
+  ref_wait<(R::stages - 1) * R::loads>();
+  read(0, 0, 0);
+  int stage = 0;
+  for (int s = 0; s < K / kRefStep; ++s) {
+#pragma unroll
+    for (int kk = 0; kk < 3; ++kk) {
+      read((kk + 1) & 1, stage, kk + 1);
+      multiply(kk & 1);
+    }
+    ref_wait<(R::stages - 2) * R::loads>();
+    load(s + R::stages, stage);
+    stage = stage + 1 == R::stages ? 0 : stage + 1;
+    read(0, stage, 0);
+    multiply(1);
   }
-  if (k0 < K) turn(IntC<0>{}, k0, IntC<1>{});
+  if (half_last) {                                     // uniform
+    read(1, stage, 1);
+    multiply(0);
+    multiply(1);
+  }
+  ref_wait<0>();                                       // the sums below take the stages
   // lane holds, per 32 x 32 block, column m = lane % 32 and rows n = 8 (r / 4) + 4 (lane / 32) + r % 4
   double s2 = 0.0;
 #pragma unroll
@@ -132,10 +174,10 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint
     const int m = m0 + wave_m * 64 + j * 32 + frag_row;
     if (m >= M) continue;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int n = n0 + wave_n * 64 + i * 32 + q * 8 + frag_half * 4;
+        const int n = n0 + wave_n * (R::cols / 2) + i * 32 + q * 8 + frag_half * 4;
         float* yo = y + (int64_t)m * ldy + n;
         const float v[4] = {acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
         if (n + 3 < N) *reinterpret_cast<float4*>(yo) = make_float4(v[0], v[1], v[2], v[3]);
@@ -148,8 +190,30 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint
         }
       }
   }
-  store_diff(s2, reinterpret_cast<double*>(lds), 256, blockIdx.y * gridDim.x + blockIdx.x,
-             Output{kOutDiff, sq, 0, nullptr, add != 0});
+  store_diff(s2, reinterpret_cast<double*>(lds), 256, tile_m * tiles_n + tile_n, Output{kOutDiff, sq, 0, nullptr, add != 0});
+}
+
+int64_t ref_tiles(int64_t M, int64_t N, int cols) { return ((M + kRefRows - 1) / kRefRows) * ((N + cols - 1) / cols); }
+
+// Columns of the reference product's tile: the ones whose fullest unit has the fewer outputs; the smaller where it is the same
+// (two workgroups run beside each other).
+int ref_cols(int64_t M, int64_t N) {
+  const auto fullest = [&](int cols) { return (ref_tiles(M, N, cols) + 255) / 256 * cols; };
+  return fullest(192) < fullest(128) ? 192 : 128;
+}
+
+template <int TN>
+int launch_ref(const RowBatches& x, const void* w, int64_t M, int64_t N, int64_t K, float* y, int64_t ldy, double* sq, bool add,
+               hipStream_t st) {
+  using R = RefTile<TN>;
+  static std::atomic<uint64_t> raised{0};
+  auto kern = ref_gemm_kernel<TN>;
+  if (int rc = allow_lds(reinterpret_cast<const void*>(kern), R::lds_bytes, raised, "hipFuncSetAttribute(ref_gemm_kernel)")) return rc;
+  const int64_t tiles_m = (M + kRefRows - 1) / kRefRows, tiles_n = (N + R::cols - 1) / R::cols;
+  if (tiles_m * tiles_n > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), R::lds_bytes, st, x, (const uint16_t*)w, (int)M, (int)N,
+                     (int)K, y, ldy, sq, add, (int)tiles_m, (int)tiles_n);
+  return check_hip(hipGetLastError(), "ref_gemm_kernel");
 }
 
 // sums[c] = sum of the tiles of candidate c (c < n_cand), sums[den_at] = sum of the reference's tiles; fixed order
@@ -222,10 +286,6 @@ struct OutWs {
 
 // tiles of the smallest size any product kernel takes
 size_t out_tiles(int64_t M, int64_t N) { return (size_t)((M + 31) / 32) * ((N + 31) / 32); }
-size_t ref_tiles(int64_t M, int64_t N) {
-  return (size_t)((M + kRefTile - 1) / kRefTile) * ((N + kRefTile - 1) / kRefTile);
-}
-
 size_t carve_out(void* base, const Plan& p, pq_format fmt, int group, int64_t M, int64_t N, int64_t K, int n_batches,
                  OutWs* w) {
   size_t off = 0;
@@ -243,7 +303,7 @@ size_t carve_out(void* base, const Plan& p, pq_format fmt, int group, int64_t M,
   const size_t o_wop = take(p.orders * operand_bytes(fmt, group, N, K));
   const size_t o_ts = take(2 * sizeof(float));
   const size_t o_num = take(kMaxCandOut * out_tiles(rows, N) * 8);
-  const size_t o_den = take(ref_tiles(rows, N) * 8);
+  const size_t o_den = take((size_t)ref_tiles(rows, N, 128) * 8);         // the smaller tile
   const size_t o_sums = take((size_t)kNumSums * 8);
   if (w) {
     char* b = (char*)base;
@@ -327,18 +387,14 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
     return x;
   };
   // the unquantized products, once
-  static std::atomic<uint64_t> raised{0};
-  if ((rc = allow_lds(reinterpret_cast<const void*>(ref_gemm_kernel), 2 * kRefStage, raised,
-                      "hipFuncSetAttribute(ref_gemm_kernel)")))
-    return rc;
+  const int cols = ref_cols(stack * M, N);
   for (int b0 = 0; b0 < n_batches; b0 += stack) {
     int64_t rows;
     const RowBatches x = rows_from(b0, &rows);
-    const dim3 grid((unsigned)((rows + kRefTile - 1) / kRefTile), (unsigned)((N + kRefTile - 1) / kRefTile));
-    hipLaunchKernelGGL(ref_gemm_kernel, grid, dim3(256), 2 * kRefStage, st, x, (const uint16_t*)w, (int)rows, (int)N, (int)K,
-                       W.y_ref + (size_t)b0 * M * ldn, ldn, W.den, b0 > 0);
+    float* y = W.y_ref + (size_t)b0 * M * ldn;
+    rc = cols == 192 ? launch_ref<3>(x, w, rows, N, K, y, ldn, W.den, b0 > 0, st) : launch_ref<2>(x, w, rows, N, K, y, ldn, W.den, b0 > 0, st);
+    if (rc) return rc;
   }
-  if ((rc = check_hip(hipGetLastError(), "ref_gemm_kernel"))) return rc;
 
   const int64_t most_rows = stack * M;
   const int tile = tile_of_call(fmt, group, M, N, K, plan);
@@ -364,7 +420,7 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
     }
   }
   hipLaunchKernelGGL(tile_sums_kernel, dim3((unsigned)(n_cand + 1)), dim3(256), 0, st, W.num, (int64_t)num_stride,
-                     qgemm_tiles(tile, most_rows, N), W.den, (int64_t)ref_tiles(most_rows, N), n_cand, kMaxCandOut, W.sums);
+                     qgemm_tiles(tile, most_rows, N), W.den, ref_tiles(most_rows, N, cols), n_cand, kMaxCandOut, W.sums);
   if ((rc = check_hip(hipGetLastError(), "tile_sums_kernel"))) return rc;
 
   double* h = pinned_doubles(kNumSums);

@@ -446,3 +446,25 @@ def test_scales_prepared_in_the_product_kernel(fmt, g, M, N, K, odd_codes):
     bits = [y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32) for y in ys]
     assert torch.equal(bits[0], bits[1]) and torch.equal(bits[0], bits[2]) and torch.equal(bits[3], bits[4])
     assert (ys[0][:, N:] == 3.0).all()
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_NVFP4, 16, 1000, 3001, 96), (pq.FMT_NVFP4, 16, 1000, 3001, 32), (pq.FMT_INT4, 64, 1000, 3001, 192),     # 128 x 192 tiles
+    (pq.FMT_NVFP4, 16, 65, 131, 32), (pq.FMT_INT4, 64, 65, 131, 64), (pq.FMT_NVFP4, 16, 129, 257, 160), (pq.FMT_INT3, 64, 130, 390, 448)])
+def test_output_error_against_the_unquantized_product(fmt, g, M, N, K):
+    """Both tiles of the unquantized product, ragged edges, one step of K and fewer than its stages, a last step of 32.  An
+    element of either product is off by at most eps = (K + 4) 2^-24 sum |x||w|, so ||Y||^2 by 2 ||Y|| ||eps|| + ||eps||^2, and the
+    error's numerator by the same with the difference in Y's place and 2 eps."""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K + g)
+    xs = [(torch.randn((M, K), generator=gen, device=DEV) * torch.exp(torch.randn(K, generator=gen, device=DEV))).to(torch.bfloat16) for _ in range(2)]
+    w = torch.randn((N, K), generator=gen, device=DEV).to(torch.bfloat16)
+    sa, sw = sum(x.double().square().sum(0) for x in xs), w.double().square().sum(0)
+    Ta, Tw = ((t.float().abs().max() / 2688).reshape(1) for t in (torch.cat(xs), w))
+    perm = torch.empty(K, dtype=torch.int32, device=DEV)
+    rep = pq.pq_select_perm_output_error(fmt, g, sa, sw, xs, w, float(Ta), float(Tw), perm)
+    x = torch.cat(xs)
+    y = x.double() @ w.double().t()
+    d = y - _dequantized(fmt, g, x, Ta)[2] @ _dequantized(fmt, g, w, Tw)[2].t()
+    eps = 1.2 * (K + 4) * 2.0 ** -24 * (x.double().abs() @ w.double().abs().t()).norm()       # 1.2: quantized magnitudes are larger
+    assert abs(rep.sum_x2 - y.norm() ** 2) <= 2 * y.norm() * eps + eps ** 2
+    assert abs(rep.e_orig * rep.sum_x2 - d.norm() ** 2) <= 2 * d.norm() * 2 * eps + 4 * eps ** 2
