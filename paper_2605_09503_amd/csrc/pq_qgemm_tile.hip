@@ -10,15 +10,16 @@ namespace pq {
 // stores of the columns past the last whole eight, one by one in the workgroups of the right edge (3.5 to 10 us of a
 // 256-row tile at N mod 8 = 7: without that term INT3 g64 2892 x 2765 x 832 took the 224-row tile at 26.6 us; 64 x 64
 // takes 21.7).
-// The coefficients (us) are least-squares fits of the logarithm of measured times, graph replays, over 1285 shapes of
-// 1e7 to 7e11 operations: NVFP4 303, INT4 and INT3 982 with groups of 32, 64, 128 and 256, 16 to 8192 rows, 128 to 12288
-// columns, K 96 to 12288, a quarter of them round sizes, half of them where a round of large tiles is partly or
-// just filled; then moved by at most 4 % a tile so that the choices cost least.  They were fitted with four waves a 64 x 64
-// and 64 x 96 tile, to single products: what eight waves take (below) and launches of several problems is not in them.
-// Measured with the kernels as they are, all tiles of 10900 random shapes of these ranges, packed: the choice costs 0.54 %
-// over the best tile in the mean, more than 5 % for 4.3 % of them, at most 21 % (INT4 g32 132 x 11376 x 160, 128 x 128 8.9 us, 64 x
-// 64 7.3).  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
-// 1024 x 3072 22 | 30 (of 128 x 128), 2048 x 3072 41 | 47, 4608 x 3072 92 | 79.
+// The coefficients (us) began as least-squares fits of the logarithm of measured times (graph replays, 1285 shapes of 1e7 to 7e11
+// operations, 16 to 8192 rows, 128 to 12288 columns, K 96 to 12288).  Those of the first three rows were then moved, a few
+// at a time, wherever that made the choices cost less over 9400 random shapes of which every tile was timed with the kernels as they
+// are: what they predict are ratios of neighbouring tiles, no longer times.  Over those shapes the choice costs over the best
+// tile in the mean (more than 5 % for, at most), before and now: NVFP4 1.2 % (7.5 %, 36 %), 0.5 % (3.6 %, 36 %); groups of 32 0.7 % (4.5 %, 39 %),
+// 0.2 % (1.4 %, 30 %); INT4 1.2 % (6.4 %, 51 %), 0.4 % (2.2 %, 38 %).  Where the choice changed (5 to 7 % of the shapes) packed operands
+// take 0.89 to 0.93 of the time and row-major ones 0.96 to 0.99 (49 measured; INT4 g64 557 x 2211 x 384 packed 1.014, NVFP4 37 x 9559 x
+// 1920 1.12, 1.25).  INT3 with larger groups keeps its first fit: packed 0.91, but row-major 1.01, up to 1.26.  In single products;
+// launches of several problems are not in them.  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
+// 1024 x 3072 22 | 32 (of 128 x 128), 2048 x 3072 37 | 47 (the same), 4608 x 3072 81 | 70.
 struct TileCost {
   float a, b, l0, l1, th, odd;
 };
@@ -29,15 +30,15 @@ static constexpr TileSize kTileSize[] = {{0, 0}, {256, 256}, {128, 128}, {224, 2
 // rows: NVFP4; INT4 and INT3 with groups of 32; INT4 with larger groups; INT3 with larger groups.  Columns: the tiles in
 // the order of their numbers.
 static constexpr TileCost kTileCost[4][8] = {
-    {{}, {9.46f, 1.347f, 0.0f, 0.0f, 1.0f, 1.4f}, {1.98f, 0.498f, 4.94f, 0.637f, 0.632f, 0.44f}, {9.17f, 1.283f, 0.0f, 0.0f, 0.858f, 1.2f},
-     {0.511f, 0.05455f, 3.35f, 0.0635f, 0.899f, 0.0f}, {1.06f, 0.07814f, 2.85f, 0.0949f, 0.929f, 0.0f}, {1.1f, 0.1194f, 3.85f, 0.168f, 0.762f, 0.079f},
-     {2.13f, 0.166f, 4.01f, 0.219f, 0.681f, 0.091f}},
-    {{}, {9.68f, 1.416f, 0.0f, 0.0f, 0.964f, 1.3f}, {2.13f, 0.537f, 4.19f, 0.66f, 0.593f, 0.54f}, {9.92f, 1.362f, 0.0f, 0.0f, 0.794f, 0.96f},
-     {0.501f, 0.06657f, 3.24f, 0.0619f, 0.841f, 0.0f}, {1.03f, 0.09627f, 2.85f, 0.116f, 0.868f, 0.0f}, {1.11f, 0.1401f, 3.89f, 0.184f, 0.71f, 0.05f},
-     {1.92f, 0.1927f, 4.15f, 0.229f, 0.808f, 0.12f}},
-    {{}, {10.0f, 1.305f, 1.33f, 0.0f, 0.975f, 1.1f}, {2.17f, 0.5552f, 4.14f, 0.696f, 0.645f, 0.49f}, {9.03f, 1.195f, 1.93f, 0.0f, 0.949f, 0.93f},
-     {0.5f, 0.06711f, 3.21f, 0.0f, 0.915f, 0.0f}, {1.04f, 0.09957f, 2.85f, 0.0f, 0.813f, 0.0f}, {1.09f, 0.1439f, 3.9f, 0.176f, 0.832f, 0.065f},
-     {1.97f, 0.1987f, 4.39f, 0.235f, 0.662f, 0.11f}},
+    {{}, {10.14f, 1.336f, 0.4999f, 0.03418f, 0.9593f, 1.699f}, {2.172f, 0.4726f, 4.863f, 0.05092f, 0.7723f, 0.5571f}, {10.48f, 1.201f, 0.13f, 0.07795f, 1.0f, 1.064f},
+     {0.6316f, 0.06518f, 3.127f, 0.06229f, 0.2271f, 0.002154f}, {1.126f, 0.07982f, 2.681f, 0.006329f, 0.7159f, 0.01633f}, {1.082f, 0.108f, 3.559f, 0.1499f, 0.6245f, 0.1685f},
+     {1.828f, 0.1479f, 3.748f, 0.02096f, 0.6285f, 0.1696f}},
+    {{}, {9.68f, 1.494f, 0.2064f, 0.0f, 0.9599f, 1.2f}, {2.072f, 0.553f, 4.296f, 1.133f, 0.8489f, 0.5345f}, {9.877f, 1.34f, 0.09746f, 0.03907f, 0.9639f, 1.174f},
+     {0.501f, 0.06817f, 3.24f, 0.05716f, 0.8612f, 0.01206f}, {1.03f, 0.09488f, 2.85f, 0.1271f, 0.8889f, 0.0f}, {1.108f, 0.1398f, 3.774f, 0.184f, 0.7875f, 0.03402f},
+     {1.887f, 0.1908f, 3.921f, 0.2287f, 0.7511f, 0.101f}},
+    {{}, {10.78f, 1.33f, 1.034f, 0.001557f, 1.0f, 1.105f}, {2.17f, 0.5597f, 3.94f, 1.029f, 0.8401f, 0.4839f}, {9.283f, 1.259f, 1.786f, 0.003477f, 1.0f, 0.9902f},
+     {0.5175f, 0.07548f, 3.21f, 0.02426f, 0.8443f, 0.0f}, {1.042f, 0.09851f, 2.85f, 0.009332f, 0.8344f, 0.0f}, {1.026f, 0.1439f, 3.9f, 0.1786f, 0.8164f, 0.04263f},
+     {1.762f, 0.1987f, 4.39f, 0.2438f, 0.6367f, 0.09061f}},
     {{}, {9.96f, 0.9593f, 0.0f, 0.0f, 0.947f, 1.4f}, {2.18f, 0.5174f, 3.71f, 0.858f, 0.616f, 0.55f}, {9.34f, 0.8692f, 0.0f, 0.0f, 0.893f, 1.2f},
      {0.609f, 0.03245f, 3.26f, 0.0435f, 0.744f, 0.0f}, {1.1f, 0.04921f, 2.92f, 0.0676f, 0.699f, 0.0f}, {1.28f, 0.07574f, 3.61f, 0.201f, 0.75f, 0.065f},
      {2.32f, 0.1103f, 4.02f, 0.176f, 0.698f, 0.038f}},
