@@ -14,17 +14,17 @@
 // sign << 7 | |z| is z 2^-9 exactly (all sixteen nibbles, -8 included).  INT3: E2M1, where 0, .5, 1, 1.5, 2
 // are the codes 0..4, so a nibble sign << 3 | |z| is z / 2 exactly for |z| <= 4.
 //
-// What bounds it.  On this chip the matrix and the vector instructions of a SIMD's two waves overlap in part only
-// (measured: a 32-cycle matrix instruction hides four vector instructions, a 64-cycle one twelve, every further one costs
-// 2.7 cycles, as much as alone), so a 32 x 32 x 64 block costs not much less than the sum of both:
+// What bounds it.  Beside matrix instructions a vector instruction takes an issue slot of 4.2 cycles and the matrix
+// instruction one more; what does not fit into the matrix cycles is added to them (measured with two waves a SIMD: 6
+// beside a 32-cycle one 34 to 39 cycles, 8 44, 16 69 to 80).  A 32 x 32 x 64 block takes:
 //   fp16 operands that carry their scale (pq_qgemm.hip)   128 matrix cycles + 16 vector instructions (the unpack)
 //   8-bit codes (here, INT4)                          64 + 32 matrix cycles + 31 (16 multiply-adds, 11 of unpack)
 //   4-bit codes (here, INT3)                          32 + 32 matrix cycles + 23 (16 multiply-adds, 4 of unpack)
 // and the 8- and 4-bit instructions draw less power: the chip holds 2.3 GHz here and 1.9 GHz there.  Forming S
 // on the vector unit instead would be 16 more instructions a block.  Measured, us and TFLOP/s (before: fp16):
-//   INT3 g64   4608 x 3072 x 3072     76 -> 52  (1.67 PFLOP/s)    8192 x 12288 x 3072   490 -> 332 (1.86)
-//   INT4 g64   4608 x 3072 x 3072     80 -> 68  (1.28)            8192 x 12288 x 3072   515 -> 430 (1.44)
-//   INT4 g64   4608 x 3072 x 12288   295 -> 240 (1.45)
+//   INT3 g64   4608 x 3072 x 3072     76 -> 49  (1.77 PFLOP/s)    8192 x 12288 x 3072   490 -> 307 (2.01)
+//   INT4 g64   4608 x 3072 x 3072     80 -> 66  (1.31)            8192 x 12288 x 3072   515 -> 411 (1.50)
+//   INT4 g64   4608 x 3072 x 12288   295 -> 234 (1.49)
 // Groups of 32 would need two half-empty matrix products and two scale products a block, 128 matrix cycles again,
 // and 32 multiply-adds: 510 us against 477 on INT3 8192 x 12288 x 3072, so they stay on the fp16 kernel, as do NVFP4's
 // groups of 16.  Issuing the next block's matrix instructions before this block's multiply-adds needs 16 to 32
@@ -58,8 +58,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   constexpr int A_ROWS = SL * (T / 2);
   constexpr int RB = FP4 ? 32 : 64;                    // LDS bytes of a row: 64 codes
   constexpr int NP = RB / 32;                          // 16-byte pieces of a 32-code slice
-  constexpr int A_CODES = 0, W_CODES = A_ROWS * RB, A_SC = W_CODES + BN * RB, W_SC = A_SC + A_ROWS * 2;
-  constexpr int STAGE_BYTES = W_SC + BN * 2, STAGES = 4;
+  constexpr int A_CODES = 0, W_CODES = A_ROWS * RB, A_SC = W_CODES + BN * RB, W_SC = A_SC + A_ROWS * 4;
+  constexpr int STAGE_BYTES = W_SC + BN * 4, STAGES = 4;
   constexpr int OUT_BYTES = OUT != kOutBf16 ? 0 : BM * (BN * 2 + 16);
   constexpr int SMEM_BYTES = STAGES * STAGE_BYTES > OUT_BYTES ? STAGES * STAGE_BYTES : OUT_BYTES;
   constexpr int FMT_SEL = FP4 ? 4 : 0;                 // operand format field of the matrix instruction
@@ -76,44 +76,32 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   const int wave_n = RAGGED_M ? wave >> 1 : wave / WGM;
   const int tm_cnt = RAGGED_M ? __builtin_amdgcn_readfirstlane(wave_m == WGM - 1 ? TM_LAST : TM) : TM;
 
-  // loader: this thread owns tile rows tid / 2 + q * (T / 2), k offset 32 * (tid & 1), of both operands
+  // loader: this thread owns tile row tid / 2, k offset 32 * (tid & 1), of both operands
   const int ld_row = tid >> 1, ld_half = tid & 1;
-  bool a_ok[SL], w_ok[SL];
-  // addresses: a uniform part (the tile, the step) and a 32-bit offset inside the tile
-  uint32_t a_coff[SL], w_coff[SL], a_soff[SL], w_soff[SL];
-#pragma unroll
-  for (int q = 0; q < SL; ++q) {
-    const int r = ld_row + q * (T / 2);
-    a_ok[q] = m0 + r < M && r < BM;
-    w_ok[q] = n0 + r < N;
-    const int a_row = min(r, M - 1 - m0), w_row = min(r, N - 1 - n0);
-    a_coff[q] = (uint32_t)a_row * (uint32_t)A.code_row;
-    w_coff[q] = (uint32_t)w_row * (uint32_t)W.code_row;
-    a_soff[q] = (uint32_t)a_row * (uint32_t)A.sc_row;
-    w_soff[q] = (uint32_t)w_row * (uint32_t)W.sc_row;
-  }
+  static_assert(SL == 1, "a thread's two slices are of one row of either tile");
+  // addresses: a uniform part (the tile, the step) and a 32-bit offset inside the tile.  Rows past the last re-read it: what
+  // they give is not stored.
+  const int a_row = min(ld_row, M - 1 - m0), w_row = min(ld_row, N - 1 - n0);
+  const uint32_t a_coff = (uint32_t)a_row * (uint32_t)A.code_row + ld_half * 16u;
+  const uint32_t w_coff = (uint32_t)w_row * (uint32_t)W.code_row + ld_half * 16u;
   const uint8_t* a_codes = A.codes + (int64_t)m0 * A.code_row;
   const uint8_t* w_codes = W.codes + (int64_t)n0 * W.code_row;
-  const uint8_t* a_scales = A.scales + (int64_t)m0 * A.sc_row;
-  const uint8_t* w_scales = W.scales + (int64_t)n0 * W.sc_row;
-  // Loads never leave the operand and never branch (a branch in the loop would split its schedule): a step
-  // past the last re-reads the last, the missing upper half of a last step of 32 k the lower one.  What such
-  // a slice holds does not matter: its scale is stored as zero.
-  const int ksteps = (K + kBK - 1) / kBK;
-  auto load_ops = [&](const uint8_t* codes, const uint32_t (&coff)[SL], int code_step, const uint8_t* scales,
-                      const uint32_t (&soff)[SL], int sc_step, int step, Slice (&r)[SL]) {
+  // of the two threads of a row the lower half's loads and stores the scale of A's, the other that of W's
+  const uint8_t* sc_row = ld_half ? W.scales + (int64_t)(n0 + w_row) * W.sc_row : A.scales + (int64_t)(m0 + a_row) * A.sc_row;
+  const int sc_step = ld_half ? W.sc_step : A.sc_step;
+  // Loads never leave the operand and never branch (a branch in the loop would split its schedule): a step past the last
+  // re-reads the last.  What it holds does not matter: its scales are stored as zero.  (K is a multiple of 64 here.)
+  const int ksteps = K / kBK;
+  auto load_codes = [&](const uint8_t* codes, uint32_t coff, int code_step, int step) {
     const int st = min(step, ksteps - 1);                             // uniform
-    const uint32_t half = st * kBK + ld_half * 32 < K ? ld_half : 0;
-    const uint8_t* c = codes + (int64_t)st * code_step;
-    const uint8_t* sc = scales + (int64_t)((st * kBK) >> g_shift) * sc_step;
-#pragma unroll
-    for (int q = 0; q < SL; ++q) {
-      r[q].codes = *reinterpret_cast<const uint4*>(c + (coff[q] + half * 16u));
-      r[q].sc = *reinterpret_cast<const uint16_t*>(sc + soff[q]);
-    }
+    return *reinterpret_cast<const uint4*>(codes + (int64_t)st * code_step + coff);
   };
-  auto load_a = [&](int step, Slice (&r)[SL]) { load_ops(a_codes, a_coff, A.code_step, a_scales, a_soff, A.sc_step, step, r); };
-  auto load_w = [&](int step, Slice (&r)[SL]) { load_ops(w_codes, w_coff, W.code_step, w_scales, w_soff, W.sc_step, step, r); };
+  auto load_a = [&](int step, uint4& r) { r = load_codes(a_codes, a_coff, A.code_step, step); };
+  auto load_w = [&](int step, uint4& r, uint32_t& sc) {
+    r = load_codes(w_codes, w_coff, W.code_step, step);
+    const int unit = (min(step, ksteps - 1) * kBK) >> g_shift;        // uniform
+    sc = *reinterpret_cast<const uint16_t*>(sc_row + (int64_t)unit * sc_step);
+  };
 
   // Placement of a row's 16-byte pieces: rotated by the row so that the 16 rows that share a 256-byte line
   // of banks in a fragment read use different banks.
@@ -121,21 +109,23 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
     const int f = FP4 ? (row >> 3) & 1 : (row >> 2) & 3;
     return row * RB + ((piece ^ f) << 4);
   };
-  // piece 0 of this thread's slice q; piece 1 is 16 bytes beside it, on the side the rotation says (stages and
+  // piece 0 of this thread's slice; piece 1 is 16 bytes beside it, on the side the rotation says (stages and
   // tiles start at multiples of 32 bytes: an exclusive or)
-  int st_off[SL];
-#pragma unroll
-  for (int q = 0; q < SL; ++q) st_off[q] = piece_at(ld_row + q * (T / 2), ld_half * NP);
-  auto put_scale = [&](int sc, const Slice& s, bool ok, int q) {
-    *reinterpret_cast<uint16_t*>(smem + sc + (ld_row + q * (T / 2)) * 2) = (uint16_t)(ok ? s.sc : 0u);
+  const int st_off = piece_at(ld_row, ld_half * NP);
+  // A row's scale has a word of its own in LDS and one thread that stores it, after the step's codes: stored as halves of a word, by
+  // both threads of the row, they were bank conflicts, 0.8 of the LDS cycles.  us, so -> now: INT4 g64 8192 x 12288 x 3072 423 -> 411,
+  // INT3 320 -> 307, 4608 x 3072 x 3072 (224 rows) 66.0 -> 66.3 and 49.9 -> 49.1; stored ahead of the codes INT4's 224-row tile 67.1.
+  const int sc_at = (ld_half ? W_SC : A_SC) + ld_row * 4;
+  auto put_scale = [&](int st, uint32_t sc, bool ok) {
+    *reinterpret_cast<uint32_t*>(smem + st + sc_at) = sc & (ok ? ~0u : 0u);
   };
   uint32_t wide = 0;
-  // 16-byte piece c of slice q: unpacked and stored
-  auto put_piece = [&](const Slice& s, int codes, int q, int c) {
-    const uint32_t d[4] = {s.codes.x, s.codes.y, s.codes.z, s.codes.w};
+  // 16-byte piece c of a slice: unpacked and stored
+  auto put_piece = [&](const uint4& s, int codes, int c) {
+    const uint32_t d[4] = {s.x, s.y, s.z, s.w};
     if constexpr (FP4) {
       if constexpr (WIDE == kWideCodes) wide |= wide_codes(d[0]) | wide_codes(d[1]) | wide_codes(d[2]) | wide_codes(d[3]);
-      *reinterpret_cast<uint4*>(smem + (codes + st_off[q])) =
+      *reinterpret_cast<uint4*>(smem + (codes + st_off)) =
           make_uint4(e2m1_nibbles(d[0]), e2m1_nibbles(d[1]), e2m1_nibbles(d[2]), e2m1_nibbles(d[3]));
     } else {
       uint32_t o[4];
@@ -145,7 +135,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
         o[2 * e] = e4m3_bytes(v & 0x0F0F0F0Fu, (v >> 3) & 0x01010101u);
         o[2 * e + 1] = e4m3_bytes((v >> 4) & 0x0F0F0F0Fu, (v >> 7) & 0x01010101u);
       }
-      *reinterpret_cast<uint4*>(smem + ((codes + st_off[q]) ^ (c << 4))) = make_uint4(o[0], o[1], o[2], o[3]);
+      *reinterpret_cast<uint4*>(smem + ((codes + st_off) ^ (c << 4))) = make_uint4(o[0], o[1], o[2], o[3]);
     }
   };
 
@@ -154,8 +144,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   const int frag_row = lane & 31, frag_half = lane >> 5;
   const int x_base = A_CODES + piece_at(wave_m * WTM + frag_row, frag_half * NP);
   const int w_base = W_CODES + piece_at(wave_n * WTN + frag_row, frag_half * NP);
-  const int xs_base = A_SC + (wave_m * WTM + frag_row) * 2;
-  const int ws_base = W_SC + (wave_n * WTN + frag_row) * 2;
+  const int xs_base = A_SC + (wave_m * WTM + frag_row) * 4;
+  const int ws_base = W_SC + (wave_n * WTN + frag_row) * 4;
 
   struct Frag {
     int4v v[NP];
@@ -168,7 +158,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
     return f;
   };
   auto read_scale = [&](int base, int stage, int tile) {
-    return (uint32_t)*reinterpret_cast<const uint16_t*>(smem + stage + base + tile * 64);
+    return *reinterpret_cast<const uint32_t*>(smem + stage + base + tile * 128);
   };
   auto operand = [&](const Frag& f) {
     if constexpr (FP4) return (int8v){f.v[0].x, f.v[0].y, f.v[0].z, f.v[0].w, 0, 0, 0, 0};
@@ -185,13 +175,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   // Slices on their way from memory: two steps' worth with 4-bit codes; with 8-bit codes, whose fragments take
   // twice the registers, one step's, reloaded as soon as it is unpacked.
   constexpr int RS = FP4 ? 2 : 1;
-  Slice raw_a[2][SL], raw_w[2][SL];                    // [1] is dead after the prologue for RS = 1
+  uint4 raw_a[2], raw_w[2];                            // [1] is dead after the prologue for RS = 1
+  uint32_t raw_sc[2];
 
   // ---- prologue: stages 0 and 1 <- steps 0 and 1, raw[0] <- step 2 (raw[1] <- step 3)
   load_a(0, raw_a[0]);
-  load_w(0, raw_w[0]);
+  load_w(0, raw_w[0], raw_sc[0]);
   load_a(1, raw_a[1]);
-  load_w(1, raw_w[1]);
+  load_w(1, raw_w[1], raw_sc[1]);
   float* const factors = reinterpret_cast<float*>(smem + SMEM_BYTES + (WIDE == kWideCodes ? T / 16 : 0));
   {
     Factors<BM, BN, T, true> f;
@@ -203,18 +194,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
     const int st = p * STAGE_BYTES;
     const bool k_ok = p * kBK < K;
 #pragma unroll
-    for (int q = 0; q < SL; ++q) {
-#pragma unroll
-      for (int c = 0; c < NP; ++c) {
-        put_piece(raw_a[p][q], st + A_CODES, q, c);
-        put_piece(raw_w[p][q], st + W_CODES, q, c);
-      }
-      put_scale(st + A_SC, raw_a[p][q], a_ok[q] && k_ok, q);
-      put_scale(st + W_SC, raw_w[p][q], w_ok[q] && k_ok, q);
+    for (int c = 0; c < NP; ++c) {
+      put_piece(raw_a[p], st + A_CODES, c);
+      put_piece(raw_w[p], st + W_CODES, c);
     }
+    put_scale(st, raw_sc[p], k_ok);
     if (p < RS) {
       load_a(p + 2, raw_a[p]);
-      load_w(p + 2, raw_w[p]);
+      load_w(p + 2, raw_w[p], raw_sc[p]);
     }
   }
   __syncthreads();
@@ -242,9 +229,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
     constexpr int TMW = decltype(TMc)::value;
     constexpr int X0 = decltype(X0c)::value;
     constexpr int NT = TMW * TN;                       // tiles of this wave
-    constexpr int NW = 2 * SL * NP;                    // pieces to unpack, all in the first half of the tiles
-    Slice(&ra)[SL] = raw_a[P % RS];
-    Slice(&rw)[SL] = raw_w[P % RS];
+    constexpr int NW = 2 * NP;                         // pieces to unpack, all in the first half of the tiles
+    uint4 &ra = raw_a[P % RS], &rw = raw_w[P % RS];
+    uint32_t& rsc = raw_sc[P % RS];
     const int st_next = stage_after(st_cur, 1), st_put = stage_after(st_cur, 2);
     const bool k_ok = (s + 2) * kBK < K;
 
@@ -275,16 +262,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
 #pragma unroll
       for (int u = 0; u < NW; ++u) {
         if (u * (NT / 2) / NW != t) continue;
-        const int q = (u / NP) % SL, c = u % NP;
-        if (u < SL * NP) {
-          put_piece(ra[q], st_put + A_CODES, q, c);
-          if (c == 0) put_scale(st_put + A_SC, ra[q], a_ok[q] && k_ok, q);
+        const int c = u % NP;
+        if (u < NP) {
+          put_piece(ra, st_put + A_CODES, c);
         } else {
-          put_piece(rw[q], st_put + W_CODES, q, c);
-          if (c == 0) put_scale(st_put + W_SC, rw[q], w_ok[q] && k_ok, q);
+          put_piece(rw, st_put + W_CODES, c);
         }
-        if (u == SL * NP - 1) load_a(s + 2 + RS, ra);
-        if (u == NW - 1) load_w(s + 2 + RS, rw);
+        if (u == NW - 1) put_scale(st_put, rsc, k_ok);
+        if (u == NP - 1) load_a(s + 2 + RS, ra);
+        if (u == NW - 1) load_w(s + 2 + RS, rw, rsc);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(p[r], sc[r], acc[i][j][r]);
@@ -336,7 +322,7 @@ static int launch_group(const OperandView& A, const OperandView& W, int M, int N
                         hipStream_t st) {
   constexpr int T = WGM * WGN * 64;
   constexpr int A_ROWS = (BM * 2 + T - 1) / T * (T / 2);
-  constexpr size_t stages = 4 * (size_t)(A_ROWS + BN) * ((FP4 ? 32 : 64) + 2);
+  constexpr size_t stages = 4 * (size_t)(A_ROWS + BN) * ((FP4 ? 32 : 64) + 4);
   constexpr size_t tile_bytes = OUT != kOutBf16 ? 0 : (size_t)BM * (BN * 2 + 16);
   constexpr size_t shmem = (stages > tile_bytes ? stages : tile_bytes) + (WIDE == kWideCodes ? WGM * WGN * 4 : 0) + kFactorBytes<BM, BN>;
   auto kern = qgemm_group_kernel<FP4, BM, BN, WGM, WGN, OUT, WIDE>;
