@@ -2,7 +2,8 @@
 // their arguments go from the interpreter's objects to the C entry points without ctypes.  A call of these launches one or two
 // kernels that may take 3 us, and the host has to keep up: issuing a launch takes 2.7 us by itself, a wrapper in Python, its
 // tensors' methods and ctypes took 2 more.  NVFP4 256 x 512 x 512, quantizer and product, one pair after another: 10.4 us before, 6.8
-// now, where the kernels alone take 6.5 (in a graph); INT4 g128 77 x 1000 x 1152 from the stored layout 13.9 -> 10.2.
+// then, where the kernels alone took 6.5 (in a graph, 5.5 now); INT4 g128 77 x 1000 x 1152 from the stored layout 13.9 -> 10.2 (7.6 with
+// one launch less).
 //
 // Marshalling only: pointers, sizes and strides of the tensors, the current stream, the result code.  pq.py holds the
 // declarations that users read, the exception type and the helpers that allocate (handed over by bind()).

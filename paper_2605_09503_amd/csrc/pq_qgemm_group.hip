@@ -112,9 +112,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_group_kernel(OperandView 
   // piece 0 of this thread's slice; piece 1 is 16 bytes beside it, on the side the rotation says (stages and
   // tiles start at multiples of 32 bytes: an exclusive or)
   const int st_off = piece_at(ld_row, ld_half * NP);
-  // A row's scale has a word of its own in LDS and one thread that stores it, after the step's codes: stored as halves of a word, by
-  // both threads of the row, they were bank conflicts, 0.8 of the LDS cycles.  us, so -> now: INT4 g64 8192 x 12288 x 3072 423 -> 411,
-  // INT3 320 -> 307, 4608 x 3072 x 3072 (224 rows) 66.0 -> 66.3 and 49.9 -> 49.1; stored ahead of the codes INT4's 224-row tile 67.1.
+  // A row's scale has a word of its own in LDS and one thread that loads and stores it, after the step's codes: a load, a store and
+  // their offsets less in every step than with both scales in both threads of a row, as halves of words.  us, so -> now: INT4 g64
+  // 8192 x 12288 x 3072 423 -> 411, INT3 320 -> 307, 4608 x 3072 x 3072 (224 rows) 66.0 -> 66.3 and 49.9 -> 49.1; stored ahead of the
+  // codes INT4's 224-row tile 67.1.  (Bank conflicts, 0.8 of the active LDS cycles, are as many as before.)
   const int sc_at = (ld_half ? W_SC : A_SC) + ld_row * 4;
   auto put_scale = [&](int st, uint32_t sc, bool ok) {
     *reinterpret_cast<uint32_t*>(smem + st + sc_at) = sc & (ok ? ~0u : 0u);
