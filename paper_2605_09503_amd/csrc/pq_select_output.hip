@@ -210,7 +210,7 @@ int launch_ref(const RowBatches& x, const void* w, int64_t M, int64_t N, int64_t
   auto kern = ref_gemm_kernel<TN>;
   if (int rc = allow_lds(reinterpret_cast<const void*>(kern), R::lds_bytes, raised, "hipFuncSetAttribute(ref_gemm_kernel)")) return rc;
   const int64_t tiles_m = (M + kRefRows - 1) / kRefRows, tiles_n = (N + R::cols - 1) / R::cols;
-  if (tiles_m * tiles_n > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
+  if (tiles_m * tiles_n > UINT32_MAX / 256) return fail(PQ_ERR_SHAPE, "too many output tiles");     // more threads than a grid holds
   hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), R::lds_bytes, st, x, (const uint16_t*)w, (int)M, (int)N,
                      (int)K, y, ldy, sq, add, (int)tiles_m, (int)tiles_n);
   return check_hip(hipGetLastError(), "ref_gemm_kernel");
