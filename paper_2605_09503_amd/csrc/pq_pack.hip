@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
         for (int64_t g = lane & 31; g < units; g += 32)
           mx = fmaxf(mx, as_f32(f32_to_bf16_rne(sc[row * units + g] * Q) << 16));
       mx = group_max<32>(mx);
-      // E = exponent(mx) - 10: the row maximum lands in [2^10, 2^11), so that the addend 24 * h
+      // E = exponent(mx) - 10: the row maximum lands in [2^10, 2^11), so that the addend 8 * h
       // of the unpack fma stays below the fp16 maximum; clamped so that 2^E and 2^-E are normal
       int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
       if (mx == 0.0f) e = 0;

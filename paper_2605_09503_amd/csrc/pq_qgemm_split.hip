@@ -20,7 +20,7 @@
 // runs nothing ahead.  Kernel alone, us: with 128 x 128 tiles -> split tiles -> the loop as it is and the factors in LDS
 //   NVFP4     256 x 512 x 512     9.4 ->  3.6 ->  2.9     512 x 3072 x 3072   30 -> 13.4 -> 11.4     500 x 1021 x 352  3.9 -> 3.35
 //   NVFP4     512 x 9216 x 3072    44 -> 32.3 -> 27.6     64 x 12288 x 3072   29 -> 10.2 ->  8.7     43 x 3659 x 10240  12.2 -> 11.2
-//   INT4 g128  77 x 1000 x 1152  15.3 ->  4.3 ->  3.9     INT4 g64   1024 x 3072 x 3072  33 -> 24.9 -> 21.5
+//   INT4 g128  77 x 1000 x 1152  15.3 ->  4.3 ->  3.9     INT4 g64   1024 x 3072 x 3072  33 -> 24.9 -> 21.2
 //   INT3 g64  512 x 3072 x 3072    31 -> 12.0 -> 10.2     INT3 g64   2048 x 3072 x 3072  49 -> 29.5 -> 28.7
 // INT4 in the 8-bit form of pq_qgemm_group.hip gained nothing here (15.5 -> 16.5, 46.9 -> 43.6 us): fp16 operands.  For the codes
 // of INT3 the next step's unpack between these blocks was 8 to 13 % slower (254 registers).
@@ -267,7 +267,7 @@ qgemm_split_kernel(
   // the order of a share's instructions: the next share's unpack between this one's matrix instructions
   auto interleave = [&]() {
     if constexpr (!CODES) {
-      constexpr int kUnpack = (TM + TN) * (FMT == kNvfp4 ? 8 : 12), N = TM * TN, EACH = (kUnpack + N - 1) / N;
+      constexpr int kUnpack = (TM + TN) * (FMT == kNvfp4 ? 8 : 11), N = TM * TN, EACH = (kUnpack + N - 1) / N;
 #pragma unroll
       for (int t = 0; t < N; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
