@@ -320,7 +320,7 @@ int pq_qgemm_check_int_scales(pq_format fmt, int group, const void* scales, int6
  * operands into the kernel's working form inside `workspace` (per-row power-of-two
  * normalisation; nothing to do for NVFP4); pq_qgemm_run then computes the product from codes
  * and that workspace.  pq_qgemm(...) == pq_qgemm_prep(...) followed by pq_qgemm_run(...) with
- * the same workspace.  Arguments as for pq_qgemm.
+ * the same workspace, which pq_qgemm too leaves ready for further calls of pq_qgemm_run.  Arguments as for pq_qgemm.
  */
 int pq_qgemm_prep(pq_format fmt, int group, const void* a_scales, const void* w_scales, int64_t M,
                   int64_t N, int64_t K, void* workspace, size_t workspace_bytes, void* stream);

@@ -501,8 +501,9 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
       W.scales = (const uint8_t*)w_scales;
       A.sc_row = W.sc_row = (K / group) * 4;
       A.sc_step = W.sc_step = 4;
-      A.raw_q = W.raw_q = (uint8_t)Q;
-      return launch_qgemm_views(fmt, group, A, W, M, N, K, Outputs{{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false}}, tile, st);
+      const Output out{out_f32 ? kOutF32 : kOutBf16, y, ldy, nullptr, false};
+      return launch_qgemm_split_raw(fmt, group, A, W, (int)M, (int)N, (int)K,
+                                    RawOutput{out, {Q, G.a_h, G.w_h, G.a_mul, G.w_mul}}, tile, st);
     }
     const bool mark = phases == 3 && fmt == PQ_FMT_INT3 && group != 32;
     if (phases & 1) {

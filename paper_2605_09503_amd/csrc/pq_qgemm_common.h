@@ -57,8 +57,6 @@ struct Slice {
 // mul: per-row epilogue factor (stride 1) or a single factor (stride 0).
 // panel: the panel layout.  marked: the sign of a row's factor says that the row holds INT3 codes beyond three bits
 // (always in the panel layout; set by the scale preparation of a row-major operand when it sees the codes)
-// raw_q: not 0 where `scales` are the INT quantizers' fp32 scales, of codes up to raw_q, which the split tiles prepare
-// themselves (RAW in pq_qgemm_split.hip); mul is null then
 // bias: bf16 value per row of this operand added to the product in the epilogue (used for the
 // weight operand, whose rows are the output columns), or null.
 struct OperandView {
@@ -71,7 +69,6 @@ struct OperandView {
   const float* mul;
   int mul_stride;
   bool panel = false, marked = false;
-  uint8_t raw_q = 0;
   const uint16_t* bias = nullptr;
 };
 
@@ -230,8 +227,18 @@ struct Outputs : Output {
   int64_t y_next = 0;
   unsigned problems = 1;
 };
-template <int OUT>
-using KernelOutput = std::conditional_t<OUT == kOutDiff, Outputs, Output>;
+// A product that prepares the scales of its row-major INT operands itself (RAW in pq_qgemm_split.hip): the scales are those of
+// codes up to q, and what a launch of the preparation would leave in the workspace goes there, for pq_qgemm_run.
+struct RawScales {
+  float q;
+  uint16_t *a_units, *w_units;
+  float *a_mul, *w_mul;
+};
+struct RawOutput : Output {
+  RawScales raw;
+};
+template <int OUT, bool RAW = false>
+using KernelOutput = std::conditional_t<RAW, RawOutput, std::conditional_t<OUT == kOutDiff, Outputs, Output>>;
 static_assert(sizeof(Output) == 40, "a larger argument has changed the registers of the 32 x 32 tiles");
 
 // the operands and the sums of this workgroup's problem (a factor of stride 0 is a tensor scale, the same for all)
@@ -336,7 +343,8 @@ __device__ __forceinline__ bool any_wide(uint32_t wide, int* flags) {
 // RAW: fp32 scales; the factors of the tile's rows and columns, and behind them 2^-E, are in LDS
 template <int BM, int BN, int WAVES, int KS, int OUT, bool RAW = false>
 __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const OperandView& W, int M, int N, int K,
-                                                int g_shift, int m0, int n0, const Output& out, const float* factors = nullptr) {
+                                                int g_shift, int m0, int n0, const KernelOutput<OUT, RAW>& out,
+                                                const float* factors = nullptr) {
   static_assert(OUT != kOutDiff, "the selection quantizes its operands itself");
   const int lane = threadIdx.x & 63;
   const int row = lane & 31, half = lane >> 5;
@@ -350,7 +358,7 @@ __device__ __forceinline__ void wide_codes_tile(const OperandView& A, const Oper
     const uint8_t *as = A.scales + ar * A.sc_row, *ws = W.scales + wr * W.sc_row;
     const float* const downs = factors + kFactorBytes<BM, BN> / 4;
     auto unit_at = [&](const uint8_t* at, int local) -> uint32_t {
-      if constexpr (RAW) return int_scale_unit(*reinterpret_cast<const float*>(at), (float)A.raw_q, downs[local]);
+      if constexpr (RAW) return int_scale_unit(*reinterpret_cast<const float*>(at), out.raw.q, downs[local]);
       else return *reinterpret_cast<const uint16_t*>(at);
     };
     float16_t sum = zero;
@@ -556,8 +564,10 @@ enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kT
 // small outputs (pq_qgemm_split.hip)
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Outputs& out, int tile, hipStream_t st);
-// whether a product of row-major INT operands prepares their scales in the product kernel
+// whether a product of row-major INT operands prepares their scales in the product kernel, and that product
 bool split_takes_raw_scales(int tile, int group, int64_t M, int64_t N, int64_t K);
+int launch_qgemm_split_raw(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
+                           const RawOutput& out, int tile, hipStream_t st);
 // the integer formats' large outputs with groups of 64 and more (pq_qgemm_group.hip)
 int launch_qgemm_group(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Outputs& out, int tile, hipStream_t st);

@@ -59,6 +59,29 @@ constexpr size_t split_lds() {
 
 typedef uint32_t uint32_any __attribute__((aligned(2)));              // two scale units, at any unit
 
+// What int_scale_prep_kernel leaves in the workspace, for pq_qgemm_run: units and factors of block's T / 16 rows, A's and then
+// W's, 16 lanes a row.  A product that prepares its scales itself has a workgroup for each block beside those of its tiles (75
+// shapes 1.003 of the time without; in the first tiles' own workgroups 1.13, up to 1.28).
+template <int T>
+__host__ __device__ constexpr int scale_blocks(int rows) { return (rows + T / 16 - 1) / (T / 16); }
+template <int T>
+__device__ __forceinline__ void leave_scales(const OperandView& A, const OperandView& W, int M, int N, int groups,
+                                             const RawScales& raw, int block) {
+  const bool is_w = block >= scale_blocks<T>(M);
+  const int row = (is_w ? block - scale_blocks<T>(M) : block) * (T / 16) + (int)threadIdx.x / 16, g0 = threadIdx.x & 15;
+  if (row >= (is_w ? N : M)) return;                   // all lanes of a row; blocks past the last
+  const uint8_t* scales = is_w ? W.scales + (int64_t)row * W.sc_row : A.scales + (int64_t)row * A.sc_row;
+  const float* s = reinterpret_cast<const float*>(scales);
+  uint16_t* units = (is_w ? raw.w_units : raw.a_units) + (int64_t)row * groups;
+  float mx = 0.0f;
+#pragma unroll 4
+  for (int g = g0; g < groups; g += 16) mx = fmaxf(mx, int_group_max(s[g], raw.q));
+  const RowScale scale = int_row_scale(group_max<16>(mx));
+#pragma unroll 1
+  for (int g = g0; g < groups; g += 16) units[g] = int_scale_unit(s[g], raw.q, scale.down);
+  if (g0 == 0) (is_w ? raw.w_mul : raw.a_mul)[row] = scale.up / raw.q;
+}
+
 // ROWS (row-major operands only): a fragment read straight from a row-major operand touches a line for each of its 32
 // rows and takes a quarter of it.  Here the workgroup loads the codes and scale units of its next KS steps together,
 // whole runs of 32 KS bytes of every row, and the waves pick their step out of LDS (two sets of steps, a barrier for
@@ -69,11 +92,12 @@ constexpr int kSplitWaves = (ROWS || WIDE == kWideMarks) && TM * TN == 4 && WIDE
 // FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 82 instead
 // of 56, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
 // RAW (row-major INT operands): the scales are the quantizers' fp32 ones.  The workgroup finds its rows' largest and a lane
-// turns each scale that it loads into the operand's unit.  See split_takes_raw_scales.
+// turns each scale that it loads into the operand's unit.  Workgroups beside those of the tiles leave units and factors in the
+// workspace.  See split_takes_raw_scales.
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW, bool RAW>
 __global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitWaves<TM, TN, WIDE, ROWS>, FEW ? 4 : 8))) void
 qgemm_split_kernel(
-    OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT> out, int tiles_m, int tiles_n) {
+    OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT, RAW> out, int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
   constexpr int T = KS * 64;
   constexpr int BM = TM * 32, BN = TN * 32;
@@ -82,6 +106,12 @@ qgemm_split_kernel(
   constexpr int ROW = 32 + 4;                          // floats of a partial sum's row in LDS
   extern __shared__ __attribute__((aligned(16))) float part[];        // [KS][BM][ROW]: one 32-column strip; then [KS] flags
 
+  if constexpr (RAW) {                                 // told by a register: the tiles' workgroups wait for no argument here
+    if (blockIdx.y) {
+      leave_scales<T>(A, W, M, N, K >> g_shift, out.raw, (int)(blockIdx.y - 1) * (tiles_m * tiles_n) + (int)blockIdx.x);
+      return;
+    }
+  }
   int tile_m, tile_n;
   assign_tile(tiles_m, tiles_n, tile_m, tile_n);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -160,7 +190,8 @@ qgemm_split_kernel(
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
   float a_down[RAW ? TM : 1], w_down[RAW ? TN : 1];    // of this lane's rows
-  const float Q = (float)A.raw_q;
+  float Q = 0.0f;
+  if constexpr (RAW) Q = out.raw.q;
   auto unit_of = [&](uint32_t sc, float down) -> uint32_t {
     if constexpr (RAW) return int_scale_unit(as_f32(sc), Q, down);
     else return sc;
@@ -579,8 +610,8 @@ bool split_takes_raw_scales(int tile, int group, int64_t M, int64_t N, int64_t K
 }
 
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW = false, bool RAW = false>
-static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
-                        hipStream_t st) {
+static int launch_split(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift,
+                        const std::conditional_t<RAW, RawOutput, Outputs>& out, hipStream_t st) {
   constexpr int BM = TM * 32, BN = TN * 32;
   constexpr size_t shmem = split_lds<TM, TN, KS, WIDE, ROWS>() + kFactorBytes<BM, BN> + (RAW ? (BM + BN) * 4 : 0);
   static_assert(shmem <= 160 * 1024, "the partial sums fit in LDS");
@@ -590,8 +621,10 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t n_tiles = (int64_t)tiles_m * tiles_n;
   if (n_tiles > 0x7FFFFFFF) return fail(PQ_ERR_SHAPE, "too many output tiles");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles, out.problems), dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, out, tiles_m,
-                     tiles_n);
+  dim3 grid((unsigned)n_tiles);
+  if constexpr (RAW) grid.y = (unsigned)(1 + (scale_blocks<KS * 64>(M) + scale_blocks<KS * 64>(N) + n_tiles - 1) / n_tiles);
+  else grid.y = out.problems;
+  hipLaunchKernelGGL(kern, grid, dim3(KS * 64), shmem, st, A, W, M, N, K, g_shift, out, tiles_m, tiles_n);
   return check_hip(hipGetLastError(), "qgemm_split_kernel");
 }
 
@@ -607,9 +640,6 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
   }
   constexpr bool kMayBeFew = TN == 1 && MODE != kSplitE2m1, kFew = kMayBeFew && TM == 2;
-  if constexpr (TN == 1 && OUT != kOutDiff && (MODE == kSplitInt || (MODE == kSplitE2m1 && WIDE == kWideCodes))) {
-    if (A.raw_q) return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, kMayBeFew, true>(A, W, M, N, K, g_shift, out, st);
-  }
   if constexpr (kMayBeFew && TM == 1) {
     if (n_tiles * out.problems <= 512)
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, true>(A, W, M, N, K, g_shift, out, st);
@@ -641,9 +671,13 @@ static int split_tile(const OperandView& A, const OperandView& W, int M, int N, 
   }
 }
 
+static int group_shift(pq_format fmt, int group) {
+  return fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
+}
+
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Outputs& out, int tile, hipStream_t st) {
-  const int g_shift = fmt == PQ_FMT_NVFP4 || group == 32 ? 5 : group == 64 ? 6 : group == 128 ? 7 : 8;
+  const int g_shift = group_shift(fmt, group);
 #define PQ_SPLIT(MODE, WIDE)                                                                                 \
   return out.kind == kOutF32    ? split_tile<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st)      \
          : out.kind == kOutDiff ? split_tile<MODE, kOutDiff, kWideNone>(A, W, M, N, K, g_shift, out, tile, st) \
@@ -655,6 +689,29 @@ int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const Ope
   }
   PQ_SPLIT(kSplitInt, kWideNone);
 #undef PQ_SPLIT
+}
+
+// Views with fp32 scales come here and nowhere else: the other kernels would read them as units, and factors where there are
+// none.
+template <int MODE, int OUT, int WIDE>
+static int split_raw(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const RawOutput& out, int tile,
+                     hipStream_t st) {
+  constexpr bool kFew = MODE != kSplitE2m1;
+  if (tile == kTileSplit32) return launch_split<MODE, 1, 1, 8, OUT, WIDE, false, kFew, true>(A, W, M, N, K, g_shift, out, st);
+  return launch_split<MODE, 2, 1, 8, OUT, WIDE, false, kFew, true>(A, W, M, N, K, g_shift, out, st);
+}
+
+int launch_qgemm_split_raw(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
+                           const RawOutput& out, int tile, hipStream_t st) {
+  if (fmt == PQ_FMT_NVFP4 || out.kind == kOutDiff || !split_takes_raw_scales(tile, group, M, N, K))
+    return fail(PQ_ERR_FORMAT, "no product with fp32 group scales of this shape");
+  const int g_shift = group_shift(fmt, group);
+#define PQ_RAW(MODE, WIDE)                                                                            \
+  return out.kind == kOutF32 ? split_raw<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st) \
+                             : split_raw<MODE, kOutBf16, WIDE>(A, W, M, N, K, g_shift, out, tile, st)
+  if (fmt == PQ_FMT_INT3 && group != 32) PQ_RAW(kSplitE2m1, kWideCodes);
+  PQ_RAW(kSplitInt, kWideNone);
+#undef PQ_RAW
 }
 
 }  // namespace pq

@@ -398,7 +398,7 @@ def pq_qgemm_prep(fmt: int, group: int, a_scales, w_scales, M: int, N: int, K: i
 def pq_qgemm_run(fmt: int, group: int, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
                  w_tensor_scale, y: torch.Tensor, workspace: Optional[torch.Tensor] = None,
                  M=None, N=None, K=None, ldy=None) -> None:
-    """Product half of pq_qgemm: the workspace must have been filled by pq_qgemm_prep."""
+    """Product half of pq_qgemm: the workspace must have been filled by pq_qgemm_prep or left by pq_qgemm."""
     _gemm(load().pq_qgemm_run, fmt, group, a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
           w_tensor_scale, y, workspace, M, N, K, ldy)
 

@@ -449,6 +449,30 @@ def test_scales_prepared_in_the_product_kernel(fmt, g, M, N, K, odd_codes):
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K", [
+    (pq.FMT_INT4, 32, 1, 128, 32), (pq.FMT_INT4, 32, 33, 257, 4096), (pq.FMT_INT4, 64, 500, 1021, 1088), (pq.FMT_INT3, 32, 61, 1001, 544),
+    (pq.FMT_INT3, 64, 61, 1001, 8192), (pq.FMT_INT3, 64, 500, 1021, 4096), (pq.FMT_INT4, 64, 61, 1001, 8256), (pq.FMT_INT3, 64, 512, 3072, 3136)])
+def test_a_product_leaves_the_workspace_ready_for_the_run(fmt, g, M, N, K):
+    """pq_qgemm == pq_qgemm_prep + pq_qgemm_run with the same workspace: after pq_qgemm, wherever it prepared the scales,
+    pq_qgemm_run multiplies with what it left, also other codes of the same scales.  The workspace starts as NaNs."""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K + g)
+    ac, as_ = _int_operand(fmt, g, M, K, gen, False)
+    wc, ws = _int_operand(fmt, g, N, K, gen, False)
+    ldy = (N + 7) // 8 * 8
+    work = torch.full((pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K),), 0xFF, dtype=torch.uint8, device=DEV)
+    prepared = work.clone()
+    y, again, want = (torch.full((M, ldy), 3.0, dtype=torch.bfloat16, device=DEV) for _ in range(3))
+    pq.pq_qgemm(fmt, g, ac, as_, None, wc, ws, None, y, workspace=work, N=N, ldy=ldy)
+    pq.pq_qgemm_prep(fmt, g, as_, ws, M, N, K, prepared)
+    for codes in (ac, ac.flip(0).contiguous()):
+        pq.pq_qgemm_run(fmt, g, codes, as_, None, wc, ws, None, again, work, N=N, ldy=ldy)
+        pq.pq_qgemm_run(fmt, g, codes, as_, None, wc, ws, None, want, prepared, N=N, ldy=ldy)
+        assert torch.equal(again.view(torch.int16), want.view(torch.int16))
+        if codes is ac:
+            assert torch.equal(again.view(torch.int16), y.view(torch.int16))
+    assert torch.equal(work, prepared)
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K", [
     (pq.FMT_NVFP4, 16, 1000, 3001, 96), (pq.FMT_NVFP4, 16, 1000, 3001, 32), (pq.FMT_INT4, 64, 1000, 3001, 192),     # 128 x 192 tiles
     (pq.FMT_NVFP4, 16, 65, 131, 32), (pq.FMT_INT4, 64, 65, 131, 64), (pq.FMT_NVFP4, 16, 129, 257, 160), (pq.FMT_INT3, 64, 130, 390, 448)])
 def test_output_error_against_the_unquantized_product(fmt, g, M, N, K):
