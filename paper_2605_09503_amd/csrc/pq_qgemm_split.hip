@@ -481,7 +481,7 @@ qgemm_split_kernel(
   if constexpr (!RAW) own_factors.put(factors);
 
   // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
-  const bool bias = W.bias != nullptr;
+  const bool bias = !RAW && W.bias != nullptr;         // RAW: refused at the launch, nothing puts it into LDS
   void* __restrict__ y = out.y;
   const int64_t ldy = out.ldy;
   double d2 = 0.0;
@@ -703,8 +703,8 @@ static int split_raw(const OperandView& A, const OperandView& W, int M, int N, i
 
 int launch_qgemm_split_raw(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                            const RawOutput& out, int tile, hipStream_t st) {
-  if (fmt == PQ_FMT_NVFP4 || out.kind == kOutDiff || !split_takes_raw_scales(tile, group, M, N, K))
-    return fail(PQ_ERR_FORMAT, "no product with fp32 group scales of this shape");
+  if (fmt == PQ_FMT_NVFP4 || out.kind == kOutDiff || W.bias || !split_takes_raw_scales(tile, group, M, N, K))
+    return fail(PQ_ERR_FORMAT, "no product with fp32 group scales of this kind");
   const int g_shift = group_shift(fmt, group);
 #define PQ_RAW(MODE, WIDE)                                                                            \
   return out.kind == kOutF32 ? split_raw<MODE, kOutF32, WIDE>(A, W, M, N, K, g_shift, out, tile, st) \
