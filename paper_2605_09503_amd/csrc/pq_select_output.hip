@@ -36,12 +36,12 @@ struct RefTile {
 };
 
 // 16 bytes a lane from memory into LDS, 1 KB a wave from byte `to` on, without a register in between: by a 64-bit address, or
-// by a uniform base and an offset.  The wait for them is ref_wait's; nothing else in the kernel uses m0.
+// by a uniform base and an offset.  The wait for them is ref_wait's.
 __device__ __forceinline__ void load_to_lds(uint32_t to, const uint8_t* from) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory", "m0");
 }
 __device__ __forceinline__ void load_to_lds(uint32_t to, const uint8_t* base, uint32_t offset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(offset), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(offset), "s"(base) : "memory", "m0");
 }
 // all but the last N loads of this wave have arrived and its LDS reads are done; then the workgroup meets
 template <int N>
