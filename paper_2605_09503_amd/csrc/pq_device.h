@@ -334,6 +334,23 @@ __device__ __forceinline__ uint32_t nv4_code_pair(float x0, float x1, float inv)
   return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x0 * inv, x1 * inv, 1.0f, 0) & 0xFFu;
 }
 
+// ---------------------------------------------------------------- INT scales in the product's operands
+// The group maximum h = bf16_rne(s Q) goes into the operands as fp16 h 2^-E, E(row) such that the row's largest lands in
+// [2^10, 2^11): the addend 8 h of the unpack fma and u h stay below the fp16 maximum.  2^E / Q goes to the epilogue.
+struct RowScale {
+  float down, up;                                      // 2^-E, 2^E
+};
+__device__ __forceinline__ float int_group_max(float s, float Q) { return as_f32(f32_to_bf16_rne(s * Q) << 16); }
+__device__ __forceinline__ RowScale int_row_scale(float largest) {
+  int e = (int)((as_u32(largest) >> 23) & 0xFF) - 127;
+  if (largest == 0.0f) e = 0;
+  const int E = max(-120, min(120, e - 10));           // both 2^-E and 2^E are normal fp32 numbers
+  return RowScale{as_f32((uint32_t)(127 - E) << 23), as_f32((uint32_t)(127 + E) << 23)};
+}
+// the unit of a group with maximum h, or with scale s; exact unless far below the row's largest
+__device__ __forceinline__ uint16_t int_unit(float h, float down) { return __builtin_bit_cast(uint16_t, (_Float16)(h * down)); }
+__device__ __forceinline__ uint16_t int_scale_unit(float s, float Q, float down) { return int_unit(int_group_max(s, Q), down); }
+
 // Workgroups go round the eight chiplets in turn: the row block that gives each chiplet a contiguous run of them, so that
 // the lines that neighbouring rows share (32 bytes of codes and 2 of a scale unit a row) meet in one L2.  us, before and
 // after: RMSNorm + NVFP4 2048 x 6144 14.6, 10.7, 4608 x 3072 15.7, 13.4; the quantizer with eight rows a workgroup, INT4

@@ -208,20 +208,14 @@ __device__ __forceinline__ void emit_row(const void* slab, const int32_t* __rest
   }
 
   if constexpr (IS_INT) {
-    // the per-row power of two of the operand layout: E = exponent(row maximum) - 10 puts the
-    // largest group maximum in [2^10, 2^11) (see pack_operand_kernel); scale units are the fp16
-    // group maxima times 2^-E, the row factor 2^E / Q
+    // the per-row power of two of the operand layout (see int_row_scale): scale units are the fp16 group maxima times 2^-E,
+    // the row factor 2^E / Q
     constexpr float Q = qmax_of(FMT);
     team_maxima<TEAM>(row_max, em.red, em.wave, em.lane);      // (with TEAM > 1 also the barrier after the h_lds writes)
-    int e = (int)((as_u32(row_max[0]) >> 23) & 0xFF) - 127;
-    if (row_max[0] == 0.0f) e = 0;
-    const int E = max(-120, min(120, e - 10));
-    const float down = as_f32((uint32_t)(127 - E) << 23);
-    if (em.tl == 0) em.mul[em.row] = as_f32((uint32_t)(127 + E) << 23) / Q;
-    for (int u = em.tl; u < em.n_units; u += TL) {             // the team's own LDS writes, ordered above
-      const _Float16 hn = (_Float16)(em.h_lds[u] * down);
-      em.scales[(int64_t)u * em.rows + em.row] = __builtin_bit_cast(uint16_t, hn);
-    }
+    const RowScale scale = int_row_scale(row_max[0]);
+    if (em.tl == 0) em.mul[em.row] = scale.up / Q;
+    for (int u = em.tl; u < em.n_units; u += TL)               // the team's own LDS writes, ordered above
+      em.scales[(int64_t)u * em.rows + em.row] = int_unit(em.h_lds[u], scale.down);
   }
 }
 

@@ -102,16 +102,11 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
       float mx = 0.0f;
       if (row < rows)
         for (int64_t g = lane & 31; g < units; g += 32)
-          mx = fmaxf(mx, as_f32(f32_to_bf16_rne(sc[row * units + g] * Q) << 16));
-      mx = group_max<32>(mx);
-      // E = exponent(mx) - 10: the row maximum lands in [2^10, 2^11), so that the addend 8 * h
-      // of the unpack fma stays below the fp16 maximum; clamped so that 2^E and 2^-E are normal
-      int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
-      if (mx == 0.0f) e = 0;
-      const int E = max(-120, min(120, e - 10));
+          mx = fmaxf(mx, int_group_max(sc[row * units + g], Q));
+      const RowScale scale = int_row_scale(group_max<32>(mx));
       if ((lane & 31) == 0) {
-        row_down[rr] = as_f32((uint32_t)(127 - E) << 23);                            // 2^-E
-        const float up = as_f32((uint32_t)(127 + E) << 23) / Q;                      // 2^E / Q
+        row_down[rr] = scale.down;
+        const float up = scale.up / Q;
         if (row < rows) p_mul[row] = MARK && row_wide[rr] ? -up : up;
       }
     }
@@ -119,11 +114,7 @@ __global__ __launch_bounds__(256) void pack_operand_kernel(const uint8_t* __rest
     const float down = row_down[r_local];
     for (int64_t u0 = 0; u0 < units; u0 += 32) {
       const int64_t u = u0 + wave * 8 + u_local;
-      if (r < rows && u < units) {
-        const float h = as_f32(f32_to_bf16_rne(sc[r * units + u] * Q) << 16);
-        const _Float16 hn = (_Float16)(h * down);           // exact unless far below the row maximum
-        p_scales[u * rows + r] = __builtin_bit_cast(uint16_t, hn);
-      }
+      if (r < rows && u < units) p_scales[u * rows + r] = int_scale_unit(sc[r * units + u], Q, down);
     }
   }
 }

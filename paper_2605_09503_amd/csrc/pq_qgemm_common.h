@@ -20,24 +20,6 @@ constexpr int kRowBytes = kBK * 2 + 16; // fp16 row in LDS, padded by one 16-byt
 __device__ __forceinline__ half2_t as_h2(uint32_t u) { return __builtin_bit_cast(half2_t, u); }
 __device__ __forceinline__ uint32_t h2_bits(half2_t h) { return __builtin_bit_cast(uint32_t, h); }
 
-// ------------------------------------------------------------------------ INT scales
-// The group maximum h = bf16_rne(s Q) goes into the operands as fp16 h 2^-E, E(row) such that the row's largest lands in
-// [2^10, 2^11): the addend 8 h of the unpack fma and u h stay below the fp16 maximum.  2^E / Q goes to the epilogue.
-struct RowScale {
-  float down, up;                                      // 2^-E, 2^E
-};
-__device__ __forceinline__ float int_group_max(float s, float Q) { return as_f32(f32_to_bf16_rne(s * Q) << 16); }
-__device__ __forceinline__ RowScale int_row_scale(float largest) {
-  int e = (int)((as_u32(largest) >> 23) & 0xFF) - 127;
-  if (largest == 0.0f) e = 0;
-  const int E = max(-120, min(120, e - 10));           // both 2^-E and 2^E are normal fp32 numbers
-  return RowScale{as_f32((uint32_t)(127 - E) << 23), as_f32((uint32_t)(127 + E) << 23)};
-}
-// exact unless far below the row's largest
-__device__ __forceinline__ uint16_t int_scale_unit(float s, float Q, float down) {
-  return __builtin_bit_cast(uint16_t, (_Float16)(int_group_max(s, Q) * down));
-}
-
 // ------------------------------------------------------------------------ operand unpack
 // Per-thread slice of a tile row: 32 consecutive k (16 bytes of codes) plus its scales.
 struct Slice {

@@ -255,19 +255,15 @@ __global__ __launch_bounds__(256) void quantize_rows_panel_kernel(PanelJob a_job
         *reinterpret_cast<uint32_t*>(p_codes + ((int64_t)(c >> 3) * rows + row) * 32 + (c & 7) * 4) = o.codes;
     }
     if constexpr (FMT != kNvfp4) {
-      // units h * 2^-E with E = exponent(row maximum) - 10, row factor 2^E / Q (see pack_operand_kernel)
+      // units h * 2^-E, row factor 2^E / Q (see int_row_scale)
       constexpr float Q = qmax_of(FMT);
       row_max = wave_max(row_max);
       if ((threadIdx.x & 63) == 0) wave_mx[threadIdx.x >> 6] = row_max;
       __syncthreads();
       const float mx = fmaxf(fmaxf(wave_mx[0], wave_mx[1]), fmaxf(wave_mx[2], wave_mx[3]));
-      int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
-      if (mx == 0.0f) e = 0;
-      const int E = max(-120, min(120, e - 10));
-      const float down = as_f32((uint32_t)(127 - E) << 23);
-      if (threadIdx.x == 0) *(reinterpret_cast<float*>(operand + lay.mul) + row) = as_f32((uint32_t)(127 + E) << 23) / Q;
-      for (int u = threadIdx.x; u < units; u += 256)
-        p_scales[(int64_t)u * rows + row] = __builtin_bit_cast(uint16_t, (_Float16)(h_lds[u] * down));
+      const RowScale scale = int_row_scale(mx);
+      if (threadIdx.x == 0) *(reinterpret_cast<float*>(operand + lay.mul) + row) = scale.up / Q;
+      for (int u = threadIdx.x; u < units; u += 256) p_scales[(int64_t)u * rows + row] = int_unit(h_lds[u], scale.down);
       if (q + 1 < q1) __syncthreads();                 // the maxima have been read
     }
   }

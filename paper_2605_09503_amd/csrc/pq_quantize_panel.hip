@@ -179,19 +179,12 @@ __global__ __launch_bounds__(64 * kQuantPanelMaxWaves) void quantize_panel_kerne
     const int wr = lane % RPW;                       // row of the write mapping
     float mx = 0.0f;
     for (int w = 0; w < n_waves; ++w) mx = fmaxf(mx, wave_rowmax[w][wr]);
-    // E = exponent(mx) - 10: the row maximum lands in [2^10, 2^11) (see pack_operand_kernel)
-    int e = (int)((as_u32(mx) >> 23) & 0xFF) - 127;
-    if (mx == 0.0f) e = 0;
-    const int E = max(-120, min(120, e - 10));
-    const float down = as_f32((uint32_t)(127 - E) << 23);
+    const RowScale scale = int_row_scale(mx);
     const int64_t row = r0 + wr;
-    if (wave == 0 && lane < RPW && row < rows) p_mul[row] = as_f32((uint32_t)(127 + E) << 23) / Q;
+    if (wave == 0 && lane < RPW && row < rows) p_mul[row] = scale.up / Q;
     for (int u0 = 0; u0 < n_units; u0 += LPR * n_waves) {
       const int u = u0 + wave * LPR + lane / RPW;
-      if (row < rows && u < n_units) {
-        const _Float16 hn = (_Float16)(h_lds[wr * n_units + u] * down);
-        p_scales[(int64_t)u * rows + row] = __builtin_bit_cast(uint16_t, hn);
-      }
+      if (row < rows && u < n_units) p_scales[(int64_t)u * rows + row] = int_unit(h_lds[wr * n_units + u], scale.down);
     }
   }
 }
