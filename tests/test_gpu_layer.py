@@ -6,6 +6,7 @@ outputs of the normalisation / rotation (see test_gpu_norm.py), so the products 
 the tolerance of the product kernel plus the effect of those steps; the Hadamard case also checks the
 qualitative claim that rotation plus reorder lowers the layer's output error on outlier-heavy
 activations."""
+import ctypes
 import sys
 
 import numpy as np
@@ -470,6 +471,40 @@ def test_a_product_leaves_the_workspace_ready_for_the_run(fmt, g, M, N, K):
         if codes is ac:
             assert torch.equal(again.view(torch.int16), y.view(torch.int16))
     assert torch.equal(work, prepared)
+
+
+def _launches(call):
+    """Kernel launches of a call: nodes of the graph it is captured into."""
+    call()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t()
+    count = pq.load().hipGraphGetNodes
+    count.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert count(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("fmt,g,M,N,K,tile,launches", [
+    (pq.FMT_INT4, 32, 77, 1000, 5120, (32, 32), 1), (pq.FMT_INT4, 32, 77, 1000, 5152, (32, 32), 2),
+    (pq.FMT_INT3, 64, 61, 1001, 5120, (32, 32), 1), (pq.FMT_INT3, 64, 61, 1001, 5184, (32, 32), 2),
+    (pq.FMT_INT4, 64, 500, 1021, 1536, (64, 32), 1), (pq.FMT_INT4, 64, 500, 1021, 1600, (64, 32), 2),
+    (pq.FMT_INT3, 64, 500, 1021, 1536, (64, 32), 1), (pq.FMT_INT3, 64, 500, 1021, 1600, (64, 32), 2),
+    (pq.FMT_INT4, 64, 32, 8192, 256, (32, 32), 1), (pq.FMT_INT4, 64, 32, 8193, 256, (32, 32), 2),
+    (pq.FMT_INT4, 64, 400, 1600, 256, (64, 64), 2), (pq.FMT_NVFP4, 16, 77, 1000, 1152, (32, 32), 1)])
+def test_which_products_prepare_their_scales(fmt, g, M, N, K, tile, launches):
+    """Either side of the lines in K, in tiles and in their size beyond which a launch prepares the scales."""
+    assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K + g)
+    x, w = (torch.randn((n, K), generator=gen, device=DEV).to(torch.bfloat16) for n in (M, N))
+    T = torch.full((1,), 2.0 ** -9, device=DEV)
+    (ac, as_), (wc, ws) = (pq.alloc_quantized(fmt, g, n, K, DEV) for n in (M, N))
+    pq.pq_quantize_act(fmt, g, x, None, T, ac, as_)
+    pq.pq_quantize_act(fmt, g, w, None, T, wc, ws)
+    y = torch.empty((M, (N + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)
+    work = torch.empty(max(16, pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K)), dtype=torch.uint8, device=DEV)
+    assert _launches(lambda: pq.pq_qgemm(fmt, g, ac, as_, T, wc, ws, T, y, workspace=work, N=N, ldy=y.shape[1])) == launches
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K", [
