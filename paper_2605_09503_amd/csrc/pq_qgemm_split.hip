@@ -89,13 +89,18 @@ __device__ __forceinline__ void leave_scales(const OperandView& A, const Operand
 // WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
 template <int TM, int TN, int WIDE, bool ROWS>
 constexpr int kSplitWaves = (ROWS || WIDE == kWideMarks) && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
-// FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 82 instead
-// of 56, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
+// FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 84 instead
+// of 58, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
+// kSplitFull: without FEW the four workgroups a unit of the 32 x 32 tiles have to be demanded (eight waves a SIMD, 64 registers; the
+// compiler's own choice is 74 to 84): 72 NVFP4 shapes of more than 512 tiles and K up to 512 0.92 of the time without, 417 integer
+// ones 0.99, row-major the same.
+template <int MODE, int TM, int TN, int OUT, bool FEW>
+constexpr bool kSplitFull = MODE != kSplitE2m1 && TM * TN == 1 && OUT != kOutDiff && !FEW;
 // RAW (row-major INT operands): the scales are the quantizers' fp32 ones.  The workgroup finds its rows' largest and a lane
 // turns each scale that it loads into the operand's unit.  Workgroups beside those of the tiles leave units and factors in the
 // workspace.  See split_takes_raw_scales.
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW, bool RAW>
-__global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitWaves<TM, TN, WIDE, ROWS>, FEW ? 4 : 8))) void
+__global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitFull<MODE, TM, TN, OUT, FEW> ? 8 : kSplitWaves<TM, TN, WIDE, ROWS>, FEW ? 4 : 8))) void
 qgemm_split_kernel(
     OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT, RAW> out, int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
@@ -470,6 +475,7 @@ qgemm_split_kernel(
     };
     fetch(0);
     put(lds);
+    own_factors.put(factors);                            // here, where the loads are waited for anyway
     fetch(1);
     __syncthreads();
     for (int o = 0; o < n_sets; o += 2) {
@@ -478,7 +484,7 @@ qgemm_split_kernel(
     }
   }
 
-  if constexpr (!RAW) own_factors.put(factors);
+  if constexpr (!RAW && !ROWS) own_factors.put(factors);
 
   // ---- the partial sums meet in LDS, one 32-column strip at a time, and are added in a fixed order
   const bool bias = !RAW && W.bias != nullptr;         // RAW: refused at the launch, nothing puts it into LDS
