@@ -607,11 +607,11 @@ static bool rows_through_lds(int64_t n_tiles, int ks, int K) {
 // Whether a product of row-major INT operands prepares their scales itself (RAW) instead of in a launch before it, which
 // takes 1.3 to 2.5 us of the device and 2.7 of the host.  Every workgroup then reads all scales of its rows ahead of its first
 // step and loads two bytes more a unit, which a long K or many rows a workgroup make longer than the launch.  Of 5400 random
-// shapes of at most 256 tiles (1 to 2048 rows, 64 to 8192 columns, K 96 to 12288, all groups) the 4361 that these lines take need
-// 0.77 of the device's time, none more than 1.004; the others 0.94, up to 1.20 (INT3 g64 1009 x 502 x 3584 15.5 -> 18.5 us, g128 15 x 154 x 11264
+// shapes of at most 256 tiles (1 to 2048 rows, 64 to 8192 columns, K 96 to 12288, all groups) the 4408 that these lines take need
+// 0.76 of the device's time, three of them more than 1.004 and at most 1.045; the others 0.94, up to 1.20 (INT3 g64 1009 x 502 x 3584 15.5 -> 18.5 us, g128 15 x 154 x 11264
 // 18.4 -> 20.1, INT4 g256 768 x 384 x 6144 20.3 -> 23.4).  us: INT4 g128 77 x 1000 x 1152 6.4 -> 5.2, INT3 g32 23 x 3117 x 3904 10.9 -> 9.8.
 bool split_takes_raw_scales(int tile, int64_t M, int64_t N, int64_t K) {
-  return qgemm_tiles(tile, M, N) <= 256 && ((tile == kTileSplit32 && K <= 5120) || (tile == kTileSplit64x32 && K <= 1536));
+  return qgemm_tiles(tile, M, N) <= 256 && ((tile == kTileSplit32 && K <= 5120) || (tile == kTileSplit64x32 && K <= 2304));
 }
 
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW = false, bool RAW = false>

@@ -489,8 +489,8 @@ def _launches(call):
 @pytest.mark.parametrize("fmt,g,M,N,K,tile,launches", [
     (pq.FMT_INT4, 32, 77, 1000, 5120, (32, 32), 1), (pq.FMT_INT4, 32, 77, 1000, 5152, (32, 32), 2),
     (pq.FMT_INT3, 64, 61, 1001, 5120, (32, 32), 1), (pq.FMT_INT3, 64, 61, 1001, 5184, (32, 32), 2),
-    (pq.FMT_INT4, 64, 500, 1021, 1536, (64, 32), 1), (pq.FMT_INT4, 64, 500, 1021, 1600, (64, 32), 2),
-    (pq.FMT_INT3, 64, 500, 1021, 1536, (64, 32), 1), (pq.FMT_INT3, 64, 500, 1021, 1600, (64, 32), 2),
+    (pq.FMT_INT4, 64, 500, 1021, 2304, (64, 32), 1), (pq.FMT_INT4, 64, 500, 1021, 2368, (64, 32), 2),
+    (pq.FMT_INT3, 64, 500, 1021, 2304, (64, 32), 1), (pq.FMT_INT3, 64, 500, 1021, 2368, (64, 32), 2),
     (pq.FMT_INT4, 64, 32, 8192, 256, (32, 32), 1), (pq.FMT_INT4, 64, 32, 8193, 256, (32, 32), 2),
     (pq.FMT_INT4, 64, 400, 1600, 256, (64, 64), 2), (pq.FMT_NVFP4, 16, 77, 1000, 1152, (32, 32), 1)])
 def test_which_products_prepare_their_scales(fmt, g, M, N, K, tile, launches):
