@@ -496,7 +496,7 @@ int run_qgemm(pq_format fmt, int group, const uint8_t* a_codes, const void* a_sc
     carve_gemm(ws, fmt, group, M, N, K, &G);
     const float Q = qmax_of((int)fmt);
     const int tile = choose_tile(fmt, group, M, N, K);
-    if (phases == 3 && split_takes_raw_scales(tile, M, N, K)) {
+    if (phases == 3 && split_takes_raw_scales(fmt, group, tile, M, N, K)) {
       A.scales = (const uint8_t*)a_scales;
       W.scales = (const uint8_t*)w_scales;
       A.sc_row = W.sc_row = (K / group) * 4;

@@ -547,7 +547,7 @@ enum Tile : int { kTile256 = 1, kTile128 = 2, kTile224 = 3, kTileSplit32 = 4, kT
 int launch_qgemm_split(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                        const Outputs& out, int tile, hipStream_t st);
 // whether a product of row-major INT operands prepares their scales in the product kernel, and that product
-bool split_takes_raw_scales(int tile, int64_t M, int64_t N, int64_t K);
+bool split_takes_raw_scales(pq_format fmt, int group, int tile, int64_t M, int64_t N, int64_t K);
 int launch_qgemm_split_raw(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                            const RawOutput& out, int tile, hipStream_t st);
 // the integer formats' large outputs with groups of 64 and more (pq_qgemm_group.hip)

@@ -605,13 +605,20 @@ static bool rows_through_lds(int64_t n_tiles, int ks, int K) {
 }
 
 // Whether a product of row-major INT operands prepares their scales itself (RAW) instead of in a launch before it, which
-// takes 1.3 to 2.5 us of the device and 2.7 of the host.  Every workgroup then reads all scales of its rows ahead of its first
-// step and loads two bytes more a unit, which a long K or many rows a workgroup make longer than the launch.  Of 5400 random
-// shapes of at most 256 tiles (1 to 2048 rows, 64 to 8192 columns, K 96 to 12288, all groups) the 4408 that these lines take need
-// 0.76 of the device's time, three of them more than 1.004 and at most 1.045; the others 0.94, up to 1.20 (INT3 g64 1009 x 502 x 3584 15.5 -> 18.5 us, g128 15 x 154 x 11264
-// 18.4 -> 20.1, INT4 g256 768 x 384 x 6144 20.3 -> 23.4).  us: INT4 g128 77 x 1000 x 1152 6.4 -> 5.2, INT3 g32 23 x 3117 x 3904 10.9 -> 9.8.
-bool split_takes_raw_scales(int tile, int64_t M, int64_t N, int64_t K) {
-  return qgemm_tiles(tile, M, N) <= 256 && ((tile == kTileSplit32 && K <= 5120) || (tile == kTileSplit64x32 && K <= 2304));
+// takes 1.3 to 2.5 us of the device and 2.7 of the host, and as long as it takes to read all codes where it looks for INT3 codes beyond
+// three bits.  Every workgroup then reads all scales of its rows ahead of its first step and loads two bytes more a unit.  With
+// many groups a row that is longer than the launch, with a long K where every row starts at a line of the cache (K a multiple of
+// 256) because the rows' lines push each other out, and earlier where a workgroup has 64 rows.  Random shapes of at most 256
+// tiles (1 to 2048 rows, 64 to 8192 columns, K 96 to 12288, all groups), device alone: the lines were drawn on 5400 and take 4687 of them in
+// 0.77 of the time of the launch and the product, two more than 1.01 and at most 1.045; of 6000 others, all with K from 1800 on, 3947 in
+// 0.85, 18 more than 1.01, at most 1.052.  Beyond the lines 0.96, up to 1.20 (INT3 g64 1009 x 502 x 3584 15.5 -> 18.5 us, INT4 g256 768 x 384 x
+// 6144 20.3 -> 23.4).  us: INT4 g128 77 x 1000 x 1152 6.4 -> 5.2, INT3 g128 24 x 6133 x 11904 28.2 -> 20.0.
+bool split_takes_raw_scales(pq_format fmt, int group, int tile, int64_t M, int64_t N, int64_t K) {
+  if (fmt == PQ_FMT_NVFP4 || (tile != kTileSplit32 && tile != kTileSplit64x32) || qgemm_tiles(tile, M, N) > 256) return false;
+  const bool marks = fmt == PQ_FMT_INT3 && group != 32, lines = K % 256 == 0;
+  if (marks && (M + N) * K >= 30000000) return true;
+  if (tile == kTileSplit32) return K <= 5120 || (!lines && K / group <= 128);
+  return K <= 2304 || (!lines && (marks || K <= 3072));
 }
 
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW = false, bool RAW = false>
@@ -708,7 +715,7 @@ static int split_raw(const OperandView& A, const OperandView& W, int M, int N, i
 
 int launch_qgemm_split_raw(pq_format fmt, int group, const OperandView& A, const OperandView& W, int M, int N, int K,
                            const RawOutput& out, int tile, hipStream_t st) {
-  if (fmt == PQ_FMT_NVFP4 || out.kind == kOutDiff || W.bias || !split_takes_raw_scales(tile, M, N, K))
+  if (out.kind == kOutDiff || W.bias || !split_takes_raw_scales(fmt, group, tile, M, N, K))
     return fail(PQ_ERR_FORMAT, "no product with fp32 group scales of this kind");
   const int g_shift = group_shift(fmt, group);
 #define PQ_RAW(MODE, WIDE)                                                                            \

@@ -488,13 +488,17 @@ def _launches(call):
 
 @pytest.mark.parametrize("fmt,g,M,N,K,tile,launches", [
     (pq.FMT_INT4, 32, 77, 1000, 5120, (32, 32), 1), (pq.FMT_INT4, 32, 77, 1000, 5152, (32, 32), 2),
-    (pq.FMT_INT3, 64, 61, 1001, 5120, (32, 32), 1), (pq.FMT_INT3, 64, 61, 1001, 5184, (32, 32), 2),
-    (pq.FMT_INT4, 64, 500, 1021, 2304, (64, 32), 1), (pq.FMT_INT4, 64, 500, 1021, 2368, (64, 32), 2),
-    (pq.FMT_INT3, 64, 500, 1021, 2304, (64, 32), 1), (pq.FMT_INT3, 64, 500, 1021, 2368, (64, 32), 2),
+    (pq.FMT_INT4, 64, 61, 1001, 5376, (32, 32), 2), (pq.FMT_INT4, 64, 61, 1001, 5440, (32, 32), 1),
+    (pq.FMT_INT4, 64, 61, 1001, 8192, (32, 32), 2), (pq.FMT_INT4, 64, 61, 1001, 8256, (32, 32), 2),
+    (pq.FMT_INT3, 64, 20, 5500, 5376, (32, 32), 2), (pq.FMT_INT3, 64, 20, 5600, 5376, (32, 32), 1), (pq.FMT_INT4, 64, 20, 5600, 5376, (32, 32), 2),
+    (pq.FMT_INT4, 64, 500, 1021, 2304, (64, 32), 1), (pq.FMT_INT4, 64, 500, 1021, 2560, (64, 32), 2),
+    (pq.FMT_INT4, 64, 500, 1021, 3008, (64, 32), 1), (pq.FMT_INT4, 64, 500, 1021, 3136, (64, 32), 2),
+    (pq.FMT_INT3, 64, 500, 1021, 2560, (64, 32), 2), (pq.FMT_INT3, 64, 500, 1021, 3136, (64, 32), 1),
     (pq.FMT_INT4, 64, 32, 8192, 256, (32, 32), 1), (pq.FMT_INT4, 64, 32, 8193, 256, (32, 32), 2),
     (pq.FMT_INT4, 64, 400, 1600, 256, (64, 64), 2), (pq.FMT_NVFP4, 16, 77, 1000, 1152, (32, 32), 1)])
 def test_which_products_prepare_their_scales(fmt, g, M, N, K, tile, launches):
-    """Either side of the lines in K, in tiles and in their size beyond which a launch prepares the scales."""
+    """Either side of each line beyond which a launch prepares the scales: in K, in groups, in tiles and their size, and in
+    the codes that the launch would read."""
     assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile
     gen = torch.Generator(device=DEV).manual_seed(M + N + K + g)
     x, w = (torch.randn((n, K), generator=gen, device=DEV).to(torch.bfloat16) for n in (M, N))
