@@ -36,12 +36,12 @@ struct RefTile {
 };
 
 // 16 bytes a lane from memory into LDS, 1 KB a wave from byte `to` on, without a register in between: by a 64-bit address, or
-// by a uniform base and an offset.  The wait for them is ref_wait's.
+// by a uniform base and an offset.  m0, an operand, holds `to`.  The wait for them is ref_wait's.
 __device__ __forceinline__ void load_to_lds(uint32_t to, const uint8_t* from) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory", "m0");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(to), "v"(from) : "memory");
 }
 __device__ __forceinline__ void load_to_lds(uint32_t to, const uint8_t* base, uint32_t offset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(offset), "s"(base) : "memory", "m0");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(to), "v"(offset), "s"(base) : "memory");
 }
 // all but the last N loads of this wave have arrived and its LDS reads are done; then the workgroup meets
 template <int N>
