@@ -4,7 +4,7 @@
 // lowers its clock, and how soon depends on the switching activity of the operands.  A loop that reuses
 // one pair of constant fragments (pq_probe_mfma) therefore overstates what a GEMM on real data can reach.
 // Here every lane unpacks eight fragments of the activation operand and four of the weight operand --
-// with the fp16 product kernel's own loader and unpack code, from rows and K positions spread over the
+// with the fp16 product kernel's own unpack code, from rows and K positions spread over the
 // operands -- and the loop cycles through them, so that both MFMA inputs change from one instruction to
 // the next.  No LDS, no vector work, no memory traffic inside the loop.
 #include "pq_qgemm_common.h"
@@ -19,8 +19,10 @@ __global__ __launch_bounds__(512) void probe_mfma_operands_kernel(OperandView A,
   auto fragment = [&](const OperandView& V, int rows, int idx) {
     const int row = (int)(((int64_t)blockIdx.x * 64 + (t >> 3) + (int64_t)idx * 8191) % rows);
     const int step = (idx * 5 + (int)blockIdx.x) % ksteps;
-    const Slice sl = load_slice<FMT, G>(V.codes + (int64_t)row * V.code_row, V.code_step,
-                                        V.scales + (int64_t)row * V.sc_row, V.sc_step, K, step, t & 1);
+    const int k = step * kBK + (t & 1) * 32, unit = FMT == kNvfp4 ? k / 32 : k / G;      // whole steps: k + 31 < K
+    Slice sl;
+    sl.codes = *reinterpret_cast<const uint4*>(V.codes + (int64_t)row * V.code_row + (int64_t)step * V.code_step + (t & 1) * 16);
+    sl.sc = *reinterpret_cast<const uint16_t*>(V.scales + (int64_t)row * V.sc_row + (int64_t)unit * V.sc_step);
     PairScale s0, s1;
     slice_scales<FMT>(sl, true, s0, s1);
     const int c = (t >> 1) & 3;

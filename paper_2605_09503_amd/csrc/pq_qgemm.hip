@@ -61,8 +61,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
   static_assert(BM % 32 == 0 && WTN % 32 == 0 && TM_LAST >= 1 && TM_LAST <= TM, "wave tile");
   static_assert(!RAGGED_M || (WGM == 2 && WGN == 4), "the uneven split is laid out for 2 x 4 waves");
   // the loader covers SL * T / 2 rows of each operand; an A tile of fewer rows (BM = 224) still gets all
-  // of them in LDS, so that no thread needs a predicate around its unpack writes (the spare rows hold zeros
-  // and are never read)
+  // of them in LDS, so that no thread needs a predicate around its unpack writes (the spare rows hold the
+  // matrix rows behind the tile and are never read)
   constexpr int A_TILE_BYTES = SL * (T / 2) * kRowBytes, W_TILE_BYTES = BN * kRowBytes;
   constexpr int STAGE_BYTES = A_TILE_BYTES + W_TILE_BYTES;
 
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void qgemm_kernel(OperandView A, Ope
   };
 
   // two steps per trip so that the LDS stage and the register set are compile-time constants;
-  // an odd step count runs one extra step on all-zero operands (loads beyond K are zeroed),
+  // an odd step count runs one extra step, the last one's codes under scales of zero,
   // which keeps a single loop exit (two exits would double the live accumulators)
   if (!RAGGED_M || tm_cnt == TM) {
     for (int s = 0; s < ksteps; s += 2) {

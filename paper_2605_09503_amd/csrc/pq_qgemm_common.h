@@ -54,31 +54,13 @@ struct OperandView {
   const uint16_t* bias = nullptr;
 };
 
-// Branch-free load of one slice.  `codes_row` / `sc_row` point at a valid row (the caller
-// clamps the row index) and a k beyond K is redirected to the row start, so the address is
-// always valid.  The loaded registers are not touched here (a use would make the wave wait for
-// the load at once); a slice that is out of range is neutralised when it is unpacked, by
-// zeroing its scale (see slice_scales).
-template <int FMT, int G>
-__device__ __forceinline__ Slice load_slice(const uint8_t* __restrict__ codes_row, int code_step,
-                                            const uint8_t* __restrict__ sc_row, int sc_step, int K,
-                                            int step, int half) {
-  const int k0 = step * kBK + half * 32;
-  const bool ok = k0 < K;
-  const int unit = FMT == kNvfp4 ? k0 >> 5 : k0 / G;
-  Slice s;
-  s.codes = *reinterpret_cast<const uint4*>(codes_row + (ok ? (int64_t)step * code_step + half * 16 : 0));
-  s.sc = *reinterpret_cast<const uint16_t*>(sc_row + (ok ? (int64_t)unit * sc_step : 0));
-  return s;
-}
-
 // Scale pair(s) handed to unpack_pair.  INT carries {h, h} and {-8 h, -8 h} (see below).
 struct PairScale {
   half2_t mul, add;
 };
 
-// {s, s} pairs of the two group scales a slice can touch; all zero when the slice is out of
-// range (row beyond the matrix or k beyond K), so that whatever codes were loaded contribute 0
+// {s, s} pairs of the two group scales a slice can touch; all zero when it lies beyond K (ok is false), so that
+// whatever codes were loaded contribute 0
 template <int FMT>
 __device__ __forceinline__ void slice_scales(const Slice& s, bool ok, PairScale& p0, PairScale& p1) {
   if constexpr (FMT == kNvfp4) {
