@@ -350,6 +350,31 @@ def test_calls_without_the_native_binding_give_the_same(tmp_path, fmt, g):
             assert torch.equal(u, v)
 
 
+class _KernelNode(ctypes.Structure):
+    """hipKernelNodeParams"""
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def _launches(call):
+    """Threads of a workgroup of each kernel that a call launches: the nodes of the graph it is captured into."""
+    call()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    lib, n, threads = pq.load(), ctypes.c_size_t(), []
+    lib.hipGraphGetNodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    lib.hipGraphKernelNodeGetParams.argtypes = [ctypes.c_void_p, ctypes.POINTER(_KernelNode)]
+    assert lib.hipGraphGetNodes(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert lib.hipGraphGetNodes(graph.raw_cuda_graph(), nodes, ctypes.byref(n)) == 0
+    for node in nodes:
+        params = _KernelNode()
+        assert lib.hipGraphKernelNodeGetParams(node, ctypes.byref(params)) == 0
+        threads.append(params.block[0] * params.block[1] * params.block[2])
+    return threads
+
+
 def _dequantized(fmt, g, x, T):
     """Q(x) of the library's own quantizer in 64 bits, from its stored codes and scales."""
     codes, scales = pq.alloc_quantized(fmt, g, x.shape[0], x.shape[1], DEV)
@@ -364,24 +389,32 @@ def _dequantized(fmt, g, x, T):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("fmt,g,M,N,K,tile", [
-    (pq.FMT_NVFP4, 16, 61, 1001, 1184, (32, 32)), (pq.FMT_NVFP4, 16, 500, 1021, 320, (64, 32)),
-    (pq.FMT_NVFP4, 16, 449, 3077, 96, (64, 64)), (pq.FMT_NVFP4, 16, 2309, 3077, 96, (128, 128)),
-    (pq.FMT_NVFP4, 16, 4099, 5125, 320, None), (pq.FMT_INT3, 32, 4099, 5125, 320, None),
-    (pq.FMT_INT4, 64, 77, 1001, 1152, (32, 32)), (pq.FMT_INT4, 64, 1100, 4099, 128, (64, 64)),
-    (pq.FMT_INT4, 64, 2309, 5125, 128, (224, 256)), (pq.FMT_INT3, 64, 2309, 5125, 128, (224, 256)),
-    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64)), (pq.FMT_INT3, 128, 100, 300, 256, (32, 32)),
+@pytest.mark.parametrize("fmt,g,M,N,K,tile,waves", [
+    # every tile of NVFP4, of groups of 32, and of the larger groups of INT4 and INT3
+    (pq.FMT_NVFP4, 16, 61, 1001, 1184, (32, 32), 8), (pq.FMT_NVFP4, 16, 500, 1021, 320, (64, 32), 8),
+    (pq.FMT_NVFP4, 16, 449, 3077, 96, (64, 64), 4), (pq.FMT_NVFP4, 16, 227, 2235, 1792, (64, 64), 8),
+    (pq.FMT_NVFP4, 16, 527, 2569, 96, (64, 96), 4), (pq.FMT_NVFP4, 16, 279, 3495, 1792, (64, 96), 8),
+    (pq.FMT_NVFP4, 16, 2309, 3077, 96, (128, 128), 4), (pq.FMT_NVFP4, 16, 4099, 5125, 320, (128, 128), 4),
+    (pq.FMT_NVFP4, 16, 2339, 3745, 160, (224, 256), 8), (pq.FMT_NVFP4, 16, 3600, 4081, 160, (256, 256), 8),
+    (pq.FMT_INT3, 32, 33, 137, 96, (32, 32), 8), (pq.FMT_INT4, 32, 500, 1021, 1632, (64, 32), 8), (pq.FMT_INT3, 32, 449, 3077, 1184, (64, 64), 4),
+    (pq.FMT_INT4, 32, 133, 3735, 2560, (64, 64), 8), (pq.FMT_INT3, 32, 2373, 425, 96, (64, 96), 4), (pq.FMT_INT4, 32, 1159, 837, 2560, (64, 96), 8),
+    (pq.FMT_INT3, 32, 4099, 5125, 320, (128, 128), 4), (pq.FMT_INT4, 32, 2101, 3921, 96, (224, 256), 8), (pq.FMT_INT3, 32, 2344, 4081, 192, (224, 256), 8),
+    (pq.FMT_INT3, 32, 3600, 4082, 192, (256, 256), 8),
+    (pq.FMT_INT4, 64, 77, 1001, 1152, (32, 32), 8), (pq.FMT_INT4, 64, 65, 2915, 64, (64, 32), 8), (pq.FMT_INT4, 64, 1100, 4099, 128, (64, 64), 4),
+    (pq.FMT_INT4, 64, 161, 3039, 2560, (64, 64), 8), (pq.FMT_INT4, 64, 2375, 457, 384, (64, 96), 4), (pq.FMT_INT4, 64, 539, 1865, 2560, (64, 96), 8),
+    (pq.FMT_INT4, 64, 2345, 833, 64, (128, 128), 4), (pq.FMT_INT4, 64, 2309, 5125, 128, (224, 256), 8), (pq.FMT_INT4, 64, 3600, 4081, 192, (256, 256), 8),
+    (pq.FMT_INT3, 128, 100, 300, 256, (32, 32), 8), (pq.FMT_INT3, 64, 65, 2881, 64, (64, 32), 8), (pq.FMT_INT3, 64, 153, 4009, 64, (64, 64), 4),
+    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64), 4), (pq.FMT_INT3, 64, 1889, 1607, 64, (64, 96), 4), (pq.FMT_INT3, 64, 585, 3289, 64, (128, 128), 4),
+    (pq.FMT_INT3, 64, 2309, 5125, 128, (224, 256), 8), (pq.FMT_INT3, 64, 3600, 4081, 192, (256, 256), 8),
     # waves that have one step, two, an odd number of them, none; a last step of 32 k
-    (pq.FMT_NVFP4, 16, 61, 1001, 32, None), (pq.FMT_NVFP4, 16, 61, 1001, 512, None), (pq.FMT_NVFP4, 16, 61, 1001, 544, None),
-    (pq.FMT_NVFP4, 16, 500, 1021, 1056, None), (pq.FMT_NVFP4, 16, 500, 1021, 1120, None), (pq.FMT_NVFP4, 16, 449, 3077, 288, None),
-    (pq.FMT_NVFP4, 16, 449, 3077, 864, None), (pq.FMT_INT4, 32, 500, 1021, 1632, None), (pq.FMT_INT3, 32, 449, 3077, 1184, None),
-    (pq.FMT_NVFP4, 16, 512, 1650, 3104, None), (pq.FMT_INT3, 64, 512, 3072, 3136, None)])
-def test_row_and_column_factors_and_bias_of_every_tile(fmt, g, M, N, K, tile):
+    (pq.FMT_NVFP4, 16, 61, 1001, 32, (32, 32), 8), (pq.FMT_NVFP4, 16, 61, 1001, 512, (32, 32), 8), (pq.FMT_NVFP4, 16, 61, 1001, 544, (32, 32), 8),
+    (pq.FMT_NVFP4, 16, 500, 1021, 1056, (64, 32), 8), (pq.FMT_NVFP4, 16, 500, 1021, 1120, (64, 32), 8), (pq.FMT_NVFP4, 16, 449, 3077, 288, (64, 64), 4),
+    (pq.FMT_NVFP4, 16, 449, 3077, 864, (64, 64), 4), (pq.FMT_NVFP4, 16, 512, 1650, 3104, (64, 64), 8), (pq.FMT_INT3, 64, 512, 3072, 3136, (64, 96), 8)])
+def test_row_and_column_factors_and_bias_of_every_tile(fmt, g, M, N, K, tile, waves):
     """Rows and columns of very different size, a bias, ragged edges: every tile's epilogue takes its own factors.  The
     fp32 product against the 64-bit product of what the quantizer stored: K roundings of 2^-24 of the magnitudes (the INT
     factors h / Q are rounded once more each); the bf16 one with the bias is the fp32 one plus the bias, rounded once."""
-    if tile is not None:
-        assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile
+    assert pq.pq_qgemm_tile(fmt, g, M, N, K) == tile, "this shape is here for its tile: choose another"
     gen = torch.Generator(device=DEV).manual_seed(M + N + K + g)
     rnd = lambda *s: torch.randn(s, generator=gen, device=DEV)
     rows, cols = torch.arange(M, device=DEV), torch.arange(N, device=DEV)
@@ -398,7 +431,8 @@ def test_row_and_column_factors_and_bias_of_every_tile(fmt, g, M, N, K, tile):
     y = torch.empty((M, ldy), dtype=torch.bfloat16, device=DEV)
     pq.pq_qgemm_packed_f32(fmt, g, a, Ta, wo, Tw, yf, M, N, K, ldy=ldy)
     pq.pq_qgemm_packed_bias(fmt, g, a, Ta, wo, Tw, bias, yb, M, N, K, ldy=ldy)
-    pq.pq_qgemm_packed(fmt, g, a, Ta, wo, Tw, y, M, N, K, ldy=ldy)
+    [threads] = _launches(lambda: pq.pq_qgemm_packed(fmt, g, a, Ta, wo, Tw, y, M, N, K, ldy=ldy))
+    assert threads == waves * 64, "this shape is here for the waves that share its tile: choose another"
     yf, yb, y = yf[:, :N], yb[:, :N], y[:, :N]
     bound = (K + 4) * 2.0 ** -24 * (xq.abs() @ wq.abs().t())
     assert ((yf.double() - xq @ wq.t()).abs() <= bound).all()
@@ -423,14 +457,16 @@ def _int_operand(fmt, g, rows, K, gen, odd_codes):
 
 
 @pytest.mark.parametrize("odd_codes", [False, True])
-@pytest.mark.parametrize("fmt,g,M,N,K", [
-    (pq.FMT_INT4, 32, 1, 128, 32), (pq.FMT_INT4, 32, 77, 1000, 1184), (pq.FMT_INT4, 32, 33, 257, 4096), (pq.FMT_INT4, 64, 31, 45, 64),
-    (pq.FMT_INT4, 64, 500, 1021, 1088), (pq.FMT_INT4, 128, 77, 1000, 1152), (pq.FMT_INT4, 256, 300, 900, 512),
-    (pq.FMT_INT4, 32, 500, 1021, 2048), (pq.FMT_INT3, 32, 61, 1001, 544), (pq.FMT_INT3, 64, 61, 1001, 8192),
-    (pq.FMT_INT3, 128, 300, 900, 640), (pq.FMT_INT3, 64, 500, 1021, 4096), (pq.FMT_INT4, 64, 61, 1001, 8256)])
-def test_scales_prepared_in_the_product_kernel(fmt, g, M, N, K, odd_codes):
-    """pq_qgemm prepares the scales of small products inside the product kernel; pq_qgemm_prep and _run keep the launch for
-    it.  The same bits, on either side of the lines between the two, and those of the packed operands."""
+@pytest.mark.parametrize("fmt,g,M,N,K,launches", [
+    (pq.FMT_INT4, 32, 1, 128, 32, 1), (pq.FMT_INT4, 32, 77, 1000, 1184, 1), (pq.FMT_INT4, 32, 33, 257, 4096, 1), (pq.FMT_INT4, 64, 31, 45, 64, 1),
+    (pq.FMT_INT4, 64, 500, 1021, 1088, 1), (pq.FMT_INT4, 128, 77, 1000, 1152, 1), (pq.FMT_INT4, 256, 300, 900, 512, 1),
+    (pq.FMT_INT4, 32, 500, 1021, 2048, 1), (pq.FMT_INT3, 32, 61, 1001, 544, 1), (pq.FMT_INT3, 64, 61, 1001, 8192, 2),
+    (pq.FMT_INT3, 128, 300, 900, 640, 1), (pq.FMT_INT3, 64, 500, 1021, 4096, 2), (pq.FMT_INT4, 64, 61, 1001, 8256, 2),
+    # one tile more than 256, of 32 and of 64 rows
+    (pq.FMT_INT4, 64, 32, 8193, 256, 2), (pq.FMT_INT3, 64, 16, 8225, 256, 2), (pq.FMT_INT3, 64, 97, 4097, 128, 2)])
+def test_scales_prepared_in_the_product_kernel(fmt, g, M, N, K, launches, odd_codes):
+    """pq_qgemm prepares the scales of small products inside the product kernel (one launch); pq_qgemm_prep and _run keep the
+    launch for it.  The same bits, on either side of the lines between the two, and those of the packed operands."""
     gen = torch.Generator(device=DEV).manual_seed(M + N + K + g + odd_codes)
     ac, as_ = _int_operand(fmt, g, M, K, gen, odd_codes)
     wc, ws = _int_operand(fmt, g, N, K, gen, odd_codes)
@@ -438,6 +474,7 @@ def test_scales_prepared_in_the_product_kernel(fmt, g, M, N, K, odd_codes):
     ys = [torch.full((M, ldy), 3.0, dtype=t, device=DEV) for t in (torch.bfloat16, torch.bfloat16, torch.bfloat16, torch.float32, torch.float32)]
     work = torch.empty(max(16, pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K)), dtype=torch.uint8, device=DEV)
     pq.pq_qgemm(fmt, g, ac, as_, None, wc, ws, None, ys[0], workspace=work, N=N, ldy=ldy)
+    assert len(_launches(lambda: pq.pq_qgemm(fmt, g, ac, as_, None, wc, ws, None, ys[0], workspace=work, N=N, ldy=ldy))) == launches
     pq.pq_qgemm_prep(fmt, g, as_, ws, M, N, K, work)
     pq.pq_qgemm_run(fmt, g, ac, as_, None, wc, ws, None, ys[1], work, N=N, ldy=ldy)
     a, w = pq.pq_pack_operand(fmt, g, ac, as_), pq.pq_pack_operand(fmt, g, wc, ws)
@@ -473,19 +510,6 @@ def test_a_product_leaves_the_workspace_ready_for_the_run(fmt, g, M, N, K):
     assert torch.equal(work, prepared)
 
 
-def _launches(call):
-    """Kernel launches of a call: nodes of the graph it is captured into."""
-    call()
-    graph = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(graph):
-        call()
-    n = ctypes.c_size_t()
-    count = pq.load().hipGraphGetNodes
-    count.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
-    assert count(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
-    return n.value
-
-
 @pytest.mark.parametrize("fmt,g,M,N,K,tile,launches", [
     (pq.FMT_INT4, 32, 77, 1000, 5120, (32, 32), 1), (pq.FMT_INT4, 32, 77, 1000, 5152, (32, 32), 2),
     (pq.FMT_INT4, 64, 61, 1001, 5376, (32, 32), 2), (pq.FMT_INT4, 64, 61, 1001, 5440, (32, 32), 1),
@@ -508,7 +532,7 @@ def test_which_products_prepare_their_scales(fmt, g, M, N, K, tile, launches):
     pq.pq_quantize_act(fmt, g, w, None, T, wc, ws)
     y = torch.empty((M, (N + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)
     work = torch.empty(max(16, pq.pq_workspace_bytes(pq.OP_QGEMM, fmt, g, M, N, K)), dtype=torch.uint8, device=DEV)
-    assert _launches(lambda: pq.pq_qgemm(fmt, g, ac, as_, T, wc, ws, T, y, workspace=work, N=N, ldy=y.shape[1])) == launches
+    assert len(_launches(lambda: pq.pq_qgemm(fmt, g, ac, as_, T, wc, ws, T, y, workspace=work, N=N, ldy=y.shape[1]))) == launches
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K", [
