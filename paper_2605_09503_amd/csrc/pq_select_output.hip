@@ -195,11 +195,14 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(RowBatches xs, const uint
 
 int64_t ref_tiles(int64_t M, int64_t N, int cols) { return ((M + kRefRows - 1) / kRefRows) * ((N + cols - 1) / cols); }
 
-// Columns of the reference product's tile: the ones whose fullest unit has the fewer outputs; the smaller where it is the same
-// (two workgroups run beside each other).
-int ref_cols(int64_t M, int64_t N) {
+// Columns of the reference product's tile: the ones whose fullest unit has the fewer outputs; the smaller where it is the same,
+// and where K is short: two workgroups run beside each other, and one's stores, which do not get shorter with K, hide behind
+// the other's loads (4592 x 6500 x 96 32.5 us, with 192 columns 40.2; 6208 x 4909 x 64 31.5, 38.9).  Over 1056 random shapes (64 to
+// 12288 rows and columns, K 64 to 12288) the better tile's time is missed by 0.2 % in the mean, by more than 5 % for 18 of them, at most
+// 11 % (873 x 9820 x 9312: three rounds of the small tile 259 us, two of the large one 233); without the line in K 0.4 %, 39, 24 %.
+int ref_cols(int64_t M, int64_t N, int64_t K) {
   const auto fullest = [&](int cols) { return (ref_tiles(M, N, cols) + 255) / 256 * cols; };
-  return fullest(192) < fullest(128) ? 192 : 128;
+  return K >= 8 * kRefStep && fullest(192) < fullest(128) ? 192 : 128;
 }
 
 template <int TN>
@@ -387,7 +390,7 @@ int run_select_output(pq_format fmt, int group, const double* act_sumsq, const d
     return x;
   };
   // the unquantized products, once
-  const int cols = ref_cols(stack * M, N);
+  const int cols = ref_cols(stack * M, N, K);
   for (int b0 = 0; b0 < n_batches; b0 += stack) {
     int64_t rows;
     const RowBatches x = rows_from(b0, &rows);

@@ -536,7 +536,8 @@ def test_which_products_prepare_their_scales(fmt, g, M, N, K, tile, launches):
 
 
 @pytest.mark.parametrize("fmt,g,M,N,K", [
-    (pq.FMT_NVFP4, 16, 1000, 3001, 96), (pq.FMT_NVFP4, 16, 1000, 3001, 32), (pq.FMT_INT4, 64, 1000, 3001, 192),     # 128 x 192 tiles
+    (pq.FMT_NVFP4, 16, 1000, 3001, 96), (pq.FMT_NVFP4, 16, 1000, 3001, 32), (pq.FMT_INT4, 64, 1000, 3001, 192),
+    (pq.FMT_NVFP4, 16, 1000, 3001, 480), (pq.FMT_NVFP4, 16, 1000, 3001, 512), (pq.FMT_NVFP4, 16, 1000, 3001, 544), (pq.FMT_INT4, 64, 1000, 3001, 576),   # 128 x 192 tiles from K = 512 on
     (pq.FMT_NVFP4, 16, 65, 131, 32), (pq.FMT_INT4, 64, 65, 131, 64), (pq.FMT_NVFP4, 16, 129, 257, 160), (pq.FMT_INT3, 64, 130, 390, 448)])
 def test_output_error_against_the_unquantized_product(fmt, g, M, N, K):
     """Both tiles of the unquantized product, ragged edges, one step of K and fewer than its stages, a last step of 32.  An
