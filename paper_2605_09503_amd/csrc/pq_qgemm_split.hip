@@ -87,10 +87,11 @@ __device__ __forceinline__ void leave_scales(const OperandView& A, const Operand
 // whole runs of 32 KS bytes of every row, and the waves pick their step out of LDS (two sets of steps, a barrier for
 // each).  The sums are the same as without, and as those of the packed operands, bit for bit.  See rows_through_lds.
 // WIDE (kSplitE2m1): how codes that E2M1 does not hold are found
-template <int TM, int TN, int WIDE, bool ROWS>
-constexpr int kSplitWaves = (ROWS || WIDE == kWideMarks) && TM * TN == 4 && WIDE != kWideCodes ? 3 : 2;      // a SIMD's; kWideCodes would spill
+template <int TM, int TN, int WIDE, bool ROWS, bool FEW>
+constexpr int kSplitWaves = (ROWS || WIDE == kWideMarks) && TM * TN == 4 && WIDE != kWideCodes && !FEW ? 3 : 2;      // a SIMD's; kWideCodes would spill
 // FEW: at most four waves a SIMD are wanted, so that the compiler spends registers on loads further ahead (32 x 32: 84 instead
-// of 58, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).
+// of 58, which is two workgroups a unit instead of four; 64 x 32: 116 instead of 89, two workgroups either way).  INT3 codes, 64 x 64:
+// two waves instead of three (184 registers instead of 162), and blocks in the compiler's order.
 // kSplitFull: without FEW the four workgroups a unit of the 32 x 32 tiles have to be demanded (eight waves a SIMD, 64 registers; the
 // compiler's own choice is 74 to 84): 72 NVFP4 shapes of more than 512 tiles and K up to 512 0.92 of the time without, 417 integer
 // ones 0.99, row-major the same.
@@ -100,7 +101,7 @@ constexpr bool kSplitFull = MODE != kSplitE2m1 && TM * TN == 1 && OUT != kOutDif
 // turns each scale that it loads into the operand's unit.  Workgroups beside those of the tiles leave units and factors in the
 // workspace.  See split_takes_raw_scales.
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE, bool ROWS, bool FEW, bool RAW>
-__global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitFull<MODE, TM, TN, OUT, FEW> ? 8 : kSplitWaves<TM, TN, WIDE, ROWS>, FEW ? 4 : 8))) void
+__global__ __launch_bounds__(KS * 64) __attribute__((amdgpu_waves_per_eu(kSplitFull<MODE, TM, TN, OUT, FEW> ? 8 : kSplitWaves<TM, TN, WIDE, ROWS, FEW>, FEW ? 4 : 8))) void
 qgemm_split_kernel(
     OperandView A, OperandView W, int M, int N, int K, int g_shift, KernelOutput<OUT, RAW> out, int tiles_m, int tiles_n) {
   if constexpr (OUT == kOutDiff) enter_problem(A, W, out);
@@ -282,7 +283,7 @@ qgemm_split_kernel(
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(p[r], s[r], acc[i][j][r]);
           // a block at a time where three workgroups share a unit: the compiler's own order takes more than 168 registers
-          if constexpr (TM * TN == 4) __builtin_amdgcn_sched_barrier(0);
+          if constexpr (TM * TN == 4 && !FEW) __builtin_amdgcn_sched_barrier(0);
         }
       }
   };
@@ -642,7 +643,9 @@ static int launch_split(const OperandView& A, const OperandView& W, int M, int N
 
 // The loader of the operands' layout and the shape.  FEW as long as two workgroups a unit hold the launch: NVFP4 109 x 140 x
 // 4928 (20 tiles) 12.7 us, FEW 12.2, 43 x 3659 x 10240 (230) 20.9, 19.9, 134 x 10981 x 320 (1720) 8.6, 11.2.  12500 shapes of these
-// tiles against FEW throughout 0.997 (0.81 to 0.95 beyond 512 tiles), 13300 against none 0.991.
+// tiles against FEW throughout 0.997 (0.81 to 0.95 beyond 512 tiles), 13300 against none 0.991.  INT3 codes on 64 x 64 up to 512 tiles,
+// 1740 shapes: 0.97 of the time of three workgroups a unit, K beyond 4096 0.91 (1.07 of what it was before there were three; 0.96
+// with FEW); up to 700 tiles three and two take the same, beyond them three win.
 template <int MODE, int TM, int TN, int KS, int OUT, int WIDE>
 static int split_loader(const OperandView& A, const OperandView& W, int M, int N, int K, int g_shift, const Outputs& out,
                         hipStream_t st) {
@@ -651,8 +654,8 @@ static int split_loader(const OperandView& A, const OperandView& W, int M, int N
     if (!(A.panel && W.panel) && rows_through_lds(n_tiles, KS, K))
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
   }
-  constexpr bool kMayBeFew = TN == 1 && MODE != kSplitE2m1, kFew = kMayBeFew && TM == 2;
-  if constexpr (kMayBeFew && TM == 1) {
+  constexpr bool kMayBeFew = MODE == kSplitE2m1 ? WIDE == kWideMarks && TM * TN == 4 : TN == 1, kFew = kMayBeFew && TM * TN == 2;
+  if constexpr (kMayBeFew && !kFew) {
     if (n_tiles * out.problems <= 512)
       return launch_split<MODE, TM, TN, KS, OUT, WIDE, false, true>(A, W, M, N, K, g_shift, out, st);
   }
@@ -667,7 +670,7 @@ static int split_eight(const OperandView& A, const OperandView& W, int M, int N,
   if constexpr (OUT != kOutDiff) {
     if (!(A.panel && W.panel)) return launch_split<MODE, 2, TN, 8, OUT, WIDE, true>(A, W, M, N, K, g_shift, out, st);
   }
-  return launch_split<MODE, 2, TN, 8, OUT, WIDE, false>(A, W, M, N, K, g_shift, out, st);
+  return launch_split<MODE, 2, TN, 8, OUT, WIDE, false, MODE == kSplitE2m1 && WIDE == kWideMarks && TN == 2>(A, W, M, N, K, g_shift, out, st);
 }
 
 template <int MODE, int OUT, int WIDE>

@@ -404,7 +404,7 @@ def _dequantized(fmt, g, x, T):
     (pq.FMT_INT4, 64, 161, 3039, 2560, (64, 64), 8), (pq.FMT_INT4, 64, 2375, 457, 384, (64, 96), 4), (pq.FMT_INT4, 64, 539, 1865, 2560, (64, 96), 8),
     (pq.FMT_INT4, 64, 2345, 833, 64, (128, 128), 4), (pq.FMT_INT4, 64, 2309, 5125, 128, (224, 256), 8), (pq.FMT_INT4, 64, 3600, 4081, 192, (256, 256), 8),
     (pq.FMT_INT3, 128, 100, 300, 256, (32, 32), 8), (pq.FMT_INT3, 64, 65, 2881, 64, (64, 32), 8), (pq.FMT_INT3, 64, 153, 4009, 64, (64, 64), 4),
-    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64), 4), (pq.FMT_INT3, 64, 1889, 1607, 64, (64, 96), 4), (pq.FMT_INT3, 64, 585, 3289, 64, (128, 128), 4),
+    (pq.FMT_INT3, 64, 449, 3077, 3072, (64, 64), 4), (pq.FMT_INT3, 64, 1000, 3077, 512, (64, 64), 4), (pq.FMT_INT3, 64, 1889, 1607, 64, (64, 96), 4), (pq.FMT_INT3, 64, 585, 3289, 64, (128, 128), 4),
     (pq.FMT_INT3, 64, 2309, 5125, 128, (224, 256), 8), (pq.FMT_INT3, 64, 3600, 4081, 192, (256, 256), 8),
     # waves that have one step, two, an odd number of them, none; a last step of 32 k
     (pq.FMT_NVFP4, 16, 61, 1001, 32, (32, 32), 8), (pq.FMT_NVFP4, 16, 61, 1001, 512, (32, 32), 8), (pq.FMT_NVFP4, 16, 61, 1001, 544, (32, 32), 8),
