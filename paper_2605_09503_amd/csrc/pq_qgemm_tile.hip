@@ -12,14 +12,18 @@ namespace pq {
 // takes 21.7).
 // The coefficients (us) began as least-squares fits of the logarithm of measured times (graph replays, 1285 shapes of 1e7 to 7e11
 // operations, 16 to 8192 rows, 128 to 12288 columns, K 96 to 12288).  Those of the first three rows were then moved, a few
-// at a time, wherever that made the choices cost less over 9400 random shapes of which every tile was timed with the kernels as they
-// are: what they predict are ratios of neighbouring tiles, no longer times.  Over those shapes the choice costs over the best
-// tile in the mean (more than 5 % for, at most), before and now: NVFP4 1.2 % (7.5 %, 36 %), 0.5 % (3.6 %, 36 %); groups of 32 0.7 % (4.5 %, 39 %),
-// 0.2 % (1.4 %, 30 %); INT4 1.2 % (6.4 %, 51 %), 0.4 % (2.2 %, 38 %).  Where the choice changed (5 to 7 % of the shapes) packed operands
-// take 0.89 to 0.93 of the time and row-major ones 0.96 to 0.99 (49 measured; INT4 g64 557 x 2211 x 384 packed 1.014, NVFP4 37 x 9559 x
-// 1920 1.12, 1.25).  INT3 with larger groups keeps its first fit: packed 0.91, but row-major 1.01, up to 1.26.  In single products;
-// launches of several problems are not in them.  Where the line lies, e.g. NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us):
-// 1024 x 3072 22 | 32 (of 128 x 128), 2048 x 3072 37 | 47 (the same), 4608 x 3072 81 | 70.
+// at a time, wherever that made the choices cost less over random shapes of which the tiles were timed: what they predict are ratios
+// of neighbouring tiles, no longer times (the third row by 3100 packed shapes; the first two by 3400 shapes of up to 8e10 operations and some
+// 900 of up to 3e12 each, in both layouts, with a price on what was slower than the choices before).  The search kept the tiles that the tests
+// ask for.  Over shapes that it had not seen, up to 8e10 operations, the choice costs over the best tile, in the mean (more than 5 %
+// for, at most): NVFP4 packed 0.7 % (4.2 %, 28 %), row-major 1.4 % (8 %); groups of 32 0.4 % (2.8 %, 24 %), 0.9 % (6 %); INT4 0.7 % (5 %, 34 %),
+// 0.6 % (5 %); INT3 with larger groups, which keeps its first fit, 1.7 % (12 %, 39 %); with the first fits 1.4, 1.7; 1.2, 1.2; 1.4, 0.9 %.
+// Where the choice differs from the first fit's (7 to 9 % of the shapes) packed operands take 0.92 to 0.93 of the time, row-major ones 0.96 to 0.97; of 1100
+// shapes each 6, 7 and 2 packed ones lose more than 2 %, at most 13 %, and 14 to 16 row-major ones, at most 17 % (NVFP4 37 x 9559 x 1920, the
+// kernels as they are: packed 8.7 -> 8.1, row-major 9.2 -> 9.6).  INT4 of 5e10 to 6e11 operations: one tile for both layouts helps the one and costs
+// the other, 0.94 and 1.07 on the 8 % of them where it changed.  In single products; a whole selection by output error, whose launches
+// hold several, takes 0.95 of the time that it took with the first fits and the kernels of then (60000 shapes, at most 1.08).  Where the line lies, e.g.
+// NVFP4, K = 3072 (split 64 x 96 | 256 or 224 x 256, us): 1024 x 3072 22 | 32 (of 128 x 128), 2048 x 3072 37 | 47 (the same), 4608 x 3072 81 | 70.
 struct TileCost {
   float a, b, l0, l1, th, odd;
 };
@@ -30,12 +34,12 @@ static constexpr TileSize kTileSize[] = {{0, 0}, {256, 256}, {128, 128}, {224, 2
 // rows: NVFP4; INT4 and INT3 with groups of 32; INT4 with larger groups; INT3 with larger groups.  Columns: the tiles in
 // the order of their numbers.
 static constexpr TileCost kTileCost[4][8] = {
-    {{}, {10.14f, 1.336f, 0.4999f, 0.03418f, 0.9593f, 1.699f}, {2.172f, 0.4726f, 4.863f, 0.05092f, 0.7723f, 0.5571f}, {10.48f, 1.201f, 0.13f, 0.07795f, 1.0f, 1.064f},
-     {0.6316f, 0.06518f, 3.127f, 0.06229f, 0.2271f, 0.002154f}, {1.126f, 0.07982f, 2.681f, 0.006329f, 0.7159f, 0.01633f}, {1.082f, 0.108f, 3.559f, 0.1499f, 0.6245f, 0.1685f},
-     {1.828f, 0.1479f, 3.748f, 0.02096f, 0.6285f, 0.1696f}},
-    {{}, {9.68f, 1.494f, 0.2064f, 0.0f, 0.9599f, 1.2f}, {2.072f, 0.553f, 4.296f, 1.133f, 0.8489f, 0.5345f}, {9.877f, 1.34f, 0.09746f, 0.03907f, 0.9639f, 1.174f},
-     {0.501f, 0.06817f, 3.24f, 0.05716f, 0.8612f, 0.01206f}, {1.03f, 0.09488f, 2.85f, 0.1271f, 0.8889f, 0.0f}, {1.108f, 0.1398f, 3.774f, 0.184f, 0.7875f, 0.03402f},
-     {1.887f, 0.1908f, 3.921f, 0.2287f, 0.7511f, 0.101f}},
+    {{}, {10.27f, 1.11f, 0.4591f, 0.03709f, 1.0f, 2.277f}, {2.149f, 0.4713f, 4.489f, 0.04796f, 0.6695f, 0.5793f}, {9.647f, 1.055f, 0.1511f, 0.06031f, 1.0f, 1.34f},
+     {0.6366f, 0.06033f, 3.127f, 0.04826f, 0.3135f, 0.002926f}, {1.126f, 0.07982f, 2.681f, 0.009439f, 0.7159f, 0.01874f}, {1.067f, 0.1055f, 3.549f, 0.1499f, 0.6649f, 0.1685f},
+     {1.814f, 0.1478f, 3.781f, 0.02284f, 0.5977f, 0.1431f}},
+    {{}, {9.662f, 1.371f, 0.2073f, 0.01711f, 0.9232f, 1.267f}, {2.067f, 0.5588f, 4.283f, 1.133f, 0.8489f, 0.5542f}, {9.772f, 1.246f, 0.1311f, 0.04011f, 1.0f, 1.309f},
+     {0.4727f, 0.07413f, 3.301f, 0.06303f, 0.8232f, 0.01681f}, {1.058f, 0.09064f, 2.855f, 0.111f, 0.8681f, 0.001728f}, {1.104f, 0.1389f, 3.774f, 0.1662f, 0.7911f, 0.03378f},
+     {1.793f, 0.1908f, 3.921f, 0.2483f, 0.7217f, 0.1146f}},
     {{}, {10.78f, 1.33f, 1.034f, 0.001557f, 1.0f, 1.105f}, {2.17f, 0.5597f, 3.94f, 1.029f, 0.8401f, 0.4839f}, {9.283f, 1.259f, 1.786f, 0.003477f, 1.0f, 0.9902f},
      {0.5175f, 0.07548f, 3.21f, 0.02426f, 0.8443f, 0.0f}, {1.042f, 0.09851f, 2.85f, 0.009332f, 0.8344f, 0.0f}, {1.026f, 0.1439f, 3.9f, 0.1786f, 0.8164f, 0.04263f},
      {1.762f, 0.1987f, 4.39f, 0.2438f, 0.6367f, 0.09061f}},
